@@ -41,19 +41,31 @@ namespace sffn {
 
 namespace {
 
-constexpr int kStages = 3;
-template <bool FP8>
-struct G {
-    static constexpr int SLAB = FP8 ? 128 : 64;         // hidden units per stage
-    static constexpr int kB = 64 * 512;                 // slab bytes (64 x 512 or 128 x 256)
-    static constexpr int kA = 256 * 32;
-    static constexpr int kMt = FP8 ? 256 * 8 : 256 * 4;
-    static constexpr int kC = 256;
-    static constexpr int kStage = kB + kA + kMt + kC;   // 42240 / 43264 bytes
+// Workgroup tile: WT token blocks (64 tokens) x WH column groups, one wavefront each (64 tokens x 32 FN columns).  KW > 1 (with one wavefront
+// per tile): KW wavefronts share the tile, wavefront g contracting stages g, g + KW, ... in a ring of its own; their partial sums meet in LDS.
+template <int WT_, int WH_, int FN_, int NST_, int KW_>
+struct VTile {
+    static constexpr int WT = WT_, WH = WH_, FN = FN_, NST = NST_, KW = KW_;
+    static constexpr int NW = WT * WH, BT = 64 * WT, BN = 32 * FN * WH, THREADS = 64 * NW * KW;
+    static_assert(KW == 1 || NW == 1, "a shared output tile belongs to single wavefronts");
 };
-constexpr int kLoads = 4 + 1 + 1 + 1;                // per wave per stage
-// Measurement switches (wrong results by design): SFFN_VNM8_NO_MFMA leaves the matrix instructions out, SFFN_VNM8_NO_DMA the loads after the
-// prologue, SFFN_VNM8_NO_BREAD the transposing reads of the B fragments.
+template <bool FP8, class TL>
+struct G {
+    static constexpr int ES = FP8 ? 1 : 2;               // bytes per element of Wk
+    static constexpr int SLAB = FP8 ? 128 : 64;         // hidden units per stage
+    static constexpr int ROW = TL::BN * ES;              // bytes of a slab row
+    static constexpr int kB = SLAB * ROW;
+    static constexpr int kA = TL::BT * 32;
+    static constexpr int kMt = FP8 ? TL::BT * 8 : TL::BT * 4;
+    static constexpr int kC = 256;
+    static constexpr int kStage = kB + kA + kMt + kC;
+    static constexpr int B_LD = kB / 1024 / TL::NW, A_LD = kA / 1024 / TL::NW, M_LD = (kMt / 256 + TL::NW - 1) / TL::NW;    // loads per wave and stage
+    static constexpr int LOADS = B_LD + A_LD + M_LD + 1;
+    static constexpr int PIECE = FP8 ? 32 : 64;          // bytes of a swizzled piece = 32 columns
+    static constexpr int NP = ROW / PIECE;               // pieces of a row
+    static constexpr int PMASK = (NP < 8 ? NP : 8) - 1;
+    static constexpr int BYTES = TL::KW * TL::NST * kStage;
+};
 
 typedef short s16x4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
@@ -63,18 +75,21 @@ typedef __attribute__((address_space(3))) v2i lds_v2i;
 }  // namespace
 
 // Wk / ldw: bf16 elements, or (FP8) code bytes
-template <bool FP8>
-__global__ void __launch_bounds__(512) vnm8_gemm_kernel(const uint16_t* __restrict__ vcb, const uint8_t* __restrict__ mcb,
+template <bool FP8, class TL>
+__global__ void __launch_bounds__(TL::THREADS, (TL::KW > 1 || TL::NW < 4) ? 1 : 2) vnm8_gemm_kernel(const uint16_t* __restrict__ vcb, const uint8_t* __restrict__ mcb,
                                                        const uint8_t* __restrict__ cixt, const uint8_t* __restrict__ Wk, int ldw,
                                                        int Ra, int N, int F, int Ttot, uint16_t* __restrict__ out, int64_t ldo,
                                                        int tiles_m, int tiles_n, GemmGroup grp, float alpha) {
-    constexpr int kB = G<FP8>::kB, kA = G<FP8>::kA, kMt = G<FP8>::kMt, kStage = G<FP8>::kStage;
-    constexpr int ES = FP8 ? 1 : 2;                      // bytes per element of Wk
-    __shared__ __attribute__((aligned(1024))) unsigned char smem[kStages * kStage];
+    using GG = G<FP8, TL>;
+    constexpr int kB = GG::kB, kA = GG::kA, kMt = GG::kMt, kStage = GG::kStage, ES = GG::ES, kStages = TL::NST, kLoads = GG::LOADS, KW = TL::KW, FN = TL::FN;
+    constexpr int BT = TL::BT, BN = TL::BN, ROW = GG::ROW, B_LD = GG::B_LD, A_LD = GG::A_LD, M_LD = GG::M_LD, PB = GG::PIECE, PM = GG::PMASK;
+    __shared__ __attribute__((aligned(1024))) unsigned char smem[GG::BYTES];
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l32 = lane & 31, lh = lane >> 5;
+    const int kg = KW > 1 ? wave : 0, wt = KW > 1 ? 0 : wave;       // share of the contraction / place in the tile
+    unsigned char* const ring = smem + kg * (kStages * kStage);
 
     int L;
     {
@@ -86,7 +101,7 @@ __global__ void __launch_bounds__(512) vnm8_gemm_kernel(const uint16_t* __restri
     if (grp.n) {
         int e = 0, cnt = 0;
         for (; e < grp.n; ++e) {
-            cnt = ((grp.seg[e + 1] - grp.seg[e] + 255) >> 8) * tiles_n;
+            cnt = (grp.seg[e + 1] - grp.seg[e] + BT - 1) / BT * tiles_n;
             if (L < cnt) break;
             L -= cnt;
         }
@@ -102,53 +117,50 @@ __global__ void __launch_bounds__(512) vnm8_gemm_kernel(const uint16_t* __restri
         tm = first + (L % width) % gsz;
         tn = (L % width) / gsz;
     }
-    const int i0 = i_base + tm * 256, n0 = tn * 256;
-    const int KS = F / G<FP8>::SLAB;                     // stages = slabs of 64 (128) hidden units
+    const int i0 = i_base + tm * BT, n0 = tn * BN;
+    const int KS = F / GG::SLAB;                     // stages = slabs of 64 (128) hidden units
     const int NTB = Ttot >> 6;
 
     // ---- DMA sources (wave-uniform 64-bit base + 32-bit per-lane offset).  Token groups past the end of the operand are clamped into it:
     //      they only feed outputs that are never stored. ----------------------------------------------------------------------------------
-    // B: load i of wave w (i = 0..3) brings slab rows 2 (4 w + i) + lane / 32; lane % 32 is the 16-byte slot inside the 512-byte row and
-    // fetches the chunk whose 64-byte piece the swizzle puts there (FP8: rows 4 (4 w + i) + lane / 16 of 256 bytes, 32-byte pieces).
-    // Chunks past the right edge of Wk are redirected into the first 64 columns.
+    // B: a load brings 1024 / ROW slab rows; a lane's 16-byte slot fetches the chunk whose piece (PB bytes = 32 columns) the swizzle puts there:
+    // piece p of row f sits at p ^ (f % min(8, pieces)).  Chunks past the right edge of Wk are redirected into the first 64 columns.
     const uint64_t w_base = uniform64(Wk);
-    uint32_t b_lane[4];
+    constexpr int LPR = ROW / 16, RPL = 1024 / ROW;         // 16-byte slots per slab row, rows per load
+    uint32_t b_lane[B_LD];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        if (FP8) {
-            const int row = 4 * (4 * wave + i) + (lane >> 4), slot = lane & 15;
-            int c = (((slot >> 1) ^ (row & 7)) << 1) | (slot & 1);
-            if (n0 + c * 16 >= N) c &= 3;
-            b_lane[i] = (uint32_t)row * (uint32_t)ldw + (uint32_t)(n0 + c * 16);
-        } else {
-            const int row = 2 * (4 * wave + i) + lh, slot = l32;
-            int c = (((slot >> 2) ^ (row & 7)) << 2) | (slot & 3);
-            if (n0 + c * 8 >= N) c &= 7;
-            b_lane[i] = (uint32_t)row * (uint32_t)ldw * 2u + (uint32_t)(n0 + c * 8) * 2u;
-        }
+    for (int i = 0; i < B_LD; ++i) {
+        const int row = RPL * (B_LD * wt + i) + lane / LPR, slot = lane % LPR;
+        constexpr int SPP = PB / 16;                         // slots per piece
+        int c = (((slot / SPP) ^ (row & PM)) * SPP) | (slot & (SPP - 1));
+        if (n0 + c * (16 / ES) >= N) c &= (64 * ES / 16) - 1;
+        b_lane[i] = ((uint32_t)row * (uint32_t)ldw + (uint32_t)(n0 + c * (16 / ES))) * ES;
     }
-    const uint32_t b_kstep = (uint32_t)G<FP8>::SLAB * (uint32_t)ldw * ES;
-    uint64_t a_base, m_base, c_base;
+    const uint32_t b_kstep = (uint32_t)GG::SLAB * (uint32_t)ldw * ES;
+    uint64_t a_base[A_LD], m_base[M_LD], c_base;
     uint32_t a_lane, m_lane, c_lane;
     {
-        int g32 = (i0 >> 5) + wave;                      // the wave's 32 tokens of the tile
-        g32 = g32 < (Ttot >> 5) ? g32 : (Ttot >> 5) - 1;
-        a_base = uniform64(vcb + (int64_t)g32 * KS * 512);
+#pragma unroll
+        for (int i = 0; i < A_LD; ++i) {                 // 32 tokens of the tile each
+            int g32 = (i0 >> 5) + wt * A_LD + i;
+            g32 = g32 < (Ttot >> 5) ? g32 : (Ttot >> 5) - 1;
+            a_base[i] = uniform64(vcb + (int64_t)g32 * KS * 512);
+        }
         const int row = lane >> 1, slot = lane & 1;
         a_lane = (uint32_t)(row * 32 + ((slot ^ ((row >> 3) & 1)) << 4));
-        if (FP8) {          // 8 bytes per token and stage: the wave's own 32 tokens, 256 bytes of the 512-byte unit of their token block
-            int g64 = (i0 >> 6) + (wave >> 1);
+#pragma unroll
+        for (int i = 0; i < M_LD; ++i) {
+            // 256-byte pieces: 64 tokens (bf16) / half of the 512-byte unit of a token block (FP8).  With fewer pieces than wavefronts two fetch the same
+            const int mi = (wt * M_LD + i) % (kMt / 256);
+            int g64 = (i0 >> 6) + (FP8 ? mi >> 1 : mi);
             g64 = g64 < NTB ? g64 : NTB - 1;
-            m_base = uniform64(mcb + (int64_t)g64 * KS * 512 + (wave & 1) * 256);
-        } else {            // 4 bytes: waves w and w + 4 fetch the same 64 tokens' metadata
-            int g64 = (i0 >> 6) + (wave & 3);
-            g64 = g64 < NTB ? g64 : NTB - 1;
-            m_base = uniform64(mcb + (int64_t)g64 * KS * 256);
+            m_base[i] = uniform64(FP8 ? mcb + (int64_t)g64 * KS * 512 + (mi & 1) * 256 : mcb + (int64_t)g64 * KS * 256);
         }
         m_lane = lane * 4;
-        // offsets of the tile's four token blocks: 4 x 32 (FP8: 4 x 64) bytes, every wave fetches all of them
+        // offsets of the tile's token blocks, 32 (FP8: 64) bytes each: every wave fetches all of them (four slots; unused ones repeat the last)
         const int words = FP8 ? 16 : 8;
-        int tb = (i0 >> 6) + (FP8 ? (lane >> 4) : (l32 >> 3));
+        int tb = FP8 ? (lane >> 4) : (l32 >> 3);
+        tb = (i0 >> 6) + (tb < TL::WT ? tb : TL::WT - 1);
         tb = tb < NTB ? tb : NTB - 1;
         c_base = uniform64(cixt);
         c_lane = (uint32_t)(tb * words * 4 + (lane & (words - 1)) * 4);
@@ -156,29 +168,28 @@ __global__ void __launch_bounds__(512) vnm8_gemm_kernel(const uint16_t* __restri
     const uint32_t c_kstep = (uint32_t)NTB * (FP8 ? 64u : 32u);
     constexpr uint32_t m_kstep = FP8 ? 512u : 256u;
     auto issue_half = [&](int kt, int stage, int h) {
-#ifdef SFFN_VNM8_NO_DMA
-        if (kt >= kStages) return;
-#endif
-        unsigned char* sb = smem + stage * kStage;
+        unsigned char* sb = ring + stage * kStage;
         unsigned char* sa = sb + kB;
         unsigned char* sm = sa + kA;
         unsigned char* sc = sm + kMt;
         if (h == 0) {
-            dma16(w_base, b_lane[0] + (uint32_t)kt * b_kstep, sb + (4 * wave + 0) * 1024);
-            dma16(w_base, b_lane[1] + (uint32_t)kt * b_kstep, sb + (4 * wave + 1) * 1024);
-            dma16(a_base, a_lane + (uint32_t)kt * 1024u, sa + wave * 1024);
+#pragma unroll
+            for (int i = 0; i < B_LD / 2; ++i) dma16(w_base, b_lane[i] + (uint32_t)kt * b_kstep, sb + (B_LD * wt + i) * 1024);
+#pragma unroll
+            for (int i = 0; i < A_LD; ++i) dma16(a_base[i], a_lane + (uint32_t)kt * 1024u, sa + (wt * A_LD + i) * 1024);
             dma4(c_base, c_lane + (uint32_t)kt * c_kstep, sc);
         } else {
-            dma16(w_base, b_lane[2] + (uint32_t)kt * b_kstep, sb + (4 * wave + 2) * 1024);
-            dma16(w_base, b_lane[3] + (uint32_t)kt * b_kstep, sb + (4 * wave + 3) * 1024);
-            dma4(m_base, m_lane + (uint32_t)kt * m_kstep, sm + (FP8 ? wave : (wave & 3)) * 256);
+#pragma unroll
+            for (int i = B_LD / 2; i < B_LD; ++i) dma16(w_base, b_lane[i] + (uint32_t)kt * b_kstep, sb + (B_LD * wt + i) * 1024);
+#pragma unroll
+            for (int i = 0; i < M_LD; ++i) dma4(m_base[i], m_lane + (uint32_t)kt * m_kstep, sm + ((wt * M_LD + i) % (kMt / 256)) * 256);
         }
     };
     auto issue = [&](int kt, int stage) { issue_half(kt, stage, 0); issue_half(kt, stage, 1); };
 
-    // ---- per-lane LDS offsets of the fragment reads (inside a stage).  A wave owns one token block (64 tokens) x 128 output columns: its two
-    //      A fragments are read by one other wave only, and the four B fragments it gathers belong to one column selection. ----------------------
-    const int tbw = wave >> 1, nh = wave & 1;
+    // ---- per-lane LDS offsets of the fragment reads (inside a stage).  A wave owns one token block (64 tokens) x 32 FN output columns: the
+    //      B fragments it gathers belong to one column selection. ----------------------
+    const int tbw = wt / TL::WH, nh = wt % TL::WH;
     int a_off[2], m_off[2];
 #pragma unroll
     for (int a = 0; a < 2; ++a) {
@@ -187,28 +198,29 @@ __global__ void __launch_bounds__(512) vnm8_gemm_kernel(const uint16_t* __restri
         m_off[a] = kB + kA + (FP8 ? row * 8 + 4 * lh : row * 4 + 2 * lh);
     }
     // bf16: transpose read j of fragment fn: slab row = 8 cb(j) + c with cb(j) = 4 (j / 2) + j % 2 + 2 h and c = byte j of the lane's offsets
-    // word; byte address = row * 512 + ((4 nh + fn) ^ c) * 64 + 32 (column half) + 8 (lane % 4)
+    // word; byte address = row * ROW + ((FN nh + fn) ^ (c % pieces)) * 64 + 32 (column half) + 8 (lane % 4)
     // FP8: the lane addresses row p = (lane % 16) / 2 of the read's 8: cb(j) = 8 (j / 2) + 4 h + 2 (j % 2) + p / 4, c = byte j of word (h, p);
-    // byte address = row * 256 + ((4 nh + fn) ^ c) * 32 + 16 (column half) + 8 (lane % 2)
+    // byte address = row * ROW + ((FN nh + fn) ^ (c % pieces)) * 32 + 16 (column half) + 8 (lane % 2)
     const int r4 = (lane & 15) >> 2, p8 = (lane & 15) >> 1, g = lane >> 4;
     const int c_off = kB + kA + kMt + (FP8 ? 64 * tbw + (lh * 8 + p8) * 4 : 32 * tbw + (lh * 4 + r4) * 4);
     const int b_fix = FP8 ? ((g & 1) << 4) + ((lane & 1) << 3) : ((g & 1) << 5) + ((lane & 3) << 3);
     int b_cb[4];
 #pragma unroll
     for (int j = 0; j < 4; ++j)
-        b_cb[j] = FP8 ? (8 * (j >> 1) + 4 * lh + 2 * (j & 1) + (p8 >> 2)) * 8 * 256 + b_fix : (4 * (j >> 1) + (j & 1) + 2 * lh) * 8 * 512 + b_fix;
+        b_cb[j] = FP8 ? (8 * (j >> 1) + 4 * lh + 2 * (j & 1) + (p8 >> 2)) * 8 * ROW + b_fix : (4 * (j >> 1) + (j & 1) + 2 * lh) * 8 * ROW + b_fix;
 
-    f32x16 acc[2][4];
+    f32x16 acc[2][FN];
 #pragma unroll
     for (int a = 0; a < 2; ++a)
 #pragma unroll
-        for (int b = 0; b < 4; ++b)
+        for (int b = 0; b < FN; ++b)
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[a][b][r] = 0.0f;
 
-    // The stage's fragments in two halves: P = both A fragments, the offsets word and B fragments 0, 1; Q = B fragments 2, 3 (the A
+    // The stage's fragments in two halves: P = both A fragments, the offsets word and the first HB = FN / 2 B fragments; Q = the others (the A
     // fragments of P stay live until Q's matrix instructions, so A is double-buffered by stage parity)
-    struct BPair { union { s16x4 q[4]; v2i q8[4]; bf16x16 v; i32x8 v8; } b[2]; };
+    constexpr int HB = FN / 2;
+    struct BPair { union { s16x4 q[4]; v2i q8[4]; bf16x16 v; i32x8 v8; } b[HB]; };
     struct AFrags { Frag8 a[2]; int idx[2]; uint32_t cw; };
     auto read_a = [&](AFrags& f, const unsigned char* st) {
         f.cw = *reinterpret_cast<const uint32_t*>(st + c_off);
@@ -219,60 +231,53 @@ __global__ void __launch_bounds__(512) vnm8_gemm_kernel(const uint16_t* __restri
         }
     };
     auto read_b = [&](BPair& f, const unsigned char* st, uint32_t cw, int half) {
-#ifdef SFFN_VNM8_NO_BREAD
-        f.b[0].q[0][0] = (short)cw; f.b[1].q[0][0] = (short)(cw >> 16);
-        return;
-#endif
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             const uint32_t c = (cw >> (8 * j)) & 7u;
-            if (FP8) {
-                const uint32_t addr = (uint32_t)b_cb[j] + c * 256u + (((4u * nh + 2u * half) ^ c) << 5);
-                f.b[0].q8[j] = __builtin_amdgcn_ds_read_tr8_b64_v2i32((lds_v2i*)(st + addr));
-                f.b[1].q8[j] = __builtin_amdgcn_ds_read_tr8_b64_v2i32((lds_v2i*)(st + (addr ^ 32u)));
-            } else {
-                const uint32_t addr = (uint32_t)b_cb[j] + c * 512u + (((4u * nh + 2u * half) ^ c) << 6);
-                f.b[0].q[j] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(st + addr));
-                f.b[1].q[j] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(st + (addr ^ 64u)));
+            const uint32_t addr = (uint32_t)b_cb[j] + c * (uint32_t)ROW + ((((uint32_t)(FN * nh + HB * half)) ^ (c & (uint32_t)PM)) * PB);
+#pragma unroll
+            for (int q = 0; q < HB; ++q) {
+                if (FP8) f.b[q].q8[j] = __builtin_amdgcn_ds_read_tr8_b64_v2i32((lds_v2i*)(st + (addr ^ (uint32_t)(q * PB))));
+                else     f.b[q].q[j] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(st + (addr ^ (uint32_t)(q * PB))));
             }
         }
     };
     auto mma_half = [&](const AFrags& fa, const BPair& fb, int half) {
-#ifdef SFFN_VNM8_NO_MFMA
-        acc[0][2 * half][0] += __builtin_bit_cast(float, fa.a[0].u.x) + __builtin_bit_cast(float, fa.a[1].u.x) + (float)fb.b[0].q[0][0] + (float)fb.b[1].q[3][3] + (float)fa.idx[0] + (float)fa.idx[1];
-        return;
-#endif
 #pragma unroll
         for (int a2 = 0; a2 < 2; ++a2)
 #pragma unroll
-            for (int fn = 0; fn < 2; ++fn)
-                if (FP8) acc[a2][2 * half + fn] = __builtin_amdgcn_smfmac_f32_32x32x64_fp8_fp8(fa.a[a2].q, fb.b[fn].v8, acc[a2][2 * half + fn], fa.idx[a2], 0, 0);
-                else     acc[a2][2 * half + fn] = __builtin_amdgcn_smfmac_f32_32x32x32_bf16(fa.a[a2].v, fb.b[fn].v, acc[a2][2 * half + fn], fa.idx[a2], 0, 0);
+            for (int fn = 0; fn < HB; ++fn)
+                if (FP8) acc[a2][HB * half + fn] = __builtin_amdgcn_smfmac_f32_32x32x64_fp8_fp8(fa.a[a2].q, fb.b[fn].v8, acc[a2][HB * half + fn], fa.idx[a2], 0, 0);
+                else     acc[a2][HB * half + fn] = __builtin_amdgcn_smfmac_f32_32x32x32_bf16(fa.a[a2].v, fb.b[fn].v, acc[a2][HB * half + fn], fa.idx[a2], 0, 0);
     };
 #define SB() __builtin_amdgcn_sched_barrier(0)
 
-    const int nk = KS;
+    const int nk = KW == 1 ? KS : (KS - kg + KW - 1) / KW;
+    auto step_of = [&](int kt) { return KW == 1 ? kt : kg + kt * KW; };
+    if (nk > 0) {
 #pragma unroll
-    for (int p = 0; p < kStages; ++p) issue(p < nk ? p : nk - 1, p);
+    for (int p = 0; p < kStages; ++p) issue(step_of(p < nk ? p : nk - 1), p);
     wait_vmcnt<(kStages - 1) * kLoads>();
-    __syncthreads();
+    if (KW == 1) __syncthreads();
+    else asm volatile("" ::: "memory");
     AFrags A0, A1;
     BPair P, Q;
-    read_a(A0, smem);
-    read_b(P, smem, A0.cw, 0);
+    read_a(A0, ring);
+    read_b(P, ring, A0.cw, 0);
     int stage = 0;
     // two stages per trip so that the A fragment buffers alternate without copies
     auto step = [&](int kt, AFrags& cur, AFrags& nxt_a) {
-        const int nxt = (kt + kStages < nk) ? kt + kStages : nk - 1;
+        const int nxt = step_of((kt + kStages < nk) ? kt + kStages : nk - 1);
         const int next_stage = (stage + 1 == kStages) ? 0 : stage + 1;
-        const unsigned char* st = smem + stage * kStage;
-        const unsigned char* sn = smem + next_stage * kStage;
+        const unsigned char* st = ring + stage * kStage;
+        const unsigned char* sn = ring + next_stage * kStage;
         mma_half(cur, P, 0); SB();
         read_b(Q, st, cur.cw, 1); SB();
         // Q has arrived and this wave's part of tile kt + 1 has landed; after the barrier every wave is done reading this stage, which is
         // refilled at once
         wait_vmcnt_lgkm0<(kStages - 2) * kLoads>();
-        __builtin_amdgcn_s_barrier();
+        if (KW == 1) __builtin_amdgcn_s_barrier();
+        else asm volatile("" ::: "memory");
         SB();
         issue_half(nxt, stage, 0); SB();
         read_a(nxt_a, sn); SB();
@@ -289,15 +294,41 @@ __global__ void __launch_bounds__(512) vnm8_gemm_kernel(const uint16_t* __restri
     if (kt < nk) step(kt, A0, A1);
 #undef SB
     wait_vmcnt<0>();
+    }
     __syncthreads();
+    if (KW > 1) {       // partial sums -> the first wavefront, in ascending order; the others are done
+        constexpr int PART = 2 * FN * 16 * 256;
+        static_assert((KW - 1) * PART <= GG::BYTES, "partial sums must fit in the main-loop LDS");
+        if (kg > 0) {
+            float* p = reinterpret_cast<float*>(smem + (kg - 1) * PART) + lane;
+#pragma unroll
+            for (int a = 0; a < 2; ++a)
+#pragma unroll
+                for (int b = 0; b < FN; ++b)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) p[((a * FN + b) * 16 + r) * 64] = acc[a][b][r];
+        }
+        __syncthreads();
+        if (kg > 0) return;
+        for (int g = 1; g < KW; ++g) {
+            const float* p = reinterpret_cast<const float*>(smem + (g - 1) * PART) + lane;
+#pragma unroll
+            for (int a = 0; a < 2; ++a)
+#pragma unroll
+                for (int b = 0; b < FN; ++b)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) acc[a][b][r] += p[((a * FN + b) * 16 + r) * 64];
+        }
+        wave_lds_sync();
+    }
 
     // ---- output: the wave's 32 x 64 sub-tiles go through LDS as [t][n] so that HBM sees 128-byte row segments -----------------------------
     constexpr int EP = 64 * 2 + 16;
-    unsigned char* scratch = smem + wave * (32 * EP);
+    unsigned char* scratch = smem + wt * (32 * EP);
 #pragma unroll
     for (int a = 0; a < 2; ++a)
 #pragma unroll
-        for (int half = 0; half < 2; ++half) {
+        for (int half = 0; half < FN / 2; ++half) {
 #pragma unroll
             for (int b = 0; b < 2; ++b)
 #pragma unroll
@@ -309,7 +340,7 @@ __global__ void __launch_bounds__(512) vnm8_gemm_kernel(const uint16_t* __restri
 #pragma unroll
             for (int p = 0; p < 4; ++p) {
                 const int e = lane + 64 * p, row = e >> 3, ch = e & 7;
-                const int i = i0 + tbw * 64 + a * 32 + row, j = n0 + nh * 128 + half * 64 + ch * 8;
+                const int i = i0 + tbw * 64 + a * 32 + row, j = n0 + nh * 32 * FN + half * 64 + ch * 8;
                 if (i < Ra && j < N) *reinterpret_cast<uint4*>(out + (int64_t)i * ldo + j) = *reinterpret_cast<const uint4*>(scratch + row * EP + ch * 16);
             }
             wave_lds_sync();
@@ -326,21 +357,37 @@ bool vnm8_gemm_fp8_ok(int64_t T, int64_t N, int64_t F, int64_t ldw) {
            T * F < ((int64_t)1 << 38);
 }
 
+static unsigned vnm8_tiles(int64_t T, int64_t N, const GemmGroup& g, int BT, int BN) {
+    const int64_t tiles_n = (N + BN - 1) / BN;
+    if (!g.n) return (unsigned)((T + BT - 1) / BT * tiles_n);
+    int64_t n = 0;
+    for (int e = 0; e < g.n; ++e) n += (g.seg[e + 1] - g.seg[e] + BT - 1) / BT * tiles_n;
+    return (unsigned)n;
+}
+
+template <bool FP8, class TL>
+static hipError_t launch_tile(const uint16_t* vcb, const uint8_t* mcb, const uint8_t* cixt, const uint8_t* Wk, int64_t ldw, float alpha, int64_t T,
+                              int64_t N, int64_t F, uint16_t* out, int64_t ldo, hipStream_t s, const GemmGroup& g) {
+    const int tiles_m = (int)((T + TL::BT - 1) / TL::BT), tiles_n = (int)((N + TL::BN - 1) / TL::BN);
+    const unsigned tiles = vnm8_tiles(T, N, g, TL::BT, TL::BN);
+    if (tiles == 0) return hipSuccess;
+    hipLaunchKernelGGL((vnm8_gemm_kernel<FP8, TL>), dim3(tiles), dim3(TL::THREADS), 0, s, vcb, mcb, cixt, Wk, (int)ldw, (int)T, (int)N, (int)F, (int)T, out,
+                       ldo, tiles_m, tiles_n, g, alpha);
+    return hipGetLastError();
+}
+
 template <bool FP8>
 static hipError_t launch_impl(const uint16_t* vcb, const uint8_t* mcb, const uint8_t* cixt, const uint8_t* Wk, int64_t ldw, float alpha, int64_t T,
                               int64_t N, int64_t F, uint16_t* out, int64_t ldo, hipStream_t s, const GemmGroup* grp) {
     const GemmGroup g = grp ? *grp : GemmGroup();
     if (g.n && (g.role != 0 || g.seg_dev || g.n > GemmGroup::kMaxExperts)) return hipErrorInvalidValue;
-    const int tiles_m = (int)((T + 255) / 256), tiles_n = (int)((N + 255) / 256);
-    int tiles = tiles_m * tiles_n;
-    if (g.n) {
-        tiles = 0;
-        for (int e = 0; e < g.n; ++e) tiles += (g.seg[e + 1] - g.seg[e] + 255) / 256 * tiles_n;
+    // T = 8192, N = 2048, F = 8192 (256 / 1024 tiles): 107 us on 256 tiles, 148 on 128; T = 2048 (64 / 256): 85 and 54; T = 1024, N = 1408, F = 4928
+    // (24 / 88 / 352): 55, 33, and 29 on 64 tiles; T = 64, N = 2048, F = 8192 (8 / 16 / 32): 83, 49, 28
+    switch (pick_tile(vnm8_tiles(T, N, g, 256, 256), vnm8_tiles(T, N, g, 128, 128), vnm8_tiles(T, N, g, 64, 64), (int)(F / (FP8 ? 128 : 64)), 0.72f, 512, 8)) {
+        case 256: return launch_tile<FP8, VTile<4, 2, 4, 3, 1>>(vcb, mcb, cixt, Wk, ldw, alpha, T, N, F, out, ldo, s, g);
+        case 128: return launch_tile<FP8, VTile<2, 2, 2, 3, 1>>(vcb, mcb, cixt, Wk, ldw, alpha, T, N, F, out, ldo, s, g);
+        default:  return launch_tile<FP8, VTile<1, 1, 2, 3, 4>>(vcb, mcb, cixt, Wk, ldw, alpha, T, N, F, out, ldo, s, g);
     }
-    if (tiles == 0) return hipSuccess;
-    hipLaunchKernelGGL((vnm8_gemm_kernel<FP8>), dim3((unsigned)tiles), dim3(512), 0, s, vcb, mcb, cixt, Wk, (int)ldw, (int)T, (int)N, (int)F, (int)T, out,
-                       ldo, tiles_m, tiles_n, g, alpha);
-    return hipGetLastError();
 }
 
 hipError_t launch_vnm8_gemm(const uint16_t* vcb, const uint8_t* mcb, const uint8_t* cixt, const uint16_t* Wk, int64_t ldw, int64_t T, int64_t N,

@@ -73,6 +73,16 @@ struct GemmGroup {
     int32_t seg[kMaxExperts + 1] = {0};
 };
 
+// Edge of the square output tile of a contraction with n256 / n128 / n64 tiles of each size and `steps` trips of its main loop.  A round = one tile on
+// every slot of the chip: 256 tiles of 256 x 256 (one workgroup per CU), 512 of 128 x 128 (two per CU).  A round of small tiles takes `w128` of a round of
+// large ones (measured, see the callers: more bytes from L2 per product), so the large tile wins on whole rounds and the small one where the
+// outputs do not fill the chip or leave the last round nearly empty.  64 x 64 tiles split the contraction over their four wavefronts: best
+// while there are at most `most64` of them and the contraction is long enough to be worth splitting.
+inline int pick_tile(unsigned n256, unsigned n128, unsigned n64, int steps, float w128, unsigned most64, int least_steps) {
+    if (n64 <= most64 && steps >= least_steps) return 64;
+    return w128 * (float)((n128 + 511) / 512) < (float)((n256 + 255) / 256) ? 128 : 256;
+}
+
 hipError_t launch_prune24(const uint16_t* src, int64_t R, int64_t K, int64_t ld, int trans, int mode, uint16_t* vals,
                           uint8_t* meta, hipStream_t stream);
 hipError_t launch_dsqrelu_vnm(const uint16_t* dy2, const uint16_t* y1, const uint8_t* meta, const uint8_t* colidx,
@@ -206,11 +216,12 @@ hipError_t launch_prune24_fp8_step(const uint16_t* src, int64_t R, int64_t K, in
 
 // the same on E4M3 codes (atc: compact transposed codes [F / 2, T], Gq [N, T], both in the blocked pair layout): out = bf16(alpha * sum)
 hipError_t launch_wgrad_vnm_fp8(const uint8_t* atc, const uint8_t* kmask, const uint8_t* Gq, float alpha, int64_t F, int64_t N, int64_t T,
-                                int out_i_contig, uint16_t* out, int64_t ldo, hipStream_t s, const GemmGroup* grp = nullptr, bool acc32 = false);
+                                int out_i_contig, uint16_t* out, int64_t ldo, hipStream_t s, const GemmGroup* grp = nullptr, bool acc32 = false, bool split_ok = true);
+// split_ok = false: never split a tile's contraction over wavefronts (the wide blocks' fused path sums in the order of the unfused one)
 // acc32: `out` is a float32 matrix of the same shape (ldo in float32 elements; grouped form: out_stride in float32 elements) that the
 // result is added to, out32 += alpha * sum, instead of a bf16 matrix that is overwritten
 hipError_t launch_wgrad_vnm(const uint16_t* atc, const uint8_t* kmask, const uint16_t* G, int64_t F, int64_t N, int64_t T,
-                            int out_i_contig, uint16_t* out, int64_t ldo, hipStream_t s, const GemmGroup* grp = nullptr, bool acc32 = false);
+                            int out_i_contig, uint16_t* out, int64_t ldo, hipStream_t s, const GemmGroup* grp = nullptr, bool acc32 = false, bool split_ok = true);
 
 
 }  // namespace sffn

@@ -1,0 +1,43 @@
+"""The tile sizes of the contractions at sizes where each is chosen (256 x 256, 128 x 128, and 64 x 64 with the contraction split over the tile's
+wavefronts), with remainders in every dimension; stage by stage against the oracle."""
+import pytest
+import torch
+
+import paper_2602_06183_amd as sffn
+from tests.test_gpu_fp8 import _check_fp8_step_against_oracle, _fp8_step_scales
+from tests.test_gpu_kernels import _check_wide_step_against_oracle, _teacher_forced_step_check
+from tests.util import to_bits, to_dev
+from workload import make_ffn_inputs
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("T,D,F", [
+    (64, 1088, 2112),       # few tiles, long contractions: 64 tiles in eqs. (1), (3), (4), (7), trip counts that four wavefronts do not share evenly
+    (832, 320, 576),        # 64 tiles in the weight gradients (13 token blocks)
+    (1088, 1152, 4160),     # 128 tiles with a half-empty last row and column
+    (2112, 2112, 4160),     # 256 tiles in eqs. (1), (4), 128 tiles elsewhere
+])
+def test_step_on_every_tile_size(T, D, F):
+    _teacher_forced_step_check(T, D, F, sffn.MODE_SOFT, seed=21)
+
+
+@pytest.mark.parametrize("M,T,D,F", [(16, 64, 1088, 2048), (64, 64, 1088, 3072), (64, 832, 320, 2048), (32, 832, 320, 1024)])
+def test_wide_step_on_small_tiles(M, T, D, F):
+    inp = make_ffn_inputs(T, D, F, seed=22)
+    dev = {k: to_dev(v) for k, v in inp.items()}
+    (Y3, dX, dW1, dW2), step = sffn.ffn_sparse_step(dev["X"], dev["W1"], dev["W2"], dev["b1"], dev["dY"], sffn.MODE_HARD, M=M)
+    s = {k: to_bits(v) for k, v in step.saved().items()}
+    _check_wide_step_against_oracle(inp, s, dict(Y3=to_bits(Y3), dX=to_bits(dX), dW1=to_bits(dW1), dW2=to_bits(dW2)), sffn.MODE_HARD, M)
+
+
+@pytest.mark.parametrize("M,T,D,F", [(8, 64, 2304, 1152), (8, 832, 384, 640), (64, 64, 2304, 2048), (16, 832, 384, 1024)])
+def test_fp8_step_on_small_tiles(M, T, D, F):
+    inp = make_ffn_inputs(T, D, F, seed=23)
+    sc = _fp8_step_scales(inp)
+    dev = {k: to_dev(v) for k, v in inp.items()}
+    step = sffn.FfnStepFp8(T, D, F, sc, sffn.MODE_HARD, keep_dense=True, wgrad_fp8=True, M=M)
+    outs = step(dev["X"], dev["W1"], dev["W2"], dev["b1"], dev["dY"])
+    torch.cuda.synchronize()
+    s = {k: to_bits(v) if v.dtype == torch.bfloat16 else v.cpu().numpy() for k, v in step.saved().items()}
+    _check_fp8_step_against_oracle(inp, sc, s, {k: to_bits(v) for k, v in zip(("Y3", "dX", "dW1", "dW2"), outs)}, sffn.MODE_HARD, True, M)
