@@ -48,7 +48,7 @@ int g_prof_n = 0;
 struct FullLayout {
     sffn_ws_layout pub;
     // internal operands of the GEMMs, all in the blocked layout
-    size_t w1_vblk, w1_mblk, w2t_vblk, w2t_mblk, x_blk, xt_blk, dy_blk, dyt_blk, w2_blk, w1t_blk, a24_vblk, a24_mblk, at_blk, kmask, total;
+    size_t w1_vblk, w1_mblk, w2t_vblk, w2t_mblk, x_blk, xt_blk, dy_blk, dyt_blk, w2_blk, w1t_blk, a24_vblk, a24_mblk, at_blk, kmask, at2, total;
     size_t scratch_end, saved_end;      // region boundaries: scratch = [0, scratch_end), saved = [scratch_end, saved_end), weights = [saved_end, total)
 };
 
@@ -87,7 +87,7 @@ bool fused_wide(const sffn_cfg* c) {
 }
 
 // E = number of experts (1 for the plain step): every weight-shaped tensor holds E matrices back to back.
-bool make_layout(const sffn_cfg* c, FullLayout* L, int n_experts = 1) {
+bool make_layout(const sffn_cfg* c, FullLayout* L, int n_experts = 1, StepTiles* tiles = nullptr) {
     if (!c || !mult64(c->T) || !mult64(c->D) || !mult64(c->F) || n_experts < 1) return false;
     if (!vnm_ok(c->V, c->M)) return false;
     const size_t M = (size_t)c->M;                                    // wider blocks: smaller packed tensors, unfused path
@@ -109,6 +109,10 @@ bool make_layout(const sffn_cfg* c, FullLayout* L, int n_experts = 1) {
     L->dy_blk = take(T * D * 2);           L->dyt_blk = take(D * T * 2);
     L->a24_vblk = take(TF);             // M = 8: the survivors in the V:2:8 kernel's units; unfused path: the plain-2:4 view
     L->w1t_blk = take(fused ? 0 : D * F * 2);      // unfused path only: W2.T or W1.T, row-major
+    StepTiles t = step_tiles(c->T, c->D, c->F, c->M, n_experts, false);
+    t.mix = t.mix && fused;
+    L->at2 = take(t.mix ? TF : 0);      // dy1v.T compacted, where eq. (4) runs beside eq. (5) (StepTiles)
+    if (tiles) *tiles = t;
     L->scratch_end = off;
     // ---- saved -------------------------------------------------------------------------------------------------------------------------
     L->pub.y2_meta = take(TF / (2 * M));   L->pub.colidx = take(TF / 64 / M * 4);
@@ -138,6 +142,13 @@ int sffn_version(void) { return 110; }
 const char* sffn_last_error(void) { return g_err; }
 // internal (not declared in the public header): lets the library's other source files leave a text behind sffn_last_error()
 int sffn_noalloc_set_error(int code, const char* text) { return fail(code, "%s", text); }
+
+// internal (noalloc.hip): the part of sffn_workspace_bytes() that only serves shared launches (StepTiles)
+size_t sffn_step_shared_launch_bytes(const sffn_cfg* cfg) {
+    FullLayout L;
+    StepTiles t;
+    return make_layout(cfg, &L, 1, &t) && t.mix ? up256((size_t)cfg->T * cfg->F) : 0;
+}
 
 size_t sffn_workspace_bytes(const sffn_cfg* cfg) {
     FullLayout L;
@@ -1022,6 +1033,15 @@ int ffn_router_full_backward(const sffn_cfg* cfg, const uint16_t* dY, uint16_t* 
     return run_router_full(cfg, nullptr, nullptr, nullptr, nullptr, nullptr, dY, nullptr, dX, dW1, dW2, workspace, ws_bytes, stream, 2);
 }
 
+// The step's preparing passes: all in one launch while X, dY, W1 and W2 together stay below 96 MiB, else in three parts (X and W1 | W2 | dY)
+static inline bool prologue_together(int64_t T, int64_t D, int64_t F, int64_t E) { return 2 * (2 * T * D + 2 * E * F * D) < ((int64_t)96 << 20); }
+static inline void split_prologue(const PrologueArgs& all, PrologueArgs (&part)[3]) {
+    part[0] = part[1] = part[2] = all;
+    part[0].W2 = nullptr; part[0].dY = nullptr;
+    part[1].X = nullptr; part[1].W1 = nullptr; part[1].dY = nullptr;
+    part[2].X = nullptr; part[2].W1 = nullptr; part[2].W2 = nullptr;
+}
+
 // Alg. 1 + Alg. 2 for n_experts independent FFNs over consecutive token segments (n_experts = 1, seg = nullptr:
 // the plain step).  Every stage is one launch; the GEMMs find their expert from the segment table.
 static int run_step(const sffn_cfg* cfg, int n_experts, const int64_t* seg, const uint16_t* X, const uint16_t* W1,
@@ -1033,7 +1053,8 @@ static int run_step(const sffn_cfg* cfg, int n_experts, const int64_t* seg, cons
     FullLayout L;
     REQUIRE(n_experts >= 1 && n_experts <= GemmGroup::kMaxExperts, SFFN_EINVAL, "ffn_sparse_step_grouped: n_experts must be in 1..64");
     REQUIRE(vnm_ok(cfg->V, cfg->M), SFFN_EUNSUPPORTED, "ffn_sparse_step: only V=64 with M in {8, 16, 32, 64} is built");
-    REQUIRE(make_layout(cfg, &L, n_experts), SFFN_EINVAL, "ffn_sparse_step: T, D, F must be positive multiples of 64 and F a multiple of 2 M");
+    StepTiles tiles;
+    REQUIRE(make_layout(cfg, &L, n_experts, &tiles), SFFN_EINVAL, "ffn_sparse_step: T, D, F must be positive multiples of 64 and F a multiple of 2 M");
     REQUIRE(cfg->M == 8 || fused_wide(cfg) || (seg == nullptr && n_experts == 1), SFFN_EUNSUPPORTED,
             "ffn_sparse_step_grouped: blocks of 16 / 32 / 64 columns need 4 F / M to be a multiple of 64 and at most 7168 (and no SFFN_FLAG_UNFUSED)");
     REQUIRE(cfg->mode == SFFN_MODE_HARD || cfg->mode == SFFN_MODE_SOFT, SFFN_EINVAL, "ffn_sparse_step: unknown mode");
@@ -1076,6 +1097,7 @@ static int run_step(const sffn_cfg* cfg, int n_experts, const int64_t* seg, cons
     uint16_t* w2b = (uint16_t*)(rg.at(L.w2_blk));         uint16_t* w1tb = (uint16_t*)(rg.at(L.w1t_blk));
     uint16_t* a24v = (uint16_t*)(rg.at(L.a24_vblk));      uint8_t* a24m = rg.at(L.a24_mblk);
     uint16_t* atb = (uint16_t*)(rg.at(L.at_blk));
+    uint16_t* at2 = tiles.mix ? (uint16_t*)(rg.at(L.at2)) : atb;      // eq. (4)'s transposed survivors: in the place of eq. (1)'s, or beside them
     uint8_t* kmask = rg.at(L.kmask);
     uint16_t* ykept = (uint16_t*)(rg.at(L.pub.y1_kept));
     const int keep_dense = (cfg->flags & SFFN_FLAG_KEEP_DENSE) ? 1 : 0;
@@ -1103,24 +1125,51 @@ static int run_step(const sffn_cfg* cfg, int n_experts, const int64_t* seg, cons
         uint16_t* w2t = w2b;                             // W2.T [F, D] per expert
         if (g_prof_on) { g_prof_n = 0; (void)hipEventRecord(g_prof_ev[0], s); }
         const bool lean_w = (cfg->flags & SFFN_FLAG_LEAN) != 0;        // no canonical copies of the packed weights (the packed activations stay: eqs. (3), (7) read them)
-        if (fwd) STAGE(launch_transpose(X, T, D, D, xtb, 1, xb, s), "step/X.T");
-        if (fwd && !packed) STAGE(launch_prune24_step(W1, E * F, D, D, 0, cfg->mode, lean_w ? nullptr : w1v, lean_w ? nullptr : w1m, w1vb, w1mb, nullptr, s), "step/prune24(W1)");
+        PrologueArgs pro = {};
+        pro.T = (int)T; pro.D = (int)D; pro.F = (int)F; pro.experts = (int)E; pro.mode = cfg->mode;
+        if (fwd) { pro.X = X; pro.xt = xtb; pro.xb = xb; }
+        if (bwd) { pro.dY = dY; pro.dyt = dytb; pro.dyb = dyb; }
+        if (fwd && !packed) {
+            pro.W1 = W1; pro.w1v = lean_w ? nullptr : w1v; pro.w1m = lean_w ? nullptr : w1m; pro.w1vb = w1vb; pro.w1mb = w1mb;
+            pro.W2 = W2; pro.w2v = lean_w ? nullptr : w2v; pro.w2m = lean_w ? nullptr : w2m; pro.w2vb = w2vb; pro.w2mb = w2mb; pro.w2t = w2t;
+        }
+        // Small inputs: one launch.  Larger ones (half of the last-level cache and more): each pass right before the contraction that reads its
+        // results, while they are still cached (T = D = 8192, F = 28672: eq. (1) is 1-2 % slower when all passes come first).
+        const bool together = tiles.mix || prologue_together(T, D, F, E);
+        PrologueArgs part[3];
+        split_prologue(pro, part);
+        if (together) STAGE(launch_step_prologue(pro, s), "step/prologue");
+        else if (fwd) STAGE(launch_step_prologue(part[0], s), "step/X.T+prune24(W1)");
         if (fwd) {
             VnmEpilogue ep;
             ep.mode = 5; ep.logM = logM; ep.store_dense = keep_dense; ep.vals = y2v; ep.meta = y2m; ep.colidx = cix; ep.kmask = kmask; ep.ykept = ykept; ep.at = atb;
-            STAGE(launch_gemm_vnm_epilogue(w1vb, w1mb, xb, b1, F, T, D, y1, ep, s, gp), "step/y1+sqrelu_vnm_compress");         // eqs. (1), (2), Section 2.3
+            STAGE(launch_gemm_vnm_epilogue(w1vb, w1mb, xb, b1, F, T, D, y1, ep, s, gp, tiles.g), "step/y1+sqrelu_vnm_compress");         // eqs. (1), (2), Section 2.3
         }
-        if (fwd && !packed) STAGE(launch_prune24_step(W2, F, D, F, 1, cfg->mode, lean_w ? nullptr : w2v, lean_w ? nullptr : w2m, w2vb, w2mb, nullptr, s, (int)E, 0, w2t), "step/prune24(W2.T)");
+        VnmEpilogue ep4;
+        ep4.mode = 6; ep4.logM = logM; ep4.store_dense = keep_dense; ep4.vals = dy1v; ep4.meta = y2m; ep4.colidx = cix; ep4.ykept = ykept; ep4.at = at2;
+        if (tiles.mix) {
+            const GemmGroup none;
+            const int Kc = (int)(4 * F / M);
+            const GatherArgs v3 = {y2v, y2m, cix, w2t, (int)D, (int)T, (int)D, Kc, logM, 0, 1.0f, Y3, D, gr ? *gr : none};
+            const GatherArgs v7 = {dy1v, y2m, cix, W1, (int)D, (int)T, (int)D, Kc, logM, 0, 1.0f, dX, D, gr ? *gr : none};
+            const GemmV2Args g4 = {w2vb, w2mb, dyb, nullptr, (int)F, (int)T, (int)D, dy2, F, 0, 0, ep4, gp ? *gp : none, 1.0f};
+            const WgradArgs w5 = {atb, kmask, dytb, 1.0f, (int)F, (int)D, (int)T, dW2, F, 0, 0, gw ? *gw : none};
+            const WgradArgs w8 = {at2, kmask, xtb, 1.0f, (int)F, (int)D, (int)T, dW1, D, 0, 0, gw ? *gw : none};
+            if (fwd && bwd && !acc32) STAGE(launch_step_mix_bf16(kMixForwardTail, logM, tiles, false, nullptr, &v3, &g4, w5, s), "step/y3+dW2+dy2");
+            else {
+                if (fwd) STAGE(launch_vnm_spmm_gather(y2v, y2m, cix, w2t, D, T, D, F, M, Y3, D, s, gr), "step/y3");
+                if (bwd) STAGE(launch_step_mix_bf16(kMixBackwardHead, logM, tiles, acc32, nullptr, nullptr, &g4, w5, s), "step/dW2+dy2");
+            }
+            if (bwd) STAGE(launch_step_mix_bf16(kMixBackwardTail, logM, tiles, acc32, nullptr, &v7, nullptr, w8, s), "step/dX+dW1");
+            return SFFN_OK;
+        }
+        if (fwd && !packed && !together) STAGE(launch_step_prologue(part[1], s), "step/prune24(W2.T)");
         if (fwd) STAGE(launch_vnm_spmm_gather(y2v, y2m, cix, w2t, D, T, D, F, M, Y3, D, s, gr), "step/y3");                              // eq. (3)
-        if (bwd) STAGE(launch_transpose(dY, T, D, D, dytb, 1, dyb, s), "step/dY.T");
-        if (bwd) STAGE(launch_wgrad_vnm(atb, kmask, dytb, F, D, T, 1, dW2, F, s, gw, acc32, false), "step/dW2");                                       // eq. (5)
-        if (bwd) {
-            VnmEpilogue ep;
-            ep.mode = 6; ep.logM = logM; ep.store_dense = keep_dense; ep.vals = dy1v; ep.meta = y2m; ep.colidx = cix; ep.ykept = ykept; ep.at = atb;
-            STAGE(launch_gemm_vnm_epilogue(w2vb, w2mb, dyb, nullptr, F, T, D, dy2, ep, s, gp), "step/dy2+dsqrelu_vnm");         // eqs. (4), (6)
-        }
+        if (bwd && !together) STAGE(launch_step_prologue(part[2], s), "step/dY.T");
+        if (bwd) STAGE(launch_wgrad_vnm(atb, kmask, dytb, F, D, T, 1, dW2, F, s, gw, acc32, false, tiles.w), "step/dW2");                       // eq. (5)
+        if (bwd) STAGE(launch_gemm_vnm_epilogue(w2vb, w2mb, dyb, nullptr, F, T, D, dy2, ep4, s, gp, tiles.g_bwd), "step/dy2+dsqrelu_vnm");      // eqs. (4), (6)
         if (bwd) STAGE(launch_vnm_spmm_gather(dy1v, y2m, cix, W1, D, T, D, F, M, dX, D, s, gr), "step/dX");                              // eq. (7), dense W1 as is
-        if (bwd) STAGE(launch_wgrad_vnm(atb, kmask, xtb, F, D, T, 0, dW1, D, s, gw, acc32, false), "step/dW1");                                        // eq. (8)
+        if (bwd) STAGE(launch_wgrad_vnm(at2, kmask, xtb, F, D, T, 0, dW1, D, s, gw, acc32, false, tiles.w), "step/dW1");                        // eq. (8)
         return SFFN_OK;
     }
     if (cfg->M != 8) {
@@ -1192,28 +1241,55 @@ static int run_step(const sffn_cfg* cfg, int n_experts, const int64_t* seg, cons
     uint8_t* cixt = a24m + up256((size_t)T * F / 16);
     uint16_t* w2t = w2b;                                         // W2.T [F, D] per expert
     g_dense.b_stride = F * D;
-    if (fwd) STAGE(launch_transpose(X, T, D, D, xtb, 1, xb, s), "step/X.T");
-    // row pruning is per row, so the E stacked [F, D] matrices are one [E * F, D] matrix
-    if (fwd && !packed) STAGE(launch_prune24_step(W1, E * F, D, D, 0, cfg->mode, lean ? nullptr : w1v, lean ? nullptr : w1m, w1vb, w1mb, nullptr, s), "step/prune24(W1)");
+    uint16_t* vcb2 = tiles.mix ? a24v + T * F / 4 : vcb;          // eq. (4)'s survivors: in the place of eq. (1)'s, or (StepTiles) in the region's second half
+    PrologueArgs pro = {};
+    pro.T = (int)T; pro.D = (int)D; pro.F = (int)F; pro.experts = (int)E; pro.mode = cfg->mode;
+    if (fwd) { pro.X = X; pro.xt = xtb; pro.xb = xb; }
+    if (bwd) { pro.dY = dY; pro.dyt = dytb; pro.dyb = dyb; }
+    if (fwd && !packed) {
+        pro.W1 = W1; pro.w1v = lean ? nullptr : w1v; pro.w1m = lean ? nullptr : w1m; pro.w1vb = w1vb; pro.w1mb = w1mb;
+        pro.W2 = W2; pro.w2v = lean ? nullptr : w2v; pro.w2m = lean ? nullptr : w2m; pro.w2vb = w2vb; pro.w2mb = w2mb; pro.w2t = w2t;
+    }
+    // Small inputs: one launch.  Larger ones (half of the last-level cache and more): each pass right before the contraction that reads its
+    // results, while they are still cached (T = D = 8192, F = 28672: eq. (1) is 1-2 % slower when all passes come first).
+    const bool together = tiles.mix || prologue_together(T, D, F, E);
+    PrologueArgs part[3];
+    split_prologue(pro, part);
+    if (together) STAGE(launch_step_prologue(pro, s), "step/prologue");
+    else if (fwd) STAGE(launch_step_prologue(part[0], s), "step/X.T+prune24(W1)");
     if (fwd) {   // eq. (1), then eq. (2) + V:N:M compression on the tile while it is still in LDS
         VnmEpilogue ep;
         ep.mode = 1; ep.store_dense = keep_dense; ep.vals = lean ? nullptr : y2v; ep.meta = y2m; ep.colidx = cix; ep.kmask = kmask; ep.ykept = ykept;
         ep.vcb = vcb; ep.mcb = mcb; ep.cixt = cixt; ep.at = atb;
-        STAGE(launch_gemm_vnm_epilogue(w1vb, w1mb, xb, b1, F, T, D, y1, ep, s, gp), "step/y1+sqrelu_vnm_compress");
+        STAGE(launch_gemm_vnm_epilogue(w1vb, w1mb, xb, b1, F, T, D, y1, ep, s, gp, tiles.g), "step/y1+sqrelu_vnm_compress");
     }
-    if (fwd && !packed) STAGE(launch_prune24_step(W2, F, D, F, 1, cfg->mode, lean ? nullptr : w2v, lean ? nullptr : w2m, w2vb, w2mb, nullptr, s, (int)E, 0, w2t), "step/prune24(W2.T)");
-    if (fwd) STAGE(launch_vnm8_gemm(vcb, mcb, cixt, w2t, D, T, D, F, Y3, D, s, gd), "step/y3");                         // eq. (3)
+    // eq. (4), then eq. (6) on y2's kept slots
+    VnmEpilogue ep4;
+    ep4.mode = 2; ep4.store_dense = keep_dense; ep4.vals = lean ? nullptr : dy1v; ep4.meta = y2m; ep4.colidx = cix; ep4.ykept = ykept;
+    ep4.vcb = vcb2; ep4.at = at2;
+    if (tiles.mix) {
+        const GemmGroup none;
+        const Vnm8Args v3 = {vcb, mcb, cixt, (const uint8_t*)w2t, (int)D, (int)T, (int)D, (int)F, Y3, D, 0, 0, gd ? *gd : none, 1.0f};
+        const Vnm8Args v7 = {vcb2, mcb, cixt, (const uint8_t*)W1, (int)D, (int)T, (int)D, (int)F, dX, D, 0, 0, gd ? *gd : none, 1.0f};
+        const GemmV2Args g4 = {w2vb, w2mb, dyb, nullptr, (int)F, (int)T, (int)D, dy2, F, 0, 0, ep4, gp ? *gp : none, 1.0f};
+        const WgradArgs w5 = {atb, kmask, dytb, 1.0f, (int)F, (int)D, (int)T, dW2, F, 0, 0, gw ? *gw : none};
+        const WgradArgs w8 = {at2, kmask, xtb, 1.0f, (int)F, (int)D, (int)T, dW1, D, 0, 0, gw ? *gw : none};
+        if (fwd && bwd && !acc32) STAGE(launch_step_mix_bf16(kMixForwardTail, 3, tiles, false, &v3, nullptr, &g4, w5, s), "step/y3+dW2+dy2");
+        else {
+            if (fwd) STAGE(launch_vnm8_gemm(vcb, mcb, cixt, w2t, D, T, D, F, Y3, D, s, gd, tiles.v), "step/y3");
+            if (bwd) STAGE(launch_step_mix_bf16(kMixBackwardHead, 3, tiles, acc32, nullptr, nullptr, &g4, w5, s), "step/dW2+dy2");
+        }
+        if (bwd) STAGE(launch_step_mix_bf16(kMixBackwardTail, 3, tiles, acc32, &v7, nullptr, nullptr, w8, s), "step/dX+dW1");
+        return SFFN_OK;
+    }
+    if (fwd && !packed && !together) STAGE(launch_step_prologue(part[1], s), "step/prune24(W2.T)");
+    if (fwd) STAGE(launch_vnm8_gemm(vcb, mcb, cixt, w2t, D, T, D, F, Y3, D, s, gd, tiles.v), "step/y3");                // eq. (3)
+    if (bwd && !together) STAGE(launch_step_prologue(part[2], s), "step/dY.T");
     // ---- Alg. 2 -------------------------------------------------------------------------------
-    if (bwd) STAGE(launch_transpose(dY, T, D, D, dytb, 1, dyb, s), "step/dY.T");
-    if (bwd) STAGE(launch_wgrad_vnm(atb, kmask, dytb, F, D, T, 1, dW2, F, s, gw, acc32), "step/dW2");                          // eq. (5)
-    if (bwd) {   // eq. (4), then eq. (6) on y2's kept slots; overwrites the survivors and the transposed tile with dy1's
-        VnmEpilogue ep;
-        ep.mode = 2; ep.store_dense = keep_dense; ep.vals = lean ? nullptr : dy1v; ep.meta = y2m; ep.colidx = cix; ep.ykept = ykept;
-        ep.vcb = vcb; ep.at = atb;
-        STAGE(launch_gemm_vnm_epilogue(w2vb, w2mb, dyb, nullptr, F, T, D, dy2, ep, s, gp), "step/dy2+dsqrelu_vnm");
-    }
-    if (bwd) STAGE(launch_vnm8_gemm(vcb, mcb, cixt, W1, D, T, D, F, dX, D, s, gd), "step/dX");                          // eq. (7), dense W1 as is
-    if (bwd) STAGE(launch_wgrad_vnm(atb, kmask, xtb, F, D, T, 0, dW1, D, s, gw, acc32), "step/dW1");                           // eq. (8)
+    if (bwd) STAGE(launch_wgrad_vnm(atb, kmask, dytb, F, D, T, 1, dW2, F, s, gw, acc32, true, tiles.w), "step/dW2");           // eq. (5)
+    if (bwd) STAGE(launch_gemm_vnm_epilogue(w2vb, w2mb, dyb, nullptr, F, T, D, dy2, ep4, s, gp, tiles.g_bwd), "step/dy2+dsqrelu_vnm");
+    if (bwd) STAGE(launch_vnm8_gemm(vcb2, mcb, cixt, W1, D, T, D, F, dX, D, s, gd, tiles.v), "step/dX");                // eq. (7), dense W1 as is
+    if (bwd) STAGE(launch_wgrad_vnm(at2, kmask, xtb, F, D, T, 0, dW1, D, s, gw, acc32, true, tiles.w), "step/dW1");            // eq. (8)
     (void)w1tb;
     return SFFN_OK;
 }

@@ -8,15 +8,16 @@ hipError_t launch_spmm_blocked(const uint16_t* a_vals, const uint8_t* a_meta, co
                                int64_t K, int out_i_contig, uint16_t* out, int64_t ldo, hipStream_t s, const GemmGroup* grp) {
     const GemmGroup g = grp ? *grp : GemmGroup();
     if (out_i_contig || g.n > GemmGroup::kMaxExperts || (g.n && g.role == 2)) return hipErrorInvalidValue;
-    return launch_gemm_v2<true, false, 0, true, false>(a_vals, a_meta, B, bias, Ra, Rb, K, out, ldo, VnmEpilogue(), g, 1.0f, s);
+    return launch_gemm_v2<true, false, 0, true, false>({a_vals, a_meta, B, bias, (int)Ra, (int)Rb, (int)K, out, ldo, 0, 0, VnmEpilogue(), g, 1.0f}, s);
 }
 
 hipError_t launch_gemm_vnm_epilogue(const uint16_t* a_vals, const uint8_t* a_meta, const uint16_t* B, const float* bias, int64_t F,
-                                    int64_t T, int64_t K, uint16_t* out, const VnmEpilogue& ep, hipStream_t s, const GemmGroup* grp) {
+                                    int64_t T, int64_t K, uint16_t* out, const VnmEpilogue& ep, hipStream_t s, const GemmGroup* grp, int tile) {
     const GemmGroup g = grp ? *grp : GemmGroup();
     if (g.n && (g.n > GemmGroup::kMaxExperts || g.role != 1)) return hipErrorInvalidValue;
     if (ep.mode >= 5 && (ep.logM < 4 || ep.logM > 6)) return hipErrorInvalidValue;
-#define SFFN_EPI(E) launch_gemm_v2<true, true, E, true, false>(a_vals, a_meta, B, bias, F, T, K, out, F, ep, g, 1.0f, s)
+    const GemmV2Args a = {a_vals, a_meta, B, bias, (int)F, (int)T, (int)K, out, F, 0, 0, ep, g, 1.0f};
+#define SFFN_EPI(E) launch_gemm_v2<true, true, E, true, false>(a, s, tile)
     switch (ep.mode) {
         case 0: return SFFN_EPI(0);       // no V:N:M work: the dense output only
         case 1: return SFFN_EPI(1);

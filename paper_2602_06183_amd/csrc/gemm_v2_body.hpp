@@ -13,6 +13,7 @@
 #pragma once
 #include "common.hpp"
 #include "kernels.hpp"
+#include "launch_mix.hpp"
 #include "lds_dma.hpp"
 
 namespace sffn {
@@ -839,22 +840,6 @@ __device__ __forceinline__ void gemm_nt_v2_body(unsigned char* __restrict__ smem
     }
 }
 
-template <bool SPARSE, bool OUT_I_CONTIG, int EPI, bool BLOCKED, bool FP8, class TL>
-__global__ void __launch_bounds__(TL::THREADS, (TL::KW > 1 || TL::NW < 4) ? 1 : 2)
-    gemm_nt_v2_kernel(const uint16_t* __restrict__ a_vals, const uint8_t* __restrict__ a_meta, const uint16_t* __restrict__ B,
-                      const float* __restrict__ bias, int Ra, int Rb, int K, uint16_t* __restrict__ out, int64_t ldo, int tiles_m, int tiles_n,
-                      VnmEpilogue ep, GemmGroup grp, float alpha) {
-    __shared__ __attribute__((aligned(1024))) unsigned char smem[GemmV2Lds<SPARSE, OUT_I_CONTIG, EPI, BLOCKED, FP8, TL>::BYTES];
-    gemm_nt_v2_body<SPARSE, OUT_I_CONTIG, EPI, BLOCKED, FP8, TL>(smem, blockIdx.x, gridDim.x, a_vals, a_meta, B, bias, Ra, Rb, K, out, ldo, tiles_m, tiles_n,
-                                                                 ep, grp, alpha);
-}
-
-// the three tiles; blocks of M = 64 columns want 128 hidden units in one wavefront (two blocks share a metadata byte)
-template <bool SPARSE> using Tile256 = Tile<2, 4, 128, SPARSE ? 3 : 4, 1>;
-template <bool SPARSE, int EPI> struct TileSel { using T128 = Tile<2, 2, 64, SPARSE ? 3 : 4, 1>; using T64 = Tile<1, 1, 64, 3, 4>; };
-template <> struct TileSel<true, 22> { using T128 = Tile<1, 2, 128, 3, 1>; using T64 = Tile<1, 1, 128, 2, 4>; };
-template <> struct TileSel<true, 38> { using T128 = Tile<1, 2, 128, 3, 1>; using T64 = Tile<1, 1, 128, 2, 4>; };
-
 // Workgroups of a launch: one per BM x BN output tile; grouped: per expert, over its token segment.
 inline unsigned grid_tiles(int64_t Ra, int64_t Rb, const GemmGroup& g, int BM, int BN) {
     const int64_t tiles_m = (Ra + BM - 1) / BM, tiles_n = (Rb + BN - 1) / BN;
@@ -867,32 +852,35 @@ inline unsigned grid_tiles(int64_t Ra, int64_t Rb, const GemmGroup& g, int BM, i
     return (unsigned)(tok_tiles * other);
 }
 
+// one contraction as a unit that launch_units (launch_mix.hpp) puts into a launch, alone or with others
 template <bool SPARSE, bool OUT_I_CONTIG, int EPI, bool BLOCKED, bool FP8, class TL>
-hipError_t launch_gemm_v2_tile(const uint16_t* a_vals, const uint8_t* a_meta, const uint16_t* B, const float* bias, int64_t Ra, int64_t Rb, int64_t K,
-                               uint16_t* out, int64_t ldo, const VnmEpilogue& ep, const GemmGroup& g, float alpha, hipStream_t s) {
-    const unsigned tiles = grid_tiles(Ra, Rb, g, TL::BM, TL::BN);
-    if (tiles == 0) return hipSuccess;
-    hipLaunchKernelGGL((gemm_nt_v2_kernel<SPARSE, OUT_I_CONTIG, EPI, BLOCKED, FP8, TL>), dim3(tiles), dim3(TL::THREADS), 0, s, a_vals, a_meta, B, bias, (int)Ra,
-                       (int)Rb, (int)K, out, ldo, (int)((Ra + TL::BM - 1) / TL::BM), (int)((Rb + TL::BN - 1) / TL::BN), ep, g, alpha);
-    return hipGetLastError();
-}
-template <bool SPARSE, bool OUT_I_CONTIG, int EPI, bool BLOCKED, bool FP8>
-hipError_t launch_gemm_v2(const uint16_t* a_vals, const uint8_t* a_meta, const uint16_t* B, const float* bias, int64_t Ra, int64_t Rb, int64_t K,
-                          uint16_t* out, int64_t ldo, const VnmEpilogue& ep, const GemmGroup& g, float alpha, hipStream_t s) {
-    using Sel = TileSel<SPARSE, EPI>;
-    const int steps = (int)(K / (SPARSE ? 64 : 32));
-    // eq. (1) / (4) at T = D = 2048, F = 8192 (256 / 1024 tiles): 55 / 47 us on 256 tiles, 61 / 54 on 128; T = 1024, D = 1408, F = 4928 (80 / 312): 39 / 30 and
-    // 26 / 23; T = 64, D = 2048, F = 8192 (32 / 64 / 128): 43 / 33, 21 / 18, and 17 / 14 on 64 tiles
-    // (grouped over tokens: counted as if ungrouped, so that a host and a device segment table choose alike)
-    auto tiles = [&](int64_t edge) { return (unsigned)((Ra + edge - 1) / edge * ((Rb + edge - 1) / edge)) * (g.role == 2 && g.n ? (unsigned)g.n : 1u); };
-    switch (pick_tile(tiles(256), tiles(128), tiles(64), steps, BLOCKED ? 0.56f : 0.7f, SPARSE ? 256 : 0, 16)) {
-        case 256: return launch_gemm_v2_tile<SPARSE, OUT_I_CONTIG, EPI, BLOCKED, FP8, Tile256<SPARSE>>(a_vals, a_meta, B, bias, Ra, Rb, K, out, ldo, ep, g, alpha, s);
-        case 128: return launch_gemm_v2_tile<SPARSE, OUT_I_CONTIG, EPI, BLOCKED, FP8, typename Sel::T128>(a_vals, a_meta, B, bias, Ra, Rb, K, out, ldo, ep, g, alpha, s);
-        default:
-            // (the dense form has no 64 tile: its two users are the stand-alone vnm_wgrad and the router's weight gradients)
-            if constexpr (SPARSE) return launch_gemm_v2_tile<SPARSE, OUT_I_CONTIG, EPI, BLOCKED, FP8, typename Sel::T64>(a_vals, a_meta, B, bias, Ra, Rb, K, out, ldo, ep, g, alpha, s);
-            else return launch_gemm_v2_tile<SPARSE, OUT_I_CONTIG, EPI, BLOCKED, FP8, typename Sel::T128>(a_vals, a_meta, B, bias, Ra, Rb, K, out, ldo, ep, g, alpha, s);
+struct GemmV2Unit {
+    using Args = GemmV2Args;
+    static constexpr int THREADS = TL::THREADS, LDS = GemmV2Lds<SPARSE, OUT_I_CONTIG, EPI, BLOCKED, FP8, TL>::BYTES;
+    static __device__ __forceinline__ void run(unsigned char* smem, int pid, int n_pid, const Args& a) {
+        gemm_nt_v2_body<SPARSE, OUT_I_CONTIG, EPI, BLOCKED, FP8, TL>(smem, pid, n_pid, a.a_vals, a.a_meta, a.B, a.bias, a.Ra, a.Rb, a.K, a.out, a.ldo, a.tiles_m, a.tiles_n,
+                                                                     a.ep, a.grp, a.alpha);
     }
+    static unsigned count(const Args& a) { return grid_tiles(a.Ra, a.Rb, a.grp, TL::BM, TL::BN); }
+    static Args args(Args a) { a.tiles_m = (a.Ra + TL::BM - 1) / TL::BM; a.tiles_n = (a.Rb + TL::BN - 1) / TL::BN; return a; }
+};
+
+// the three tiles; blocks of M = 64 columns want 128 hidden units in one wavefront (two blocks share a metadata byte): 256 x 128 in the place of 128 x 128
+template <bool SPARSE> using Tile256 = Tile<2, 4, 128, SPARSE ? 3 : 4, 1>;
+template <bool SPARSE, int EPI> struct TileSel { using T128 = Tile<2, 2, 64, SPARSE ? 3 : 4, 1>; using T64 = Tile<1, 1, 64, 3, 4>; };
+template <> struct TileSel<true, 22> { using T128 = Tile<2, 2, 128, 2, 1>; using T64 = Tile<1, 1, 128, 2, 4>; };
+template <> struct TileSel<true, 38> { using T128 = Tile<2, 2, 128, 2, 1>; using T64 = Tile<1, 1, 128, 2, 4>; };
+
+// tile: 256 / 128 / 64, or 0 to choose here
+template <bool SPARSE, bool OUT_I_CONTIG, int EPI, bool BLOCKED, bool FP8>
+hipError_t launch_gemm_v2(const GemmV2Args& a, hipStream_t s, int tile = 0) {
+    using Sel = TileSel<SPARSE, EPI>;
+    if (!tile) tile = pick_gemm_tile(a.Ra, a.Rb, a.K / (SPARSE ? 64 : 32), a.grp, BLOCKED ? 0.56f : 0.7f, SPARSE);
+    if (tile == 256) return launch_units<GemmV2Unit<SPARSE, OUT_I_CONTIG, EPI, BLOCKED, FP8, Tile256<SPARSE>>>(s, a);
+    if (tile == 128) return launch_units<GemmV2Unit<SPARSE, OUT_I_CONTIG, EPI, BLOCKED, FP8, typename Sel::T128>>(s, a);
+    // (the dense form has no 64 tile: its two users are the stand-alone vnm_wgrad and the router's weight gradients)
+    if constexpr (SPARSE) return launch_units<GemmV2Unit<SPARSE, OUT_I_CONTIG, EPI, BLOCKED, FP8, typename Sel::T64>>(s, a);
+    else return launch_units<GemmV2Unit<SPARSE, OUT_I_CONTIG, EPI, BLOCKED, FP8, typename Sel::T128>>(s, a);
 }
 
 }  // namespace sffn

@@ -8,23 +8,21 @@ hipError_t launch_gemm_nt(int sparse_a, const uint16_t* a_vals, const uint8_t* a
                              const GemmGroup* grp) {
     const GemmGroup g = grp ? *grp : GemmGroup();
     if (g.n && (sparse_a || g.role != 2 || g.n > GemmGroup::kMaxExperts)) return hipErrorInvalidValue;
-    const VnmEpilogue none;
-    if (sparse_a) return out_i_contig ? launch_gemm_v2<true, true, 0, false, false>(a_vals, a_meta, B, bias, Ra, Rb, K, out, ldo, none, g, 1.0f, s)
-                                      : launch_gemm_v2<true, false, 0, false, false>(a_vals, a_meta, B, bias, Ra, Rb, K, out, ldo, none, g, 1.0f, s);
-    return out_i_contig ? launch_gemm_v2<false, true, 0, false, false>(a_vals, a_meta, B, bias, Ra, Rb, K, out, ldo, none, g, 1.0f, s)
-                        : launch_gemm_v2<false, false, 0, false, false>(a_vals, a_meta, B, bias, Ra, Rb, K, out, ldo, none, g, 1.0f, s);
+    const GemmV2Args a = {a_vals, a_meta, B, bias, (int)Ra, (int)Rb, (int)K, out, ldo, 0, 0, VnmEpilogue(), g, 1.0f};
+    if (sparse_a) return out_i_contig ? launch_gemm_v2<true, true, 0, false, false>(a, s)
+                                      : launch_gemm_v2<true, false, 0, false, false>(a, s);
+    return out_i_contig ? launch_gemm_v2<false, true, 0, false, false>(a, s)
+                        : launch_gemm_v2<false, false, 0, false, false>(a, s);
 }
 
 hipError_t launch_spmm24_fp8(const uint8_t* a_codes, const uint8_t* a_meta, const uint8_t* Bq, const float* bias, float alpha, int64_t Ra, int64_t Rb,
                              int64_t K, int out_i_contig, uint16_t* out, int64_t ldo, hipStream_t s) {
     if (K % 128 != 0) return hipErrorInvalidValue;
-    const VnmEpilogue none;
-    const GemmGroup g;
     // the kernel addresses its operands in 2-byte units: K / 2 of them per B row, K / 4 per A row
-    const uint16_t* a = reinterpret_cast<const uint16_t*>(a_codes);
-    const uint16_t* b = reinterpret_cast<const uint16_t*>(Bq);
-    return out_i_contig ? launch_gemm_v2<true, true, 0, false, true>(a, a_meta, b, bias, Ra, Rb, K / 2, out, ldo, none, g, alpha, s)
-                        : launch_gemm_v2<true, false, 0, false, true>(a, a_meta, b, bias, Ra, Rb, K / 2, out, ldo, none, g, alpha, s);
+    const GemmV2Args a = {reinterpret_cast<const uint16_t*>(a_codes), a_meta, reinterpret_cast<const uint16_t*>(Bq), bias, (int)Ra, (int)Rb, (int)(K / 2), out, ldo,
+                          0, 0, VnmEpilogue(), GemmGroup(), alpha};
+    return out_i_contig ? launch_gemm_v2<true, true, 0, false, true>(a, s)
+                        : launch_gemm_v2<true, false, 0, false, true>(a, s);
 }
 
 }  // namespace sffn

@@ -1,0 +1,363 @@
+// Eqs. (3), (7) of the paper for V:2:8 activations (V = 64, M = 8: the fused step's own format) without re-expressing the activation as a
+// plain 2:4 matrix over all F columns:
+//     out[t, n] = sum_k' Ac[t, k'] * Wk[row(t / 64, k'), n],      row(tb, k') = (k' / 4) * 8 + colidx[tb, k' / 4, k' % 4]
+// Ac = the packed activation read as a 2:4 matrix of logical width K' = F / 2 (two survivors per four kept columns), Wk = [F, ldw]
+// with the contraction index as row (W2.T for eq. (3), W1 as it is for eq. (7)).  The plain-2:4 route of gemm_v2.hip issues one
+// structured-sparse matrix instruction per 32 columns of F; this kernel issues one per 64, and fetches half the activation bytes.
+//
+// Tile: 256 tokens x 256 output columns, 8 wavefronts as 4 (token blocks) x 2 (column halves).  A 64-row tile (the
+// gathered-row kernel of gemm_gather.hip, which fetches only the kept rows) halves the reuse of Wk and is bound by L2 -> LDS delivery at
+// M = 8; here the whole [64 f x 256 n] slab of Wk of a stage goes to LDS once for the tile's four token blocks, and each token block picks
+// its kept rows when it READS its B fragments: ds_read_b64_tr_b16 takes one address per lane (inside a group of 16 lanes, lane s supplies 4
+// consecutive elements of row s / 4, lane l receives element l of those 4 rows), so the 4 rows of a read are the 4 kept hidden units of
+// one column block.  The 64-byte pieces of a slab row are XOR-swizzled by f % 8: the four rows of a read lie in one group of 8 rows and
+// therefore in four different pieces.
+//
+// Operands as the fused epilogues of eqs. (1), (4) write them (common.hpp: vcb_off, mcb_off, cixt_off):
+//   values    [T / 32][F / 64][32 tokens][16 values]   1 KB per (32 tokens, 64 hidden units): one wave-wide LDS-DMA load
+//   metadata  [T / 64][F / 64][64 tokens][4 bytes]     the canonical nibbles of the 8 column blocks of a stage
+//   offsets   [F / 64][T / 64][8 words]                word (h, r), byte j = kept column r of column block 4 (j / 2) + j % 2 + 2 h of the
+//                                                      stage: the four rows that lane (h = lane / 32, r = (lane % 16) / 4) addresses in read j
+// A stage = 64 hidden units = 32 k' = one matrix instruction step per fragment pair; 3 stages of 41.25 KB.
+//
+// FP8 (the fp8 step): the same kernel on E4M3 codes with v_smfmac_f32_32x32x64_fp8_fp8, out = bf16(alpha * sum).  A stage is 128 hidden
+// units = 64 k' (the instruction's K): the slab is 128 rows x 256 bytes, the survivors' codes fill the same 32 bytes per token and stage,
+// the metadata 8 bytes.  The B fragments are read with ds_read_b64_tr_b8 (inside a group of 16 lanes, lane s supplies 8 consecutive bytes of
+// row s / 2, lane l receives byte l of those 8 rows), so a read covers the kept rows of TWO column blocks; the offsets unit of a (128 hidden
+// units, token block) is 16 words: word (h, p), byte j = kept column p % 4 of column block 8 (j / 2) + 4 h + 2 (j % 2) + p / 4.  The 32-byte
+// pieces of a slab row are swizzled by f % 8.
+#pragma once
+#include "common.hpp"
+#include "kernels.hpp"
+#include "launch_mix.hpp"
+#include "lds_dma.hpp"
+
+// Tile rows per band of the workgroup -> tile map (see SFFN_TILE_GROUP in common.hpp).  A tile fetches four times as many bytes of Wk as of
+// the packed activation, so the 32 tiles that an XCD runs at a time should share few column slabs of Wk: tall bands (measured at
+// T = D = 8192, F = 28672: 1.49 / 1.42 / 1.38 / 1.36 ms per launch with 2 / 4 / 8 / 16 tile rows per band).
+#ifndef SFFN_VNM8_GROUP
+#define SFFN_VNM8_GROUP 16
+#endif
+
+namespace sffn {
+
+// Workgroup tile: WT token blocks (64 tokens) x WH column groups, one wavefront each (64 tokens x 32 FN columns).  KW > 1 (with one wavefront
+// per tile): KW wavefronts share the tile, wavefront g contracting stages g, g + KW, ... in a ring of its own; their partial sums meet in LDS.
+template <int WT_, int WH_, int FN_, int NST_, int KW_>
+struct VTile {
+    static constexpr int WT = WT_, WH = WH_, FN = FN_, NST = NST_, KW = KW_;
+    static constexpr int NW = WT * WH, BT = 64 * WT, BN = 32 * FN * WH, THREADS = 64 * NW * KW;
+    static_assert(KW == 1 || NW == 1, "a shared output tile belongs to single wavefronts");
+};
+template <bool FP8, class TL>
+struct G {
+    static constexpr int ES = FP8 ? 1 : 2;               // bytes per element of Wk
+    static constexpr int SLAB = FP8 ? 128 : 64;         // hidden units per stage
+    static constexpr int ROW = TL::BN * ES;              // bytes of a slab row
+    static constexpr int kB = SLAB * ROW;
+    static constexpr int kA = TL::BT * 32;
+    static constexpr int kMt = FP8 ? TL::BT * 8 : TL::BT * 4;
+    static constexpr int kC = 256;
+    static constexpr int kStage = kB + kA + kMt + kC;
+    static constexpr int B_LD = kB / 1024 / TL::NW, A_LD = kA / 1024 / TL::NW, M_LD = (kMt / 256 + TL::NW - 1) / TL::NW;    // loads per wave and stage
+    static constexpr int LOADS = B_LD + A_LD + M_LD + 1;
+    static constexpr int PIECE = FP8 ? 32 : 64;          // bytes of a swizzled piece = 32 columns
+    static constexpr int NP = ROW / PIECE;               // pieces of a row
+    static constexpr int PMASK = (NP < 8 ? NP : 8) - 1;
+    static constexpr int BYTES = TL::KW * TL::NST * kStage;
+};
+
+// Wk / ldw: bf16 elements, or (FP8) code bytes
+template <bool FP8, class TL>
+__device__ __forceinline__ void vnm8_gemm_body(unsigned char* __restrict__ smem, int pid, int n_pid, const uint16_t* __restrict__ vcb, const uint8_t* __restrict__ mcb,
+                                               const uint8_t* __restrict__ cixt, const uint8_t* __restrict__ Wk, int ldw,
+                                               int Ra, int N, int F, int Ttot, uint16_t* __restrict__ out, int64_t ldo,
+                                               int tiles_m, int tiles_n, const GemmGroup& grp, float alpha) {
+    using GG = G<FP8, TL>;
+    constexpr int kB = GG::kB, kA = GG::kA, kMt = GG::kMt, kStage = GG::kStage, ES = GG::ES, kStages = TL::NST, kLoads = GG::LOADS, KW = TL::KW, FN = TL::FN;
+    constexpr int BT = TL::BT, BN = TL::BN, ROW = GG::ROW, B_LD = GG::B_LD, A_LD = GG::A_LD, M_LD = GG::M_LD, PB = GG::PIECE, PM = GG::PMASK;
+
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int l32 = lane & 31, lh = lane >> 5;
+    const int kg = KW > 1 ? wave : 0, wt = KW > 1 ? 0 : wave;       // share of the contraction / place in the tile
+    unsigned char* const ring = smem + kg * (kStages * kStage);
+
+    int L;
+    {
+        const int per = n_pid >> 3;
+        L = (pid < per * 8) ? (pid & 7) * per + (pid >> 3) : pid;
+    }
+    // Grouped form (role 0): the token tiles of segment e meet expert e's matrix
+    int i_base = 0;
+    if (grp.n) {
+        int e = 0, cnt = 0;
+        for (; e < grp.n; ++e) {
+            cnt = (grp.seg[e + 1] - grp.seg[e] + BT - 1) / BT * tiles_n;
+            if (L < cnt) break;
+            L -= cnt;
+        }
+        if (e == grp.n) return;
+        tiles_m = cnt / tiles_n; i_base = grp.seg[e]; Ra = grp.seg[e + 1];
+        Wk += (int64_t)e * grp.b_stride * ES;
+    }
+    int tm, tn;
+    {
+        constexpr int GROUP = SFFN_VNM8_GROUP;
+        const int width = GROUP * tiles_n, group = L / width, first = group * GROUP;
+        const int gsz = (tiles_m - first) < GROUP ? (tiles_m - first) : GROUP;
+        tm = first + (L % width) % gsz;
+        tn = (L % width) / gsz;
+    }
+    const int i0 = i_base + tm * BT, n0 = tn * BN;
+    const int KS = F / GG::SLAB;                     // stages = slabs of 64 (128) hidden units
+    const int NTB = Ttot >> 6;
+
+    // ---- DMA sources (wave-uniform 64-bit base + 32-bit per-lane offset).  Token groups past the end of the operand are clamped into it:
+    //      they only feed outputs that are never stored. ----------------------------------------------------------------------------------
+    // B: a load brings 1024 / ROW slab rows; a lane's 16-byte slot fetches the chunk whose piece (PB bytes = 32 columns) the swizzle puts there:
+    // piece p of row f sits at p ^ (f % min(8, pieces)).  Chunks past the right edge of Wk are redirected into the first 64 columns.
+    const uint64_t w_base = uniform64(Wk);
+    constexpr int LPR = ROW / 16, RPL = 1024 / ROW;         // 16-byte slots per slab row, rows per load
+    uint32_t b_lane[B_LD];
+#pragma unroll
+    for (int i = 0; i < B_LD; ++i) {
+        const int row = RPL * (B_LD * wt + i) + lane / LPR, slot = lane % LPR;
+        constexpr int SPP = PB / 16;                         // slots per piece
+        int c = (((slot / SPP) ^ (row & PM)) * SPP) | (slot & (SPP - 1));
+        if (n0 + c * (16 / ES) >= N) c &= (64 * ES / 16) - 1;
+        b_lane[i] = ((uint32_t)row * (uint32_t)ldw + (uint32_t)(n0 + c * (16 / ES))) * ES;
+    }
+    const uint32_t b_kstep = (uint32_t)GG::SLAB * (uint32_t)ldw * ES;
+    uint64_t a_base[A_LD], m_base[M_LD], c_base;
+    uint32_t a_lane, m_lane, c_lane;
+    {
+#pragma unroll
+        for (int i = 0; i < A_LD; ++i) {                 // 32 tokens of the tile each
+            int g32 = (i0 >> 5) + wt * A_LD + i;
+            g32 = g32 < (Ttot >> 5) ? g32 : (Ttot >> 5) - 1;
+            a_base[i] = uniform64(vcb + (int64_t)g32 * KS * 512);
+        }
+        const int row = lane >> 1, slot = lane & 1;
+        a_lane = (uint32_t)(row * 32 + ((slot ^ ((row >> 3) & 1)) << 4));
+#pragma unroll
+        for (int i = 0; i < M_LD; ++i) {
+            // 256-byte pieces: 64 tokens (bf16) / half of the 512-byte unit of a token block (FP8).  With fewer pieces than wavefronts two fetch the same
+            const int mi = (wt * M_LD + i) % (kMt / 256);
+            int g64 = (i0 >> 6) + (FP8 ? mi >> 1 : mi);
+            g64 = g64 < NTB ? g64 : NTB - 1;
+            m_base[i] = uniform64(FP8 ? mcb + (int64_t)g64 * KS * 512 + (mi & 1) * 256 : mcb + (int64_t)g64 * KS * 256);
+        }
+        m_lane = lane * 4;
+        // offsets of the tile's token blocks, 32 (FP8: 64) bytes each: every wave fetches all of them (four slots; unused ones repeat the last)
+        const int words = FP8 ? 16 : 8;
+        int tb = FP8 ? (lane >> 4) : (l32 >> 3);
+        tb = (i0 >> 6) + (tb < TL::WT ? tb : TL::WT - 1);
+        tb = tb < NTB ? tb : NTB - 1;
+        c_base = uniform64(cixt);
+        c_lane = (uint32_t)(tb * words * 4 + (lane & (words - 1)) * 4);
+    }
+    const uint32_t c_kstep = (uint32_t)NTB * (FP8 ? 64u : 32u);
+    constexpr uint32_t m_kstep = FP8 ? 512u : 256u;
+    auto issue_half = [&](int kt, int stage, int h) {
+        unsigned char* sb = ring + stage * kStage;
+        unsigned char* sa = sb + kB;
+        unsigned char* sm = sa + kA;
+        unsigned char* sc = sm + kMt;
+        if (h == 0) {
+#pragma unroll
+            for (int i = 0; i < B_LD / 2; ++i) dma16(w_base, b_lane[i] + (uint32_t)kt * b_kstep, sb + (B_LD * wt + i) * 1024);
+#pragma unroll
+            for (int i = 0; i < A_LD; ++i) dma16(a_base[i], a_lane + (uint32_t)kt * 1024u, sa + (wt * A_LD + i) * 1024);
+            dma4(c_base, c_lane + (uint32_t)kt * c_kstep, sc);
+        } else {
+#pragma unroll
+            for (int i = B_LD / 2; i < B_LD; ++i) dma16(w_base, b_lane[i] + (uint32_t)kt * b_kstep, sb + (B_LD * wt + i) * 1024);
+#pragma unroll
+            for (int i = 0; i < M_LD; ++i) dma4(m_base[i], m_lane + (uint32_t)kt * m_kstep, sm + ((wt * M_LD + i) % (kMt / 256)) * 256);
+        }
+    };
+    auto issue = [&](int kt, int stage) { issue_half(kt, stage, 0); issue_half(kt, stage, 1); };
+
+    // ---- per-lane LDS offsets of the fragment reads (inside a stage).  A wave owns one token block (64 tokens) x 32 FN output columns: the
+    //      B fragments it gathers belong to one column selection. ----------------------
+    const int tbw = wt / TL::WH, nh = wt % TL::WH;
+    int a_off[2], m_off[2];
+#pragma unroll
+    for (int a = 0; a < 2; ++a) {
+        const int row = tbw * 64 + a * 32 + l32;
+        a_off[a] = kB + row * 32 + ((lh ^ ((row >> 3) & 1)) << 4);
+        m_off[a] = kB + kA + (FP8 ? row * 8 + 4 * lh : row * 4 + 2 * lh);
+    }
+    // bf16: transpose read j of fragment fn: slab row = 8 cb(j) + c with cb(j) = 4 (j / 2) + j % 2 + 2 h and c = byte j of the lane's offsets
+    // word; byte address = row * ROW + ((FN nh + fn) ^ (c % pieces)) * 64 + 32 (column half) + 8 (lane % 4)
+    // FP8: the lane addresses row p = (lane % 16) / 2 of the read's 8: cb(j) = 8 (j / 2) + 4 h + 2 (j % 2) + p / 4, c = byte j of word (h, p);
+    // byte address = row * ROW + ((FN nh + fn) ^ (c % pieces)) * 32 + 16 (column half) + 8 (lane % 2)
+    const int r4 = (lane & 15) >> 2, p8 = (lane & 15) >> 1, g = lane >> 4;
+    const int c_off = kB + kA + kMt + (FP8 ? 64 * tbw + (lh * 8 + p8) * 4 : 32 * tbw + (lh * 4 + r4) * 4);
+    const int b_fix = FP8 ? ((g & 1) << 4) + ((lane & 1) << 3) : ((g & 1) << 5) + ((lane & 3) << 3);
+    int b_cb[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+        b_cb[j] = FP8 ? (8 * (j >> 1) + 4 * lh + 2 * (j & 1) + (p8 >> 2)) * 8 * ROW + b_fix : (4 * (j >> 1) + (j & 1) + 2 * lh) * 8 * ROW + b_fix;
+
+    f32x16 acc[2][FN];
+#pragma unroll
+    for (int a = 0; a < 2; ++a)
+#pragma unroll
+        for (int b = 0; b < FN; ++b)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[a][b][r] = 0.0f;
+
+    // The stage's fragments in two halves: P = both A fragments, the offsets word and the first HB = FN / 2 B fragments; Q = the others (the A
+    // fragments of P stay live until Q's matrix instructions, so A is double-buffered by stage parity)
+    constexpr int HB = FN / 2;
+    struct BPair { union { s16x4 q[4]; v2i q8[4]; bf16x16 v; i32x8 v8; } b[HB]; };
+    struct AFrags { Frag8 a[2]; int idx[2]; uint32_t cw; };
+    auto read_a = [&](AFrags& f, const unsigned char* st) {
+        f.cw = *reinterpret_cast<const uint32_t*>(st + c_off);
+#pragma unroll
+        for (int a2 = 0; a2 < 2; ++a2) {
+            f.a[a2].u = *reinterpret_cast<const uint4*>(st + a_off[a2]);
+            f.idx[a2] = FP8 ? (int)*reinterpret_cast<const uint32_t*>(st + m_off[a2]) : (int)*reinterpret_cast<const uint16_t*>(st + m_off[a2]);
+        }
+    };
+    auto read_b = [&](BPair& f, const unsigned char* st, uint32_t cw, int half) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const uint32_t c = (cw >> (8 * j)) & 7u;
+            const uint32_t addr = (uint32_t)b_cb[j] + c * (uint32_t)ROW + ((((uint32_t)(FN * nh + HB * half)) ^ (c & (uint32_t)PM)) * PB);
+#pragma unroll
+            for (int q = 0; q < HB; ++q) {
+                if (FP8) f.b[q].q8[j] = __builtin_amdgcn_ds_read_tr8_b64_v2i32((lds_v2i*)(st + (addr ^ (uint32_t)(q * PB))));
+                else     f.b[q].q[j] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(st + (addr ^ (uint32_t)(q * PB))));
+            }
+        }
+    };
+    auto mma_half = [&](const AFrags& fa, const BPair& fb, int half) {
+#pragma unroll
+        for (int a2 = 0; a2 < 2; ++a2)
+#pragma unroll
+            for (int fn = 0; fn < HB; ++fn)
+                if (FP8) acc[a2][HB * half + fn] = __builtin_amdgcn_smfmac_f32_32x32x64_fp8_fp8(fa.a[a2].q, fb.b[fn].v8, acc[a2][HB * half + fn], fa.idx[a2], 0, 0);
+                else     acc[a2][HB * half + fn] = __builtin_amdgcn_smfmac_f32_32x32x32_bf16(fa.a[a2].v, fb.b[fn].v, acc[a2][HB * half + fn], fa.idx[a2], 0, 0);
+    };
+#define SB() __builtin_amdgcn_sched_barrier(0)
+
+    const int nk = KW == 1 ? KS : (KS - kg + KW - 1) / KW;
+    auto step_of = [&](int kt) { return KW == 1 ? kt : kg + kt * KW; };
+    if (nk > 0) {
+#pragma unroll
+    for (int p = 0; p < kStages; ++p) issue(step_of(p < nk ? p : nk - 1), p);
+    wait_vmcnt<(kStages - 1) * kLoads>();
+    if (KW == 1) __syncthreads();
+    else asm volatile("" ::: "memory");
+    AFrags A0, A1;
+    BPair P, Q;
+    read_a(A0, ring);
+    read_b(P, ring, A0.cw, 0);
+    int stage = 0;
+    // two stages per trip so that the A fragment buffers alternate without copies
+    auto step = [&](int kt, AFrags& cur, AFrags& nxt_a) {
+        const int nxt = step_of((kt + kStages < nk) ? kt + kStages : nk - 1);
+        const int next_stage = (stage + 1 == kStages) ? 0 : stage + 1;
+        const unsigned char* st = ring + stage * kStage;
+        const unsigned char* sn = ring + next_stage * kStage;
+        mma_half(cur, P, 0); SB();
+        read_b(Q, st, cur.cw, 1); SB();
+        // Q has arrived and this wave's part of tile kt + 1 has landed; after the barrier every wave is done reading this stage, which is
+        // refilled at once
+        wait_vmcnt_lgkm0<(kStages - 2) * kLoads>();
+        if (KW == 1) __builtin_amdgcn_s_barrier();
+        else asm volatile("" ::: "memory");
+        SB();
+        issue_half(nxt, stage, 0); SB();
+        read_a(nxt_a, sn); SB();
+        mma_half(cur, Q, 1); SB();
+        issue_half(nxt, stage, 1); SB();
+        read_b(P, sn, nxt_a.cw, 0); SB();
+        stage = next_stage;
+    };
+    int kt = 0;
+    for (; kt + 1 < nk; kt += 2) {
+        step(kt, A0, A1);
+        step(kt + 1, A1, A0);
+    }
+    if (kt < nk) step(kt, A0, A1);
+#undef SB
+    wait_vmcnt<0>();
+    }
+    __syncthreads();
+    if (KW > 1) {       // partial sums -> the first wavefront, in ascending order; the others are done
+        constexpr int PART = 2 * FN * 16 * 256;
+        static_assert((KW - 1) * PART <= GG::BYTES, "partial sums must fit in the main-loop LDS");
+        if (kg > 0) {
+            float* p = reinterpret_cast<float*>(smem + (kg - 1) * PART) + lane;
+#pragma unroll
+            for (int a = 0; a < 2; ++a)
+#pragma unroll
+                for (int b = 0; b < FN; ++b)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) p[((a * FN + b) * 16 + r) * 64] = acc[a][b][r];
+        }
+        __syncthreads();
+        if (kg > 0) return;
+        for (int g = 1; g < KW; ++g) {
+            const float* p = reinterpret_cast<const float*>(smem + (g - 1) * PART) + lane;
+#pragma unroll
+            for (int a = 0; a < 2; ++a)
+#pragma unroll
+                for (int b = 0; b < FN; ++b)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) acc[a][b][r] += p[((a * FN + b) * 16 + r) * 64];
+        }
+        wave_lds_sync();
+    }
+
+    // ---- output: the wave's 32 x 64 sub-tiles go through LDS as [t][n] so that HBM sees 128-byte row segments -----------------------------
+    constexpr int EP = 64 * 2 + 16;
+    unsigned char* scratch = smem + wt * (32 * EP);
+#pragma unroll
+    for (int a = 0; a < 2; ++a)
+#pragma unroll
+        for (int half = 0; half < FN / 2; ++half) {
+#pragma unroll
+            for (int b = 0; b < 2; ++b)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) {
+                    const int row = 8 * (r >> 2) + 4 * lh + (r & 3);
+                    *reinterpret_cast<uint16_t*>(scratch + row * EP + (b * 32 + l32) * 2) = (uint16_t)f2bf(FP8 ? acc[a][2 * half + b][r] * alpha : acc[a][2 * half + b][r]);
+                }
+            wave_lds_sync();
+#pragma unroll
+            for (int p = 0; p < 4; ++p) {
+                const int e = lane + 64 * p, row = e >> 3, ch = e & 7;
+                const int i = i0 + tbw * 64 + a * 32 + row, j = n0 + nh * 32 * FN + half * 64 + ch * 8;
+                if (i < Ra && j < N) *reinterpret_cast<uint4*>(out + (int64_t)i * ldo + j) = *reinterpret_cast<const uint4*>(scratch + row * EP + ch * 16);
+            }
+            wave_lds_sync();
+        }
+}
+
+inline unsigned vnm8_tiles(int64_t T, int64_t N, const GemmGroup& g, int BT, int BN) {
+    const int64_t tiles_n = (N + BN - 1) / BN;
+    if (!g.n) return (unsigned)((T + BT - 1) / BT * tiles_n);
+    int64_t n = 0;
+    for (int e = 0; e < g.n; ++e) n += (g.seg[e + 1] - g.seg[e] + BT - 1) / BT * tiles_n;
+    return (unsigned)n;
+}
+template <bool FP8, class TL>
+struct Vnm8Unit {
+    using Args = Vnm8Args;
+    static constexpr int THREADS = TL::THREADS, LDS = G<FP8, TL>::BYTES;
+    static __device__ __forceinline__ void run(unsigned char* smem, int pid, int n_pid, const Args& a) {
+        vnm8_gemm_body<FP8, TL>(smem, pid, n_pid, a.vcb, a.mcb, a.cixt, a.Wk, a.ldw, a.T, a.N, a.F, a.T, a.out, a.ldo, a.tiles_m, a.tiles_n, a.grp, a.alpha);
+    }
+    static unsigned count(const Args& a) { return vnm8_tiles(a.T, a.N, a.grp, TL::BT, TL::BN); }
+    static Args args(Args a) { a.tiles_m = (a.T + TL::BT - 1) / TL::BT; a.tiles_n = (a.N + TL::BN - 1) / TL::BN; return a; }
+};
+template <bool FP8> using Vnm8Unit256 = Vnm8Unit<FP8, VTile<4, 2, 4, 3, 1>>;
+template <bool FP8> using Vnm8Unit128 = Vnm8Unit<FP8, VTile<2, 2, 2, 3, 1>>;
+template <bool FP8> using Vnm8Unit64 = Vnm8Unit<FP8, VTile<1, 1, 2, 3, 4>>;
+
+}  // namespace sffn

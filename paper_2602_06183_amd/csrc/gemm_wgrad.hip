@@ -1,636 +1,32 @@
-// Weight-gradient contractions of the fused step, eq. (5) dW2 = y2.T dY and eq. (8) dW1 = dy1.T X (Alg. 2 lines 3, 6):
-//   C[f, n] = sum_t A[t, f] * G[t, n],  A = the V:N:M activation (y2 or dy1), G = dY or X, contraction over tokens.
-// The 2:4 structure of A lies along the output rows here, so the structured-sparse matrix instruction does not apply;
-// what the format still gives is that, inside a block of 64 tokens, only 4 of every 8 hidden units are non-zero.
-// The producer (the V:N:M epilogue of gemm_v2.hip) therefore stores the transposed activation compacted to those
-// rows ("atc": row 4 g + p of token block tb = hidden unit 8 g + colidx[tb, g, p]; [F / 2 rows, T tokens], blocked
-// layout of common.hpp), which halves its bytes in HBM, in L2 and on the way into LDS.  This kernel runs dense
-// v_mfma_f32_32x32x16_bf16 on a 256 (hidden) x 256 tile; a lane that needs hidden unit f looks up, once per
-// 64-token stage, whether f is one of its group's four kept units (a bit mask per group, written by the producer;
-// the position among the kept units is a population count) and reads either that compact row or a row of zeros
-// kept at the end of the tile.  Same ring / barrier / LDS-DMA discipline as gemm_v2.hip: 3 stages of 64
-// tokens (A 16 KB as two 32-token halves, G 32 KB as two halves, 8 private copies of the tile's 32 mask bytes).
-#include "common.hpp"
-#include "kernels.hpp"
-#include "lds_dma.hpp"
+// Launchers of the weight-gradient contractions (gemm_wgrad_body.hpp).
+#include "gemm_wgrad_body.hpp"
 
 namespace sffn {
 
-// Workgroup tile: WVM x WVN wavefronts of WM hidden units x 64 columns each; KW > 1 (with one wavefront per tile): KW wavefronts share the
-// tile, wavefront g contracting token blocks g, g + KW, ... in a ring of its own; their partial sums meet in LDS.
-template <int WVM_, int WVN_, int WM_, int NST_, int KW_>
-struct WTile {
-    static constexpr int WVM = WVM_, WVN = WVN_, WM = WM_, NST = NST_, KW = KW_;
-    static constexpr int NW = WVM * WVN, BM = WVM * WM, BN = WVN * 64, FM = WM / 32, FN = 2, THREADS = 64 * NW * KW;
-    static_assert(KW == 1 || NW == 1, "a shared output tile belongs to single wavefronts");
-    // bf16 stage (64 tokens): BM / 2 compact rows x 32 tokens and a row of zeros, twice; G likewise in two halves; a private copy of the mask bytes per wavefront
-    static constexpr int kZero = BM / 2 * 64, kAHalf = kZero + 64, kABytes = 2 * kAHalf, kBHalf = BN * 64, kBBytes = 2 * kBHalf;
-    static constexpr int kStage = kABytes + kBBytes + NW * 256;
-    static constexpr int A_LD = BM / 32 / NW, B_LD = kBBytes / 1024 / NW, kLoads = 1 + 2 * A_LD + B_LD;      // LDS-DMA loads per wavefront per stage
-    // fp8 stage (64 tokens, one byte each): half of everything
-    static constexpr int k8A = kAHalf, k8B = kBHalf, k8Stage = k8A + k8B + NW * 256, B8_LD = k8B / 1024 / NW, k8Loads = 1 + A_LD + B8_LD;
-    static constexpr int EPI = NW * 64 * (64 * 4 + 16) / 2 > NW * 64 * (64 * 2 + 16) ? NW * 64 * (64 * 4 + 16) / 2 : NW * 64 * (64 * 2 + 16);   // wgrad_store's staging
-    static constexpr int BYTES = KW * NST * kStage > EPI ? KW * NST * kStage : EPI;
-    static constexpr int BYTES8 = KW * NST * k8Stage > EPI ? KW * NST * k8Stage : EPI;
-};
-
-// partial sums of KW wavefronts -> the first one, in ascending order; returns false for the wavefronts that are done
-template <class TL>
-__device__ __forceinline__ bool wgrad_join(f32x16 (&acc)[TL::FM][TL::FN], unsigned char* smem, int kg, int lane) {
-    constexpr int PART = TL::FM * TL::FN * 16 * 256;
-    static_assert((TL::KW - 1) * PART <= TL::BYTES && (TL::KW - 1) * PART <= TL::BYTES8, "partial sums must fit in the main-loop LDS");
-    if (kg > 0) {
-        float* p = reinterpret_cast<float*>(smem + (kg - 1) * PART) + lane;
-#pragma unroll
-        for (int a = 0; a < TL::FM; ++a)
-#pragma unroll
-            for (int b = 0; b < TL::FN; ++b)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) p[((a * TL::FN + b) * 16 + r) * 64] = acc[a][b][r];
-    }
-    __syncthreads();
-    if (kg > 0) return false;
-    for (int g = 1; g < TL::KW; ++g) {
-        const float* p = reinterpret_cast<const float*>(smem + (g - 1) * PART) + lane;
-#pragma unroll
-        for (int a = 0; a < TL::FM; ++a)
-#pragma unroll
-            for (int b = 0; b < TL::FN; ++b)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) acc[a][b][r] += p[((a * TL::FN + b) * 16 + r) * 64];
-    }
-    wave_lds_sync();
-    return true;
-}
-
-// Accumulators of one WM x 64 wave tile -> bf16 output (one rounding; `alpha` = product of the operand scales of the fp8 form, 1 otherwise).
-// ACC32: `out` is a float32 matrix of the same shape that the tile is ADDED to (gradient accumulation over the micro-batches of an
-// optimizer step): out32 = out32 + alpha * sum, both in float32.
-template <bool OUT_I_CONTIG, bool ACC32, class TL>
-__device__ __forceinline__ void wgrad_store(f32x16 (&acc)[TL::FM][TL::FN], float alpha, unsigned char* smem, int wave, int lane, int i0, int j0, int F, int N,
-                                            uint16_t* __restrict__ out, int64_t ldo) {
-    constexpr int WM = TL::WM, WN = 64, FM = TL::FM, FN = TL::FN;
-    const int wm = wave / TL::WVN, wn = wave % TL::WVN, l32 = lane & 31, lh = lane >> 5;
-    if (ACC32 && OUT_I_CONTIG) {
-        // out32[j * ldo + i]: a lane owns 4 consecutive i of one j; stage [32 j][64 i] through LDS so that HBM sees 256-byte row
-        // segments in 16-byte accesses (read, add, write)
-        float* out32 = reinterpret_cast<float*>(out);
-        constexpr int EP = 64 * 4 + 16;
-        unsigned char* scratch = smem + wave * (32 * EP);
-#pragma unroll
-        for (int h = 0; h < WM / 64; ++h)
-#pragma unroll
-            for (int b = 0; b < FN; ++b) {
-                const int f0 = i0 + wm * WM + h * 64, n0 = j0 + wn * WN + b * 32;
-#pragma unroll
-                for (int a2 = 0; a2 < 2; ++a2)
-#pragma unroll
-                    for (int g = 0; g < 4; ++g) {
-                        const int a = 2 * h + a2;
-                        *reinterpret_cast<float4*>(scratch + l32 * EP + (a2 * 32 + 8 * g + 4 * lh) * 4) =
-                            make_float4(acc[a][b][4 * g] * alpha, acc[a][b][4 * g + 1] * alpha, acc[a][b][4 * g + 2] * alpha, acc[a][b][4 * g + 3] * alpha);
-                    }
-                wave_lds_sync();
-                // all of the slab's old values are requested before the first sum is stored (a store would otherwise stand between the loads)
-                float4 old[8];
-#pragma unroll
-                for (int p = 0; p < 8; ++p) {
-                    const int row = p * 4 + (lane >> 4), ch = lane & 15;
-                    const int j = n0 + row, i = f0 + ch * 4;
-                    old[p] = (j < N && i < F) ? *reinterpret_cast<const float4*>(out32 + (int64_t)j * ldo + i) : make_float4(0.f, 0.f, 0.f, 0.f);
-                }
-#pragma unroll
-                for (int p = 0; p < 8; ++p) {
-                    const int row = p * 4 + (lane >> 4), ch = lane & 15;
-                    const int j = n0 + row, i = f0 + ch * 4;
-                    if (j < N && i < F) {
-                        const float4 add = *reinterpret_cast<const float4*>(scratch + row * EP + ch * 16);
-                        *reinterpret_cast<float4*>(out32 + (int64_t)j * ldo + i) = make_float4(old[p].x + add.x, old[p].y + add.y, old[p].z + add.z, old[p].w + add.w);
-                    }
-                }
-                wave_lds_sync();
-            }
-    } else if (ACC32) {
-        // out32[i * ldo + j]: each 32-row slab goes through LDS, as in the bf16 form below, for 16-byte accesses on 256-byte row segments;
-        // the products are rounded to float32 before they are staged, so the addition is never a fused multiply-add
-        float* out32 = reinterpret_cast<float*>(out);
-        constexpr int EP = WN * 4 + 16;
-        unsigned char* scratch = smem + wave * (32 * EP);
-#pragma unroll
-        for (int a = 0; a < FM; ++a) {
-#pragma unroll
-            for (int b = 0; b < FN; ++b)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    const int row = 8 * (r >> 2) + 4 * lh + (r & 3);
-                    *reinterpret_cast<float*>(scratch + row * EP + (b * 32 + l32) * 4) = acc[a][b][r] * alpha;
-                }
-            wave_lds_sync();
-            float4 old[8];
-#pragma unroll
-            for (int p = 0; p < 8; ++p) {
-                const int row = p * 4 + (lane >> 4), ch = lane & 15;
-                const int i = i0 + wm * WM + a * 32 + row, j = j0 + wn * WN + ch * 4;
-                old[p] = (i < F && j < N) ? *reinterpret_cast<const float4*>(out32 + (int64_t)i * ldo + j) : make_float4(0.f, 0.f, 0.f, 0.f);
-            }
-#pragma unroll
-            for (int p = 0; p < 8; ++p) {
-                const int row = p * 4 + (lane >> 4), ch = lane & 15;
-                const int i = i0 + wm * WM + a * 32 + row, j = j0 + wn * WN + ch * 4;
-                if (i < F && j < N) {
-                    const float4 add = *reinterpret_cast<const float4*>(scratch + row * EP + ch * 16);
-                    *reinterpret_cast<float4*>(out32 + (int64_t)i * ldo + j) = make_float4(old[p].x + add.x, old[p].y + add.y, old[p].z + add.z, old[p].w + add.w);
-                }
-            }
-            wave_lds_sync();
-        }
-    } else if (OUT_I_CONTIG) {
-        // out[j * ldo + i]: a lane owns 4 consecutive i of one j; stage [j][i] through LDS (two halves of 64 i)
-        // so that HBM sees 128-byte row segments
-        constexpr int EP = 64 * 2 + 16;
-        unsigned char* scratch = smem + wave * (WN * EP);
-#pragma unroll
-        for (int h = 0; h < WM / 64; ++h) {
-            const int f0 = i0 + wm * WM + h * 64, n0 = j0 + wn * WN;
-#pragma unroll
-            for (int a2 = 0; a2 < 2; ++a2)
-#pragma unroll
-                for (int b = 0; b < FN; ++b)
-#pragma unroll
-                    for (int g = 0; g < 4; ++g) {
-                        const int a = 2 * h + a2, il = a2 * 32 + 8 * g + 4 * lh;
-                        *reinterpret_cast<uint2*>(scratch + (b * 32 + l32) * EP + il * 2) =
-                            make_uint2(f2bf2(acc[a][b][4 * g] * alpha, acc[a][b][4 * g + 1] * alpha), f2bf2(acc[a][b][4 * g + 2] * alpha, acc[a][b][4 * g + 3] * alpha));
-                    }
-            wave_lds_sync();
-#pragma unroll
-            for (int p = 0; p < WN / 8; ++p) {
-                const int row = p * 8 + (lane >> 3), ch = lane & 7;
-                const int j = n0 + row, i = f0 + ch * 8;
-                if (j < N && i < F)
-                    *reinterpret_cast<uint4*>(out + (int64_t)j * ldo + i) = *reinterpret_cast<const uint4*>(scratch + row * EP + ch * 16);
-            }
-            wave_lds_sync();
-        }
-    } else {
-        // out[i * ldo + j]: transpose each 32-row slab through LDS for 16-byte row stores
-        constexpr int EP = WN * 2 + 16;
-        unsigned char* scratch = smem + wave * (32 * EP);
-#pragma unroll
-        for (int a = 0; a < FM; ++a) {
-#pragma unroll
-            for (int b = 0; b < FN; ++b)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    const int row = 8 * (r >> 2) + 4 * lh + (r & 3);
-                    *reinterpret_cast<uint16_t*>(scratch + row * EP + (b * 32 + l32) * 2) = (uint16_t)f2bf(acc[a][b][r] * alpha);
-                }
-            wave_lds_sync();
-#pragma unroll
-            for (int p = 0; p < 32 * (WN / 8) / 64; ++p) {
-                const int e = lane + 64 * p, row = e / (WN / 8), ch = e % (WN / 8);
-                const int i = i0 + wm * WM + a * 32 + row, j = j0 + wn * WN + ch * 8;
-                if (i < F && j < N)
-                    *reinterpret_cast<uint4*>(out + (int64_t)i * ldo + j) = *reinterpret_cast<const uint4*>(scratch + row * EP + ch * 16);
-            }
-            wave_lds_sync();
-        }
-    }
-}
-
-template <bool OUT_I_CONTIG, bool ACC32, class TL>
-__global__ void __launch_bounds__(TL::THREADS, (TL::KW > 1 || TL::NW < 4) ? 1 : 2) wgrad_vnm_kernel(const uint16_t* __restrict__ atc, const uint8_t* __restrict__ kmask,
-                                                       const uint16_t* __restrict__ G, int F, int N, int Ttot,
-                                                       uint16_t* __restrict__ out, int64_t ldo, int tiles_m, int tiles_n,
-                                                       GemmGroup grp) {
-    constexpr int BM = TL::BM, BN = TL::BN, WM = TL::WM, WN = 64, FM = TL::FM, FN = TL::FN, KW = TL::KW;
-    constexpr int kStages = TL::NST, kStage = TL::kStage, kAHalf = TL::kAHalf, kABytes = TL::kABytes, kBHalf = TL::kBHalf, kBBytes = TL::kBBytes, kLoads = TL::kLoads;
-    constexpr int A_LD = TL::A_LD, B_LD = TL::B_LD;
-    __shared__ __attribute__((aligned(1024))) unsigned char smem[TL::BYTES];
-
-    const int tid = threadIdx.x, lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int kg = KW > 1 ? wave : 0, wt = KW > 1 ? 0 : wave;       // share of the contraction / place in the tile
-    const int wm = wt / TL::WVN, wn = wt % TL::WVN;
-    const int l32 = lane & 31, lh = lane >> 5;
-    unsigned char* const ring = smem + kg * (kStages * kStage);
-
-    // workgroup -> tile: an XCD gets a run of consecutive logical ids, which walk bands of 4 tile rows
-    int L;
-    {
-        const int n = gridDim.x, pid = blockIdx.x, per = n >> 3;
-        L = (pid < per * 8) ? (pid & 7) * per + (pid >> 3) : pid;
-    }
-    int k_base = 0, K = Ttot;                     // grouped: every expert contracts over its own token segment
-    if (grp.n) {
-        const int per = tiles_m * tiles_n, e = L / per;
-        L -= e * per;
-        k_base = grp.seg[e];
-        K = grp.seg[e + 1] - k_base;
-        out += e * grp.out_stride * (ACC32 ? 2 : 1);          // (float32 elements are two uint16_t wide)
-    }
-    int tm, tn;
-    {
-        constexpr int GROUP = SFFN_TILE_GROUP;
-        const int width = GROUP * tiles_n, group = L / width, first = group * GROUP;
-        const int gsz = (tiles_m - first) < GROUP ? (tiles_m - first) : GROUP;
-        tm = first + (L % width) % gsz;
-        tn = (L % width) / gsz;
-    }
-    const int i0 = tm * BM, j0 = tn * BN;
-    const int KC = Ttot / 32;                     // 32-token chunks per row of the blocked operands
-
-    // ---- wave-uniform sources of the DMA loads (tile 0 of the k loop) and per-lane offsets.  Rows past the
-    //      matrix edge are clamped into it: they only feed outputs that are never stored. ------------------
-    uint64_t a_base[A_LD][2], b_base[B_LD], c_base;
-    const int rb = lane >> 2;
-    const uint32_t blk_lane = (uint32_t)(rb * 32 + ((lane & 3) ^ ((rb >> 2) & 3)) * 8) * 2;   // chunk swizzle, see gemm_v2.hip
-    {
-#pragma unroll
-        for (int n = 0; n < A_LD; ++n) {
-            int cr = i0 / 2 + (wt * A_LD + n) * 16; cr = cr < F / 2 ? cr : F / 2 - 16;
-#pragma unroll
-            for (int kc = 0; kc < 2; ++kc) a_base[n][kc] = uniform64(atc + (((int64_t)(cr >> 4) * KC + k_base / 32 + kc) << 9));
-        }
-#pragma unroll
-        for (int n = 0; n < B_LD; ++n) {
-            const int bk = wt * B_LD + n, h = bk / (BN / 16);
-            int gr = j0 + (bk % (BN / 16)) * 16; gr = gr < N ? gr : N - 16;
-            b_base[n] = uniform64(G + (((int64_t)(gr >> 4) * KC + k_base / 32 + h) << 9));
-        }
-        c_base = uniform64(kmask + (int64_t)(k_base / 64) * (F / 8));
-    }
-    // mask bytes of the tile's 32 groups of 8 hidden units (lanes 0-7 bring 4 each, the others repeat them); every
-    // wavefront fetches its own copy
-    uint32_t c_lane;
-    {
-        int g = i0 / 8 + 4 * (lane & 7); g = g < F / 8 ? g : F / 8 - 4;
-        c_lane = (uint32_t)g;
-    }
-    const uint32_t c_kstep = (uint32_t)(F / 8);
-
-    auto issue_half = [&](int kt, int stage, int h) {
-        unsigned char* sa = ring + stage * kStage;
-        unsigned char* sb = sa + kABytes;
-        unsigned char* sc = sb + kBBytes;
-        const uint32_t o = blk_lane + (uint32_t)kt * 2048;      // k position in the per-lane offset; bases stay in SGPRs
-        if (h == 0) {
-            dma4(c_base, c_lane + (uint32_t)kt * c_kstep, sc + wt * 256);     // first: the look-up wants it earliest
-#pragma unroll
-            for (int n = 0; n < A_LD; ++n) {
-                dma16(a_base[n][0], o, sa + (wt * A_LD + n) * 1024);
-                dma16(a_base[n][1], o, sa + kAHalf + (wt * A_LD + n) * 1024);
-            }
-#pragma unroll
-            for (int n = 0; n < B_LD / 2; ++n) dma16(b_base[n], o, sb + (wt * B_LD + n) * 1024);
-        } else {
-#pragma unroll
-            for (int n = B_LD / 2; n < B_LD; ++n) dma16(b_base[n], o, sb + (wt * B_LD + n) * 1024);
-        }
-    };
-
-    // ---- fragment reads.  Sub-step s (16 tokens) of a stage lives in half s / 2 at chunk pair s % 2. ----
-    int b_off[FN];
-#pragma unroll
-    for (int b = 0; b < FN; ++b) {
-        const int row = wn * WN + b * 32 + l32;
-        b_off[b] = kABytes + row * 64 + ((lh ^ ((row >> 2) & 3)) << 4);
-    }
-    // hidden unit of fragment a in this lane: f = i0 + wm * WM + a * 32 + l32 -> group wm * WM / 8 + a * 4 + l32 / 8 of the tile,
-    // column l32 % 8 of the group.  a_off[a] = its row in a half-tile (or the zero row), set per stage by lookup().
-    // a_off[a][0 / 1] = LDS address of its row (or of the zero row) for the even / odd 16-token sub-steps of a half-tile
-    int a_off[FM][2], a_next[FM][2];
-    const uint32_t col = l32 & 7, below = (1u << col) - 1u;
-    // the zero row is read at the chunk pair the lanes of the same 16-lane phase do not use for kept rows (no bank conflict)
-    const int zero_row = TL::kZero + ((lh ^ (l32 >> 3) ^ 2) << 4);
-    uint32_t mk[FM];
-    auto lookup_read = [&](int stage) {
-        const unsigned char* sc = ring + stage * kStage + kABytes + kBBytes + wt * 256;
-#pragma unroll
-        for (int a = 0; a < FM; ++a) mk[a] = sc[wm * (WM / 8) + a * 4 + (l32 >> 3)];
-    };
-    auto lookup = [&](int stage) {
-        const int sa = stage * kStage;
-#pragma unroll
-        for (int a = 0; a < FM; ++a) {
-            const int gl = wm * (WM / 8) + a * 4 + (l32 >> 3);
-            const int row = gl * 4 + __builtin_popcount(mk[a] & below);                   // (row >> 2) & 3 == l32 >> 3
-            const int off = ((mk[a] >> col) & 1u) ? row * 64 + ((lh ^ (l32 >> 3)) << 4) : zero_row;
-            a_next[a][0] = sa + off;
-            a_next[a][1] = sa + (off ^ 32);
-        }
-    };
-    struct FragSet { Frag8 a[FM]; Frag8 b[FN]; };
-    auto read_a = [&](FragSet& f, const unsigned char* st, int s, int a) {
-        (void)st;
-        f.a[a].u = *reinterpret_cast<const uint4*>(ring + a_off[a][s & 1] + (s >> 1) * kAHalf);
-    };
-    auto read_b = [&](FragSet& f, const unsigned char* st, int s, int b) {
-        f.b[b].u = *reinterpret_cast<const uint4*>(st + (s >> 1) * kBHalf + (b_off[b] ^ (32 * (s & 1))));
-    };
-
-    f32x16 acc[FM][FN];
-#pragma unroll
-    for (int a = 0; a < FM; ++a)
-#pragma unroll
-        for (int b = 0; b < FN; ++b)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) acc[a][b][r] = 0.0f;
-    auto mma_row = [&](const FragSet& f, int a) {
-#pragma unroll
-        for (int b = 0; b < FN; ++b) acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.a[a].v, f.b[b].v, acc[a][b], 0, 0, 0);
-    };
-#define SB() __builtin_amdgcn_sched_barrier(0)
-
-    // token blocks of this wavefront: all of them, or (KW > 1) every KW-th one from its own on.  0 for an expert without tokens: its gradient is zero
-    const int nk = KW == 1 ? K / 64 : (K / 64 - kg + KW - 1) / KW;
-    auto step_of = [&](int kt) { return KW == 1 ? kt : kg + kt * KW; };
-    if (nk > 0) {
-        // rows of zeros behind both half-tiles of every stage (never touched by the DMA)
-        for (int i = wt * 64 + lane; i < kStages * 2 * 16; i += TL::NW * 64)
-            *reinterpret_cast<uint32_t*>(ring + (i >> 5) * kStage + ((i >> 4) & 1) * kAHalf + TL::kZero + (i & 15) * 4) = 0u;
-#pragma unroll
-        for (int p = 0; p < kStages; ++p) { issue_half(step_of(p < nk ? p : nk - 1), p, 0); issue_half(step_of(p < nk ? p : nk - 1), p, 1); }
-        wait_vmcnt<(kStages - 1) * kLoads>();
-        if (KW == 1) __syncthreads();
-        else { wave_lds_sync(); asm volatile("" ::: "memory"); }
-        FragSet P, Q;
-        lookup_read(0);
-        lookup(0);
-#pragma unroll
-        for (int a = 0; a < FM; ++a) { a_off[a][0] = a_next[a][0]; a_off[a][1] = a_next[a][1]; read_a(P, ring, 0, a); }
-#pragma unroll
-        for (int b = 0; b < FN; ++b) read_b(P, ring, 0, b);
-        int stage = 0;
-        // the matrix instructions of sub-step set C with the reads of the next sub-step s (into set R) in between
-        auto sub_step = [&](const FragSet& C, FragSet& R, const unsigned char* st, int s, auto mid, auto late) {
-            mma_row(C, 0); SB();
-            read_a(R, st, s, 0); read_a(R, st, s, 1); read_b(R, st, s, 0); if (FM == 2) read_b(R, st, s, 1); SB();
-            mma_row(C, 1); SB();
-            if (FM == 4) { read_a(R, st, s, FM - 2); read_a(R, st, s, FM - 1); read_b(R, st, s, 1); SB(); }
-            mid(); SB();
-            if (FM == 4) { mma_row(C, FM - 2); SB(); }
-            late(); SB();
-            if (FM == 4) { mma_row(C, FM - 1); SB(); }
-        };
-        // One step = one stage = four sub-steps of FM x FN matrix instructions; the fragments of a sub-step are read
-        // while the matrix cores work on the one before.  Before the last sub-step every wavefront has read all of
-        // the stage (barrier), which is then refilled with the tile three steps ahead while the next stage's rows
-        // are looked up and its first fragments fetched.
-        for (int kt = 0; kt < nk; ++kt) {
-            const int nxt = step_of((kt + kStages < nk) ? kt + kStages : nk - 1);
-            const int next_stage = (stage + 1 == kStages) ? 0 : stage + 1;
-            const unsigned char* st = ring + stage * kStage;
-            const unsigned char* sn = ring + next_stage * kStage;
-            sub_step(P, Q, st, 1, [&] {}, [&] {});
-            sub_step(Q, P, st, 2, [&] {
-                // the next tile's mask bytes were the first load of its batch: all but kLoads - 1 of that batch and
-                // the batch after it may still be in flight
-                wait_vmcnt<(kStages - 2) * kLoads + kLoads - 1>();
-                if (KW > 1) asm volatile("" ::: "memory");
-                lookup_read(next_stage);
-            }, [&] {});
-            sub_step(P, Q, st, 3, [&] { lookup(next_stage); }, [&] {});
-            wait_vmcnt_lgkm0<(kStages - 2) * kLoads>();      // Q is here, tile kt + 1 has landed (this wavefront's part)
-            if (KW == 1) __builtin_amdgcn_s_barrier();
-            else asm volatile("" ::: "memory");
-            SB();
-#pragma unroll
-            for (int a = 0; a < FM; ++a) { a_off[a][0] = a_next[a][0]; a_off[a][1] = a_next[a][1]; }
-            sub_step(Q, P, sn, 0, [&] { issue_half(nxt, stage, 0); }, [&] { issue_half(nxt, stage, 1); });
-            stage = next_stage;
-        }
-        wait_vmcnt<0>();
-    }
-#undef SB
-    __syncthreads();
-    if (KW > 1 && !wgrad_join<TL>(acc, smem, kg, lane)) return;
-
-    wgrad_store<OUT_I_CONTIG, ACC32, TL>(acc, 1.0f, smem, wt, lane, i0, j0, F, N, out, ldo);
-}
-
-// The same contraction on E4M3 codes (the fp8 step with SFFN_FLAG_FP8_WGRAD): atc and G hold one code per element, in the blocked layout
-// with a pair of codes per 2-byte element, so one 64-byte chunk of a row is exactly one 64-token block.  v_mfma_scale_f32_32x32x64_f8f6f4 with
-// unit scales contracts one such block per instruction (measured: lane l supplies k 32 (l / 32) .. + 31 of row / column l % 32 in both
-// operands; 2x the bf16 rate).  A stage of the ring is therefore ONE token block: compact A 8 KB + a row of zeros, G 16 KB, 8 private copies
-// of the block's 32 mask bytes; 5 stages; per stage four rows of two matrix instructions, the A fragments read one row ahead, the G
-// fragments one stage ahead.  out = bf16(alpha * sum), alpha = product of the two tensor scales.
-template <bool OUT_I_CONTIG, bool ACC32, class TL>
-__global__ void __launch_bounds__(TL::THREADS, (TL::KW > 1 || TL::NW < 4) ? 1 : 2) wgrad_vnm_fp8_kernel(const uint16_t* __restrict__ atc, const uint8_t* __restrict__ kmask,
-                                                           const uint16_t* __restrict__ G, int F, int N, int Ttot, float alpha,
-                                                           uint16_t* __restrict__ out, int64_t ldo, int tiles_m, int tiles_n, GemmGroup grp) {
-    constexpr int BM = TL::BM, BN = TL::BN, WM = TL::WM, WN = 64, FM = TL::FM, FN = TL::FN, KW = TL::KW;
-    constexpr int kStages = TL::NST, kStage = TL::k8Stage, k8A = TL::k8A, k8B = TL::k8B, kLoads = TL::k8Loads, A_LD = TL::A_LD, B_LD = TL::B8_LD;
-    __shared__ __attribute__((aligned(1024))) unsigned char smem[TL::BYTES8];
-
-    const int tid = threadIdx.x, lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int kg = KW > 1 ? wave : 0, wt = KW > 1 ? 0 : wave;       // share of the contraction / place in the tile
-    const int wm = wt / TL::WVN, wn = wt % TL::WVN;
-    const int l32 = lane & 31, lh = lane >> 5;
-    unsigned char* const ring = smem + kg * (kStages * kStage);
-    int L;
-    {
-        const int n = gridDim.x, pid = blockIdx.x, per = n >> 3;
-        L = (pid < per * 8) ? (pid & 7) * per + (pid >> 3) : pid;
-    }
-    int k_base = 0, K = Ttot;                     // grouped: every expert contracts over its own token segment
-    if (grp.n) {
-        const int per = tiles_m * tiles_n, e = L / per;
-        L -= e * per;
-        k_base = grp.seg[e];
-        K = grp.seg[e + 1] - k_base;
-        out += e * grp.out_stride * (ACC32 ? 2 : 1);          // (float32 elements are two uint16_t wide)
-    }
-    int tm, tn;
-    {
-        constexpr int GROUP = SFFN_TILE_GROUP;
-        const int width = GROUP * tiles_n, group = L / width, first = group * GROUP;
-        const int gsz = (tiles_m - first) < GROUP ? (tiles_m - first) : GROUP;
-        tm = first + (L % width) % gsz;
-        tn = (L % width) / gsz;
-    }
-    const int i0 = tm * BM, j0 = tn * BN;
-    const int KC = Ttot / 64;                     // 64-token chunks (64 bytes) per row of the blocked operands
-
-    uint64_t a_base[A_LD], b_base[B_LD], c_base;
-    const int rb = lane >> 2;
-    const uint32_t blk_lane = (uint32_t)(rb * 32 + ((lane & 3) ^ ((rb >> 2) & 3)) * 8) * 2;   // chunk swizzle, as in the bf16 kernel
-    {
-#pragma unroll
-        for (int n = 0; n < A_LD; ++n) {
-            int cr = i0 / 2 + (wt * A_LD + n) * 16; cr = cr < F / 2 ? cr : F / 2 - 16;
-            a_base[n] = uniform64(atc + (((int64_t)(cr >> 4) * KC + k_base / 64) << 9));
-        }
-#pragma unroll
-        for (int n = 0; n < B_LD; ++n) {
-            int gr = j0 + (wt * B_LD + n) * 16; gr = gr < N ? gr : N - 16;
-            b_base[n] = uniform64(G + (((int64_t)(gr >> 4) * KC + k_base / 64) << 9));
-        }
-        c_base = uniform64(kmask + (int64_t)(k_base / 64) * (F / 8));
-    }
-    uint32_t c_lane;
-    {
-        int g = i0 / 8 + 4 * (lane & 7); g = g < F / 8 ? g : F / 8 - 4;
-        c_lane = (uint32_t)g;
-    }
-    const uint32_t c_kstep = (uint32_t)(F / 8);
-    auto issue = [&](int kt, int stage) {
-        unsigned char* sa = ring + stage * kStage;
-        const uint32_t o = blk_lane + (uint32_t)kt * 1024;
-        dma4(c_base, c_lane + (uint32_t)kt * c_kstep, sa + k8A + k8B + wt * 256);     // first: the look-up wants it earliest
-#pragma unroll
-        for (int n = 0; n < A_LD; ++n) dma16(a_base[n], o, sa + (wt * A_LD + n) * 1024);
-#pragma unroll
-        for (int n = 0; n < B_LD; ++n) dma16(b_base[n], o, sa + k8A + (wt * B_LD + n) * 1024);
-    };
-
-    // fragment reads: a lane wants the 32 bytes k 32 lh .. + 31 of its row = 16-byte chunks 2 lh, 2 lh + 1 (slot = chunk ^ ((row >> 2) & 3))
-    int b_off[FN];
-#pragma unroll
-    for (int b = 0; b < FN; ++b) {
-        const int row = wn * WN + b * 32 + l32;
-        b_off[b] = k8A + row * 64 + (((2 * lh) ^ ((row >> 2) & 3)) << 4);
-    }
-    int a_off[FM], a_next[FM];
-    const uint32_t col = l32 & 7, below = (1u << col) - 1u;
-    const int zero_row = TL::kZero + (((2 * lh) ^ (l32 >> 3) ^ 2) << 4);
-    uint32_t mk[FM];
-    auto lookup_read = [&](int stage) {
-        const unsigned char* sc = ring + stage * kStage + k8A + k8B + wt * 256;
-#pragma unroll
-        for (int a = 0; a < FM; ++a) mk[a] = sc[wm * (WM / 8) + a * 4 + (l32 >> 3)];
-    };
-    auto lookup = [&](int stage) {
-        const int sa = stage * kStage;
-#pragma unroll
-        for (int a = 0; a < FM; ++a) {
-            const int gl = wm * (WM / 8) + a * 4 + (l32 >> 3);
-            const int row = gl * 4 + __builtin_popcount(mk[a] & below);                   // (row >> 2) & 3 == l32 >> 3
-            a_next[a] = sa + (((mk[a] >> col) & 1u) ? row * 64 + (((2 * lh) ^ (l32 >> 3)) << 4) : zero_row);
-        }
-    };
-    auto read_a = [&](Frag16& f, int off) {
-        f.u[0] = *reinterpret_cast<const uint4*>(ring + off);
-        f.u[1] = *reinterpret_cast<const uint4*>(ring + (off ^ 16));
-    };
-    auto read_b = [&](Frag16& f, const unsigned char* st, int b) {
-        f.u[0] = *reinterpret_cast<const uint4*>(st + b_off[b]);
-        f.u[1] = *reinterpret_cast<const uint4*>(st + (b_off[b] ^ 16));
-    };
-    f32x16 acc[FM][FN];
-#pragma unroll
-    for (int a = 0; a < FM; ++a)
-#pragma unroll
-        for (int b = 0; b < FN; ++b)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) acc[a][b][r] = 0.0f;
-    auto mma_row = [&](const Frag16& fa, const Frag16 (&fb)[FN], int a) {
-#pragma unroll
-        for (int b = 0; b < FN; ++b)
-            acc[a][b] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(fa.q, fb[b].q, acc[a][b], 0, 0, 0, 0x7F, 0, 0x7F);   // fp8 x fp8, scales 2^0
-    };
-#define SB() __builtin_amdgcn_sched_barrier(0)
-    const int nk = KW == 1 ? K / 64 : (K / 64 - kg + KW - 1) / KW;                // 0 for an expert without tokens: its gradient is zero
-    auto step_of = [&](int kt) { return KW == 1 ? kt : kg + kt * KW; };
-    if (nk > 0) {
-        for (int i = wt * 64 + lane; i < kStages * 16; i += TL::NW * 64) *reinterpret_cast<uint32_t*>(ring + (i >> 4) * kStage + TL::kZero + (i & 15) * 4) = 0u;   // the rows of zeros
-#pragma unroll
-        for (int p = 0; p < kStages; ++p) issue(step_of(p < nk ? p : nk - 1), p);
-        wait_vmcnt<(kStages - 1) * kLoads>();
-        if (KW == 1) __syncthreads();
-        else { wave_lds_sync(); asm volatile("" ::: "memory"); }
-        Frag16 A0, A1, B0[FN], B1[FN];
-        lookup_read(0);
-        lookup(0);
-#pragma unroll
-        for (int a = 0; a < FM; ++a) a_off[a] = a_next[a];
-        read_a(A0, a_off[0]);
-#pragma unroll
-        for (int b = 0; b < FN; ++b) read_b(B0[b], ring, b);
-        int stage = 0;
-        // One step = one token block; two steps per loop trip so that the two G fragment sets alternate by name.
-        auto step = [&](int kt, Frag16 (&Bc)[FN], Frag16 (&Bn)[FN]) {
-            const int nxt = step_of((kt + kStages < nk) ? kt + kStages : nk - 1);
-            const int next_stage = (stage + 1 == kStages) ? 0 : stage + 1;
-            const unsigned char* sn = ring + next_stage * kStage;
-            read_a(A1, a_off[1]); SB();
-            if (FM == 4) {
-                mma_row(A0, Bc, 0); SB();
-                read_a(A0, a_off[FM - 2]); SB();
-                mma_row(A1, Bc, 1); SB();
-                read_a(A1, a_off[FM - 1]); SB();
-            }
-            // the next block's mask bytes were the first load of its batch
-            wait_vmcnt<(kStages - 2) * kLoads + kLoads - 1>();
-            if (KW > 1) asm volatile("" ::: "memory");
-            lookup_read(next_stage); SB();
-            mma_row(A0, Bc, FM - 2); SB();
-            wait_vmcnt_lgkm0<(kStages - 2) * kLoads>();      // my reads of this stage are done, block kt + 1 has landed (this wavefront's part)
-            if (KW == 1) __builtin_amdgcn_s_barrier();
-            else asm volatile("" ::: "memory");
-            SB();
-            issue(nxt, stage); SB();
-            lookup(next_stage); SB();
-#pragma unroll
-            for (int a = 0; a < FM; ++a) a_off[a] = a_next[a];
-            read_a(A0, a_off[0]);
-#pragma unroll
-            for (int b = 0; b < FN; ++b) read_b(Bn[b], sn, b);
-            SB();
-            mma_row(A1, Bc, FM - 1); SB();
-            stage = next_stage;
-        };
-        int kt = 0;
-        for (; kt + 1 < nk; kt += 2) { step(kt, B0, B1); step(kt + 1, B1, B0); }
-        if (kt < nk) step(kt, B0, B1);
-        wait_vmcnt<0>();
-    }
-#undef SB
-    __syncthreads();
-    if (KW > 1 && !wgrad_join<TL>(acc, smem, kg, lane)) return;
-    wgrad_store<OUT_I_CONTIG, ACC32, TL>(acc, alpha, smem, wt, lane, i0, j0, F, N, out, ldo);
-}
-
-template <bool FP8, bool OUT_I_CONTIG, bool ACC32, class TL>
-static hipError_t launch_tile(const uint16_t* a, const uint8_t* kmask, const uint16_t* G, float alpha, int64_t F, int64_t N, int64_t T, uint16_t* out,
-                              int64_t ldo, hipStream_t s, const GemmGroup& g) {
-    const int tiles_m = (int)((F + TL::BM - 1) / TL::BM), tiles_n = (int)((N + TL::BN - 1) / TL::BN);
-    const dim3 grid((unsigned)(tiles_m * tiles_n * (g.n ? g.n : 1)));
-    if constexpr (FP8)
-        hipLaunchKernelGGL((wgrad_vnm_fp8_kernel<OUT_I_CONTIG, ACC32, TL>), grid, dim3(TL::THREADS), 0, s, a, kmask, G, (int)F, (int)N, (int)T, alpha, out, ldo, tiles_m, tiles_n, g);
-    else
-        hipLaunchKernelGGL((wgrad_vnm_kernel<OUT_I_CONTIG, ACC32, TL>), grid, dim3(TL::THREADS), 0, s, a, kmask, G, (int)F, (int)N, (int)T, out, ldo, tiles_m, tiles_n, g);
-    return hipGetLastError();
-}
 template <bool FP8, bool OUT_I_CONTIG, bool ACC32>
-static hipError_t launch_sized(const uint16_t* a, const uint8_t* kmask, const uint16_t* G, float alpha, int64_t F, int64_t N, int64_t T, uint16_t* out,
-                               int64_t ldo, hipStream_t s, const GemmGroup* grp, bool split_ok) {
-    const GemmGroup g = grp ? *grp : GemmGroup();
-    if (T % 64 != 0 || T <= 0 || (g.n && (g.n > GemmGroup::kMaxExperts || g.role != 2))) return hipErrorInvalidValue;
-    const unsigned e = g.n ? (unsigned)g.n : 1u;
-    auto tiles = [&](int64_t edge) { return (unsigned)((F + edge - 1) / edge * ((N + edge - 1) / edge)) * e; };
-    // F = 8192, N = 2048, T = 2048 (256 / 1024 tiles): 55 us on 256 tiles, 60 on 128; F = 4096, N = 1024, T = 8192 (64 / 256 / 1024): 145, 65, and 91 on 64
-    // tiles; F = 1024, N = 256, T = 16384 (4 / 16 / 64): 277, 109, 39
-    switch (pick_tile(tiles(256), tiles(128), tiles(64), (int)(T / 64 / e), 0.56f, split_ok ? 256 : 0, 12)) {
-        case 256: return launch_tile<FP8, OUT_I_CONTIG, ACC32, WTile<2, 4, 128, FP8 ? 5 : 3, 1>>(a, kmask, G, alpha, F, N, T, out, ldo, s, g);
-        case 128: return launch_tile<FP8, OUT_I_CONTIG, ACC32, WTile<2, 2, 64, FP8 ? 5 : 3, 1>>(a, kmask, G, alpha, F, N, T, out, ldo, s, g);
-        default:  return launch_tile<FP8, OUT_I_CONTIG, ACC32, WTile<1, 1, 64, 3, 4>>(a, kmask, G, alpha, F, N, T, out, ldo, s, g);
-    }
+static hipError_t launch_sized(const WgradArgs& a, hipStream_t s, int tile) {
+    if (tile == 256) return launch_units<WgradUnit256<FP8, OUT_I_CONTIG, ACC32>>(s, a);
+    if (tile == 128) return launch_units<WgradUnit128<FP8, OUT_I_CONTIG, ACC32>>(s, a);
+    return launch_units<WgradUnit64<FP8, OUT_I_CONTIG, ACC32>>(s, a);
+}
+template <bool FP8>
+static hipError_t launch_impl(WgradArgs a, int out_i_contig, hipStream_t s, const GemmGroup* grp, bool acc32, bool split_ok, int tile) {
+    a.grp = grp ? *grp : GemmGroup();
+    if (a.T % 64 != 0 || a.T <= 0 || (a.grp.n && (a.grp.n > GemmGroup::kMaxExperts || a.grp.role != 2))) return hipErrorInvalidValue;
+    if (!tile) tile = pick_wgrad_tile(a.F, a.N, a.T, a.grp.n, split_ok);
+    if (out_i_contig) return acc32 ? launch_sized<FP8, true, true>(a, s, tile) : launch_sized<FP8, true, false>(a, s, tile);
+    return acc32 ? launch_sized<FP8, false, true>(a, s, tile) : launch_sized<FP8, false, false>(a, s, tile);
 }
 
 hipError_t launch_wgrad_vnm_fp8(const uint8_t* atc, const uint8_t* kmask, const uint8_t* Gq, float alpha, int64_t F, int64_t N, int64_t T,
-                                int out_i_contig, uint16_t* out, int64_t ldo, hipStream_t s, const GemmGroup* grp, bool acc32, bool split_ok) {
-    const uint16_t* a = reinterpret_cast<const uint16_t*>(atc);
-    const uint16_t* g = reinterpret_cast<const uint16_t*>(Gq);
-    if (out_i_contig) return acc32 ? launch_sized<true, true, true>(a, kmask, g, alpha, F, N, T, out, ldo, s, grp, split_ok) : launch_sized<true, true, false>(a, kmask, g, alpha, F, N, T, out, ldo, s, grp, split_ok);
-    return acc32 ? launch_sized<true, false, true>(a, kmask, g, alpha, F, N, T, out, ldo, s, grp, split_ok) : launch_sized<true, false, false>(a, kmask, g, alpha, F, N, T, out, ldo, s, grp, split_ok);
+                                int out_i_contig, uint16_t* out, int64_t ldo, hipStream_t s, const GemmGroup* grp, bool acc32, bool split_ok, int tile) {
+    return launch_impl<true>({reinterpret_cast<const uint16_t*>(atc), kmask, reinterpret_cast<const uint16_t*>(Gq), alpha, (int)F, (int)N, (int)T, out, ldo, 0, 0, GemmGroup()},
+                             out_i_contig, s, grp, acc32, split_ok, tile);
 }
 
 hipError_t launch_wgrad_vnm(const uint16_t* atc, const uint8_t* kmask, const uint16_t* G, int64_t F, int64_t N, int64_t T,
-                            int out_i_contig, uint16_t* out, int64_t ldo, hipStream_t s, const GemmGroup* grp, bool acc32, bool split_ok) {
-    if (out_i_contig) return acc32 ? launch_sized<false, true, true>(atc, kmask, G, 1.0f, F, N, T, out, ldo, s, grp, split_ok) : launch_sized<false, true, false>(atc, kmask, G, 1.0f, F, N, T, out, ldo, s, grp, split_ok);
-    return acc32 ? launch_sized<false, false, true>(atc, kmask, G, 1.0f, F, N, T, out, ldo, s, grp, split_ok) : launch_sized<false, false, false>(atc, kmask, G, 1.0f, F, N, T, out, ldo, s, grp, split_ok);
+                            int out_i_contig, uint16_t* out, int64_t ldo, hipStream_t s, const GemmGroup* grp, bool acc32, bool split_ok, int tile) {
+    return launch_impl<false>({atc, kmask, G, 1.0f, (int)F, (int)N, (int)T, out, ldo, 0, 0, GemmGroup()}, out_i_contig, s, grp, acc32, split_ok, tile);
 }
 
 }  // namespace sffn

@@ -73,14 +73,86 @@ struct GemmGroup {
     int32_t seg[kMaxExperts + 1] = {0};
 };
 
+// arguments of the tile kernels' units (gemm_*_body.hpp; tiles_m / tiles_n are filled in at the launch)
+struct GemmV2Args {
+    const uint16_t* a_vals; const uint8_t* a_meta; const uint16_t* B; const float* bias;
+    int Ra, Rb, K; uint16_t* out; int64_t ldo; int tiles_m, tiles_n; VnmEpilogue ep; GemmGroup grp; float alpha;
+};
+struct Vnm8Args {
+    const uint16_t* vcb; const uint8_t* mcb; const uint8_t* cixt; const uint8_t* Wk; int ldw, T, N, F; uint16_t* out; int64_t ldo; int tiles_m, tiles_n;
+    GemmGroup grp; float alpha;
+};
+struct GatherArgs {
+    const void* a_vals; const uint8_t* a_meta; const uint8_t* colidx; const void* Wk; int ldw, T, N, Kc, logM, tiles_n; float alpha; uint16_t* out; int64_t ldo; GemmGroup grp;
+};
+struct WgradArgs {
+    const uint16_t* atc; const uint8_t* kmask; const uint16_t* G; float alpha; int F, N, T; uint16_t* out; int64_t ldo; int tiles_m, tiles_n; GemmGroup grp;
+};
+
+// Tiles of a step's contractions: g = eqs. (1), (4), v = eqs. (3), (7), w = eqs. (5), (8).  mix: none of them wants the 256 tile (the outputs do not fill
+// the chip), so that the contractions that do not depend on each other share launches (step_mix_*.hip): eqs. (3), (5), (4) in one and eqs. (7), (8) in
+// another (a backward call: eqs. (5), (4), then (7), (8)).  Eq. (4) then takes the 128 tile and its results need operand buffers of their own, since
+// eqs. (3), (5) still read those of eq. (1).
+struct StepTiles { int g = 0, g_bwd = 0, v = 0, w = 0; bool mix = false; };
+inline StepTiles step_tiles(int64_t T, int64_t D, int64_t F, int M, int experts, bool fp8);
+enum { kMixForwardTail = 0, kMixBackwardHead = 1, kMixBackwardTail = 2 };      // {(3), (5), (4)}, {(5), (4)}, {(7), (8)}
+// M = 8: v8 (else null: va); acc32: not with kMixForwardTail
+hipError_t launch_step_mix_bf16(int what, int logM, const StepTiles& t, bool acc32, const Vnm8Args* v8, const GatherArgs* va, const GemmV2Args* g, const WgradArgs& w, hipStream_t s);
+hipError_t launch_step_mix_fp8(int what, int logM, const StepTiles& t, const Vnm8Args* v8, const GatherArgs* va, const GemmV2Args* g, const WgradArgs& w, hipStream_t s);
+
+// The passes that only depend on the step's inputs, in one launch (prologue.hip): the blocked copies of X and dY and their transposes, the pruning of W1
+// and W2.  Absent parts: null X / dY / W1 / W2.  experts: W1, W2 are stacks of that many matrices.
+struct PrologueArgs {
+    int T, D, F, experts, mode;
+    const uint16_t *X, *dY; uint16_t *xt, *xb, *dyt, *dyb;
+    const uint16_t* W1; uint16_t *w1v, *w1vb; uint8_t *w1m, *w1mb;
+    const uint16_t* W2; uint16_t *w2v, *w2vb, *w2t; uint8_t *w2m, *w2mb;
+};
+hipError_t launch_step_prologue(const PrologueArgs& a, hipStream_t s);
+
 // Edge of the square output tile of a contraction with n256 / n128 / n64 tiles of each size and `steps` trips of its main loop.  A round = one tile on
 // every slot of the chip: 256 tiles of 256 x 256 (one workgroup per CU), 512 of 128 x 128 (two per CU).  A round of small tiles takes `w128` of a round of
-// large ones (measured, see the callers: more bytes from L2 per product), so the large tile wins on whole rounds and the small one where the
+// large ones (measured, see below: more bytes from L2 per product), so the large tile wins on whole rounds and the small one where the
 // outputs do not fill the chip or leave the last round nearly empty.  64 x 64 tiles split the contraction over their four wavefronts: best
 // while there are at most `most64` of them and the contraction is long enough to be worth splitting.
 inline int pick_tile(unsigned n256, unsigned n128, unsigned n64, int steps, float w128, unsigned most64, int least_steps) {
     if (n64 <= most64 && steps >= least_steps) return 64;
     return w128 * (float)((n128 + 511) / 512) < (float)((n256 + 255) / 256) ? 128 : 256;
+}
+
+// gemm_v2 (i x j outputs; grouped over tokens: counted as if ungrouped, so that a host and a device segment table choose alike).
+// Eq. (1) / (4) at T = D = 2048, F = 8192 (256 / 1024 tiles): 55 / 47 us on 256 tiles, 61 / 54 on 128; T = 1024, D = 1408, F = 4928 (80 / 312): 39 / 30 and
+// 26 / 23; T = 64, D = 2048, F = 8192 (32 / 64 / 128): 43 / 33, 21 / 18, and 17 / 14 on 64 tiles
+inline int pick_gemm_tile(int64_t Ra, int64_t Rb, int steps, const GemmGroup& g, float w128, bool split) {
+    auto tiles = [&](int64_t edge) { return (unsigned)((Ra + edge - 1) / edge * ((Rb + edge - 1) / edge)) * (g.role == 2 && g.n ? (unsigned)g.n : 1u); };
+    return pick_tile(tiles(256), tiles(128), tiles(64), steps, w128, split ? 256 : 0, 16);
+}
+// V:2:8 activation GEMM.  T = 8192, N = 2048, F = 8192 (256 / 1024 tiles): 107 us on 256 tiles, 148 on 128; T = 2048 (64 / 256): 85 and 54; T = 1024,
+// N = 1408, F = 4928 (24 / 88 / 352): 55, 33, and 29 on 64 tiles; T = 64, N = 2048, F = 8192 (8 / 16 / 32): 83, 49, 28
+inline int pick_vnm8_tile(int64_t T, int64_t N, int steps) {
+    auto tiles = [&](int64_t edge) { return (unsigned)((T + edge - 1) / edge * ((N + edge - 1) / edge)); };
+    return pick_tile(tiles(256), tiles(128), tiles(64), steps, 0.72f, 512, 8);
+}
+// gathered-row activation GEMM: 64 tokens x 256 columns, or 64 x 64
+// (T = 256, N = 1024, F = 4096, M = 16: 19 us and 12 us; T = N = 1024: 20 and 12; T = 512, N = 4096, F = 16384: 90 and 67; T = 1984, N = 1344, M = 32: 14 and 23)
+inline int pick_gather_tile(int64_t T, int64_t N, int steps) { return (T / 64) * ((N + 63) / 64) <= 512 && steps >= 6 ? 64 : 256; }
+// weight gradients.  F = 8192, N = 2048, T = 2048 (256 / 1024 tiles): 55 us on 256 tiles, 60 on 128; F = 4096, N = 1024, T = 8192 (64 / 256 / 1024): 145, 65,
+// and 91 on 64 tiles; F = 1024, N = 256, T = 16384 (4 / 16 / 64): 277, 109, 39
+inline int pick_wgrad_tile(int64_t F, int64_t N, int64_t T, int experts, bool split_ok) {
+    const unsigned e = experts ? (unsigned)experts : 1u;
+    auto tiles = [&](int64_t edge) { return (unsigned)((F + edge - 1) / edge * ((N + edge - 1) / edge)) * e; };
+    return pick_tile(tiles(256), tiles(128), tiles(64), (int)(T / 64 / e), 0.56f, split_ok ? 256 : 0, 12);
+}
+
+inline StepTiles step_tiles(int64_t T, int64_t D, int64_t F, int M, int experts, bool fp8) {
+    StepTiles t;
+    const int unit = fp8 ? 128 : 64;
+    t.g = t.g_bwd = pick_gemm_tile(F, T, (int)(D / unit), GemmGroup(), 0.56f, true);
+    t.v = M == 8 ? pick_vnm8_tile(T, D, (int)(F / unit)) : fp8 ? 256 : pick_gather_tile(T, D, (int)(4 * F / M / 64));
+    t.w = pick_wgrad_tile(F, D, T, experts > 1 ? experts : 0, M == 8 || fp8);
+    t.mix = t.g != 256 && t.w != 256 && (M != 8 || t.v != 256);
+    if (t.mix) t.g_bwd = 128;
+    return t;
 }
 
 hipError_t launch_prune24(const uint16_t* src, int64_t R, int64_t K, int64_t ld, int trans, int mode, uint16_t* vals,
@@ -114,7 +186,7 @@ hipError_t launch_vnm_spmm_gather(const uint16_t* a_vals, const uint8_t* a_meta,
 // contraction index as row; T, N, F multiples of 64.  grp as above (b_stride in elements).
 bool vnm8_gemm_ok(int64_t T, int64_t N, int64_t F, int64_t ldw);
 hipError_t launch_vnm8_gemm(const uint16_t* vcb, const uint8_t* mcb, const uint8_t* cixt, const uint16_t* Wk, int64_t ldw, int64_t T, int64_t N,
-                            int64_t F, uint16_t* out, int64_t ldo, hipStream_t s, const GemmGroup* grp = nullptr);
+                            int64_t F, uint16_t* out, int64_t ldo, hipStream_t s, const GemmGroup* grp = nullptr, int tile = 0);
 // vnm.hip: the canonical V:2:8 arrays (vals [T, F/4], meta [T, F/16], colidx [T/64, F/8, 4]) regrouped into those units
 hipError_t launch_vnm8_repack(const uint16_t* vals, const uint8_t* meta, const uint8_t* colidx, int64_t T, int64_t F, uint16_t* vcb, uint8_t* mcb,
                               uint8_t* cixt, hipStream_t s);
@@ -124,7 +196,7 @@ bool vnm8_gemm_fp8_ok(int64_t T, int64_t N, int64_t F, int64_t ldw);
 hipError_t launch_vnm8_repack_fp8(const uint8_t* codes, const uint8_t* meta, const uint8_t* colidx, int64_t T, int64_t F, uint8_t* vcb, uint8_t* mcb,
                                   uint8_t* cixt, hipStream_t s);
 hipError_t launch_vnm8_gemm_fp8(const uint8_t* vcb, const uint8_t* mcb, const uint8_t* cixt, const uint8_t* Wq, int64_t ldw, float alpha, int64_t T,
-                                int64_t N, int64_t F, uint16_t* out, int64_t ldo, hipStream_t s, const GemmGroup* grp = nullptr);
+                                int64_t N, int64_t F, uint16_t* out, int64_t ldo, hipStream_t s, const GemmGroup* grp = nullptr, int tile = 0);
 // The same on E4M3 codes: a_codes [T, 2 F / M] + the same metadata and column offsets, Wq = codes [F, ldw bytes], out = bf16(alpha * sum);
 // 4 F / M a multiple of 128; b_stride of grp in bytes.
 bool vnm_spmm_gather_fp8_ok(int64_t T, int64_t N, int64_t F, int M);
@@ -151,7 +223,7 @@ hipError_t launch_transpose(const uint16_t* in, int64_t R, int64_t C, int64_t ld
 // grp (optional, blocked launchers only): grouped form, see GemmGroup; Ra / Rb / K then count all tokens on the token axis.
 hipError_t launch_gemm_vnm_epilogue(const uint16_t* a_vals, const uint8_t* a_meta, const uint16_t* B, const float* bias, int64_t F,
                                     int64_t T, int64_t K, uint16_t* out, const VnmEpilogue& ep, hipStream_t s,
-                                    const GemmGroup* grp = nullptr);
+                                    const GemmGroup* grp = nullptr, int tile = 0);
 hipError_t launch_spmm_blocked(const uint16_t* a_vals, const uint8_t* a_meta, const uint16_t* B, const float* bias, int64_t Ra, int64_t Rb,
                                int64_t K, int out_i_contig, uint16_t* out, int64_t ldo, hipStream_t s, const GemmGroup* grp = nullptr);
 hipError_t launch_gemm_nt(int sparse_a, const uint16_t* a_vals, const uint8_t* a_meta, const uint16_t* B, const float* bias,
@@ -198,7 +270,7 @@ hipError_t launch_spmm24_fp8(const uint8_t* a_codes, const uint8_t* a_meta, cons
 // codes [Ra, K/2], a_meta in the fp8 metadata units of common.hpp, Bq = codes [Rb, K]; eq. (1) / eq. (4) with the fused V:N:M epilogue ep
 // (mode 1 or 2: M = 8; mode 5 or 6: M = 2^logM = 16, 32, 64), Ra = hidden units, Rb = tokens, out [T, F] if ep->store_dense.
 hipError_t launch_gemm_fp8_blocked(const uint8_t* a_codes, const uint8_t* a_meta, const uint8_t* Bq, const float* bias, float alpha, int64_t Ra,
-                                   int64_t Rb, int64_t K, uint16_t* out, int64_t ldo, const VnmEpilogue* ep, hipStream_t s, const GemmGroup* grp = nullptr);
+                                   int64_t Rb, int64_t K, uint16_t* out, int64_t ldo, const VnmEpilogue* ep, hipStream_t s, const GemmGroup* grp = nullptr, int tile = 0);
 // fp8.hip, producers of such operands: quantised copy in the same orientation / transposed; 2:4 pruning that also writes the blocked codes
 // (amax, optional: the tensor's amax slots, see below)
 hipError_t launch_quantize_fp8_blocked(const uint16_t* src, int64_t R, int64_t C, int64_t ld, float inv, uint8_t* out_blk, hipStream_t s, float* amax = nullptr);
@@ -216,12 +288,12 @@ hipError_t launch_prune24_fp8_step(const uint16_t* src, int64_t R, int64_t K, in
 
 // the same on E4M3 codes (atc: compact transposed codes [F / 2, T], Gq [N, T], both in the blocked pair layout): out = bf16(alpha * sum)
 hipError_t launch_wgrad_vnm_fp8(const uint8_t* atc, const uint8_t* kmask, const uint8_t* Gq, float alpha, int64_t F, int64_t N, int64_t T,
-                                int out_i_contig, uint16_t* out, int64_t ldo, hipStream_t s, const GemmGroup* grp = nullptr, bool acc32 = false, bool split_ok = true);
+                                int out_i_contig, uint16_t* out, int64_t ldo, hipStream_t s, const GemmGroup* grp = nullptr, bool acc32 = false, bool split_ok = true, int tile = 0);
 // split_ok = false: never split a tile's contraction over wavefronts (the wide blocks' fused path sums in the order of the unfused one)
 // acc32: `out` is a float32 matrix of the same shape (ldo in float32 elements; grouped form: out_stride in float32 elements) that the
 // result is added to, out32 += alpha * sum, instead of a bf16 matrix that is overwritten
 hipError_t launch_wgrad_vnm(const uint16_t* atc, const uint8_t* kmask, const uint16_t* G, int64_t F, int64_t N, int64_t T,
-                            int out_i_contig, uint16_t* out, int64_t ldo, hipStream_t s, const GemmGroup* grp = nullptr, bool acc32 = false, bool split_ok = true);
+                            int out_i_contig, uint16_t* out, int64_t ldo, hipStream_t s, const GemmGroup* grp = nullptr, bool acc32 = false, bool split_ok = true, int tile = 0);
 
 
 }  // namespace sffn

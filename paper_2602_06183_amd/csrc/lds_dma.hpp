@@ -27,6 +27,12 @@ typedef __attribute__((ext_vector_type(8))) int i32x8;
 union Frag8 { uint4 u; bf16x8 v; i32x4 q; };            // q: the same 16 bytes as 16 fp8 codes
 union Frag16 { uint4 u[2]; bf16x16 v; i32x8 q; };
 
+// operands of the transposing LDS reads (ds_read_b64_tr_b16 / _b8)
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
+typedef int v2i __attribute__((ext_vector_type(2)));
+typedef __attribute__((address_space(3))) v2i lds_v2i;
+
 typedef __attribute__((address_space(3))) void lds_void;
 typedef const __attribute__((address_space(1))) void glb_void;
 

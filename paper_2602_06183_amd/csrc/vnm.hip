@@ -3,6 +3,7 @@
 // are HBM-bound scans.  The stand-alone compressor of eq. (2) + Section 2.3 lives in vnm_general.hip, for every M.
 #include "common.hpp"
 #include "kernels.hpp"
+#include "scans.hpp"
 
 namespace sffn {
 
@@ -89,52 +90,11 @@ __global__ void __launch_bounds__(256) vnm_expand_t_kernel(const uint16_t* __res
     }
 }
 
-// out[c, r] = in[r, c]; R, C multiples of 64.
-// blocked = 1: out (the transpose) and, when given, out_same (a copy of `in`) are written in the blocked
-// operand layout instead of row-major.
 __global__ void __launch_bounds__(256) transpose_bf16_kernel(const uint16_t* __restrict__ in, int64_t R, int64_t C, int64_t ld,
                                                             uint16_t* __restrict__ out, int blocked, uint16_t* __restrict__ out_same, int map_logM,
                                                             const int32_t* __restrict__ in_perm) {
-    __shared__ __attribute__((aligned(16))) uint16_t tile[64][64 + 2];
-    const int tid = threadIdx.x;
-    const int64_t r0 = (int64_t)blockIdx.y * 64, c0 = (int64_t)blockIdx.x * 64;
-    {   // batched form: matrix blockIdx.z of a stack of [R, C] matrices (map_logM: all read the one source, see the launcher)
-        const int64_t m = (int64_t)blockIdx.z * R * C;
-        if (!map_logM) in += m;
-        if (out) out += m;
-        if (out_same) out_same += m;
-    }
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-        const int e = tid + 256 * i, rr = e >> 3, seg = e & 7;
-        int64_t rs = r0 + rr;
-        if (map_logM) rs = ((rs >> 2) << map_logM) + 4 * blockIdx.z + (rs & 3);
-        if (in_perm) rs = in_perm[rs];                       // row r of the matrix is row in_perm[r] of `in`; negative: a zero row
-        uint4 w = make_uint4(0, 0, 0, 0);
-        if (rs >= 0) w = *reinterpret_cast<const uint4*>(in + rs * ld + c0 + seg * 8);
-        uint32_t* p = reinterpret_cast<uint32_t*>(&tile[rr][seg * 8]);
-        p[0] = w.x; p[1] = w.y; p[2] = w.z; p[3] = w.w;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-        const int e = tid + 256 * i;
-        int cc, rs;                          // output row (a column of `in`) and first of 8 source rows
-        if (blocked) { const int bk = e >> 6, l = e & 63; cc = (bk >> 1) * 16 + (l >> 2); rs = (bk & 1) * 32 + (l & 3) * 8; }
-        else { cc = e >> 3; rs = (e & 7) * 8; }
-        if (out) {                           // (out = nullptr: only the blocked copy of `in` is wanted)
-            uint32_t o[4];
-#pragma unroll
-            for (int j = 0; j < 4; ++j) o[j] = tile[rs + 2 * j][cc] | ((uint32_t)tile[rs + 2 * j + 1][cc] << 16);
-            uint16_t* dst = blocked ? out + blk_off(c0 + cc, r0 + rs, R / 32) : out + (c0 + cc) * R + r0 + rs;
-            *reinterpret_cast<uint4*>(dst) = make_uint4(o[0], o[1], o[2], o[3]);
-        }
-        if (out_same) {
-            const int bk = e >> 6, l = e & 63, rr = (bk >> 1) * 16 + (l >> 2), cs = (bk & 1) * 32 + (l & 3) * 8;
-            const uint32_t* p = reinterpret_cast<const uint32_t*>(&tile[rr][cs]);
-            *reinterpret_cast<uint4*>(out_same + blk_off(r0 + rr, c0 + cs, C / 32)) = make_uint4(p[0], p[1], p[2], p[3]);
-        }
-    }
+    __shared__ __attribute__((aligned(16))) unsigned char smem[kTransposeLds];
+    transpose_bf16_body(smem, blockIdx.x, blockIdx.y, blockIdx.z, in, R, C, ld, out, blocked, out_same, map_logM, in_perm);
 }
 
 hipError_t launch_dsqrelu_vnm(const uint16_t* dy2, const uint16_t* y1, const uint8_t* meta, const uint8_t* colidx, int64_t T,
