@@ -1081,6 +1081,7 @@ static int run_step(const sffn_cfg* cfg, int n_experts, const int64_t* seg, cons
                     "ffn_sparse_step_grouped: seg_offsets must be ascending multiples of 64");
         g.n = (int)E;
         for (int e = 0; e <= E; ++e) g.seg[e] = (int32_t)seg[e];
+        refine_tiles(&tiles, D, F, cfg->M, g);
     }
 
     hipStream_t s = (hipStream_t)stream;
@@ -1115,6 +1116,10 @@ static int run_step(const sffn_cfg* cfg, int n_experts, const int64_t* seg, cons
         // pass of W2 also writes W2.T), eqs. (5), (8) on the compacted transposed activation that the epilogues write in the M = 8 format
         // (no group of 8 hidden units keeps more than 4 when a block of M >= 16 keeps 4).  10 launches.
         const int M = cfg->M, logM = M == 16 ? 4 : M == 32 ? 5 : 6;
+        // eqs. (5), (8) on the kept rows only (gemm_wgrad_wide_body.hpp), from 768 tokens per expert on: with fewer the matrix work that is
+        // saved is less than clearing a tile in LDS and reading it out again (D = 4096, F = 16384, M = 32: 82 us for 73 at 512 tokens,
+        // 94 for 94 at 768, 840 for 1390 at 16384)
+        const int kept = !tiles.mix && M >= 32 && T >= 768 * (int64_t)E;
         GemmGroup g_packed = g, g_rows = g, g_wgrad = g;
         g_packed.role = 1; g_packed.a_stride = F * D / 2; g_packed.m_stride = F * D / 8; g_packed.bias_stride = F;
         g_rows.role = 0;   g_rows.b_stride = F * D;
@@ -1126,7 +1131,7 @@ static int run_step(const sffn_cfg* cfg, int n_experts, const int64_t* seg, cons
         if (g_prof_on) { g_prof_n = 0; (void)hipEventRecord(g_prof_ev[0], s); }
         const bool lean_w = (cfg->flags & SFFN_FLAG_LEAN) != 0;        // no canonical copies of the packed weights (the packed activations stay: eqs. (3), (7) read them)
         PrologueArgs pro = {};
-        pro.T = (int)T; pro.D = (int)D; pro.F = (int)F; pro.experts = (int)E; pro.mode = cfg->mode;
+        pro.T = (int)T; pro.D = (int)D; pro.F = (int)F; pro.experts = (int)E; pro.mode = cfg->mode; pro.t_layout = kept ? 2 : 1;
         if (fwd) { pro.X = X; pro.xt = xtb; pro.xb = xb; }
         if (bwd) { pro.dY = dY; pro.dyt = dytb; pro.dyb = dyb; }
         if (fwd && !packed) {
@@ -1142,11 +1147,11 @@ static int run_step(const sffn_cfg* cfg, int n_experts, const int64_t* seg, cons
         else if (fwd) STAGE(launch_step_prologue(part[0], s), "step/X.T+prune24(W1)");
         if (fwd) {
             VnmEpilogue ep;
-            ep.mode = 5; ep.logM = logM; ep.store_dense = keep_dense; ep.vals = y2v; ep.meta = y2m; ep.colidx = cix; ep.kmask = kmask; ep.ykept = ykept; ep.at = atb;
+            ep.mode = 5; ep.logM = logM; ep.store_dense = keep_dense; ep.vals = y2v; ep.meta = y2m; ep.colidx = cix; ep.kmask = kmask; ep.ykept = ykept; ep.at = atb; ep.at_kept = kept;
             STAGE(launch_gemm_vnm_epilogue(w1vb, w1mb, xb, b1, F, T, D, y1, ep, s, gp, tiles.g), "step/y1+sqrelu_vnm_compress");         // eqs. (1), (2), Section 2.3
         }
         VnmEpilogue ep4;
-        ep4.mode = 6; ep4.logM = logM; ep4.store_dense = keep_dense; ep4.vals = dy1v; ep4.meta = y2m; ep4.colidx = cix; ep4.ykept = ykept; ep4.at = at2;
+        ep4.mode = 6; ep4.logM = logM; ep4.store_dense = keep_dense; ep4.vals = dy1v; ep4.meta = y2m; ep4.colidx = cix; ep4.ykept = ykept; ep4.at = at2; ep4.at_kept = kept;
         if (tiles.mix) {
             const GemmGroup none;
             const int Kc = (int)(4 * F / M);
@@ -1166,10 +1171,12 @@ static int run_step(const sffn_cfg* cfg, int n_experts, const int64_t* seg, cons
         if (fwd && !packed && !together) STAGE(launch_step_prologue(part[1], s), "step/prune24(W2.T)");
         if (fwd) STAGE(launch_vnm_spmm_gather(y2v, y2m, cix, w2t, D, T, D, F, M, Y3, D, s, gr), "step/y3");                              // eq. (3)
         if (bwd && !together) STAGE(launch_step_prologue(part[2], s), "step/dY.T");
-        if (bwd) STAGE(launch_wgrad_vnm(atb, kmask, dytb, F, D, T, 1, dW2, F, s, gw, acc32, false, tiles.w), "step/dW2");                       // eq. (5)
+        if (bwd && kept) STAGE(launch_wgrad_wide(atb, kmask, dytb, F, D, T, logM, 1, dW2, F, s, gw, acc32), "step/dW2");                       // eq. (5)
+        else if (bwd) STAGE(launch_wgrad_vnm(atb, kmask, dytb, F, D, T, 1, dW2, F, s, gw, acc32, false, tiles.w), "step/dW2");                       // eq. (5)
         if (bwd) STAGE(launch_gemm_vnm_epilogue(w2vb, w2mb, dyb, nullptr, F, T, D, dy2, ep4, s, gp, tiles.g_bwd), "step/dy2+dsqrelu_vnm");      // eqs. (4), (6)
         if (bwd) STAGE(launch_vnm_spmm_gather(dy1v, y2m, cix, W1, D, T, D, F, M, dX, D, s, gr), "step/dX");                              // eq. (7), dense W1 as is
-        if (bwd) STAGE(launch_wgrad_vnm(at2, kmask, xtb, F, D, T, 0, dW1, D, s, gw, acc32, false, tiles.w), "step/dW1");                        // eq. (8)
+        if (bwd && kept) STAGE(launch_wgrad_wide(at2, kmask, xtb, F, D, T, logM, 0, dW1, D, s, gw, acc32), "step/dW1");                        // eq. (8)
+        else if (bwd) STAGE(launch_wgrad_vnm(at2, kmask, xtb, F, D, T, 0, dW1, D, s, gw, acc32, false, tiles.w), "step/dW1");                        // eq. (8)
         return SFFN_OK;
     }
     if (cfg->M != 8) {
@@ -1243,7 +1250,7 @@ static int run_step(const sffn_cfg* cfg, int n_experts, const int64_t* seg, cons
     g_dense.b_stride = F * D;
     uint16_t* vcb2 = tiles.mix ? a24v + T * F / 4 : vcb;          // eq. (4)'s survivors: in the place of eq. (1)'s, or (StepTiles) in the region's second half
     PrologueArgs pro = {};
-    pro.T = (int)T; pro.D = (int)D; pro.F = (int)F; pro.experts = (int)E; pro.mode = cfg->mode;
+    pro.T = (int)T; pro.D = (int)D; pro.F = (int)F; pro.experts = (int)E; pro.mode = cfg->mode; pro.t_layout = 1;
     if (fwd) { pro.X = X; pro.xt = xtb; pro.xb = xb; }
     if (bwd) { pro.dY = dY; pro.dyt = dytb; pro.dyb = dyb; }
     if (fwd && !packed) {

@@ -92,6 +92,12 @@ __host__ __device__ __forceinline__ int64_t blk_off(int64_t r, int64_t k, int64_
 }
 // fp8 operands use the same layout with a pair of 1-byte codes in the place of a 2-byte element (a block = 16 rows x 64 codes):
 // blk_off(r, kbyte / 2, row bytes / 64) indexes 16-bit pairs.
+// A transposed operand [rows, T] in the order in which v_mfma_f32_32x32x16_bf16 takes it (gemm_wgrad_wide_body.hpp): [T / 64][rows / 32][4 steps of 16 tokens]
+// [64 lanes][8 tokens], lane = 32 (t / 8 % 2) + r % 32; element (r, t), t a multiple of 8.
+__host__ __device__ __forceinline__ int64_t lane_off(int64_t r, int64_t t, int64_t R32) {
+    return ((((t >> 6) * R32 + (r >> 5)) * 4 + ((t >> 4) & 3)) * 64 + ((t >> 3) & 1) * 32 + (r & 31)) * 8;
+}
+
 // Metadata of a 2:4 matrix, blocked for the sparse matrix instruction: one 256-byte unit per (32 rows, 64 k).
 // v_smfmac_f32_32x32x32_bf16 wants, in lane (row % 32) + 32 * h, the sixteen index bits of the row's survivors
 // in k 16h..16h+15 of a 32-k step; a unit stores, for each such lane, the two 32-k steps s = 0, 1 of its 64 k as

@@ -580,9 +580,12 @@ __device__ __forceinline__ void gemm_nt_v2_body(unsigned char* __restrict__ smem
                         cw |= (uint32_t)__builtin_ctzll(bits) << (8 * n);
                         bits &= bits - 1ull;
                     }
-                    if (valid && c < M / 8) {          // lane c of a block: its column offsets (c = 0) and the mask byte of its group c of 8 hidden units
+                    if (valid && c < (ep.at_kept ? 1 : M / 8)) {          // lane c of a block: its column offsets (c = 0) and the mask byte of its group c of 8 hidden units
                         if (c == 0) *reinterpret_cast<uint32_t*>(ep.colidx + ((int64_t)(t0 >> 6) * nblkM + blk0 + (lane >> LOGM)) * 4) = cw;
-                        ep.kmask[(int64_t)(t0 >> 6) * (F >> 3) + (f0 >> 3) + (lane >> LOGM) * (M / 8) + c] = (uint8_t)(mine >> (8 * c));
+                        if (ep.at_kept) {       // the offsets once more, grouped as gemm_wgrad_wide_body.hpp reads them
+                            const int64_t blk = blk0 + (lane >> LOGM);
+                            reinterpret_cast<uint32_t*>(ep.kmask)[((int64_t)(t0 >> 6) * (nblkM >> 3) + (blk >> 3)) * 8 + (blk & 1) * 4 + ((blk & 7) >> 1)] = cw;
+                        } else ep.kmask[(int64_t)(t0 >> 6) * (F >> 3) + (f0 >> 3) + (lane >> LOGM) * (M / 8) + c] = (uint8_t)(mine >> (8 * c));
                     }
                     cb = (uint32_t)__shfl((int)cw, b << LOGM, 64);
                     bmask = (unsigned long long)(uint32_t)__shfl((int)(uint32_t)mine, b << LOGM, 64);
@@ -647,14 +650,26 @@ __device__ __forceinline__ void gemm_nt_v2_body(unsigned char* __restrict__ smem
                         // that group below o
                         const uint32_t o0 = (cb >> (8 * (nib & 3u))) & 0xFFu, o1 = (cb >> (8 * (nib >> 2))) & 0xFFu;
                         const uint32_t g0 = (uint32_t)(bmask >> (o0 & ~7u)) & 0xFFu, g1 = (uint32_t)(bmask >> (o1 & ~7u)) & 0xFFu;
-                        const uint32_t r0 = ((b * (M / 8) + (o0 >> 3)) << 2) + __builtin_popcount(g0 & ((1u << (o0 & 7u)) - 1u));
-                        const uint32_t r1 = ((b * (M / 8) + (o1 >> 3)) << 2) + __builtin_popcount(g1 & ((1u << (o1 & 7u)) - 1u));
+                        // (at_kept: the block's four kept rows)
+                        const uint32_t r0 = ep.at_kept ? 4 * b + (nib & 3u) : ((b * (M / 8) + (o0 >> 3)) << 2) + __builtin_popcount(g0 & ((1u << (o0 & 7u)) - 1u));
+                        const uint32_t r1 = ep.at_kept ? 4 * b + (nib >> 2) : ((b * (M / 8) + (o1 >> 3)) << 2) + __builtin_popcount(g1 & ((1u << (o1 & 7u)) - 1u));
                         *reinterpret_cast<uint16_t*>(ttile + r0 * EP + t * 2) = (uint16_t)(v & 0xFFFFu);
                         *reinterpret_cast<uint16_t*>(ttile + r1 * EP + t * 2) = (uint16_t)(v >> 16);
                     }
                 }
                 if (FP8) vmax_tile = __builtin_fmaxf(vmax_tile, vmax);
                 wave_lds_sync();
+                if (!FP8 && ep.at_kept) {       // 4 NB kept rows x 8 chunks of 8 tokens; consecutive lanes take consecutive rows
+                    const int64_t R32 = F >> (LOGM + 3);
+#pragma unroll
+                    for (int q = 0; q < (NB + 1) / 2; ++q) {
+                        const int e = q * 64 + lane, rr = e % (4 * NB), c8 = e / (4 * NB);
+                        const int64_t R = (f0 >> LOGM) * 4 + rr;
+                        if (valid && c8 < 8)
+                            *reinterpret_cast<uint4*>(ep.at + lane_off(R, t0 + 8 * c8, R32)) =
+                                *reinterpret_cast<const uint4*>(ttile + rr * EP + c8 * 16);
+                    }
+                } else {
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {          // 2 groups of 16 compact rows x 2 chunks of 32 tokens, 1 KB each
                     const int fr = (q >> 1) * 16 + (lane >> 2), tc = (q & 1) * 32 + (lane & 3) * 8;
@@ -667,6 +682,7 @@ __device__ __forceinline__ void gemm_nt_v2_body(unsigned char* __restrict__ smem
                     } else if (valid) {
                         *reinterpret_cast<uint4*>(ep.at + blk_off(f0 / 2 + fr, t0 + tc, tok_ld / 32)) = w;
                     }
+                }
                 }
             }
             if (EPI == 1 || EPI == 2) {

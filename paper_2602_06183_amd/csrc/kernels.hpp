@@ -43,6 +43,7 @@ struct VnmEpilogue {
     float* amax = nullptr;          // fp8 modes 1 / 2: amax slots for the survivors' magnitudes (y2 / dy1)
     // modes 1 / 2: the operands of the V:2:8 activation GEMM (gemm_vnm8.hip; layouts: vcb_off, mcb_off, cixt_off in common.hpp, fp8: vcb8_off, ...):
     // vcb = the survivors (both modes; fp8: their codes), mcb = their metadata and cixt = the regrouped kept-column offsets (mode 1; mode 2 reuses them)
+    int at_kept = 0;                // modes 5 / 6, bf16, M = 32, 64: `at` receives only the kept rows, in the order of gemm_wgrad_wide_body.hpp, and `kmask` (mode 5) that kernel's column offsets
     uint16_t* vcb = nullptr;
     uint8_t* mcb = nullptr;
     uint8_t* cixt = nullptr;
@@ -104,6 +105,7 @@ hipError_t launch_step_mix_fp8(int what, int logM, const StepTiles& t, const Vnm
 // and W2.  Absent parts: null X / dY / W1 / W2.  experts: W1, W2 are stacks of that many matrices.
 struct PrologueArgs {
     int T, D, F, experts, mode;
+    int t_layout;                   // of xt, dyt: 1 = blocked, 2 = lane_off (common.hpp)
     const uint16_t *X, *dY; uint16_t *xt, *xb, *dyt, *dyb;
     const uint16_t* W1; uint16_t *w1v, *w1vb; uint8_t *w1m, *w1mb;
     const uint16_t* W2; uint16_t *w2v, *w2vb, *w2t; uint8_t *w2m, *w2mb;
@@ -120,17 +122,24 @@ inline int pick_tile(unsigned n256, unsigned n128, unsigned n64, int steps, floa
     return w128 * (float)((n128 + 511) / 512) < (float)((n256 + 255) / 256) ? 128 : 256;
 }
 
-// gemm_v2 (i x j outputs; grouped over tokens: counted as if ungrouped, so that a host and a device segment table choose alike).
+// tiles along the tokens when they come in `groups` segments (0: one), taken as equally long: a host and a device segment table choose alike
+inline int64_t token_tiles(int64_t T, int groups, int64_t edge) {
+    const int64_t n = groups ? groups : 1;
+    return n * (((T + n - 1) / n + edge - 1) / edge);
+}
+// gemm_v2 (i x j outputs).
 // Eq. (1) / (4) at T = D = 2048, F = 8192 (256 / 1024 tiles): 55 / 47 us on 256 tiles, 61 / 54 on 128; T = 1024, D = 1408, F = 4928 (80 / 312): 39 / 30 and
 // 26 / 23; T = 64, D = 2048, F = 8192 (32 / 64 / 128): 43 / 33, 21 / 18, and 17 / 14 on 64 tiles
 inline int pick_gemm_tile(int64_t Ra, int64_t Rb, int steps, const GemmGroup& g, float w128, bool split) {
-    auto tiles = [&](int64_t edge) { return (unsigned)((Ra + edge - 1) / edge * ((Rb + edge - 1) / edge)) * (g.role == 2 && g.n ? (unsigned)g.n : 1u); };
+    auto tiles = [&](int64_t edge) {
+        return (unsigned)(token_tiles(Ra, g.n && g.role == 0 ? g.n : 0, edge) * token_tiles(Rb, g.n && g.role == 1 ? g.n : 0, edge) * (g.role == 2 && g.n ? g.n : 1));
+    };
     return pick_tile(tiles(256), tiles(128), tiles(64), steps, w128, split ? 256 : 0, 16);
 }
 // V:2:8 activation GEMM.  T = 8192, N = 2048, F = 8192 (256 / 1024 tiles): 107 us on 256 tiles, 148 on 128; T = 2048 (64 / 256): 85 and 54; T = 1024,
 // N = 1408, F = 4928 (24 / 88 / 352): 55, 33, and 29 on 64 tiles; T = 64, N = 2048, F = 8192 (8 / 16 / 32): 83, 49, 28
-inline int pick_vnm8_tile(int64_t T, int64_t N, int steps) {
-    auto tiles = [&](int64_t edge) { return (unsigned)((T + edge - 1) / edge * ((N + edge - 1) / edge)); };
+inline int pick_vnm8_tile(int64_t T, int64_t N, int steps, int groups) {
+    auto tiles = [&](int64_t edge) { return (unsigned)(token_tiles(T, groups, edge) * ((N + edge - 1) / edge)); };
     return pick_tile(tiles(256), tiles(128), tiles(64), steps, 0.72f, 512, 8);
 }
 // gathered-row activation GEMM: 64 tokens x 256 columns, or 64 x 64
@@ -141,18 +150,37 @@ inline int pick_gather_tile(int64_t T, int64_t N, int steps) { return (T / 64) *
 inline int pick_wgrad_tile(int64_t F, int64_t N, int64_t T, int experts, bool split_ok) {
     const unsigned e = experts ? (unsigned)experts : 1u;
     auto tiles = [&](int64_t edge) { return (unsigned)((F + edge - 1) / edge * ((N + edge - 1) / edge)) * e; };
-    return pick_tile(tiles(256), tiles(128), tiles(64), (int)(T / 64 / e), 0.56f, split_ok ? 256 : 0, 12);
+    return pick_tile(tiles(256), tiles(128), tiles(64), (int)(T / 64 / e), 0.58f, split_ok ? 256 : 0, 12);
 }
 
 inline StepTiles step_tiles(int64_t T, int64_t D, int64_t F, int M, int experts, bool fp8) {
     StepTiles t;
     const int unit = fp8 ? 128 : 64;
-    t.g = t.g_bwd = pick_gemm_tile(F, T, (int)(D / unit), GemmGroup(), 0.56f, true);
-    t.v = M == 8 ? pick_vnm8_tile(T, D, (int)(F / unit)) : fp8 ? 256 : pick_gather_tile(T, D, (int)(4 * F / M / 64));
+    GemmGroup g;
+    g.role = 1; g.n = experts > 1 ? experts : 0;
+    t.g = t.g_bwd = pick_gemm_tile(F, T, (int)(D / unit), g, 0.56f, true);
+    t.v = M == 8 ? pick_vnm8_tile(T, D, (int)(F / unit), g.n) : fp8 ? 256 : pick_gather_tile(T, D, (int)(4 * F / M / 64));
     t.w = pick_wgrad_tile(F, D, T, experts > 1 ? experts : 0, M == 8 || fp8);
     t.mix = t.g != 256 && t.w != 256 && (M != 8 || t.v != 256);
     if (t.mix) t.g_bwd = 128;
     return t;
+}
+
+// the same once the experts' segments are known: 256 or 128 by the exact number of tiles (the two give the same bits; sharing launches and splitting
+// contractions were decided from the sizes alone)
+inline void refine_tiles(StepTiles* t, int64_t D, int64_t F, int M, const GemmGroup& g) {
+    if (t->mix || !g.n) return;
+    auto count = [&](int64_t other, int64_t edge) {
+        int64_t n = 0;
+        for (int e = 0; e < g.n; ++e) n += (g.seg[e + 1] - g.seg[e] + edge - 1) / edge;
+        return (unsigned)(n * ((other + edge - 1) / edge));
+    };
+    // 256 tokens and less per expert: one large tile covers them and reads the expert's weights once (128 tokens each, D = 3776, F = 12672: eq. (1) 168 us
+    // on 256 tiles, 200 on 128)
+    const bool few = g.seg[g.n] <= 256 * g.n;
+    if (t->g != 64) t->g = few ? 256 : pick_tile(count(F, 256), count(F, 128), ~0u, 0, 0.56f, 0, 0);
+    if (t->g_bwd != 64) t->g_bwd = t->g;
+    if (M == 8 && t->v != 64) t->v = few ? 256 : pick_tile(count(D, 256), count(D, 128), ~0u, 0, 0.72f, 0, 0);
 }
 
 hipError_t launch_prune24(const uint16_t* src, int64_t R, int64_t K, int64_t ld, int trans, int mode, uint16_t* vals,
@@ -295,5 +323,10 @@ hipError_t launch_wgrad_vnm_fp8(const uint8_t* atc, const uint8_t* kmask, const 
 hipError_t launch_wgrad_vnm(const uint16_t* atc, const uint8_t* kmask, const uint16_t* G, int64_t F, int64_t N, int64_t T,
                             int out_i_contig, uint16_t* out, int64_t ldo, hipStream_t s, const GemmGroup* grp = nullptr, bool acc32 = false, bool split_ok = true, int tile = 0);
 
+
+// the same for blocks of M = 2^logM = 32, 64 columns on the kept rows only: at_kept = the epilogues' `at` with at_kept set, [4 F / M rows, T];
+// cixl = their `kmask` with it; 4 F / M a multiple of 32.  Same sums, bit for bit, as launch_wgrad_vnm on the other form of `at`.
+hipError_t launch_wgrad_wide(const uint16_t* at_kept, const uint8_t* cixl, const uint16_t* G, int64_t F, int64_t N, int64_t T, int logM, int out_i_contig, uint16_t* out,
+                             int64_t ldo, hipStream_t s, const GemmGroup* grp = nullptr, bool acc32 = false);
 
 }  // namespace sffn

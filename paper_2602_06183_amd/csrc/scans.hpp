@@ -8,6 +8,7 @@ namespace sffn {
 constexpr int kTransposeLds = 64 * (64 + 2) * 2, kPruneColsLds = 128 * (64 + 8) * 2;
 
 // out[c, r] = in[r, c]; R, C multiples of 64.
+// blocked = 2: out in the order of lane_off (common.hpp), out_same as for 1.
 // blocked = 1: out (the transpose) and, when given, out_same (a copy of `in`) are written in the blocked
 // operand layout instead of row-major.
 __device__ __forceinline__ void transpose_bf16_body(void* smem, int bx, int by, int bz, const uint16_t* __restrict__ in, int64_t R, int64_t C, int64_t ld,
@@ -38,13 +39,14 @@ __device__ __forceinline__ void transpose_bf16_body(void* smem, int bx, int by, 
     for (int i = 0; i < 2; ++i) {
         const int e = tid + 256 * i;
         int cc, rs;                          // output row (a column of `in`) and first of 8 source rows
-        if (blocked) { const int bk = e >> 6, l = e & 63; cc = (bk >> 1) * 16 + (l >> 2); rs = (bk & 1) * 32 + (l & 3) * 8; }
+        if (blocked == 2) { cc = ((e >> 8) & 1) * 32 + (e & 31); rs = ((e >> 6) & 3) * 16 + ((e >> 5) & 1) * 8; }
+        else if (blocked) { const int bk = e >> 6, l = e & 63; cc = (bk >> 1) * 16 + (l >> 2); rs = (bk & 1) * 32 + (l & 3) * 8; }
         else { cc = e >> 3; rs = (e & 7) * 8; }
         if (out) {                           // (out = nullptr: only the blocked copy of `in` is wanted)
             uint32_t o[4];
 #pragma unroll
             for (int j = 0; j < 4; ++j) o[j] = tile[rs + 2 * j][cc] | ((uint32_t)tile[rs + 2 * j + 1][cc] << 16);
-            uint16_t* dst = blocked ? out + blk_off(c0 + cc, r0 + rs, R / 32) : out + (c0 + cc) * R + r0 + rs;
+            uint16_t* dst = blocked == 2 ? out + lane_off(c0 + cc, r0 + rs, C / 32) : blocked ? out + blk_off(c0 + cc, r0 + rs, R / 32) : out + (c0 + cc) * R + r0 + rs;
             *reinterpret_cast<uint4*>(dst) = make_uint4(o[0], o[1], o[2], o[3]);
         }
         if (out_same) {

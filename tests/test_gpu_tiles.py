@@ -41,3 +41,40 @@ def test_fp8_step_on_small_tiles(M, T, D, F):
     torch.cuda.synchronize()
     s = {k: to_bits(v) if v.dtype == torch.bfloat16 else v.cpu().numpy() for k, v in step.saved().items()}
     _check_fp8_step_against_oracle(inp, sc, s, {k: to_bits(v) for k, v in zip(("Y3", "dX", "dW1", "dW2"), outs)}, sffn.MODE_HARD, True, M)
+
+
+@pytest.mark.parametrize("M,T,D,F", [
+    (32, 2112, 1088, 6656),     # kept rows only (the outputs fill the chip): a half-empty last tile in both dimensions, 33 token blocks
+    (64, 2048, 1344, 7168),
+    (64, 768, 1344, 7168),      # the fewest tokens of this form
+])
+def test_wide_weight_gradients_on_kept_rows(M, T, D, F):
+    """Eqs. (5), (8) on the kept rows only: the same bits as the unfused path, which multiplies the rows of zeros too, in bf16 and as float32
+    accumulators."""
+    inp = make_ffn_inputs(T, D, F, seed=24)
+    dev = [to_dev(inp[k]) for k in ("X", "W1", "W2", "b1", "dY")]
+    plain = [t.clone() for t in sffn.FfnStep(T, D, F, M=M, lean=True)(*dev)]
+    for a, b in zip(plain, sffn.FfnStep(T, D, F, M=M, unfused=True)(*dev)):
+        assert torch.equal(a, b)
+    acc = sffn.FfnStep(T, D, F, M=M, lean=True, dw_fp32=True)
+    acc(*dev)
+    assert torch.equal(acc.dW1.to(torch.bfloat16), plain[2]) and torch.equal(acc.dW2.to(torch.bfloat16), plain[3])
+
+
+@pytest.mark.parametrize("M", [32, 64])
+def test_wide_weight_gradients_of_experts_on_kept_rows(M):
+    """Experts with 1, 0, 24 and 23 token blocks: each one's weight gradients are those of a step on its tokens alone (bit for bit, except where
+    64 tokens alone are contracted by several wavefronts)."""
+    seg, D, F = [0, 64, 64, 1600, 3072], 1344, 7168
+    inp = [make_ffn_inputs(seg[-1], D, F, seed=25 + e) for e in range(4)]
+    X, dY = to_dev(inp[0]["X"]), to_dev(inp[0]["dY"])
+    W1, W2, b1 = (torch.stack([to_dev(i[k]) for i in inp]) for k in ("W1", "W2", "b1"))
+    step = sffn.FfnStepGrouped(seg, D, F, M=M, lean=True)
+    step(X, W1, W2, b1, dY)
+    for e, (a, b) in enumerate(zip(seg, seg[1:])):
+        if a == b:
+            assert not step.dW1[e].any() and not step.dW2[e].any()
+            continue
+        alone = sffn.FfnStep(b - a, D, F, M=M, unfused=True)(X[a:b].contiguous(), W1[e], W2[e], b1[e], dY[a:b].contiguous())
+        for got, want in ((step.dW1[e], alone[2]), (step.dW2[e], alone[3])):
+            assert torch.equal(got, want) or (b - a == 64 and (got.float() - want.float()).norm() < 2e-2 * want.float().norm())
