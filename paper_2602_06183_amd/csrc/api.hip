@@ -80,6 +80,11 @@ inline int place_regions(const sffn_buffers* buf, void* workspace, size_t ws_byt
     return SFFN_OK;
 }
 
+// Weight gradients on the kept rows only (gemm_wgrad_wide_body.hpp), from 768 tokens per expert on: with fewer the matrix work that is saved is
+// less than clearing a tile in LDS and reading it out again (D = 4096, F = 16384, M = 32: 82 us for 73 at 512 tokens, 94 for 94 at 768, 840 for
+// 1390 at 16384).
+int wgrad_on_kept_rows(int64_t T, int64_t F, int M, int64_t experts) { return M >= 32 && F % (8 * M) == 0 && T >= 768 * experts; }
+
 // Blocks of M = 16, 32, 64 columns take the fused path (V:N:M epilogues inside eqs. (1), (4), gathered-row eqs. (3), (7)) when the
 // gathered-row kernel covers the shape and the caller does not ask for the unfused reference path.
 bool fused_wide(const sffn_cfg* c) {
@@ -352,12 +357,16 @@ int vnm_wgrad(const uint16_t* a_vals, const uint8_t* a_meta, const uint8_t* a_co
     hipStream_t s = (hipStream_t)stream;
     uint16_t* at = (uint16_t*)workspace;
     uint16_t* gt = (uint16_t*)((unsigned char*)workspace + up256((size_t)F * T * 2));
-    if (M == 8) LAUNCH(launch_vnm_expand_t(a_vals, a_meta, a_colidx, T, F, at, 0, s), "vnm_wgrad/expand");
-    else        LAUNCH(launch_vnm_expand_t_m(a_vals, a_meta, a_colidx, T, F, M, at, s), "vnm_wgrad/expand");
-    LAUNCH(launch_transpose(G, T, N, N, gt, 0, nullptr, s), "vnm_wgrad/transpose");
+    // the kernels of the fused step on its operands: the survivors compacted to at most half of the rows, their masks behind them, G.T
+    const int kept = wgrad_on_kept_rows(T, F, M, 1);
+    uint8_t* mask = (uint8_t*)at + up256((size_t)F * T);
+    LAUNCH(launch_vnm_compact_t(a_vals, a_meta, a_colidx, T, F, M, kept, at, mask, s), "vnm_wgrad/compact");
+    LAUNCH(launch_transpose(G, T, N, N, gt, kept ? 2 : 1, nullptr, s), "vnm_wgrad/transpose");
     // C[i=f][j=n]; out_f_major: out[f*N + n] (j contiguous) else out[n*F + f] (i contiguous)
-    if (out_f_major) LAUNCH(launch_gemm_nt(0, at, nullptr, gt, nullptr, F, N, T, 0, out, N, s), "vnm_wgrad/gemm");
-    else             LAUNCH(launch_gemm_nt(0, at, nullptr, gt, nullptr, F, N, T, 1, out, F, s), "vnm_wgrad/gemm");
+    const int i_contig = !out_f_major;
+    const int64_t ldo = out_f_major ? N : F;
+    if (kept) LAUNCH(launch_wgrad_wide(at, mask, gt, F, N, T, M == 32 ? 5 : 6, i_contig, out, ldo, s), "vnm_wgrad/gemm");
+    else      LAUNCH(launch_wgrad_vnm(at, mask, gt, F, N, T, i_contig, out, ldo, s), "vnm_wgrad/gemm");
     return SFFN_OK;
 }
 
@@ -1116,10 +1125,7 @@ static int run_step(const sffn_cfg* cfg, int n_experts, const int64_t* seg, cons
         // pass of W2 also writes W2.T), eqs. (5), (8) on the compacted transposed activation that the epilogues write in the M = 8 format
         // (no group of 8 hidden units keeps more than 4 when a block of M >= 16 keeps 4).  10 launches.
         const int M = cfg->M, logM = M == 16 ? 4 : M == 32 ? 5 : 6;
-        // eqs. (5), (8) on the kept rows only (gemm_wgrad_wide_body.hpp), from 768 tokens per expert on: with fewer the matrix work that is
-        // saved is less than clearing a tile in LDS and reading it out again (D = 4096, F = 16384, M = 32: 82 us for 73 at 512 tokens,
-        // 94 for 94 at 768, 840 for 1390 at 16384)
-        const int kept = !tiles.mix && M >= 32 && T >= 768 * (int64_t)E;
+        const int kept = !tiles.mix && wgrad_on_kept_rows(T, F, M, E);      // eqs. (5), (8)
         GemmGroup g_packed = g, g_rows = g, g_wgrad = g;
         g_packed.role = 1; g_packed.a_stride = F * D / 2; g_packed.m_stride = F * D / 8; g_packed.bias_stride = F;
         g_rows.role = 0;   g_rows.b_stride = F * D;

@@ -232,8 +232,10 @@ hipError_t launch_vnm_spmm_gather_fp8(const uint8_t* a_codes, const uint8_t* a_m
                                       int64_t T, int64_t N, int64_t F, int M, uint16_t* out, int64_t ldo, hipStream_t s, const GemmGroup* grp = nullptr);
 hipError_t launch_vnm_to_24(const uint16_t* vals, const uint8_t* meta, const uint8_t* colidx, int64_t T, int64_t F,
                             uint16_t* vals24, uint8_t* meta24, hipStream_t s);
-hipError_t launch_vnm_expand_t(const uint16_t* vals, const uint8_t* meta, const uint8_t* colidx, int64_t T, int64_t F,
-                               uint16_t* out, int blocked, hipStream_t s);
+// vnm.hip: the transposed operand of eqs. (5), (8) from the canonical arrays: kept = 0: at [F / 2, T], mask [T / 64, F / 8] for launch_wgrad_vnm;
+// kept = 1 (M = 32, 64, F a multiple of 8 M): at [4 F / M, T], mask [T / 64, F / M] words for launch_wgrad_wide
+hipError_t launch_vnm_compact_t(const uint16_t* vals, const uint8_t* meta, const uint8_t* colidx, int64_t T, int64_t F, int M, int kept, uint16_t* at,
+                                uint8_t* mask, hipStream_t s);
 // batch > 1: `batch` matrices [R, C] (ld = C) back to back, transposed one by one.
 // cluster_M (with batch = M / 4 experts, R = hidden units per expert): matrix e reads the rows of `in` that belong to expert e,
 // row r of it = row (r / 4) * M + 4 e + r % 4 of the one [F, C] source (Section 3.3's expert-major order).

@@ -51,42 +51,71 @@ __global__ void __launch_bounds__(256) vnm_to_24_kernel(const uint16_t* __restri
     meta24[t * (F / 8) + blk] = (uint8_t)mb;
 }
 
-// Dense, transposed expansion AT[f, t] of a V:N:M matrix (K-contiguous operand for the
-// weight-gradient GEMMs).  One workgroup = 64 rows x 8 column blocks.
-__global__ void __launch_bounds__(256) vnm_expand_t_kernel(const uint16_t* __restrict__ vals, const uint8_t* __restrict__ meta,
-                                                          const uint8_t* __restrict__ colidx, int64_t T, int64_t F, int nblk,
-                                                          uint16_t* __restrict__ out, int blocked) {
-    __shared__ __attribute__((aligned(16))) uint16_t tile[64][64 + 8];
+// The transposed operand of the weight-gradient contractions from the canonical arrays, as the fused epilogues write it: KEPT = false: at = the
+// survivors compacted to 4 rows per 8 hidden units (gemm_wgrad_body.hpp), [F / 2, T] blocked, and mask = the kept-column bits of every 8;
+// KEPT = true (M = 32, 64): the 4 kept rows of every block in the order of gemm_wgrad_wide_body.hpp, and that kernel's column offsets.
+// One workgroup = 64 tokens x 256 (KEPT: 16 M) hidden units through LDS: rows of 128 bytes at M = 8 in, whole 1 KB blocks out.
+//   Bound: HBM.  T = F = 8192, M = 8: 42 MB in, 67 MB out: 29 us; the dense [F, T] expansion took 51 us.
+template <bool KEPT>
+__global__ void __launch_bounds__(256) vnm_compact_t_kernel(const uint16_t* __restrict__ vals, const uint8_t* __restrict__ meta, const uint8_t* __restrict__ colidx,
+                                                           int64_t T, int64_t F, int logM, uint16_t* __restrict__ at, uint8_t* __restrict__ mask) {
+    constexpr int ROWS = KEPT ? 64 : 128, PITCH = 64 + 2;
+    __shared__ uint32_t tile32[ROWS * PITCH / 2];
+    __shared__ uint32_t cols[32];                  // kept columns of the workgroup's blocks
+    __shared__ uint8_t gm[32];                     // and, as bits, of its groups of 8 hidden units
+    uint16_t* const tile = reinterpret_cast<uint16_t*>(tile32);
     const int tid = threadIdx.x;
-    for (int i = tid; i < 64 * 72 / 2; i += 256) reinterpret_cast<uint32_t*>(&tile[0][0])[i] = 0;
+    const int64_t tb = blockIdx.y, nblk = F >> logM;
+    const int lognb = KEPT ? 4 : 8 - logM, nb = 1 << lognb;              // blocks of the workgroup
+    const int64_t b0 = (int64_t)blockIdx.x << lognb;
+    const int here = nblk - b0 < nb ? (int)(nblk - b0) : nb;
+    for (int i = tid; i < ROWS * PITCH / 2; i += 256) tile32[i] = 0;
+    if (tid < here) cols[tid] = *reinterpret_cast<const uint32_t*>(colidx + (tb * nblk + b0 + tid) * 4);
     __syncthreads();
-    const int64_t tb = blockIdx.y;
-    const int b0 = blockIdx.x * 8;
+    if (!KEPT) {
+        if (tid < here << (logM - 3)) {            // a group of 8 hidden units: which of them are among its block's kept columns
+            const uint32_t c = cols[tid >> (logM - 3)], g = tid & ((1 << (logM - 3)) - 1);
+            uint32_t m = 0;
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
-        const int e = tid + 256 * i;           // 64 rows x 8 blocks
-        const int r = e >> 3, bl = e & 7, blk = b0 + bl;
-        const int64_t t = tb * 64 + r;
-        const uint32_t cw = *reinterpret_cast<const uint32_t*>(colidx + (tb * nblk + blk) * 4);
-        const uint32_t nib = (meta[t * (F / 16) + (blk >> 1)] >> (4 * (blk & 1))) & 0xFu;
-        const uint32_t o0 = (cw >> (8 * (nib & 3u))) & 0xFFu, o1 = (cw >> (8 * (nib >> 2))) & 0xFFu;
-        const uint32_t v = *reinterpret_cast<const uint32_t*>(vals + t * (F / 4) + (int64_t)blk * 2);
-        tile[bl * 8 + o0][r] = (uint16_t)(v & 0xFFFFu);
-        tile[bl * 8 + o1][r] = (uint16_t)(v >> 16);
+            for (int p = 0; p < 4; ++p) {
+                const uint32_t o = (c >> (8 * p)) & 0xFFu;
+                m |= (o >> 3) == g ? 1u << (o & 7) : 0u;
+            }
+            gm[tid] = (uint8_t)m;
+            mask[tb * (F >> 3) + (b0 << (logM - 3)) + tid] = (uint8_t)m;
+        }
+        __syncthreads();
+    } else if (tid < here) {                       // word (b % 2, b % 8 / 2) of every 8 blocks
+        const int64_t blk = b0 + tid;
+        reinterpret_cast<uint32_t*>(mask)[(tb * (nblk >> 3) + (blk >> 3)) * 8 + (blk & 1) * 4 + ((blk & 7) >> 1)] = cols[tid];
+    }
+    for (int e = tid; e < 64 << lognb; e += 256) {
+        const int r = e >> lognb, bl = e & (nb - 1);
+        if (bl >= here) continue;
+        const int64_t t = tb * 64 + r, blk = b0 + bl;
+        const uint32_t nib = (meta[t * (nblk >> 1) + (blk >> 1)] >> (4 * (blk & 1))) & 0xFu;
+        const uint32_t v = *reinterpret_cast<const uint32_t*>(vals + t * (2 * nblk) + blk * 2);
+        const uint32_t p0 = nib & 3u, p1 = nib >> 2;
+        int r0 = bl * 4 + p0, r1 = bl * 4 + p1;
+        if (!KEPT) {
+            const uint32_t o0 = (cols[bl] >> (8 * p0)) & 0xFFu, o1 = (cols[bl] >> (8 * p1)) & 0xFFu;
+            const int g0 = (bl << (logM - 3)) + (o0 >> 3), g1 = (bl << (logM - 3)) + (o1 >> 3);
+            r0 = g0 * 4 + __builtin_popcount(gm[g0] & ((1u << (o0 & 7)) - 1u));
+            r1 = g1 * 4 + __builtin_popcount(gm[g1] & ((1u << (o1 & 7)) - 1u));
+        }
+        tile[r0 * PITCH + r] = (uint16_t)(v & 0xFFFFu);
+        tile[r1 * PITCH + r] = (uint16_t)(v >> 16);
     }
     __syncthreads();
+    const int64_t row0 = KEPT ? b0 * 4 : b0 << (logM - 1), rows = KEPT ? nblk * 4 : F >> 1;
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
-        const int e = tid + 256 * i;           // 64 f rows x 8 segments of 8 tokens
-        if (blocked) {                      // 8 blocks of 16 f-rows x 32 tokens, one per 64 consecutive e
-            const int bk = e >> 6, l = e & 63, fr = (bk >> 1) * 16 + (l >> 2), tc = (bk & 1) * 32 + (l & 3) * 8;
-            *reinterpret_cast<uint4*>(out + blk_off((int64_t)b0 * 8 + fr, tb * 64 + tc, T / 32)) =
-                *reinterpret_cast<const uint4*>(&tile[fr][tc]);
-        } else {
-            const int fr = e >> 3, seg = e & 7;
-            *reinterpret_cast<uint4*>(out + ((int64_t)b0 * 8 + fr) * T + tb * 64 + seg * 8) =
-                *reinterpret_cast<const uint4*>(&tile[fr][seg * 8]);
-        }
+    for (int i = 0; i < ROWS / 32; ++i) {
+        const int e = tid + 256 * i, l = e & 63;
+        const int fr = KEPT ? (e >> 8) * 32 + (e & 31) : (e >> 7) * 16 + (l >> 2);
+        const int tc = KEPT ? ((e >> 6) & 3) * 16 + ((e >> 5) & 1) * 8 : ((e >> 6) & 1) * 32 + (l & 3) * 8;
+        if (row0 + fr >= rows) continue;
+        const uint32_t* p = tile32 + (fr * PITCH + tc) / 2;
+        *reinterpret_cast<uint4*>(at + (KEPT ? lane_off(row0 + fr, tb * 64 + tc, rows >> 5) : blk_off(row0 + fr, tb * 64 + tc, T / 32))) = make_uint4(p[0], p[1], p[2], p[3]);
     }
 }
 
@@ -105,37 +134,41 @@ hipError_t launch_dsqrelu_vnm(const uint16_t* dy2, const uint16_t* y1, const uin
     return hipGetLastError();
 }
 
-// The canonical V:2:8 arrays regrouped into the units of the V:2:8 activation GEMM (gemm_vnm8.hip; the fused epilogues write them directly):
-// one thread per (token, 64 hidden units) moves 16 survivors and 4 metadata bytes; the first 8 threads of a token block also build the 8
-// offset words of their (token block, 64 hidden units).
+// The canonical V:2:8 arrays regrouped into the units of the V:2:8 activation GEMM (gemm_vnm8.hip; the fused epilogues write them directly).
+// One workgroup = 64 tokens x 512 hidden units: a wavefront reads 256 bytes of each of 4 tokens and writes 128 bytes of each of 8 units.
+//   Bound: HBM.  T = F = 8192: 75 MB in all; 44 us when every lane moved 32 bytes of a unit of its own, 16 us now.
 __global__ void __launch_bounds__(256) vnm8_repack_kernel(const uint16_t* __restrict__ vals, const uint8_t* __restrict__ meta,
                                                          const uint8_t* __restrict__ colidx, int64_t T, int F, uint16_t* __restrict__ vcb,
                                                          uint8_t* __restrict__ mcb, uint8_t* __restrict__ cixt) {
-    const int KS = F >> 6;
-    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (i >= T * KS) return;
-    const int64_t t = i / KS;
-    const int kt = (int)(i - t * KS);
-    const uint4* src = reinterpret_cast<const uint4*>(vals + t * (F >> 2) + kt * 16);
-    uint4* dst = reinterpret_cast<uint4*>(vcb + vcb_off(t, (int64_t)kt * 8, F));
-    dst[0] = src[0];
-    dst[1] = src[1];
-    *reinterpret_cast<uint32_t*>(mcb + mcb_off(t, kt, F)) = *reinterpret_cast<const uint32_t*>(meta + t * (F >> 4) + kt * 4);
-    const int q = (int)(t & 63);
-    if (q < 8) {        // word (h, r), byte j = kept column r of column block 4 (j / 2) + j % 2 + 2 h
+    const int KS = F >> 6, tid = threadIdx.x, kt0 = blockIdx.x * 8;
+    const int64_t tb = blockIdx.y;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {                      // 64 tokens x 8 units x two 16-byte halves
+        const int e = tid + 256 * i, half = e & 1, kt = kt0 + ((e >> 1) & 7);
+        const int64_t t = tb * 64 + (e >> 4);
+        if (kt < KS)
+            *reinterpret_cast<uint4*>(vcb + vcb_off(t, (int64_t)kt * 8, F) + half * 8) = *reinterpret_cast<const uint4*>(vals + t * (F >> 2) + kt * 16 + half * 8);
+    }
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const int e = tid + 256 * i, kt = kt0 + (e & 7);
+        const int64_t t = tb * 64 + (e >> 3);
+        if (kt < KS) *reinterpret_cast<uint32_t*>(mcb + mcb_off(t, kt, F)) = *reinterpret_cast<const uint32_t*>(meta + t * (F >> 4) + kt * 4);
+    }
+    const int kt = kt0 + (tid >> 3), q = tid & 7;
+    if (tid < 64 && kt < KS) {        // word (h, r), byte j = kept column r of column block 4 (j / 2) + j % 2 + 2 h
         const int h = q >> 2, r = q & 3;
-        const uint8_t* c = colidx + ((t >> 6) * (F >> 3) + kt * 8) * 4;
+        const uint8_t* c = colidx + (tb * (F >> 3) + kt * 8) * 4;
         uint32_t dw = 0;
 #pragma unroll
         for (int j = 0; j < 4; ++j) dw |= (uint32_t)c[(4 * (j >> 1) + (j & 1) + 2 * h) * 4 + r] << (8 * j);
-        *reinterpret_cast<uint32_t*>(cixt + cixt_off(t >> 6, kt, T >> 6) + q * 4) = dw;
+        *reinterpret_cast<uint32_t*>(cixt + cixt_off(tb, kt, T >> 6) + q * 4) = dw;
     }
 }
 
 hipError_t launch_vnm8_repack(const uint16_t* vals, const uint8_t* meta, const uint8_t* colidx, int64_t T, int64_t F, uint16_t* vcb, uint8_t* mcb,
                               uint8_t* cixt, hipStream_t s) {
-    const int64_t n = T * (F / 64);
-    hipLaunchKernelGGL(vnm8_repack_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, vals, meta, colidx, T, (int)F, vcb, mcb, cixt);
+    hipLaunchKernelGGL(vnm8_repack_kernel, dim3((unsigned)((F + 511) / 512), (unsigned)(T / 64)), dim3(256), 0, s, vals, meta, colidx, T, (int)F, vcb, mcb, cixt);
     return hipGetLastError();
 }
 
@@ -147,11 +180,14 @@ hipError_t launch_vnm_to_24(const uint16_t* vals, const uint8_t* meta, const uin
     return hipGetLastError();
 }
 
-hipError_t launch_vnm_expand_t(const uint16_t* vals, const uint8_t* meta, const uint8_t* colidx, int64_t T, int64_t F,
-                               uint16_t* out, int blocked, hipStream_t s) {
-    const int nblk = (int)(F / 8);
-    dim3 grid((unsigned)(nblk / 8), (unsigned)(T / 64));
-    hipLaunchKernelGGL(vnm_expand_t_kernel, grid, dim3(256), 0, s, vals, meta, colidx, T, F, nblk, out, blocked);
+hipError_t launch_vnm_compact_t(const uint16_t* vals, const uint8_t* meta, const uint8_t* colidx, int64_t T, int64_t F, int M, int kept, uint16_t* at,
+                                uint8_t* mask, hipStream_t s) {
+    const int logM = M == 8 ? 3 : M == 16 ? 4 : M == 32 ? 5 : M == 64 ? 6 : 0;
+    if (!logM || T / 64 > 65535 || (kept && F % (8 * M))) return hipErrorInvalidValue;
+    const int64_t width = kept ? 16 * M : 256;
+    dim3 grid((unsigned)((F + width - 1) / width), (unsigned)(T / 64));
+    if (kept) hipLaunchKernelGGL(vnm_compact_t_kernel<true>, grid, dim3(256), 0, s, vals, meta, colidx, T, F, logM, at, mask);
+    else hipLaunchKernelGGL(vnm_compact_t_kernel<false>, grid, dim3(256), 0, s, vals, meta, colidx, T, F, logM, at, mask);
     return hipGetLastError();
 }
 

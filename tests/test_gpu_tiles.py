@@ -1,13 +1,15 @@
 """The tile sizes of the contractions at sizes where each is chosen (256 x 256, 128 x 128, and 64 x 64 with the contraction split over the tile's
 wavefronts), with remainders in every dimension; stage by stage against the oracle."""
+import numpy as np
 import pytest
 import torch
 
+import oracle
 import paper_2602_06183_amd as sffn
 from tests.test_gpu_fp8 import _check_fp8_step_against_oracle, _fp8_step_scales
 from tests.test_gpu_kernels import _check_wide_step_against_oracle, _teacher_forced_step_check
-from tests.util import to_bits, to_dev
-from workload import make_ffn_inputs
+from tests.util import assert_gemm_close, to_bits, to_dev
+from workload import bf16_bits_from_f32, make_ffn_inputs
 
 pytestmark = pytest.mark.gpu
 
@@ -78,3 +80,20 @@ def test_wide_weight_gradients_of_experts_on_kept_rows(M):
         alone = sffn.FfnStep(b - a, D, F, M=M, unfused=True)(X[a:b].contiguous(), W1[e], W2[e], b1[e], dY[a:b].contiguous())
         for got, want in ((step.dW1[e], alone[2]), (step.dW2[e], alone[3])):
             assert torch.equal(got, want) or (b - a == 64 and (got.float() - want.float()).norm() < 2e-2 * want.float().norm())
+
+
+@pytest.mark.parametrize("M,T,N,F", [
+    (8, 64, 64, 64), (8, 192, 320, 832), (16, 128, 192, 320), (32, 832, 64, 320), (64, 64, 64, 128),      # compacted rows: edges of the 256-unit pieces
+    (32, 768, 128, 768), (64, 832, 64, 1536),                                                             # kept rows only: half-empty last pieces
+])
+def test_standalone_weight_gradients(M, T, N, F):
+    rng = np.random.default_rng(31)
+    y1 = bf16_bits_from_f32(rng.standard_normal((T, F)).astype(np.float32))
+    G = bf16_bits_from_f32(rng.standard_normal((T, N)).astype(np.float32))
+    a = sffn.sqrelu_vnm_compress(to_dev(y1), 64, M)
+    bits = [to_bits(t) for t in a]
+    for f_major in (0, 1):
+        assert_gemm_close(to_bits(sffn.vnm_wgrad(*a, to_dev(G), f_major, 64, M)), oracle.vnm_wgrad(*bits, G, f_major, 64, M), "wgrad")
+    if M == 8:
+        W = bf16_bits_from_f32(rng.standard_normal((N, F)).astype(np.float32))
+        assert_gemm_close(to_bits(sffn.vnm_spmm(*a, to_dev(W), 0, 64, M)), oracle.vnm_spmm(*bits, W, 0, 64, M), "spmm")
