@@ -151,7 +151,7 @@ def _ptr(t, rows_strided=False):
     ok = t.is_contiguous() or (rows_strided and t.dim() == 2 and t.stride(1) == 1)
     if not t.is_cuda or not ok:
         raise SffnError("expected a contiguous device tensor")
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()          # (every entry point declares its argument types: ctypes makes the pointer)
 
 
 _BF16 = (torch.bfloat16, torch.int16, torch.uint16)      # bf16 values or their bit patterns
@@ -163,6 +163,8 @@ _I32 = (torch.int32,)
 def _want(name, t, shape, kinds, optional=False):
     """The C ABI sees raw pointers only, so sizes and element types are checked here, before any call: a short or
     mistyped tensor would otherwise become an out-of-bounds device access inside a kernel."""
+    if t is not None and t.dtype in kinds and t.shape == shape:          # (a torch.Size compares like the tuple it is)
+        return
     if t is None:
         if optional:
             return
@@ -173,16 +175,21 @@ def _want(name, t, shape, kinds, optional=False):
         raise SffnError("%s: expected dtype %s, got %s" % (name, " / ".join(str(k) for k in kinds), t.dtype))
 
 
+# torch's current stream as a bare handle where this torch has the call: current_stream() builds a Stream object first, a fifth of the host time of an
+# entry point on a small shape
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream():
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    return _raw_stream(torch.cuda.current_device()) if _raw_stream else torch.cuda.current_stream().cuda_stream
 
 
 def _bf16(shape, dev):
-    return torch.empty(shape, dtype=torch.bfloat16, device=dev)
+    return torch.empty(*shape, dtype=torch.bfloat16, device=dev)
 
 
 def _u8(shape, dev):
-    return torch.empty(shape, dtype=torch.uint8, device=dev)
+    return torch.empty(*shape, dtype=torch.uint8, device=dev)
 
 
 def version():

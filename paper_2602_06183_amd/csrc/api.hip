@@ -295,12 +295,9 @@ int vnm_spmm(const uint16_t* a_vals, const uint8_t* a_meta, const uint8_t* a_col
         uint16_t* vcb = v24;
         uint8_t* mcb = m24;
         uint8_t* cixt = m24 + up256((size_t)T * Kfull / 16);
-        int64_t ldk = ldw;
-        if (!w_kmajor) {
-            LAUNCH(launch_transpose(Wd, N, Kfull, ldw, wcopy, 0, nullptr, s), "vnm_spmm/transpose");
-            W = wcopy; ldk = N;
-        }
-        LAUNCH(launch_vnm8_repack(a_vals, a_meta, a_colidx, T, Kfull, vcb, mcb, cixt, s), "vnm_spmm/repack");
+        LAUNCH(launch_vnm8_repack(a_vals, a_meta, a_colidx, T, Kfull, vcb, mcb, cixt, w_kmajor ? nullptr : Wd, N, Kfull, ldw, wcopy, s), "vnm_spmm/repack");
+        const int64_t ldk = w_kmajor ? ldw : N;
+        if (!w_kmajor) W = wcopy;
         LAUNCH(launch_vnm8_gemm(vcb, mcb, cixt, W, ldk, T, N, Kfull, out, N, s), "vnm_spmm/gemm");
         return SFFN_OK;
     }
@@ -360,8 +357,7 @@ int vnm_wgrad(const uint16_t* a_vals, const uint8_t* a_meta, const uint8_t* a_co
     // the kernels of the fused step on its operands: the survivors compacted to at most half of the rows, their masks behind them, G.T
     const int kept = wgrad_on_kept_rows(T, F, M, 1);
     uint8_t* mask = (uint8_t*)at + up256((size_t)F * T);
-    LAUNCH(launch_vnm_compact_t(a_vals, a_meta, a_colidx, T, F, M, kept, at, mask, s), "vnm_wgrad/compact");
-    LAUNCH(launch_transpose(G, T, N, N, gt, kept ? 2 : 1, nullptr, s), "vnm_wgrad/transpose");
+    LAUNCH(launch_vnm_compact_t(a_vals, a_meta, a_colidx, T, F, M, kept, at, mask, G, N, gt, s), "vnm_wgrad/compact");
     // C[i=f][j=n]; out_f_major: out[f*N + n] (j contiguous) else out[n*F + f] (i contiguous)
     const int i_contig = !out_f_major;
     const int64_t ldo = out_f_major ? N : F;

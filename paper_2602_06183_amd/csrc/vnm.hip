@@ -56,18 +56,19 @@ __global__ void __launch_bounds__(256) vnm_to_24_kernel(const uint16_t* __restri
 // KEPT = true (M = 32, 64): the 4 kept rows of every block in the order of gemm_wgrad_wide_body.hpp, and that kernel's column offsets.
 // One workgroup = 64 tokens x 256 (KEPT: 16 M) hidden units through LDS: rows of 128 bytes at M = 8 in, whole 1 KB blocks out.
 //   Bound: HBM.  T = F = 8192, M = 8: 42 MB in, 67 MB out: 29 us; the dense [F, T] expansion took 51 us.
+constexpr int kCompactRows = 128, kCompactPitch = 64 + 2, kCompactLds = kCompactRows * kCompactPitch * 2 + 32 * 4 + 32;
 template <bool KEPT>
-__global__ void __launch_bounds__(256) vnm_compact_t_kernel(const uint16_t* __restrict__ vals, const uint8_t* __restrict__ meta, const uint8_t* __restrict__ colidx,
-                                                           int64_t T, int64_t F, int logM, uint16_t* __restrict__ at, uint8_t* __restrict__ mask) {
-    constexpr int ROWS = KEPT ? 64 : 128, PITCH = 64 + 2;
-    __shared__ uint32_t tile32[ROWS * PITCH / 2];
-    __shared__ uint32_t cols[32];                  // kept columns of the workgroup's blocks
-    __shared__ uint8_t gm[32];                     // and, as bits, of its groups of 8 hidden units
+__device__ __forceinline__ void vnm_compact_t_body(void* smem, int bx, int64_t tb, const uint16_t* __restrict__ vals, const uint8_t* __restrict__ meta,
+                                                   const uint8_t* __restrict__ colidx, int64_t T, int64_t F, int logM, uint16_t* __restrict__ at, uint8_t* __restrict__ mask) {
+    constexpr int ROWS = KEPT ? 64 : kCompactRows, PITCH = kCompactPitch;
+    uint32_t* const tile32 = reinterpret_cast<uint32_t*>(smem);
+    uint32_t* const cols = tile32 + kCompactRows * PITCH / 2;              // kept columns of the workgroup's blocks
+    uint8_t* const gm = reinterpret_cast<uint8_t*>(cols + 32);             // and, as bits, of its groups of 8 hidden units
     uint16_t* const tile = reinterpret_cast<uint16_t*>(tile32);
     const int tid = threadIdx.x;
-    const int64_t tb = blockIdx.y, nblk = F >> logM;
+    const int64_t nblk = F >> logM;
     const int lognb = KEPT ? 4 : 8 - logM, nb = 1 << lognb;              // blocks of the workgroup
-    const int64_t b0 = (int64_t)blockIdx.x << lognb;
+    const int64_t b0 = (int64_t)bx << lognb;
     const int here = nblk - b0 < nb ? (int)(nblk - b0) : nb;
     for (int i = tid; i < ROWS * PITCH / 2; i += 256) tile32[i] = 0;
     if (tid < here) cols[tid] = *reinterpret_cast<const uint32_t*>(colidx + (tb * nblk + b0 + tid) * 4);
@@ -137,11 +138,10 @@ hipError_t launch_dsqrelu_vnm(const uint16_t* dy2, const uint16_t* y1, const uin
 // The canonical V:2:8 arrays regrouped into the units of the V:2:8 activation GEMM (gemm_vnm8.hip; the fused epilogues write them directly).
 // One workgroup = 64 tokens x 512 hidden units: a wavefront reads 256 bytes of each of 4 tokens and writes 128 bytes of each of 8 units.
 //   Bound: HBM.  T = F = 8192: 75 MB in all; 44 us when every lane moved 32 bytes of a unit of its own, 16 us now.
-__global__ void __launch_bounds__(256) vnm8_repack_kernel(const uint16_t* __restrict__ vals, const uint8_t* __restrict__ meta,
-                                                         const uint8_t* __restrict__ colidx, int64_t T, int F, uint16_t* __restrict__ vcb,
-                                                         uint8_t* __restrict__ mcb, uint8_t* __restrict__ cixt) {
-    const int KS = F >> 6, tid = threadIdx.x, kt0 = blockIdx.x * 8;
-    const int64_t tb = blockIdx.y;
+__device__ __forceinline__ void vnm8_repack_body(int bx, int64_t tb, const uint16_t* __restrict__ vals, const uint8_t* __restrict__ meta,
+                                                 const uint8_t* __restrict__ colidx, int64_t T, int F, uint16_t* __restrict__ vcb,
+                                                 uint8_t* __restrict__ mcb, uint8_t* __restrict__ cixt) {
+    const int KS = F >> 6, tid = threadIdx.x, kt0 = bx * 8;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {                      // 64 tokens x 8 units x two 16-byte halves
         const int e = tid + 256 * i, half = e & 1, kt = kt0 + ((e >> 1) & 7);
@@ -166,9 +166,36 @@ __global__ void __launch_bounds__(256) vnm8_repack_kernel(const uint16_t* __rest
     }
 }
 
+// Both passes come with the transpose of the contraction's other operand, in one launch (on small shapes a launch of its own costs as much as the
+// pass): workgroups past the first nc x n_tb tiles take 64 x 64 tiles of it, tc per 64 rows.
+struct TransposeOf { const uint16_t* in; int64_t R, C, ld; uint16_t* out; int layout, tc; };
+__device__ __forceinline__ void transpose_part(void* smem, int i, const TransposeOf& t) {
+    transpose_bf16_body(smem, i % t.tc, i / t.tc, 0, t.in, t.R, t.C, t.ld, t.out, t.layout, nullptr, 0, nullptr);
+}
+__global__ void __launch_bounds__(256) vnm8_repack_kernel(const uint16_t* __restrict__ vals, const uint8_t* __restrict__ meta, const uint8_t* __restrict__ colidx, int64_t T,
+                                                         int F, uint16_t* __restrict__ vcb, uint8_t* __restrict__ mcb, uint8_t* __restrict__ cixt, int nc, int n_own, TransposeOf t) {
+    __shared__ __attribute__((aligned(16))) unsigned char smem[kTransposeLds];
+    const int i = blockIdx.x;
+    if (i < n_own) vnm8_repack_body(i % nc, i / nc, vals, meta, colidx, T, F, vcb, mcb, cixt);
+    else transpose_part(smem, i - n_own, t);
+}
+template <bool KEPT>
+__global__ void __launch_bounds__(256) vnm_compact_t_kernel(const uint16_t* __restrict__ vals, const uint8_t* __restrict__ meta, const uint8_t* __restrict__ colidx, int64_t T,
+                                                           int64_t F, int logM, uint16_t* __restrict__ at, uint8_t* __restrict__ mask, int nc, int n_own, TransposeOf t) {
+    __shared__ __attribute__((aligned(16))) unsigned char smem[kCompactLds];
+    static_assert(kCompactLds >= kTransposeLds, "either part");
+    const int i = blockIdx.x;
+    if (i < n_own) vnm_compact_t_body<KEPT>(smem, i % nc, i / nc, vals, meta, colidx, T, F, logM, at, mask);
+    else transpose_part(smem, i - n_own, t);
+}
+static int64_t transpose_tiles(TransposeOf* t) { t->tc = (int)(t->C / 64); return t->in ? t->C / 64 * (t->R / 64) : 0; }
+
 hipError_t launch_vnm8_repack(const uint16_t* vals, const uint8_t* meta, const uint8_t* colidx, int64_t T, int64_t F, uint16_t* vcb, uint8_t* mcb,
-                              uint8_t* cixt, hipStream_t s) {
-    hipLaunchKernelGGL(vnm8_repack_kernel, dim3((unsigned)((F + 511) / 512), (unsigned)(T / 64)), dim3(256), 0, s, vals, meta, colidx, T, (int)F, vcb, mcb, cixt);
+                              uint8_t* cixt, const uint16_t* W, int64_t R, int64_t C, int64_t ld, uint16_t* wt, hipStream_t s) {
+    TransposeOf t = {W, R, C, ld, wt, 0, 0};
+    const int64_t nc = (F + 511) / 512, own = nc * (T / 64), n = own + transpose_tiles(&t);
+    if (n >= ((int64_t)1 << 31)) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(vnm8_repack_kernel, dim3((unsigned)n), dim3(256), 0, s, vals, meta, colidx, T, (int)F, vcb, mcb, cixt, (int)nc, (int)own, t);
     return hipGetLastError();
 }
 
@@ -181,13 +208,14 @@ hipError_t launch_vnm_to_24(const uint16_t* vals, const uint8_t* meta, const uin
 }
 
 hipError_t launch_vnm_compact_t(const uint16_t* vals, const uint8_t* meta, const uint8_t* colidx, int64_t T, int64_t F, int M, int kept, uint16_t* at,
-                                uint8_t* mask, hipStream_t s) {
+                                uint8_t* mask, const uint16_t* G, int64_t N, uint16_t* gt, hipStream_t s) {
     const int logM = M == 8 ? 3 : M == 16 ? 4 : M == 32 ? 5 : M == 64 ? 6 : 0;
-    if (!logM || T / 64 > 65535 || (kept && F % (8 * M))) return hipErrorInvalidValue;
-    const int64_t width = kept ? 16 * M : 256;
-    dim3 grid((unsigned)((F + width - 1) / width), (unsigned)(T / 64));
-    if (kept) hipLaunchKernelGGL(vnm_compact_t_kernel<true>, grid, dim3(256), 0, s, vals, meta, colidx, T, F, logM, at, mask);
-    else hipLaunchKernelGGL(vnm_compact_t_kernel<false>, grid, dim3(256), 0, s, vals, meta, colidx, T, F, logM, at, mask);
+    if (!logM || (kept && F % (8 * M))) return hipErrorInvalidValue;
+    TransposeOf t = {G, T, N, N, gt, kept ? 2 : 1, 0};
+    const int64_t width = kept ? 16 * M : 256, nc = (F + width - 1) / width, own = nc * (T / 64), n = own + transpose_tiles(&t);
+    if (n >= ((int64_t)1 << 31)) return hipErrorInvalidValue;
+    if (kept) hipLaunchKernelGGL(vnm_compact_t_kernel<true>, dim3((unsigned)n), dim3(256), 0, s, vals, meta, colidx, T, F, logM, at, mask, (int)nc, (int)own, t);
+    else hipLaunchKernelGGL(vnm_compact_t_kernel<false>, dim3((unsigned)n), dim3(256), 0, s, vals, meta, colidx, T, F, logM, at, mask, (int)nc, (int)own, t);
     return hipGetLastError();
 }
 
