@@ -796,7 +796,7 @@ int venom_expert_matmul(const sffn_cfg* cfg, const int64_t* seg_offsets, const u
         TailFill tf;
         tf.add(vals, Kc, 0); tf.add(meta, Kc / 8, 0x44);
         if (y1c) tf.add(y1c, Kc * 2, 0);
-        LAUNCH(launch_fill_tail_rows(tf, nullptr, seg_offsets[E], cap, cap - seg_offsets[E], s), "venom_expert_matmul/clear");
+        LAUNCH(launch_fill_tail_rows(tf, seg_offsets[E], cap, s), "venom_expert_matmul/clear");
     }
     VnmEpilogue ep;
     ep.mode = 3; ep.store_dense = y1c ? 1 : 0; ep.vals = vals; ep.meta = meta; ep.perm = perm;
@@ -808,7 +808,7 @@ int venom_expert_matmul(const sffn_cfg* cfg, const int64_t* seg_offsets, const u
 namespace {
 struct RouterLayout {
     sffn_router_layout pub;
-    size_t xpt, xb, dypt, dyb, w1cv, w1cm, w1cvb, w1cmb, w2t, w2cv, w2cm, w2cvb, w2cmb, at, avb, amb, w2e, w1et, total;
+    size_t xpt, xb, dypt, dyb, w1cvb, w1cmb, dw2t, w2cvb, w2cmb, at, avb, amb, w2e, w1et, total;
 };
 bool make_router_layout(const sffn_cfg* c, RouterLayout* L) {
     if (!c || c->T <= 0 || !mult64(c->D) || !mult64(c->F) || !vnm_ok(c->V, c->M)) return false;
@@ -821,9 +821,9 @@ bool make_router_layout(const sffn_cfg* c, RouterLayout* L) {
     L->pub.dy2c = take(rows * Kc * 2);     L->pub.dvals = take(rows * Kc);
     L->xpt = take(rows * D * 2);  L->xb = take(rows * D * 2);
     L->dypt = take(rows * D * 2); L->dyb = take(rows * D * 2);
-    L->w1cv = take(F * D); L->w1cm = take(F * D / 8); L->w1cvb = take(F * D); L->w1cmb = take(F * D / 8);
-    L->w2t = take(F * D * 2);
-    L->w2cv = take(F * D); L->w2cm = take(F * D / 8); L->w2cvb = take(F * D); L->w2cmb = take(F * D / 8);
+    L->w1cvb = take(F * D); L->w1cmb = take(F * D / 8);
+    L->dw2t = take(F * D * 2);
+    L->w2cvb = take(F * D); L->w2cmb = take(F * D / 8);
     L->at = take(rows * Kc * 2);
     L->avb = take(rows * Kc); L->amb = take(rows * Kc / 8);     // packed activation (y2, then dy1) in the blocked operand layout
     L->w2e = take(F * D * 2);                                    // per expert: its slice of W2 as [D, Kc], blocked (eq. (3))
@@ -845,6 +845,9 @@ int sffn_router_workspace_layout(const sffn_cfg* cfg, sffn_router_layout* out) {
     *out = L.pub;
     return SFFN_OK;
 }
+
+// The step's preparing passes: all in one launch while X, dY, W1 and W2 together stay below 96 MiB, else in three parts (X and W1 | W2 | dY)
+static inline bool prologue_together(int64_t T, int64_t D, int64_t F, int64_t E) { return 2 * (2 * T * D + 2 * E * F * D) < ((int64_t)96 << 20); }
 
 // The router's training step.  The run offsets come either as a host array (validated here, passed to the kernels by value)
 // or as a device array written earlier on the same stream by this library's own grouping kernels (seg_dev).
@@ -896,46 +899,51 @@ static int run_router_step(const sffn_cfg* cfg, const int64_t* seg_offsets, cons
     uint8_t* colidx = ws + L.pub.colidx;           uint16_t* dy2c = (uint16_t*)(ws + L.pub.dy2c);   uint16_t* dvals = (uint16_t*)(ws + L.pub.dvals);
     uint16_t* xpt = (uint16_t*)(ws + L.xpt);   uint16_t* xb = (uint16_t*)(ws + L.xb);
     uint16_t* dypt = (uint16_t*)(ws + L.dypt); uint16_t* dyb = (uint16_t*)(ws + L.dyb);
-    uint16_t* w1cv = (uint16_t*)(ws + L.w1cv); uint8_t* w1cm = ws + L.w1cm; uint16_t* w1cvb = (uint16_t*)(ws + L.w1cvb); uint8_t* w1cmb = ws + L.w1cmb;
-    uint16_t* w2t = (uint16_t*)(ws + L.w2t);
-    uint16_t* w2cv = (uint16_t*)(ws + L.w2cv); uint8_t* w2cm = ws + L.w2cm; uint16_t* w2cvb = (uint16_t*)(ws + L.w2cvb); uint8_t* w2cmb = ws + L.w2cmb;
+    uint16_t* w1cvb = (uint16_t*)(ws + L.w1cvb); uint8_t* w1cmb = ws + L.w1cmb;
+    uint16_t* dw2t = (uint16_t*)(ws + L.dw2t);
+    uint16_t* w2cvb = (uint16_t*)(ws + L.w2cvb); uint8_t* w2cmb = ws + L.w2cmb;
     uint16_t* at = (uint16_t*)(ws + L.at);
     uint16_t* avb = (uint16_t*)(ws + L.avb); uint8_t* amb = ws + L.amb;
     uint16_t* w2e = (uint16_t*)(ws + L.w2e); uint16_t* w1et = (uint16_t*)(ws + L.w1et);
-    uint16_t* dw2t = w2t;                               // eq. (5)'s transposed result: W2.T is only needed while the weights are prepared
-    // SFFN_FLAG_WEIGHTS_PACKED: the five weight-preparation launches (all in the forward half) are skipped; the workspace still holds
+    // SFFN_FLAG_WEIGHTS_PACKED: the weights' preparation (all in the forward half) is skipped; the workspace still holds
     // what they wrote for the previous call (Section 3.4: weights are converted once per optimizer step)
     const bool packed = (cfg->flags & SFFN_FLAG_WEIGHTS_PACKED) != 0;
 
     if (g_prof_on) { g_prof_n = 0; (void)hipEventRecord(g_prof_ev[0], s); }
     // ---- Alg. 1 with Alg. 3 as the sparsifier ---------------------------------------------------------------------
-    if (fwd) STAGE(launch_transpose(X, rows, D, D, xpt, 0, xb, s, 1, 0, perm), "router/X[perm].T");     // permuted rows: transposed (eq. (8)) and blocked (eq. (1))
-    if (fwd && !packed) STAGE(launch_prune24_step(W1, F, D, D, 0, cfg->mode, w1cv, w1cm, w1cvb, w1cmb, nullptr, s, 1, M), "router/prune24(W1)");
-    if (fwd) STAGE(launch_venom_colidx(g1, rows, F / M, colidx, s), "router/colidx");
-    if (fwd) {   // rows past the last run are padding that no contraction writes: one launch clears them in the five row-indexed outputs
-        TailFill tf;
-        tf.add(vals, Kc, 0); tf.add(meta, Kc / 8, 0x44); tf.add(y1c, Kc * 2, 0); tf.add(dy2c, Kc * 2, 0); tf.add(dvals, Kc, 0);
-        if (seg_dev) LAUNCH(launch_fill_tail_rows(tf, seg_dev + E, 0, rows, 64 * (E + 1), s), "router/clear");      // at most 64 (E + 1) such rows
-        else if (used < rows) LAUNCH(launch_fill_tail_rows(tf, nullptr, used, rows, rows - used, s), "router/clear");
+    RouterPrologueArgs pro = {};
+    pro.rows = (int)rows; pro.D = (int)D; pro.F = (int)F; pro.logM = logM; pro.mode = cfg->mode; pro.perm = perm; pro.seg = g1;
+    if (fwd) {
+        pro.X = X; pro.xt = xpt; pro.xb = xb;           // permuted rows: transposed (eq. (8)) and blocked (eq. (1))
+        pro.colidx = colidx;
+        // rows past the last run are padding that no contraction writes (device table: at most 64 (E + 1) of them)
+        pro.max_tail = (int)(seg_dev ? 64 * (E + 1) : rows - used);
+        pro.tail.add(vals, Kc, 0); pro.tail.add(meta, Kc / 8, 0x44); pro.tail.add(y1c, Kc * 2, 0); pro.tail.add(dy2c, Kc * 2, 0); pro.tail.add(dvals, Kc, 0);
     }
+    if (fwd && !packed) {
+        pro.W1 = W1; pro.w1vb = w1cvb; pro.w1mb = w1cmb; pro.w1t = w1et;
+        pro.W2 = W2; pro.w2vb = w2cvb; pro.w2mb = w2cmb; pro.w2e = w2e;
+    }
+    if (bwd) { pro.dY = dY; pro.dyt = dypt; pro.dyb = dyb; }
+    // one launch for small inputs, else each part right before its readers, as in the plain step
+    const bool together = prologue_together(rows, D, F, 1);
+    RouterPrologueArgs p_w2 = pro, p_dy = pro;
+    p_w2.X = p_w2.dY = p_w2.W1 = nullptr; p_w2.colidx = nullptr; p_w2.tail.n = 0;
+    p_dy.X = p_dy.W1 = p_dy.W2 = nullptr; p_dy.colidx = nullptr; p_dy.tail.n = 0;
+    if (!together) { pro.dY = nullptr; pro.W2 = nullptr; }
+    if (together || fwd) STAGE(launch_router_prologue(pro, s), "router/prologue");
     // Inside a run every 64-row block keeps the same columns, so eqs. (3), (7) are plain grouped 2:4 contractions of the
     // packed [rows, Kc] activation with the expert's own [D, Kc] slice of W2 / W1.T (256 x 256 tiles; gathering rows per
     // 64-row block would re-read the same lines from every CU at once)
     if (fwd) {
         VnmEpilogue ep;
-        ep.mode = 3; ep.store_dense = 1; ep.vals = vals; ep.meta = meta; ep.perm = perm; ep.logM = logM; ep.v24 = avb; ep.m24 = amb;
+        ep.mode = 3; ep.store_dense = 1; ep.vals = vals; ep.meta = meta; ep.perm = perm; ep.logM = logM; ep.v24 = avb; ep.m24 = amb; ep.at = at; ep.at_ld = rows;
         STAGE(launch_gemm_vnm_epilogue(w1cvb, w1cmb, xb, b1, Kc, rows, D, y1c, ep, s, &g1), "router/y1c+sqrelu+2:4");    // eqs. (1), (2), Section 2.3
     }
-    if (fwd && !packed) {       // the rest of the weight preparation, Alg. 2 line 2 included: the backward half prepares nothing
-        STAGE(launch_transpose(W2, D, F, F, w2t, 0, nullptr, s), "router/W2.T");
-        STAGE(launch_transpose(w2t, Kc, D, D, w2e, 1, nullptr, s, E, M), "router/W2[:,e]");
-        STAGE(launch_prune24_step(w2t, F, D, D, 0, cfg->mode, w2cv, w2cm, w2cvb, w2cmb, nullptr, s, 1, M), "router/prune24(W2.T)");
-        STAGE(launch_transpose(W1, Kc, D, D, w1et, 1, nullptr, s, E, M), "router/W1[e].T");
-    }
+    if (fwd && !packed && !together) STAGE(launch_router_prologue(p_w2, s), "router/prepare(W2)");
     if (fwd) STAGE(launch_spmm_blocked(avb, amb, w2e, nullptr, rows, D, Kc, 0, Y3, D, s, &g0), "router/y3");                       // eq. (3)
     // ---- Alg. 2 ------------------------------------------------------------------------------------------------------
-    if (bwd) STAGE(launch_transpose(dY, rows, D, D, dypt, 0, dyb, s, 1, 0, perm), "router/dY[perm].T");
-    if (bwd) STAGE(launch_venom_expand_t_compact(vals, meta, rows, Kc, at, s), "router/expand(y2)");
+    if (bwd && !together) STAGE(launch_router_prologue(p_dy, s), "router/dY[perm].T");
     // eq. (5) is computed as dW2.T [F, D] (whole 2 D-byte rows per hidden unit) and transposed: writing dW2 [D, F] directly
     // would scatter 8-byte pieces M hidden units apart
     if (bwd) STAGE(launch_gemm_nt(0, at, nullptr, dypt, nullptr, Kc, D, rows, 0, dw2t, D, s, &g2), "router/dW2.T");                 // eq. (5)
@@ -944,11 +952,10 @@ static int run_router_step(const sffn_cfg* cfg, const int64_t* seg_offsets, cons
         GemmGroup g4 = g1;
         g4.bias_stride = 0;
         VnmEpilogue ep;
-        ep.mode = 4; ep.store_dense = (cfg->flags & SFFN_FLAG_KEEP_DENSE) ? 1 : 0; ep.vals = dvals; ep.meta = meta; ep.ykept = y1c; ep.v24 = avb;
+        ep.mode = 4; ep.store_dense = (cfg->flags & SFFN_FLAG_KEEP_DENSE) ? 1 : 0; ep.vals = dvals; ep.meta = meta; ep.ykept = y1c; ep.v24 = avb; ep.at = at; ep.at_ld = rows;
         STAGE(launch_gemm_vnm_epilogue(w2cvb, w2cmb, dyb, nullptr, Kc, rows, D, dy2c, ep, s, &g4), "router/dy2c+dsqrelu");
     }
     if (bwd) STAGE(launch_spmm_blocked(avb, amb, w1et, nullptr, rows, D, Kc, 0, dX, D, s, &g0), "router/dX");                       // eq. (7)
-    if (bwd) STAGE(launch_venom_expand_t_compact(dvals, meta, rows, Kc, at, s), "router/expand(dy1)");
     if (bwd) STAGE(launch_gemm_nt(0, at, nullptr, xpt, nullptr, Kc, D, rows, 0, dW1, D, s, &g2), "router/dW1");                    // eq. (8)
     return SFFN_OK;
 }
@@ -1038,8 +1045,6 @@ int ffn_router_full_backward(const sffn_cfg* cfg, const uint16_t* dY, uint16_t* 
     return run_router_full(cfg, nullptr, nullptr, nullptr, nullptr, nullptr, dY, nullptr, dX, dW1, dW2, workspace, ws_bytes, stream, 2);
 }
 
-// The step's preparing passes: all in one launch while X, dY, W1 and W2 together stay below 96 MiB, else in three parts (X and W1 | W2 | dY)
-static inline bool prologue_together(int64_t T, int64_t D, int64_t F, int64_t E) { return 2 * (2 * T * D + 2 * E * F * D) < ((int64_t)96 << 20); }
 static inline void split_prologue(const PrologueArgs& all, PrologueArgs (&part)[3]) {
     part[0] = part[1] = part[2] = all;
     part[0].W2 = nullptr; part[0].dY = nullptr;

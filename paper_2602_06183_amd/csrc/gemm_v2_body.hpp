@@ -451,6 +451,31 @@ __device__ __forceinline__ void gemm_nt_v2_body(unsigned char* __restrict__ smem
             tok_ok[b] = true;
             if (EPI == 3) { int j = t0 + b * 32 + l32; j = j < Rb ? j : Rb - 1; tok_ok[b] = ep.perm[j] >= 0; }
         }
+        // EPI 3, 4: the survivors as the dense transposed matrix at[f, t] (row length ep.at_ld), zeros at the dropped positions: the A operand of the
+        // experts' weight gradients.  The half tile is turned in place (its rows have been read): two tokens make a word of one of the four rows of
+        // the lane's group; the 16-byte chunks of a row are permuted by (row / 16) % 4 so that the 64 words of a store fall into 64 LDS banks.
+        // (As a pass of its own over the packed matrix: 15 us at 8192 rows, 2048 columns and 4 experts.)
+        auto transposed_out = [&](const uint32_t (&v)[16], const uint32_t (&nib)[2], int f0, bool valid) {
+            const int g = lane & 15;
+            wave_lds_sync();
+#pragma unroll
+            for (int p = 0; p < 8; ++p) {
+                const uint32_t n = nib[p >> 2] >> (8 * (p & 3)), a0 = n & 3u, a1 = (n >> 2) & 3u, b0 = (n >> 4) & 3u, b1 = (n >> 6) & 3u;
+#pragma unroll
+                for (uint32_t c = 0; c < 4; ++c) {
+                    const uint32_t lo = c == a0 ? v[2 * p] & 0xFFFFu : c == a1 ? v[2 * p] >> 16 : 0u;
+                    const uint32_t hi = c == b0 ? v[2 * p + 1] << 16 : c == b1 ? v[2 * p + 1] & 0xFFFF0000u : 0u;
+                    *reinterpret_cast<uint32_t*>(scratch + (4 * g + c) * EP + ((p ^ (g >> 2)) * 4 + (lane >> 4)) * 4) = lo | hi;
+                }
+            }
+            wave_lds_sync();
+#pragma unroll
+            for (int p = 0; p < 8; ++p) {
+                const int row = p * 8 + (lane >> 3), ch = lane & 7;
+                if (valid)
+                    *reinterpret_cast<uint4*>(ep.at + (int64_t)(f0 + row) * ep.at_ld + t0 + ch * 8) = *reinterpret_cast<const uint4*>(scratch + row * EP + (ch ^ ((row >> 4) & 3)) * 16);
+            }
+        };
 #pragma unroll
         for (int h = 0; h < NH; ++h) {
             const int f0 = i0 + wm * WM + h * 64;
@@ -499,14 +524,16 @@ __device__ __forceinline__ void gemm_nt_v2_body(unsigned char* __restrict__ smem
                 }
             }
             if (EPI == 3) {
-                // lane = (token t = lane / 16 + 4 it, group of four compact columns g = lane % 16): eq. (2), then the 2:4 rule
+                // lane = (tokens t = 2 (lane / 16) + 8 (it / 2) + it % 2, group of four compact columns g = lane % 16): eq. (2), then the 2:4 rule
                 const int g = lane & 15;
+                uint32_t vv[16], nn[2] = {0u, 0u};
 #pragma unroll
                 for (int it = 0; it < 16; ++it) {
-                    const int t = (lane >> 4) + 4 * it;
+                    const int t = 2 * (lane >> 4) + 8 * (it >> 1) + (it & 1);
                     const uint2 w = *reinterpret_cast<const uint2*>(scratch + t * EP + g * 8);
                     uint32_t nib;
                     const uint32_t v = select24<false>(sqrelu16(w.x & 0xFFFFu), sqrelu16(w.x >> 16), sqrelu16(w.y & 0xFFFFu), sqrelu16(w.y >> 16), nib);
+                    vv[it] = v; nn[it >> 3] |= nib << (4 * (it & 7));
                     uint32_t mw = nib | (row_shl<1>(nib) << 4);            // metadata of 8 groups -> one 32-bit store from every eighth lane
                     mw |= row_shl<2>(mw) << 8;
                     mw |= row_shl<4>(mw) << 16;
@@ -519,23 +546,24 @@ __device__ __forceinline__ void gemm_nt_v2_body(unsigned char* __restrict__ smem
                         }
                     }
                 }
+                if (ep.at) transposed_out(vv, nn, f0, valid);
             }
             if (EPI == 4) {
                 // eq. (6) on the compact tile: lane = (token, group of four compact columns); the two kept positions come from the
                 // forward pass's metadata, y1 from the stored compact y1c (ep.ykept); dy2 is the bf16-rounded tile in LDS
                 const int g = lane & 15;
                 uint2 yv[16];
-                uint32_t mb[16];
+                uint32_t mb[16], vv[16], nn[2] = {0u, 0u};
 #pragma unroll
                 for (int it = 0; it < 16; ++it) {
-                    const int t = (lane >> 4) + 4 * it;
+                    const int t = 2 * (lane >> 4) + 8 * (it >> 1) + (it & 1);
                     const bool ok = valid && t0 + t < Rb;
                     yv[it] = ok ? *reinterpret_cast<const uint2*>(ep.ykept + (int64_t)(t0 + t) * F + f0 + 4 * g) : make_uint2(0u, 0u);
                     mb[it] = ok ? ep.meta[(int64_t)(t0 + t) * (F / 8) + (f0 >> 3) + (g >> 1)] : 0x44u;
                 }
 #pragma unroll
                 for (int it = 0; it < 16; ++it) {
-                    const int t = (lane >> 4) + 4 * it;
+                    const int t = 2 * (lane >> 4) + 8 * (it >> 1) + (it & 1);
                     const uint2 w = *reinterpret_cast<const uint2*>(scratch + t * EP + g * 8);
                     const uint32_t nib = (mb[it] >> (4 * (g & 1))) & 0xFu, p0 = nib & 3u, p1 = nib >> 2;
                     const uint32_t d0 = ((p0 >> 1) ? w.y : w.x) >> (16 * (p0 & 1)), d1 = ((p1 >> 1) ? w.y : w.x) >> (16 * (p1 & 1));
@@ -546,7 +574,9 @@ __device__ __forceinline__ void gemm_nt_v2_body(unsigned char* __restrict__ smem
                         *reinterpret_cast<uint32_t*>(ep.vals + (int64_t)(t0 + t) * (F / 2) + (f0 >> 1) + 2 * g) = v;
                         *reinterpret_cast<uint32_t*>(ep.v24 + blk_off(t0 + t, (f0 >> 1) + 2 * g, F / 64)) = v;
                     }
+                    vv[it] = v; nn[it >> 3] |= nib << (4 * (it & 7));
                 }
+                if (ep.at) transposed_out(vv, nn, f0, valid);
             }
             if (GEN_F || GEN_B) {
                 // Blocks of M = 16 / 32 / 64 columns (Table 5): the wave's 64 tokens x 64 hidden units hold NB = 64 / M whole blocks.
@@ -891,7 +921,9 @@ template <> struct TileSel<true, 38> { using T128 = Tile<2, 2, 128, 2, 1>; using
 template <bool SPARSE, bool OUT_I_CONTIG, int EPI, bool BLOCKED, bool FP8>
 hipError_t launch_gemm_v2(const GemmV2Args& a, hipStream_t s, int tile = 0) {
     using Sel = TileSel<SPARSE, EPI>;
-    if (!tile) tile = pick_gemm_tile(a.Ra, a.Rb, a.K / (SPARSE ? 64 : 32), a.grp, BLOCKED ? 0.56f : 0.7f, SPARSE);
+    // a round of 128 tiles: the V:N:M epilogues (half of a tile's time at K = 2048) overlap with the other workgroup's main loop; without one it is the
+    // bytes from L2 that count (the router's eq. (3), 918 / 3564 tiles of K = 5504: 338 us on 256 tiles, 447 on 128; 288 / 1120 of K = 2048: 76 and 68)
+    if (!tile) tile = pick_gemm_tile(a.Ra, a.Rb, a.K / (SPARSE ? 64 : 32), a.grp, EPI != 0 ? 0.56f : 0.72f, SPARSE, EPI != 0 ? 1.0f : 0.6f);
     if (tile == 256) return launch_units<GemmV2Unit<SPARSE, OUT_I_CONTIG, EPI, BLOCKED, FP8, Tile256<SPARSE>>>(s, a);
     if (tile == 128) return launch_units<GemmV2Unit<SPARSE, OUT_I_CONTIG, EPI, BLOCKED, FP8, typename Sel::T128>>(s, a);
     // (the dense form has no 64 tile: its two users are the stand-alone vnm_wgrad and the router's weight gradients)

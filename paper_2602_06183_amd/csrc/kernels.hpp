@@ -29,6 +29,7 @@ struct VnmEpilogue {
     //        compact columns: outputs vals, meta; padding rows (perm < 0) come out as zeros; `out` = y1c [rows, F] if store_dense.
     // mode 4 (the same experts, backward): the tile of dy2c meets (meta, ykept = the stored y1c [rows, F]) and becomes dy1 in y2's
     //        slots: outputs vals (canonical) and v24 (the same, blocked); `out` = dy2c if store_dense.
+    //        Both, with `at`: the survivors as a dense transposed matrix [F, at_ld tokens], row-major, zeros at the dropped positions.
     // mode 5 / 6 (blocks of M = 2^logM = 16, 32, 64 columns, Table 5): as modes 1 / 2 with outputs vals, meta, colidx (mode 5), ykept
     //        ([T/64][F/64][64 tokens][64/M blocks] pairs), `at` + kmask (mode 5) exactly as for modes 1 / 2 (a block of M columns keeps 4, so no
     //        group of 8 hidden units keeps more than 4); no v24 / m24 (eqs. (3), (7) gather the kept rows of the dense operand from the
@@ -43,6 +44,7 @@ struct VnmEpilogue {
     float* amax = nullptr;          // fp8 modes 1 / 2: amax slots for the survivors' magnitudes (y2 / dy1)
     // modes 1 / 2: the operands of the V:2:8 activation GEMM (gemm_vnm8.hip; layouts: vcb_off, mcb_off, cixt_off in common.hpp, fp8: vcb8_off, ...):
     // vcb = the survivors (both modes; fp8: their codes), mcb = their metadata and cixt = the regrouped kept-column offsets (mode 1; mode 2 reuses them)
+    int64_t at_ld = 0;
     int at_kept = 0;                // modes 5 / 6, bf16, M = 32, 64: `at` receives only the kept rows, in the order of gemm_wgrad_wide_body.hpp, and `kmask` (mode 5) that kernel's column offsets
     uint16_t* vcb = nullptr;
     uint8_t* mcb = nullptr;
@@ -116,10 +118,12 @@ hipError_t launch_step_prologue(const PrologueArgs& a, hipStream_t s);
 // every slot of the chip: 256 tiles of 256 x 256 (one workgroup per CU), 512 of 128 x 128 (two per CU).  A round of small tiles takes `w128` of a round of
 // large ones (measured, see below: more bytes from L2 per product), so the large tile wins on whole rounds and the small one where the
 // outputs do not fill the chip or leave the last round nearly empty.  64 x 64 tiles split the contraction over their four wavefronts: best
-// while there are at most `most64` of them and the contraction is long enough to be worth splitting.
-inline int pick_tile(unsigned n256, unsigned n128, unsigned n64, int steps, float w128, unsigned most64, int least_steps) {
+// while there are at most `most64` of them and the contraction is long enough to be worth splitting.  last: what a last round of small tiles takes, as a
+// part of a full one, when it leaves every workgroup a CU of its own.
+inline int pick_tile(unsigned n256, unsigned n128, unsigned n64, int steps, float w128, unsigned most64, int least_steps, float last = 1.0f) {
     if (n64 <= most64 && steps >= least_steps) return 64;
-    return w128 * (float)((n128 + 511) / 512) < (float)((n256 + 255) / 256) ? 128 : 256;
+    const unsigned rest = n128 % 512;
+    return w128 * ((float)(n128 / 512) + (rest == 0 ? 0.0f : rest <= 256 ? last : 1.0f)) < (float)((n256 + 255) / 256) ? 128 : 256;
 }
 
 // tiles along the tokens when they come in `groups` segments (0: one), taken as equally long: a host and a device segment table choose alike
@@ -130,11 +134,11 @@ inline int64_t token_tiles(int64_t T, int groups, int64_t edge) {
 // gemm_v2 (i x j outputs).
 // Eq. (1) / (4) at T = D = 2048, F = 8192 (256 / 1024 tiles): 55 / 47 us on 256 tiles, 61 / 54 on 128; T = 1024, D = 1408, F = 4928 (80 / 312): 39 / 30 and
 // 26 / 23; T = 64, D = 2048, F = 8192 (32 / 64 / 128): 43 / 33, 21 / 18, and 17 / 14 on 64 tiles
-inline int pick_gemm_tile(int64_t Ra, int64_t Rb, int steps, const GemmGroup& g, float w128, bool split) {
+inline int pick_gemm_tile(int64_t Ra, int64_t Rb, int steps, const GemmGroup& g, float w128, bool split, float last = 1.0f) {
     auto tiles = [&](int64_t edge) {
         return (unsigned)(token_tiles(Ra, g.n && g.role == 0 ? g.n : 0, edge) * token_tiles(Rb, g.n && g.role == 1 ? g.n : 0, edge) * (g.role == 2 && g.n ? g.n : 1));
     };
-    return pick_tile(tiles(256), tiles(128), tiles(64), steps, w128, split ? 256 : 0, 16);
+    return pick_tile(tiles(256), tiles(128), tiles(64), steps, w128, split ? 256 : 0, 16, last);
 }
 // V:2:8 activation GEMM.  T = 8192, N = 2048, F = 8192 (256 / 1024 tiles): 107 us on 256 tiles, 148 on 128; T = 2048 (64 / 256): 85 and 54; T = 1024,
 // N = 1408, F = 4928 (24 / 88 / 352): 55, 33, and 29 on 64 tiles; T = 64, N = 2048, F = 8192 (8 / 16 / 32): 83, 49, 28
@@ -238,12 +242,8 @@ hipError_t launch_vnm_to_24(const uint16_t* vals, const uint8_t* meta, const uin
 // the layout that kernel reads
 hipError_t launch_vnm_compact_t(const uint16_t* vals, const uint8_t* meta, const uint8_t* colidx, int64_t T, int64_t F, int M, int kept, uint16_t* at,
                                 uint8_t* mask, const uint16_t* G, int64_t N, uint16_t* gt, hipStream_t s);
-// batch > 1: `batch` matrices [R, C] (ld = C) back to back, transposed one by one.
-// cluster_M (with batch = M / 4 experts, R = hidden units per expert): matrix e reads the rows of `in` that belong to expert e,
-// row r of it = row (r / 4) * M + 4 e + r % 4 of the one [F, C] source (Section 3.3's expert-major order).
-// in_perm (batch = 1): row r of the [R, C] matrix is row in_perm[r] of `in` (a negative entry: a zero row).
-hipError_t launch_transpose(const uint16_t* in, int64_t R, int64_t C, int64_t ld, uint16_t* out, int blocked, uint16_t* out_same,
-                            hipStream_t s, int batch = 1, int cluster_M = 0, const int32_t* in_perm = nullptr);
+// blocked: out in the blocked operand layout (1) or in the order of lane_off (2, common.hpp); out_same: also a blocked copy of `in`
+hipError_t launch_transpose(const uint16_t* in, int64_t R, int64_t C, int64_t ld, uint16_t* out, int blocked, uint16_t* out_same, hipStream_t s);
 
 // C[i, j] = sum_k A[i, k] * B[j, k]  (both operands K-contiguous).
 //   sparse_a: A given as 2:4 packed (a_vals [Ra, K/2], a_meta [Ra, K/8]) and multiplied on the
@@ -271,7 +271,6 @@ hipError_t launch_venom_route(const uint16_t* X, const uint16_t* means, int64_t 
 hipError_t launch_venom_permute(const int32_t* expert, int64_t T, int E, int64_t cap, int32_t* blockcnt, int32_t* seg, int32_t* perm,
                                 int32_t* row_of_token, hipStream_t s);
 hipError_t launch_venom_gather_x(const uint16_t* X, const int32_t* perm, int64_t cap, int64_t D, uint16_t* xb, hipStream_t s);
-hipError_t launch_venom_expand_t_compact(const uint16_t* vals, const uint8_t* meta, int64_t rows, int64_t Kc, uint16_t* at, hipStream_t s);
 struct TailFill {                   // up to five arrays of `rows` rows whose tail rows get a fill word
     int n = 0;
     uint32_t* p[5] = {nullptr, nullptr, nullptr, nullptr, nullptr};
@@ -279,8 +278,20 @@ struct TailFill {                   // up to five arrays of `rows` rows whose ta
     uint32_t v[5] = {0, 0, 0, 0, 0};
     void add(void* ptr, int64_t row_bytes, uint8_t byte) { p[n] = (uint32_t*)ptr; row_words[n] = row_bytes / 4; v[n] = 0x01010101u * byte; ++n; }
 };
-hipError_t launch_fill_tail_rows(const TailFill& f, const int32_t* first_dev, int64_t first_imm, int64_t rows, int64_t max_tail_rows,
-                                 hipStream_t s);
+hipError_t launch_fill_tail_rows(const TailFill& f, int64_t first, int64_t rows, hipStream_t s);
+// Everything the router's step prepares, in one launch (router.hip): permuted X and dY, row-major transposed and blocked; the experts' weights: W1 and
+// W2.T pruned and packed expert-major (blocked), and the experts' slices of W2 and W1.T as [D, 4 F / M] matrices (blocked); colidx and the rows past
+// the last run.  Absent parts: null X / dY / W1 / W2 / colidx.  seg: the run offsets (seg or seg_dev); at most max_tail rows lie past the last run.
+struct RouterPrologueArgs {
+    int rows, D, F, logM, mode;
+    const int32_t* perm;
+    const uint16_t *X, *dY; uint16_t *xt, *xb, *dyt, *dyb;
+    const uint16_t* W1; uint16_t *w1vb, *w1t; uint8_t* w1mb;
+    const uint16_t* W2; uint16_t *w2vb, *w2e; uint8_t* w2mb;
+    uint8_t* colidx; TailFill tail; int max_tail;
+    GemmGroup seg;
+};
+hipError_t launch_router_prologue(const RouterPrologueArgs& a, hipStream_t s);
 hipError_t launch_venom_colidx(const GemmGroup& g, int64_t cap, int64_t groups, uint8_t* colidx, hipStream_t s);
 
 // fp8 operands (fp8.hip; Section 3.4's closing paragraph): E4M3 codes, inv = 1 / scale; amax (optional, device float) receives the largest

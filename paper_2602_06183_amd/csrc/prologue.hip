@@ -26,8 +26,8 @@ __global__ void __launch_bounds__(256) step_prologue_kernel(PrologueArgs a, int 
     }
     b -= n_w1;
     const int gx = a.D / 64;
-    if (b < n_x) transpose_bf16_body(smem, b % gx, b / gx, 0, a.X, a.T, a.D, a.D, a.xt, a.t_layout, a.xb, 0, nullptr);
-    else { b -= n_x; transpose_bf16_body(smem, b % gx, b / gx, 0, a.dY, a.T, a.D, a.D, a.dyt, a.t_layout, a.dyb, 0, nullptr); }
+    if (b < n_x) transpose_bf16_body(smem, b % gx, b / gx, a.X, a.T, a.D, a.D, a.xt, a.t_layout, a.xb, nullptr);
+    else { b -= n_x; transpose_bf16_body(smem, b % gx, b / gx, a.dY, a.T, a.D, a.D, a.dyt, a.t_layout, a.dyb, nullptr); }
 }
 
 hipError_t launch_step_prologue(const PrologueArgs& a, hipStream_t s) {

@@ -11,24 +11,17 @@ constexpr int kTransposeLds = 64 * (64 + 2) * 2, kPruneColsLds = 128 * (64 + 8) 
 // blocked = 2: out in the order of lane_off (common.hpp), out_same as for 1.
 // blocked = 1: out (the transpose) and, when given, out_same (a copy of `in`) are written in the blocked
 // operand layout instead of row-major.
-__device__ __forceinline__ void transpose_bf16_body(void* smem, int bx, int by, int bz, const uint16_t* __restrict__ in, int64_t R, int64_t C, int64_t ld,
-                                                            uint16_t* __restrict__ out, int blocked, uint16_t* __restrict__ out_same, int map_logM,
-                                                            const int32_t* __restrict__ in_perm) {
+// in_perm: row r of the matrix is row in_perm[r] of `in`; negative: a zero row.
+__device__ __forceinline__ void transpose_bf16_body(void* smem, int bx, int by, const uint16_t* __restrict__ in, int64_t R, int64_t C, int64_t ld,
+                                                    uint16_t* __restrict__ out, int blocked, uint16_t* __restrict__ out_same, const int32_t* __restrict__ in_perm) {
     uint16_t (*tile)[64 + 2] = reinterpret_cast<uint16_t (*)[64 + 2]>(smem);
     const int tid = threadIdx.x;
     const int64_t r0 = (int64_t)by * 64, c0 = (int64_t)bx * 64;
-    {   // batched form: matrix bz of a stack of [R, C] matrices (map_logM: all read the one source, see the launcher)
-        const int64_t m = (int64_t)bz * R * C;
-        if (!map_logM) in += m;
-        if (out) out += m;
-        if (out_same) out_same += m;
-    }
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
         const int e = tid + 256 * i, rr = e >> 3, seg = e & 7;
         int64_t rs = r0 + rr;
-        if (map_logM) rs = ((rs >> 2) << map_logM) + 4 * bz + (rs & 3);
-        if (in_perm) rs = in_perm[rs];                       // row r of the matrix is row in_perm[r] of `in`; negative: a zero row
+        if (in_perm) rs = in_perm[rs];
         uint4 w = make_uint4(0, 0, 0, 0);
         if (rs >= 0) w = *reinterpret_cast<const uint4*>(in + rs * ld + c0 + seg * 8);
         uint32_t* p = reinterpret_cast<uint32_t*>(&tile[rr][seg * 8]);

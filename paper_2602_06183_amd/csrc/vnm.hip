@@ -121,10 +121,9 @@ __device__ __forceinline__ void vnm_compact_t_body(void* smem, int bx, int64_t t
 }
 
 __global__ void __launch_bounds__(256) transpose_bf16_kernel(const uint16_t* __restrict__ in, int64_t R, int64_t C, int64_t ld,
-                                                            uint16_t* __restrict__ out, int blocked, uint16_t* __restrict__ out_same, int map_logM,
-                                                            const int32_t* __restrict__ in_perm) {
+                                                            uint16_t* __restrict__ out, int blocked, uint16_t* __restrict__ out_same) {
     __shared__ __attribute__((aligned(16))) unsigned char smem[kTransposeLds];
-    transpose_bf16_body(smem, blockIdx.x, blockIdx.y, blockIdx.z, in, R, C, ld, out, blocked, out_same, map_logM, in_perm);
+    transpose_bf16_body(smem, blockIdx.x, blockIdx.y, in, R, C, ld, out, blocked, out_same, nullptr);
 }
 
 hipError_t launch_dsqrelu_vnm(const uint16_t* dy2, const uint16_t* y1, const uint8_t* meta, const uint8_t* colidx, int64_t T,
@@ -170,7 +169,7 @@ __device__ __forceinline__ void vnm8_repack_body(int bx, int64_t tb, const uint1
 // pass): workgroups past the first nc x n_tb tiles take 64 x 64 tiles of it, tc per 64 rows.
 struct TransposeOf { const uint16_t* in; int64_t R, C, ld; uint16_t* out; int layout, tc; };
 __device__ __forceinline__ void transpose_part(void* smem, int i, const TransposeOf& t) {
-    transpose_bf16_body(smem, i % t.tc, i / t.tc, 0, t.in, t.R, t.C, t.ld, t.out, t.layout, nullptr, 0, nullptr);
+    transpose_bf16_body(smem, i % t.tc, i / t.tc, t.in, t.R, t.C, t.ld, t.out, t.layout, nullptr, nullptr);
 }
 __global__ void __launch_bounds__(256) vnm8_repack_kernel(const uint16_t* __restrict__ vals, const uint8_t* __restrict__ meta, const uint8_t* __restrict__ colidx, int64_t T,
                                                          int F, uint16_t* __restrict__ vcb, uint8_t* __restrict__ mcb, uint8_t* __restrict__ cixt, int nc, int n_own, TransposeOf t) {
@@ -219,15 +218,9 @@ hipError_t launch_vnm_compact_t(const uint16_t* vals, const uint8_t* meta, const
     return hipGetLastError();
 }
 
-hipError_t launch_transpose(const uint16_t* in, int64_t R, int64_t C, int64_t ld, uint16_t* out, int blocked, uint16_t* out_same,
-                            hipStream_t s, int batch, int cluster_M, const int32_t* in_perm) {
-    if (batch > 1 && ld != C) return hipErrorInvalidValue;
-    if (in_perm && (batch > 1 || cluster_M)) return hipErrorInvalidValue;
-    if (cluster_M && batch * 4 != cluster_M) return hipErrorInvalidValue;
-    const int logM = cluster_M == 8 ? 3 : cluster_M == 16 ? 4 : cluster_M == 32 ? 5 : cluster_M == 64 ? 6 : 0;
-    if (cluster_M && !logM) return hipErrorInvalidValue;
-    dim3 grid((unsigned)(C / 64), (unsigned)(R / 64), (unsigned)batch);
-    hipLaunchKernelGGL(transpose_bf16_kernel, grid, dim3(256), 0, s, in, R, C, ld, out, blocked, out_same, logM, in_perm);
+hipError_t launch_transpose(const uint16_t* in, int64_t R, int64_t C, int64_t ld, uint16_t* out, int blocked, uint16_t* out_same, hipStream_t s) {
+    dim3 grid((unsigned)(C / 64), (unsigned)(R / 64));
+    hipLaunchKernelGGL(transpose_bf16_kernel, grid, dim3(256), 0, s, in, R, C, ld, out, blocked, out_same);
     return hipGetLastError();
 }
 

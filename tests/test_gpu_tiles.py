@@ -9,7 +9,7 @@ import paper_2602_06183_amd as sffn
 from tests.test_gpu_fp8 import _check_fp8_step_against_oracle, _fp8_step_scales
 from tests.test_gpu_kernels import _check_wide_step_against_oracle, _teacher_forced_step_check
 from tests.util import assert_gemm_close, to_bits, to_dev
-from workload import bf16_bits_from_f32, make_ffn_inputs
+from workload import bf16_bits_from_f32, make_ffn_inputs, make_router_inputs
 
 pytestmark = pytest.mark.gpu
 
@@ -97,3 +97,12 @@ def test_standalone_weight_gradients(M, T, N, F):
     if M == 8:
         W = bf16_bits_from_f32(rng.standard_normal((N, F)).astype(np.float32))
         assert_gemm_close(to_bits(sffn.vnm_spmm(*a, to_dev(W), 0, 64, M)), oracle.vnm_spmm(*bits, W, 0, 64, M), "spmm")
+
+
+@pytest.mark.parametrize("T,M", [(1023, 8), (1024, 64), (1025, 16), (32768, 32), (32769, 32)])
+def test_grouping_at_the_edges_of_its_blocks(T, M):
+    inp = make_router_inputs(T, 64, 256, M, seed=T)
+    r = sffn.venom_route(to_dev(inp["X"]), to_dev(inp["means"]), M)
+    perm, seg = oracle.expert_permutation(to_bits(r["expert"]), M // 4)
+    assert r["seg"] == [int(v) for v in seg] and np.array_equal(to_bits(r["perm"]), perm)
+    assert np.array_equal(perm[to_bits(r["row_of_token"])], np.arange(T))
