@@ -242,7 +242,7 @@ int prune24_compress_prepared(const uint16_t* src, int64_t R, int64_t K, int64_t
     REQUIRE(aligned16(src) && aligned16(vals) && aligned16(meta) && aligned16(prepared), SFFN_EINVAL, "prune24_compress_prepared: pointers must be 16-byte aligned");
     REQUIRE(fits_int(R) && fits_int(K) && R / 16 < 65536 * 16, SFFN_EUNSUPPORTED, "prune24_compress_prepared: dimension too large");
     uint8_t* pb = (uint8_t*)prepared;
-    LAUNCH(launch_prune24_step(src, R, K, ld, 0, mode, vals, meta, (uint16_t*)pb, pb + up256((size_t)R * K), nullptr, (hipStream_t)stream),
+    LAUNCH(launch_prune24_step(src, R, K, ld, 0, mode, vals, meta, (uint16_t*)pb, pb + up256((size_t)R * K), (hipStream_t)stream),
            "prune24_compress_prepared");
     return SFFN_OK;
 }
@@ -789,7 +789,7 @@ int venom_expert_matmul(const sffn_cfg* cfg, const int64_t* seg_offsets, const u
     uint16_t* wvb = (uint16_t*)ws;                     ws += up256((size_t)F * D);
     uint8_t* wmb = ws;
     LAUNCH(launch_venom_gather_x(X, perm, cap, D, xb, s), "venom_expert_matmul/gather(X)");
-    LAUNCH(launch_prune24_step(W1, F, D, D, 0, cfg->mode, wv, wm, wvb, wmb, nullptr, s, 1, M), "venom_expert_matmul/prune24(W1)");
+    LAUNCH(launch_prune24_step(W1, F, D, D, 0, cfg->mode, wv, wm, wvb, wmb, s, M), "venom_expert_matmul/prune24(W1)");
     LAUNCH(launch_venom_colidx(g, cap, F / M, colidx, s), "venom_expert_matmul/colidx");
     // rows past the last run are never touched by the grouped contraction: clear them (they are padding)
     if (seg_offsets[E] < cap) {
@@ -1199,7 +1199,7 @@ static int run_step(const sffn_cfg* cfg, int n_experts, const int64_t* seg, cons
         uint16_t* w1t = w1tb;                            // W2.T (gathered route) or W1.T (plain-2:4 route), [F, D] / [D, F] row-major
         const VnmEpilogue plain;                         // eqs. (1), (4) on the blocked operands, dense output only
         STAGE(launch_transpose(X, T, D, D, xt, 0, xb, s), "step/X.T");
-        STAGE(launch_prune24_step(W1, F, D, D, 0, cfg->mode, w1v, w1m, w1vb, w1mb, nullptr, s), "step/prune24(W1)");
+        STAGE(launch_prune24_step(W1, F, D, D, 0, cfg->mode, w1v, w1m, w1vb, w1mb, s), "step/prune24(W1)");
         STAGE(launch_gemm_vnm_epilogue(w1vb, w1mb, xb, b1, F, T, D, y1, plain, s), "step/y1");                        // eq. (1)
         STAGE(launch_sqrelu_vnm_compress_m(y1, T, F, M, y2v, y2m, cix, s), "step/sqrelu_vnm_compress");               // eq. (2), Section 2.3
         // eqs. (3), (7): gather the kept rows of the dense operand (matrix work and traffic shrink with 4 / M); shapes the
@@ -1212,7 +1212,7 @@ static int run_step(const sffn_cfg* cfg, int n_experts, const int64_t* seg, cons
             STAGE(launch_vnm_to_24_m(y2v, y2m, cix, T, F, M, a24v, a24m, s), "step/to24(y2)");
             STAGE(launch_gemm_nt(1, a24v, a24m, W2, nullptr, T, D, F, 0, Y3, D, s), "step/y3");                       // eq. (3)
         }
-        STAGE(launch_prune24_step(W2, F, D, F, 1, cfg->mode, w2v, w2m, w2vb, w2mb, nullptr, s), "step/prune24(W2.T)");
+        STAGE(launch_prune24_step(W2, F, D, F, 1, cfg->mode, w2v, w2m, w2vb, w2mb, s), "step/prune24(W2.T)");
         // eq. (5) before eq. (4): the weight-gradient kernel is faster while dY.T is still in the last-level cache
         STAGE(launch_transpose(dY, T, D, D, dyt, 0, dyb, s), "step/dY.T");
         STAGE(launch_vnm_expand_t_m(y2v, y2m, cix, T, F, M, at, s), "step/expand(y2)");

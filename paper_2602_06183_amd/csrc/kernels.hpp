@@ -191,13 +191,10 @@ hipError_t launch_prune24(const uint16_t* src, int64_t R, int64_t K, int64_t ld,
                           uint8_t* meta, hipStream_t stream);
 hipError_t launch_dsqrelu_vnm(const uint16_t* dy2, const uint16_t* y1, const uint8_t* meta, const uint8_t* colidx,
                               int64_t T, int64_t F, uint16_t* dvals, hipStream_t s);
-// 2:4 prune-and-pack for the fused step: canonical outputs plus the blocked copies the GEMMs read;
-// trans = 1 can also emit a blocked copy of the source matrix itself (rows = its rows, K = its columns).
-// batch > 1 (trans = 1 only): `batch` matrices of the same shape, consecutive in every argument.
+// 2:4 prune-and-pack: canonical outputs plus the blocked copies the GEMMs read
 hipError_t launch_prune24_step(const uint16_t* src, int64_t R, int64_t K, int64_t ld, int trans, int mode, uint16_t* vals,
-                               uint8_t* meta, uint16_t* vblk, uint8_t* mblk, uint16_t* src_blk, hipStream_t stream, int batch = 1,
-                               int cluster_M = 0,    // cluster_M (trans = 0): rows come out expert-major, see prune24.hip
-                               uint16_t* src_t = nullptr);   // trans = 1: also the unpruned transposed source [R, K] row-major
+                               uint8_t* meta, uint16_t* vblk, uint8_t* mblk, hipStream_t stream,
+                               int cluster_M = 0);    // cluster_M (trans = 0): rows come out expert-major, see scans.hpp
 // vnm_general.hip: the stand-alone compressor for M in {8, 16, 32, 64}, and eq. (6) / 2:4 re-expression / transposed expansion for M in {16, 32, 64}.
 hipError_t launch_sqrelu_vnm_compress_m(const uint16_t* y1, int64_t T, int64_t F, int M, uint16_t* vals, uint8_t* meta, uint8_t* colidx,
                                         hipStream_t s);

@@ -15,7 +15,7 @@ __global__ void __launch_bounds__(256) step_prologue_kernel(PrologueArgs a, int 
     if (b < n_w2) {         // 64 hidden units x 128 of d_model, matrix by matrix
         const int gx = a.F / 64, gy = (a.D + 127) / 128;
         const int e = b / (gx * gy), r = b - e * (gx * gy);
-        prune24_cols_body<SOFT>(smem, r % gx, r / gx, e, a.W2, a.F, a.D, a.F, a.w2v, a.w2m, a.w2vb, a.w2mb, nullptr, a.w2t);
+        prune24_cols_body<SOFT>(smem, r % gx, r / gx, e, a.W2, a.F, a.D, a.F, a.w2v, a.w2m, a.w2vb, a.w2mb, a.w2t);
         return;
     }
     b -= n_w2;

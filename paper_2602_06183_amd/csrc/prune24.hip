@@ -40,10 +40,9 @@ __global__ void __launch_bounds__(256) prune24_rows_kernel(const uint16_t* __res
 
 template <bool SOFT>
 __global__ void __launch_bounds__(256) prune24_cols_kernel(const uint16_t* __restrict__ src, int64_t R, int K, int64_t ld, uint16_t* __restrict__ vals,
-                                                          uint8_t* __restrict__ meta, uint16_t* __restrict__ vblk, uint8_t* __restrict__ mblk,
-                                                          uint16_t* __restrict__ src_blk, uint16_t* __restrict__ src_t = nullptr) {
+                                                          uint8_t* __restrict__ meta, uint16_t* __restrict__ vblk, uint8_t* __restrict__ mblk) {
     __shared__ __attribute__((aligned(16))) unsigned char smem[kPruneColsLds];
-    prune24_cols_body<SOFT>(smem, blockIdx.x, blockIdx.y, blockIdx.z, src, R, K, ld, vals, meta, vblk, mblk, src_blk, src_t);
+    prune24_cols_body<SOFT>(smem, blockIdx.x, blockIdx.y, 0, src, R, K, ld, vals, meta, vblk, mblk, nullptr);
 }
 template <bool SOFT>
 __global__ void __launch_bounds__(256) prune24_rows_step_kernel(const uint16_t* __restrict__ src, int K, int64_t ld, uint16_t* __restrict__ vals, uint8_t* __restrict__ meta,
@@ -67,16 +66,14 @@ hipError_t launch_prune24(const uint16_t* src, int64_t R, int64_t K, int64_t ld,
         }
     } else {
         dim3 grid((unsigned)(R / 64), (unsigned)((K + 127) / 128));
-        if (mode == 0) hipLaunchKernelGGL((prune24_cols_kernel<false>), grid, dim3(256), 0, stream, src, R, (int)K, ld, vals, meta, (uint16_t*)nullptr, (uint8_t*)nullptr, (uint16_t*)nullptr);
-        else           hipLaunchKernelGGL((prune24_cols_kernel<true>), grid, dim3(256), 0, stream, src, R, (int)K, ld, vals, meta, (uint16_t*)nullptr, (uint8_t*)nullptr, (uint16_t*)nullptr);
+        if (mode == 0) hipLaunchKernelGGL((prune24_cols_kernel<false>), grid, dim3(256), 0, stream, src, R, (int)K, ld, vals, meta, (uint16_t*)nullptr, (uint8_t*)nullptr);
+        else           hipLaunchKernelGGL((prune24_cols_kernel<true>), grid, dim3(256), 0, stream, src, R, (int)K, ld, vals, meta, (uint16_t*)nullptr, (uint8_t*)nullptr);
     }
     return hipGetLastError();
 }
 
 hipError_t launch_prune24_step(const uint16_t* src, int64_t R, int64_t K, int64_t ld, int trans, int mode, uint16_t* vals,
-                               uint8_t* meta, uint16_t* vblk, uint8_t* mblk, uint16_t* src_blk, hipStream_t stream, int batch, int cluster_M,
-                               uint16_t* src_t) {
-    if (batch > 1 && (!trans || ld != R)) return hipErrorInvalidValue;
+                               uint8_t* meta, uint16_t* vblk, uint8_t* mblk, hipStream_t stream, int cluster_M) {
     if (cluster_M && (trans || (cluster_M != 8 && cluster_M != 16 && cluster_M != 32 && cluster_M != 64) || R % cluster_M)) return hipErrorInvalidValue;
     if (!trans) {
         dim3 grid((unsigned)((K / 64 + 3) / 4), (unsigned)(R / 16));
@@ -85,9 +82,9 @@ hipError_t launch_prune24_step(const uint16_t* src, int64_t R, int64_t K, int64_
         if (mode == 0) hipLaunchKernelGGL((prune24_rows_step_kernel<false>), grid, dim3(256), 0, stream, src, (int)K, ld, vals, meta, vblk, mblk, logM, Kc);
         else           hipLaunchKernelGGL((prune24_rows_step_kernel<true>), grid, dim3(256), 0, stream, src, (int)K, ld, vals, meta, vblk, mblk, logM, Kc);
     } else {
-        dim3 grid((unsigned)(R / 64), (unsigned)((K + 127) / 128), (unsigned)batch);
-        if (mode == 0) hipLaunchKernelGGL((prune24_cols_kernel<false>), grid, dim3(256), 0, stream, src, R, (int)K, ld, vals, meta, vblk, mblk, src_blk, src_t);
-        else           hipLaunchKernelGGL((prune24_cols_kernel<true>), grid, dim3(256), 0, stream, src, R, (int)K, ld, vals, meta, vblk, mblk, src_blk, src_t);
+        dim3 grid((unsigned)(R / 64), (unsigned)((K + 127) / 128));
+        if (mode == 0) hipLaunchKernelGGL((prune24_cols_kernel<false>), grid, dim3(256), 0, stream, src, R, (int)K, ld, vals, meta, vblk, mblk);
+        else           hipLaunchKernelGGL((prune24_cols_kernel<true>), grid, dim3(256), 0, stream, src, R, (int)K, ld, vals, meta, vblk, mblk);
     }
     return hipGetLastError();
 }

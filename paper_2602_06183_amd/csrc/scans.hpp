@@ -5,7 +5,7 @@
 
 namespace sffn {
 
-constexpr int kTransposeLds = 64 * (64 + 2) * 2, kPruneColsLds = 128 * (64 + 8) * 2;
+constexpr int kTransposeLds = 64 * (64 + 2) * 2, kPruneColsLds = 128 * (64 + 2) * 2;
 
 // out[c, r] = in[r, c]; R, C multiples of 64.
 // blocked = 2: out in the order of lane_off (common.hpp), out_same as for 1.
@@ -51,16 +51,18 @@ __device__ __forceinline__ void transpose_bf16_body(void* smem, int bx, int by, 
 }
 
 // ---- groups run along the strided axis: S[r,k] = src[k*ld + r] ---------------------------------
-// A workgroup takes 64 logical rows x 128 k: the 128 x 64 source tile goes through LDS so that
-// both the HBM reads (128 B row segments) and the packed writes (32 B per thread, 128 B per row)
-// stay contiguous.
+// A workgroup takes 64 logical rows x 128 k: the 128 x 64 source tile goes through LDS so that both the HBM reads (128-byte row segments) and the
+// packed writes stay contiguous: lane = (row, 32 k), 4 lanes write 128 consecutive bytes of a row and a wavefront whole blocks.  Bound: HBM.
+//   R = 16384, K = 4096: 65 us with one row per lane (32 bytes at a row's distance), 52 now; with the unpruned transpose, R = 28672, K = 8192:
+//   296 and 248 us (5.0 TB/s, a large copy's rate).
 template <bool SOFT>
 __device__ __forceinline__ void prune24_cols_body(void* smem, int bx, int by, int bz, const uint16_t* __restrict__ src, int64_t R, int K, int64_t ld,
                                                           uint16_t* __restrict__ vals, uint8_t* __restrict__ meta,
                                                           uint16_t* __restrict__ vblk, uint8_t* __restrict__ mblk,
-                                                          uint16_t* __restrict__ src_blk, uint16_t* __restrict__ src_t) {
-    constexpr int TK = 128, TR = 64, PITCH = TR + 8;
+                                                          uint16_t* __restrict__ src_t) {
+    constexpr int TK = 128, TR = 64, PITCH = TR + 2;
     uint16_t* tile = reinterpret_cast<uint16_t*>(smem);
+    (void)TK;
     const int64_t r0 = (int64_t)bx * TR;
     const int k0 = by * TK;
     const int tid = threadIdx.x;
@@ -69,7 +71,6 @@ __device__ __forceinline__ void prune24_cols_body(void* smem, int bx, int by, in
         src += m;
         if (vals) { vals += m / 2; meta += m / 8; }
         if (vblk) { vblk += m / 2; mblk += m / 8; }
-        if (src_blk) src_blk += m;
         if (src_t) src_t += m;
     }
 #pragma unroll
@@ -77,24 +78,15 @@ __device__ __forceinline__ void prune24_cols_body(void* smem, int bx, int by, in
         const int kk = tid / 8 + 32 * i, seg = tid % 8;
         uint4 w = make_uint4(0, 0, 0, 0);
         if (k0 + kk < K) w = *reinterpret_cast<const uint4*>(src + (int64_t)(k0 + kk) * ld + r0 + seg * 8);
-        *reinterpret_cast<uint4*>(&tile[kk * PITCH + seg * 8]) = w;
+        uint32_t* p = reinterpret_cast<uint32_t*>(&tile[kk * PITCH + seg * 8]);
+        p[0] = w.x; p[1] = w.y; p[2] = w.z; p[3] = w.w;
     }
     __syncthreads();
-    if (src_blk) {      // blocked copy of the source tile itself: rows = k (128), columns = r (64) -> 16 blocks of 1 KB
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int e = tid + 256 * i, bk = e >> 6, l = e & 63;
-            const int kr = (bk >> 1) * 16 + (l >> 2), rc = (bk & 1) * 32 + (l & 3) * 8;
-            if (k0 + kr < K)
-                *reinterpret_cast<uint4*>(src_blk + blk_off(k0 + kr, r0 + rc, R / 32)) = *reinterpret_cast<const uint4*>(&tile[kr * PITCH + rc]);
-        }
-    }
     if (src_t) {        // the unpruned transposed tile: logical rows r (64) x k (128) -> [R, K] row-major, 16 bytes per thread and pass
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            // row r0 + tr, k segment of 8 starting at 8 ks; neighbouring lanes take the two halves of a 32-byte piece of one output row
-            // (whole sectors in HBM; the LDS reads of a wavefront then fall into two bank groups x 16 words: no conflicts)
-            const int e = tid + 256 * i, tr = (e >> 1) & 63, ks = ((e >> 7) << 1) | (e & 1);
+            // row r0 + tr, k segment of 8 starting at 8 ks: 16 lanes take 256 consecutive bytes of a row
+            const int e = tid + 256 * i, tr = e >> 4, ks = e & 15;
             if (k0 + 8 * ks < K) {
                 uint32_t w[4];
 #pragma unroll
@@ -104,7 +96,7 @@ __device__ __forceinline__ void prune24_cols_body(void* smem, int bx, int by, in
             }
         }
     }
-    const int rr = tid % 64, q = tid / 64;
+    const int rr = tid >> 2, q = tid & 3;
     if (k0 + 32 * q >= K) return;
     uint32_t ov[8], mbytes = 0;
 #pragma unroll
