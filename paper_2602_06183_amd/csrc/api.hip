@@ -4,6 +4,7 @@
 #include <string.h>
 
 #include "../../include/sparseffn.h"
+#include "common.hpp"
 #include "kernels.hpp"
 
 using namespace sffn;
@@ -473,15 +474,18 @@ int vnm_spmm_fp8(const uint8_t* a_codes, const uint8_t* a_meta, const uint8_t* a
     return SFFN_OK;
 }
 
+// The step's preparing passes: all in one launch while X, dY, W1 and W2 together stay below 96 MiB, else in three parts (X and W1 | W2 | dY)
+static inline bool prologue_together(int64_t T, int64_t D, int64_t F, int64_t E) { return 2 * (2 * T * D + 2 * E * F * D) < ((int64_t)96 << 20); }
+
 // ---- the training step with fp8 operands in eqs. (1), (3), (4), (7) (Section 3.4, closing paragraph) ---------------------------
 namespace {
 struct Fp8Layout {
     sffn_fp8_ws_layout pub;
-    size_t w1_blk, w1_mblk, w2t_blk, w2t_mblk, xq, xt_blk, dyq, dyt_blk, w2q, w1tq, v24, m24, at_blk, kmask, amax_slots, total;
+    size_t w1_blk, w1_mblk, w2t_blk, w2t_mblk, xq, xt_blk, dyq, dyt_blk, w2q, w1tq, v24, m24, at_blk, at2, kmask, amax, total;
     size_t scratch_end, saved_end;      // [scratch | saved | weights], as in FullLayout
 };
 // E = number of experts (1 for the plain step): weight-shaped tensors hold E matrices back to back
-bool make_fp8_layout(const sffn_cfg* c, Fp8Layout* L, int n_experts = 1) {
+bool make_fp8_layout(const sffn_cfg* c, Fp8Layout* L, int n_experts = 1, StepTiles* tiles = nullptr) {
     if (!c || !mult64(c->T) || !mult128(c->D) || !mult128(c->F) || c->V != 64 || n_experts < 1) return false;
     if (c->M != 8 && !(vnm_ok(c->V, c->M) && vnm_spmm_gather_fp8_ok(c->T, c->D, c->F, c->M))) return false;
     if (c->flags & ~(SFFN_FLAG_KEEP_DENSE | SFFN_FLAG_FP8_WGRAD | SFFN_FLAG_LEAN | SFFN_FLAG_WEIGHTS_PACKED | SFFN_FLAG_DW_FP32_ACCUMULATE)) return false;
@@ -498,7 +502,13 @@ bool make_fp8_layout(const sffn_cfg* c, Fp8Layout* L, int n_experts = 1) {
     L->xq = take(T * D);                   L->dyq = take(T * D);
     L->dyt_blk = take(T * D * 2);
     L->v24 = take(TF / 2);
-    L->amax_slots = take((size_t)6 * 64 * 64 * sizeof(float));      // 6 tensors x 64 slots x 256 bytes
+    // shared launches: with fp8 weight gradients, not into float32 accumulators (their units: step_mix_fp8.hip)
+    StepTiles t = step_tiles(c->T, c->D, c->F, c->M, n_experts, true);
+    t.mix = t.mix && (c->flags & SFFN_FLAG_FP8_WGRAD) && !(c->flags & SFFN_FLAG_DW_FP32_ACCUMULATE);
+    if (tiles) *tiles = t;
+    L->at2 = take(t.mix ? TF / 2 : 0);                              // eq. (4)'s transposed codes, beside eq. (1)'s
+    const Fp8Parts parts = fp8_parts(c->T, c->D, c->F, n_experts);
+    L->amax = take(sizeof(float) * (2 * (size_t)parts.x + parts.w1 + parts.w2 + 2 * kAmaxSlots * kAmaxSlotStride));     // x, w1, w2, dy: one float per workgroup of their passes; y2, dy1: slots
     L->scratch_end = off;
     // ---- saved (what the backward pass reads of the forward pass) -------------------------------------------------------------------------
     L->pub.y2_meta = take(TF / (2 * M));    L->pub.colidx = take(TF / 64 / M * 4);
@@ -528,7 +538,8 @@ int run_fp8_step(const sffn_cfg* cfg, const sffn_fp8_scales* sc, int n_experts, 
     Fp8Layout L;
     REQUIRE(n_experts >= 1 && n_experts <= GemmGroup::kMaxExperts, SFFN_EINVAL, "ffn_sparse_step_fp8_grouped: n_experts must be in 1..64");
     REQUIRE(vnm_ok(cfg->V, cfg->M), SFFN_EUNSUPPORTED, "ffn_sparse_step_fp8: only V = 64 with M in {8, 16, 32, 64} is built");
-    REQUIRE(make_fp8_layout(cfg, &L, n_experts), SFFN_EINVAL,
+    StepTiles tiles;
+    REQUIRE(make_fp8_layout(cfg, &L, n_experts, &tiles), SFFN_EINVAL,
             "ffn_sparse_step_fp8: T must be a positive multiple of 64, D and F of 128 (M >= 16: 4 F / M a multiple of 128); flags: "
             "SFFN_FLAG_KEEP_DENSE, SFFN_FLAG_FP8_WGRAD, SFFN_FLAG_LEAN, SFFN_FLAG_WEIGHTS_PACKED, SFFN_FLAG_DW_FP32_ACCUMULATE");
     REQUIRE(cfg->mode == SFFN_MODE_HARD || cfg->mode == SFFN_MODE_SOFT, SFFN_EINVAL, "ffn_sparse_step_fp8: unknown mode");
@@ -578,15 +589,23 @@ int run_fp8_step(const sffn_cfg* cfg, const sffn_fp8_scales* sc, int n_experts, 
     const GemmGroup* gp = g.n ? &g_packed : nullptr;
     const GemmGroup* gd = g.n ? &g_dense : nullptr;
     const GemmGroup* gw = g.n ? &g_wgrad : nullptr;
-    // amax[0..5] = largest magnitude of x, w1, w2, y2's survivors, dy, dy1's survivors (what next step's scales are made of)
-    // (collected in 64 slots per tensor inside the workspace, folded by the last launch)
-    float* slots = amax ? (float*)(rg.at(L.amax_slots)) : nullptr;
-    auto slot_of = [&](int i) { return slots ? slots + (size_t)i * 64 * 64 : nullptr; };
-    float *ax = slot_of(0), *aw1 = slot_of(1), *aw2 = slot_of(2), *ay2 = slot_of(3), *ady = slot_of(4), *ady1 = slot_of(5);
+    const bool packed = (cfg->flags & SFFN_FLAG_WEIGHTS_PACKED) != 0;    // both weight passes skipped: the previous call's codes are still in the workspace
+    // amax[0..5] = largest magnitude of x, w1, w2, y2's survivors, dy, dy1's survivors (what next step's scales are made of), collected in the
+    // workspace and folded by the last launch.  The forward pass owns 0-3, the backward pass 4-5; a split call folds only its own.
+    const Fp8Parts parts = fp8_parts(T, D, F, E);
+    float* const am = amax ? (float*)(rg.at(L.amax)) : nullptr;
+    float *ax = am, *ady = am ? ax + parts.x : nullptr, *aw1 = am ? ady + parts.x : nullptr, *aw2 = am ? aw1 + parts.w1 : nullptr, *ay2 = am ? aw2 + parts.w2 : nullptr;
+    float* ady1 = am ? ay2 + kAmaxSlots * kAmaxSlotStride : nullptr;
+    AmaxFold fold = {};
+    {
+        const float* p[6] = {ax, aw1, aw2, ay2, ady, ady1};
+        const int n[6] = {parts.x, packed ? 0 : parts.w1, packed ? 0 : parts.w2, kAmaxSlots, parts.x, kAmaxSlots};
+        const int stride[6] = {1, 1, 1, kAmaxSlotStride, 1, kAmaxSlotStride}, first = fwd ? 0 : 4;
+        fold.count = (bwd ? 6 : 4) - first;
+        fold.out = amax ? amax + first : nullptr;
+        for (int i = 0; i < fold.count; ++i) { fold.p[i] = p[first + i]; fold.n[i] = n[first + i]; fold.stride[i] = stride[first + i]; }
+    }
     if (g_prof_on) { g_prof_n = 0; (void)hipEventRecord(g_prof_ev[0], s); }
-    // amax: the forward pass owns tensors 0-3 (x, w1, w2, y2), the backward pass 4-5 (dy, dy1); a split call clears and folds only its own
-    const int a_first = fwd ? 0 : 4, a_count = (bwd ? 6 : 4) - a_first;
-    if (amax) STAGE(launch_amax_clear(slot_of(a_first), a_count, s), "step/clear(amax)");
     // One data flow for every block width.  M = 8: the epilogues of eqs. (1), (4) also write the survivors' codes in the units of the V:2:8
     // activation GEMM (gemm_vnm8.hip), which picks the kept rows of the quantised W2.T / W1 while it reads its fragments.  M = 16, 32, 64
     // (Table 5): the general-M epilogues; eqs. (3), (7) fetch only the kept rows (gemm_gather.hip) and read the canonical codes.
@@ -598,50 +617,72 @@ int run_fp8_step(const sffn_cfg* cfg, const sffn_fp8_scales* sc, int n_experts, 
     GemmGroup g_rows = g;
     g_rows.role = 0; g_rows.b_stride = F * D;
     const GemmGroup* gr = g.n ? &g_rows : nullptr;
-    // ---- Alg. 1 -------------------------------------------------------------------------------
-    if (fwd && w8) {       // X.T codes for eq. (8) and X codes for eq. (1) in one pass over X
-        STAGE(launch_transpose_quantize_fp8_blocked(X, T, D, D, ix, (uint8_t*)xtb, s, ax, xq), "step/quantize(X, X.T)");
-    } else if (fwd) {
-        STAGE(launch_transpose(X, T, D, D, xtb, 1, nullptr, s), "step/X.T");                                // bf16, for eq. (8)
-        STAGE(launch_quantize_fp8_blocked(X, T, D, D, ix, xq, s, ax), "step/quantize(X)");
+    uint8_t* vcb2 = tiles.mix ? vcb + T * F / 4 : vcb;                                            // (as in the bf16 step: StepTiles)
+    uint16_t* at2 = tiles.mix ? (uint16_t*)(rg.at(L.at2)) : atb;
+    // Codes of X for eq. (1) and X.T (codes or bf16) for eq. (8) in one pass; W1 pruned (canonical + blocked codes) for eq. (1) and unpruned as codes for
+    // eq. (7); W2 likewise for eqs. (4), (3); dY for eqs. (4), (5).  One launch for small inputs, else each part before its readers.
+    Fp8PrologueArgs pro = {};
+    pro.T = (int)T; pro.D = (int)D; pro.F = (int)F; pro.experts = (int)E; pro.mode = cfg->mode; pro.t_codes = w8;
+    pro.inv_x = ix; pro.inv_dy = idy; pro.inv_w1 = iw1; pro.inv_w2 = iw2;
+    pro.amax_x = ax; pro.amax_w1 = aw1; pro.amax_w2 = aw2; pro.amax_dy = ady; pro.slots_y2 = ay2; pro.slots_dy1 = ady1;
+    if (fwd) { pro.X = X; pro.xt = (uint8_t*)xtb; pro.xq = xq; }
+    if (bwd) { pro.dY = dY; pro.dyt = (uint8_t*)dytb; pro.dyq = dyq; }
+    if (fwd && !packed) {
+        pro.W1 = W1; pro.w1c = w1c; pro.w1m = w1m; pro.w1b = w1b; pro.w1mb = w1mb; pro.w1q = w1q;
+        pro.W2 = W2; pro.w2c = w2c; pro.w2m = w2m; pro.w2b = w2b; pro.w2mb = w2mb; pro.w2q = w2tq;
     }
-    // W1 in one pass per expert: pruned (canonical + blocked codes) for eq. (1), and the un-pruned W1 as codes for eq. (7)
-    const bool packed = (cfg->flags & SFFN_FLAG_WEIGHTS_PACKED) != 0;    // both weight passes skipped: the previous call's codes are still in the workspace
-    for (int64_t e = 0; e < E && fwd && !packed; ++e)
-        STAGE(launch_prune24_fp8_step(W1 + e * F * D, F, D, D, 0, cfg->mode, iw1, w1c ? w1c + e * F * D / 2 : nullptr, w1m ? w1m + e * F * D / 8 : nullptr,
-                                      w1b + e * F * D / 2, w1mb + e * F * D / 8, s, aw1, w1q + e * F * D), "step/prune24_fp8(W1)+quantize(W1)");
+    const bool together = tiles.mix || prologue_together(T, D, F, E);
+    Fp8PrologueArgs p_w2 = pro, p_dy = pro;
+    p_w2.X = p_w2.dY = p_w2.W1 = nullptr;
+    p_dy.X = p_dy.W1 = p_dy.W2 = nullptr;
+    if (!together) { pro.dY = nullptr; pro.W2 = nullptr; }
+    // ---- Alg. 1 -------------------------------------------------------------------------------
+    if (together) STAGE(launch_fp8_prologue(pro, s), "step/prologue");
+    else if (fwd) STAGE(launch_fp8_prologue(pro, s), "step/quantize(X, X.T)+prune24_fp8(W1)");
     if (fwd) {   // eq. (1) on codes, then eq. (2) + V:N:M compression on the bf16 tile; the survivors leave as codes (and in bf16 for eq. (5))
         VnmEpilogue ep;
         ep.mode = wide ? 5 : 1; ep.logM = logM; ep.store_dense = keep_dense; ep.vals = (uint16_t*)y2c; ep.meta = y2m; ep.colidx = cix; ep.kmask = kmask;
         ep.ykept = ykept; ep.at = atb; ep.inv_out = 1.0f / sc->y2; ep.at_fp8 = w8; ep.amax = ay2;
         if (!wide) { ep.vcb = (uint16_t*)vcb; ep.mcb = mcb; ep.cixt = cixt; }
-        STAGE(launch_gemm_fp8_blocked(w1b, w1mb, xq, b1, sc->x * sc->w1, F, T, D, y1, F, &ep, s, gp), "step/y1+sqrelu_vnm_compress");
+        STAGE(launch_gemm_fp8_blocked(w1b, w1mb, xq, b1, sc->x * sc->w1, F, T, D, y1, F, &ep, s, gp, tiles.mix ? tiles.g : 0), "step/y1+sqrelu_vnm_compress");
     }
-    for (int64_t e = 0; e < E && fwd && !packed; ++e)
-        STAGE(launch_prune24_fp8_step(W2 + e * D * F, F, D, F, 1, cfg->mode, iw2, w2c ? w2c + e * F * D / 2 : nullptr, w2m ? w2m + e * F * D / 8 : nullptr,
-                                      w2b + e * F * D / 2, w2mb + e * F * D / 8, s, aw2, w2tq + e * F * D), "step/prune24_fp8(W2.T)+quantize(W2.T)");
+    // eq. (4) on codes, then eq. (6) in bf16 on y2's kept slots; dy1 leaves as codes (eq. (7)) and, at M = 8, in bf16 (canonical)
+    VnmEpilogue ep4;
+    ep4.mode = wide ? 6 : 2; ep4.logM = logM; ep4.store_dense = keep_dense; ep4.vals = wide ? (uint16_t*)dy1c : dy1v; ep4.meta = y2m; ep4.colidx = cix;
+    ep4.ykept = ykept; ep4.at = at2; ep4.inv_out = 1.0f / sc->dy1; ep4.at_fp8 = w8; ep4.amax = ady1;
+    if (!wide) ep4.vcb = (uint16_t*)vcb2;
+    if (tiles.mix) {
+        const GemmGroup none;
+        const int Kc = (int)(4 * F / M);
+        const float a3 = sc->y2 * sc->w2, a7 = sc->dy1 * sc->w1;
+        const Vnm8Args v3 = {(const uint16_t*)vcb, mcb, cixt, w2tq, (int)D, (int)T, (int)D, (int)F, Y3, D, 0, 0, gr ? *gr : none, a3};
+        const Vnm8Args v7 = {(const uint16_t*)vcb2, mcb, cixt, w1q, (int)D, (int)T, (int)D, (int)F, dX, D, 0, 0, gr ? *gr : none, a7};
+        const GatherArgs u3 = {y2c, y2m, cix, w2tq, (int)D, (int)T, (int)D, Kc, logM, 0, a3, Y3, D, gr ? *gr : none};
+        const GatherArgs u7 = {dy1c, y2m, cix, w1q, (int)D, (int)T, (int)D, Kc, logM, 0, a7, dX, D, gr ? *gr : none};
+        const GemmV2Args g4 = {(const uint16_t*)w2b, w2mb, (const uint16_t*)dyq, nullptr, (int)F, (int)T, (int)(D / 2), dy2, F, 0, 0, ep4, gp ? *gp : none, sc->dy * sc->w2};
+        const WgradArgs w5 = {atb, kmask, dytb, sc->y2 * sc->dy, (int)F, (int)D, (int)T, dW2, F, 0, 0, gw ? *gw : none};
+        const WgradArgs w8a = {at2, kmask, xtb, sc->dy1 * sc->x, (int)F, (int)D, (int)T, dW1, D, 0, 0, gw ? *gw : none};
+        if (fwd && bwd) STAGE(launch_step_mix_fp8(kMixForwardTail, logM, tiles, &v3, &u3, &g4, w5, s), "step/y3+dW2+dy2");
+        else if (fwd) {
+            if (wide) STAGE(launch_vnm_spmm_gather_fp8(y2c, y2m, cix, w2tq, D, a3, T, D, F, M, Y3, D, s, gr), "step/y3");
+            else STAGE(launch_vnm8_gemm_fp8(vcb, mcb, cixt, w2tq, D, a3, T, D, F, Y3, D, s, gr, tiles.v), "step/y3");
+            if (amax) STAGE(launch_amax_fold(fold, s), "step/fold(amax)");
+        } else STAGE(launch_step_mix_fp8(kMixBackwardHead, logM, tiles, nullptr, nullptr, &g4, w5, s), "step/dW2+dy2");
+        if (bwd) STAGE(launch_step_mix_fp8(kMixBackwardTail, logM, tiles, &v7, &u7, nullptr, w8a, s, amax ? &fold : nullptr), "step/dX+dW1");
+        return SFFN_OK;
+    }
+    if (fwd && !packed && !together) STAGE(launch_fp8_prologue(p_w2, s), "step/prune24_fp8(W2.T)");
     if (fwd) {
         if (wide) STAGE(launch_vnm_spmm_gather_fp8(y2c, y2m, cix, w2tq, D, sc->y2 * sc->w2, T, D, F, M, Y3, D, s, gr), "step/y3");      // eq. (3)
         else STAGE(launch_vnm8_gemm_fp8(vcb, mcb, cixt, w2tq, D, sc->y2 * sc->w2, T, D, F, Y3, D, s, gr), "step/y3");
     }
     // ---- Alg. 2 -------------------------------------------------------------------------------
-    if (bwd && w8) {
-        STAGE(launch_transpose_quantize_fp8_blocked(dY, T, D, D, idy, (uint8_t*)dytb, s, ady, dyq), "step/quantize(dY, dY.T)");
-    } else if (bwd) {
-        STAGE(launch_transpose(dY, T, D, D, dytb, 1, nullptr, s), "step/dY.T");                             // bf16, for eq. (5)
-        STAGE(launch_quantize_fp8_blocked(dY, T, D, D, idy, dyq, s, ady), "step/quantize(dY)");
-    }
+    if (bwd && !together) STAGE(launch_fp8_prologue(p_dy, s), "step/quantize(dY, dY.T)");
     if (bwd) {
         if (w8) STAGE(launch_wgrad_vnm_fp8((const uint8_t*)atb, kmask, (const uint8_t*)dytb, sc->y2 * sc->dy, F, D, T, 1, dW2, F, s, gw, acc32), "step/dW2");   // eq. (5) on codes
         else STAGE(launch_wgrad_vnm(atb, kmask, dytb, F, D, T, 1, dW2, F, s, gw, acc32), "step/dW2");               // eq. (5), bf16
     }
-    if (bwd) {   // eq. (4) on codes, then eq. (6) in bf16 on y2's kept slots; dy1 leaves as codes (eq. (7)) and, at M = 8, in bf16 (canonical)
-        VnmEpilogue ep;
-        ep.mode = wide ? 6 : 2; ep.logM = logM; ep.store_dense = keep_dense; ep.vals = wide ? (uint16_t*)dy1c : dy1v; ep.meta = y2m; ep.colidx = cix;
-        ep.ykept = ykept; ep.at = atb; ep.inv_out = 1.0f / sc->dy1; ep.at_fp8 = w8; ep.amax = ady1;
-        if (!wide) ep.vcb = (uint16_t*)vcb;
-        STAGE(launch_gemm_fp8_blocked(w2b, w2mb, dyq, nullptr, sc->dy * sc->w2, F, T, D, dy2, F, &ep, s, gp), "step/dy2+dsqrelu_vnm");
-    }
+    if (bwd) STAGE(launch_gemm_fp8_blocked(w2b, w2mb, dyq, nullptr, sc->dy * sc->w2, F, T, D, dy2, F, &ep4, s, gp), "step/dy2+dsqrelu_vnm");
     if (bwd) {
         if (wide) STAGE(launch_vnm_spmm_gather_fp8(dy1c, y2m, cix, w1q, D, sc->dy1 * sc->w1, T, D, F, M, dX, D, s, gr), "step/dX");     // eq. (7)
         else STAGE(launch_vnm8_gemm_fp8(vcb, mcb, cixt, w1q, D, sc->dy1 * sc->w1, T, D, F, dX, D, s, gr), "step/dX");
@@ -650,7 +691,7 @@ int run_fp8_step(const sffn_cfg* cfg, const sffn_fp8_scales* sc, int n_experts, 
         if (w8) STAGE(launch_wgrad_vnm_fp8((const uint8_t*)atb, kmask, (const uint8_t*)xtb, sc->dy1 * sc->x, F, D, T, 0, dW1, D, s, gw, acc32), "step/dW1");   // eq. (8) on codes
         else STAGE(launch_wgrad_vnm(atb, kmask, xtb, F, D, T, 0, dW1, D, s, gw, acc32), "step/dW1");                // eq. (8), bf16
     }
-    if (amax) STAGE(launch_amax_finish(slot_of(a_first), a_count, amax + a_first, s), "step/finish(amax)");
+    if (amax) STAGE(launch_amax_fold(fold, s), "step/fold(amax)");
     return SFFN_OK;
 }
 }  // namespace
@@ -845,9 +886,6 @@ int sffn_router_workspace_layout(const sffn_cfg* cfg, sffn_router_layout* out) {
     *out = L.pub;
     return SFFN_OK;
 }
-
-// The step's preparing passes: all in one launch while X, dY, W1 and W2 together stay below 96 MiB, else in three parts (X and W1 | W2 | dY)
-static inline bool prologue_together(int64_t T, int64_t D, int64_t F, int64_t E) { return 2 * (2 * T * D + 2 * E * F * D) < ((int64_t)96 << 20); }
 
 // The router's training step.  The run offsets come either as a host array (validated here, passed to the kernels by value)
 // or as a device array written earlier on the same stream by this library's own grouping kernels (seg_dev).

@@ -45,13 +45,9 @@ __device__ __forceinline__ void note_amax(float* amax, float m) {
     }
 }
 
-// The same for the kernels of the fused fp8 step: 64 slots per tensor, 256 bytes apart (slot = workgroup id % 64), so that the reads and
-// atomics of a launch spread over cache lines and L2 channels; amax_finish_kernel (fp8.hip) folds the slots at the end of the step.
+// The same for the epilogues of the fused fp8 step: 64 slots per tensor, 256 bytes apart (slot = workgroup id % 64), so that the reads and
+// atomics of a launch spread over cache lines and L2 channels; the step's last launch folds them (amax_fold.hpp).
 constexpr int kAmaxSlots = 64, kAmaxSlotStride = 64;      // floats
-__device__ __forceinline__ void note_amax_slots(float* slots, float m) {
-    if (slots) note_amax(slots + (((blockIdx.y * gridDim.x + blockIdx.x) & (kAmaxSlots - 1)) * kAmaxSlotStride), m);
-    else note_amax(nullptr, m);
-}
 
 // 2:4 selection on one group of four bf16 (a0..a3 as 16-bit patterns): rank by magnitude
 // descending, index ascending; the two first survive (Section 2.2 of the paper, with the tie rule
@@ -80,6 +76,25 @@ __device__ __forceinline__ uint32_t select24(uint32_t a0, uint32_t a1, uint32_t 
     }
     nib = p0 | (p1 << 2);
     return v0 | (v1 << 16);
+}
+
+// 2:4 selection as select24 (common.hpp) but returning the survivors as float32 reals: bit copies widened (HARD) or
+// a -/+ t evaluated in float32 (SOFT), not rounded to bf16.
+template <bool SOFT>
+__device__ __forceinline__ void select24_f32(uint32_t a0, uint32_t a1, uint32_t a2, uint32_t a3, uint32_t& nib, float& f0, float& f1) {
+    const uint32_t m0 = a0 & 0x7FFFu, m1 = a1 & 0x7FFFu, m2 = a2 & 0x7FFFu, m3 = a3 & 0x7FFFu;
+    const int c01 = m0 >= m1, c02 = m0 >= m2, c03 = m0 >= m3, c12 = m1 >= m2, c13 = m1 >= m3, c23 = m2 >= m3;
+    const int r0 = 3 - c01 - c02 - c03, r1 = c01 + 2 - c12 - c13, r2 = c02 + c12 + 1 - c23, r3 = c03 + c13 + c23;
+    const bool k0 = r0 < 2, k1 = r1 < 2, k2 = r2 < 2, k3 = r3 < 2;
+    const uint32_t p0 = k0 ? 0u : (k1 ? 1u : 2u), p1 = k3 ? 3u : (k2 ? 2u : 1u);
+    const uint32_t v0 = k0 ? a0 : (k1 ? a1 : a2), v1 = k3 ? a3 : (k2 ? a2 : a1);
+    nib = p0 | (p1 << 2);
+    f0 = bf2f(v0); f1 = bf2f(v1);
+    if (SOFT) {
+        const float t = bf2f((r0 == 2) ? m0 : (r1 == 2) ? m1 : (r2 == 2) ? m2 : m3);
+        f0 = (v0 & 0x8000u) ? f0 + t : f0 - t;
+        f1 = (v1 & 0x8000u) ? f1 + t : f1 - t;
+    }
 }
 
 // "Blocked" operand layout used between the kernels of the fused step: a K-contiguous matrix of
@@ -142,8 +157,8 @@ __host__ __device__ __forceinline__ int64_t cixt8_off(int64_t tb, int64_t s128, 
     return (s128 * n_tok_blocks + tb) << 6;
 }
 
-// The same in two steps, for kernels whose stores would otherwise stand between the early-out read and its use (loads and stores share one
-// in-order counter): amax_slot_peek reads the workgroup's slot before the stores are issued, note_amax_slots_seen compares against that value.
+// In two steps, since the epilogue's stores would otherwise stand between the early-out read and its use (loads and stores share one in-order
+// counter): amax_slot_peek reads the workgroup's slot before the stores are issued, note_amax_slots_seen compares against that value.
 __device__ __forceinline__ uint32_t amax_slot_peek(const float* slots) {
     if (!slots) return 0u;
     const unsigned int* p = reinterpret_cast<const unsigned int*>(slots + (((blockIdx.y * gridDim.x + blockIdx.x) & (kAmaxSlots - 1)) * kAmaxSlotStride));

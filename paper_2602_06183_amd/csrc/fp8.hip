@@ -8,8 +8,7 @@
 //   sqrelu_vnm_compress_fp8        eq. (2) + Section 2.3 + quantisation: codes [T, 2F/M], metadata, column indices
 //   vnm_to_24_fp8                  the V:2:M code matrix as a plain 2:4 code matrix over all columns (operand of eqs. (3), (7))
 //   transpose_u8                   [R, C] bytes -> [C, R]
-//   quantize_fp8_blocked / transpose_quantize_fp8_blocked / prune24_*_fp8 with codes_blk: operands of the fused fp8 step, in the blocked
-//                                  layout of common.hpp with a pair of codes per 2-byte element
+// (the fused fp8 step's own scans: prologue_fp8.hip)
 // Every kernel can record the largest magnitude it quantised (float32, atomic max on the bit pattern) for the caller's next scale.
 #include "common.hpp"
 #include "kernels.hpp"
@@ -19,25 +18,6 @@ namespace sffn {
 namespace {
 
 __device__ __forceinline__ uint32_t enc2(float a, float b, float inv) { return fp8_enc2(a, b, inv); }
-
-// 2:4 selection as select24 (common.hpp) but returning the survivors as float32 reals: bit copies widened (HARD) or
-// a -/+ t evaluated in float32 (SOFT), not rounded to bf16.
-template <bool SOFT>
-__device__ __forceinline__ void select24_f32(uint32_t a0, uint32_t a1, uint32_t a2, uint32_t a3, uint32_t& nib, float& f0, float& f1) {
-    const uint32_t m0 = a0 & 0x7FFFu, m1 = a1 & 0x7FFFu, m2 = a2 & 0x7FFFu, m3 = a3 & 0x7FFFu;
-    const int c01 = m0 >= m1, c02 = m0 >= m2, c03 = m0 >= m3, c12 = m1 >= m2, c13 = m1 >= m3, c23 = m2 >= m3;
-    const int r0 = 3 - c01 - c02 - c03, r1 = c01 + 2 - c12 - c13, r2 = c02 + c12 + 1 - c23, r3 = c03 + c13 + c23;
-    const bool k0 = r0 < 2, k1 = r1 < 2, k2 = r2 < 2, k3 = r3 < 2;
-    const uint32_t p0 = k0 ? 0u : (k1 ? 1u : 2u), p1 = k3 ? 3u : (k2 ? 2u : 1u);
-    const uint32_t v0 = k0 ? a0 : (k1 ? a1 : a2), v1 = k3 ? a3 : (k2 ? a2 : a1);
-    nib = p0 | (p1 << 2);
-    f0 = bf2f(v0); f1 = bf2f(v1);
-    if (SOFT) {
-        const float t = bf2f((r0 == 2) ? m0 : (r1 == 2) ? m1 : (r2 == 2) ? m2 : m3);
-        f0 = (v0 & 0x8000u) ? f0 + t : f0 - t;
-        f1 = (v1 & 0x8000u) ? f1 + t : f1 - t;
-    }
-}
 
 }  // namespace
 
@@ -58,94 +38,61 @@ __global__ void __launch_bounds__(256) quantize_fp8_kernel(const uint4* __restri
 // rows K-contiguous: one thread per 8 consecutive elements (two groups) -> 4 codes + 1 metadata byte
 template <bool SOFT>
 __global__ void __launch_bounds__(256) prune24_rows_fp8_kernel(const uint16_t* __restrict__ src, int64_t nchunks, int cpr, int64_t ld, float inv,
-                                                              uint8_t* __restrict__ codes, uint8_t* __restrict__ meta, float* __restrict__ amax,
-                                                              uint16_t* __restrict__ codes_blk, uint8_t* __restrict__ meta_blk, uint8_t* __restrict__ src_q,
-                                                              float* __restrict__ amax_src) {
+                                                              uint8_t* __restrict__ codes, uint8_t* __restrict__ meta, float* __restrict__ amax) {
     const int64_t c = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    float m = 0.0f, m_src = 0.0f;
+    float m = 0.0f;
     if (c < nchunks) {
         const int64_t r = c / cpr;
         const uint4 w = *reinterpret_cast<const uint4*>(src + r * ld + (c - r * cpr) * 8);
-        if (src_q) {        // the unpruned source itself, quantised, row-major [R, K] codes (its dense use shares the scale)
-            const float f[8] = {bf2f(w.x & 0xFFFFu), bf2f(w.x >> 16), bf2f(w.y & 0xFFFFu), bf2f(w.y >> 16),
-                                bf2f(w.z & 0xFFFFu), bf2f(w.z >> 16), bf2f(w.w & 0xFFFFu), bf2f(w.w >> 16)};
-#pragma unroll
-            for (int e = 0; e < 8; ++e) m_src = __builtin_fmaxf(m_src, __builtin_fabsf(f[e]));
-            *reinterpret_cast<uint2*>(src_q + c * 8) =
-                make_uint2(enc2(f[0], f[1], inv) | (enc2(f[2], f[3], inv) << 16), enc2(f[4], f[5], inv) | (enc2(f[6], f[7], inv) << 16));
-        }
         uint32_t n0, n1;
         float a, b, d, e;
         select24_f32<SOFT>(w.x & 0xFFFFu, w.x >> 16, w.y & 0xFFFFu, w.y >> 16, n0, a, b);
         select24_f32<SOFT>(w.z & 0xFFFFu, w.z >> 16, w.w & 0xFFFFu, w.w >> 16, n1, d, e);
         m = __builtin_fmaxf(__builtin_fmaxf(__builtin_fabsf(a), __builtin_fabsf(b)), __builtin_fmaxf(__builtin_fabsf(d), __builtin_fabsf(e)));
         const uint32_t q4 = enc2(a, b, inv) | (enc2(d, e, inv) << 16);
-        if (codes) {
-            *reinterpret_cast<uint32_t*>(codes + c * 4) = q4;
-            meta[c] = (uint8_t)(n0 | (n1 << 4));
-        }
-        if (codes_blk) *reinterpret_cast<uint32_t*>(codes_blk + blk_off(r, (c - r * cpr) * 2, cpr / 16)) = q4;   // 4 codes = pairs 2 c', 2 c' + 1; K / 2 bytes per row
-        if (meta_blk) meta_blk[m8blk_off(r, (c - r * cpr) * 8, cpr / 16)] = (uint8_t)(n0 | (n1 << 4));
+        *reinterpret_cast<uint32_t*>(codes + c * 4) = q4;
+        meta[c] = (uint8_t)(n0 | (n1 << 4));
     }
     note_amax(amax, m);
-    if (amax_src) note_amax_slots(amax_src, m_src);
 }
 
 // groups run along the strided axis: S[r, k] = src[k * ld + r]; a workgroup takes 64 logical rows x 128 k through LDS
 template <bool SOFT>
 __global__ void __launch_bounds__(256) prune24_cols_fp8_kernel(const uint16_t* __restrict__ src, int64_t R, int K, int64_t ld, float inv,
-                                                              uint8_t* __restrict__ codes, uint8_t* __restrict__ meta, float* __restrict__ amax,
-                                                              uint16_t* __restrict__ codes_blk, float* __restrict__ amax_src,
-                                                              uint8_t* __restrict__ meta_blk, uint8_t* __restrict__ s_q) {
+                                                              uint8_t* __restrict__ codes, uint8_t* __restrict__ meta, float* __restrict__ amax) {
     constexpr int TK = 128, TR = 64, PITCH = TR + 8;
     __shared__ __attribute__((aligned(16))) uint16_t tile[TK * PITCH];
     const int64_t r0 = (int64_t)blockIdx.x * TR;
     const int k0 = blockIdx.y * TK;
     const int tid = threadIdx.x;
-    float m_src = 0.0f;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
         const int kk = tid / 8 + 32 * i, seg = tid % 8;
         uint4 w = make_uint4(0, 0, 0, 0);
         if (k0 + kk < K) w = *reinterpret_cast<const uint4*>(src + (int64_t)(k0 + kk) * ld + r0 + seg * 8);
         *reinterpret_cast<uint4*>(&tile[kk * PITCH + seg * 8]) = w;
-        if (s_q && amax_src) {      // the magnitudes of the source (its dense use, written below as S itself quantised, shares the scale)
-            m_src = __builtin_fmaxf(m_src, __builtin_fmaxf(__builtin_fmaxf(bf2f(w.x & 0x7FFFu), bf2f((w.x >> 16) & 0x7FFFu)), __builtin_fmaxf(bf2f(w.y & 0x7FFFu), bf2f((w.y >> 16) & 0x7FFFu))));
-            m_src = __builtin_fmaxf(m_src, __builtin_fmaxf(__builtin_fmaxf(bf2f(w.z & 0x7FFFu), bf2f((w.z >> 16) & 0x7FFFu)), __builtin_fmaxf(bf2f(w.w & 0x7FFFu), bf2f((w.w >> 16) & 0x7FFFu))));
-        }
     }
     __syncthreads();
     const int rr = tid % 64, q = tid / 64;
     float m = 0.0f;
     if (k0 + 32 * q < K) {
-        uint32_t oc[4], mbytes = 0, sq[8];
+        uint32_t oc[4], mbytes = 0;
 #pragma unroll
         for (int g = 0; g < 8; ++g) {
             const uint16_t* p = &tile[(32 * q + 4 * g) * PITCH + rr];
             uint32_t nib;
             float a, b;
             select24_f32<SOFT>(p[0], p[PITCH], p[2 * PITCH], p[3 * PITCH], nib, a, b);
-            if (s_q) sq[g] = enc2(bf2f(p[0]), bf2f(p[PITCH]), inv) | (enc2(bf2f(p[2 * PITCH]), bf2f(p[3 * PITCH]), inv) << 16);
             m = __builtin_fmaxf(m, __builtin_fmaxf(__builtin_fabsf(a), __builtin_fabsf(b)));
             const uint32_t c2 = enc2(a, b, inv);
             if (g & 1) oc[g >> 1] |= c2 << 16; else oc[g >> 1] = c2;
             mbytes |= nib << (4 * g);
         }
         const int64_t r = r0 + rr;
-        if (codes) {
-            *reinterpret_cast<uint4*>(codes + r * (K / 2) + (k0 + 32 * q) / 2) = make_uint4(oc[0], oc[1], oc[2], oc[3]);
-            *reinterpret_cast<uint32_t*>(meta + r * (K / 8) + (k0 + 32 * q) / 8) = mbytes;
-        }
-        if (codes_blk) *reinterpret_cast<uint4*>(codes_blk + blk_off(r, (k0 + 32 * q) / 4, K / 128)) = make_uint4(oc[0], oc[1], oc[2], oc[3]);   // 16 codes = 8 pairs
-        if (meta_blk) *reinterpret_cast<uint32_t*>(meta_blk + m8blk_off(r, k0 + 32 * q, K / 128)) = mbytes;
-        if (s_q) {          // the unpruned logical matrix S itself, quantised, row-major [R, K] codes (eq. (3) contracts its kept rows)
-            uint4* d = reinterpret_cast<uint4*>(s_q + r * K + k0 + 32 * q);
-            d[0] = make_uint4(sq[0], sq[1], sq[2], sq[3]);
-            d[1] = make_uint4(sq[4], sq[5], sq[6], sq[7]);
-        }
+        *reinterpret_cast<uint4*>(codes + r * (K / 2) + (k0 + 32 * q) / 2) = make_uint4(oc[0], oc[1], oc[2], oc[3]);
+        *reinterpret_cast<uint32_t*>(meta + r * (K / 8) + (k0 + 32 * q) / 8) = mbytes;
     }
     note_amax(amax, m);
-    if (amax_src) note_amax_slots(amax_src, m_src);      // over every element of the source
 }
 
 // eq. (2) + V:N:M compression with fp8 values: the structure of sqrelu_vnm_compress_m_kernel (vnm_general.hip): one workgroup =
@@ -271,127 +218,25 @@ __global__ void __launch_bounds__(256) transpose_u8_kernel(const uint8_t* __rest
     }
 }
 
-// [R, C] bf16 (row stride ld) -> codes in the blocked pair layout, same orientation: one thread per 8 elements
-__global__ void __launch_bounds__(256) quantize_fp8_blocked_kernel(const uint16_t* __restrict__ src, int64_t R, int C8, int64_t ld, float inv,
-                                                                  uint16_t* __restrict__ out, float* __restrict__ amax) {
-    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    float m = 0.0f;
-    if (i < R * C8) {
-        const int64_t r = i / C8;
-        const int c = (int)(i - r * C8) * 8;
-        const uint4 w = *reinterpret_cast<const uint4*>(src + r * ld + c);
-        const float f[8] = {bf2f(w.x & 0xFFFFu), bf2f(w.x >> 16), bf2f(w.y & 0xFFFFu), bf2f(w.y >> 16),
-                            bf2f(w.z & 0xFFFFu), bf2f(w.z >> 16), bf2f(w.w & 0xFFFFu), bf2f(w.w >> 16)};
-#pragma unroll
-        for (int e = 0; e < 8; ++e) m = __builtin_fmaxf(m, __builtin_fabsf(f[e]));
-        *reinterpret_cast<uint2*>(out + blk_off(r, c / 2, C8 / 8)) =
-            make_uint2(enc2(f[0], f[1], inv) | (enc2(f[2], f[3], inv) << 16), enc2(f[4], f[5], inv) | (enc2(f[6], f[7], inv) << 16));
-    }
-    note_amax_slots(amax, m);
-}
-
-// [R, C] bf16 -> codes of the transposed matrix [C, R] in the blocked pair layout; 64 x 64 tiles through LDS.  While the tile is in
-// registers the same pass can also write (EXTRA) the codes in the source's own orientation, blocked (X, dY of the fp8 step with fp8
-// weight gradients).
-template <bool EXTRA>
-__global__ void __launch_bounds__(256) transpose_quantize_fp8_blocked_kernel(const uint16_t* __restrict__ src, int64_t R, int64_t C, int64_t ld, float inv,
-                                                                            uint16_t* __restrict__ out, float* __restrict__ amax, uint16_t* __restrict__ out_same) {
-    __shared__ uint16_t tile[64][64 + 2];
-    const int tid = threadIdx.x;
-    const int64_t r0 = (int64_t)blockIdx.y * 64, c0 = (int64_t)blockIdx.x * 64;
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-        const int r = tid / 8 + 32 * i, seg = tid % 8;
-        const uint4 w = *reinterpret_cast<const uint4*>(src + (r0 + r) * ld + c0 + seg * 8);
-        uint32_t* d = reinterpret_cast<uint32_t*>(&tile[r][seg * 8]);
-        d[0] = w.x; d[1] = w.y; d[2] = w.z; d[3] = w.w;
-        if (EXTRA)
-            *reinterpret_cast<uint2*>(out_same + blk_off(r0 + r, (c0 + seg * 8) / 2, C / 64)) =
-                make_uint2(enc2(bf2f(w.x & 0xFFFFu), bf2f(w.x >> 16), inv) | (enc2(bf2f(w.y & 0xFFFFu), bf2f(w.y >> 16), inv) << 16),
-                           enc2(bf2f(w.z & 0xFFFFu), bf2f(w.z >> 16), inv) | (enc2(bf2f(w.w & 0xFFFFu), bf2f(w.w >> 16), inv) << 16));
-    }
-    __syncthreads();
-    float m = 0.0f;
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-        const int c = tid / 8 + 32 * i, rs = (tid % 8) * 8;          // output row c0 + c, its 8 codes for source rows r0 + rs .. + 7
-        uint32_t q[4];
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const float lo = bf2f(tile[rs + 2 * j][c]), hi = bf2f(tile[rs + 2 * j + 1][c]);
-            m = __builtin_fmaxf(m, __builtin_fmaxf(__builtin_fabsf(lo), __builtin_fabsf(hi)));
-            q[j] = enc2(lo, hi, inv);
-        }
-        *reinterpret_cast<uint2*>(out + blk_off(c0 + c, (r0 + rs) / 2, R / 64)) = make_uint2(q[0] | (q[1] << 16), q[2] | (q[3] << 16));
-    }
-    note_amax_slots(amax, m);
-}
-
-hipError_t launch_quantize_fp8_blocked(const uint16_t* src, int64_t R, int64_t C, int64_t ld, float inv, uint8_t* out_blk, hipStream_t s, float* amax) {
-    if (C % 64 != 0 || R % 16 != 0) return hipErrorInvalidValue;
-    const int64_t n = R * (C / 8);
-    hipLaunchKernelGGL(quantize_fp8_blocked_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, src, R, (int)(C / 8), ld, inv, reinterpret_cast<uint16_t*>(out_blk), amax);
-    return hipGetLastError();
-}
-
-// The amax slots of the fused fp8 step (common.hpp): n tensors x 64 slots.  clear: before the first kernel (a kernel, not a memset node:
-// the step may be captured in a graph); finish: out[i] = max over tensor i's slots.
-__global__ void amax_clear_kernel(float* slots) { slots[(blockIdx.x * kAmaxSlots + threadIdx.x) * kAmaxSlotStride] = 0.0f; }
-__global__ void amax_finish_kernel(const float* slots, float* out) {
-    float m = slots[(blockIdx.x * kAmaxSlots + threadIdx.x) * kAmaxSlotStride];
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) m = __builtin_fmaxf(m, __shfl_xor(m, o, 64));
-    if (threadIdx.x == 0) out[blockIdx.x] = m;
-}
-hipError_t launch_amax_clear(float* slots, int n, hipStream_t s) {
-    hipLaunchKernelGGL(amax_clear_kernel, dim3(n), dim3(kAmaxSlots), 0, s, slots);
-    return hipGetLastError();
-}
-hipError_t launch_amax_finish(const float* slots, int n, float* out, hipStream_t s) {
-    hipLaunchKernelGGL(amax_finish_kernel, dim3(n), dim3(kAmaxSlots), 0, s, slots, out);
-    return hipGetLastError();
-}
-
-hipError_t launch_transpose_quantize_fp8_blocked(const uint16_t* src, int64_t R, int64_t C, int64_t ld, float inv, uint8_t* out_t_blk, hipStream_t s, float* amax,
-                                                 uint8_t* out_same_blk) {
-    if (C % 64 != 0 || R % 64 != 0) return hipErrorInvalidValue;
-    dim3 grid((unsigned)(C / 64), (unsigned)(R / 64));
-    uint16_t* o = reinterpret_cast<uint16_t*>(out_t_blk);
-    if (out_same_blk) hipLaunchKernelGGL((transpose_quantize_fp8_blocked_kernel<true>), grid, dim3(256), 0, s, src, R, C, ld, inv, o, amax, reinterpret_cast<uint16_t*>(out_same_blk));
-    else              hipLaunchKernelGGL((transpose_quantize_fp8_blocked_kernel<false>), grid, dim3(256), 0, s, src, R, C, ld, inv, o, amax, (uint16_t*)nullptr);
-    return hipGetLastError();
-}
-
 hipError_t launch_quantize_fp8(const uint16_t* src, int64_t n, float inv, uint8_t* codes, float* amax, hipStream_t s) {
     const int64_t n8 = n / 8, blocks = (n8 + 255) / 256;
     hipLaunchKernelGGL(quantize_fp8_kernel, dim3((unsigned)(blocks < 8192 ? blocks : 8192)), dim3(256), 0, s, (const uint4*)src, n8, inv, (uint2*)codes, amax);
     return hipGetLastError();
 }
 
-static hipError_t launch_prune24_fp8_impl(const uint16_t* src, int64_t R, int64_t K, int64_t ld, int trans, int mode, float inv, uint8_t* codes, uint8_t* meta,
-                                          float* amax, uint16_t* blk, float* amax_src, uint8_t* mblk, uint8_t* s_q, hipStream_t s) {
+hipError_t launch_prune24_fp8(const uint16_t* src, int64_t R, int64_t K, int64_t ld, int trans, int mode, float inv, uint8_t* codes, uint8_t* meta,
+                              float* amax, hipStream_t s) {
     if (!trans) {
         const int64_t nchunks = R * (K / 8);
         const unsigned grid = (unsigned)((nchunks + 255) / 256);
-        if (mode == 0) hipLaunchKernelGGL((prune24_rows_fp8_kernel<false>), dim3(grid), dim3(256), 0, s, src, nchunks, (int)(K / 8), ld, inv, codes, meta, amax, blk, mblk, s_q, amax_src);
-        else           hipLaunchKernelGGL((prune24_rows_fp8_kernel<true>), dim3(grid), dim3(256), 0, s, src, nchunks, (int)(K / 8), ld, inv, codes, meta, amax, blk, mblk, s_q, amax_src);
+        if (mode == 0) hipLaunchKernelGGL((prune24_rows_fp8_kernel<false>), dim3(grid), dim3(256), 0, s, src, nchunks, (int)(K / 8), ld, inv, codes, meta, amax);
+        else           hipLaunchKernelGGL((prune24_rows_fp8_kernel<true>), dim3(grid), dim3(256), 0, s, src, nchunks, (int)(K / 8), ld, inv, codes, meta, amax);
     } else {
         dim3 grid((unsigned)(R / 64), (unsigned)((K + 127) / 128));
-        if (mode == 0) hipLaunchKernelGGL((prune24_cols_fp8_kernel<false>), grid, dim3(256), 0, s, src, R, (int)K, ld, inv, codes, meta, amax, blk, amax_src, mblk, s_q);
-        else           hipLaunchKernelGGL((prune24_cols_fp8_kernel<true>), grid, dim3(256), 0, s, src, R, (int)K, ld, inv, codes, meta, amax, blk, amax_src, mblk, s_q);
+        if (mode == 0) hipLaunchKernelGGL((prune24_cols_fp8_kernel<false>), grid, dim3(256), 0, s, src, R, (int)K, ld, inv, codes, meta, amax);
+        else           hipLaunchKernelGGL((prune24_cols_fp8_kernel<true>), grid, dim3(256), 0, s, src, R, (int)K, ld, inv, codes, meta, amax);
     }
     return hipGetLastError();
-}
-
-hipError_t launch_prune24_fp8(const uint16_t* src, int64_t R, int64_t K, int64_t ld, int trans, int mode, float inv, uint8_t* codes, uint8_t* meta,
-                              float* amax, hipStream_t s) {
-    return launch_prune24_fp8_impl(src, R, K, ld, trans, mode, inv, codes, meta, amax, nullptr, nullptr, nullptr, nullptr, s);
-}
-
-hipError_t launch_prune24_fp8_step(const uint16_t* src, int64_t R, int64_t K, int64_t ld, int trans, int mode, float inv, uint8_t* codes, uint8_t* meta,
-                                   uint8_t* codes_blk, uint8_t* meta_blk, hipStream_t s, float* amax_src, uint8_t* s_q) {
-    if (K % 128 != 0 || R % 64 != 0 || !codes_blk || !meta_blk || !s_q) return hipErrorInvalidValue;   // a block row holds whole 64-byte pieces of the K / 2 codes per row
-    return launch_prune24_fp8_impl(src, R, K, ld, trans, mode, inv, codes, meta, nullptr, reinterpret_cast<uint16_t*>(codes_blk), amax_src, meta_blk, s_q, s);
 }
 
 hipError_t launch_sqrelu_vnm_compress_fp8(const uint16_t* y1, int64_t T, int64_t F, int M, float inv, uint8_t* codes, uint8_t* meta, uint8_t* colidx,

@@ -101,7 +101,11 @@ inline StepTiles step_tiles(int64_t T, int64_t D, int64_t F, int M, int experts,
 enum { kMixForwardTail = 0, kMixBackwardHead = 1, kMixBackwardTail = 2 };      // {(3), (5), (4)}, {(5), (4)}, {(7), (8)}
 // M = 8: v8 (else null: va); acc32: not with kMixForwardTail
 hipError_t launch_step_mix_bf16(int what, int logM, const StepTiles& t, bool acc32, const Vnm8Args* v8, const GatherArgs* va, const GemmV2Args* g, const WgradArgs& w, hipStream_t s);
-hipError_t launch_step_mix_fp8(int what, int logM, const StepTiles& t, const Vnm8Args* v8, const GatherArgs* va, const GemmV2Args* g, const WgradArgs& w, hipStream_t s);
+// (amax: with kMixBackwardTail, the fold of the step's maxima in the same launch)
+struct AmaxFold { const float* p[6]; int n[6], stride[6]; float* out; int count; };
+hipError_t launch_amax_fold(const AmaxFold& a, hipStream_t s);
+hipError_t launch_step_mix_fp8(int what, int logM, const StepTiles& t, const Vnm8Args* v8, const GatherArgs* va, const GemmV2Args* g, const WgradArgs& w, hipStream_t s,
+                               const AmaxFold* amax = nullptr);
 
 // The passes that only depend on the step's inputs, in one launch (prologue.hip): the blocked copies of X and dY and their transposes, the pruning of W1
 // and W2.  Absent parts: null X / dY / W1 / W2.  experts: W1, W2 are stacks of that many matrices.
@@ -113,6 +117,19 @@ struct PrologueArgs {
     const uint16_t* W2; uint16_t *w2v, *w2vb, *w2t; uint8_t *w2m, *w2mb;
 };
 hipError_t launch_step_prologue(const PrologueArgs& a, hipStream_t s);
+// The same for the fp8 step (prologue_fp8.hip).  t_codes: xt, dyt as codes instead of bf16.  Canonical codes / metadata (w1c, w1m, w2c, w2m) may be null.
+// amax_*: one float per workgroup of the part (fp8_parts: x and dy have as many), slots_*: the epilogues' slots, cleared by the parts over X / dY; null: not wanted.
+struct Fp8PrologueArgs {
+    int T, D, F, experts, mode, t_codes;
+    float inv_x, inv_dy, inv_w1, inv_w2;
+    const uint16_t *X, *dY; uint8_t *xt, *xq, *dyt, *dyq;
+    const uint16_t* W1; uint8_t *w1c, *w1m, *w1b, *w1mb, *w1q;
+    const uint16_t* W2; uint8_t *w2c, *w2m, *w2b, *w2mb, *w2q;
+    float *amax_x, *amax_w1, *amax_w2, *amax_dy, *slots_y2, *slots_dy1;
+};
+struct Fp8Parts { int x, w1, w2; };
+Fp8Parts fp8_parts(int64_t T, int64_t D, int64_t F, int64_t experts);
+hipError_t launch_fp8_prologue(const Fp8PrologueArgs& a, hipStream_t s);
 
 // Edge of the square output tile of a contraction with n256 / n128 / n64 tiles of each size and `steps` trips of its main loop.  A round = one tile on
 // every slot of the chip: 256 tiles of 256 x 256 (one workgroup per CU), 512 of 128 x 128 (two per CU).  A round of small tiles takes `w128` of a round of
@@ -311,21 +328,6 @@ hipError_t launch_spmm24_fp8(const uint8_t* a_codes, const uint8_t* a_meta, cons
 // (mode 1 or 2: M = 8; mode 5 or 6: M = 2^logM = 16, 32, 64), Ra = hidden units, Rb = tokens, out [T, F] if ep->store_dense.
 hipError_t launch_gemm_fp8_blocked(const uint8_t* a_codes, const uint8_t* a_meta, const uint8_t* Bq, const float* bias, float alpha, int64_t Ra,
                                    int64_t Rb, int64_t K, uint16_t* out, int64_t ldo, const VnmEpilogue* ep, hipStream_t s, const GemmGroup* grp = nullptr, int tile = 0);
-// fp8.hip, producers of such operands: quantised copy in the same orientation / transposed; 2:4 pruning that also writes the blocked codes
-// (amax, optional: the tensor's amax slots, see below)
-hipError_t launch_quantize_fp8_blocked(const uint16_t* src, int64_t R, int64_t C, int64_t ld, float inv, uint8_t* out_blk, hipStream_t s, float* amax = nullptr);
-// (out_same_blk: also the codes in the source's orientation)
-hipError_t launch_transpose_quantize_fp8_blocked(const uint16_t* src, int64_t R, int64_t C, int64_t ld, float inv, uint8_t* out_t_blk, hipStream_t s,
-                                                 float* amax = nullptr, uint8_t* out_same_blk = nullptr);
-// amax slots of the fused fp8 step: n tensors x 64 slots x 256 bytes (kAmaxSlots, kAmaxSlotStride in common.hpp); the step's kernels take a tensor's slot base
-hipError_t launch_amax_clear(float* slots, int n, hipStream_t s);
-hipError_t launch_amax_finish(const float* slots, int n, float* out, hipStream_t s);
-// 2:4 pruning + quantisation for the fp8 step, rows (trans = 0) or strided groups (trans = 1): the packed codes blocked (codes_blk) with the metadata in
-// the fp8 units of common.hpp (meta_blk), and s_q = the unpruned logical matrix [R, K] itself as row-major codes (the operand of eqs. (3), (7),
-// whose kept rows are picked or gathered per token block); amax_src: amax slots of the unpruned tensor; codes / meta (canonical) may be null
-hipError_t launch_prune24_fp8_step(const uint16_t* src, int64_t R, int64_t K, int64_t ld, int trans, int mode, float inv, uint8_t* codes, uint8_t* meta,
-                                   uint8_t* codes_blk, uint8_t* meta_blk, hipStream_t s, float* amax_src, uint8_t* s_q);
-
 // the same on E4M3 codes (atc: compact transposed codes [F / 2, T], Gq [N, T], both in the blocked pair layout): out = bf16(alpha * sum)
 hipError_t launch_wgrad_vnm_fp8(const uint8_t* atc, const uint8_t* kmask, const uint8_t* Gq, float alpha, int64_t F, int64_t N, int64_t T,
                                 int out_i_contig, uint16_t* out, int64_t ldo, hipStream_t s, const GemmGroup* grp = nullptr, bool acc32 = false, bool split_ok = true, int tile = 0);
