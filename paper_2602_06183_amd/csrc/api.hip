@@ -49,7 +49,7 @@ int g_prof_n = 0;
 struct FullLayout {
     sffn_ws_layout pub;
     // internal operands of the GEMMs, all in the blocked layout
-    size_t w1_vblk, w1_mblk, w2t_vblk, w2t_mblk, x_blk, xt_blk, dy_blk, dyt_blk, w2_blk, w1t_blk, a24_vblk, a24_mblk, at_blk, kmask, at2, total;
+    size_t w1_vblk, w1_mblk, w2t_vblk, w2t_mblk, x_blk, xt_blk, dy_blk, dyt_blk, w2_blk, w1t_blk, a24_vblk, a24_mblk, at_blk, kmask, at2, split, total;
     size_t scratch_end, saved_end;      // region boundaries: scratch = [0, scratch_end), saved = [scratch_end, saved_end), weights = [saved_end, total)
 };
 
@@ -118,6 +118,7 @@ bool make_layout(const sffn_cfg* c, FullLayout* L, int n_experts = 1, StepTiles*
     StepTiles t = step_tiles(c->T, c->D, c->F, c->M, n_experts, false);
     t.mix = t.mix && fused;
     L->at2 = take(t.mix ? TF : 0);      // dy1v.T compacted, where eq. (4) runs beside eq. (5) (StepTiles)
+    L->split = take(split_bytes({t.v, t.v_split}, c->T, c->D));
     if (tiles) *tiles = t;
     L->scratch_end = off;
     // ---- saved -------------------------------------------------------------------------------------------------------------------------
@@ -149,11 +150,11 @@ const char* sffn_last_error(void) { return g_err; }
 // internal (not declared in the public header): lets the library's other source files leave a text behind sffn_last_error()
 int sffn_noalloc_set_error(int code, const char* text) { return fail(code, "%s", text); }
 
-// internal (noalloc.hip): the part of sffn_workspace_bytes() that only serves shared launches (StepTiles)
+// internal (noalloc.hip): the part of sffn_workspace_bytes() that only serves shared launches and split contractions (StepTiles)
 size_t sffn_step_shared_launch_bytes(const sffn_cfg* cfg) {
     FullLayout L;
     StepTiles t;
-    return make_layout(cfg, &L, 1, &t) && t.mix ? up256((size_t)cfg->T * cfg->F) : 0;
+    return make_layout(cfg, &L, 1, &t) ? up256(t.mix ? (size_t)cfg->T * cfg->F : 0) + up256(split_bytes({t.v, t.v_split}, cfg->T, cfg->D)) : 0;
 }
 
 size_t sffn_workspace_bytes(const sffn_cfg* cfg) {
@@ -172,7 +173,12 @@ int sffn_workspace_layout(const sffn_cfg* cfg, sffn_ws_layout* out) {
 size_t sffn_vnm_spmm_workspace_bytes(int64_t T, int64_t N, int64_t Kfull, int w_kmajor) {
     if (!mult64(T) || !mult64(N) || !mult64(Kfull)) return 0;
     (void)w_kmajor;         // either orientation may need the other one's copy of Wd (plain-2:4 route: [N, Kfull]; gathered route: [Kfull, N])
-    return up256((size_t)T * Kfull) + up256((size_t)T * Kfull / 8) + up256((size_t)N * Kfull * 2);
+    size_t split = split_bytes(plan_vnm8(T, N, (int)(Kfull / 64), 0), T, N);
+    for (int M = 16; M <= 64; M *= 2) {
+        const size_t b = split_bytes(plan_gather(T, N, (int)(4 * Kfull / M / 64), 0), T, N);
+        split = split > b ? split : b;
+    }
+    return up256((size_t)T * Kfull) + up256((size_t)T * Kfull / 8) + up256((size_t)N * Kfull * 2) + up256(split);
 }
 
 size_t sffn_vnm_wgrad_workspace_bytes(int64_t T, int64_t F, int64_t N) {
@@ -291,26 +297,30 @@ int vnm_spmm(const uint16_t* a_vals, const uint8_t* a_meta, const uint8_t* a_col
     uint8_t* m24 = ws + up256((size_t)T * Kfull);
     const uint16_t* W = Wd;
     uint16_t* wcopy = (uint16_t*)(m24 + up256((size_t)T * Kfull / 8));
+    void* sums = (unsigned char*)wcopy + up256((size_t)N * Kfull * 2);
     if (M == 8 && vnm8_gemm_ok(T, N, Kfull, w_kmajor ? ldw : N)) {
         // the 256-token tile kernel of the fused step: the packed arrays regrouped into its units (one small pass), Wd contraction-major
         uint16_t* vcb = v24;
         uint8_t* mcb = m24;
         uint8_t* cixt = m24 + up256((size_t)T * Kfull / 16);
-        LAUNCH(launch_vnm8_repack(a_vals, a_meta, a_colidx, T, Kfull, vcb, mcb, cixt, w_kmajor ? nullptr : Wd, N, Kfull, ldw, wcopy, s), "vnm_spmm/repack");
+        const SplitPlan plan = plan_vnm8(T, N, (int)(Kfull / 64), 0);
+        const Split split = split_at(sums, plan, T, N);
+        LAUNCH(launch_vnm8_repack(a_vals, a_meta, a_colidx, T, Kfull, vcb, mcb, cixt, w_kmajor ? nullptr : Wd, N, Kfull, ldw, wcopy, split.count, s), "vnm_spmm/repack");
         const int64_t ldk = w_kmajor ? ldw : N;
         if (!w_kmajor) W = wcopy;
-        LAUNCH(launch_vnm8_gemm(vcb, mcb, cixt, W, ldk, T, N, Kfull, out, N, s), "vnm_spmm/gemm");
+        LAUNCH(launch_vnm8_gemm(vcb, mcb, cixt, W, ldk, T, N, Kfull, out, N, s, nullptr, plan.tile, &split), "vnm_spmm/gemm");
         return SFFN_OK;
     }
     if ((M >= 16 || w_kmajor) && vnm_spmm_gather_ok(T, N, Kfull, M) && Kfull * (w_kmajor ? ldw : N) * 2 < ((int64_t)1 << 31)) {
         // contract over the 4 Kfull / M kept columns only, gathering their rows of the [Kfull, N] operand (M = 8: the two routes
         // are equally fast, so it is taken only when it saves the transpose of Wd)
         int64_t ldk = ldw;
+        const Split split = split_at(sums, plan_gather(T, N, (int)(4 * Kfull / M / 64), 0), T, N);
         if (!w_kmajor) {
-            LAUNCH(launch_transpose(Wd, N, Kfull, ldw, wcopy, 0, nullptr, s), "vnm_spmm/transpose");
+            LAUNCH(launch_transpose(Wd, N, Kfull, ldw, wcopy, 0, nullptr, s, split.count), "vnm_spmm/transpose");
             W = wcopy; ldk = N;
-        }
-        LAUNCH(launch_vnm_spmm_gather(a_vals, a_meta, a_colidx, W, ldk, T, N, Kfull, M, out, N, s), "vnm_spmm/gather");
+        } else if (split.n > 1) LAUNCH(launch_clear_counters(split.count, s), "vnm_spmm/clear");
+        LAUNCH(launch_vnm_spmm_gather(a_vals, a_meta, a_colidx, W, ldk, T, N, Kfull, M, out, N, s, nullptr, &split), "vnm_spmm/gather");
         return SFFN_OK;
     }
     REQUIRE(T < 65536, SFFN_EUNSUPPORTED, "vnm_spmm: T must be below 65536 on the plain-2:4 route (shapes the gathered-row kernel does not cover)");
@@ -481,7 +491,7 @@ static inline bool prologue_together(int64_t T, int64_t D, int64_t F, int64_t E)
 namespace {
 struct Fp8Layout {
     sffn_fp8_ws_layout pub;
-    size_t w1_blk, w1_mblk, w2t_blk, w2t_mblk, xq, xt_blk, dyq, dyt_blk, w2q, w1tq, v24, m24, at_blk, at2, kmask, amax, total;
+    size_t w1_blk, w1_mblk, w2t_blk, w2t_mblk, xq, xt_blk, dyq, dyt_blk, w2q, w1tq, v24, m24, at_blk, at2, split, kmask, amax, total;
     size_t scratch_end, saved_end;      // [scratch | saved | weights], as in FullLayout
 };
 // E = number of experts (1 for the plain step): weight-shaped tensors hold E matrices back to back
@@ -507,6 +517,7 @@ bool make_fp8_layout(const sffn_cfg* c, Fp8Layout* L, int n_experts = 1, StepTil
     t.mix = t.mix && (c->flags & SFFN_FLAG_FP8_WGRAD) && !(c->flags & SFFN_FLAG_DW_FP32_ACCUMULATE);
     if (tiles) *tiles = t;
     L->at2 = take(t.mix ? TF / 2 : 0);                              // eq. (4)'s transposed codes, beside eq. (1)'s
+    L->split = take(split_bytes({t.v, t.v_split}, c->T, c->D));
     const Fp8Parts parts = fp8_parts(c->T, c->D, c->F, n_experts);
     L->amax = take(sizeof(float) * (2 * (size_t)parts.x + parts.w1 + parts.w2 + 2 * kAmaxSlots * kAmaxSlotStride));     // x, w1, w2, dy: one float per workgroup of their passes; y2, dy1: slots
     L->scratch_end = off;
@@ -617,6 +628,7 @@ int run_fp8_step(const sffn_cfg* cfg, const sffn_fp8_scales* sc, int n_experts, 
     GemmGroup g_rows = g;
     g_rows.role = 0; g_rows.b_stride = F * D;
     const GemmGroup* gr = g.n ? &g_rows : nullptr;
+    const Split split = split_at(rg.at(L.split), {tiles.v, tiles.v_split}, T, D);
     uint8_t* vcb2 = tiles.mix ? vcb + T * F / 4 : vcb;                                            // (as in the bf16 step: StepTiles)
     uint16_t* at2 = tiles.mix ? (uint16_t*)(rg.at(L.at2)) : atb;
     // Codes of X for eq. (1) and X.T (codes or bf16) for eq. (8) in one pass; W1 pruned (canonical + blocked codes) for eq. (1) and unpruned as codes for
@@ -624,7 +636,7 @@ int run_fp8_step(const sffn_cfg* cfg, const sffn_fp8_scales* sc, int n_experts, 
     Fp8PrologueArgs pro = {};
     pro.T = (int)T; pro.D = (int)D; pro.F = (int)F; pro.experts = (int)E; pro.mode = cfg->mode; pro.t_codes = w8;
     pro.inv_x = ix; pro.inv_dy = idy; pro.inv_w1 = iw1; pro.inv_w2 = iw2;
-    pro.amax_x = ax; pro.amax_w1 = aw1; pro.amax_w2 = aw2; pro.amax_dy = ady; pro.slots_y2 = ay2; pro.slots_dy1 = ady1;
+    pro.amax_x = ax; pro.amax_w1 = aw1; pro.amax_w2 = aw2; pro.amax_dy = ady; pro.slots_y2 = ay2; pro.slots_dy1 = ady1; pro.counters = split.count;
     if (fwd) { pro.X = X; pro.xt = (uint8_t*)xtb; pro.xq = xq; }
     if (bwd) { pro.dY = dY; pro.dyt = (uint8_t*)dytb; pro.dyq = dyq; }
     if (fwd && !packed) {
@@ -655,17 +667,17 @@ int run_fp8_step(const sffn_cfg* cfg, const sffn_fp8_scales* sc, int n_experts, 
         const GemmGroup none;
         const int Kc = (int)(4 * F / M);
         const float a3 = sc->y2 * sc->w2, a7 = sc->dy1 * sc->w1;
-        const Vnm8Args v3 = {(const uint16_t*)vcb, mcb, cixt, w2tq, (int)D, (int)T, (int)D, (int)F, Y3, D, 0, 0, gr ? *gr : none, a3};
-        const Vnm8Args v7 = {(const uint16_t*)vcb2, mcb, cixt, w1q, (int)D, (int)T, (int)D, (int)F, dX, D, 0, 0, gr ? *gr : none, a7};
-        const GatherArgs u3 = {y2c, y2m, cix, w2tq, (int)D, (int)T, (int)D, Kc, logM, 0, a3, Y3, D, gr ? *gr : none};
-        const GatherArgs u7 = {dy1c, y2m, cix, w1q, (int)D, (int)T, (int)D, Kc, logM, 0, a7, dX, D, gr ? *gr : none};
+        const Vnm8Args v3 = {(const uint16_t*)vcb, mcb, cixt, w2tq, (int)D, (int)T, (int)D, (int)F, Y3, D, 0, 0, gr ? *gr : none, a3, split};
+        const Vnm8Args v7 = {(const uint16_t*)vcb2, mcb, cixt, w1q, (int)D, (int)T, (int)D, (int)F, dX, D, 0, 0, gr ? *gr : none, a7, split};
+        const GatherArgs u3 = {y2c, y2m, cix, w2tq, (int)D, (int)T, (int)D, Kc, logM, 0, a3, Y3, D, gr ? *gr : none, Split()};
+        const GatherArgs u7 = {dy1c, y2m, cix, w1q, (int)D, (int)T, (int)D, Kc, logM, 0, a7, dX, D, gr ? *gr : none, Split()};
         const GemmV2Args g4 = {(const uint16_t*)w2b, w2mb, (const uint16_t*)dyq, nullptr, (int)F, (int)T, (int)(D / 2), dy2, F, 0, 0, ep4, gp ? *gp : none, sc->dy * sc->w2};
         const WgradArgs w5 = {atb, kmask, dytb, sc->y2 * sc->dy, (int)F, (int)D, (int)T, dW2, F, 0, 0, gw ? *gw : none};
         const WgradArgs w8a = {at2, kmask, xtb, sc->dy1 * sc->x, (int)F, (int)D, (int)T, dW1, D, 0, 0, gw ? *gw : none};
         if (fwd && bwd) STAGE(launch_step_mix_fp8(kMixForwardTail, logM, tiles, &v3, &u3, &g4, w5, s), "step/y3+dW2+dy2");
         else if (fwd) {
             if (wide) STAGE(launch_vnm_spmm_gather_fp8(y2c, y2m, cix, w2tq, D, a3, T, D, F, M, Y3, D, s, gr), "step/y3");
-            else STAGE(launch_vnm8_gemm_fp8(vcb, mcb, cixt, w2tq, D, a3, T, D, F, Y3, D, s, gr, tiles.v), "step/y3");
+            else STAGE(launch_vnm8_gemm_fp8(vcb, mcb, cixt, w2tq, D, a3, T, D, F, Y3, D, s, gr, tiles.v, &split), "step/y3");
             if (amax) STAGE(launch_amax_fold(fold, s), "step/fold(amax)");
         } else STAGE(launch_step_mix_fp8(kMixBackwardHead, logM, tiles, nullptr, nullptr, &g4, w5, s), "step/dW2+dy2");
         if (bwd) STAGE(launch_step_mix_fp8(kMixBackwardTail, logM, tiles, &v7, &u7, nullptr, w8a, s, amax ? &fold : nullptr), "step/dX+dW1");
@@ -674,7 +686,7 @@ int run_fp8_step(const sffn_cfg* cfg, const sffn_fp8_scales* sc, int n_experts, 
     if (fwd && !packed && !together) STAGE(launch_fp8_prologue(p_w2, s), "step/prune24_fp8(W2.T)");
     if (fwd) {
         if (wide) STAGE(launch_vnm_spmm_gather_fp8(y2c, y2m, cix, w2tq, D, sc->y2 * sc->w2, T, D, F, M, Y3, D, s, gr), "step/y3");      // eq. (3)
-        else STAGE(launch_vnm8_gemm_fp8(vcb, mcb, cixt, w2tq, D, sc->y2 * sc->w2, T, D, F, Y3, D, s, gr), "step/y3");
+        else STAGE(launch_vnm8_gemm_fp8(vcb, mcb, cixt, w2tq, D, sc->y2 * sc->w2, T, D, F, Y3, D, s, gr, tiles.v, &split), "step/y3");
     }
     // ---- Alg. 2 -------------------------------------------------------------------------------
     if (bwd && !together) STAGE(launch_fp8_prologue(p_dy, s), "step/quantize(dY, dY.T)");
@@ -685,7 +697,7 @@ int run_fp8_step(const sffn_cfg* cfg, const sffn_fp8_scales* sc, int n_experts, 
     if (bwd) STAGE(launch_gemm_fp8_blocked(w2b, w2mb, dyq, nullptr, sc->dy * sc->w2, F, T, D, dy2, F, &ep4, s, gp), "step/dy2+dsqrelu_vnm");
     if (bwd) {
         if (wide) STAGE(launch_vnm_spmm_gather_fp8(dy1c, y2m, cix, w1q, D, sc->dy1 * sc->w1, T, D, F, M, dX, D, s, gr), "step/dX");     // eq. (7)
-        else STAGE(launch_vnm8_gemm_fp8(vcb, mcb, cixt, w1q, D, sc->dy1 * sc->w1, T, D, F, dX, D, s, gr), "step/dX");
+        else STAGE(launch_vnm8_gemm_fp8(vcb, mcb, cixt, w1q, D, sc->dy1 * sc->w1, T, D, F, dX, D, s, gr, tiles.v, &split), "step/dX");
     }
     if (bwd) {
         if (w8) STAGE(launch_wgrad_vnm_fp8((const uint8_t*)atb, kmask, (const uint8_t*)xtb, sc->dy1 * sc->x, F, D, T, 0, dW1, D, s, gw, acc32), "step/dW1");   // eq. (8) on codes
@@ -1148,6 +1160,7 @@ static int run_step(const sffn_cfg* cfg, int n_experts, const int64_t* seg, cons
     uint16_t* atb = (uint16_t*)(rg.at(L.at_blk));
     uint16_t* at2 = tiles.mix ? (uint16_t*)(rg.at(L.at2)) : atb;      // eq. (4)'s transposed survivors: in the place of eq. (1)'s, or beside them
     uint8_t* kmask = rg.at(L.kmask);
+    const Split split = split_at(rg.at(L.split), {tiles.v, tiles.v_split}, T, D);       // eqs. (3), (7) on few tokens (split.hpp)
     uint16_t* ykept = (uint16_t*)(rg.at(L.pub.y1_kept));
     const int keep_dense = (cfg->flags & SFFN_FLAG_KEEP_DENSE) ? 1 : 0;
     // SFFN_FLAG_WEIGHTS_PACKED: the workspace still holds the packed weights (and W2.T) of the previous call: no pruning passes (Section 3.4:
@@ -1176,7 +1189,7 @@ static int run_step(const sffn_cfg* cfg, int n_experts, const int64_t* seg, cons
         if (g_prof_on) { g_prof_n = 0; (void)hipEventRecord(g_prof_ev[0], s); }
         const bool lean_w = (cfg->flags & SFFN_FLAG_LEAN) != 0;        // no canonical copies of the packed weights (the packed activations stay: eqs. (3), (7) read them)
         PrologueArgs pro = {};
-        pro.T = (int)T; pro.D = (int)D; pro.F = (int)F; pro.experts = (int)E; pro.mode = cfg->mode; pro.t_layout = kept ? 2 : 1;
+        pro.T = (int)T; pro.D = (int)D; pro.F = (int)F; pro.experts = (int)E; pro.mode = cfg->mode; pro.t_layout = kept ? 2 : 1; pro.counters = split.count;
         if (fwd) { pro.X = X; pro.xt = xtb; pro.xb = xb; }
         if (bwd) { pro.dY = dY; pro.dyt = dytb; pro.dyb = dyb; }
         if (fwd && !packed) {
@@ -1200,26 +1213,26 @@ static int run_step(const sffn_cfg* cfg, int n_experts, const int64_t* seg, cons
         if (tiles.mix) {
             const GemmGroup none;
             const int Kc = (int)(4 * F / M);
-            const GatherArgs v3 = {y2v, y2m, cix, w2t, (int)D, (int)T, (int)D, Kc, logM, 0, 1.0f, Y3, D, gr ? *gr : none};
-            const GatherArgs v7 = {dy1v, y2m, cix, W1, (int)D, (int)T, (int)D, Kc, logM, 0, 1.0f, dX, D, gr ? *gr : none};
+            const GatherArgs v3 = {y2v, y2m, cix, w2t, (int)D, (int)T, (int)D, Kc, logM, 0, 1.0f, Y3, D, gr ? *gr : none, split};
+            const GatherArgs v7 = {dy1v, y2m, cix, W1, (int)D, (int)T, (int)D, Kc, logM, 0, 1.0f, dX, D, gr ? *gr : none, split};
             const GemmV2Args g4 = {w2vb, w2mb, dyb, nullptr, (int)F, (int)T, (int)D, dy2, F, 0, 0, ep4, gp ? *gp : none, 1.0f};
             const WgradArgs w5 = {atb, kmask, dytb, 1.0f, (int)F, (int)D, (int)T, dW2, F, 0, 0, gw ? *gw : none};
             const WgradArgs w8 = {at2, kmask, xtb, 1.0f, (int)F, (int)D, (int)T, dW1, D, 0, 0, gw ? *gw : none};
             if (fwd && bwd && !acc32) STAGE(launch_step_mix_bf16(kMixForwardTail, logM, tiles, false, nullptr, &v3, &g4, w5, s), "step/y3+dW2+dy2");
             else {
-                if (fwd) STAGE(launch_vnm_spmm_gather(y2v, y2m, cix, w2t, D, T, D, F, M, Y3, D, s, gr), "step/y3");
+                if (fwd) STAGE(launch_vnm_spmm_gather(y2v, y2m, cix, w2t, D, T, D, F, M, Y3, D, s, gr, &split), "step/y3");
                 if (bwd) STAGE(launch_step_mix_bf16(kMixBackwardHead, logM, tiles, acc32, nullptr, nullptr, &g4, w5, s), "step/dW2+dy2");
             }
             if (bwd) STAGE(launch_step_mix_bf16(kMixBackwardTail, logM, tiles, acc32, nullptr, &v7, nullptr, w8, s), "step/dX+dW1");
             return SFFN_OK;
         }
         if (fwd && !packed && !together) STAGE(launch_step_prologue(part[1], s), "step/prune24(W2.T)");
-        if (fwd) STAGE(launch_vnm_spmm_gather(y2v, y2m, cix, w2t, D, T, D, F, M, Y3, D, s, gr), "step/y3");                              // eq. (3)
+        if (fwd) STAGE(launch_vnm_spmm_gather(y2v, y2m, cix, w2t, D, T, D, F, M, Y3, D, s, gr, &split), "step/y3");                              // eq. (3)
         if (bwd && !together) STAGE(launch_step_prologue(part[2], s), "step/dY.T");
         if (bwd && kept) STAGE(launch_wgrad_wide(atb, kmask, dytb, F, D, T, logM, 1, dW2, F, s, gw, acc32), "step/dW2");                       // eq. (5)
         else if (bwd) STAGE(launch_wgrad_vnm(atb, kmask, dytb, F, D, T, 1, dW2, F, s, gw, acc32, false, tiles.w), "step/dW2");                       // eq. (5)
         if (bwd) STAGE(launch_gemm_vnm_epilogue(w2vb, w2mb, dyb, nullptr, F, T, D, dy2, ep4, s, gp, tiles.g_bwd), "step/dy2+dsqrelu_vnm");      // eqs. (4), (6)
-        if (bwd) STAGE(launch_vnm_spmm_gather(dy1v, y2m, cix, W1, D, T, D, F, M, dX, D, s, gr), "step/dX");                              // eq. (7), dense W1 as is
+        if (bwd) STAGE(launch_vnm_spmm_gather(dy1v, y2m, cix, W1, D, T, D, F, M, dX, D, s, gr, &split), "step/dX");                              // eq. (7), dense W1 as is
         if (bwd && kept) STAGE(launch_wgrad_wide(at2, kmask, xtb, F, D, T, logM, 0, dW1, D, s, gw, acc32), "step/dW1");                        // eq. (8)
         else if (bwd) STAGE(launch_wgrad_vnm(at2, kmask, xtb, F, D, T, 0, dW1, D, s, gw, acc32, false, tiles.w), "step/dW1");                        // eq. (8)
         return SFFN_OK;
@@ -1236,7 +1249,7 @@ static int run_step(const sffn_cfg* cfg, int n_experts, const int64_t* seg, cons
         uint16_t* dyt = dytb;
         uint16_t* w1t = w1tb;                            // W2.T (gathered route) or W1.T (plain-2:4 route), [F, D] / [D, F] row-major
         const VnmEpilogue plain;                         // eqs. (1), (4) on the blocked operands, dense output only
-        STAGE(launch_transpose(X, T, D, D, xt, 0, xb, s), "step/X.T");
+        STAGE(launch_transpose(X, T, D, D, xt, 0, xb, s, split.count), "step/X.T");
         STAGE(launch_prune24_step(W1, F, D, D, 0, cfg->mode, w1v, w1m, w1vb, w1mb, s), "step/prune24(W1)");
         STAGE(launch_gemm_vnm_epilogue(w1vb, w1mb, xb, b1, F, T, D, y1, plain, s), "step/y1");                        // eq. (1)
         STAGE(launch_sqrelu_vnm_compress_m(y1, T, F, M, y2v, y2m, cix, s), "step/sqrelu_vnm_compress");               // eq. (2), Section 2.3
@@ -1245,7 +1258,7 @@ static int run_step(const sffn_cfg* cfg, int n_experts, const int64_t* seg, cons
         const bool gather = vnm_spmm_gather_ok(T, D, F, M) && F * D * 2 < ((int64_t)1 << 31);
         if (gather) {
             STAGE(launch_transpose(W2, D, F, F, w1t, 0, nullptr, s), "step/W2.T");
-            STAGE(launch_vnm_spmm_gather(y2v, y2m, cix, w1t, D, T, D, F, M, Y3, D, s), "step/y3");                    // eq. (3)
+            STAGE(launch_vnm_spmm_gather(y2v, y2m, cix, w1t, D, T, D, F, M, Y3, D, s, nullptr, &split), "step/y3");                    // eq. (3)
         } else {
             STAGE(launch_vnm_to_24_m(y2v, y2m, cix, T, F, M, a24v, a24m, s), "step/to24(y2)");
             STAGE(launch_gemm_nt(1, a24v, a24m, W2, nullptr, T, D, F, 0, Y3, D, s), "step/y3");                       // eq. (3)
@@ -1258,7 +1271,7 @@ static int run_step(const sffn_cfg* cfg, int n_experts, const int64_t* seg, cons
         STAGE(launch_gemm_vnm_epilogue(w2vb, w2mb, dyb, nullptr, F, T, D, dy2, plain, s), "step/dy2");                // eq. (4)
         STAGE(launch_dsqrelu_vnm_m(dy2, y1, y2m, cix, T, F, M, dy1v, s), "step/dsqrelu_vnm");                         // eq. (6)
         if (gather) {
-            STAGE(launch_vnm_spmm_gather(dy1v, y2m, cix, W1, D, T, D, F, M, dX, D, s), "step/dX");                    // eq. (7)
+            STAGE(launch_vnm_spmm_gather(dy1v, y2m, cix, W1, D, T, D, F, M, dX, D, s, nullptr, &split), "step/dX");                    // eq. (7)
         } else {
             STAGE(launch_vnm_to_24_m(dy1v, y2m, cix, T, F, M, a24v, a24m, s), "step/to24(dy1)");
             STAGE(launch_transpose(W1, F, D, D, w1t, 0, nullptr, s), "step/W1.T");
@@ -1295,7 +1308,7 @@ static int run_step(const sffn_cfg* cfg, int n_experts, const int64_t* seg, cons
     g_dense.b_stride = F * D;
     uint16_t* vcb2 = tiles.mix ? a24v + T * F / 4 : vcb;          // eq. (4)'s survivors: in the place of eq. (1)'s, or (StepTiles) in the region's second half
     PrologueArgs pro = {};
-    pro.T = (int)T; pro.D = (int)D; pro.F = (int)F; pro.experts = (int)E; pro.mode = cfg->mode; pro.t_layout = 1;
+    pro.T = (int)T; pro.D = (int)D; pro.F = (int)F; pro.experts = (int)E; pro.mode = cfg->mode; pro.t_layout = 1; pro.counters = split.count;
     if (fwd) { pro.X = X; pro.xt = xtb; pro.xb = xb; }
     if (bwd) { pro.dY = dY; pro.dyt = dytb; pro.dyb = dyb; }
     if (fwd && !packed) {
@@ -1321,26 +1334,26 @@ static int run_step(const sffn_cfg* cfg, int n_experts, const int64_t* seg, cons
     ep4.vcb = vcb2; ep4.at = at2;
     if (tiles.mix) {
         const GemmGroup none;
-        const Vnm8Args v3 = {vcb, mcb, cixt, (const uint8_t*)w2t, (int)D, (int)T, (int)D, (int)F, Y3, D, 0, 0, gd ? *gd : none, 1.0f};
-        const Vnm8Args v7 = {vcb2, mcb, cixt, (const uint8_t*)W1, (int)D, (int)T, (int)D, (int)F, dX, D, 0, 0, gd ? *gd : none, 1.0f};
+        const Vnm8Args v3 = {vcb, mcb, cixt, (const uint8_t*)w2t, (int)D, (int)T, (int)D, (int)F, Y3, D, 0, 0, gd ? *gd : none, 1.0f, split};
+        const Vnm8Args v7 = {vcb2, mcb, cixt, (const uint8_t*)W1, (int)D, (int)T, (int)D, (int)F, dX, D, 0, 0, gd ? *gd : none, 1.0f, split};
         const GemmV2Args g4 = {w2vb, w2mb, dyb, nullptr, (int)F, (int)T, (int)D, dy2, F, 0, 0, ep4, gp ? *gp : none, 1.0f};
         const WgradArgs w5 = {atb, kmask, dytb, 1.0f, (int)F, (int)D, (int)T, dW2, F, 0, 0, gw ? *gw : none};
         const WgradArgs w8 = {at2, kmask, xtb, 1.0f, (int)F, (int)D, (int)T, dW1, D, 0, 0, gw ? *gw : none};
         if (fwd && bwd && !acc32) STAGE(launch_step_mix_bf16(kMixForwardTail, 3, tiles, false, &v3, nullptr, &g4, w5, s), "step/y3+dW2+dy2");
         else {
-            if (fwd) STAGE(launch_vnm8_gemm(vcb, mcb, cixt, w2t, D, T, D, F, Y3, D, s, gd, tiles.v), "step/y3");
+            if (fwd) STAGE(launch_vnm8_gemm(vcb, mcb, cixt, w2t, D, T, D, F, Y3, D, s, gd, tiles.v, &split), "step/y3");
             if (bwd) STAGE(launch_step_mix_bf16(kMixBackwardHead, 3, tiles, acc32, nullptr, nullptr, &g4, w5, s), "step/dW2+dy2");
         }
         if (bwd) STAGE(launch_step_mix_bf16(kMixBackwardTail, 3, tiles, acc32, &v7, nullptr, nullptr, w8, s), "step/dX+dW1");
         return SFFN_OK;
     }
     if (fwd && !packed && !together) STAGE(launch_step_prologue(part[1], s), "step/prune24(W2.T)");
-    if (fwd) STAGE(launch_vnm8_gemm(vcb, mcb, cixt, w2t, D, T, D, F, Y3, D, s, gd, tiles.v), "step/y3");                // eq. (3)
+    if (fwd) STAGE(launch_vnm8_gemm(vcb, mcb, cixt, w2t, D, T, D, F, Y3, D, s, gd, tiles.v, &split), "step/y3");                // eq. (3)
     if (bwd && !together) STAGE(launch_step_prologue(part[2], s), "step/dY.T");
     // ---- Alg. 2 -------------------------------------------------------------------------------
     if (bwd) STAGE(launch_wgrad_vnm(atb, kmask, dytb, F, D, T, 1, dW2, F, s, gw, acc32, true, tiles.w), "step/dW2");           // eq. (5)
     if (bwd) STAGE(launch_gemm_vnm_epilogue(w2vb, w2mb, dyb, nullptr, F, T, D, dy2, ep4, s, gp, tiles.g_bwd), "step/dy2+dsqrelu_vnm");
-    if (bwd) STAGE(launch_vnm8_gemm(vcb2, mcb, cixt, W1, D, T, D, F, dX, D, s, gd, tiles.v), "step/dX");                // eq. (7), dense W1 as is
+    if (bwd) STAGE(launch_vnm8_gemm(vcb2, mcb, cixt, W1, D, T, D, F, dX, D, s, gd, tiles.v, &split), "step/dX");                // eq. (7), dense W1 as is
     if (bwd) STAGE(launch_wgrad_vnm(at2, kmask, xtb, F, D, T, 0, dW1, D, s, gw, acc32, true, tiles.w), "step/dW1");            // eq. (8)
     (void)w1tb;
     return SFFN_OK;

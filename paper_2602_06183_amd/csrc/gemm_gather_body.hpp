@@ -22,6 +22,7 @@
 #include "kernels.hpp"
 #include "launch_mix.hpp"
 #include "lds_dma.hpp"
+#include "split.hpp"
 
 namespace sffn {
 
@@ -43,7 +44,7 @@ template <class TL>
 __device__ __forceinline__ void vnm_gather_body(unsigned char* __restrict__ smem, int pid, int n_pid, const uint16_t* __restrict__ a_vals, const uint8_t* __restrict__ a_meta,
                                                              const uint8_t* __restrict__ colidx, const uint16_t* __restrict__ Wk,
                                                              int ldw, int N, int Kc, int logM, int nblk_tok, int tiles_n,
-                                                             uint16_t* __restrict__ out, int64_t ldo, const GemmGroup& grp) {
+                                                             uint16_t* __restrict__ out, int64_t ldo, const GemmGroup& grp, const Split& split) {
     constexpr int KW = TL::KW, ROW = TL::ROW, kGB = TL::kB, kGA = TL::kA, kGStage = TL::kStage, kGStages = TL::NST, kGLoads = TL::kLoads;
     unsigned char* const cix = smem + TL::RING;
 
@@ -59,6 +60,13 @@ __device__ __forceinline__ void vnm_gather_body(unsigned char* __restrict__ smem
     {
         const int per = n_pid >> 3;
         L = (pid < per * 8) ? (pid & 7) * per + (pid >> 3) : pid;
+    }
+    int ks0 = 0, ks1 = Kc >> 6, sp = 0;                  // this workgroup's stages (split.hpp)
+    if (KW > 1 && split.n > 1) {
+        const int per = nblk_tok * tiles_n;
+        sp = L / per;
+        L -= sp * per;
+        ks0 = sp * (Kc >> 6) / split.n; ks1 = (sp + 1) * (Kc >> 6) / split.n;
     }
     const int tn = L / nblk_tok, tb = L - tn * nblk_tok;
     const int t0 = tb * 64, n0 = tn * TL::BN;
@@ -176,8 +184,8 @@ __device__ __forceinline__ void vnm_gather_body(unsigned char* __restrict__ smem
     };
 #define SB() __builtin_amdgcn_sched_barrier(0)
 
-    const int nk = KW == 1 ? Kc >> 6 : ((Kc >> 6) - kg + KW - 1) / KW;
-    auto step_of = [&](int kt) { return KW == 1 ? kt : kg + kt * KW; };
+    const int nk = (ks1 - ks0 - kg + KW - 1) / KW;
+    auto step_of = [&](int kt) { return ks0 + kg + kt * KW; };
     if (nk > 0) {
 #pragma unroll
     for (int p = 0; p < kGStages; ++p) {
@@ -214,6 +222,12 @@ __device__ __forceinline__ void vnm_gather_body(unsigned char* __restrict__ smem
     }
 #undef SB
     __syncthreads();
+    if constexpr (KW == 4)
+        if (split.n > 1) {
+            float q[16];
+            if (split_join4(acc, smem, split, L, sp, wave, lane, q)) store_quarter(q, 1.0f, smem, wave, lane, out, ldo, t0, n0, t0 + 64, N);
+            return;
+        }
     if (KW > 1) {       // partial sums -> the first wavefront, in ascending order; the others are done
         constexpr int PART = 4 * 16 * 256;
         static_assert((KW - 1) * PART <= TL::RING, "partial sums must fit in the main-loop LDS");
@@ -453,9 +467,9 @@ struct GatherUnit {
     using Args = GatherArgs;
     static constexpr int THREADS = TL::THREADS, LDS = TL::RING + kGMaxKc;
     static __device__ __forceinline__ void run(unsigned char* smem, int pid, int n_pid, const Args& a) {
-        vnm_gather_body<TL>(smem, pid, n_pid, (const uint16_t*)a.a_vals, a.a_meta, a.colidx, (const uint16_t*)a.Wk, a.ldw, a.N, a.Kc, a.logM, a.T >> 6, a.tiles_n, a.out, a.ldo, a.grp);
+        vnm_gather_body<TL>(smem, pid, n_pid, (const uint16_t*)a.a_vals, a.a_meta, a.colidx, (const uint16_t*)a.Wk, a.ldw, a.N, a.Kc, a.logM, a.T >> 6, a.tiles_n, a.out, a.ldo, a.grp, a.split);
     }
-    static unsigned count(const Args& a) { return (unsigned)((a.T >> 6) * ((a.N + TL::BN - 1) / TL::BN)); }
+    static unsigned count(const Args& a) { return (unsigned)((a.T >> 6) * ((a.N + TL::BN - 1) / TL::BN) * a.split.n); }
     static Args args(Args a) { a.tiles_n = (a.N + TL::BN - 1) / TL::BN; return a; }
 };
 using GatherUnit256 = GatherUnit<GTile<4, 2, 1>>;      // 64 tokens x 256 columns, two workgroups per CU

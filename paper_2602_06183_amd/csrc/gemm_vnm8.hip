@@ -14,23 +14,25 @@ bool vnm8_gemm_fp8_ok(int64_t T, int64_t N, int64_t F, int64_t ldw) {
 }
 
 template <bool FP8>
-static hipError_t launch_impl(Vnm8Args a, hipStream_t s, const GemmGroup* grp, int tile) {
+static hipError_t launch_impl(Vnm8Args a, hipStream_t s, const GemmGroup* grp, int tile, const Split* split) {
     a.grp = grp ? *grp : GemmGroup();
     if (a.grp.n && (a.grp.role != 0 || a.grp.seg_dev || a.grp.n > GemmGroup::kMaxExperts)) return hipErrorInvalidValue;
     if (!tile) tile = pick_vnm8_tile(a.T, a.N, a.F / (FP8 ? 128 : 64), a.grp.n);
+    if (split) a.split = *split;
+    if (a.split.n > 1 && (a.grp.n || tile == 256)) return hipErrorInvalidValue;
     return tile == 256 ? launch_units<Vnm8Unit256<FP8>>(s, a) : tile == 128 ? launch_units<Vnm8Unit128<FP8>>(s, a) : launch_units<Vnm8Unit64<FP8>>(s, a);
 }
 
 hipError_t launch_vnm8_gemm(const uint16_t* vcb, const uint8_t* mcb, const uint8_t* cixt, const uint16_t* Wk, int64_t ldw, int64_t T, int64_t N,
-                            int64_t F, uint16_t* out, int64_t ldo, hipStream_t s, const GemmGroup* grp, int tile) {
+                            int64_t F, uint16_t* out, int64_t ldo, hipStream_t s, const GemmGroup* grp, int tile, const Split* split) {
     if (!vnm8_gemm_ok(T, N, F, ldw)) return hipErrorInvalidValue;
-    return launch_impl<false>({vcb, mcb, cixt, reinterpret_cast<const uint8_t*>(Wk), (int)ldw, (int)T, (int)N, (int)F, out, ldo, 0, 0, GemmGroup(), 1.0f}, s, grp, tile);
+    return launch_impl<false>({vcb, mcb, cixt, reinterpret_cast<const uint8_t*>(Wk), (int)ldw, (int)T, (int)N, (int)F, out, ldo, 0, 0, GemmGroup(), 1.0f, Split()}, s, grp, tile, split);
 }
 
 hipError_t launch_vnm8_gemm_fp8(const uint8_t* vcb, const uint8_t* mcb, const uint8_t* cixt, const uint8_t* Wq, int64_t ldw, float alpha, int64_t T,
-                                int64_t N, int64_t F, uint16_t* out, int64_t ldo, hipStream_t s, const GemmGroup* grp, int tile) {
+                                int64_t N, int64_t F, uint16_t* out, int64_t ldo, hipStream_t s, const GemmGroup* grp, int tile, const Split* split) {
     if (!vnm8_gemm_fp8_ok(T, N, F, ldw)) return hipErrorInvalidValue;
-    return launch_impl<true>({reinterpret_cast<const uint16_t*>(vcb), mcb, cixt, Wq, (int)ldw, (int)T, (int)N, (int)F, out, ldo, 0, 0, GemmGroup(), alpha}, s, grp, tile);
+    return launch_impl<true>({reinterpret_cast<const uint16_t*>(vcb), mcb, cixt, Wq, (int)ldw, (int)T, (int)N, (int)F, out, ldo, 0, 0, GemmGroup(), alpha, Split()}, s, grp, tile, split);
 }
 
 }  // namespace sffn

@@ -31,6 +31,7 @@
 #include "kernels.hpp"
 #include "launch_mix.hpp"
 #include "lds_dma.hpp"
+#include "split.hpp"
 
 // Tile rows per band of the workgroup -> tile map (see SFFN_TILE_GROUP in common.hpp).  A tile fetches four times as many bytes of Wk as of
 // the packed activation, so the 32 tiles that an XCD runs at a time should share few column slabs of Wk: tall bands (measured at
@@ -72,7 +73,7 @@ template <bool FP8, class TL>
 __device__ __forceinline__ void vnm8_gemm_body(unsigned char* __restrict__ smem, int pid, int n_pid, const uint16_t* __restrict__ vcb, const uint8_t* __restrict__ mcb,
                                                const uint8_t* __restrict__ cixt, const uint8_t* __restrict__ Wk, int ldw,
                                                int Ra, int N, int F, int Ttot, uint16_t* __restrict__ out, int64_t ldo,
-                                               int tiles_m, int tiles_n, const GemmGroup& grp, float alpha) {
+                                               int tiles_m, int tiles_n, const GemmGroup& grp, float alpha, const Split& split) {
     using GG = G<FP8, TL>;
     constexpr int kB = GG::kB, kA = GG::kA, kMt = GG::kMt, kStage = GG::kStage, ES = GG::ES, kStages = TL::NST, kLoads = GG::LOADS, KW = TL::KW, FN = TL::FN;
     constexpr int BT = TL::BT, BN = TL::BN, ROW = GG::ROW, B_LD = GG::B_LD, A_LD = GG::A_LD, M_LD = GG::M_LD, PB = GG::PIECE, PM = GG::PMASK;
@@ -101,6 +102,16 @@ __device__ __forceinline__ void vnm8_gemm_body(unsigned char* __restrict__ smem,
         tiles_m = cnt / tiles_n; i_base = grp.seg[e]; Ra = grp.seg[e + 1];
         Wk += (int64_t)e * grp.b_stride * ES;
     }
+    constexpr bool SPLIT = KW == 4;
+    const int KS = F / GG::SLAB;                     // stages = slabs of 64 (128) hidden units
+    int ks0 = 0, ks1 = KS, sp = 0, tile = 0;         // this workgroup's stages
+    if (SPLIT && split.n > 1) {
+        const int per = tiles_m * tiles_n;
+        sp = L / per;
+        L -= sp * per;
+        tile = L;
+        ks0 = sp * KS / split.n; ks1 = (sp + 1) * KS / split.n;
+    }
     int tm, tn;
     {
         constexpr int GROUP = SFFN_VNM8_GROUP;
@@ -110,7 +121,6 @@ __device__ __forceinline__ void vnm8_gemm_body(unsigned char* __restrict__ smem,
         tn = (L % width) / gsz;
     }
     const int i0 = i_base + tm * BT, n0 = tn * BN;
-    const int KS = F / GG::SLAB;                     // stages = slabs of 64 (128) hidden units
     const int NTB = Ttot >> 6;
 
     // ---- DMA sources (wave-uniform 64-bit base + 32-bit per-lane offset).  Token groups past the end of the operand are clamped into it:
@@ -244,8 +254,8 @@ __device__ __forceinline__ void vnm8_gemm_body(unsigned char* __restrict__ smem,
     };
 #define SB() __builtin_amdgcn_sched_barrier(0)
 
-    const int nk = KW == 1 ? KS : (KS - kg + KW - 1) / KW;
-    auto step_of = [&](int kt) { return KW == 1 ? kt : kg + kt * KW; };
+    const int nk = (ks1 - ks0 - kg + KW - 1) / KW;
+    auto step_of = [&](int kt) { return ks0 + kg + kt * KW; };
     if (nk > 0) {
 #pragma unroll
     for (int p = 0; p < kStages; ++p) issue(step_of(p < nk ? p : nk - 1), p);
@@ -288,6 +298,12 @@ __device__ __forceinline__ void vnm8_gemm_body(unsigned char* __restrict__ smem,
     wait_vmcnt<0>();
     }
     __syncthreads();
+    if constexpr (SPLIT)
+        if (split.n > 1) {
+            float q[16];
+            if (split_join4(acc, smem, split, tile, sp, wave, lane, q)) store_quarter(q, FP8 ? alpha : 1.0f, smem, wave, lane, out, ldo, i0, n0, Ra, N);
+            return;
+        }
     if (KW > 1) {       // partial sums -> the first wavefront, in ascending order; the others are done
         constexpr int PART = 2 * FN * 16 * 256;
         static_assert((KW - 1) * PART <= GG::BYTES, "partial sums must fit in the main-loop LDS");
@@ -351,9 +367,9 @@ struct Vnm8Unit {
     using Args = Vnm8Args;
     static constexpr int THREADS = TL::THREADS, LDS = G<FP8, TL>::BYTES;
     static __device__ __forceinline__ void run(unsigned char* smem, int pid, int n_pid, const Args& a) {
-        vnm8_gemm_body<FP8, TL>(smem, pid, n_pid, a.vcb, a.mcb, a.cixt, a.Wk, a.ldw, a.T, a.N, a.F, a.T, a.out, a.ldo, a.tiles_m, a.tiles_n, a.grp, a.alpha);
+        vnm8_gemm_body<FP8, TL>(smem, pid, n_pid, a.vcb, a.mcb, a.cixt, a.Wk, a.ldw, a.T, a.N, a.F, a.T, a.out, a.ldo, a.tiles_m, a.tiles_n, a.grp, a.alpha, a.split);
     }
-    static unsigned count(const Args& a) { return vnm8_tiles(a.T, a.N, a.grp, TL::BT, TL::BN); }
+    static unsigned count(const Args& a) { return vnm8_tiles(a.T, a.N, a.grp, TL::BT, TL::BN) * (unsigned)a.split.n; }
     static Args args(Args a) { a.tiles_m = (a.T + TL::BT - 1) / TL::BT; a.tiles_n = (a.N + TL::BN - 1) / TL::BN; return a; }
 };
 template <bool FP8> using Vnm8Unit256 = Vnm8Unit<FP8, VTile<4, 2, 4, 3, 1>>;

@@ -81,22 +81,25 @@ struct GemmV2Args {
     const uint16_t* a_vals; const uint8_t* a_meta; const uint16_t* B; const float* bias;
     int Ra, Rb, K; uint16_t* out; int64_t ldo; int tiles_m, tiles_n; VnmEpilogue ep; GemmGroup grp; float alpha;
 };
+// Split: n workgroups per output tile, each on a range of the contraction (split.hpp); part: float32 sums, count: zeroed counters
+struct Split { float* part = nullptr; unsigned* count = nullptr; int n = 1; };
 struct Vnm8Args {
     const uint16_t* vcb; const uint8_t* mcb; const uint8_t* cixt; const uint8_t* Wk; int ldw, T, N, F; uint16_t* out; int64_t ldo; int tiles_m, tiles_n;
-    GemmGroup grp; float alpha;
+    GemmGroup grp; float alpha; Split split;
 };
 struct GatherArgs {
     const void* a_vals; const uint8_t* a_meta; const uint8_t* colidx; const void* Wk; int ldw, T, N, Kc, logM, tiles_n; float alpha; uint16_t* out; int64_t ldo; GemmGroup grp;
+    Split split;
 };
 struct WgradArgs {
     const uint16_t* atc; const uint8_t* kmask; const uint16_t* G; float alpha; int F, N, T; uint16_t* out; int64_t ldo; int tiles_m, tiles_n; GemmGroup grp;
 };
 
-// Tiles of a step's contractions: g = eqs. (1), (4), v = eqs. (3), (7), w = eqs. (5), (8).  mix: none of them wants the 256 tile (the outputs do not fill
+// Tiles of a step's contractions: g = eqs. (1), (4), v = eqs. (3), (7) (v_split workgroups each), w = eqs. (5), (8).  mix: none of them wants the 256 tile (the outputs do not fill
 // the chip), so that the contractions that do not depend on each other share launches (step_mix_*.hip): eqs. (3), (5), (4) in one and eqs. (7), (8) in
 // another (a backward call: eqs. (5), (4), then (7), (8)).  Eq. (4) then takes the 128 tile and its results need operand buffers of their own, since
 // eqs. (3), (5) still read those of eq. (1).
-struct StepTiles { int g = 0, g_bwd = 0, v = 0, w = 0; bool mix = false; };
+struct StepTiles { int g = 0, g_bwd = 0, v = 0, v_split = 1, w = 0; bool mix = false; };
 inline StepTiles step_tiles(int64_t T, int64_t D, int64_t F, int M, int experts, bool fp8);
 enum { kMixForwardTail = 0, kMixBackwardHead = 1, kMixBackwardTail = 2 };      // {(3), (5), (4)}, {(5), (4)}, {(7), (8)}
 // M = 8: v8 (else null: va); acc32: not with kMixForwardTail
@@ -115,6 +118,7 @@ struct PrologueArgs {
     const uint16_t *X, *dY; uint16_t *xt, *xb, *dyt, *dyb;
     const uint16_t* W1; uint16_t *w1v, *w1vb; uint8_t *w1m, *w1mb;
     const uint16_t* W2; uint16_t *w2v, *w2vb, *w2t; uint8_t *w2m, *w2mb;
+    unsigned* counters;             // kSplitCounters of them are cleared, or null
 };
 hipError_t launch_step_prologue(const PrologueArgs& a, hipStream_t s);
 // The same for the fp8 step (prologue_fp8.hip).  t_codes: xt, dyt as codes instead of bf16.  Canonical codes / metadata (w1c, w1m, w2c, w2m) may be null.
@@ -126,6 +130,7 @@ struct Fp8PrologueArgs {
     const uint16_t* W1; uint8_t *w1c, *w1m, *w1b, *w1mb, *w1q;
     const uint16_t* W2; uint8_t *w2c, *w2m, *w2b, *w2mb, *w2q;
     float *amax_x, *amax_w1, *amax_w2, *amax_dy, *slots_y2, *slots_dy1;
+    unsigned* counters;             // as above
 };
 struct Fp8Parts { int x, w1, w2; };
 Fp8Parts fp8_parts(int64_t T, int64_t D, int64_t F, int64_t experts);
@@ -166,6 +171,49 @@ inline int pick_vnm8_tile(int64_t T, int64_t N, int steps, int groups) {
 // gathered-row activation GEMM: 64 tokens x 256 columns, or 64 x 64
 // (T = 256, N = 1024, F = 4096, M = 16: 19 us and 12 us; T = N = 1024: 20 and 12; T = 512, N = 4096, F = 16384: 90 and 67; T = 1984, N = 1344, M = 32: 14 and 23)
 inline int pick_gather_tile(int64_t T, int64_t N, int steps) { return (T / 64) * ((N + 63) / 64) <= 512 && steps >= 6 ? 64 : 256; }
+
+// Tile and number of workgroups per tile of eqs. (3), (7).  Estimated from what a stage of a tile takes (us): us64 for a 64 tile (one workgroup per
+// CU, its four wavefronts together), 0.42 for a 128 tile alone on its CU, 0.58 for two of them; splitting costs 6 us and writes and reads
+// `n` float32 copies of the output (at most kSplitMost bytes) at 4 TB/s.  Taken where that saves 15 % and more.  T = 64, N = 4096, F = 16384: 94 -> 38 us
+// (4 splits; from HBM instead of the last-level cache: 90 -> 60), N = 2048, F = 8192: 28 -> 16 (8 splits); fp8: 40 -> 23; M = 16: 41 -> 22.  Not where eqs.
+// (3), (7) share a launch: its workgroups fill the chip as it is (T = 192, N = 1024, F = 4096: the step 64 us, 74 with 5 splits).
+constexpr int64_t kSplitMost = (int64_t)32 << 20;
+struct SplitPlan { int tile, n; };
+inline SplitPlan plan_split(int64_t T, int64_t N, int steps, int tile, float us64) {
+    auto tiles = [&](int64_t edge) { return ((T + edge - 1) / edge) * ((N + edge - 1) / edge); };
+    auto cost = [&](int edge, int n) {
+        const int64_t w = tiles(edge) * n;
+        const float rounds = edge == 64 ? us64 * (float)((w + 255) / 256) : 0.58f * (float)(w / 512) + (w % 512 == 0 ? 0.0f : w % 512 <= 256 ? 0.42f : 0.58f);
+        return rounds * (float)((steps + n - 1) / n) + (n > 1 ? 6.0f + (float)(tiles(edge) * edge * edge) * 8.0f * (float)n / 4.0e6f : 0.0f);
+    };
+    SplitPlan best = {tile, 1};
+    if (tile == 256) return best;
+    float least = 0.85f * cost(tile, 1);
+    for (int n = 2; n <= 16 && steps / n >= 8 && tiles(64) * 64 * 64 * 4 * n <= kSplitMost; ++n) {
+        const float c = cost(64, n);
+        if (c < least) { least = c; best = {64, n}; }
+    }
+    return best;
+}
+inline SplitPlan plan_vnm8(int64_t T, int64_t N, int steps, int groups) {
+    const int tile = pick_vnm8_tile(T, N, steps, groups);
+    return groups ? SplitPlan{tile, 1} : plan_split(T, N, steps, tile, 0.205f);
+}
+inline SplitPlan plan_gather(int64_t T, int64_t N, int steps, int groups) {
+    const int tile = pick_gather_tile(T, N, steps);
+    return groups ? SplitPlan{tile, 1} : plan_split(T, N, steps, tile, 0.5f);
+}
+// bytes of the sums and, behind them, of the counters (one per tile: with 2 and more splits of 8 and more stages there are at most kSplitMost / 32 KB)
+inline size_t split_part_bytes(const SplitPlan& p, int64_t T, int64_t N) {
+    return p.n > 1 ? (size_t)(((T + p.tile - 1) / p.tile) * ((N + p.tile - 1) / p.tile)) * p.tile * p.tile * 4 * p.n : 0;
+}
+constexpr int kSplitCounters = 1024;
+inline size_t split_bytes(const SplitPlan& p, int64_t T, int64_t N) { return p.n > 1 ? split_part_bytes(p, T, N) + kSplitCounters * sizeof(unsigned) : 0; }
+inline Split split_at(void* p, const SplitPlan& plan, int64_t T, int64_t N) {
+    Split s;
+    if (plan.n > 1) { s.part = (float*)p; s.count = (unsigned*)((unsigned char*)p + split_part_bytes(plan, T, N)); s.n = plan.n; }
+    return s;
+}
 // weight gradients.  F = 8192, N = 2048, T = 2048 (256 / 1024 tiles): 55 us on 256 tiles, 60 on 128; F = 4096, N = 1024, T = 8192 (64 / 256 / 1024): 145, 65,
 // and 91 on 64 tiles; F = 1024, N = 256, T = 16384 (4 / 16 / 64): 277, 109, 39
 inline int pick_wgrad_tile(int64_t F, int64_t N, int64_t T, int experts, bool split_ok) {
@@ -180,10 +228,12 @@ inline StepTiles step_tiles(int64_t T, int64_t D, int64_t F, int M, int experts,
     GemmGroup g;
     g.role = 1; g.n = experts > 1 ? experts : 0;
     t.g = t.g_bwd = pick_gemm_tile(F, T, (int)(D / unit), g, 0.56f, true);
+    const SplitPlan v = M == 8 ? plan_vnm8(T, D, (int)(F / unit), g.n) : fp8 ? SplitPlan{256, 1} : plan_gather(T, D, (int)(4 * F / M / 64), g.n);
     t.v = M == 8 ? pick_vnm8_tile(T, D, (int)(F / unit), g.n) : fp8 ? 256 : pick_gather_tile(T, D, (int)(4 * F / M / 64));
     t.w = pick_wgrad_tile(F, D, T, experts > 1 ? experts : 0, M == 8 || fp8);
     t.mix = t.g != 256 && t.w != 256 && (M != 8 || t.v != 256);
     if (t.mix) t.g_bwd = 128;
+    else { t.v = v.tile; t.v_split = v.n; }
     return t;
 }
 
@@ -227,23 +277,23 @@ hipError_t launch_vnm_expand_t_m(const uint16_t* vals, const uint8_t* meta, cons
 bool vnm_spmm_gather_ok(int64_t T, int64_t N, int64_t F, int M);
 // grp (role 0, host segment table): the token blocks of segment e take expert e's matrix Wk + e * b_stride.
 hipError_t launch_vnm_spmm_gather(const uint16_t* a_vals, const uint8_t* a_meta, const uint8_t* colidx, const uint16_t* Wk, int64_t ldw,
-                                  int64_t T, int64_t N, int64_t F, int M, uint16_t* out, int64_t ldo, hipStream_t s, const GemmGroup* grp = nullptr);
+                                  int64_t T, int64_t N, int64_t F, int M, uint16_t* out, int64_t ldo, hipStream_t s, const GemmGroup* grp = nullptr, const Split* split = nullptr);
 // eqs. (3), (7) for M = 8 on a 256-token tile (gemm_vnm8.hip): the activation as the epilogues' vcb / mcb / cixt arrays, Wk = [F, ldw] with the
 // contraction index as row; T, N, F multiples of 64.  grp as above (b_stride in elements).
 bool vnm8_gemm_ok(int64_t T, int64_t N, int64_t F, int64_t ldw);
 hipError_t launch_vnm8_gemm(const uint16_t* vcb, const uint8_t* mcb, const uint8_t* cixt, const uint16_t* Wk, int64_t ldw, int64_t T, int64_t N,
-                            int64_t F, uint16_t* out, int64_t ldo, hipStream_t s, const GemmGroup* grp = nullptr, int tile = 0);
+                            int64_t F, uint16_t* out, int64_t ldo, hipStream_t s, const GemmGroup* grp = nullptr, int tile = 0, const Split* split = nullptr);
 // vnm.hip: the canonical V:2:8 arrays (vals [T, F/4], meta [T, F/16], colidx [T/64, F/8, 4]) regrouped into those units; with W [R, C] (row stride ld)
-// also its transpose wt [C, R]
+// also its transpose wt [C, R]; counters (or null): kSplitCounters of them are cleared
 hipError_t launch_vnm8_repack(const uint16_t* vals, const uint8_t* meta, const uint8_t* colidx, int64_t T, int64_t F, uint16_t* vcb, uint8_t* mcb,
-                              uint8_t* cixt, const uint16_t* W, int64_t R, int64_t C, int64_t ld, uint16_t* wt, hipStream_t s);
+                              uint8_t* cixt, const uint16_t* W, int64_t R, int64_t C, int64_t ld, uint16_t* wt, unsigned* counters, hipStream_t s);
 // (fp8 step: codes; F a multiple of 128, Wq = [F, ldw bytes], out = bf16(alpha * sum); the arrays in the layouts of vcb8_off, mcb8_off, cixt8_off)
 bool vnm8_gemm_fp8_ok(int64_t T, int64_t N, int64_t F, int64_t ldw);
 // fp8.hip: the canonical fp8 V:2:8 arrays (codes [T, F/4], meta, colidx) regrouped into those units; F a multiple of 128
 hipError_t launch_vnm8_repack_fp8(const uint8_t* codes, const uint8_t* meta, const uint8_t* colidx, int64_t T, int64_t F, uint8_t* vcb, uint8_t* mcb,
                                   uint8_t* cixt, hipStream_t s);
 hipError_t launch_vnm8_gemm_fp8(const uint8_t* vcb, const uint8_t* mcb, const uint8_t* cixt, const uint8_t* Wq, int64_t ldw, float alpha, int64_t T,
-                                int64_t N, int64_t F, uint16_t* out, int64_t ldo, hipStream_t s, const GemmGroup* grp = nullptr, int tile = 0);
+                                int64_t N, int64_t F, uint16_t* out, int64_t ldo, hipStream_t s, const GemmGroup* grp = nullptr, int tile = 0, const Split* split = nullptr);
 // The same on E4M3 codes: a_codes [T, 2 F / M] + the same metadata and column offsets, Wq = codes [F, ldw bytes], out = bf16(alpha * sum);
 // 4 F / M a multiple of 128; b_stride of grp in bytes.
 bool vnm_spmm_gather_fp8_ok(int64_t T, int64_t N, int64_t F, int M);
@@ -256,8 +306,9 @@ hipError_t launch_vnm_to_24(const uint16_t* vals, const uint8_t* meta, const uin
 // the layout that kernel reads
 hipError_t launch_vnm_compact_t(const uint16_t* vals, const uint8_t* meta, const uint8_t* colidx, int64_t T, int64_t F, int M, int kept, uint16_t* at,
                                 uint8_t* mask, const uint16_t* G, int64_t N, uint16_t* gt, hipStream_t s);
-// blocked: out in the blocked operand layout (1) or in the order of lane_off (2, common.hpp); out_same: also a blocked copy of `in`
-hipError_t launch_transpose(const uint16_t* in, int64_t R, int64_t C, int64_t ld, uint16_t* out, int blocked, uint16_t* out_same, hipStream_t s);
+// blocked: out in the blocked operand layout (1) or in the order of lane_off (2, common.hpp); out_same: also a blocked copy of `in`; counters: as above
+hipError_t launch_transpose(const uint16_t* in, int64_t R, int64_t C, int64_t ld, uint16_t* out, int blocked, uint16_t* out_same, hipStream_t s, unsigned* counters = nullptr);
+hipError_t launch_clear_counters(unsigned* counters, hipStream_t s);
 
 // C[i, j] = sum_k A[i, k] * B[j, k]  (both operands K-contiguous).
 //   sparse_a: A given as 2:4 packed (a_vals [Ra, K/2], a_meta [Ra, K/8]) and multiplied on the

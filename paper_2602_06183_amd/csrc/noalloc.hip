@@ -11,8 +11,9 @@ namespace {
 
 // The workspace itself.  In host code this name is only a stand-in for the device symbol: its device address is obtained
 // once per device with hipGetSymbolAddress (below) and only that address is ever handed to kernels.
-// (16 MiB on top of the documented limit: the operand buffer of shared launches, T F bytes, does not count towards it)
-constexpr size_t kScratchBytes = (size_t)SFFN_NOALLOC_WORKSPACE_MAX + (16u << 20);
+// (48 MiB on top of the documented limit: the operand buffer of shared launches, T F bytes, and the sums of split contractions, at most 32 MiB, do not
+// count towards it)
+constexpr size_t kScratchBytes = (size_t)SFFN_NOALLOC_WORKSPACE_MAX + (49u << 20);
 static __device__ __align__(256) unsigned char scratch[kScratchBytes];
 
 constexpr int kMaxDevices = 64;

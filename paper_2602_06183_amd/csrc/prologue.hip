@@ -12,6 +12,7 @@ template <bool SOFT>
 __global__ void __launch_bounds__(256) step_prologue_kernel(PrologueArgs a, int n_w2, int n_w1, int n_x) {
     __shared__ __attribute__((aligned(16))) unsigned char smem[kPruneColsLds > kTransposeLds ? kPruneColsLds : kTransposeLds];
     int b = blockIdx.x;
+    if (a.counters && b == 0) for (int k = threadIdx.x; k < kSplitCounters; k += 256) a.counters[k] = 0;
     if (b < n_w2) {         // 64 hidden units x 128 of d_model, matrix by matrix
         const int gx = a.F / 64, gy = (a.D + 127) / 128;
         const int e = b / (gx * gy), r = b - e * (gx * gy);

@@ -153,6 +153,7 @@ __global__ void __launch_bounds__(256) fp8_prologue_kernel(Fp8PrologueArgs a, in
     __shared__ __attribute__((aligned(16))) unsigned char smem[kLds];
     __shared__ float part[4];
     int b = blockIdx.x;
+    if (a.counters && b == 0) for (int k = threadIdx.x; k < kSplitCounters; k += 256) a.counters[k] = 0;
     if (b < n_w2) {
         const int gx = a.F / 64, per = gx * (a.D / 128), e = b / per, r = b - e * per;
         const int64_t o = (int64_t)e * a.F * a.D;

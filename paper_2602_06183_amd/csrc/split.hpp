@@ -1,0 +1,82 @@
+// A contraction shared by several workgroups of one output tile (eqs. (3), (7) on few tokens: 64 x 64 tiles of a T = 64 call occupy N / 64 of the 256
+// CUs, and what bounds them is the rate at which one CU can be fed).  Split s contracts its own range of stages; every workgroup leaves its float32
+// sums in memory and counts itself in; the one that finds the others there adds all of them in the order of the splits, so the result does not depend
+// on who was last, and goes on to the output.  Nothing waits.  The counters are zero before the launch (the step's preparing launch clears them)
+// and zero after it.
+#pragma once
+#include "common.hpp"
+#include "kernels.hpp"
+#include "lds_dma.hpp"
+
+namespace sffn {
+
+// The sums travel as agent-scope atomics (written through to memory and read from there: every XCD has its own L2), which the count follows once they are
+// complete.  A fence would write back and invalidate the whole L2 instead, for every wavefront: 250 us for a contraction of 130.
+
+// Sum over the KW wavefronts of a workgroup, which share a 64 x 64 tile (64 sums a lane, in `acc`), and over the workgroups that share it.  Wavefront w
+// is left with its quarter of the tile's sums, q[16] (accumulators 16 w .. 16 w + 15 of a lane in the order [a][b][r]); false: the others are not there
+// yet, the workgroup is done.  smem: 4 x 16 KB.
+__device__ __forceinline__ bool split_join4(const f32x16 (&acc)[2][2], unsigned char* smem, const Split& sp, int tile, int s, int wave, int lane, float (&q)[16]) {
+    float* const part = reinterpret_cast<float*>(smem) + lane;
+#pragma unroll
+    for (int a = 0; a < 2; ++a)
+#pragma unroll
+        for (int b = 0; b < 2; ++b)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) part[(wave * 64 + (a * 2 + b) * 16 + r) * 64] = acc[a][b][r];
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < 16; ++k) q[k] = part[(wave * 16 + k) * 64];
+#pragma unroll
+    for (int g = 1; g < 4; ++g)
+#pragma unroll
+        for (int k = 0; k < 16; ++k) q[k] += part[(g * 64 + wave * 16 + k) * 64];
+    unsigned long long* const p = reinterpret_cast<unsigned long long*>(sp.part) + ((int64_t)tile * sp.n * 4 + wave) * (8 * 64) + lane;
+#pragma unroll
+    for (int k = 0; k < 8; ++k)
+        __hip_atomic_store(p + (s * 4 * 8 + k) * 64, (unsigned long long)__float_as_uint(q[2 * k]) | ((unsigned long long)__float_as_uint(q[2 * k + 1]) << 32), __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_AGENT);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();                     // (all four quarters are out, and the LDS sums have been read)
+    unsigned* const last = reinterpret_cast<unsigned*>(smem);
+    if (wave == 0 && lane == 0) *last = __hip_atomic_fetch_add(sp.count + tile, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1 == (unsigned)sp.n;
+    __syncthreads();
+    const bool go = *last != 0;
+    __syncthreads();
+    if (!go) return false;
+    if (wave == 0 && lane == 0) sp.count[tile] = 0;
+#pragma unroll
+    for (int k = 0; k < 16; ++k) q[k] = 0.0f;
+    for (int g0 = 0; g0 < sp.n; g0 += 4) {                  // four splits' loads at a time
+        unsigned long long v[4][8];
+#pragma unroll
+        for (int g = 0; g < 4; ++g)
+#pragma unroll
+            for (int k = 0; k < 8; ++k)
+                v[g][k] = g0 + g < sp.n ? __hip_atomic_load(p + ((g0 + g) * 4 * 8 + k) * 64, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0ull;
+#pragma unroll
+        for (int g = 0; g < 4; ++g)
+#pragma unroll
+            for (int k = 0; k < 8; ++k) { q[2 * k] += __uint_as_float((uint32_t)v[g][k]); q[2 * k + 1] += __uint_as_float((uint32_t)(v[g][k] >> 32)); }
+    }
+    return true;
+}
+
+// The quarter's output: accumulators 16 w .. of the layout [a][b][r] are the 32 x 32 sub-tile (a, b) = (w / 2, w % 2); rows of 64 bytes through LDS
+__device__ __forceinline__ void store_quarter(const float (&q)[16], float alpha, unsigned char* smem, int wave, int lane, uint16_t* __restrict__ out, int64_t ldo, int i0, int j0,
+                                              int Ra, int N) {
+    constexpr int EP = 32 * 2 + 16;
+    const int l32 = lane & 31, lh = lane >> 5;
+    unsigned char* const scratch = smem + wave * (32 * EP);
+#pragma unroll
+    for (int r = 0; r < 16; ++r) *reinterpret_cast<uint16_t*>(scratch + (8 * (r >> 2) + 4 * lh + (r & 3)) * EP + l32 * 2) = (uint16_t)f2bf(q[r] * alpha);
+    wave_lds_sync();
+#pragma unroll
+    for (int p = 0; p < 2; ++p) {
+        const int e = lane + 64 * p, row = e >> 2, ch = e & 3;
+        const int i = i0 + (wave >> 1) * 32 + row, j = j0 + (wave & 1) * 32 + ch * 8;
+        if (i < Ra && j < N) *reinterpret_cast<uint4*>(out + (int64_t)i * ldo + j) = *reinterpret_cast<const uint4*>(scratch + row * EP + ch * 16);
+    }
+}
+
+}  // namespace sffn

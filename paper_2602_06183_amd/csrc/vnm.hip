@@ -121,8 +121,9 @@ __device__ __forceinline__ void vnm_compact_t_body(void* smem, int bx, int64_t t
 }
 
 __global__ void __launch_bounds__(256) transpose_bf16_kernel(const uint16_t* __restrict__ in, int64_t R, int64_t C, int64_t ld,
-                                                            uint16_t* __restrict__ out, int blocked, uint16_t* __restrict__ out_same) {
+                                                            uint16_t* __restrict__ out, int blocked, uint16_t* __restrict__ out_same, unsigned* __restrict__ counters) {
     __shared__ __attribute__((aligned(16))) unsigned char smem[kTransposeLds];
+    if (counters && blockIdx.x == 0 && blockIdx.y == 0) for (int k = threadIdx.x; k < kSplitCounters; k += 256) counters[k] = 0;
     transpose_bf16_body(smem, blockIdx.x, blockIdx.y, in, R, C, ld, out, blocked, out_same, nullptr);
 }
 
@@ -172,9 +173,10 @@ __device__ __forceinline__ void transpose_part(void* smem, int i, const Transpos
     transpose_bf16_body(smem, i % t.tc, i / t.tc, t.in, t.R, t.C, t.ld, t.out, t.layout, nullptr, nullptr);
 }
 __global__ void __launch_bounds__(256) vnm8_repack_kernel(const uint16_t* __restrict__ vals, const uint8_t* __restrict__ meta, const uint8_t* __restrict__ colidx, int64_t T,
-                                                         int F, uint16_t* __restrict__ vcb, uint8_t* __restrict__ mcb, uint8_t* __restrict__ cixt, int nc, int n_own, TransposeOf t) {
+                                                         int F, uint16_t* __restrict__ vcb, uint8_t* __restrict__ mcb, uint8_t* __restrict__ cixt, int nc, int n_own, TransposeOf t, unsigned* __restrict__ counters) {
     __shared__ __attribute__((aligned(16))) unsigned char smem[kTransposeLds];
     const int i = blockIdx.x;
+    if (i == 0 && counters) for (int k = threadIdx.x; k < kSplitCounters; k += 256) counters[k] = 0;
     if (i < n_own) vnm8_repack_body(i % nc, i / nc, vals, meta, colidx, T, F, vcb, mcb, cixt);
     else transpose_part(smem, i - n_own, t);
 }
@@ -190,11 +192,11 @@ __global__ void __launch_bounds__(256) vnm_compact_t_kernel(const uint16_t* __re
 static int64_t transpose_tiles(TransposeOf* t) { t->tc = (int)(t->C / 64); return t->in ? t->C / 64 * (t->R / 64) : 0; }
 
 hipError_t launch_vnm8_repack(const uint16_t* vals, const uint8_t* meta, const uint8_t* colidx, int64_t T, int64_t F, uint16_t* vcb, uint8_t* mcb,
-                              uint8_t* cixt, const uint16_t* W, int64_t R, int64_t C, int64_t ld, uint16_t* wt, hipStream_t s) {
+                              uint8_t* cixt, const uint16_t* W, int64_t R, int64_t C, int64_t ld, uint16_t* wt, unsigned* counters, hipStream_t s) {
     TransposeOf t = {W, R, C, ld, wt, 0, 0};
     const int64_t nc = (F + 511) / 512, own = nc * (T / 64), n = own + transpose_tiles(&t);
     if (n >= ((int64_t)1 << 31)) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(vnm8_repack_kernel, dim3((unsigned)n), dim3(256), 0, s, vals, meta, colidx, T, (int)F, vcb, mcb, cixt, (int)nc, (int)own, t);
+    hipLaunchKernelGGL(vnm8_repack_kernel, dim3((unsigned)n), dim3(256), 0, s, vals, meta, colidx, T, (int)F, vcb, mcb, cixt, (int)nc, (int)own, t, counters);
     return hipGetLastError();
 }
 
@@ -218,9 +220,15 @@ hipError_t launch_vnm_compact_t(const uint16_t* vals, const uint8_t* meta, const
     return hipGetLastError();
 }
 
-hipError_t launch_transpose(const uint16_t* in, int64_t R, int64_t C, int64_t ld, uint16_t* out, int blocked, uint16_t* out_same, hipStream_t s) {
+hipError_t launch_transpose(const uint16_t* in, int64_t R, int64_t C, int64_t ld, uint16_t* out, int blocked, uint16_t* out_same, hipStream_t s, unsigned* counters) {
     dim3 grid((unsigned)(C / 64), (unsigned)(R / 64));
-    hipLaunchKernelGGL(transpose_bf16_kernel, grid, dim3(256), 0, s, in, R, C, ld, out, blocked, out_same);
+    hipLaunchKernelGGL(transpose_bf16_kernel, grid, dim3(256), 0, s, in, R, C, ld, out, blocked, out_same, counters);
+    return hipGetLastError();
+}
+
+__global__ void __launch_bounds__(256) clear_counters_kernel(unsigned* counters) { counters[blockIdx.x * 256 + threadIdx.x] = 0; }
+hipError_t launch_clear_counters(unsigned* counters, hipStream_t s) {
+    hipLaunchKernelGGL(clear_counters_kernel, dim3(kSplitCounters / 256), dim3(256), 0, s, counters);
     return hipGetLastError();
 }
 

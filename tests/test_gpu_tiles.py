@@ -106,3 +106,23 @@ def test_grouping_at_the_edges_of_its_blocks(T, M):
     perm, seg = oracle.expert_permutation(to_bits(r["expert"]), M // 4)
     assert r["seg"] == [int(v) for v in seg] and np.array_equal(to_bits(r["perm"]), perm)
     assert np.array_equal(perm[to_bits(r["row_of_token"])], np.arange(T))
+
+
+@pytest.mark.parametrize("M,T,D,F", [
+    (8, 64, 3968, 8192),
+    (8, 192, 2048, 8256),       # several token blocks; 129 stages
+    (16, 64, 3968, 8192),       # gathered rows
+])
+def test_split_activation_contractions(M, T, D, F):
+    """Eqs. (3), (7) shared by several workgroups per tile: twice in a row (the counters are left as they were found), alone and in the step."""
+    inp = make_ffn_inputs(T, D, F, seed=33)
+    dev = [to_dev(inp[k]) for k in ("X", "W1", "W2", "b1", "dY")]
+    step = sffn.FfnStep(T, D, F, M=M)
+    first = [t.clone() for t in step(*dev)]
+    for a, b in zip(first, step(*dev)):
+        assert torch.equal(a, b)
+    y2 = [to_bits(step.saved()[k]) for k in ("y2_vals", "y2_meta", "colidx")]
+    assert_gemm_close(to_bits(first[0]), oracle.vnm_spmm(*y2, inp["W2"], 0, 64, M), "y3")
+    assert_gemm_close(to_bits(first[1]), oracle.vnm_spmm(to_bits(step.saved()["dy1_vals"]), *y2[1:], inp["W1"], 1, 64, M), "dX")
+    alone = sffn.vnm_spmm(*[step.saved()[k] for k in ("y2_vals", "y2_meta", "colidx")], dev[2], 0, 64, M)
+    assert_gemm_close(to_bits(alone), to_bits(first[0]), "y3 alone")
