@@ -192,34 +192,33 @@ __device__ __forceinline__ void gemm_nt_v2_body(unsigned char* __restrict__ smem
             m_lane = lane * 4; m_kstep = 512;
         }
     }
-    // the DMA loads of one stage, issued in two halves (h = 0, 1) so that they can sit between matrix instructions
-    auto issue_half = [&](int kt, int stage, int h) {
+    // DMA loads lo .. hi - 1 of a stage's LD (compile-time bounds): they are issued one at a time between matrix instructions
+    constexpr int LD = A_LD + B_LD + (FP8 ? 2 * M_LD : M_LD);
+    static_assert(LD == C::LOADS, "loads in flight");
+    auto issue = [&](int kt, int stage, int lo, int hi) {
         unsigned char* sa = ring + stage * C::STAGE;
         unsigned char* sb = sa + C::A_BYTES;
         unsigned char* sm = sb + C::B_BYTES;
         // the k position goes into the 32-bit per-lane offset (one vector add per operand); the bases stay put in SGPRs
-        if (h == 0) {
-            const uint32_t ao = a_lane + (uint32_t)kt * a_kstep, bo = b_lane + (uint32_t)kt * b_kstep, bo1 = b_lane1 + (uint32_t)kt * b_kstep;
+        const uint32_t ao = a_lane + (uint32_t)kt * a_kstep, bo = b_lane + (uint32_t)kt * b_kstep, bo1 = b_lane1 + (uint32_t)kt * b_kstep;
 #pragma unroll
-            for (int n = 0; n < A_LD; ++n) dma16(a_base[n], ao, sa + (wt * A_LD + n) * 1024);
+        for (int n = 0; n < A_LD; ++n)
+            if (n >= lo && n < hi) dma16(a_base[n], ao, sa + (wt * A_LD + n) * 1024);
 #pragma unroll
-            for (int n = 0; n < B_LD / 2; ++n) dma16(b_base[n], (lineB && (n & 1)) ? bo1 : bo, sb + (wt * B_LD + n) * 1024);
-        } else {
-            const uint32_t bo = b_lane + (uint32_t)kt * b_kstep, bo1 = b_lane1 + (uint32_t)kt * b_kstep;
+        for (int n = 0; n < B_LD; ++n)
+            if (A_LD + n >= lo && A_LD + n < hi) dma16(b_base[n], (lineB && (n & 1)) ? bo1 : bo, sb + (wt * B_LD + n) * 1024);
 #pragma unroll
-            for (int n = B_LD / 2; n < B_LD; ++n) dma16(b_base[n], (lineB && (n & 1)) ? bo1 : bo, sb + (wt * B_LD + n) * 1024);
-#pragma unroll
-            for (int n = 0; n < M_LD; ++n) {
-                if (!FP8) dma4(m_base[n], m_lane + (uint32_t)kt * m_kstep, sm + (wt * M_LD + n) * 256);
-                else {
-                    dma4(m_base[n], m_lane + (uint32_t)kt * m_kstep, sm + (wt * M_LD + n) * 512);
-                    // second half of the 32 rows: the next 256 bytes of a blocked unit, or 16 rows further down a row-major array
-                    dma4(m_base[n], m_lane + (blocked ? 256u : (uint32_t)(16 * (Kld / 4))) + (uint32_t)kt * m_kstep, sm + (wt * M_LD + n) * 512 + 256);
-                }
+        for (int n = 0; n < M_LD; ++n) {
+            if (!FP8) {
+                if (A_LD + B_LD + n >= lo && A_LD + B_LD + n < hi) dma4(m_base[n], m_lane + (uint32_t)kt * m_kstep, sm + (wt * M_LD + n) * 256);
+            } else {
+                const int i = A_LD + B_LD + 2 * n;
+                if (i >= lo && i < hi) dma4(m_base[n], m_lane + (uint32_t)kt * m_kstep, sm + (wt * M_LD + n) * 512);
+                // second half of the 32 rows: the next 256 bytes of a blocked unit, or 16 rows further down a row-major array
+                if (i + 1 >= lo && i + 1 < hi) dma4(m_base[n], m_lane + (blocked ? 256u : (uint32_t)(16 * (Kld / 4))) + (uint32_t)kt * m_kstep, sm + (wt * M_LD + n) * 512 + 256);
             }
         }
     };
-    auto issue = [&](int kt, int stage) { issue_half(kt, stage, 0); issue_half(kt, stage, 1); };
 
     // ---- per-lane LDS offsets of the fragment reads (inside a stage) --------------------------------
     int a_off[FM], b_off[FN], m_off[FM];
@@ -302,47 +301,58 @@ __device__ __forceinline__ void gemm_nt_v2_body(unsigned char* __restrict__ smem
     // barrier that ends its last fragment reads, so a tile has almost NSTAGE - 1 steps to arrive.
     // (KW > 1: the ring belongs to one wavefront, whose own waits order its loads and reads.)
 #pragma unroll
-    for (int p = 0; p < C::NSTAGE; ++p) issue(step_of(p < nk ? p : nk - 1), p);
+    for (int p = 0; p < C::NSTAGE; ++p) issue(step_of(p < nk ? p : nk - 1), p, 0, LD);
     wait_vmcnt<(C::NSTAGE - 1) * C::LOADS>();
     if (KW == 1) __syncthreads();
     else asm volatile("" ::: "memory");
     FragSet P, Q;
     read_frags(P, 0, 0);
     int stage = 0;
-    // One step = two halves of FM x FN matrix instructions.  Each row of matrix instructions (64+ cycles of
-    // the matrix pipe) is followed in program order by a few LDS reads for the other fragment set or by
-    // half of a stage's DMA issue, so the non-matrix work of a wave hides behind its own MFMAs.
+    // One step = two halves of FM x FN matrix instructions.  Each row of matrix instructions (64+ cycles of the matrix pipe) is followed in program
+    // order by a few LDS reads for the other fragment set and by one or two of the loads of a stage: a CU takes 57 bytes of them per cycle,
+    // and a wavefront that has to wait for its turn cannot issue matrix instructions either.  The refill of a stage therefore stretches from
+    // the barrier that frees it to the next one.  (All of it right behind the barrier, T = D = 8192, F = 28672: 2045 us; spread: 1930.)
+    constexpr int SLOTS = C::NSTAGE > 2 ? 2 * FM : FM;
+#define ISSUE(i) issue(re_kt, re_stage, LD * (i) / SLOTS, LD * ((i) + 1) / SLOTS)
+    int re_kt = step_of(C::NSTAGE - 1 < nk ? C::NSTAGE - 1 : nk - 1), re_stage = C::NSTAGE - 1;      // (the first step's second half of a refill: the last stage's again)
     for (int kt = 0; kt < nk; ++kt) {
-        const int nxt = step_of((kt + C::NSTAGE < nk) ? kt + C::NSTAGE : nk - 1);
         const int next_stage = (stage + 1 == C::NSTAGE) ? 0 : stage + 1;
         const unsigned char* st = ring + stage * C::STAGE;
         const unsigned char* sn = ring + next_stage * C::STAGE;
         mma_row(P, 0, false); SB();
+        ISSUE(FM);
         read_a(Q, P, st, 1, 0); read_a(Q, P, st, 1, 1); read_b(Q, st, 1, 0); if (FM == 2) read_b(Q, st, 1, 1); SB();
         mma_row(P, 1, false); SB();
+        ISSUE(FM + 1);
         if (FM == 4) {
             read_a(Q, P, st, 1, FM - 2); read_a(Q, P, st, 1, FM - 1); read_b(Q, st, 1, 1); SB();
             mma_row(P, FM - 2, false); SB();
+            ISSUE(2 * FM - 2); SB();
             mma_row(P, FM - 1, false); SB();
+            ISSUE(2 * FM - 1); SB();
         }
         // Q has arrived and tile kt+1 has landed (this wave's part); after the barrier every wave is done
-        // reading this stage, which is refilled at once, and every wave's part of tile kt+1 is in LDS
+        // reading this stage, which is refilled, and every wave's part of tile kt+1 is in LDS
         wait_vmcnt_lgkm0<(C::NSTAGE - 2) * C::LOADS>();
         if (KW == 1) __builtin_amdgcn_s_barrier();
         else asm volatile("" ::: "memory");
         SB();
+        re_kt = step_of((kt + C::NSTAGE < nk) ? kt + C::NSTAGE : nk - 1); re_stage = stage;
         mma_row(Q, 0, true); SB();
-        issue_half(nxt, stage, 0); SB();
+        ISSUE(0);
         read_a(P, P, sn, 0, 0); read_a(P, P, sn, 0, 1); read_b(P, sn, 0, 0); if (FM == 2) read_b(P, sn, 0, 1); SB();
         mma_row(Q, 1, true); SB();
-        issue_half(nxt, stage, 1); SB();
+        ISSUE(1); SB();
         if (FM == 4) {
             read_a(P, P, sn, 0, FM - 2); read_a(P, P, sn, 0, FM - 1); read_b(P, sn, 0, 1); SB();
             mma_row(Q, FM - 2, true); SB();
+            ISSUE(2); SB();
             mma_row(Q, FM - 1, true); SB();
+            ISSUE(3); SB();
         }
         stage = next_stage;
     }
+#undef ISSUE
 #undef SB
     wait_vmcnt<0>();
     }

@@ -169,25 +169,23 @@ __device__ __forceinline__ void vnm8_gemm_body(unsigned char* __restrict__ smem,
     }
     const uint32_t c_kstep = (uint32_t)NTB * (FP8 ? 64u : 32u);
     constexpr uint32_t m_kstep = FP8 ? 512u : 256u;
-    auto issue_half = [&](int kt, int stage, int h) {
+    // loads lo .. hi - 1 of a stage's kLoads (compile-time bounds)
+    auto issue = [&](int kt, int stage, int lo, int hi) {
         unsigned char* sb = ring + stage * kStage;
         unsigned char* sa = sb + kB;
         unsigned char* sm = sa + kA;
         unsigned char* sc = sm + kMt;
-        if (h == 0) {
 #pragma unroll
-            for (int i = 0; i < B_LD / 2; ++i) dma16(w_base, b_lane[i] + (uint32_t)kt * b_kstep, sb + (B_LD * wt + i) * 1024);
+        for (int i = 0; i < B_LD; ++i)
+            if (i >= lo && i < hi) dma16(w_base, b_lane[i] + (uint32_t)kt * b_kstep, sb + (B_LD * wt + i) * 1024);
 #pragma unroll
-            for (int i = 0; i < A_LD; ++i) dma16(a_base[i], a_lane + (uint32_t)kt * 1024u, sa + (wt * A_LD + i) * 1024);
-            dma4(c_base, c_lane + (uint32_t)kt * c_kstep, sc);
-        } else {
+        for (int i = 0; i < A_LD; ++i)
+            if (B_LD + i >= lo && B_LD + i < hi) dma16(a_base[i], a_lane + (uint32_t)kt * 1024u, sa + (wt * A_LD + i) * 1024);
 #pragma unroll
-            for (int i = B_LD / 2; i < B_LD; ++i) dma16(w_base, b_lane[i] + (uint32_t)kt * b_kstep, sb + (B_LD * wt + i) * 1024);
-#pragma unroll
-            for (int i = 0; i < M_LD; ++i) dma4(m_base[i], m_lane + (uint32_t)kt * m_kstep, sm + ((wt * M_LD + i) % (kMt / 256)) * 256);
-        }
+        for (int i = 0; i < M_LD; ++i)
+            if (B_LD + A_LD + i >= lo && B_LD + A_LD + i < hi) dma4(m_base[i], m_lane + (uint32_t)kt * m_kstep, sm + ((wt * M_LD + i) % (kMt / 256)) * 256);
+        if (kLoads - 1 >= lo && kLoads - 1 < hi) dma4(c_base, c_lane + (uint32_t)kt * c_kstep, sc);
     };
-    auto issue = [&](int kt, int stage) { issue_half(kt, stage, 0); issue_half(kt, stage, 1); };
 
     // ---- per-lane LDS offsets of the fragment reads (inside a stage).  A wave owns one token block (64 tokens) x 32 FN output columns: the
     //      B fragments it gathers belong to one column selection. ----------------------
@@ -244,9 +242,7 @@ __device__ __forceinline__ void vnm8_gemm_body(unsigned char* __restrict__ smem,
             }
         }
     };
-    auto mma_half = [&](const AFrags& fa, const BPair& fb, int half) {
-#pragma unroll
-        for (int a2 = 0; a2 < 2; ++a2)
+    auto mma_half = [&](const AFrags& fa, const BPair& fb, int half, int a2) {
 #pragma unroll
             for (int fn = 0; fn < HB; ++fn)
                 if (FP8) acc[a2][HB * half + fn] = __builtin_amdgcn_smfmac_f32_32x32x64_fp8_fp8(fa.a[a2].q, fb.b[fn].v8, acc[a2][HB * half + fn], fa.idx[a2], 0, 0);
@@ -258,7 +254,7 @@ __device__ __forceinline__ void vnm8_gemm_body(unsigned char* __restrict__ smem,
     auto step_of = [&](int kt) { return ks0 + kg + kt * KW; };
     if (nk > 0) {
 #pragma unroll
-    for (int p = 0; p < kStages; ++p) issue(step_of(p < nk ? p : nk - 1), p);
+    for (int p = 0; p < kStages; ++p) issue(step_of(p < nk ? p : nk - 1), p, 0, kLoads);
     wait_vmcnt<(kStages - 1) * kLoads>();
     if (KW == 1) __syncthreads();
     else asm volatile("" ::: "memory");
@@ -267,27 +263,34 @@ __device__ __forceinline__ void vnm8_gemm_body(unsigned char* __restrict__ smem,
     read_a(A0, ring);
     read_b(P, ring, A0.cw, 0);
     int stage = 0;
-    // two stages per trip so that the A fragment buffers alternate without copies
+    // two stages per trip so that the A fragment buffers alternate without copies.  The loads of a refill are spread from the barrier that frees its stage
+    // to the next one (gemm_v2_body.hpp says why); the first step's first ones repeat the last stage's.
+    int re_kt = step_of(kStages - 1 < nk ? kStages - 1 : nk - 1), re_stage = kStages - 1;
+#define ISSUE(i) issue(re_kt, re_stage, kLoads * (i) / 4, kLoads * ((i) + 1) / 4)
     auto step = [&](int kt, AFrags& cur, AFrags& nxt_a) {
-        const int nxt = step_of((kt + kStages < nk) ? kt + kStages : nk - 1);
         const int next_stage = (stage + 1 == kStages) ? 0 : stage + 1;
         const unsigned char* st = ring + stage * kStage;
         const unsigned char* sn = ring + next_stage * kStage;
-        mma_half(cur, P, 0); SB();
+        mma_half(cur, P, 0, 0); SB();
+        ISSUE(2); SB();
+        mma_half(cur, P, 0, 1); SB();
         read_b(Q, st, cur.cw, 1); SB();
-        // Q has arrived and this wave's part of tile kt + 1 has landed; after the barrier every wave is done reading this stage, which is
-        // refilled at once
+        ISSUE(3); SB();
+        // Q has arrived and this wave's part of tile kt + 1 has landed; after the barrier every wave is done reading this stage
         wait_vmcnt_lgkm0<(kStages - 2) * kLoads>();
         if (KW == 1) __builtin_amdgcn_s_barrier();
         else asm volatile("" ::: "memory");
         SB();
-        issue_half(nxt, stage, 0); SB();
+        re_kt = step_of((kt + kStages < nk) ? kt + kStages : nk - 1); re_stage = stage;
+        ISSUE(0); SB();
         read_a(nxt_a, sn); SB();
-        mma_half(cur, Q, 1); SB();
-        issue_half(nxt, stage, 1); SB();
+        mma_half(cur, Q, 1, 0); SB();
+        ISSUE(1); SB();
+        mma_half(cur, Q, 1, 1); SB();
         read_b(P, sn, nxt_a.cw, 0); SB();
         stage = next_stage;
     };
+#undef ISSUE
     int kt = 0;
     for (; kt + 1 < nk; kt += 2) {
         step(kt, A0, A1);

@@ -270,24 +270,19 @@ __device__ __forceinline__ void wgrad_vnm_body(unsigned char* __restrict__ smem,
     }
     const uint32_t c_kstep = (uint32_t)(F / 8);
 
-    auto issue_half = [&](int kt, int stage, int h) {
+    // loads lo .. hi - 1 of a stage's kLoads (compile-time bounds)
+    auto issue = [&](int kt, int stage, int lo, int hi) {
         unsigned char* sa = ring + stage * kStage;
         unsigned char* sb = sa + kABytes;
         unsigned char* sc = sb + kBBytes;
         const uint32_t o = blk_lane + (uint32_t)kt * 2048;      // k position in the per-lane offset; bases stay in SGPRs
-        if (h == 0) {
-            dma4(c_base, c_lane + (uint32_t)kt * c_kstep, sc + wt * 256);     // first: the look-up wants it earliest
+        if (lo <= 0 && hi > 0) dma4(c_base, c_lane + (uint32_t)kt * c_kstep, sc + wt * 256);     // first: the look-up wants it earliest
 #pragma unroll
-            for (int n = 0; n < A_LD; ++n) {
-                dma16(a_base[n][0], o, sa + (wt * A_LD + n) * 1024);
-                dma16(a_base[n][1], o, sa + kAHalf + (wt * A_LD + n) * 1024);
-            }
+        for (int n = 0; n < 2 * A_LD; ++n)
+            if (1 + n >= lo && 1 + n < hi) dma16(a_base[n >> 1][n & 1], o, sa + (n & 1) * kAHalf + (wt * A_LD + (n >> 1)) * 1024);
 #pragma unroll
-            for (int n = 0; n < B_LD / 2; ++n) dma16(b_base[n], o, sb + (wt * B_LD + n) * 1024);
-        } else {
-#pragma unroll
-            for (int n = B_LD / 2; n < B_LD; ++n) dma16(b_base[n], o, sb + (wt * B_LD + n) * 1024);
-        }
+        for (int n = 0; n < B_LD; ++n)
+            if (1 + 2 * A_LD + n >= lo && 1 + 2 * A_LD + n < hi) dma16(b_base[n], o, sb + (wt * B_LD + n) * 1024);
     };
 
     // ---- fragment reads.  Sub-step s (16 tokens) of a stage lives in half s / 2 at chunk pair s % 2. ----
@@ -351,7 +346,7 @@ __device__ __forceinline__ void wgrad_vnm_body(unsigned char* __restrict__ smem,
         for (int i = wt * 64 + lane; i < kStages * 2 * 16; i += TL::NW * 64)
             *reinterpret_cast<uint32_t*>(ring + (i >> 5) * kStage + ((i >> 4) & 1) * kAHalf + TL::kZero + (i & 15) * 4) = 0u;
 #pragma unroll
-        for (int p = 0; p < kStages; ++p) { issue_half(step_of(p < nk ? p : nk - 1), p, 0); issue_half(step_of(p < nk ? p : nk - 1), p, 1); }
+        for (int p = 0; p < kStages; ++p) issue(step_of(p < nk ? p : nk - 1), p, 0, kLoads);
         wait_vmcnt<(kStages - 1) * kLoads>();
         if (KW == 1) __syncthreads();
         else { wave_lds_sync(); asm volatile("" ::: "memory"); }
@@ -377,14 +372,17 @@ __device__ __forceinline__ void wgrad_vnm_body(unsigned char* __restrict__ smem,
         // One step = one stage = four sub-steps of FM x FN matrix instructions; the fragments of a sub-step are read
         // while the matrix cores work on the one before.  Before the last sub-step every wavefront has read all of
         // the stage (barrier), which is then refilled with the tile three steps ahead while the next stage's rows
-        // are looked up and its first fragments fetched.
+        // are looked up and its first fragments fetched.  The loads are spread over three sub-steps (gemm_v2_body.hpp says why), all of them
+        // before the wait for the next mask bytes; the first step's first ones repeat the last stage's.
+        int re_kt = step_of(kStages - 1 < nk ? kStages - 1 : nk - 1), re_stage = kStages - 1;
+#define ISSUE(i) issue(re_kt, re_stage, kLoads * (i) / 6, kLoads * ((i) + 1) / 6)
         for (int kt = 0; kt < nk; ++kt) {
-            const int nxt = step_of((kt + kStages < nk) ? kt + kStages : nk - 1);
             const int next_stage = (stage + 1 == kStages) ? 0 : stage + 1;
             const unsigned char* st = ring + stage * kStage;
             const unsigned char* sn = ring + next_stage * kStage;
-            sub_step(P, Q, st, 1, [&] {}, [&] {});
+            sub_step(P, Q, st, 1, [&] { ISSUE(2); }, [&] { ISSUE(3); });
             sub_step(Q, P, st, 2, [&] {
+                ISSUE(4); ISSUE(5);
                 // the next tile's mask bytes were the first load of its batch: all but kLoads - 1 of that batch and
                 // the batch after it may still be in flight
                 wait_vmcnt<(kStages - 2) * kLoads + kLoads - 1>();
@@ -398,9 +396,11 @@ __device__ __forceinline__ void wgrad_vnm_body(unsigned char* __restrict__ smem,
             SB();
 #pragma unroll
             for (int a = 0; a < FM; ++a) { a_off[a][0] = a_next[a][0]; a_off[a][1] = a_next[a][1]; }
-            sub_step(Q, P, sn, 0, [&] { issue_half(nxt, stage, 0); }, [&] { issue_half(nxt, stage, 1); });
+            re_kt = step_of((kt + kStages < nk) ? kt + kStages : nk - 1); re_stage = stage;
+            sub_step(Q, P, sn, 0, [&] { ISSUE(0); }, [&] { ISSUE(1); });
             stage = next_stage;
         }
+#undef ISSUE
         wait_vmcnt<0>();
     }
 #undef SB
@@ -475,14 +475,16 @@ __device__ __forceinline__ void wgrad_vnm_fp8_body(unsigned char* __restrict__ s
         c_lane = (uint32_t)g;
     }
     const uint32_t c_kstep = (uint32_t)(F / 8);
-    auto issue = [&](int kt, int stage) {
+    auto issue = [&](int kt, int stage, int lo, int hi) {
         unsigned char* sa = ring + stage * kStage;
         const uint32_t o = blk_lane + (uint32_t)kt * 1024;
-        dma4(c_base, c_lane + (uint32_t)kt * c_kstep, sa + k8A + k8B + wt * 256);     // first: the look-up wants it earliest
+        if (lo <= 0 && hi > 0) dma4(c_base, c_lane + (uint32_t)kt * c_kstep, sa + k8A + k8B + wt * 256);     // first: the look-up wants it earliest
 #pragma unroll
-        for (int n = 0; n < A_LD; ++n) dma16(a_base[n], o, sa + (wt * A_LD + n) * 1024);
+        for (int n = 0; n < A_LD; ++n)
+            if (1 + n >= lo && 1 + n < hi) dma16(a_base[n], o, sa + (wt * A_LD + n) * 1024);
 #pragma unroll
-        for (int n = 0; n < B_LD; ++n) dma16(b_base[n], o, sa + k8A + (wt * B_LD + n) * 1024);
+        for (int n = 0; n < B_LD; ++n)
+            if (1 + A_LD + n >= lo && 1 + A_LD + n < hi) dma16(b_base[n], o, sa + k8A + (wt * B_LD + n) * 1024);
     };
 
     // fragment reads: a lane wants the 32 bytes k 32 lh .. + 31 of its row = 16-byte chunks 2 lh, 2 lh + 1 (slot = chunk ^ ((row >> 2) & 3))
@@ -536,7 +538,7 @@ __device__ __forceinline__ void wgrad_vnm_fp8_body(unsigned char* __restrict__ s
     if (nk > 0) {
         for (int i = wt * 64 + lane; i < kStages * 16; i += TL::NW * 64) *reinterpret_cast<uint32_t*>(ring + (i >> 4) * kStage + TL::kZero + (i & 15) * 4) = 0u;   // the rows of zeros
 #pragma unroll
-        for (int p = 0; p < kStages; ++p) issue(step_of(p < nk ? p : nk - 1), p);
+        for (int p = 0; p < kStages; ++p) issue(step_of(p < nk ? p : nk - 1), p, 0, kLoads);
         wait_vmcnt<(kStages - 1) * kLoads>();
         if (KW == 1) __syncthreads();
         else { wave_lds_sync(); asm volatile("" ::: "memory"); }
@@ -549,16 +551,21 @@ __device__ __forceinline__ void wgrad_vnm_fp8_body(unsigned char* __restrict__ s
 #pragma unroll
         for (int b = 0; b < FN; ++b) read_b(B0[b], ring, b);
         int stage = 0;
-        // One step = one token block; two steps per loop trip so that the two G fragment sets alternate by name.
+        // One step = one token block; two steps per loop trip so that the two G fragment sets alternate by name.  The loads of a refill are spread
+        // as in the bf16 kernel.
+        constexpr int SLOTS = FM == 4 ? 4 : 2;
+        int re_kt = step_of(kStages - 1 < nk ? kStages - 1 : nk - 1), re_stage = kStages - 1;
+#define ISSUE(i) issue(re_kt, re_stage, kLoads * (i) / SLOTS, kLoads * ((i) + 1) / SLOTS)
         auto step = [&](int kt, Frag16 (&Bc)[FN], Frag16 (&Bn)[FN]) {
-            const int nxt = step_of((kt + kStages < nk) ? kt + kStages : nk - 1);
             const int next_stage = (stage + 1 == kStages) ? 0 : stage + 1;
             const unsigned char* sn = ring + next_stage * kStage;
             read_a(A1, a_off[1]); SB();
             if (FM == 4) {
                 mma_row(A0, Bc, 0); SB();
+                ISSUE(2);
                 read_a(A0, a_off[FM - 2]); SB();
                 mma_row(A1, Bc, 1); SB();
+                ISSUE(3);
                 read_a(A1, a_off[FM - 1]); SB();
             }
             // the next block's mask bytes were the first load of its batch
@@ -570,7 +577,8 @@ __device__ __forceinline__ void wgrad_vnm_fp8_body(unsigned char* __restrict__ s
             if (KW == 1) __builtin_amdgcn_s_barrier();
             else asm volatile("" ::: "memory");
             SB();
-            issue(nxt, stage); SB();
+            re_kt = step_of((kt + kStages < nk) ? kt + kStages : nk - 1); re_stage = stage;
+            ISSUE(0); SB();
             lookup(next_stage); SB();
 #pragma unroll
             for (int a = 0; a < FM; ++a) a_off[a] = a_next[a];
@@ -579,11 +587,13 @@ __device__ __forceinline__ void wgrad_vnm_fp8_body(unsigned char* __restrict__ s
             for (int b = 0; b < FN; ++b) read_b(Bn[b], sn, b);
             SB();
             mma_row(A1, Bc, FM - 1); SB();
+            ISSUE(1); SB();
             stage = next_stage;
         };
         int kt = 0;
         for (; kt + 1 < nk; kt += 2) { step(kt, B0, B1); step(kt + 1, B1, B0); }
         if (kt < nk) step(kt, B0, B1);
+#undef ISSUE
         wait_vmcnt<0>();
     }
 #undef SB
