@@ -662,7 +662,7 @@ int run_fp8_step(const sffn_cfg* cfg, const sffn_fp8_scales* sc, int n_experts, 
     VnmEpilogue ep4;
     ep4.mode = wide ? 6 : 2; ep4.logM = logM; ep4.store_dense = keep_dense; ep4.vals = wide ? (uint16_t*)dy1c : dy1v; ep4.meta = y2m; ep4.colidx = cix;
     ep4.ykept = ykept; ep4.at = at2; ep4.inv_out = 1.0f / sc->dy1; ep4.at_fp8 = w8; ep4.amax = ady1;
-    if (!wide) ep4.vcb = (uint16_t*)vcb2;
+    if (!wide) { ep4.vcb = (uint16_t*)vcb2; ep4.mcb = mcb; }
     if (tiles.mix) {
         const GemmGroup none;
         const int Kc = (int)(4 * F / M);
@@ -1331,7 +1331,7 @@ static int run_step(const sffn_cfg* cfg, int n_experts, const int64_t* seg, cons
     // eq. (4), then eq. (6) on y2's kept slots
     VnmEpilogue ep4;
     ep4.mode = 2; ep4.store_dense = keep_dense; ep4.vals = lean ? nullptr : dy1v; ep4.meta = y2m; ep4.colidx = cix; ep4.ykept = ykept;
-    ep4.vcb = vcb2; ep4.at = at2;
+    ep4.vcb = vcb2; ep4.mcb = mcb; ep4.at = at2;
     if (tiles.mix) {
         const GemmGroup none;
         const Vnm8Args v3 = {vcb, mcb, cixt, (const uint8_t*)w2t, (int)D, (int)T, (int)D, (int)F, Y3, D, 0, 0, gd ? *gd : none, 1.0f, split};

@@ -197,6 +197,23 @@ __device__ __forceinline__ uint32_t row_shl(uint32_t x) {
     return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x100 | N, 0xF, 0xF, true);
 }
 
+// the same with any control word: permutations inside groups of 4, mirrored groups of 8, rotation of a row of 16 (| 1 .. 15, lane i <- lane i - n)
+constexpr int kQuadXor1 = 0xB1, kQuadXor2 = 0x4E, kQuadXor3 = 0x1B, kRowHalfMirror = 0x141, kRowRor = 0x120;
+template <int CTRL>
+__device__ __forceinline__ uint32_t dpp(uint32_t x) {
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, CTRL, 0xF, 0xF, true);
+}
+// bitwise OR over every aligned group of 8 lanes, in all of them
+__device__ __forceinline__ uint32_t or_of_8(uint32_t x) {
+    x |= dpp<kQuadXor1>(x);
+    x |= dpp<kQuadXor2>(x);
+    return x | dpp<kRowHalfMirror>(x);
+}
+
+// lane I of every aligned group of 8 lanes, in all of them
+template <int I>
+__device__ __forceinline__ uint32_t bcast_of_8(uint32_t x) { return (uint32_t)__builtin_amdgcn_ds_swizzle((int)x, (I << 5) | 0x18); }
+
 // y1 at y2's kept slots, as the fused epilogues write and read it: 2 KB runs of (64 tokens x 8 column blocks);
 // index in 32-bit words of (token t, column block blk), F = d_ffn.
 __host__ __device__ __forceinline__ int64_t ykept_off(int64_t t, int64_t blk, int64_t F) {

@@ -46,13 +46,64 @@ struct Cfg {
     static constexpr int LOADS = A_LD + B_LD + M_LD * (FP8 ? 2 : 1);
 };
 
-// bf16 bits -> max(y, 0)^2 rounded to bf16 (RNE), returned as the fp32 bit pattern (low half zero).
-// r * r is never NaN here (a NaN input fails the comparison and becomes 0), so no NaN path is needed.
+// max(x, 0) in one instruction, 0 for NaN.  (As a comparison, as fmaxf or with an infinity that the compiler sees: two, the first to quiet a NaN.)
+__device__ __forceinline__ float relu1(float x) {
+    float inf = __builtin_inff();
+    asm("" : "+s"(inf));
+    return __builtin_amdgcn_fmed3f(x, 0.0f, inf);
+}
+// eq. (2): bf16 bits -> max(y, 0)^2 rounded to bf16 (RNE), one value or the two of a word
 __device__ __forceinline__ uint32_t sqrelu16(uint32_t y) {
-    const float f = bf2f(y), r = f > 0.0f ? f : 0.0f;
+    const float r = relu1(bf2f(y));
     return f2bf(r * r);
 }
-__device__ __forceinline__ uint32_t sqrelu_hi(uint32_t y) { return sqrelu16(y) << 16; }
+__device__ __forceinline__ uint32_t sqrelu2(uint32_t w) {
+    const float a = relu1(__uint_as_float(w << 16)), b = relu1(__uint_as_float(w & 0xFFFF0000u));
+    return f2bf2(a * a, b * b);
+}
+// The 2:4 choice of the V:N:M epilogues among the four kept columns of a block, for values that are not negative (y2): the two largest, ties to the lower
+// column, in ascending column order as low | high << 16.  A key is the value in its upper half over tag[i], which falls with i, so that the order of the
+// keys is the order of the rule; keys come back with the values.  (With ranks out of six comparisons: 50 instructions instead of 20.)
+__device__ __forceinline__ uint32_t pick24_pos(uint32_t y01, uint32_t y23, const uint32_t (&tag)[4], uint32_t& low, uint32_t& high) {
+    const uint32_t k0 = (y01 << 16) | tag[0], k1 = (y01 & 0xFFFF0000u) | tag[1], k2 = (y23 << 16) | tag[2], k3 = (y23 & 0xFFFF0000u) | tag[3];
+    const uint32_t a = k0 > k1 ? k0 : k1, b = k0 > k1 ? k1 : k0, c = k2 > k3 ? k2 : k3, d = k2 > k3 ? k3 : k2;
+    const uint32_t first = a > c ? a : c, ac = a > c ? c : a, bd = b > d ? b : d, second = ac > bd ? ac : bd;
+    const bool ordered = (uint16_t)first > (uint16_t)second;      // the larger tag is the lower column
+    low = ordered ? first : second;
+    high = ordered ? second : first;
+    return __builtin_amdgcn_perm(high, low, 0x07060302u);         // upper halves
+}
+// Is the score of this lane's column among the four largest of its block of M lanes (ties to the lower column)?  sc: float32 bits, not negative.
+__device__ __forceinline__ bool keep4_of_8(uint32_t sc, int lane) {
+    const uint32_t a1 = lane & 1, a2 = (lane >> 1) & 1, a4 = (lane >> 2) & 1;         // lane ^ k is a lower column if the top bit of k is set in lane
+    const uint32_t m7 = dpp<kRowHalfMirror>(sc);
+    return (dpp<kQuadXor1>(sc) + a1 > sc) + (dpp<kQuadXor2>(sc) + a2 > sc) + (dpp<kQuadXor3>(sc) + a2 > sc) + (m7 + a4 > sc) + (dpp<kQuadXor1>(m7) + a4 > sc) +
+               (dpp<kQuadXor2>(m7) + a4 > sc) + (dpp<kQuadXor3>(m7) + a4 > sc) < 4;
+}
+// (M >= 16: the largest of the block four times over; M - 1 comparisons are more)
+template <int M>
+__device__ __forceinline__ bool keep4_of(uint32_t sc, int lane) {
+    const int c = lane & (M - 1);
+    int mine = (int)sc;
+    bool kept = false;
+#pragma unroll
+    for (int n = 0; n < 4; ++n) {
+        int x = mine, o;
+        o = (int)dpp<kRowRor | 8>((uint32_t)x); x = x > o ? x : o;
+        o = (int)dpp<kRowRor | 4>((uint32_t)x); x = x > o ? x : o;
+        o = (int)dpp<kRowRor | 2>((uint32_t)x); x = x > o ? x : o;
+        o = (int)dpp<kRowRor | 1>((uint32_t)x); x = x > o ? x : o;
+        if (M >= 32) { o = __builtin_amdgcn_ds_swizzle(x, (0x10 << 10) | 0x1F); x = x > o ? x : o; }
+        if (M == 64) { o = __shfl_xor(x, 32, 64); x = x > o ? x : o; }
+        const unsigned long long eq = __ballot(mine == x);
+        const uint32_t half = (uint32_t)(lane < 32 ? eq : eq >> 32);
+        const int first = M == 64 ? __builtin_ctzll(eq) : M == 32 ? __builtin_ctz(half) : __builtin_ctz((half >> (lane & 16)) & 0xFFFFu);
+        const bool me = first == c;
+        kept |= me;
+        mine = me ? -1 : mine;
+    }
+    return kept;
+}
 template <bool SPARSE, bool OUT_I_CONTIG, int EPI, bool BLOCKED, bool FP8, class TL>
 struct GemmV2Lds {
     using C = Cfg<SPARSE, FP8, TL>;
@@ -399,11 +450,12 @@ __device__ __forceinline__ void gemm_nt_v2_body(unsigned char* __restrict__ smem
         const int nblk = Ra >> 3;
         const int64_t F = Ra;
         uint32_t nib_h0 = 0;                                  // M = 64: the metadata nibble of the first half waits for the second's
-        // The lane's 32 bias values of each half, and (EPI 2) the saved column offsets, metadata and y1 of its 8 sweeps: all fetched here, for
+        // The lane's 32 bias values of each half (eq. (4) has none), and (EPI 2) the saved column offsets, metadata and y1 of its 8 sweeps: all fetched here, for
         // both halves.  Loads and stores share one in-order counter, so a load issued after the first half's stores would wait for all of them
         // (and for its own latency) in the middle of the epilogue.
+        constexpr bool BIAS = EPI != 2 && EPI != 4 && !GEN_B;
         float4 bb_all[NH][2][4];
-        uint32_t pre_cw[NH], pre_m_all[NH][8], pre_y_all[NH][8];
+        uint32_t pre_cw[NH], pre_m[NH], pre_y_all[NH][8];
         const uint32_t amax_seen = (FP8 && EPI != 0) ? amax_slot_peek(ep.amax) : 0u;
         float vmax_tile = 0.0f;                                 // fp8: largest survivor magnitude of the wave's tile
 #pragma unroll
@@ -414,23 +466,21 @@ __device__ __forceinline__ void gemm_nt_v2_body(unsigned char* __restrict__ smem
 #pragma unroll
                 for (int g = 0; g < 4; ++g) {
                     bb_all[h][a2][g] = make_float4(0.f, 0.f, 0.f, 0.f);
-                    if (bias) {
+                    if (BIAS && bias) {
                         int i = f0 + a2 * 32 + 8 * g + 4 * lh; i = i < Ra ? i : Ra - 4;
                         // EPI 3: compact column i of the expert is hidden unit (i / 4) * M + 4 e + i % 4 (bias already points at 4 e)
                         bb_all[h][a2][g] = *reinterpret_cast<const float4*>(EPI == 3 ? bias + ((int64_t)(i >> 2) << ep.logM) : bias + i);
                     }
                 }
             pre_cw[h] = 0x03020100u;
+            pre_m[h] = 0;
             if (EPI == 2 && t0 < Rb && f0 < Ra) {
-                const int64_t blk = (f0 >> 3) + (lane & 7);
-                pre_cw[h] = *reinterpret_cast<const uint32_t*>(ep.colidx + ((int64_t)(t0 >> 6) * nblk + blk) * 4);
-                const uint32_t* kp = reinterpret_cast<const uint32_t*>(ep.ykept) + ykept_off(t0 + (lane >> 3), blk, F);
-                const uint8_t* mp = ep.meta + (int64_t)(t0 + (lane >> 3)) * (F / 16) + (blk >> 1);
+                pre_cw[h] = *reinterpret_cast<const uint32_t*>(ep.colidx + ((int64_t)(t0 >> 6) * nblk + (f0 >> 3) + (lane & 7)) * 4);
+                // lane -> token lane / 8 + 8 (lane % 8): sweep `it` finds its eight nibbles in lane % 8 = it of its group of 8 lanes
+                pre_m[h] = *reinterpret_cast<const uint32_t*>(ep.mcb + (FP8 ? mcb8_off(t0, f0 >> 6, F) : mcb_off(t0, f0 >> 6, F)) + ((lane >> 3) + 8 * (lane & 7)) * (FP8 ? 8 : 4));
+                const uint32_t* kp = reinterpret_cast<const uint32_t*>(ep.ykept) + ykept_off(t0, f0 >> 3, F);
 #pragma unroll
-                for (int it = 0; it < 8; ++it) {
-                    pre_m_all[h][it] = mp[(int64_t)it * 8 * (F / 16)];
-                    pre_y_all[h][it] = kp[it * 64];
-                }
+                for (int it = 0; it < 8; ++it) pre_y_all[h][it] = kp[lane + it * 64];
             }
         }
         // (the same for the backward epilogue of the wide blocks)
@@ -461,6 +511,24 @@ __device__ __forceinline__ void gemm_nt_v2_body(unsigned char* __restrict__ smem
             tok_ok[b] = true;
             if (EPI == 3) { int j = t0 + b * 32 + l32; j = j < Rb ? j : Rb - 1; tok_ok[b] = ep.perm[j] >= 0; }
         }
+        // Column scores of the half tile: lane = column, strict ascending-row float32 sum of y2.  A transposing read hands every lane four rows of its column.
+        // (One 2-byte read per row: 64 reads and 450 vector instructions instead of 16 and 350.)
+        auto column_scores = [&]() {
+            const unsigned char* p = scratch + ((lane & 15) >> 2) * EP + (lane >> 4) * 32 + (lane & 3) * 8;
+            float sc = 0.0f;
+#pragma unroll
+            for (int r = 0; r < WN; r += 4) {
+                const uint2 w = __builtin_bit_cast(uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(p + r * EP)));
+                const uint32_t u = sqrelu2(w.x), v = sqrelu2(w.y);
+                sc = sc + __uint_as_float(u << 16);
+                sc = sc + __uint_as_float(u & 0xFFFF0000u);
+                sc = sc + __uint_as_float(v << 16);
+                sc = sc + __uint_as_float(v & 0xFFFF0000u);
+            }
+            return sc;
+        };
+        const uint32_t s_off = (uint32_t)(wt * WAVE_LDS);      // the scratch tile as an offset into smem (a multiple of 16, and so are its rows)
+        auto lds_u16 = [&](uint32_t off) { return (uint32_t)*reinterpret_cast<const uint16_t*>(smem + off); };
         // EPI 3, 4: the survivors as the dense transposed matrix at[f, t] (row length ep.at_ld), zeros at the dropped positions: the A operand of the
         // experts' weight gradients.  The half tile is turned in place (its rows have been read): two tokens make a word of one of the four rows of
         // the lane's group; the 16-byte chunks of a row are permuted by (row / 16) % 4 so that the 64 words of a store fall into 64 LDS banks.
@@ -500,7 +568,10 @@ __device__ __forceinline__ void gemm_nt_v2_body(unsigned char* __restrict__ smem
                         const int a = 2 * h + a2;
                         const int il = a2 * 32 + 8 * g + 4 * lh;              // i inside the 64-wide half
                         float v0, v1, v2, v3;
-                        if (FP8) {      // codes were multiplied: the product of the two tensor scales comes first, one rounding, then the bias
+                        if (!BIAS) {
+                            const float al = FP8 ? alpha : 1.0f;
+                            v0 = acc[a][b][4 * g] * al; v1 = acc[a][b][4 * g + 1] * al; v2 = acc[a][b][4 * g + 2] * al; v3 = acc[a][b][4 * g + 3] * al;
+                        } else if (FP8) {      // codes were multiplied: the product of the two tensor scales comes first, one rounding, then the bias
                             v0 = acc[a][b][4 * g] * alpha + bb[a2][g].x;     v1 = acc[a][b][4 * g + 1] * alpha + bb[a2][g].y;
                             v2 = acc[a][b][4 * g + 2] * alpha + bb[a2][g].z; v3 = acc[a][b][4 * g + 3] * alpha + bb[a2][g].w;
                         } else {
@@ -541,8 +612,9 @@ __device__ __forceinline__ void gemm_nt_v2_body(unsigned char* __restrict__ smem
                 for (int it = 0; it < 16; ++it) {
                     const int t = 2 * (lane >> 4) + 8 * (it >> 1) + (it & 1);
                     const uint2 w = *reinterpret_cast<const uint2*>(scratch + t * EP + g * 8);
-                    uint32_t nib;
-                    const uint32_t v = select24<false>(sqrelu16(w.x & 0xFFFFu), sqrelu16(w.x >> 16), sqrelu16(w.y & 0xFFFFu), sqrelu16(w.y >> 16), nib);
+                    uint32_t nib, low, high;
+                    const uint32_t v = pick24_pos(sqrelu2(w.x), sqrelu2(w.y), {3u, 2u, 1u, 0u}, low, high);
+                    nib = ((low & 3u) | ((high & 3u) << 2)) ^ 0xFu;
                     vv[it] = v; nn[it >> 3] |= nib << (4 * (it & 7));
                     uint32_t mw = nib | (row_shl<1>(nib) << 4);            // metadata of 8 groups -> one 32-bit store from every eighth lane
                     mw |= row_shl<2>(mw) << 8;
@@ -600,18 +672,9 @@ __device__ __forceinline__ void gemm_nt_v2_body(unsigned char* __restrict__ smem
                 uint32_t cb;                                              // the four kept column offsets of block b
                 unsigned long long bmask;                                 // and the same as a bit mask over the block's M columns
                 if (GEN_F) {
-                    float sc = 0.0f;
-#pragma unroll 8
-                    for (int r = 0; r < WN; ++r)
-                        sc = sc + __uint_as_float(sqrelu_hi(*reinterpret_cast<const uint16_t*>(scratch + r * EP + lane * 2)));
+                    const float sc = column_scores();
                     const int c = lane & (M - 1), base = lane - c;
-                    int rank = 0;
-#pragma unroll 8
-                    for (int k = 0; k < M; ++k) {
-                        const float o = __shfl(sc, base + k, 64);
-                        rank += (k < c) ? (o >= sc) : ((k > c) ? (o > sc) : 0);
-                    }
-                    const unsigned long long kept = __ballot(rank < 4);
+                    const unsigned long long kept = __ballot(keep4_of<M>(__float_as_uint(sc), lane));
                     unsigned long long bits = (M == 64) ? kept : ((kept >> base) & ((1ull << (M & 63)) - 1ull));
                     const unsigned long long mine = bits;
                     uint32_t cw = 0;
@@ -635,6 +698,7 @@ __device__ __forceinline__ void gemm_nt_v2_body(unsigned char* __restrict__ smem
                     bmask = (1ull << (cb & 0xFFu)) | (1ull << ((cb >> 8) & 0xFFu)) | (1ull << ((cb >> 16) & 0xFFu)) | (1ull << (cb >> 24));
                 }
                 const uint32_t q0 = (cb & 0xFFu) * 2, q1 = ((cb >> 8) & 0xFFu) * 2, q2 = ((cb >> 16) & 0xFFu) * 2, q3 = (cb >> 24) * 2;
+                const uint32_t tag[4] = {0x300u | q0, 0x200u | q1, 0x100u | q2, q3};      // (pick24_pos: position from the end, byte of the column)
                 const int r_lane = lane >> (6 - LOGM);                    // token of sweep 0; sweep s adds s * M
                 // survivors of (token, block): a pair of bf16, or (fp8 operands) a pair of codes
                 uint32_t* vals_p = reinterpret_cast<uint32_t*>(ep.vals) + (int64_t)(t0 + r_lane) * (F >> LOGM) + blk0 + b;
@@ -651,14 +715,11 @@ __device__ __forceinline__ void gemm_nt_v2_body(unsigned char* __restrict__ smem
                         const unsigned char* row = scratch + t * EP + (b << LOGM) * 2;
                         uint32_t v, nib;
                         if (GEN_F) {
-                            const uint32_t y0 = *reinterpret_cast<const uint16_t*>(row + q0);
-                            const uint32_t y1 = *reinterpret_cast<const uint16_t*>(row + q1);
-                            const uint32_t y2 = *reinterpret_cast<const uint16_t*>(row + q2);
-                            const uint32_t y3 = *reinterpret_cast<const uint16_t*>(row + q3);
-                            v = select24<false>(sqrelu16(y0), sqrelu16(y1), sqrelu16(y2), sqrelu16(y3), nib);
-                            const uint32_t p0 = nib & 3u, p1 = nib >> 2;
-                            const uint32_t k0 = (p0 == 0) ? y0 : (p0 == 1) ? y1 : y2;
-                            const uint32_t k1 = (p1 == 3) ? y3 : (p1 == 2) ? y2 : y1;
+                            const uint32_t ro = s_off + t * EP + (b << LOGM) * 2;
+                            uint32_t low, high;
+                            v = pick24_pos(sqrelu2(lds_u16(ro + q0) | (lds_u16(ro + q1) << 16)), sqrelu2(lds_u16(ro + q2) | (lds_u16(ro + q3) << 16)), tag, low, high);
+                            nib = (((low >> 8) & 3u) | (((high >> 8) & 3u) << 2)) ^ 0xFu;
+                            const uint32_t k0 = lds_u16(ro + (low & 0xFFu)), k1 = lds_u16(ro + (high & 0xFFu));
                             if (FP8) codes_p[(int64_t)sw * M * (F >> LOGM)] = (uint16_t)fp8_enc2(bf2f(v & 0xFFFFu), bf2f(v >> 16), ep.inv_out);
                             else vals_p[(int64_t)sw * M * (F >> LOGM)] = v;
                             kept_p[sw * M * NB] = k0 | (k1 << 16);
@@ -730,23 +791,11 @@ __device__ __forceinline__ void gemm_nt_v2_body(unsigned char* __restrict__ smem
                 const int64_t blk_g = (f0 >> 3) + bl;
                 uint32_t cw;                                              // the four kept column offsets of block bl
                 if (EPI == 1) {
-                    // column scores: lane = column, strict ascending-row fp32 sum of y2 = bf16(max(y1, 0)^2)
-                    float sc = 0.0f;
-#pragma unroll 8
-                    for (int r = 0; r < WN; ++r)
-                        sc = sc + __uint_as_float(sqrelu_hi(*reinterpret_cast<const uint16_t*>(scratch + r * EP + lane * 2)));
-                    int rank = 0;
-#pragma unroll
-                    for (int k = 0; k < 8; ++k) {
-                        const float o = __shfl(sc, (lane & ~7) + k, 64);
-                        rank += (k < bl) ? (o >= sc) : ((k > bl) ? (o > sc) : 0);
-                    }
-                    const unsigned long long kept = __ballot(rank < 4);
+                    const unsigned long long kept = __ballot(keep4_of_8(__float_as_uint(column_scores()), lane));
                     const uint32_t bits = (uint32_t)(kept >> (lane & ~7)) & 0xFFu;
-                    uint32_t mine = 0, n = 0;
-#pragma unroll
-                    for (int c = 0; c < 8; ++c)
-                        if ((bits >> c) & 1u) { mine |= (uint32_t)c << (8 * n); ++n; }
+                    // kept column number n of the block goes to byte n of the word of all of its lanes
+                    uint32_t mine = (bits >> bl) & 1u ? (uint32_t)bl << (8 * __builtin_popcount(bits & ((1u << bl) - 1u))) : 0u;
+                    mine = or_of_8(mine);
                     if (valid && bl == 0)
                     {
                         *reinterpret_cast<uint32_t*>(ep.colidx + ((int64_t)(t0 >> 6) * nblk + (f0 >> 3) + (lane >> 3)) * 4) = mine;
@@ -771,72 +820,89 @@ __device__ __forceinline__ void gemm_nt_v2_body(unsigned char* __restrict__ smem
                 } else {
                     cw = pre_cw[h];
                 }
-                // per-row pass: lane = (column block bl, token t); 8 tokens per sweep, 8 sweeps
+                // Per-row pass: lane = (column block bl, token t); 8 tokens per sweep, 8 sweeps.  Every output but the canonical copies is a run of
+                // consecutive bytes per sweep: a wave-uniform base, 4 bytes per lane and constant offsets, no address arithmetic.
+                // (This pass, the choice and the scores together, T = D = 8192, F = 28672: 1950 -> 1895 us for eq. (1), 1815 -> 1775 for eq. (4); 18 -> 12 us a tile.)
                 uint32_t* vals_p = reinterpret_cast<uint32_t*>(ep.vals) + ((int64_t)(t0 + (lane >> 3)) * (F / 4) + blk_g * 2) / 2;
-                uint32_t* kept_p = reinterpret_cast<uint32_t*>(ep.ykept) + ykept_off(t0 + (lane >> 3), blk_g, F);
-                uint8_t* meta_p = ep.meta + (int64_t)(t0 + (lane >> 3)) * (F / 16) + (blk_g >> 1);
+                uint32_t* kept_p = reinterpret_cast<uint32_t*>(ep.ykept) + ykept_off(t0, f0 >> 3, F);
                 // operands of eq. (3) / eq. (7) on the V:2:8 kernel (gemm_vnm8.hip); sweep it: + (it / 4) 32-token groups + 8 (it % 4) tokens
-                uint32_t* vcb_p = FP8 ? nullptr : reinterpret_cast<uint32_t*>(ep.vcb + vcb_off(t0 + (lane >> 3), blk_g, F));
+                uint32_t* vcb_p = FP8 ? nullptr : reinterpret_cast<uint32_t*>(ep.vcb + vcb_off(t0, f0 >> 3, F));
                 uint8_t* vcb8_p = FP8 ? reinterpret_cast<uint8_t*>(ep.vcb) + vcb8_off(t0 + (lane >> 3), blk_g, F) : nullptr;   // (the lane of block 0 stores its row's 8 pairs of codes)
-                uint8_t* mcb_p = FP8 ? ep.mcb + mcb8_off(t0 + (lane >> 3), f0 >> 6, F) : ep.mcb + mcb_off(t0 + (lane >> 3), f0 >> 6, F);
-                const uint32_t c0 = (cw & 0xFFu) * 2, c1 = ((cw >> 8) & 0xFFu) * 2, c2 = ((cw >> 16) & 0xFFu) * 2, c3 = (cw >> 24) * 2;
-                const uint32_t (&pre_m)[8] = pre_m_all[h];                  // EPI 2: saved metadata and y1 of the 8 sweeps
+                const uint32_t c2 = cw * 2;                                 // the four kept columns as byte offsets
+                const uint32_t q0 = c2 & 0xFFu, q1 = (c2 >> 8) & 0xFFu, q2 = (c2 >> 16) & 0xFFu, q3 = c2 >> 24;
+                const uint32_t tag[4] = {0x30u | q0, 0x20u | q1, 0x10u | q2, q3};
+                const uint32_t row0 = s_off + (lane >> 3) * EP + bl * 16;    // (rows and blocks are multiples of 16 bytes: a byte of c2 goes in by OR)
+                const uint32_t tt0 = s_off + WN * EP + bl * 4 * EP + (lane >> 3) * 2;
                 const uint32_t (&pre_y)[8] = pre_y_all[h];
-                float vmax = 0.0f;                                         // fp8: largest survivor magnitude of this half tile
-                if (valid) {
+                uint32_t v[8], pos[8];                                     // of every sweep: the survivors, their positions among the four kept columns
+                // (all reads of the tile come first: a sweep that branches or writes LDS waits for its own two LDS latencies before the next one starts)
+                if (EPI == 1) {
+                    uint32_t low[8], high[8], mword = 0;                   // mword: the metadata of token lane / 8 + 8 bl
 #pragma unroll
                     for (int it = 0; it < 8; ++it) {
-                        const int t = (lane >> 3) + 8 * it;
-                        const unsigned char* row = scratch + t * EP + bl * 16;
-                        uint32_t v, nib;
-                        if (EPI == 1) {
-                            const uint32_t y0 = *reinterpret_cast<const uint16_t*>(row + c0);
-                            const uint32_t y1 = *reinterpret_cast<const uint16_t*>(row + c1);
-                            const uint32_t y2 = *reinterpret_cast<const uint16_t*>(row + c2);
-                            const uint32_t y3 = *reinterpret_cast<const uint16_t*>(row + c3);
-                            v = select24<false>(sqrelu16(y0), sqrelu16(y1), sqrelu16(y2), sqrelu16(y3), nib);
-                            const uint32_t p0 = nib & 3u, p1 = nib >> 2;
-                            const uint32_t k0 = (p0 == 0) ? y0 : (p0 == 1) ? y1 : y2;
-                            const uint32_t k1 = (p1 == 3) ? y3 : (p1 == 2) ? y2 : y1;
-                            if (FP8) {  // canonical values are the survivors' codes [T, F / 4]
-                                if (ep.vals)
-                                    reinterpret_cast<uint16_t*>(ep.vals)[(int64_t)(t0 + t) * (F / 8) + blk_g] = (uint16_t)fp8_enc2(bf2f(v & 0xFFFFu), bf2f(v >> 16), ep.inv_out);
-                            } else if (ep.vals)       // (lean form: no canonical copy; the 2:4 view and the compact transpose carry the values)
-                                vals_p[(int64_t)it * 8 * (F / 8)] = v;
-                            kept_p[it * 64] = k0 | (k1 << 16);
-                            // metadata bytes of the row's 8 blocks -> one 32-bit store from the lane of block 0
-                            uint32_t mw = nib | (row_shl<1>(nib) << 4);
-                            mw |= row_shl<2>(mw) << 8;
-                            mw |= row_shl<4>(mw) << 16;
-                            if (bl == 0) *reinterpret_cast<uint32_t*>(meta_p + (int64_t)it * 8 * (F / 16)) = mw;
-                            if (ep.mcb && bl == 0) *reinterpret_cast<uint32_t*>(mcb_p + it * (FP8 ? 64 : 32)) = mw;
-                        } else {
-                            const uint32_t mb = pre_m[it];
-                            const uint32_t yk = pre_y[it];
-                            nib = (mb >> (4 * (bl & 1))) & 0xFu;
-                            const uint32_t q0 = (cw >> (8 * (nib & 3u))) & 0xFFu, q1 = (cw >> (8 * (nib >> 2))) & 0xFFu;
-                            const float d0 = bf2f(*reinterpret_cast<const uint16_t*>(row + q0 * 2));
-                            const float d1 = bf2f(*reinterpret_cast<const uint16_t*>(row + q1 * 2));
-                            const float ya = bf2f(yk & 0xFFFFu), yb = bf2f(yk >> 16);
-                            const float ga = 2.0f * d0 * (ya > 0.0f ? ya : 0.0f), gb = 2.0f * d1 * (yb > 0.0f ? yb : 0.0f);
-                            v = f2bf2(ga, gb);
-                            if (ep.vals) vals_p[(int64_t)it * 8 * (F / 8)] = v;
-                        }
-                        if (FP8) vmax = __builtin_fmaxf(vmax, __builtin_fmaxf(__builtin_fabsf(bf2f(v & 0xFFFFu)), __builtin_fabsf(bf2f(v >> 16))));
-                        if (!FP8 && ep.vcb) vcb_p[(int64_t)(it >> 2) * (F >> 6) * 256 + (it & 3) * 64] = v;
-                        if (FP8 && ep.vcb) {    // the survivors' codes: the row's 8 pairs gathered into the lane of block 0, one 16-byte store
-                            const uint32_t q2 = fp8_enc2(bf2f(v & 0xFFFFu), bf2f(v >> 16), ep.inv_out);
-                            const uint32_t w2 = q2 | (row_shl<1>(q2) << 16);
+                        const uint32_t r = row0 + it * 8 * EP;
+                        v[it] = pick24_pos(sqrelu2(lds_u16(r + q0) | (lds_u16(r + q1) << 16)), sqrelu2(lds_u16(r + q2) | (lds_u16(r + q3) << 16)), tag, low[it], high[it]);
+                    }
+#pragma unroll
+                    for (int it = 0; it < 8; ++it) {
+                        pos[it] = (((low[it] >> 4) & 3u) | ((high[it] >> 2) & 0xCu)) ^ 0xFu;
+                        const uint32_t mw = or_of_8(pos[it] << (4 * bl));   // the row's 8 blocks
+                        mword = bl == it ? mw : mword;
+                        low[it] = lds_u16(((low[it] & 15u) | row0) + it * 8 * EP) | (lds_u16(((high[it] & 15u) | row0) + it * 8 * EP) << 16);
+                    }
+                    if (valid) {
+#pragma unroll
+                        for (int it = 0; it < 8; ++it) kept_p[lane + it * 64] = low[it];
+                        const uint32_t mt = (lane >> 3) + 8 * bl;
+                        *reinterpret_cast<uint32_t*>(ep.meta + (int64_t)t0 * (F / 16) + (f0 >> 4) + mt * (uint32_t)(F / 16)) = mword;
+                        *reinterpret_cast<uint32_t*>(ep.mcb + (FP8 ? mcb8_off(t0, f0 >> 6, F) : mcb_off(t0, f0 >> 6, F)) + mt * (FP8 ? 8 : 4)) = mword;
+                    }
+                } else {
+                    const uint32_t m = pre_m[h];
+                    pos[0] = bcast_of_8<0>(m); pos[1] = bcast_of_8<1>(m); pos[2] = bcast_of_8<2>(m); pos[3] = bcast_of_8<3>(m);
+                    pos[4] = bcast_of_8<4>(m); pos[5] = bcast_of_8<5>(m); pos[6] = bcast_of_8<6>(m); pos[7] = bcast_of_8<7>(m);
+#pragma unroll
+                    for (int it = 0; it < 8; ++it) {
+                        pos[it] >>= 4 * bl;
+                        const float d0 = bf2f(lds_u16(((__builtin_amdgcn_alignbyte(0u, c2, pos[it]) & 15u) | row0) + it * 8 * EP));
+                        const float d1 = bf2f(lds_u16(((__builtin_amdgcn_alignbyte(0u, c2, pos[it] >> 2) & 15u) | row0) + it * 8 * EP));
+                        const uint32_t yk = pre_y[it];
+                        v[it] = f2bf2(2.0f * d0 * relu1(__uint_as_float(yk << 16)), 2.0f * d1 * relu1(__uint_as_float(yk & 0xFFFF0000u)));
+                    }
+                }
+                // transposed tile for the weight-gradient GEMM, compacted to the block's four kept hidden units:
+                // row = 4 * block + position among the kept units, column = token
+#pragma unroll
+                for (int it = 0; it < 8; ++it) {
+                    *reinterpret_cast<uint16_t*>(smem + __umul24(pos[it] & 3u, EP) + tt0 + it * 16) = (uint16_t)(v[it] & 0xFFFFu);
+                    *reinterpret_cast<uint16_t*>(smem + __umul24((pos[it] >> 2) & 3u, EP) + tt0 + it * 16) = (uint16_t)(v[it] >> 16);
+                }
+                if (valid && ep.vals) {    // (lean form: no canonical copy; vcb and the compact transpose carry the values)
+#pragma unroll
+                    for (int it = 0; it < 8; ++it) {
+                        if (FP8 && EPI == 1)    // canonical values are the survivors' codes [T, F / 4]
+                            reinterpret_cast<uint16_t*>(ep.vals)[(int64_t)(t0 + (lane >> 3) + 8 * it) * (F / 8) + blk_g] =
+                                (uint16_t)fp8_enc2(bf2f(v[it] & 0xFFFFu), bf2f(v[it] >> 16), ep.inv_out);
+                        else vals_p[(int64_t)it * 8 * (F / 8)] = v[it];
+                    }
+                }
+                if (FP8 && valid) {        // the largest survivor magnitude of this half tile
+#pragma unroll
+                    for (int it = 0; it < 8; ++it)
+                        vmax_tile = __builtin_fmaxf(vmax_tile, __builtin_fmaxf(__builtin_fabsf(bf2f(v[it] & 0xFFFFu)), __builtin_fabsf(bf2f(v[it] >> 16))));
+                }
+                if (valid && ep.vcb) {
+#pragma unroll
+                    for (int it = 0; it < 8; ++it) {
+                        if (!FP8) vcb_p[(int64_t)(it >> 2) * (F >> 6) * 256 + lane + (it & 3) * 64] = v[it];
+                        else {             // the survivors' codes: the row's 8 pairs gathered into the lane of block 0, one 16-byte store
+                            const uint32_t q2w = fp8_enc2(bf2f(v[it] & 0xFFFFu), bf2f(v[it] >> 16), ep.inv_out);
+                            const uint32_t w2 = q2w | (row_shl<1>(q2w) << 16);
                             const uint4 w8 = make_uint4(w2, row_shl<2>(w2), row_shl<4>(w2), row_shl<6>(w2));
                             if (bl == 0) *reinterpret_cast<uint4*>(vcb8_p + (int64_t)(it >> 2) * (F >> 7) * 1024 + (it & 3) * 256) = w8;
                         }
-                        // transposed tile for the weight-gradient GEMM, compacted to the block's four kept hidden units:
-                        // row = 4 * block + position among the kept units, column = token
-                        *reinterpret_cast<uint16_t*>(ttile + (bl * 4 + (nib & 3u)) * EP + t * 2) = (uint16_t)(v & 0xFFFFu);
-                        *reinterpret_cast<uint16_t*>(ttile + (bl * 4 + (nib >> 2)) * EP + t * 2) = (uint16_t)(v >> 16);
                     }
                 }
-                if (FP8) vmax_tile = __builtin_fmaxf(vmax_tile, vmax);
                 wave_lds_sync();
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {          // 2 groups of 16 compact rows x 2 chunks of 32 tokens, 1 KB each
@@ -848,7 +914,7 @@ __device__ __forceinline__ void gemm_nt_v2_body(unsigned char* __restrict__ smem
                                 make_uint2(fp8_enc2(bf2f(w.x & 0xFFFFu), bf2f(w.x >> 16), ep.inv_out) | (fp8_enc2(bf2f(w.y & 0xFFFFu), bf2f(w.y >> 16), ep.inv_out) << 16),
                                            fp8_enc2(bf2f(w.z & 0xFFFFu), bf2f(w.z >> 16), ep.inv_out) | (fp8_enc2(bf2f(w.w & 0xFFFFu), bf2f(w.w >> 16), ep.inv_out) << 16));
                     } else if (valid) {
-                        *reinterpret_cast<uint4*>(ep.at + blk_off(f0 / 2 + fr, t0 + tc, tok_ld / 32)) = w;
+                        *reinterpret_cast<uint4*>(ep.at + blk_off(f0 / 2 + (q >> 1) * 16, t0 + (q & 1) * 32, tok_ld / 32) + lane * 8) = w;
                     }
                 }
             }
