@@ -11,9 +11,10 @@ namespace {
 
 // The workspace itself.  In host code this name is only a stand-in for the device symbol: its device address is obtained
 // once per device with hipGetSymbolAddress (below) and only that address is ever handed to kernels.
-// (48 MiB on top of the documented limit: the operand buffer of shared launches, T F bytes, and the sums of split contractions, at most 32 MiB, do not
-// count towards it)
-constexpr size_t kScratchBytes = (size_t)SFFN_NOALLOC_WORKSPACE_MAX + (49u << 20);
+// (8 MiB on top of the documented limit: the operand buffer of shared launches, T F bytes, and the sums of contractions that several workgroups share do
+// not count towards it; a step has one of the two or neither.  Of the shapes within the limit T = 4352, D = 256, F = 1920 without the canonical copies
+// needs most, 39.95 MiB in all.)
+constexpr size_t kScratchBytes = (size_t)SFFN_NOALLOC_WORKSPACE_MAX + (8u << 20);
 static __device__ __align__(256) unsigned char scratch[kScratchBytes];
 
 constexpr int kMaxDevices = 64;
@@ -23,6 +24,7 @@ std::mutex g_mu;
 }  // namespace
 
 extern "C" size_t sffn_step_shared_launch_bytes(const sffn_cfg* cfg);   // api.hip
+extern "C" size_t sffn_noalloc_buffer_bytes(void) { return kScratchBytes; }     // internal (not declared in the public header)
 extern "C" int sffn_noalloc_set_error(int code, const char* text);   // api.hip: records the text behind sffn_last_error()
 
 extern "C" int ffn_sparse_step_noalloc(const sffn_cfg* cfg, const uint16_t* X, const uint16_t* W1, const uint16_t* W2, const float* b1,
@@ -31,10 +33,11 @@ extern "C" int ffn_sparse_step_noalloc(const sffn_cfg* cfg, const uint16_t* X, c
     const size_t need = sffn_workspace_bytes(cfg);
     if (need == 0)
         return sffn_noalloc_set_error(SFFN_EINVAL, "ffn_sparse_step_noalloc: T, D, F must be positive multiples of 64, V = 64, M in {8, 16, 32, 64}, F a multiple of 2 M");
-    if (need - sffn_step_shared_launch_bytes(cfg) > (size_t)SFFN_NOALLOC_WORKSPACE_MAX || need > kScratchBytes) {
+    const size_t counted = need - sffn_step_shared_launch_bytes(cfg);
+    if (counted > (size_t)SFFN_NOALLOC_WORKSPACE_MAX || need > kScratchBytes) {
         char msg[200];
         snprintf(msg, sizeof(msg), "ffn_sparse_step_noalloc: this shape needs %zu bytes of workspace, the built-in buffer holds %zu; use ffn_sparse_step",
-                 need, (size_t)SFFN_NOALLOC_WORKSPACE_MAX);
+                 counted, (size_t)SFFN_NOALLOC_WORKSPACE_MAX);
         return sffn_noalloc_set_error(SFFN_EWORKSPACE, msg);
     }
     int dev = -1;

@@ -2,6 +2,8 @@
 the same inputs: same kernels, so every output must be the same bits.  Two calls in a row, the second on a smaller
 shape (the built-in buffer then still holds the first call's contents)."""
 import ctypes
+import os
+import re
 
 import numpy as np
 import pytest
@@ -67,3 +69,37 @@ def test_noalloc_step_refuses_shapes_beyond_its_buffer():
     assert lib.ffn_sparse_step_noalloc(ctypes.byref(bad), *([fake] * 9), None) == -1
     m12 = binding._Cfg(512, 256, 1024, 64, 12, 0, 0)
     assert lib.ffn_sparse_step_noalloc(ctypes.byref(m12), *([fake] * 9), None) == -1
+
+
+def test_noalloc_buffer_is_what_the_largest_accepted_shapes_need():
+    """Host-side: the built-in buffer holds every shape whose workspace, less what shared launches and shared contractions take, is within the documented limit;
+    it is no more than 256 KiB larger than the largest of them needs, and the header states its size."""
+    lib = sffn.load()
+    lib.sffn_step_shared_launch_bytes.restype = lib.sffn_noalloc_buffer_bytes.restype = lib.sffn_workspace_bytes.restype = ctypes.c_size_t
+    held, limit = lib.sffn_noalloc_buffer_bytes(), sffn.NOALLOC_WORKSPACE_MAX
+    header = open(os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "include", "sparseffn.h")).read()
+    assert held == int(re.search(r"device array built into the library \((\d+) MiB", header).group(1)) << 20
+
+    def need(T, D, F, M, flags):
+        cfg = binding._Cfg(T, D, F, 64, M, 0, flags)
+        total = lib.sffn_workspace_bytes(ctypes.byref(cfg))
+        return total, total - lib.sffn_step_shared_launch_bytes(ctypes.byref(cfg))
+
+    largest = 0
+    for M, flags in ((8, 0), (8, binding.FLAG_LEAN), (16, 0), (16, binding.FLAG_KEEP_DENSE), (16, binding.FLAG_UNFUSED), (64, binding.FLAG_LEAN)):
+        unit = 64 if M == 8 else 16 * M                # (M >= 16: other sizes take the unfused path, whose dense tensors are larger)
+        for T in range(64, 1 << 16, 64):
+            for D in range(64, 1 << 16, 64):
+                lo, hi = 0, (1 << 16) // unit          # the most hidden units within the limit (what counts grows with F)
+                while lo < hi:
+                    mid = (lo + hi + 1) // 2
+                    lo, hi = (mid, hi) if need(T, D, mid * unit, M, flags)[1] <= limit else (lo, mid - 1)
+                if lo == 0:
+                    break
+                for n in range(max(1, lo - 2), lo + 1):    # (whether launches are shared may change from one size to the next)
+                    total, counted = need(T, D, n * unit, M, flags)
+                    if counted <= limit:
+                        largest = max(largest, total)
+            if lo == 0 and D == 64:
+                break
+    assert held - (256 << 10) <= largest <= held
