@@ -997,9 +997,12 @@ template <> struct TileSel<true, 38> { using T128 = Tile<2, 2, 128, 2, 1>; using
 template <bool SPARSE, bool OUT_I_CONTIG, int EPI, bool BLOCKED, bool FP8>
 hipError_t launch_gemm_v2(const GemmV2Args& a, hipStream_t s, int tile = 0) {
     using Sel = TileSel<SPARSE, EPI>;
-    // a round of 128 tiles: the V:N:M epilogues (half of a tile's time at K = 2048) overlap with the other workgroup's main loop; without one it is the
-    // bytes from L2 that count (the router's eq. (3), 918 / 3564 tiles of K = 5504: 338 us on 256 tiles, 447 on 128; 288 / 1120 of K = 2048: 76 and 68)
-    if (!tile) tile = pick_gemm_tile(a.Ra, a.Rb, a.K / (SPARSE ? 64 : 32), a.grp, EPI != 0 ? 0.56f : 0.72f, SPARSE, EPI != 0 ? 1.0f : 0.6f);
+    if (!tile) {
+        const int steps = a.K / (SPARSE ? 64 : 32);
+        constexpr int what = EPI == 0 ? kGemmPlain : EPI == 2 || EPI == 4 || EPI >= 32 ? kGemmBackward : kGemmForward;
+        constexpr bool tall = Sel::T128::BM == 256;
+        tile = pick_gemm_tile(a.Ra, a.Rb, steps, a.grp, small_round(what, steps, tall), SPARSE, last_round(what, steps, tall), tall);
+    }
     if (tile == 256) return launch_units<GemmV2Unit<SPARSE, OUT_I_CONTIG, EPI, BLOCKED, FP8, Tile256<SPARSE>>>(s, a);
     if (tile == 128) return launch_units<GemmV2Unit<SPARSE, OUT_I_CONTIG, EPI, BLOCKED, FP8, typename Sel::T128>>(s, a);
     // (the dense form has no 64 tile: its two users are the stand-alone vnm_wgrad and the router's weight gradients)

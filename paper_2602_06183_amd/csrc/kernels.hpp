@@ -153,14 +153,38 @@ inline int64_t token_tiles(int64_t T, int groups, int64_t edge) {
     const int64_t n = groups ? groups : 1;
     return n * (((T + n - 1) / n + edge - 1) / edge);
 }
-// gemm_v2 (i x j outputs).
-// Eq. (1) / (4) at T = D = 2048, F = 8192 (256 / 1024 tiles): 55 / 47 us on 256 tiles, 61 / 54 on 128; T = 1024, D = 1408, F = 4928 (80 / 312): 39 / 30 and
-// 26 / 23; T = 64, D = 2048, F = 8192 (32 / 64 / 128): 43 / 33, 21 / 18, and 17 / 14 on 64 tiles
-inline int pick_gemm_tile(int64_t Ra, int64_t Rb, int steps, const GemmGroup& g, float w128, bool split, float last = 1.0f) {
-    auto tiles = [&](int64_t edge) {
-        return (unsigned)(token_tiles(Ra, g.n && g.role == 0 ? g.n : 0, edge) * token_tiles(Rb, g.n && g.role == 1 ? g.n : 0, edge) * (g.role == 2 && g.n ? g.n : 1));
+// What a round of 128 tiles takes of a round of 256 tiles in gemm_v2, by the trips of the main loop: the V:N:M epilogues of eqs. (1) and
+// (4), whose part of a tile overlaps with the other workgroup's main loop.  The longer the contraction the more the bytes from L2 count, of which the small
+// tile needs twice as many per product.  Measured over 170 shapes (T 64 - 15000, D 256 - 6000, 1 - 8 experts; bf16, and fp8 by its own trips of 128):
+//   eq. (1)  12 trips 0.57, 17 0.59, 29 0.68, 36 0.69, 60 0.70, 84 0.74      (T = 5504, D = 768, F = 3072: 43 us on 256 tiles, 37 on 128; 8 x 512 tokens,
+//   eq. (4)  12 trips 0.63, 17 0.63, 29 0.72, 36 0.76, 60 0.71, 84 0.74       D = 3840, F = 12672: eq. (1) 292 and 370, eq. (4) 285 and 371)
+// Blocks of M = 64 columns want 128 hidden units in one wavefront, so that their small tile is 256 hidden units x 128 tokens (`tall`): a round of them, two
+// per CU, is no less work than one of 256 tiles (1.03 - 1.16 of it), and alone on its CU such a tile takes 0.85 - 1.1 of a 256 tile (5 trips 0.88, 13 0.93, 30
+// 0.97, 55 1.06, 88 1.08; eq. (4) 0.91, 0.96, 1.03, 1.27, 1.02).
+enum { kGemmPlain = 0, kGemmForward = 1, kGemmBackward = 2 };
+inline float small_round(int what, int steps, bool tall = false) {
+    const float n = (float)steps;
+    if (tall) return 1.06f;
+    if (what == kGemmPlain) return 0.72f;
+    return (n < 35.0f ? 0.56f + 0.004f * n : 0.70f) + (what == kGemmBackward ? 0.04f : 0.0f);
+}
+// plain stores: it is the bytes from L2 that count (the router's eq. (3), 918 / 3564 tiles of K = 5504: 338 us on 256 tiles, 447 on 128; 288 / 1120 of K = 2048:
+// 76 and 68)
+inline float last_round(int what, int steps, bool tall = false) {
+    if (tall) return (0.87f + 0.004f * (float)steps + (what == kGemmBackward ? 0.03f : 0.0f)) / 1.06f;
+    return what == kGemmPlain ? 0.6f : 1.0f;
+}
+// gemm_v2 (i x j outputs); w128, last: see pick_tile.  64 tiles: T = 64, D = 2048, F = 8192 (32 / 64 / 128 tiles): eqs. (1), (4) 43 / 33 us on 256 tiles,
+// 21 / 18 on 128, 17 / 14 on 64; with more than 256 of them they lose to 128 (T = 128, D = 1984, F = 8512, 266 of them: 25 and 19 us).
+inline int pick_gemm_tile(int64_t Ra, int64_t Rb, int steps, const GemmGroup& g, float w128, bool split, float last = 1.0f, bool tall = false) {
+    auto tiles = [&](int64_t ei, int64_t ej) {
+        return (unsigned)(token_tiles(Ra, g.n && g.role == 0 ? g.n : 0, ei) * token_tiles(Rb, g.n && g.role == 1 ? g.n : 0, ej) * (g.role == 2 && g.n ? g.n : 1));
     };
-    return pick_tile(tiles(256), tiles(128), tiles(64), steps, w128, split ? 256 : 0, 16, last);
+    return pick_tile(tiles(256, 256), tiles(tall ? 256 : 128, 128), tiles(64, 64), steps, w128, split ? 256 : 0, 16, last);
+}
+// eqs. (1), (4) with their epilogues; M: columns per V:N:M block
+inline int pick_epilogue_tile(int64_t F, int64_t T, int steps, const GemmGroup& g, int what, int M) {
+    return pick_gemm_tile(F, T, steps, g, small_round(what, steps, M == 64), true, last_round(what, steps, M == 64), M == 64);
 }
 // V:2:8 activation GEMM.  T = 8192, N = 2048, F = 8192 (256 / 1024 tiles): 107 us on 256 tiles, 148 on 128; T = 2048 (64 / 256): 85 and 54; T = 1024,
 // N = 1408, F = 4928 (24 / 88 / 352): 55, 33, and 29 on 64 tiles; T = 64, N = 2048, F = 8192 (8 / 16 / 32): 83, 49, 28
@@ -224,14 +248,16 @@ inline int pick_wgrad_tile(int64_t F, int64_t N, int64_t T, int experts, bool sp
 
 inline StepTiles step_tiles(int64_t T, int64_t D, int64_t F, int M, int experts, bool fp8) {
     StepTiles t;
-    const int unit = fp8 ? 128 : 64;
+    const int unit = fp8 ? 128 : 64, steps = (int)(D / unit);
     GemmGroup g;
     g.role = 1; g.n = experts > 1 ? experts : 0;
-    t.g = t.g_bwd = pick_gemm_tile(F, T, (int)(D / unit), g, 0.56f, true);
+    t.g = pick_epilogue_tile(F, T, steps, g, kGemmForward, M);
+    t.g_bwd = pick_epilogue_tile(F, T, steps, g, kGemmBackward, M);
     const SplitPlan v = M == 8 ? plan_vnm8(T, D, (int)(F / unit), g.n) : fp8 ? SplitPlan{256, 1} : plan_gather(T, D, (int)(4 * F / M / 64), g.n);
     t.v = M == 8 ? pick_vnm8_tile(T, D, (int)(F / unit), g.n) : fp8 ? 256 : pick_gather_tile(T, D, (int)(4 * F / M / 64));
     t.w = pick_wgrad_tile(F, D, T, experts > 1 ? experts : 0, M == 8 || fp8);
-    t.mix = t.g != 256 && t.w != 256 && (M != 8 || t.v != 256);
+    // (0.56: in a shared launch the small tiles pay where eqs. (1), (4) by themselves would be even)
+    t.mix = pick_gemm_tile(F, T, steps, g, 0.56f, true) != 256 && t.w != 256 && (M != 8 || t.v != 256);
     if (t.mix) t.g_bwd = 128;
     else { t.v = v.tile; t.v_split = v.n; }
     return t;
@@ -249,8 +275,13 @@ inline void refine_tiles(StepTiles* t, int64_t D, int64_t F, int M, const GemmGr
     // 256 tokens and less per expert: one large tile covers them and reads the expert's weights once (128 tokens each, D = 3776, F = 12672: eq. (1) 168 us
     // on 256 tiles, 200 on 128)
     const bool few = g.seg[g.n] <= 256 * g.n;
-    if (t->g != 64) t->g = few ? 256 : pick_tile(count(F, 256), count(F, 128), ~0u, 0, 0.56f, 0, 0);
-    if (t->g_bwd != 64) t->g_bwd = t->g;
+    auto pick = [&](int what) {
+        const int steps = (int)(D / 64);
+        const bool tall = M == 64;
+        return pick_tile(count(F, 256), count(F, 128) / (tall ? 2 : 1), ~0u, 0, small_round(what, steps, tall), 0, 0, last_round(what, steps, tall));
+    };
+    if (t->g != 64) t->g = few ? 256 : pick(kGemmForward);
+    if (t->g_bwd != 64) t->g_bwd = few ? 256 : pick(kGemmBackward);
     if (M == 8 && t->v != 64) t->v = few ? 256 : pick_tile(count(D, 256), count(D, 128), ~0u, 0, 0.72f, 0, 0);
 }
 

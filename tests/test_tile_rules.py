@@ -1,0 +1,40 @@
+"""The host-side rules that choose a contraction's output tile (kernels.hpp), against measured times of every tile (tests/golden/tile_times.txt): over
+the calls of a group, what the rules choose takes at most 4 % longer than the best tile of each call, and no call a third longer."""
+import os
+import subprocess
+
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+TILES = (256, 128, 64)
+
+
+@pytest.fixture(scope="module")
+def chosen(tmp_path_factory):
+    """[(call, its measured times, what the rules print for it)]"""
+    calls = [line.strip().split(" | ") for line in open(os.path.join(HERE, "golden", "tile_times.txt")) if not line.startswith("#")]
+    exe = str(tmp_path_factory.mktemp("tiles") / "tile_rules")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-w", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include", os.path.join(HERE, "tile_rules.cpp"), "-o", exe], check=True)
+    out = subprocess.run([exe], input="\n".join(c[0] for c in calls), capture_output=True, text=True, check=True).stdout.split("\n")
+    times = [{t.split()[0]: {e: float(v) for e, v in zip(TILES, t.split()[1:]) if v != "-"} for t in c[1:]} for c in calls]
+    return [(c[0].split(), t, [int(v) for v in o.split()]) for c, t, o in zip(calls, times, out)]
+
+
+def check(rows):
+    """rows: (times by tile, tile chosen)"""
+    assert len(rows) >= 2
+    for times, tile in rows:
+        assert times[tile] <= 1.34 * min(times.values()), (times, tile)
+    assert sum(times[tile] for times, tile in rows) <= 1.04 * sum(min(times.values()) for times, _ in rows), rows
+
+
+def steps(chosen, fp8, grouped, tall=False):
+    """Calls of the step, not those whose contractions share launches."""
+    return [(t, o) for c, t, o in chosen if c[0] == "step" and c[1] == str(int(fp8)) and (c[5] != "1") == grouped and (c[2] == "64") == tall and not o[4]]
+
+
+@pytest.mark.parametrize("tall", [False, True])
+def test_tiles_of_the_epilogue_contractions(chosen, tall):
+    rows = steps(chosen, False, False, tall)
+    check([(t["eq1"], o[0]) for t, o in rows])
+    check([(t["eq4"], o[1]) for t, o in rows])

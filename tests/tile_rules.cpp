@@ -1,0 +1,30 @@
+// Prints what the host-side tile rules (kernels.hpp) choose, for tests/test_tile_rules.py.  One line of standard input is one call:
+//   step <fp8> <M> <D> <F> <experts> <offset 0> ... <offset n>   -> tiles of eq. (1), eq. (4), eqs. (3), (7), weight gradients; shared launches
+//   plain <T> <N> <K>                                            -> tile of a 2:4 contraction with a plain store
+#include <stdio.h>
+#include <string.h>
+
+#include "../paper_2602_06183_amd/csrc/kernels.hpp"
+
+using namespace sffn;
+
+int main() {
+    char what[16];
+    while (scanf("%15s", what) == 1) {
+        long a, b, c, d, e;
+        if (!strcmp(what, "plain")) {
+            if (scanf("%ld %ld %ld", &a, &b, &c) != 3) return 1;
+            const int steps = (int)(c / 64);
+            printf("%d\n", pick_gemm_tile(b, a, steps, GemmGroup(), small_round(kGemmPlain, steps), true, last_round(kGemmPlain, steps)));
+            continue;
+        }
+        if (scanf("%ld %ld %ld %ld %ld", &a, &b, &c, &d, &e) != 5 || e > GemmGroup::kMaxExperts) return 1;
+        GemmGroup g;
+        g.n = e > 1 ? (int)e : 0;
+        for (int i = 0; i <= e; ++i) if (scanf("%d", &g.seg[i]) != 1) return 1;
+        StepTiles t = step_tiles(g.seg[e], c, d, (int)b, (int)e, a != 0);
+        if (!a) refine_tiles(&t, c, d, (int)b, g);
+        printf("%d %d %d %d %d\n", t.g, t.g_bwd, t.v, t.w, (int)t.mix);
+    }
+    return 0;
+}
