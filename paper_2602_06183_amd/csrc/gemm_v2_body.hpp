@@ -997,8 +997,9 @@ template <> struct TileSel<true, 38> { using T128 = Tile<2, 2, 128, 2, 1>; using
 template <bool SPARSE, bool OUT_I_CONTIG, int EPI, bool BLOCKED, bool FP8>
 hipError_t launch_gemm_v2(const GemmV2Args& a, hipStream_t s, int tile = 0) {
     using Sel = TileSel<SPARSE, EPI>;
+    // (grouped along the contraction, role 2: a tile contracts its own expert's tokens only)
     if (!tile) {
-        const int steps = a.K / (SPARSE ? 64 : 32);
+        const int steps = a.K / (SPARSE ? 64 : 32) / (a.grp.n && a.grp.role == 2 ? a.grp.n : 1);
         constexpr int what = EPI == 0 ? kGemmPlain : EPI == 2 || EPI == 4 || EPI >= 32 ? kGemmBackward : kGemmForward;
         constexpr bool tall = Sel::T128::BM == 256;
         tile = pick_gemm_tile(a.Ra, a.Rb, steps, a.grp, small_round(what, steps, tall), SPARSE, last_round(what, steps, tall), tall);

@@ -153,11 +153,12 @@ inline int64_t token_tiles(int64_t T, int groups, int64_t edge) {
     const int64_t n = groups ? groups : 1;
     return n * (((T + n - 1) / n + edge - 1) / edge);
 }
-// What a round of 128 tiles takes of a round of 256 tiles in gemm_v2, by the trips of the main loop: the V:N:M epilogues of eqs. (1) and
+// What a round of 128 tiles takes of a round of 256 tiles in gemm_v2, by the trips of the main loop: plain stores, or the V:N:M epilogues of eqs. (1) and
 // (4), whose part of a tile overlaps with the other workgroup's main loop.  The longer the contraction the more the bytes from L2 count, of which the small
 // tile needs twice as many per product.  Measured over 170 shapes (T 64 - 15000, D 256 - 6000, 1 - 8 experts; bf16, and fp8 by its own trips of 128):
 //   eq. (1)  12 trips 0.57, 17 0.59, 29 0.68, 36 0.69, 60 0.70, 84 0.74      (T = 5504, D = 768, F = 3072: 43 us on 256 tiles, 37 on 128; 8 x 512 tokens,
 //   eq. (4)  12 trips 0.63, 17 0.63, 29 0.72, 36 0.76, 60 0.71, 84 0.74       D = 3840, F = 12672: eq. (1) 292 and 370, eq. (4) 285 and 371)
+//   plain    26 trips 0.71, 46 0.73, 64 0.76 - 0.80, 86 0.89, 114 0.94       (T = 8000, N = 2560, K = 7296: 239 us and 293)
 // Blocks of M = 64 columns want 128 hidden units in one wavefront, so that their small tile is 256 hidden units x 128 tokens (`tall`): a round of them, two
 // per CU, is no less work than one of 256 tiles (1.03 - 1.16 of it), and alone on its CU such a tile takes 0.85 - 1.1 of a 256 tile (5 trips 0.88, 13 0.93, 30
 // 0.97, 55 1.06, 88 1.08; eq. (4) 0.91, 0.96, 1.03, 1.27, 1.02).
@@ -165,14 +166,14 @@ enum { kGemmPlain = 0, kGemmForward = 1, kGemmBackward = 2 };
 inline float small_round(int what, int steps, bool tall = false) {
     const float n = (float)steps;
     if (tall) return 1.06f;
-    if (what == kGemmPlain) return 0.72f;
+    if (what == kGemmPlain) return n < 110.0f ? 0.68f + 0.002f * n : 0.90f;
     return (n < 35.0f ? 0.56f + 0.004f * n : 0.70f) + (what == kGemmBackward ? 0.04f : 0.0f);
 }
-// plain stores: it is the bytes from L2 that count (the router's eq. (3), 918 / 3564 tiles of K = 5504: 338 us on 256 tiles, 447 on 128; 288 / 1120 of K = 2048:
-// 76 and 68)
+// plain stores: a last round of up to 256 small tiles counts 0.6 up to 48 trips (the router's eq. (3), 288 / 1120 tiles of K = 2048: 76 us on 256 tiles, 68 on
+// 128; T = 8000, N = 2560, K = 7296, 320 / 1260 tiles: 239 and 293)
 inline float last_round(int what, int steps, bool tall = false) {
     if (tall) return (0.87f + 0.004f * (float)steps + (what == kGemmBackward ? 0.03f : 0.0f)) / 1.06f;
-    return what == kGemmPlain ? 0.6f : 1.0f;
+    return what == kGemmPlain && steps <= 48 ? 0.6f : 1.0f;
 }
 // gemm_v2 (i x j outputs); w128, last: see pick_tile.  64 tiles: T = 64, D = 2048, F = 8192 (32 / 64 / 128 tiles): eqs. (1), (4) 43 / 33 us on 256 tiles,
 // 21 / 18 on 128, 17 / 14 on 64; with more than 256 of them they lose to 128 (T = 128, D = 1984, F = 8512, 266 of them: 25 and 19 us).

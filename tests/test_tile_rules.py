@@ -1,5 +1,5 @@
 """The host-side rules that choose a contraction's output tile (kernels.hpp), against measured times of every tile (tests/golden/tile_times.txt): over
-the calls of a group, what the rules choose takes at most 4 % longer than the best tile of each call, and no call a third longer."""
+the calls of a group, what the rules choose takes at most 4 % longer than the best tile of each call, and no call more than `most` times as long."""
 import os
 import subprocess
 
@@ -20,11 +20,11 @@ def chosen(tmp_path_factory):
     return [(c[0].split(), t, [int(v) for v in o.split()]) for c, t, o in zip(calls, times, out)]
 
 
-def check(rows):
+def check(rows, most=1.34):
     """rows: (times by tile, tile chosen)"""
     assert len(rows) >= 2
     for times, tile in rows:
-        assert times[tile] <= 1.34 * min(times.values()), (times, tile)
+        assert times[tile] <= most * min(times.values()), (times, tile)
     assert sum(times[tile] for times, tile in rows) <= 1.04 * sum(min(times.values()) for times, _ in rows), rows
 
 
@@ -38,3 +38,8 @@ def test_tiles_of_the_epilogue_contractions(chosen, tall):
     rows = steps(chosen, False, False, tall)
     check([(t["eq1"], o[0]) for t, o in rows])
     check([(t["eq4"], o[1]) for t, o in rows])
+
+
+def test_tiles_of_the_plain_contractions(chosen):
+    rows = [(t["bf16"], o[0]) for c, t, o in chosen if c[0] == "plain"]
+    check([(t, tile) for t, tile in rows if tile in t], 1.2)
