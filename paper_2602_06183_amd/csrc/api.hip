@@ -569,6 +569,7 @@ int run_fp8_step(const sffn_cfg* cfg, const sffn_fp8_scales* sc, int n_experts, 
             REQUIRE(seg[e + 1] >= seg[e] && seg[e + 1] % 64 == 0, SFFN_EINVAL, "ffn_sparse_step_fp8_grouped: seg_offsets must be ascending multiples of 64");
         g.n = (int)E;
         for (int e = 0; e <= E; ++e) g.seg[e] = (int32_t)seg[e];
+        refine_tiles(&tiles, D, F, cfg->M, g, true);
     }
     Regions rg;
     {
@@ -656,7 +657,7 @@ int run_fp8_step(const sffn_cfg* cfg, const sffn_fp8_scales* sc, int n_experts, 
         ep.mode = wide ? 5 : 1; ep.logM = logM; ep.store_dense = keep_dense; ep.vals = (uint16_t*)y2c; ep.meta = y2m; ep.colidx = cix; ep.kmask = kmask;
         ep.ykept = ykept; ep.at = atb; ep.inv_out = 1.0f / sc->y2; ep.at_fp8 = w8; ep.amax = ay2;
         if (!wide) { ep.vcb = (uint16_t*)vcb; ep.mcb = mcb; ep.cixt = cixt; }
-        STAGE(launch_gemm_fp8_blocked(w1b, w1mb, xq, b1, sc->x * sc->w1, F, T, D, y1, F, &ep, s, gp, tiles.mix ? tiles.g : 0), "step/y1+sqrelu_vnm_compress");
+        STAGE(launch_gemm_fp8_blocked(w1b, w1mb, xq, b1, sc->x * sc->w1, F, T, D, y1, F, &ep, s, gp, tiles.g), "step/y1+sqrelu_vnm_compress");
     }
     // eq. (4) on codes, then eq. (6) in bf16 on y2's kept slots; dy1 leaves as codes (eq. (7)) and, at M = 8, in bf16 (canonical)
     VnmEpilogue ep4;
@@ -694,7 +695,7 @@ int run_fp8_step(const sffn_cfg* cfg, const sffn_fp8_scales* sc, int n_experts, 
         if (w8) STAGE(launch_wgrad_vnm_fp8((const uint8_t*)atb, kmask, (const uint8_t*)dytb, sc->y2 * sc->dy, F, D, T, 1, dW2, F, s, gw, acc32), "step/dW2");   // eq. (5) on codes
         else STAGE(launch_wgrad_vnm(atb, kmask, dytb, F, D, T, 1, dW2, F, s, gw, acc32), "step/dW2");               // eq. (5), bf16
     }
-    if (bwd) STAGE(launch_gemm_fp8_blocked(w2b, w2mb, dyq, nullptr, sc->dy * sc->w2, F, T, D, dy2, F, &ep4, s, gp), "step/dy2+dsqrelu_vnm");
+    if (bwd) STAGE(launch_gemm_fp8_blocked(w2b, w2mb, dyq, nullptr, sc->dy * sc->w2, F, T, D, dy2, F, &ep4, s, gp, tiles.g_bwd), "step/dy2+dsqrelu_vnm");
     if (bwd) {
         if (wide) STAGE(launch_vnm_spmm_gather_fp8(dy1c, y2m, cix, w1q, D, sc->dy1 * sc->w1, T, D, F, M, dX, D, s, gr), "step/dX");     // eq. (7)
         else STAGE(launch_vnm8_gemm_fp8(vcb, mcb, cixt, w1q, D, sc->dy1 * sc->w1, T, D, F, dX, D, s, gr, tiles.v, &split), "step/dX");
@@ -1141,7 +1142,7 @@ static int run_step(const sffn_cfg* cfg, int n_experts, const int64_t* seg, cons
                     "ffn_sparse_step_grouped: seg_offsets must be ascending multiples of 64");
         g.n = (int)E;
         for (int e = 0; e <= E; ++e) g.seg[e] = (int32_t)seg[e];
-        refine_tiles(&tiles, D, F, cfg->M, g);
+        refine_tiles(&tiles, D, F, cfg->M, g, false);
     }
 
     hipStream_t s = (hipStream_t)stream;

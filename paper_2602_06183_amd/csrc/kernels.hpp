@@ -265,25 +265,22 @@ inline StepTiles step_tiles(int64_t T, int64_t D, int64_t F, int M, int experts,
 }
 
 // the same once the experts' segments are known: 256 or 128 by the exact number of tiles (the two give the same bits; sharing launches and splitting
-// contractions were decided from the sizes alone)
-inline void refine_tiles(StepTiles* t, int64_t D, int64_t F, int M, const GemmGroup& g) {
+// contractions were decided from the sizes alone).  8 experts x 128 tokens, D = 3840, F = 12672: eqs. (3), (7) 181, 138 us on 128 tiles, 221, 191 on 256.
+inline void refine_tiles(StepTiles* t, int64_t D, int64_t F, int M, const GemmGroup& g, bool fp8) {
     if (t->mix || !g.n) return;
-    auto count = [&](int64_t other, int64_t edge) {
+    auto count = [&](int64_t other, int64_t other_edge, int64_t edge) {
         int64_t n = 0;
         for (int e = 0; e < g.n; ++e) n += (g.seg[e + 1] - g.seg[e] + edge - 1) / edge;
-        return (unsigned)(n * ((other + edge - 1) / edge));
+        return (unsigned)(n * ((other + other_edge - 1) / other_edge));
     };
-    // 256 tokens and less per expert: one large tile covers them and reads the expert's weights once (128 tokens each, D = 3776, F = 12672: eq. (1) 168 us
-    // on 256 tiles, 200 on 128)
-    const bool few = g.seg[g.n] <= 256 * g.n;
     auto pick = [&](int what) {
-        const int steps = (int)(D / 64);
+        const int steps = (int)(D / (fp8 ? 128 : 64));
         const bool tall = M == 64;
-        return pick_tile(count(F, 256), count(F, 128) / (tall ? 2 : 1), ~0u, 0, small_round(what, steps, tall), 0, 0, last_round(what, steps, tall));
+        return pick_tile(count(F, 256, 256), count(F, tall ? 256 : 128, 128), ~0u, 0, small_round(what, steps, tall), 0, 0, last_round(what, steps, tall));
     };
-    if (t->g != 64) t->g = few ? 256 : pick(kGemmForward);
-    if (t->g_bwd != 64) t->g_bwd = few ? 256 : pick(kGemmBackward);
-    if (M == 8 && t->v != 64) t->v = few ? 256 : pick_tile(count(D, 256), count(D, 128), ~0u, 0, 0.72f, 0, 0);
+    if (t->g != 64) t->g = pick(kGemmForward);
+    if (t->g_bwd != 64) t->g_bwd = pick(kGemmBackward);
+    if (M == 8 && t->v != 64) t->v = pick_tile(count(D, 256, 256), count(D, 128, 128), ~0u, 0, 0.72f, 0, 0);
 }
 
 hipError_t launch_prune24(const uint16_t* src, int64_t R, int64_t K, int64_t ld, int trans, int mode, uint16_t* vals,

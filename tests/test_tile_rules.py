@@ -1,5 +1,5 @@
 """The host-side rules that choose a contraction's output tile (kernels.hpp), against measured times of every tile (tests/golden/tile_times.txt): over
-the calls of a group, what the rules choose takes at most 4 % longer than the best tile of each call, and no call more than `most` times as long."""
+the calls of a group, what the rules choose takes at most 4 % longer than the best tile of each call (where not said otherwise), and no call a third longer."""
 import os
 import subprocess
 
@@ -20,12 +20,12 @@ def chosen(tmp_path_factory):
     return [(c[0].split(), t, [int(v) for v in o.split()]) for c, t, o in zip(calls, times, out)]
 
 
-def check(rows, most=1.34):
+def check(rows, most=1.34, total=1.04):
     """rows: (times by tile, tile chosen)"""
     assert len(rows) >= 2
     for times, tile in rows:
         assert times[tile] <= most * min(times.values()), (times, tile)
-    assert sum(times[tile] for times, tile in rows) <= 1.04 * sum(min(times.values()) for times, _ in rows), rows
+    assert sum(times[tile] for times, tile in rows) <= total * sum(min(times.values()) for times, _ in rows), rows
 
 
 def steps(chosen, fp8, grouped, tall=False):
@@ -43,3 +43,12 @@ def test_tiles_of_the_epilogue_contractions(chosen, tall):
 def test_tiles_of_the_plain_contractions(chosen):
     rows = [(t["bf16"], o[0]) for c, t, o in chosen if c[0] == "plain"]
     check([(t, tile) for t, tile in rows if tile in t], 1.2)
+
+
+@pytest.mark.parametrize("fp8", [False, True])
+def test_tiles_of_grouped_steps(chosen, fp8):
+    rows = steps(chosen, fp8, True)
+    check([(t["eq1"], o[0]) for t, o in rows])
+    check([(t["eq4"], o[1]) for t, o in rows])
+    # (one call of the list has experts whose weights do not stay in a cache for a second round of small tiles: 396 us for 320)
+    check([(t["eq3"], o[2]) for t, o in rows if "eq3" in t and o[2] != 64], total=1.08)

@@ -23,7 +23,7 @@ int main() {
         g.n = e > 1 ? (int)e : 0;
         for (int i = 0; i <= e; ++i) if (scanf("%d", &g.seg[i]) != 1) return 1;
         StepTiles t = step_tiles(g.seg[e], c, d, (int)b, (int)e, a != 0);
-        if (!a) refine_tiles(&t, c, d, (int)b, g);
+        refine_tiles(&t, c, d, (int)b, g, a != 0);
         printf("%d %d %d %d %d\n", t.g, t.g_bwd, t.v, t.w, (int)t.mix);
     }
     return 0;
