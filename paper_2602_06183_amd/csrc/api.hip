@@ -173,7 +173,7 @@ int sffn_workspace_layout(const sffn_cfg* cfg, sffn_ws_layout* out) {
 size_t sffn_vnm_spmm_workspace_bytes(int64_t T, int64_t N, int64_t Kfull, int w_kmajor) {
     if (!mult64(T) || !mult64(N) || !mult64(Kfull)) return 0;
     (void)w_kmajor;         // either orientation may need the other one's copy of Wd (plain-2:4 route: [N, Kfull]; gathered route: [Kfull, N])
-    size_t split = split_bytes(plan_vnm8(T, N, (int)(Kfull / 64), 0), T, N);
+    size_t split = split_bytes(plan_vnm8(T, N, (int)(Kfull / 64), 0, false), T, N);
     for (int M = 16; M <= 64; M *= 2) {
         const size_t b = split_bytes(plan_gather(T, N, (int)(4 * Kfull / M / 64), 0), T, N);
         split = split > b ? split : b;
@@ -303,7 +303,7 @@ int vnm_spmm(const uint16_t* a_vals, const uint8_t* a_meta, const uint8_t* a_col
         uint16_t* vcb = v24;
         uint8_t* mcb = m24;
         uint8_t* cixt = m24 + up256((size_t)T * Kfull / 16);
-        const SplitPlan plan = plan_vnm8(T, N, (int)(Kfull / 64), 0);
+        const SplitPlan plan = plan_vnm8(T, N, (int)(Kfull / 64), 0, false);
         const Split split = split_at(sums, plan, T, N);
         LAUNCH(launch_vnm8_repack(a_vals, a_meta, a_colidx, T, Kfull, vcb, mcb, cixt, w_kmajor ? nullptr : Wd, N, Kfull, ldw, wcopy, split.count, s), "vnm_spmm/repack");
         const int64_t ldk = w_kmajor ? ldw : N;

@@ -17,7 +17,7 @@ template <bool FP8>
 static hipError_t launch_impl(Vnm8Args a, hipStream_t s, const GemmGroup* grp, int tile, const Split* split) {
     a.grp = grp ? *grp : GemmGroup();
     if (a.grp.n && (a.grp.role != 0 || a.grp.seg_dev || a.grp.n > GemmGroup::kMaxExperts)) return hipErrorInvalidValue;
-    if (!tile) tile = pick_vnm8_tile(a.T, a.N, a.F / (FP8 ? 128 : 64), a.grp.n);
+    if (!tile) tile = pick_vnm8_tile(a.T, a.N, a.F / (FP8 ? 128 : 64), a.grp.n, FP8);
     if (split) a.split = *split;
     if (a.split.n > 1 && (a.grp.n || tile == 256)) return hipErrorInvalidValue;
     return tile == 256 ? launch_units<Vnm8Unit256<FP8>>(s, a) : tile == 128 ? launch_units<Vnm8Unit128<FP8>>(s, a) : launch_units<Vnm8Unit64<FP8>>(s, a);

@@ -189,9 +189,11 @@ inline int pick_epilogue_tile(int64_t F, int64_t T, int steps, const GemmGroup& 
 }
 // V:2:8 activation GEMM.  T = 8192, N = 2048, F = 8192 (256 / 1024 tiles): 107 us on 256 tiles, 148 on 128; T = 2048 (64 / 256): 85 and 54; T = 1024,
 // N = 1408, F = 4928 (24 / 88 / 352): 55, 33, and 29 on 64 tiles; T = 64, N = 2048, F = 8192 (8 / 16 / 32): 83, 49, 28
-inline int pick_vnm8_tile(int64_t T, int64_t N, int steps, int groups) {
+// More than 256 of the 64 tiles: only for long contractions of bf16 (T = 256, N = 5824, F = 24704, 364 of them: 169 us, 192 on 128 tiles; 24 - 78 trips: even or
+// up to a third slower than 128); fp8 loses to every other tile there (T = 4864, N = 384, F = 1408, 456 of them: 18.5 us, 10.6 on 128, 16.0 on 256).
+inline int pick_vnm8_tile(int64_t T, int64_t N, int steps, int groups, bool fp8) {
     auto tiles = [&](int64_t edge) { return (unsigned)(token_tiles(T, groups, edge) * ((N + edge - 1) / edge)); };
-    return pick_tile(tiles(256), tiles(128), tiles(64), steps, 0.72f, 512, 8);
+    return pick_tile(tiles(256), tiles(128), tiles(64), steps, 0.72f, !fp8 && steps >= 96 ? 512 : 256, 8);
 }
 // gathered-row activation GEMM: 64 tokens x 256 columns, or 64 x 64
 // (T = 256, N = 1024, F = 4096, M = 16: 19 us and 12 us; T = N = 1024: 20 and 12; T = 512, N = 4096, F = 16384: 90 and 67; T = 1984, N = 1344, M = 32: 14 and 23)
@@ -220,8 +222,8 @@ inline SplitPlan plan_split(int64_t T, int64_t N, int steps, int tile, float us6
     }
     return best;
 }
-inline SplitPlan plan_vnm8(int64_t T, int64_t N, int steps, int groups) {
-    const int tile = pick_vnm8_tile(T, N, steps, groups);
+inline SplitPlan plan_vnm8(int64_t T, int64_t N, int steps, int groups, bool fp8) {
+    const int tile = pick_vnm8_tile(T, N, steps, groups, fp8);
     return groups ? SplitPlan{tile, 1} : plan_split(T, N, steps, tile, 0.205f);
 }
 inline SplitPlan plan_gather(int64_t T, int64_t N, int steps, int groups) {
@@ -254,8 +256,8 @@ inline StepTiles step_tiles(int64_t T, int64_t D, int64_t F, int M, int experts,
     g.role = 1; g.n = experts > 1 ? experts : 0;
     t.g = pick_epilogue_tile(F, T, steps, g, kGemmForward, M);
     t.g_bwd = pick_epilogue_tile(F, T, steps, g, kGemmBackward, M);
-    const SplitPlan v = M == 8 ? plan_vnm8(T, D, (int)(F / unit), g.n) : fp8 ? SplitPlan{256, 1} : plan_gather(T, D, (int)(4 * F / M / 64), g.n);
-    t.v = M == 8 ? pick_vnm8_tile(T, D, (int)(F / unit), g.n) : fp8 ? 256 : pick_gather_tile(T, D, (int)(4 * F / M / 64));
+    const SplitPlan v = M == 8 ? plan_vnm8(T, D, (int)(F / unit), g.n, fp8) : fp8 ? SplitPlan{256, 1} : plan_gather(T, D, (int)(4 * F / M / 64), g.n);
+    t.v = M == 8 ? pick_vnm8_tile(T, D, (int)(F / unit), g.n, fp8) : fp8 ? 256 : pick_gather_tile(T, D, (int)(4 * F / M / 64));
     t.w = pick_wgrad_tile(F, D, T, experts > 1 ? experts : 0, M == 8 || fp8);
     // (0.56: in a shared launch the small tiles pay where eqs. (1), (4) by themselves would be even)
     t.mix = pick_gemm_tile(F, T, steps, g, 0.56f, true) != 256 && t.w != 256 && (M != 8 || t.v != 256);

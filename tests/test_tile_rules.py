@@ -52,3 +52,10 @@ def test_tiles_of_grouped_steps(chosen, fp8):
     check([(t["eq4"], o[1]) for t, o in rows])
     # (one call of the list has experts whose weights do not stay in a cache for a second round of small tiles: 396 us for 320)
     check([(t["eq3"], o[2]) for t, o in rows if "eq3" in t and o[2] != 64], total=1.08)
+
+
+@pytest.mark.parametrize("fp8", [False, True])
+def test_tiles_of_the_activation_contractions(chosen, fp8):
+    """Eqs. (3), (7) at M = 8 by themselves and in a shared launch."""
+    rows = [(t["eq3"], o[2]) for c, t, o in chosen if c[0] == "step" and c[1] == str(int(fp8)) and "eq3" in t and 64 in t["eq3"]]
+    check(rows, 1.3, 1.06)
