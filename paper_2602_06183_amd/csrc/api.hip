@@ -116,7 +116,7 @@ bool make_layout(const sffn_cfg* c, FullLayout* L, int n_experts = 1, StepTiles*
     L->a24_vblk = take(TF);             // M = 8: the survivors in the V:2:8 kernel's units; unfused path: the plain-2:4 view
     L->w1t_blk = take(fused ? 0 : D * F * 2);      // unfused path only: W2.T or W1.T, row-major
     StepTiles t = step_tiles(c->T, c->D, c->F, c->M, n_experts, false);
-    t.mix = t.mix && fused;
+    t.mix = t.mix && fused;             // (the rest of the plan stays: the unfused path has to sum in the order of the fused one)
     L->at2 = take(t.mix ? TF : 0);      // dy1v.T compacted, where eq. (4) runs beside eq. (5) (StepTiles)
     L->split = take(split_bytes({t.v, t.v_split}, c->T, c->D));
     if (tiles) *tiles = t;
@@ -512,12 +512,13 @@ bool make_fp8_layout(const sffn_cfg* c, Fp8Layout* L, int n_experts = 1, StepTil
     L->xq = take(T * D);                   L->dyq = take(T * D);
     L->dyt_blk = take(T * D * 2);
     L->v24 = take(TF / 2);
-    // shared launches: with fp8 weight gradients, not into float32 accumulators (their units: step_mix_fp8.hip)
-    StepTiles t = step_tiles(c->T, c->D, c->F, c->M, n_experts, true);
-    t.mix = t.mix && (c->flags & SFFN_FLAG_FP8_WGRAD) && !(c->flags & SFFN_FLAG_DW_FP32_ACCUMULATE);
-    if (tiles) *tiles = t;
-    L->at2 = take(t.mix ? TF / 2 : 0);                              // eq. (4)'s transposed codes, beside eq. (1)'s
-    L->split = take(split_bytes({t.v, t.v_split}, c->T, c->D));
+    // shared launches: with fp8 weight gradients, not into float32 accumulators (their units: step_mix_fp8.hip).  Eq. (4)'s transposed codes beside eq. (1)'s
+    // there, the sums of split contractions elsewhere: one region for either, so that the size does not depend on how the weight gradients are taken
+    const bool may_share = (c->flags & SFFN_FLAG_FP8_WGRAD) && !(c->flags & SFFN_FLAG_DW_FP32_ACCUMULATE);
+    const StepTiles shared = step_tiles(c->T, c->D, c->F, c->M, n_experts, true, true), alone = step_tiles(c->T, c->D, c->F, c->M, n_experts, true, false);
+    if (tiles) *tiles = may_share ? shared : alone;
+    const size_t codes = shared.mix ? TF / 2 : 0, sums = split_bytes({alone.v, alone.v_split}, c->T, c->D);
+    L->at2 = L->split = take(codes > sums ? codes : sums);
     const Fp8Parts parts = fp8_parts(c->T, c->D, c->F, n_experts);
     L->amax = take(sizeof(float) * (2 * (size_t)parts.x + parts.w1 + parts.w2 + 2 * kAmaxSlots * kAmaxSlotStride));     // x, w1, w2, dy: one float per workgroup of their passes; y2, dy1: slots
     L->scratch_end = off;

@@ -100,7 +100,7 @@ struct WgradArgs {
 // another (a backward call: eqs. (5), (4), then (7), (8)).  Eq. (4) then takes the 128 tile and its results need operand buffers of their own, since
 // eqs. (3), (5) still read those of eq. (1).
 struct StepTiles { int g = 0, g_bwd = 0, v = 0, v_split = 1, w = 0; bool mix = false; };
-inline StepTiles step_tiles(int64_t T, int64_t D, int64_t F, int M, int experts, bool fp8);
+inline StepTiles step_tiles(int64_t T, int64_t D, int64_t F, int M, int experts, bool fp8, bool may_share = true);
 enum { kMixForwardTail = 0, kMixBackwardHead = 1, kMixBackwardTail = 2 };      // {(3), (5), (4)}, {(5), (4)}, {(7), (8)}
 // M = 8: v8 (else null: va); acc32: not with kMixForwardTail
 hipError_t launch_step_mix_bf16(int what, int logM, const StepTiles& t, bool acc32, const Vnm8Args* v8, const GatherArgs* va, const GemmV2Args* g, const WgradArgs& w, hipStream_t s);
@@ -249,7 +249,8 @@ inline int pick_wgrad_tile(int64_t F, int64_t N, int64_t T, int experts, bool sp
     return pick_tile(tiles(256), tiles(128), tiles(64), (int)(T / 64 / e), 0.58f, split_ok ? 256 : 0, 12);
 }
 
-inline StepTiles step_tiles(int64_t T, int64_t D, int64_t F, int M, int experts, bool fp8) {
+// may_share: false where the shared launches are not built for the call
+inline StepTiles step_tiles(int64_t T, int64_t D, int64_t F, int M, int experts, bool fp8, bool may_share) {
     StepTiles t;
     const int unit = fp8 ? 128 : 64, steps = (int)(D / unit);
     GemmGroup g;
@@ -260,7 +261,7 @@ inline StepTiles step_tiles(int64_t T, int64_t D, int64_t F, int M, int experts,
     t.v = M == 8 ? pick_vnm8_tile(T, D, (int)(F / unit), g.n, fp8) : fp8 ? 256 : pick_gather_tile(T, D, (int)(4 * F / M / 64));
     t.w = pick_wgrad_tile(F, D, T, experts > 1 ? experts : 0, M == 8 || fp8);
     // (0.56: in a shared launch the small tiles pay where eqs. (1), (4) by themselves would be even)
-    t.mix = pick_gemm_tile(F, T, steps, g, 0.56f, true) != 256 && t.w != 256 && (M != 8 || t.v != 256);
+    t.mix = may_share && pick_gemm_tile(F, T, steps, g, 0.56f, true) != 256 && t.w != 256 && (M != 8 || t.v != 256);
     if (t.mix) t.g_bwd = 128;
     else { t.v = v.tile; t.v_split = v.n; }
     return t;

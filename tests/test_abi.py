@@ -362,3 +362,18 @@ def test_workspace_layout_properties_over_random_configurations():
             assert lay["total"] - less["total"] == (0 if lean else 2 * E * F * D + 2 * (E * F * D // 8) + (2 * (4 * T * F // M) if M == 8 else 0))
 
     check()
+
+
+def test_fp8_steps_without_shared_launches_have_room_for_split_contractions():
+    """T = 64, d_model = 1024, d_ff = 8192: with fp8 weight gradients the step shares launches; without them, or into float32 buffers, eqs. (3), (7) are
+    shared by several workgroups a tile, whose float32 sums (a multiple of T x d_model, and the counters) the workspace holds.  The size is the same, so that
+    one scratch buffer serves both."""
+    lib, T, D, F = sffn.load(), 64, 1024, 8192
+    lib.sffn_fp8_workspace_bytes.restype = ctypes.c_size_t
+    size = lambda flags: lib.sffn_fp8_workspace_bytes(ctypes.byref(binding._Cfg(T, D, F, 64, 8, 0, flags)))  # noqa: E731
+    sizes = {f: size(f) for f in (0, binding.FLAG_FP8_WGRAD, binding.FLAG_DW_FP32_ACCUMULATE, binding.FLAG_FP8_WGRAD | binding.FLAG_DW_FP32_ACCUMULATE)}
+    assert len(set(sizes.values())) == 1
+    # everything else the workspace holds, without the canonical copies: X and dY (codes, and transposed), the activation in its forms, both weights
+    other = T * D * 2 + 2 * T * D * 2 + T * F * (1 / 2 + 1 / 2 + 1 / 8 + 1 + 1 / 2 + 1 / 4 + 1 / 16 + 1 / 128 + 1 / 512) + F * D * (2 * 5 / 8 + 2 * 5 / 8 + 2)
+    rest = sizes[0] - other
+    assert any(n * T * D * 4 + 4096 <= rest <= n * T * D * 4 + 4096 + (64 << 10) for n in range(2, 17)), rest

@@ -126,3 +126,19 @@ def test_split_activation_contractions(M, T, D, F):
     assert_gemm_close(to_bits(first[1]), oracle.vnm_spmm(to_bits(step.saved()["dy1_vals"]), *y2[1:], inp["W1"], 1, 64, M), "dX")
     alone = sffn.vnm_spmm(*[step.saved()[k] for k in ("y2_vals", "y2_meta", "colidx")], dev[2], 0, 64, M)
     assert_gemm_close(to_bits(alone), to_bits(first[0]), "y3 alone")
+
+
+@pytest.mark.parametrize("wgrad_fp8,dw_fp32", [(False, False), (True, True)])
+def test_split_activation_contractions_of_the_fp8_step(wgrad_fp8, dw_fp32):
+    """The same on codes, in the steps that do not share launches: against the oracle, and twice in a row."""
+    T, D, F = 64, 1024, 8192
+    inp = make_ffn_inputs(T, D, F, seed=34)
+    sc = _fp8_step_scales(inp)
+    dev = [to_dev(inp[k]) for k in ("X", "W1", "W2", "b1", "dY")]
+    step = sffn.FfnStepFp8(T, D, F, sc, sffn.MODE_HARD, keep_dense=True, wgrad_fp8=wgrad_fp8, dw_fp32=dw_fp32)
+    first = [t.clone() for t in step(*dev)]
+    s = {k: to_bits(v) if v.dtype == torch.bfloat16 else v.cpu().numpy() for k, v in step.saved().items()}
+    outs = {k: to_bits(v.to(torch.bfloat16)) for k, v in zip(("Y3", "dX", "dW1", "dW2"), first)}
+    _check_fp8_step_against_oracle(inp, sc, s, outs, sffn.MODE_HARD, wgrad_fp8, 8)
+    second = step(*dev)
+    assert torch.equal(first[0], second[0]) and torch.equal(first[1], second[1])
