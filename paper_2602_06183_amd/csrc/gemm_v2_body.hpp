@@ -1000,7 +1000,7 @@ hipError_t launch_gemm_v2(const GemmV2Args& a, hipStream_t s, int tile = 0) {
     // (grouped along the contraction, role 2: a tile contracts its own expert's tokens only)
     if (!tile) {
         const int steps = a.K / (SPARSE ? 64 : 32) / (a.grp.n && a.grp.role == 2 ? a.grp.n : 1);
-        constexpr int what = EPI == 0 ? kGemmPlain : EPI == 2 || EPI == 4 || EPI >= 32 ? kGemmBackward : kGemmForward;
+        constexpr int what = EPI == 0 ? kGemmPlain : EPI == 3 || EPI == 4 ? kGemmRouter : EPI == 2 || EPI >= 32 ? kGemmBackward : kGemmForward;
         constexpr bool tall = Sel::T128::BM == 256;
         tile = pick_gemm_tile(a.Ra, a.Rb, steps, a.grp, small_round(what, steps, tall), SPARSE, last_round(what, steps, tall), tall);
     }

@@ -154,26 +154,30 @@ inline int64_t token_tiles(int64_t T, int groups, int64_t edge) {
     return n * (((T + n - 1) / n + edge - 1) / edge);
 }
 // What a round of 128 tiles takes of a round of 256 tiles in gemm_v2, by the trips of the main loop: plain stores, or the V:N:M epilogues of eqs. (1) and
-// (4), whose part of a tile overlaps with the other workgroup's main loop.  The longer the contraction the more the bytes from L2 count, of which the small
-// tile needs twice as many per product.  Measured over 170 shapes (T 64 - 15000, D 256 - 6000, 1 - 8 experts; bf16, and fp8 by its own trips of 128):
-//   eq. (1)  12 trips 0.57, 17 0.59, 29 0.68, 36 0.69, 60 0.70, 84 0.74      (T = 5504, D = 768, F = 3072: 43 us on 256 tiles, 37 on 128; 8 x 512 tokens,
-//   eq. (4)  12 trips 0.63, 17 0.63, 29 0.72, 36 0.76, 60 0.71, 84 0.74       D = 3840, F = 12672: eq. (1) 292 and 370, eq. (4) 285 and 371)
-//   plain    26 trips 0.71, 46 0.73, 64 0.76 - 0.80, 86 0.89, 114 0.94       (T = 8000, N = 2560, K = 7296: 239 us and 293)
+// (4), whose part of a tile overlaps with the other workgroup's main loop (the router's are shorter).  The longer the contraction the more the bytes from L2
+// count, of which the small tile needs twice as many per product.  Fitted to 250 shapes (T 64 - 15000, D 256 - 6000, 1 - 8 experts; bf16, and fp8 by its own
+// trips of 128), over which what is chosen takes 0.03 % (eq. (1)) and 0.1 % (eq. (4)) longer than the better tile of each.  Some of them, on 256 / 128 tiles:
+//   eq. (1)  T = 5504, D = 768, F = 3072 43 / 37 us; T = 8192, D = 960, F = 3008 57 / 57; T = 2816, D = 2624, F = 7488 92 / 97; 8 x 512 tokens, D = 3840,
+//            F = 12672 292 / 370
+//   eq. (4)  33 / 31; 54 / 59; 79 / 91; 285 / 371
+//   router   T = 8192, D = 2048, F = 8192, M = 16 95 / 86, eq. (4) 94 / 92; T = 4096, D = 4096, F = 16384 147 / 161, 149 / 160
+//   plain    26 trips 0.71, 46 0.73, 64 0.76 - 0.80, 86 0.89, 114 0.94 (T = 8000, N = 2560, K = 7296: 239 / 293 us)
+// last_round: what the last round takes when it has at most 256 small tiles, one per CU (plain stores: 0.6 up to 48 trips, the router's eq. (3), 288 / 1120 tiles
+// of K = 2048: 76 / 68 us; T = 8000, N = 2560, K = 7296 has 320 / 1260).
 // Blocks of M = 64 columns want 128 hidden units in one wavefront, so that their small tile is 256 hidden units x 128 tokens (`tall`): a round of them, two
 // per CU, is no less work than one of 256 tiles (1.03 - 1.16 of it), and alone on its CU such a tile takes 0.85 - 1.1 of a 256 tile (5 trips 0.88, 13 0.93, 30
 // 0.97, 55 1.06, 88 1.08; eq. (4) 0.91, 0.96, 1.03, 1.27, 1.02).
-enum { kGemmPlain = 0, kGemmForward = 1, kGemmBackward = 2 };
+enum { kGemmPlain = 0, kGemmForward = 1, kGemmBackward = 2, kGemmRouter = 3 };
 inline float small_round(int what, int steps, bool tall = false) {
     const float n = (float)steps;
     if (tall) return 1.06f;
     if (what == kGemmPlain) return n < 110.0f ? 0.68f + 0.002f * n : 0.90f;
-    return (n < 35.0f ? 0.56f + 0.004f * n : 0.70f) + (what == kGemmBackward ? 0.04f : 0.0f);
+    const float w = what == kGemmRouter ? 0.53f + 0.0031f * n : (what == kGemmBackward ? 0.62f : 0.50f) + 0.006f * n;
+    return w < 0.74f ? w : 0.74f;
 }
-// plain stores: a last round of up to 256 small tiles counts 0.6 up to 48 trips (the router's eq. (3), 288 / 1120 tiles of K = 2048: 76 us on 256 tiles, 68 on
-// 128; T = 8000, N = 2560, K = 7296, 320 / 1260 tiles: 239 and 293)
 inline float last_round(int what, int steps, bool tall = false) {
     if (tall) return (0.87f + 0.004f * (float)steps + (what == kGemmBackward ? 0.03f : 0.0f)) / 1.06f;
-    return what == kGemmPlain && steps <= 48 ? 0.6f : 1.0f;
+    return what != kGemmPlain ? 0.75f : steps <= 48 ? 0.6f : 1.0f;
 }
 // gemm_v2 (i x j outputs); w128, last: see pick_tile.  64 tiles: T = 64, D = 2048, F = 8192 (32 / 64 / 128 tiles): eqs. (1), (4) 43 / 33 us on 256 tiles,
 // 21 / 18 on 128, 17 / 14 on 64; with more than 256 of them they lose to 128 (T = 128, D = 1984, F = 8512, 266 of them: 25 and 19 us).
@@ -189,11 +193,12 @@ inline int pick_epilogue_tile(int64_t F, int64_t T, int steps, const GemmGroup& 
 }
 // V:2:8 activation GEMM.  T = 8192, N = 2048, F = 8192 (256 / 1024 tiles): 107 us on 256 tiles, 148 on 128; T = 2048 (64 / 256): 85 and 54; T = 1024,
 // N = 1408, F = 4928 (24 / 88 / 352): 55, 33, and 29 on 64 tiles; T = 64, N = 2048, F = 8192 (8 / 16 / 32): 83, 49, 28
-// More than 256 of the 64 tiles: only for long contractions of bf16 (T = 256, N = 5824, F = 24704, 364 of them: 169 us, 192 on 128 tiles; 24 - 78 trips: even or
-// up to a third slower than 128); fp8 loses to every other tile there (T = 4864, N = 384, F = 1408, 456 of them: 18.5 us, 10.6 on 128, 16.0 on 256).
+// More than 256 of the 64 tiles: only for long contractions of bf16 (T = 256, N = 5824, F = 24704, 364 of them: 169 us, 192 on 128 tiles; 24 trips: a third
+// slower than 128, 44: 15 %, 63 - 84: even, but in a shared launch 128 tiles are better up to there: T = 1664, D = 1216, F = 4032 the step 147 us, 106 on 128);
+// fp8 loses to every other tile there (T = 4864, N = 384, F = 1408, 456 of them: 18.5 us, 10.6 on 128, 16.0 on 256).
 inline int pick_vnm8_tile(int64_t T, int64_t N, int steps, int groups, bool fp8) {
     auto tiles = [&](int64_t edge) { return (unsigned)(token_tiles(T, groups, edge) * ((N + edge - 1) / edge)); };
-    return pick_tile(tiles(256), tiles(128), tiles(64), steps, 0.72f, !fp8 && steps >= 96 ? 512 : 256, 8);
+    return pick_tile(tiles(256), tiles(128), tiles(64), steps, 0.72f, !fp8 && steps >= 84 ? 512 : 256, 8);
 }
 // gathered-row activation GEMM: 64 tokens x 256 columns, or 64 x 64
 // (T = 256, N = 1024, F = 4096, M = 16: 19 us and 12 us; T = N = 1024: 20 and 12; T = 512, N = 4096, F = 16384: 90 and 67; T = 1984, N = 1344, M = 32: 14 and 23)

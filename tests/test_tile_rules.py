@@ -59,3 +59,9 @@ def test_tiles_of_the_activation_contractions(chosen, fp8):
     """Eqs. (3), (7) at M = 8 by themselves and in a shared launch."""
     rows = [(t["eq3"], o[2]) for c, t, o in chosen if c[0] == "step" and c[1] == str(int(fp8)) and "eq3" in t and 64 in t["eq3"]]
     check(rows, 1.3, 1.06)
+
+
+def test_tiles_of_the_routers_contractions(chosen):
+    rows = [(t, o[0]) for c, t, o in chosen if c[0] == "router"]
+    check([(t["eq1"], tile) for t, tile in rows])
+    check([(t["eq4"], tile) for t, tile in rows])

@@ -1,5 +1,6 @@
 // Prints what the host-side tile rules (kernels.hpp) choose, for tests/test_tile_rules.py.  One line of standard input is one call:
 //   step <fp8> <M> <D> <F> <experts> <offset 0> ... <offset n>   -> tiles of eq. (1), eq. (4), eqs. (3), (7), weight gradients; shared launches
+//   router <M> <D> <F> <T>                                       -> tile of its eqs. (1), (4)
 //   plain <T> <N> <K>                                            -> tile of a 2:4 contraction with a plain store
 #include <stdio.h>
 #include <string.h>
@@ -16,6 +17,15 @@ int main() {
             if (scanf("%ld %ld %ld", &a, &b, &c) != 3) return 1;
             const int steps = (int)(c / 64);
             printf("%d\n", pick_gemm_tile(b, a, steps, GemmGroup(), small_round(kGemmPlain, steps), true, last_round(kGemmPlain, steps)));
+            continue;
+        }
+        if (!strcmp(what, "router")) {
+            if (scanf("%ld %ld %ld %ld", &a, &b, &c, &d) != 4) return 1;
+            GemmGroup g;
+            g.n = (int)(a / 4);
+            g.role = 1;
+            const int steps = (int)(b / 64);
+            printf("%d\n", pick_gemm_tile(4 * c / a, (d + 63) / 64 * 64 + 16 * a, steps, g, small_round(kGemmRouter, steps), true, last_round(kGemmRouter, steps)));
             continue;
         }
         if (scanf("%ld %ld %ld %ld %ld", &a, &b, &c, &d, &e) != 5 || e > GemmGroup::kMaxExperts) return 1;
