@@ -16,7 +16,11 @@
  *     rule); base pointers 16-byte aligned.  V must be 64; M is 8, 16, 32 or 64 (Table 5 of the paper) and the
  *     compressed axis a multiple of 2 M.
  *   - Rounding: products accumulate in fp32 on the matrix cores; every stored bf16 is one
- *     round-to-nearest-even of an fp32 value.
+ *     round-to-nearest-even of an fp32 value.  The order of a sum depends on the call's sizes:
+ *     outputs of few tiles are summed by several wavefronts or workgroups, a fixed share each,
+ *     whose fp32 sums are added in a fixed order.  The same call gives the same bits every time;
+ *     an expert of a grouped step and the same tokens alone, or a stand-alone contraction and
+ *     that of the step, may differ in the last place.
  *
  * Packed formats (bit-exact contract)
  *   2:4   logical S[R,K]; group g of row r is S[r,4g..4g+3]; the two entries of largest
@@ -313,7 +317,7 @@ int ffn_router_full_step(const sffn_cfg* cfg, const uint16_t* means, const uint1
  * untouched between them (one per layer in flight; the backward call consumes what the forward call left, so each forward call is
  * followed by one backward call); the backward call takes the same seg_offsets and perm as the forward call
  * (ffn_router_full_backward reads the routing that ffn_router_full_forward left in the workspace) and no weights.
- * SFFN_FLAG_WEIGHTS_PACKED (one-call and forward forms): the five weight-preparation launches are skipped and the call reads what
+ * SFFN_FLAG_WEIGHTS_PACKED (one-call and forward forms): the weights' preparation is skipped and the call reads what
  * the previous call on this workspace prepared from the same W1, W2 (the caller's promise, as for ffn_sparse_step). */
 int ffn_router_forward(const sffn_cfg* cfg, const int64_t* seg_offsets, const int32_t* perm, const uint16_t* X,
                        const uint16_t* W1, const uint16_t* W2, const float* b1, uint16_t* Y3, void* workspace, size_t ws_bytes,
@@ -371,8 +375,8 @@ int ffn_sparse_step_grouped(const sffn_cfg* cfg, int n_experts, const int64_t* s
                             uint16_t* dX, uint16_t* dW1, uint16_t* dW2, void* workspace, size_t ws_bytes, void* stream);
 
 /* Alg. 1 (forward pass) and Alg. 2 (backward pass) as separate calls, for a training loop in which other layers run between a
- * layer's forward and its backward pass.  Together the two calls enqueue exactly the launches of the one-call step, in its order, and
- * give the same bits in every output and intermediate.
+ * layer's forward and its backward pass.  Together the two calls do what the one-call step does and give the same bits in every output
+ * and intermediate (small layers: the one-call step puts contractions of both passes into one launch, the two calls only those of a pass).
  *   forward  = Alg. 1, eqs. (1)-(3): X, W1, W2, b1 -> Y3.  It also packs W2.T (Alg. 2 line 2), because that pass over W2 is the one that
  *              writes the W2.T copy eq. (3) reads.  SFFN_FLAG_WEIGHTS_PACKED applies to this call.
  *   backward = Alg. 2, eqs. (4)-(8): dY -> dX, dW1, dW2.  The bf16 form reads the dense W1 in place (eq. (7)); the fp8 form reads the

@@ -7,8 +7,8 @@
 //              trip along k is the whole cost.
 //   SPARSE: A packed 2:4 -> v_smfmac_f32_32x32x32_bf16; ring of 3 stages of 64 k.  Eqs. (1), (3), (4), (7):
 //           in the fused step on blocked operands (eqs. (1), (4) with the V:N:M epilogue), stand-alone on row-major ones.
-//   dense : v_mfma_f32_32x32x16_bf16; ring of 4 stages of 32 k; row-major operands only (stand-alone
-//           vnm_wgrad; the fused step's weight gradients have their own kernel, gemm_wgrad.hip).
+//   dense : v_mfma_f32_32x32x16_bf16; ring of 4 stages of 32 k; row-major operands only: the weight gradients of the router's step and of the unfused
+//           path (those of the fused steps and the stand-alone vnm_wgrad: gemm_wgrad.hip, gemm_wgrad_wide.hip).
 // Register layouts of the two instructions are documented in lds_dma.hpp.
 #pragma once
 #include "common.hpp"
@@ -1006,7 +1006,7 @@ hipError_t launch_gemm_v2(const GemmV2Args& a, hipStream_t s, int tile = 0) {
     }
     if (tile == 256) return launch_units<GemmV2Unit<SPARSE, OUT_I_CONTIG, EPI, BLOCKED, FP8, Tile256<SPARSE>>>(s, a);
     if (tile == 128) return launch_units<GemmV2Unit<SPARSE, OUT_I_CONTIG, EPI, BLOCKED, FP8, typename Sel::T128>>(s, a);
-    // (the dense form has no 64 tile: its two users are the stand-alone vnm_wgrad and the router's weight gradients)
+    // (the dense form has no 64 tile)
     if constexpr (SPARSE) return launch_units<GemmV2Unit<SPARSE, OUT_I_CONTIG, EPI, BLOCKED, FP8, typename Sel::T64>>(s, a);
     else return launch_units<GemmV2Unit<SPARSE, OUT_I_CONTIG, EPI, BLOCKED, FP8, typename Sel::T128>>(s, a);
 }

@@ -262,6 +262,7 @@ inline StepTiles step_tiles(int64_t T, int64_t D, int64_t F, int M, int experts,
     g.role = 1; g.n = experts > 1 ? experts : 0;
     t.g = pick_epilogue_tile(F, T, steps, g, kGemmForward, M);
     t.g_bwd = pick_epilogue_tile(F, T, steps, g, kGemmBackward, M);
+    // (the gathered-row kernel on codes has the 256-column tile only, so wide fp8 blocks neither take 64 x 64 tiles nor split: not built)
     const SplitPlan v = M == 8 ? plan_vnm8(T, D, (int)(F / unit), g.n, fp8) : fp8 ? SplitPlan{256, 1} : plan_gather(T, D, (int)(4 * F / M / 64), g.n);
     t.v = M == 8 ? pick_vnm8_tile(T, D, (int)(F / unit), g.n, fp8) : fp8 ? 256 : pick_gather_tile(T, D, (int)(4 * F / M / 64));
     t.w = pick_wgrad_tile(F, D, T, experts > 1 ? experts : 0, M == 8 || fp8);
