@@ -22,11 +22,21 @@ sys.path.insert(0, ROOT)
 
 MFMA_BF16_PEAK_TFLOPS = 2500.0     # MI355X dense bf16 matrix-core peak
 HBM_PEAK_GBS = 8000.0
-SPARSE_GEMM = "gemm_nt_v2_kernel<sparse A, smfmac_f32_32x32x32_bf16>"
-DENSE_GEMM = "gemm_nt_v2_kernel<dense A, mfma_f32_32x32x16_bf16>"
-WGRAD = "wgrad_vnm_kernel<compact V:N:M A, mfma_f32_32x32x16_bf16>"
-VNM8_GEMM = "vnm8_gemm_kernel<V:2:8 A, smfmac_f32_32x32x32_bf16>"
+# the contraction kernels by their units (csrc/launch_mix.hpp)
+SPARSE_GEMM = "GemmV2Unit<2:4 A, smfmac_f32_32x32x32_bf16>"
+DENSE_GEMM = "GemmV2Unit<dense A, mfma_f32_32x32x16_bf16>"
+WGRAD = "WgradUnit<compacted V:N:M A, mfma_f32_32x32x16_bf16>"
+WGRAD_WIDE = "WgradWideUnit<kept rows of V:N:M A, mfma_f32_32x32x16_bf16>"
+VNM8_GEMM = "Vnm8Unit<V:2:8 A, smfmac_f32_32x32x32_bf16>"
+GATHER_GEMM = "GatherUnit<gathered rows, smfmac_f32_32x32x32_bf16>"
+SHARED = "several units in one launch"
 ROUTER_GEMMS = ("router/y1c+sqrelu+2:4", "router/dy2c+dsqrelu", "router/y3", "router/dX", "router/dW2.T", "router/dW1")
+
+
+def shared_parts(stage):
+    """The contractions of a launch that several of them share (small layers), else None."""
+    parts = ["step/" + p for p in stage[5:].split("+")] if stage.startswith("step/") else []
+    return parts if len(parts) > 1 and set(parts) <= {"step/y3", "step/dX", "step/dW2", "step/dW1", "step/dy2"} else None
 
 
 def algorithmic_flops(stage, T, D, F, M=8):
@@ -35,8 +45,15 @@ def algorithmic_flops(stage, T, D, F, M=8):
     act = 4.0 / M * tdf                                          # V:2:M activations: 2 of M survive (M = 8: a quarter)
     if stage.startswith("router/"):                              # neuron-level experts: every contraction covers 4 / M of the hidden units
         return act if stage in ROUTER_GEMMS else None
+    if shared_parts(stage):
+        return sum(algorithmic_flops(p, T, D, F, M) for p in shared_parts(stage))
     return {"step/y1+sqrelu_vnm_compress": tdf, "step/dy2+dsqrelu_vnm": tdf, "step/y1": tdf, "step/dy2": tdf,   # 2:4 weights: half of K survives
             "step/y3": act, "step/dX": act, "step/dW2": act, "step/dW1": act}.get(stage)
+
+
+def wgrad_kept_rows(T, F, M):
+    """Blocks of M = 32 and 64 columns, from 768 tokens on: eqs. (5), (8) multiply the kept rows only."""
+    return M >= 32 and F % (8 * M) == 0 and T >= 768
 
 
 def executed_flops(stage, T, D, F, M=8, gathered=True):
@@ -44,9 +61,12 @@ def executed_flops(stage, T, D, F, M=8, gathered=True):
     tdf = float(T) * D * F
     if stage.startswith("router/"):
         return 8.0 / M * tdf if stage in ROUTER_GEMMS else None
+    if shared_parts(stage):
+        return sum(executed_flops(p, T, D, F, 8 if p in ("step/dW2", "step/dW1") else M, gathered) for p in shared_parts(stage))
     act = (8.0 / M * tdf) if gathered else 2 * tdf              # eqs. (3), (7): only the kept columns are contracted / all F as plain 2:4
+    wgrad = (8.0 / M if wgrad_kept_rows(T, F, M) else 2.0) * tdf
     return {"step/y1+sqrelu_vnm_compress": 2 * tdf, "step/dy2+dsqrelu_vnm": 2 * tdf, "step/y1": 2 * tdf, "step/dy2": 2 * tdf,
-            "step/y3": act, "step/dX": act, "step/dW2": 2 * tdf, "step/dW1": 2 * tdf}.get(stage)
+            "step/y3": act, "step/dX": act, "step/dW2": wgrad, "step/dW1": wgrad}.get(stage)
 
 
 KERNEL_OF_STAGE = {"step/y1+sqrelu_vnm_compress": SPARSE_GEMM, "step/dy2+dsqrelu_vnm": SPARSE_GEMM, "step/y1": SPARSE_GEMM, "step/dy2": SPARSE_GEMM,
@@ -371,13 +391,15 @@ def main():
     kos = dict(KERNEL_OF_STAGE)
     if M == 8 and not args.router:      # eqs. (3), (7) contract the V:2:8 activation as it is, kept rows picked at the fragment reads
         kos.update({"step/y3": VNM8_GEMM, "step/dX": VNM8_GEMM})
-    if M != 8:      # wide blocks: eqs. (3), (7) gather rows, eqs. (5), (8) contract the dense transposed activation with the dense-operand tile kernel
+    if M != 8:      # wide blocks: eqs. (3), (7) gather rows, eqs. (5), (8) contract the compacted operand or (M = 32, 64) its kept rows only
         if "step/to24(y2)" not in acc:
-            kos.update({"step/y3": "vnm_spmm_gather_kernel<smfmac_f32_32x32x32_bf16>", "step/dX": "vnm_spmm_gather_kernel<smfmac_f32_32x32x32_bf16>"})
+            kos.update({"step/y3": GATHER_GEMM, "step/dX": GATHER_GEMM})
+            if wgrad_kept_rows(T, F, M):
+                kos.update({"step/dW2": WGRAD_WIDE, "step/dW1": WGRAD_WIDE})
         if "step/expand(y2)" in acc:    # the unfused path contracts the dense transposed activation; the fused one the compacted operand
             kos.update({"step/dW2": DENSE_GEMM, "step/dW1": DENSE_GEMM})
     for name, ms in acc.items():
-        by_kernel.setdefault(kos.get(name, name), []).append((name, ms))
+        by_kernel.setdefault(SHARED if shared_parts(name) else kos.get(name, name), []).append((name, ms))
     dom_kernel = max(by_kernel, key=lambda k: sum(ms for _, ms in by_kernel[k]))
     launches = by_kernel[dom_kernel]
     avg_ms = sum(ms for _, ms in launches) / len(launches)
