@@ -15,10 +15,10 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("T,D,F", [
-    (64, 1088, 2112),       # few tiles, long contractions: 64 tiles in eqs. (1), (3), (4), (7), trip counts that four wavefronts do not share evenly
+    (64, 1088, 2112),       # few tiles, long contractions: 64 tiles in eqs. (1), (3), (7), trip counts that four wavefronts do not share evenly
     (832, 320, 576),        # 64 tiles in the weight gradients (13 token blocks)
     (1088, 1152, 4160),     # 128 tiles with a half-empty last row and column
-    (2112, 2112, 4160),     # 256 tiles in eqs. (1), (4), 128 tiles elsewhere
+    (2112, 2112, 4160),     # 256 tiles in eqs. (1), (4), (5), (8), 128 tiles in eqs. (3), (7)
 ])
 def test_step_on_every_tile_size(T, D, F):
     _teacher_forced_step_check(T, D, F, sffn.MODE_SOFT, seed=21)
@@ -110,8 +110,10 @@ def test_grouping_at_the_edges_of_its_blocks(T, M):
 
 @pytest.mark.parametrize("M,T,D,F", [
     (8, 64, 3968, 8192),
-    (8, 192, 2048, 8256),       # several token blocks; 129 stages
+    (8, 192, 2048, 8256),       # several token blocks; 129 stages (the step shares launches, so that only the stand-alone call is split)
+    (8, 128, 576, 13120),       # two token blocks, 14 workgroups a tile, which do not share 205 stages evenly
     (16, 64, 3968, 8192),       # gathered rows
+    (16, 128, 576, 13312),
 ])
 def test_split_activation_contractions(M, T, D, F):
     """Eqs. (3), (7) shared by several workgroups per tile: twice in a row (the counters are left as they were found), alone and in the step."""
@@ -142,3 +144,33 @@ def test_split_activation_contractions_of_the_fp8_step(wgrad_fp8, dw_fp32):
     _check_fp8_step_against_oracle(inp, sc, s, outs, sffn.MODE_HARD, wgrad_fp8, 8)
     second = step(*dev)
     assert torch.equal(first[0], second[0]) and torch.equal(first[1], second[1])
+
+
+@pytest.mark.parametrize("fp8,M,D,F,seg", [
+    (False, 8, 2240, 9664, [0, 128, 128, 448, 640]),         # 128 tiles in eqs. (1), (4)
+    (False, 8, 2240, 9664, [0, 512, 512, 1216, 1792]),       # 128 tiles in eqs. (1), (3), (7), 256 in eq. (4)
+    (False, 64, 2240, 9216, [0, 128, 128, 448, 640]),        # 256 tiles
+    (True, 8, 2304, 9728, [0, 128, 128, 448, 640]),          # on codes: 128 tiles in eqs. (1), (3), (4), (7)
+])
+def test_grouped_step_on_tiles_chosen_by_the_segments(fp8, M, D, F, seg):
+    """Experts with 0 and odd numbers of 64-token blocks: packed metadata and weight gradients are the bits of a step on the expert's tokens alone, whose tiles
+    are others (128 and 256 tiles sum in the same order); Y3 and dX are the same sums in another order where 64 tiles are among them: 2^-8, a bf16's last place."""
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(41)
+    randn = lambda *shape: torch.randn(shape, dtype=torch.bfloat16, device="cuda", generator=gen)  # noqa: E731
+    E, T = len(seg) - 1, seg[-1]
+    X, dY, W1, W2 = randn(T, D), randn(T, D), randn(E, F, D).mul_(0.02), randn(E, D, F).mul_(0.02)
+    b1 = torch.full((E, F), -0.5 * 0.02 * D ** 0.5, device="cuda")
+    sc = dict(x=5 / 448, w1=0.1 / 448, w2=0.1 / 448, y2=0.05, dy=5 / 448, dy1=0.05)
+    step = sffn.FfnStepFp8Grouped(seg, D, F, sc, M=M, wgrad_fp8=True) if fp8 else sffn.FfnStepGrouped(seg, D, F, M=M)
+    Y3, dX, dW1, dW2 = step(X, W1, W2, b1, dY)
+    for e, (a, b) in enumerate(zip(seg, seg[1:])):
+        if a == b:
+            assert not dW1[e].any() and not dW2[e].any()
+            continue
+        alone = sffn.FfnStepFp8(b - a, D, F, sc, M=M, wgrad_fp8=True) if fp8 else sffn.FfnStep(b - a, D, F, M=M)
+        want = alone(X[a:b].contiguous(), W1[e], W2[e], b1[e], dY[a:b].contiguous())
+        assert torch.equal(dW1[e], want[2]) and torch.equal(dW2[e], want[3])
+        assert torch.equal(step.saved()["y2_meta"][a:b], alone.saved()["y2_meta"])
+        for got, ref in ((Y3[a:b], want[0]), (dX[a:b], want[1])):
+            assert (got.float() - ref.float()).norm() <= 2.0 ** -8 * ref.float().norm()
