@@ -209,7 +209,9 @@ inline int pick_gather_tile(int64_t T, int64_t N, int steps) { return (T / 64) *
 // `n` float32 copies of the output (at most kSplitMost bytes) at 4 TB/s.  Taken where that saves 15 % and more.  T = 64, N = 4096, F = 16384: 94 -> 38 us
 // (4 splits; from HBM instead of the last-level cache: 90 -> 60), N = 2048, F = 8192: 28 -> 16 (8 splits); fp8: 40 -> 23; M = 16: 41 -> 22.  Not where eqs.
 // (3), (7) share a launch: its workgroups fill the chip as it is (T = 192, N = 1024, F = 4096: the step 64 us, 74 with 5 splits).
-constexpr int64_t kSplitMost = (int64_t)32 << 20;
+// At most 1024 workgroups: with more, each with its start and its sums, the estimate is off (T = 384, N = 3072, F = 10752: 60 us undivided, 59 with 3 splits,
+// 69 with 4; T = 256, N = 4736, F = 16320: 70, 72 and 80).
+constexpr int64_t kSplitMost = (int64_t)32 << 20, kSplitMostGroups = 1024;
 struct SplitPlan { int tile, n; };
 inline SplitPlan plan_split(int64_t T, int64_t N, int steps, int tile, float us64) {
     auto tiles = [&](int64_t edge) { return ((T + edge - 1) / edge) * ((N + edge - 1) / edge); };
@@ -221,7 +223,7 @@ inline SplitPlan plan_split(int64_t T, int64_t N, int steps, int tile, float us6
     SplitPlan best = {tile, 1};
     if (tile == 256) return best;
     float least = 0.85f * cost(tile, 1);
-    for (int n = 2; n <= 16 && steps / n >= 8 && tiles(64) * 64 * 64 * 4 * n <= kSplitMost; ++n) {
+    for (int n = 2; n <= 16 && steps / n >= 8 && tiles(64) * n <= kSplitMostGroups && tiles(64) * 64 * 64 * 4 * n <= kSplitMost; ++n) {
         const float c = cost(64, n);
         if (c < least) { least = c; best = {64, n}; }
     }

@@ -1,6 +1,7 @@
 // Prints what the host-side tile rules (kernels.hpp) choose, for tests/test_tile_rules.py.  One line of standard input is one call:
 //   step <fp8> <M> <D> <F> <experts> <offset 0> ... <offset n>   -> tiles of eq. (1), eq. (4), eqs. (3), (7), weight gradients; shared launches
 //   router <M> <D> <F> <T>                                       -> tile of its eqs. (1), (4)
+//   split <T> <N> <F>                                            -> workgroups per tile of eq. (3) at M = 8
 //   plain <T> <N> <K>                                            -> tile of a 2:4 contraction with a plain store
 #include <stdio.h>
 #include <string.h>
@@ -17,6 +18,11 @@ int main() {
             if (scanf("%ld %ld %ld", &a, &b, &c) != 3) return 1;
             const int steps = (int)(c / 64);
             printf("%d\n", pick_gemm_tile(b, a, steps, GemmGroup(), small_round(kGemmPlain, steps), true, last_round(kGemmPlain, steps)));
+            continue;
+        }
+        if (!strcmp(what, "split")) {
+            if (scanf("%ld %ld %ld", &a, &b, &c) != 3) return 1;
+            printf("%d\n", plan_vnm8(a, b, (int)(c / 64), 0, false).n);
             continue;
         }
         if (!strcmp(what, "router")) {
