@@ -1001,8 +1001,8 @@ hipError_t launch_gemm_v2(const GemmV2Args& a, hipStream_t s, int tile = 0) {
     if (!tile) {
         const int steps = a.K / (SPARSE ? 64 : 32) / (a.grp.n && a.grp.role == 2 ? a.grp.n : 1);
         constexpr int what = EPI == 0 ? kGemmPlain : EPI == 3 || EPI == 4 ? kGemmRouter : EPI == 2 || EPI >= 32 ? kGemmBackward : kGemmForward;
-        constexpr bool tall = Sel::T128::BM == 256;
-        tile = pick_gemm_tile(a.Ra, a.Rb, steps, a.grp, small_round(what, steps, tall), SPARSE, last_round(what, steps, tall), tall);
+        constexpr int M = Sel::T128::BM == 256 ? 64 : EPI >= 20 ? 16 : 8;
+        tile = pick_gemm_tile(a.Ra, a.Rb, steps, a.grp, small_round(what, steps, M, FP8), SPARSE, last_round(what, steps, M, FP8), M == 64);
     }
     if (tile == 256) return launch_units<GemmV2Unit<SPARSE, OUT_I_CONTIG, EPI, BLOCKED, FP8, Tile256<SPARSE>>>(s, a);
     if (tile == 128) return launch_units<GemmV2Unit<SPARSE, OUT_I_CONTIG, EPI, BLOCKED, FP8, typename Sel::T128>>(s, a);

@@ -155,29 +155,37 @@ inline int64_t token_tiles(int64_t T, int groups, int64_t edge) {
 }
 // What a round of 128 tiles takes of a round of 256 tiles in gemm_v2, by the trips of the main loop: plain stores, or the V:N:M epilogues of eqs. (1) and
 // (4), whose part of a tile overlaps with the other workgroup's main loop (the router's are shorter).  The longer the contraction the more the bytes from L2
-// count, of which the small tile needs twice as many per product.  Fitted to 250 shapes (T 64 - 15000, D 256 - 6000, 1 - 8 experts; bf16, and fp8 by its own
-// trips of 128), over which what is chosen takes 0.03 % (eq. (1)) and 0.1 % (eq. (4)) longer than the better tile of each.  Some of them, on 256 / 128 tiles:
+// count, of which the small tile needs twice as many per product.  Fitted to 400 shapes (T 64 - 16000, D 256 - 6000, 1 - 8 experts; bf16, and fp8 by its own
+// trips of 128, with weights of its own), over which what is chosen takes 0.05 - 0.1 % longer than the better tile of each.  Some of them, on 256 / 128 tiles:
 //   eq. (1)  T = 5504, D = 768, F = 3072 43 / 37 us; T = 8192, D = 960, F = 3008 57 / 57; T = 2816, D = 2624, F = 7488 92 / 97; 8 x 512 tokens, D = 3840,
 //            F = 12672 292 / 370
 //   eq. (4)  33 / 31; 54 / 59; 79 / 91; 285 / 371
+//   fp8      eq. (1) T = 3072, D = 3712, F = 11136 132 / 123; T = 6784, D = 2560, F = 7936 147 / 142; eq. (4) T = 9152, D = 1408, F = 3712 69 / 65
+//   M = 16   eq. (4) T = 2560, D = 1984, F = 7936 67.5 / 63.0
 //   router   T = 8192, D = 2048, F = 8192, M = 16 95 / 86, eq. (4) 94 / 92; T = 4096, D = 4096, F = 16384 147 / 161, 149 / 160
 //   plain    26 trips 0.71, 46 0.73, 64 0.76 - 0.80, 86 0.89, 114 0.94 (T = 8000, N = 2560, K = 7296: 239 / 293 us)
 // last_round: what the last round takes when it has at most 256 small tiles, one per CU (plain stores: 0.6 up to 48 trips, the router's eq. (3), 288 / 1120 tiles
 // of K = 2048: 76 / 68 us; T = 8000, N = 2560, K = 7296 has 320 / 1260).
 // Blocks of M = 64 columns want 128 hidden units in one wavefront, so that their small tile is 256 hidden units x 128 tokens (`tall`): a round of them, two
-// per CU, is no less work than one of 256 tiles (1.03 - 1.16 of it), and alone on its CU such a tile takes 0.85 - 1.1 of a 256 tile (5 trips 0.88, 13 0.93, 30
-// 0.97, 55 1.06, 88 1.08; eq. (4) 0.91, 0.96, 1.03, 1.27, 1.02).
+// per CU, is about the work of one of 256 tiles, and alone on its CU such a tile takes 0.85 - 1.1 of a 256 tile (bf16: 5 trips 0.91, 13 0.94, 33 0.98, eq.
+// (4) 0.04 more; fp8: 2 trips 0.84, 14 0.87 - 0.9, 26 0.95).  Over 150 shapes what is chosen takes 0.02 % longer than the better tile (bf16) and 0.15 % (fp8):
+// fp8 T = 8384, D = 1280, F = 4096 eq. (1) 64.4 us on 256, 59.0 on 256 x 128; T = 3392, D = 5120, F = 14336 190 / 172, eq. (4) 174 / 163; bf16 T = 11712,
+// D = 1152, F = 3072 75.9 / 73.5; T = 2944, D = 4416, F = 18432 292 / 320.
 enum { kGemmPlain = 0, kGemmForward = 1, kGemmBackward = 2, kGemmRouter = 3 };
-inline float small_round(int what, int steps, bool tall = false) {
+inline float small_round(int what, int steps, int M = 8, bool fp8 = false) {
     const float n = (float)steps;
-    if (tall) return 1.06f;
+    float w;
     if (what == kGemmPlain) return n < 110.0f ? 0.68f + 0.002f * n : 0.90f;
-    const float w = what == kGemmRouter ? 0.53f + 0.0031f * n : (what == kGemmBackward ? 0.62f : 0.50f) + 0.006f * n;
+    if (what == kGemmRouter) w = 0.53f + 0.0031f * n;
+    else if (M == 64) return !fp8 ? 1.02f : n < 47.5f ? 0.96f + 0.004f * n : 1.15f;
+    else if (what == kGemmForward) w = 0.50f + (fp8 ? 0.004f : 0.006f) * n;
+    else w = fp8 ? 0.54f + 0.006f * n : M == 8 ? 0.62f + 0.006f * n : 0.56f + 0.004f * n;
     return w < 0.74f ? w : 0.74f;
 }
-inline float last_round(int what, int steps, bool tall = false) {
-    if (tall) return (0.87f + 0.004f * (float)steps + (what == kGemmBackward ? 0.03f : 0.0f)) / 1.06f;
-    return what != kGemmPlain ? 0.75f : steps <= 48 ? 0.6f : 1.0f;
+inline float last_round(int what, int steps, int M = 8, bool fp8 = false) {
+    if (what == kGemmPlain) return steps <= 48 ? 0.6f : 1.0f;
+    if (what == kGemmRouter || M != 64) return fp8 ? 0.8f : 0.75f;
+    return (fp8 ? 0.82f + 0.003f * (float)steps : 0.86f + 0.004f * (float)steps + (what == kGemmBackward ? 0.03f : 0.0f)) / small_round(what, steps, M, fp8);
 }
 // gemm_v2 (i x j outputs); w128, last: see pick_tile.  64 tiles: T = 64, D = 2048, F = 8192 (32 / 64 / 128 tiles): eqs. (1), (4) 43 / 33 us on 256 tiles,
 // 21 / 18 on 128, 17 / 14 on 64; with more than 256 of them they lose to 128 (T = 128, D = 1984, F = 8512, 266 of them: 25 and 19 us).
@@ -188,8 +196,8 @@ inline int pick_gemm_tile(int64_t Ra, int64_t Rb, int steps, const GemmGroup& g,
     return pick_tile(tiles(256, 256), tiles(tall ? 256 : 128, 128), tiles(64, 64), steps, w128, split ? 256 : 0, 16, last);
 }
 // eqs. (1), (4) with their epilogues; M: columns per V:N:M block
-inline int pick_epilogue_tile(int64_t F, int64_t T, int steps, const GemmGroup& g, int what, int M) {
-    return pick_gemm_tile(F, T, steps, g, small_round(what, steps, M == 64), true, last_round(what, steps, M == 64), M == 64);
+inline int pick_epilogue_tile(int64_t F, int64_t T, int steps, const GemmGroup& g, int what, int M, bool fp8) {
+    return pick_gemm_tile(F, T, steps, g, small_round(what, steps, M, fp8), true, last_round(what, steps, M, fp8), M == 64);
 }
 // V:2:8 activation GEMM.  T = 8192, N = 2048, F = 8192 (256 / 1024 tiles): 107 us on 256 tiles, 148 on 128; T = 2048 (64 / 256): 85 and 54; T = 1024,
 // N = 1408, F = 4928 (24 / 88 / 352): 55, 33, and 29 on 64 tiles; T = 64, N = 2048, F = 8192 (8 / 16 / 32): 83, 49, 28
@@ -262,8 +270,8 @@ inline StepTiles step_tiles(int64_t T, int64_t D, int64_t F, int M, int experts,
     const int unit = fp8 ? 128 : 64, steps = (int)(D / unit);
     GemmGroup g;
     g.role = 1; g.n = experts > 1 ? experts : 0;
-    t.g = pick_epilogue_tile(F, T, steps, g, kGemmForward, M);
-    t.g_bwd = pick_epilogue_tile(F, T, steps, g, kGemmBackward, M);
+    t.g = pick_epilogue_tile(F, T, steps, g, kGemmForward, M, fp8);
+    t.g_bwd = pick_epilogue_tile(F, T, steps, g, kGemmBackward, M, fp8);
     // (the gathered-row kernel on codes has the 256-column tile only, so wide fp8 blocks neither take 64 x 64 tiles nor split: not built)
     const SplitPlan v = M == 8 ? plan_vnm8(T, D, (int)(F / unit), g.n, fp8) : fp8 ? SplitPlan{256, 1} : plan_gather(T, D, (int)(4 * F / M / 64), g.n);
     t.v = M == 8 ? pick_vnm8_tile(T, D, (int)(F / unit), g.n, fp8) : fp8 ? 256 : pick_gather_tile(T, D, (int)(4 * F / M / 64));
@@ -286,8 +294,7 @@ inline void refine_tiles(StepTiles* t, int64_t D, int64_t F, int M, const GemmGr
     };
     auto pick = [&](int what) {
         const int steps = (int)(D / (fp8 ? 128 : 64));
-        const bool tall = M == 64;
-        return pick_tile(count(F, 256, 256), count(F, tall ? 256 : 128, 128), ~0u, 0, small_round(what, steps, tall), 0, 0, last_round(what, steps, tall));
+        return pick_tile(count(F, 256, 256), count(F, M == 64 ? 256 : 128, 128), ~0u, 0, small_round(what, steps, M, fp8), 0, 0, last_round(what, steps, M, fp8));
     };
     if (t->g != 64) t->g = pick(kGemmForward);
     if (t->g_bwd != 64) t->g_bwd = pick(kGemmBackward);

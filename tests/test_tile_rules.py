@@ -41,6 +41,16 @@ def test_tiles_of_the_epilogue_contractions(chosen, tall):
     check([(t["eq4"], o[1]) for t, o in rows])
 
 
+@pytest.mark.parametrize("M", [(8,), (16, 32), (64,)])
+@pytest.mark.parametrize("fp8", [False, True])
+def test_tiles_of_the_epilogue_contractions_by_type_and_width(chosen, fp8, M):
+    """Eqs. (1), (4) on tiles of 256 and 128 (M = 64: 256 x 128): no call more than 5 % above the better one, 2 % in total (two runs of one tile differ by 1 - 2 %)."""
+    rows = [(t, o) for c, t, o in chosen if c[0] == "step" and c[1] == str(int(fp8)) and int(c[2]) in M and c[5] == "1"]
+    big = lambda t: {e: t[e] for e in (256, 128) if e in t}
+    check([(big(t["eq1"]), o[0]) for t, o in rows if o[0] != 64], 1.05, 1.02)
+    check([(big(t["eq4"]), o[1]) for t, o in rows if "eq4" in t and o[1] != 64 and not o[4]], 1.05, 1.02)
+
+
 def test_tiles_of_the_plain_contractions(chosen):
     rows = [(t["bf16"], o[0]) for c, t, o in chosen if c[0] == "plain"]
     check([(t, tile) for t, tile in rows if tile in t], 1.2)
