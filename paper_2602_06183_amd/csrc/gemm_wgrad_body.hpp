@@ -25,8 +25,8 @@ struct WTile {
     static constexpr int WVM = WVM_, WVN = WVN_, WM = WM_, NST = NST_, KW = KW_;
     static constexpr int NW = WVM * WVN, BM = WVM * WM, BN = WVN * 64, FM = WM / 32, FN = 2, THREADS = 64 * NW * KW;
     static_assert(KW == 1 || NW == 1, "a shared output tile belongs to single wavefronts");
-    // bf16 stage (64 tokens): BM / 2 compact rows x 32 tokens and a row of zeros, twice; G likewise in two halves; a private copy of the mask bytes per wavefront
-    static constexpr int kZero = BM / 2 * 64, kAHalf = kZero + 64, kABytes = 2 * kAHalf, kBHalf = BN * 64, kBBytes = 2 * kBHalf;
+    // bf16 stage (64 tokens): BM / 2 compact rows x 32 tokens and four rows of zeros, twice; G likewise in two halves; a private copy of the mask bytes per wavefront
+    static constexpr int kZero = BM / 2 * 64, kZeros = 256, kAHalf = kZero + kZeros, kABytes = 2 * kAHalf, kBHalf = BN * 64, kBBytes = 2 * kBHalf;
     static constexpr int kStage = kABytes + kBBytes + NW * 256;
     static constexpr int A_LD = BM / 32 / NW, B_LD = kBBytes / 1024 / NW, kLoads = 1 + 2 * A_LD + B_LD;      // LDS-DMA loads per wavefront per stage
     // fp8 stage (64 tokens, one byte each): half of everything
@@ -35,6 +35,13 @@ struct WTile {
     static constexpr int BYTES = KW * NST * kStage > EPI ? KW * NST * kStage : EPI;
     static constexpr int BYTES8 = KW * NST * k8Stage > EPI ? KW * NST * k8Stage : EPI;
 };
+
+// Which of the four rows of zeros a lane reads for a hidden unit that is not kept.  A ds_read_b128 is served in phases of 16 lanes, and a phase is
+// lanes 0-3, 12-15, 20-27 of a half-wavefront or its other 16 (measured: two lanes' reads of one bank take longer exactly then): columns 0-3 or 4-7 of each of
+// four groups of hidden units.  A group's four kept rows lie in four different quarters of the banks at one 16-byte chunk, its kept columns below 4 from the
+// first quarter up, the others up to the last.  So with a unit that is not kept in columns 0-3 the last quarter is free in their phase, with one in columns
+// 4-7 the first.  (One row of zeros for all, at another group's chunk: 0.16 ms of 2.5 at T = D = 8192, F = 28672 went into bank conflicts.)
+__device__ __forceinline__ int zero_lane(int l32) { return (l32 & 4) ? 0 : 3 * 64; }
 
 // partial sums of KW wavefronts -> the first one, in ascending order; returns false for the wavefronts that are done
 template <class TL>
@@ -297,8 +304,8 @@ __device__ __forceinline__ void wgrad_vnm_body(unsigned char* __restrict__ smem,
     // a_off[a][0 / 1] = LDS address of its row (or of the zero row) for the even / odd 16-token sub-steps of a half-tile
     int a_off[FM][2], a_next[FM][2];
     const uint32_t col = l32 & 7, below = (1u << col) - 1u;
-    // the zero row is read at the chunk pair the lanes of the same 16-lane phase do not use for kept rows (no bank conflict)
-    const int zero_row = TL::kZero + ((lh ^ (l32 >> 3) ^ 2) << 4);
+    // a hidden unit that is not kept reads zeros, from the row that its half-group leaves free (zero_lane)
+    const int zero_row = TL::kZero + zero_lane(l32) + ((lh ^ (l32 >> 3)) << 4);
     uint32_t mk[FM];
     auto lookup_read = [&](int stage) {
         const unsigned char* sc = ring + stage * kStage + kABytes + kBBytes + wt * 256;
@@ -343,8 +350,9 @@ __device__ __forceinline__ void wgrad_vnm_body(unsigned char* __restrict__ smem,
     auto step_of = [&](int kt) { return KW == 1 ? kt : kg + kt * KW; };
     if (nk > 0) {
         // rows of zeros behind both half-tiles of every stage (never touched by the DMA)
-        for (int i = wt * 64 + lane; i < kStages * 2 * 16; i += TL::NW * 64)
-            *reinterpret_cast<uint32_t*>(ring + (i >> 5) * kStage + ((i >> 4) & 1) * kAHalf + TL::kZero + (i & 15) * 4) = 0u;
+        constexpr int ZW = TL::kZeros / 4;
+        for (int i = wt * 64 + lane; i < kStages * 2 * ZW; i += TL::NW * 64)
+            *reinterpret_cast<uint32_t*>(ring + i / (2 * ZW) * kStage + (i / ZW & 1) * kAHalf + TL::kZero + i % ZW * 4) = 0u;
 #pragma unroll
         for (int p = 0; p < kStages; ++p) issue(step_of(p < nk ? p : nk - 1), p, 0, kLoads);
         wait_vmcnt<(kStages - 1) * kLoads>();
@@ -496,7 +504,7 @@ __device__ __forceinline__ void wgrad_vnm_fp8_body(unsigned char* __restrict__ s
     }
     int a_off[FM], a_next[FM];
     const uint32_t col = l32 & 7, below = (1u << col) - 1u;
-    const int zero_row = TL::kZero + (((2 * lh) ^ (l32 >> 3) ^ 2) << 4);
+    const int zero_row = TL::kZero + zero_lane(l32) + (((2 * lh) ^ (l32 >> 3)) << 4);
     uint32_t mk[FM];
     auto lookup_read = [&](int stage) {
         const unsigned char* sc = ring + stage * kStage + k8A + k8B + wt * 256;
@@ -536,7 +544,8 @@ __device__ __forceinline__ void wgrad_vnm_fp8_body(unsigned char* __restrict__ s
     const int nk = KW == 1 ? K / 64 : (K / 64 - kg + KW - 1) / KW;                // 0 for an expert without tokens: its gradient is zero
     auto step_of = [&](int kt) { return KW == 1 ? kt : kg + kt * KW; };
     if (nk > 0) {
-        for (int i = wt * 64 + lane; i < kStages * 16; i += TL::NW * 64) *reinterpret_cast<uint32_t*>(ring + (i >> 4) * kStage + TL::kZero + (i & 15) * 4) = 0u;   // the rows of zeros
+        constexpr int ZW = TL::kZeros / 4;
+        for (int i = wt * 64 + lane; i < kStages * ZW; i += TL::NW * 64) *reinterpret_cast<uint32_t*>(ring + i / ZW * kStage + TL::kZero + i % ZW * 4) = 0u;   // the rows of zeros
 #pragma unroll
         for (int p = 0; p < kStages; ++p) issue(step_of(p < nk ? p : nk - 1), p, 0, kLoads);
         wait_vmcnt<(kStages - 1) * kLoads>();
