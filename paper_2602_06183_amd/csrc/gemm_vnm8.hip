@@ -13,6 +13,14 @@ bool vnm8_gemm_fp8_ok(int64_t T, int64_t N, int64_t F, int64_t ldw) {
            T * F < ((int64_t)1 << 38);
 }
 
+// The large tile as 512 tokens x 128 columns or 256 x 256: the same work, 7 % faster in the first form (3 % on codes), which rounds segments of tokens up
+// to more of them and columns to fewer; by the rounds of 256 workgroups that the call takes in either.  (8 experts of about 4100 tokens, D = 4096, F = 14336:
+// 9 rounds in both, 1443 us and 1646.)
+template <bool FP8>
+static bool long_tile(const Vnm8Args& a) {
+    return 0.93f * (float)((Vnm8Unit512<FP8>::count(a) + 255) / 256) <= (float)((Vnm8Unit256<FP8>::count(a) + 255) / 256);
+}
+
 template <bool FP8>
 static hipError_t launch_impl(Vnm8Args a, hipStream_t s, const GemmGroup* grp, int tile, const Split* split) {
     a.grp = grp ? *grp : GemmGroup();
@@ -20,7 +28,8 @@ static hipError_t launch_impl(Vnm8Args a, hipStream_t s, const GemmGroup* grp, i
     if (!tile) tile = pick_vnm8_tile(a.T, a.N, a.F / (FP8 ? 128 : 64), a.grp.n, FP8);
     if (split) a.split = *split;
     if (a.split.n > 1 && (a.grp.n || tile == 256)) return hipErrorInvalidValue;
-    return tile == 256 ? launch_units<Vnm8Unit256<FP8>>(s, a) : tile == 128 ? launch_units<Vnm8Unit128<FP8>>(s, a) : launch_units<Vnm8Unit64<FP8>>(s, a);
+    if (tile == 256) return long_tile<FP8>(a) ? launch_units<Vnm8Unit512<FP8>>(s, a) : launch_units<Vnm8Unit256<FP8>>(s, a);
+    return tile == 128 ? launch_units<Vnm8Unit128<FP8>>(s, a) : launch_units<Vnm8Unit64<FP8>>(s, a);
 }
 
 hipError_t launch_vnm8_gemm(const uint16_t* vcb, const uint8_t* mcb, const uint8_t* cixt, const uint16_t* Wk, int64_t ldw, int64_t T, int64_t N,

@@ -5,20 +5,22 @@
 // with the contraction index as row (W2.T for eq. (3), W1 as it is for eq. (7)).  The plain-2:4 route of gemm_v2.hip issues one
 // structured-sparse matrix instruction per 32 columns of F; this kernel issues one per 64, and fetches half the activation bytes.
 //
-// Tile: 256 tokens x 256 output columns, 8 wavefronts as 4 (token blocks) x 2 (column halves).  A 64-row tile (the
+// Tile: 512 tokens x 128 output columns, a wavefront for each of its 8 token blocks, or 256 x 256 with 4 (token blocks) x 2 (column halves) wavefronts.
+// What bounds both is the delivery of their operands to the CU (profiles/tile_kernels_70b_loop_parts.txt), and the first takes 34.25 KB per stage, the second
+// 41.25: the slab of Wk weighs four times the rest, and every token block uses half of it.  T = D = 8192, F = 28672: 1222 us, 1307 on 256 x 256; T = 8192,
+// D = 2048, F = 8192: 91, 100; on codes 687, 709 (gemm_vnm8.hip chooses).  A 64-row tile (the
 // gathered-row kernel of gemm_gather.hip, which fetches only the kept rows) halves the reuse of Wk and is bound by L2 -> LDS delivery at
-// M = 8; here the whole [64 f x 256 n] slab of Wk of a stage goes to LDS once for the tile's four token blocks, and each token block picks
+// M = 8; here the whole [64 f x columns] slab of Wk of a stage goes to LDS once for the tile's token blocks, and each token block picks
 // its kept rows when it READS its B fragments: ds_read_b64_tr_b16 takes one address per lane (inside a group of 16 lanes, lane s supplies 4
 // consecutive elements of row s / 4, lane l receives element l of those 4 rows), so the 4 rows of a read are the 4 kept hidden units of
-// one column block.  The 64-byte pieces of a slab row are XOR-swizzled by f % 8: the four rows of a read lie in one group of 8 rows and
-// therefore in four different pieces.
+// one column block.  The 64-byte pieces of a slab row are XOR-swizzled by f % 8 (128 columns: f % 4): the four rows of a read lie in one group of 8 rows.
 //
 // Operands as the fused epilogues of eqs. (1), (4) write them (common.hpp: vcb_off, mcb_off, cixt_off):
 //   values    [T / 32][F / 64][32 tokens][16 values]   1 KB per (32 tokens, 64 hidden units): one wave-wide LDS-DMA load
 //   metadata  [T / 64][F / 64][64 tokens][4 bytes]     the canonical nibbles of the 8 column blocks of a stage
 //   offsets   [F / 64][T / 64][8 words]                word (h, r), byte j = kept column r of column block 4 (j / 2) + j % 2 + 2 h of the
 //                                                      stage: the four rows that lane (h = lane / 32, r = (lane % 16) / 4) addresses in read j
-// A stage = 64 hidden units = 32 k' = one matrix instruction step per fragment pair; 3 stages of 41.25 KB.
+// A stage = 64 hidden units = 32 k' = one matrix instruction step per fragment pair; 3 stages.
 //
 // FP8 (the fp8 step): the same kernel on E4M3 codes with v_smfmac_f32_32x32x64_fp8_fp8, out = bf16(alpha * sum).  A stage is 128 hidden
 // units = 64 k' (the instruction's K): the slab is 128 rows x 256 bytes, the survivors' codes fill the same 32 bytes per token and stage,
@@ -33,13 +35,6 @@
 #include "lds_dma.hpp"
 #include "split.hpp"
 
-// Tile rows per band of the workgroup -> tile map (see SFFN_TILE_GROUP in common.hpp).  A tile fetches four times as many bytes of Wk as of
-// the packed activation, so the 32 tiles that an XCD runs at a time should share few column slabs of Wk: tall bands (measured at
-// T = D = 8192, F = 28672: 1.49 / 1.42 / 1.38 / 1.36 ms per launch with 2 / 4 / 8 / 16 tile rows per band).
-#ifndef SFFN_VNM8_GROUP
-#define SFFN_VNM8_GROUP 16
-#endif
-
 namespace sffn {
 
 // Workgroup tile: WT token blocks (64 tokens) x WH column groups, one wavefront each (64 tokens x 32 FN columns).  KW > 1 (with one wavefront
@@ -49,6 +44,10 @@ struct VTile {
     static constexpr int WT = WT_, WH = WH_, FN = FN_, NST = NST_, KW = KW_;
     static constexpr int NW = WT * WH, BT = 64 * WT, BN = 32 * FN * WH, THREADS = 64 * NW * KW;
     static_assert(KW == 1 || NW == 1, "a shared output tile belongs to single wavefronts");
+    // Tile rows per band of the workgroup -> tile map (see SFFN_TILE_GROUP in common.hpp).  A tile of 256 x 256 fetches four times as many bytes of Wk as of the
+    // packed activation, so the 32 tiles that an XCD runs at a time should share few column slabs of Wk: tall bands (T = D = 8192, F = 28672: 1.49 / 1.42 /
+    // 1.38 / 1.36 ms per launch with 2 / 4 / 8 / 16 tile rows).  A tile of 512 x 128 fetches about as many of either (8 rows 1222 us, 16 rows 1233; on codes 687, 706).
+    static constexpr int BAND = BT == 512 ? 8 : 16;
 };
 template <bool FP8, class TL>
 struct G {
@@ -58,7 +57,8 @@ struct G {
     static constexpr int kB = SLAB * ROW;
     static constexpr int kA = TL::BT * 32;
     static constexpr int kMt = FP8 ? TL::BT * 8 : TL::BT * 4;
-    static constexpr int kC = 256;
+    static constexpr int kC = TL::WT * (FP8 ? 64 : 32) > 256 ? TL::WT * (FP8 ? 64 : 32) : 256;
+    static constexpr int C_PARTS = kC / 256;             // wave-wide loads of the offsets; every wavefront issues one of them
     static constexpr int kStage = kB + kA + kMt + kC;
     static constexpr int B_LD = kB / 1024 / TL::NW, A_LD = kA / 1024 / TL::NW, M_LD = (kMt / 256 + TL::NW - 1) / TL::NW;    // loads per wave and stage
     static constexpr int LOADS = B_LD + A_LD + M_LD + 1;
@@ -114,7 +114,7 @@ __device__ __forceinline__ void vnm8_gemm_body(unsigned char* __restrict__ smem,
     }
     int tm, tn;
     {
-        constexpr int GROUP = SFFN_VNM8_GROUP;
+        constexpr int GROUP = TL::BAND;
         const int width = GROUP * tiles_n, group = L / width, first = group * GROUP;
         const int gsz = (tiles_m - first) < GROUP ? (tiles_m - first) : GROUP;
         tm = first + (L % width) % gsz;
@@ -159,9 +159,9 @@ __device__ __forceinline__ void vnm8_gemm_body(unsigned char* __restrict__ smem,
             m_base[i] = uniform64(FP8 ? mcb + (int64_t)g64 * KS * 512 + (mi & 1) * 256 : mcb + (int64_t)g64 * KS * 256);
         }
         m_lane = lane * 4;
-        // offsets of the tile's token blocks, 32 (FP8: 64) bytes each: every wave fetches all of them (four slots; unused ones repeat the last)
+        // offsets of the tile's token blocks, 32 (FP8: 64) bytes each: a load brings 256 bytes (slots past the tile's last block repeat it)
         const int words = FP8 ? 16 : 8;
-        int tb = FP8 ? (lane >> 4) : (l32 >> 3);
+        int tb = (wt % GG::C_PARTS * 64 + lane) / words;
         tb = (i0 >> 6) + (tb < TL::WT ? tb : TL::WT - 1);
         tb = tb < NTB ? tb : NTB - 1;
         c_base = uniform64(cixt);
@@ -184,7 +184,7 @@ __device__ __forceinline__ void vnm8_gemm_body(unsigned char* __restrict__ smem,
 #pragma unroll
         for (int i = 0; i < M_LD; ++i)
             if (B_LD + A_LD + i >= lo && B_LD + A_LD + i < hi) dma4(m_base[i], m_lane + (uint32_t)kt * m_kstep, sm + ((wt * M_LD + i) % (kMt / 256)) * 256);
-        if (kLoads - 1 >= lo && kLoads - 1 < hi) dma4(c_base, c_lane + (uint32_t)kt * c_kstep, sc);
+        if (kLoads - 1 >= lo && kLoads - 1 < hi) dma4(c_base, c_lane + (uint32_t)kt * c_kstep, sc + wt % GG::C_PARTS * 256);
     };
 
     // ---- per-lane LDS offsets of the fragment reads (inside a stage).  A wave owns one token block (64 tokens) x 32 FN output columns: the
@@ -375,6 +375,7 @@ struct Vnm8Unit {
     static unsigned count(const Args& a) { return vnm8_tiles(a.T, a.N, a.grp, TL::BT, TL::BN) * (unsigned)a.split.n; }
     static Args args(Args a) { a.tiles_m = (a.T + TL::BT - 1) / TL::BT; a.tiles_n = (a.N + TL::BN - 1) / TL::BN; return a; }
 };
+template <bool FP8> using Vnm8Unit512 = Vnm8Unit<FP8, VTile<8, 1, 4, 3, 1>>;
 template <bool FP8> using Vnm8Unit256 = Vnm8Unit<FP8, VTile<4, 2, 4, 3, 1>>;
 template <bool FP8> using Vnm8Unit128 = Vnm8Unit<FP8, VTile<2, 2, 2, 3, 1>>;
 template <bool FP8> using Vnm8Unit64 = Vnm8Unit<FP8, VTile<1, 1, 2, 3, 4>>;

@@ -174,3 +174,26 @@ def test_grouped_step_on_tiles_chosen_by_the_segments(fp8, M, D, F, seg):
         assert torch.equal(step.saved()["y2_meta"][a:b], alone.saved()["y2_meta"])
         for got, ref in ((Y3[a:b], want[0]), (dX[a:b], want[1])):
             assert (got.float() - ref.float()).norm() <= 2.0 ** -8 * ref.float().norm()
+
+
+@pytest.mark.parametrize("D,F", [(3904, 512), (3968, 640)])
+def test_step_on_tiles_of_512_tokens(D, F):
+    """Eqs. (3), (7) on 512 x 128 tiles: one token block in the last tile row; half a tile in the last column (D = 3904)."""
+    _teacher_forced_step_check(2112, D, F, sffn.MODE_HARD, seed=26)
+
+
+def test_fp8_step_on_tiles_of_512_tokens():
+    T, D, F = 2112, 3968, 512
+    inp = make_ffn_inputs(T, D, F, seed=27)
+    sc = _fp8_step_scales(inp)
+    dev = {k: to_dev(v) for k, v in inp.items()}
+    step = sffn.FfnStepFp8(T, D, F, sc, sffn.MODE_HARD, keep_dense=True, wgrad_fp8=True)
+    outs = step(dev["X"], dev["W1"], dev["W2"], dev["b1"], dev["dY"])
+    s = {k: to_bits(v) if v.dtype == torch.bfloat16 else v.cpu().numpy() for k, v in step.saved().items()}
+    _check_fp8_step_against_oracle(inp, sc, s, {k: to_bits(v) for k, v in zip(("Y3", "dX", "dW1", "dW2"), outs)}, sffn.MODE_HARD, True, 8)
+
+
+@pytest.mark.parametrize("fp8,D,F", [(False, 3904, 8256), (True, 3968, 8320)])
+def test_grouped_step_on_tiles_of_512_tokens(fp8, D, F):
+    """Experts of 2, 0, 10 and 23 token blocks (F: eq. (1) of an expert alone takes no 64 tile, which would sum in another order)."""
+    test_grouped_step_on_tiles_chosen_by_the_segments(fp8, 8, D, F, [0, 128, 128, 768, 2240])
