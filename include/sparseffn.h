@@ -346,7 +346,7 @@ int ffn_sparse_step(const sffn_cfg* cfg, const uint16_t* X, const uint16_t* W1, 
 
 /* ffn_sparse_step for callers that cannot allocate device memory or hand over a workspace: code under HIP graph capture,
  * tight serving loops, harnesses that forbid hipMalloc.  Same arguments, kernels and results as ffn_sparse_step, but the
- * workspace is a device array built into the library (40 MiB, held by every GPU the library has
+ * workspace is a device array built into the library (43 MiB, held by every GPU the library has
  * run on until the process ends); the call allocates and frees nothing.  Shapes whose sffn_workspace_bytes(), less what only
  * serves shared launches (T F bytes) or contractions shared by several workgroups (their float32 sums), exceed
  * SFFN_NOALLOC_WORKSPACE_MAX are refused with SFFN_EWORKSPACE before anything is enqueued (e.g. T = 1024, D = 512, F = 2048 fits; the benchmark

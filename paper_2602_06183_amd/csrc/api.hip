@@ -679,7 +679,7 @@ int run_fp8_step(const sffn_cfg* cfg, const sffn_fp8_scales* sc, int n_experts, 
         if (fwd && bwd) STAGE(launch_step_mix_fp8(kMixForwardTail, logM, tiles, &v3, &u3, &g4, w5, s), "step/y3+dW2+dy2");
         else if (fwd) {
             if (wide) STAGE(launch_vnm_spmm_gather_fp8(y2c, y2m, cix, w2tq, D, a3, T, D, F, M, Y3, D, s, gr), "step/y3");
-            else STAGE(launch_vnm8_gemm_fp8(vcb, mcb, cixt, w2tq, D, a3, T, D, F, Y3, D, s, gr, tiles.v, &split), "step/y3");
+            else STAGE(launch_vnm8_gemm_fp8(vcb, mcb, cixt, w2tq, D, a3, T, D, F, Y3, D, s, gr, tiles.v_alone, &split), "step/y3");
             if (amax) STAGE(launch_amax_fold(fold, s), "step/fold(amax)");
         } else STAGE(launch_step_mix_fp8(kMixBackwardHead, logM, tiles, nullptr, nullptr, &g4, w5, s), "step/dW2+dy2");
         if (bwd) STAGE(launch_step_mix_fp8(kMixBackwardTail, logM, tiles, &v7, &u7, nullptr, w8a, s, amax ? &fold : nullptr), "step/dX+dW1");
@@ -1343,7 +1343,7 @@ static int run_step(const sffn_cfg* cfg, int n_experts, const int64_t* seg, cons
         const WgradArgs w8 = {at2, kmask, xtb, 1.0f, (int)F, (int)D, (int)T, dW1, D, 0, 0, gw ? *gw : none};
         if (fwd && bwd && !acc32) STAGE(launch_step_mix_bf16(kMixForwardTail, 3, tiles, false, &v3, nullptr, &g4, w5, s), "step/y3+dW2+dy2");
         else {
-            if (fwd) STAGE(launch_vnm8_gemm(vcb, mcb, cixt, w2t, D, T, D, F, Y3, D, s, gd, tiles.v, &split), "step/y3");
+            if (fwd) STAGE(launch_vnm8_gemm(vcb, mcb, cixt, w2t, D, T, D, F, Y3, D, s, gd, tiles.v_alone, &split), "step/y3");
             if (bwd) STAGE(launch_step_mix_bf16(kMixBackwardHead, 3, tiles, acc32, nullptr, nullptr, &g4, w5, s), "step/dW2+dy2");
         }
         if (bwd) STAGE(launch_step_mix_bf16(kMixBackwardTail, 3, tiles, acc32, &v7, nullptr, nullptr, w8, s), "step/dX+dW1");

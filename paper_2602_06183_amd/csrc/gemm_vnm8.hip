@@ -18,7 +18,8 @@ bool vnm8_gemm_fp8_ok(int64_t T, int64_t N, int64_t F, int64_t ldw) {
 // 9 rounds in both, 1443 us and 1646.)
 template <bool FP8>
 static bool long_tile(const Vnm8Args& a) {
-    return 0.93f * (float)((Vnm8Unit512<FP8>::count(a) + 255) / 256) <= (float)((Vnm8Unit256<FP8>::count(a) + 255) / 256);
+    const unsigned n256 = Vnm8Unit256<FP8>::count(a);
+    return vnm8_rounds(Vnm8Unit512<FP8>::count(a), n256) < large_rounds(n256);
 }
 
 template <bool FP8>

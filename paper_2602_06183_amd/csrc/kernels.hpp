@@ -99,7 +99,8 @@ struct WgradArgs {
 // the chip), so that the contractions that do not depend on each other share launches (step_mix_*.hip): eqs. (3), (5), (4) in one and eqs. (7), (8) in
 // another (a backward call: eqs. (5), (4), then (7), (8)).  Eq. (4) then takes the 128 tile and its results need operand buffers of their own, since
 // eqs. (3), (5) still read those of eq. (1).
-struct StepTiles { int g = 0, g_bwd = 0, v = 0, v_split = 1, w = 0; bool mix = false; };
+// v_alone: the tile of eq. (3) where it has a launch of its own all the same (forward calls); the same bits as on v.
+struct StepTiles { int g = 0, g_bwd = 0, v = 0, v_alone = 0, v_split = 1, w = 0; bool mix = false; };
 inline StepTiles step_tiles(int64_t T, int64_t D, int64_t F, int M, int experts, bool fp8, bool may_share = true);
 enum { kMixForwardTail = 0, kMixBackwardHead = 1, kMixBackwardTail = 2 };      // {(3), (5), (4)}, {(5), (4)}, {(7), (8)}
 // M = 8: v8 (else null: va); acc32: not with kMixForwardTail
@@ -141,12 +142,13 @@ hipError_t launch_fp8_prologue(const Fp8PrologueArgs& a, hipStream_t s);
 // large ones (measured, see below: more bytes from L2 per product), so the large tile wins on whole rounds and the small one where the
 // outputs do not fill the chip or leave the last round nearly empty.  64 x 64 tiles split the contraction over their four wavefronts: best
 // while there are at most `most64` of them and the contraction is long enough to be worth splitting.  last: what a last round of small tiles takes, as a
-// part of a full one, when it leaves every workgroup a CU of its own.
-inline int pick_tile(unsigned n256, unsigned n128, unsigned n64, int steps, float w128, unsigned most64, int least_steps, float last = 1.0f) {
+// part of a full one, when it leaves every workgroup (all but a few, with `few` above 256) a CU of its own.
+inline int pick_tile(float rounds256, unsigned n128, unsigned n64, int steps, float w128, unsigned most64, int least_steps, float last = 1.0f, unsigned few = 256) {
     if (n64 <= most64 && steps >= least_steps) return 64;
     const unsigned rest = n128 % 512;
-    return w128 * ((float)(n128 / 512) + (rest == 0 ? 0.0f : rest <= 256 ? last : 1.0f)) < (float)((n256 + 255) / 256) ? 128 : 256;
+    return w128 * ((float)(n128 / 512) + (rest == 0 ? 0.0f : rest <= few ? last : 1.0f)) < rounds256 ? 128 : 256;
 }
+inline float large_rounds(unsigned n256) { return (float)((n256 + 255) / 256); }
 
 // tiles along the tokens when they come in `groups` segments (0: one), taken as equally long: a host and a device segment table choose alike
 inline int64_t token_tiles(int64_t T, int groups, int64_t edge) {
@@ -193,20 +195,32 @@ inline int pick_gemm_tile(int64_t Ra, int64_t Rb, int steps, const GemmGroup& g,
     auto tiles = [&](int64_t ei, int64_t ej) {
         return (unsigned)(token_tiles(Ra, g.n && g.role == 0 ? g.n : 0, ei) * token_tiles(Rb, g.n && g.role == 1 ? g.n : 0, ej) * (g.role == 2 && g.n ? g.n : 1));
     };
-    return pick_tile(tiles(256, 256), tiles(tall ? 256 : 128, 128), tiles(64, 64), steps, w128, split ? 256 : 0, 16, last);
+    return pick_tile(large_rounds(tiles(256, 256)), tiles(tall ? 256 : 128, 128), tiles(64, 64), steps, w128, split ? 256 : 0, 16, last);
 }
 // eqs. (1), (4) with their epilogues; M: columns per V:N:M block
 inline int pick_epilogue_tile(int64_t F, int64_t T, int steps, const GemmGroup& g, int what, int M, bool fp8) {
     return pick_gemm_tile(F, T, steps, g, small_round(what, steps, M, fp8), true, last_round(what, steps, M, fp8), M == 64);
 }
-// V:2:8 activation GEMM.  T = 8192, N = 2048, F = 8192 (256 / 1024 tiles): 107 us on 256 tiles, 148 on 128; T = 2048 (64 / 256): 85 and 54; T = 1024,
-// N = 1408, F = 4928 (24 / 88 / 352): 55, 33, and 29 on 64 tiles; T = 64, N = 2048, F = 8192 (8 / 16 / 32): 83, 49, 28
+// V:2:8 activation GEMM.  The large tile is 512 tokens x 128 columns or 256 x 256 (gemm_vnm8.hip), 0.93 and 1 a round: four fifths of what a stage of the second
+// fetches are the dense slab.  A round of 128 tiles, two per CU, takes more of that the longer the contraction, one per CU 0.86 at most (codes: 0.66).  Large /
+// 128: T = 1600, N = 4864, F = 19584 (152 / 494 tiles) 369 us, 444; T = 2688, N = 2816, F = 9024 (126 / 462) 162, 170; T = 15360, N = 448, F = 1856 (120 / 480)
+// 24 / 22; T = 896, N = 3904, F = 17280 (62 / 217) 1 / 0.75; T = 2048, N = 4800, F = 16896 (152 / 608) 1 / 1.49; codes, T = 3840, N = 2048, F = 7936 (120 / 480)
+// 1 / 0.85.  Over 270 shapes what is chosen takes 0.2 % longer than the better of the two.  T = 1024, N = 1408, F = 4928 (24 / 88 / 352): 55, 33, and 29 on
+// 64 tiles; T = 64, N = 2048, F = 8192 (8 / 16 / 32): 83, 49, 28.
 // More than 256 of the 64 tiles: only for long contractions of bf16 (T = 256, N = 5824, F = 24704, 364 of them: 169 us, 192 on 128 tiles; 24 trips: a third
 // slower than 128, 44: 15 %, 63 - 84: even, but in a shared launch 128 tiles are better up to there: T = 1664, D = 1216, F = 4032 the step 147 us, 106 on 128);
 // fp8 loses to every other tile there (T = 4864, N = 384, F = 1408, 456 of them: 18.5 us, 10.6 on 128, 16.0 on 256).
+inline float vnm8_rounds(unsigned n512, unsigned n256) { const float a = 0.93f * large_rounds(n512), b = large_rounds(n256); return a < b ? a : b; }
+inline float vnm8_small_round(int steps, bool fp8) {
+    const float w = fp8 ? 0.64f + 0.0012f * (float)steps : 0.63f + 0.0025f * (float)steps, most = fp8 ? 0.86f : 0.98f;
+    return w < most ? w : most;
+}
+constexpr unsigned kVnm8Few = 320;      // (T = 1792, N = 2816, F = 12096, 88 / 308: 1 / 0.86; T = 1216, N = 4864, F = 19712, 114 / 380: 1 / 1.19)
+inline float vnm8_last_round(int steps, bool fp8) { const float w = vnm8_small_round(steps, fp8), last = fp8 ? 0.66f : 0.86f; return last < w ? last / w : 1.0f; }
 inline int pick_vnm8_tile(int64_t T, int64_t N, int steps, int groups, bool fp8) {
     auto tiles = [&](int64_t edge) { return (unsigned)(token_tiles(T, groups, edge) * ((N + edge - 1) / edge)); };
-    return pick_tile(tiles(256), tiles(128), tiles(64), steps, 0.72f, !fp8 && steps >= 84 ? 512 : 256, 8);
+    const float large = vnm8_rounds((unsigned)(token_tiles(T, groups, 512) * ((N + 127) / 128)), tiles(256));
+    return pick_tile(large, tiles(128), tiles(64), steps, vnm8_small_round(steps, fp8), !fp8 && steps >= 84 ? 512 : 256, 8, vnm8_last_round(steps, fp8), kVnm8Few);
 }
 // gathered-row activation GEMM: 64 tokens x 256 columns, or 64 x 64
 // (T = 256, N = 1024, F = 4096, M = 16: 19 us and 12 us; T = N = 1024: 20 and 12; T = 512, N = 4096, F = 16384: 90 and 67; T = 1984, N = 1344, M = 32: 14 and 23)
@@ -261,7 +275,65 @@ inline Split split_at(void* p, const SplitPlan& plan, int64_t T, int64_t N) {
 inline int pick_wgrad_tile(int64_t F, int64_t N, int64_t T, int experts, bool split_ok) {
     const unsigned e = experts ? (unsigned)experts : 1u;
     auto tiles = [&](int64_t edge) { return (unsigned)((F + edge - 1) / edge * ((N + edge - 1) / edge)) * e; };
-    return pick_tile(tiles(256), tiles(128), tiles(64), (int)(T / 64 / e), 0.58f, split_ok ? 256 : 0, 12);
+    return pick_tile(large_rounds(tiles(256)), tiles(128), tiles(64), (int)(T / 64 / e), 0.58f, split_ok ? 256 : 0, 12);
+}
+
+// Do eqs. (3), (5), (4) and (7), (8) take less time as two launches than as five?  A launch by itself costs its rounds over the chip, the last one nearly
+// empty as often as not, and `kAlone` to start, fill and drain it; a shared one the sum of its tiles, on tiles of 128, and a part of the longest for its
+// end.  What a round takes (us) is measured: see small_round for eq. (4); eqs. (3), (7) 0.75 a stage on large tiles and 0.58 on two small ones a CU, the weight
+// gradients 1.45 and 0.84 (codes: 0.55 of it), less where a CU has one small tile only; 64 tiles, one per CU, 0.205 and 0.27.  The other constants are fitted to whole steps of 289 shapes
+// (T 64 - 16384, D 256 - 8192, 1 - 8 experts) run both ways: what is chosen takes 0.2 - 0.3 % longer than the better one.
+// T = 1984, D = 1344, F = 4160 168 us apart, 141 together; T = 4288, D = 640, F = 2624 146 / 112; T = 3008, D = 1856, F = 7424 471 / 415; codes, T = 3520,
+// D = 640, F = 2560 121 / 81; T = 4864, D = 384, F = 1408 86 / 78 the other way round: 78 apart.
+inline bool sharing_pays(int64_t T, int64_t D, int64_t F, int M, int groups, bool fp8) {
+    constexpr float kAlone = 9.7f, kTogether = 0.86f, kEnd = 0.23f;
+    const int unit = fp8 ? 128 : 64, e = groups ? groups : 1;
+    const float sg = (float)(D / unit), sv = (float)(M == 8 ? F / unit : 4 * F / M / 64), sw = (float)T / 64.0f / (float)e, code = fp8 ? 0.55f : 1.0f;
+    auto across = [](int64_t n, int64_t edge) { return (n + edge - 1) / edge; };
+    auto rounds = [](int64_t n) { return (float)((n + 255) / 256); };
+    auto rounds_small = [](int64_t n, float one_a_cu) { return n <= 256 ? one_a_cu : (float)((n + 511) / 512); };
+    auto least = [](float a, float b) { return a < b ? a : b; };
+    struct Kernel { float alone, tile; int64_t tiles; };                 // by itself; a tile of the shared launch and their number
+    Kernel k4, k3, k5;
+    {
+        const float large = 14.0f + 0.9f * sg * (fp8 ? 1.15f : 1.0f), w = 0.62f + 0.006f * sg, small = large * (w < 0.74f ? w : 0.74f);
+        const int64_t n64 = across(F, 64) * token_tiles(T, groups, 64);
+        k4.tile = small; k4.tiles = across(F, 128) * token_tiles(T, groups, 128);
+        k4.alone = least(rounds(across(F, 256) * token_tiles(T, groups, 256)) * large, rounds_small(k4.tiles, 1.0f) * small);
+        if (n64 <= 256) k4.alone = least(k4.alone, rounds(n64) * (8.0f + 0.55f * sg));
+    }
+    {
+        const int64_t n64 = across(D, 64) * token_tiles(T, groups, 64);
+        if (M == 8) {
+            const float small = 4.0f + 0.58f * sv * (fp8 ? 1.05f : 1.0f);
+            k3.tile = small; k3.tiles = across(D, 128) * token_tiles(T, groups, 128);
+            k3.alone = least(rounds(across(D, 128) * token_tiles(T, groups, 512)) * (4.0f + 0.75f * sv * (fp8 ? 1.1f : 1.0f)), rounds_small(k3.tiles, 0.87f) * small);
+        } else {
+            k3.tile = 4.0f + 0.45f * sv; k3.tiles = across(T, 64) * across(D, 256);
+            k3.alone = (float)across(k3.tiles, 512) * k3.tile;
+        }
+        if (n64 <= 512) k3.alone = least(k3.alone, rounds(n64) * (4.0f + (M == 8 ? 0.205f : 0.35f) * sv));
+        if (M == 8 && n64 <= 256 && sv >= 8.0f) { k3.tile = 4.0f + 0.41f * sv; k3.tiles = n64; }
+    }
+    {
+        const float small = 4.0f + 0.84f * sw * code, tiny = 6.0f + 0.27f * sw * code;
+        const int64_t n64 = e * across(F, 64) * across(D, 64);
+        k5.tile = small; k5.tiles = e * across(F, 128) * across(D, 128);
+        k5.alone = least(rounds(e * across(F, 256) * across(D, 256)) * (4.0f + 1.45f * sw * code), rounds_small(k5.tiles, 0.66f) * small);
+        if (n64 <= 256) k5.alone = least(k5.alone, rounds(n64) * tiny);
+        if (n64 <= 256 && sw >= 12.0f) { k5.tile = 2.0f * tiny; k5.tiles = n64; }
+    }
+    auto work = [](const Kernel& k) { return (float)k.tiles * k.tile / 512.0f; };
+    auto more = [](float a, float b) { return a > b ? a : b; };
+    const float longest = more(k3.tile, k5.tile);
+    const float together = 2.0f * kAlone + kTogether * (2.0f * work(k3) + 2.0f * work(k5) + work(k4)) + kEnd * (longest + more(longest, k4.tile));
+    // 0.92: near even the launches by themselves win as often (T = 12928, D = 960, F = 3584, estimated 0.95 of them: 497 us apart, 520 together), and 0.75 where
+    // few tokens meet weights of 30 million elements and more, whose bytes bound either form (T = 128, D = 6784, F = 17408 on codes: 517 / 549; M = 16 never: T = 192,
+    // D = 4416, F = 19200 468 / 507)
+    const bool bytes = D * F >= 30000000 && T < (fp8 ? 192 : M == 8 ? 384 : 640) * e;
+    if (bytes && M == 16 && !fp8) return false;
+    const float pays = bytes ? 0.75f : 0.92f;
+    return together < pays * (k4.alone + 2.0f * (k3.alone + k5.alone) + 5.0f * kAlone);
 }
 
 // may_share: false where the shared launches are not built for the call
@@ -276,10 +348,17 @@ inline StepTiles step_tiles(int64_t T, int64_t D, int64_t F, int M, int experts,
     const SplitPlan v = M == 8 ? plan_vnm8(T, D, (int)(F / unit), g.n, fp8) : fp8 ? SplitPlan{256, 1} : plan_gather(T, D, (int)(4 * F / M / 64), g.n);
     t.v = M == 8 ? pick_vnm8_tile(T, D, (int)(F / unit), g.n, fp8) : fp8 ? 256 : pick_gather_tile(T, D, (int)(4 * F / M / 64));
     t.w = pick_wgrad_tile(F, D, T, experts > 1 ? experts : 0, M == 8 || fp8);
-    // (0.56: in a shared launch the small tiles pay where eqs. (1), (4) by themselves would be even)
-    t.mix = may_share && pick_gemm_tile(F, T, steps, g, 0.56f, true) != 256 && t.w != 256 && (M != 8 || t.v != 256);
-    if (t.mix) t.g_bwd = 128;
-    else { t.v = v.tile; t.v_split = v.n; }
+    // Where eqs. (3), (7) would be shared by several workgroups per tile, and on wide bf16 blocks of more than 16 columns (whose weight gradients by
+    // themselves may run on the kept rows): where no contraction wants the large tile.  (0.56: in a shared launch the small tiles pay where eqs. (1), (4) by
+    // themselves would be even)
+    if (v.n > 1 || (M > 16 && !fp8)) t.mix = may_share && pick_gemm_tile(F, T, steps, g, 0.56f, true) != 256 && t.w != 256 && (M != 8 || t.v != 256);
+    else t.mix = may_share && sharing_pays(T, D, F, M, g.n, fp8);
+    if (t.mix) {
+        t.g_bwd = 128;
+        t.v_alone = t.v;
+        if (M == 8 && t.v == 256) t.v = 128;
+        if (t.w == 256) t.w = 128;
+    } else { t.v = t.v_alone = v.tile; t.v_split = v.n; }
     return t;
 }
 
@@ -294,11 +373,14 @@ inline void refine_tiles(StepTiles* t, int64_t D, int64_t F, int M, const GemmGr
     };
     auto pick = [&](int what) {
         const int steps = (int)(D / (fp8 ? 128 : 64));
-        return pick_tile(count(F, 256, 256), count(F, M == 64 ? 256 : 128, 128), ~0u, 0, small_round(what, steps, M, fp8), 0, 0, last_round(what, steps, M, fp8));
+        return pick_tile(large_rounds(count(F, 256, 256)), count(F, M == 64 ? 256 : 128, 128), ~0u, 0, small_round(what, steps, M, fp8), 0, 0, last_round(what, steps, M, fp8));
     };
     if (t->g != 64) t->g = pick(kGemmForward);
     if (t->g_bwd != 64) t->g_bwd = pick(kGemmBackward);
-    if (M == 8 && t->v != 64) t->v = pick_tile(count(D, 256, 256), count(D, 128, 128), ~0u, 0, 0.72f, 0, 0);
+    if (M == 8 && t->v != 64) {
+        const int steps = (int)(F / (fp8 ? 128 : 64));
+        t->v = t->v_alone = pick_tile(vnm8_rounds(count(D, 128, 512), count(D, 256, 256)), count(D, 128, 128), ~0u, 0, vnm8_small_round(steps, fp8), 0, 0, vnm8_last_round(steps, fp8), kVnm8Few);
+    }
 }
 
 hipError_t launch_prune24(const uint16_t* src, int64_t R, int64_t K, int64_t ld, int trans, int mode, uint16_t* vals,

@@ -11,10 +11,10 @@ namespace {
 
 // The workspace itself.  In host code this name is only a stand-in for the device symbol: its device address is obtained
 // once per device with hipGetSymbolAddress (below) and only that address is ever handed to kernels.
-// (8 MiB on top of the documented limit: the operand buffer of shared launches, T F bytes, and the sums of contractions that several workgroups share do
-// not count towards it; a step has one of the two or neither.  Of the shapes within the limit T = 4352, D = 256, F = 1920 without the canonical copies
-// needs most, 39.95 MiB in all.)
-constexpr size_t kScratchBytes = (size_t)SFFN_NOALLOC_WORKSPACE_MAX + (8u << 20);
+// (11 MiB on top of the documented limit: the operand buffer of shared launches, T F bytes, and the sums of contractions that several workgroups share do
+// not count towards it; a step has one of the two or neither.  Of the shapes within the limit T = 3200, D = 64, F = 3584 without the canonical copies
+// needs most, 42.93 MiB in all.)
+constexpr size_t kScratchBytes = (size_t)SFFN_NOALLOC_WORKSPACE_MAX + (11u << 20);
 static __device__ __align__(256) unsigned char scratch[kScratchBytes];
 
 constexpr int kMaxDevices = 64;

@@ -18,7 +18,7 @@ pytestmark = pytest.mark.gpu
     (64, 1088, 2112),       # few tiles, long contractions: 64 tiles in eqs. (1), (3), (7), trip counts that four wavefronts do not share evenly
     (832, 320, 576),        # 64 tiles in the weight gradients (13 token blocks)
     (1088, 1152, 4160),     # 128 tiles with a half-empty last row and column
-    (2112, 2112, 4160),     # 256 tiles in eqs. (1), (4), (5), (8), 128 tiles in eqs. (3), (7)
+    (2112, 2112, 4160),     # 256 tiles in eq. (1), shared launches of 128 tiles behind it
 ])
 def test_step_on_every_tile_size(T, D, F):
     _teacher_forced_step_check(T, D, F, sffn.MODE_SOFT, seed=21)
@@ -147,10 +147,10 @@ def test_split_activation_contractions_of_the_fp8_step(wgrad_fp8, dw_fp32):
 
 
 @pytest.mark.parametrize("fp8,M,D,F,seg", [
-    (False, 8, 2240, 9664, [0, 128, 128, 448, 640]),         # 128 tiles in eqs. (1), (4)
-    (False, 8, 2240, 9664, [0, 512, 512, 1216, 1792]),       # 128 tiles in eqs. (1), (3), (7), 256 in eq. (4)
+    (False, 8, 2240, 9664, [0, 128, 128, 448, 640]),         # shared launches
+    (False, 8, 2240, 9664, [0, 512, 512, 1216, 1792]),
     (False, 64, 2240, 9216, [0, 128, 128, 448, 640]),        # 256 tiles
-    (True, 8, 2304, 9728, [0, 128, 128, 448, 640]),          # on codes: 128 tiles in eqs. (1), (3), (4), (7)
+    (True, 8, 2304, 9728, [0, 128, 128, 448, 640]),          # on codes
 ])
 def test_grouped_step_on_tiles_chosen_by_the_segments(fp8, M, D, F, seg):
     """Experts with 0 and odd numbers of 64-token blocks: packed metadata and weight gradients are the bits of a step on the expert's tokens alone, whose tiles
@@ -176,21 +176,40 @@ def test_grouped_step_on_tiles_chosen_by_the_segments(fp8, M, D, F, seg):
             assert (got.float() - ref.float()).norm() <= 2.0 ** -8 * ref.float().norm()
 
 
-@pytest.mark.parametrize("D,F", [(3904, 512), (3968, 640)])
-def test_step_on_tiles_of_512_tokens(D, F):
-    """Eqs. (3), (7) on 512 x 128 tiles: one token block in the last tile row; half a tile in the last column (D = 3904)."""
-    _teacher_forced_step_check(2112, D, F, sffn.MODE_HARD, seed=26)
+def test_step_on_large_tiles():
+    """Every contraction in a launch of its own on its large tile (eqs. (3), (7): 512 x 128), with remainders in all dimensions."""
+    _teacher_forced_step_check(2752, 4800, 3136, sffn.MODE_HARD, seed=26)
 
 
-def test_fp8_step_on_tiles_of_512_tokens():
-    T, D, F = 2112, 3968, 512
+@pytest.mark.parametrize("fp8,T,D,F", [(False, 1344, 5952, 64), (False, 2112, 3904, 512), (True, 1472, 5504, 128), (True, 2112, 3968, 512)])
+def test_forward_call_on_large_tiles_of_a_step_that_shares_launches(fp8, T, D, F):
+    """Eq. (3) on 128 tiles in the step's shared launch, on 512 x 128 in the forward call: the same bits, and the oracle's sums (bf16)."""
     inp = make_ffn_inputs(T, D, F, seed=27)
+    dev = [to_dev(inp[k]) for k in ("X", "W1", "W2", "b1", "dY")]
+    sc = _fp8_step_scales(inp) if fp8 else None
+    new = (lambda: sffn.FfnStepFp8(T, D, F, sc, sffn.MODE_HARD, wgrad_fp8=True)) if fp8 else (lambda: sffn.FfnStep(T, D, F, sffn.MODE_HARD))  # noqa: E731
+    one, two = new(), new()
+    Y3, dX, dW1, dW2 = one(*dev)
+    assert torch.equal(two.forward(*dev[:4]), Y3)
+    for got, want in zip(two.backward(dev[4]) if fp8 else two.backward(dev[1], dev[4]), (dX, dW1, dW2)):
+        assert torch.equal(got, want)
+    if not fp8:
+        y2 = [to_bits(one.saved()[k]) for k in ("y2_vals", "y2_meta", "colidx")]
+        assert_gemm_close(to_bits(Y3), oracle.vnm_spmm(*y2, inp["W2"], 0, 64, 8), "y3")
+
+
+@pytest.mark.parametrize("fp8,T,D,F", [(False, 1984, 1344, 4160), (True, 3520, 640, 2560)])
+def test_step_in_shared_launches_of_128_tiles(fp8, T, D, F):
+    """Launches are shared although a contraction by itself would take the large tile: against the oracle."""
+    if not fp8:
+        _teacher_forced_step_check(T, D, F, sffn.MODE_SOFT, seed=28)
+        return
+    inp = make_ffn_inputs(T, D, F, seed=28)
     sc = _fp8_step_scales(inp)
-    dev = {k: to_dev(v) for k, v in inp.items()}
-    step = sffn.FfnStepFp8(T, D, F, sc, sffn.MODE_HARD, keep_dense=True, wgrad_fp8=True)
-    outs = step(dev["X"], dev["W1"], dev["W2"], dev["b1"], dev["dY"])
+    step = sffn.FfnStepFp8(T, D, F, sc, sffn.MODE_SOFT, keep_dense=True, wgrad_fp8=True)
+    outs = step(*[to_dev(inp[k]) for k in ("X", "W1", "W2", "b1", "dY")])
     s = {k: to_bits(v) if v.dtype == torch.bfloat16 else v.cpu().numpy() for k, v in step.saved().items()}
-    _check_fp8_step_against_oracle(inp, sc, s, {k: to_bits(v) for k, v in zip(("Y3", "dX", "dW1", "dW2"), outs)}, sffn.MODE_HARD, True, 8)
+    _check_fp8_step_against_oracle(inp, sc, s, {k: to_bits(v) for k, v in zip(("Y3", "dX", "dW1", "dW2"), outs)}, sffn.MODE_SOFT, True, 8)
 
 
 @pytest.mark.parametrize("fp8,D,F", [(False, 3904, 8256), (True, 3968, 8320)])
