@@ -1203,12 +1203,15 @@ static int run_step(const sffn_cfg* cfg, int n_experts, const int64_t* seg, cons
         const bool together = tiles.mix || prologue_together(T, D, F, E);
         PrologueArgs part[3];
         split_prologue(pro, part);
-        if (together) STAGE(launch_step_prologue(pro, s), "step/prologue");
+        const bool x_as_is = fwd && !bwd && packed && forward_reads_x(tiles.g);
+        if (x_as_is) {}
+        else if (together) STAGE(launch_step_prologue(pro, s), "step/prologue");
         else if (fwd) STAGE(launch_step_prologue(part[0], s), "step/X.T+prune24(W1)");
         if (fwd) {
             VnmEpilogue ep;
             ep.mode = 5; ep.logM = logM; ep.store_dense = keep_dense; ep.vals = y2v; ep.meta = y2m; ep.colidx = cix; ep.kmask = kmask; ep.ykept = ykept; ep.at = atb; ep.at_kept = kept;
-            STAGE(launch_gemm_vnm_epilogue(w1vb, w1mb, xb, b1, F, T, D, y1, ep, s, gp, tiles.g), "step/y1+sqrelu_vnm_compress");         // eqs. (1), (2), Section 2.3
+            if (x_as_is) STAGE(launch_forward_packed(w1vb, w1mb, b1, F, y1, ep, {(int)T, (int)D, pro.t_layout, X, xtb, split.count}, s, gp, tiles.g), "step/X.T+y1+sqrelu_vnm_compress");
+            else STAGE(launch_gemm_vnm_epilogue(w1vb, w1mb, xb, b1, F, T, D, y1, ep, s, gp, tiles.g), "step/y1+sqrelu_vnm_compress");         // eqs. (1), (2), Section 2.3
         }
         VnmEpilogue ep4;
         ep4.mode = 6; ep4.logM = logM; ep4.store_dense = keep_dense; ep4.vals = dy1v; ep4.meta = y2m; ep4.colidx = cix; ep4.ykept = ykept; ep4.at = at2; ep4.at_kept = kept;
@@ -1322,13 +1325,16 @@ static int run_step(const sffn_cfg* cfg, int n_experts, const int64_t* seg, cons
     const bool together = tiles.mix || prologue_together(T, D, F, E);
     PrologueArgs part[3];
     split_prologue(pro, part);
-    if (together) STAGE(launch_step_prologue(pro, s), "step/prologue");
+    const bool x_as_is = fwd && !bwd && packed && forward_reads_x(tiles.g);
+    if (x_as_is) {}
+    else if (together) STAGE(launch_step_prologue(pro, s), "step/prologue");
     else if (fwd) STAGE(launch_step_prologue(part[0], s), "step/X.T+prune24(W1)");
     if (fwd) {   // eq. (1), then eq. (2) + V:N:M compression on the tile while it is still in LDS
         VnmEpilogue ep;
         ep.mode = 1; ep.store_dense = keep_dense; ep.vals = lean ? nullptr : y2v; ep.meta = y2m; ep.colidx = cix; ep.kmask = kmask; ep.ykept = ykept;
         ep.vcb = vcb; ep.mcb = mcb; ep.cixt = cixt; ep.at = atb;
-        STAGE(launch_gemm_vnm_epilogue(w1vb, w1mb, xb, b1, F, T, D, y1, ep, s, gp, tiles.g), "step/y1+sqrelu_vnm_compress");
+        if (x_as_is) STAGE(launch_forward_packed(w1vb, w1mb, b1, F, y1, ep, {(int)T, (int)D, 1, X, xtb, split.count}, s, gp, tiles.g), "step/X.T+y1+sqrelu_vnm_compress");
+        else STAGE(launch_gemm_vnm_epilogue(w1vb, w1mb, xb, b1, F, T, D, y1, ep, s, gp, tiles.g), "step/y1+sqrelu_vnm_compress");
     }
     // eq. (4), then eq. (6) on y2's kept slots
     VnmEpilogue ep4;

@@ -112,7 +112,8 @@ struct GemmV2Lds {
     static constexpr int BYTES = RING > EPI_LDS ? RING : EPI_LDS;
 };
 // pid / n_pid: this workgroup's id and the number of workgroups of the contraction (a launch may hold several contractions)
-template <bool SPARSE, bool OUT_I_CONTIG, int EPI, bool BLOCKED, bool FP8, class TL>
+// BROW: B row-major although A is blocked (the forward call on packed weights and few tokens: forward_packed.hip)
+template <bool SPARSE, bool OUT_I_CONTIG, int EPI, bool BLOCKED, bool FP8, class TL, bool BROW>
 __device__ __forceinline__ void gemm_nt_v2_body(unsigned char* __restrict__ smem, int pid, int n_pid,
                                                         const uint16_t* __restrict__ a_vals, const uint8_t* __restrict__ a_meta,
                                                         const uint16_t* __restrict__ B, const float* __restrict__ bias,
@@ -124,7 +125,7 @@ __device__ __forceinline__ void gemm_nt_v2_body(unsigned char* __restrict__ smem
     constexpr int LOGM = (GEN_F || GEN_B) ? (EPI & 15) : 3;
     static_assert(!(GEN_F || GEN_B) || (LOGM >= 4 && LOGM <= 6), "wide V:N:M blocks: M = 16, 32 or 64");
     static_assert(!FP8 || (SPARSE && (EPI == 0 || (BLOCKED && (EPI == 1 || EPI == 2 || GEN_F || GEN_B)))), "fp8 operands: structured-sparse kernel; the step's fused epilogues");
-    constexpr bool blocked = BLOCKED;       // operands in the blocked layout of common.hpp (fused step) or row-major (stand-alone entry points)
+    constexpr bool blocked = BLOCKED, blockedB = BLOCKED && !BROW;       // operands in the blocked layout of common.hpp (fused step) or row-major (stand-alone entry points)
     using C = Cfg<SPARSE, FP8, TL>;
     constexpr int BM = C::BM, BN = C::BN, WM = TL::WM, WN = 64, FM = WM / 32, FN = 2, NH = WM / 64, KW = TL::KW;
     static_assert(LOGM < 6 || WM == 128, "the two blocks of 64 columns that share a metadata byte belong to one wavefront");
@@ -197,7 +198,7 @@ __device__ __forceinline__ void gemm_nt_v2_body(unsigned char* __restrict__ smem
     constexpr int A_LD = C::A_LD, B_LD = C::B_LD, M_LD = C::M_LD;          // issues per wave and stage
     // Row-major operands of the sparse kernel: a B row's 64 k of a stage are one 128-byte line, fetched whole (8 rows per
     // load, tile [256][128 bytes], 16-byte chunks swizzled by (row / 2) % 8) rather than as two 64-byte halves.
-    constexpr bool lineB = SPARSE && !BLOCKED;
+    constexpr bool lineB = SPARSE && !blockedB;
     uint64_t a_base[A_LD], b_base[B_LD], m_base[M_LD > 0 ? M_LD : 1];     // wave-uniform byte addresses of kt = 0
     uint32_t a_lane, b_lane, b_lane1 = 0, m_lane;        // per-lane byte offsets (b_lane1: odd loads of the line layout)
     uint32_t a_kstep, b_kstep, m_kstep;                  // bytes per main-loop step
@@ -216,10 +217,10 @@ __device__ __forceinline__ void gemm_nt_v2_body(unsigned char* __restrict__ smem
             const int bk = wt * B_LD + n, h = SPARSE ? bk / (BN / 16) : 0;
             int gr = j0 + (bk % (BN / 16)) * 16; gr = gr < Rb ? gr : Rb - 16;
             if (lineB) { gr = j0 + bk * 8; gr = gr < Rb ? gr : Rb - 8; }
-            b_base[n] = uniform64(blocked ? B + (((int64_t)(gr >> 4) * KCb + h) << 9) : lineB ? B + (int64_t)gr * Kld : B + (int64_t)gr * Kld + h * 32);
+            b_base[n] = uniform64(blockedB ? B + (((int64_t)(gr >> 4) * KCb + h) << 9) : lineB ? B + (int64_t)gr * Kld : B + (int64_t)gr * Kld + h * 32);
         }
         a_lane = blocked ? (rb * 32 + c * 8) * 2 : (uint32_t)(rb * lda + c * 8) * 2;
-        b_lane = blocked ? (rb * 32 + c * 8) * 2 : (uint32_t)(rb * Kld + c * 8) * 2;
+        b_lane = blockedB ? (rb * 32 + c * 8) * 2 : (uint32_t)(rb * Kld + c * 8) * 2;
         if (lineB) {        // lane -> (row lane / 8 of the load's 8 rows, slot lane % 8); tile row = 8 * load + row, load parity = n % 2
             const int r8 = lane >> 3, slot = lane & 7;
             b_lane = (uint32_t)(r8 * Kld + ((slot ^ (r8 >> 1)) * 8)) * 2;
@@ -237,7 +238,7 @@ __device__ __forceinline__ void gemm_nt_v2_body(unsigned char* __restrict__ smem
                                       : blocked ? a_meta + ((int64_t)(gr >> 5) * (Kld / 64) << 8) : a_meta + (int64_t)gr * (Kld / 8));
         }
         a_kstep = blocked ? 1024 : 64;
-        b_kstep = blocked ? 1024 * (C::BK / 32) : C::BK * 2;
+        b_kstep = blockedB ? 1024 * (C::BK / 32) : C::BK * 2;
         m_kstep = (blocked && !FP8) ? 256 : C::META_ROW;
         if (FP8 && blocked) {       // fp8 metadata units of common.hpp (m8blk_off): 512 contiguous bytes per (32 rows, 128 k), row-major inside
             m_lane = lane * 4; m_kstep = 512;
@@ -975,12 +976,12 @@ inline unsigned grid_tiles(int64_t Ra, int64_t Rb, const GemmGroup& g, int BM, i
 }
 
 // one contraction as a unit that launch_units (launch_mix.hpp) puts into a launch, alone or with others
-template <bool SPARSE, bool OUT_I_CONTIG, int EPI, bool BLOCKED, bool FP8, class TL>
+template <bool SPARSE, bool OUT_I_CONTIG, int EPI, bool BLOCKED, bool FP8, class TL, bool BROW = false>
 struct GemmV2Unit {
     using Args = GemmV2Args;
     static constexpr int THREADS = TL::THREADS, LDS = GemmV2Lds<SPARSE, OUT_I_CONTIG, EPI, BLOCKED, FP8, TL>::BYTES;
     static __device__ __forceinline__ void run(unsigned char* smem, int pid, int n_pid, const Args& a) {
-        gemm_nt_v2_body<SPARSE, OUT_I_CONTIG, EPI, BLOCKED, FP8, TL>(smem, pid, n_pid, a.a_vals, a.a_meta, a.B, a.bias, a.Ra, a.Rb, a.K, a.out, a.ldo, a.tiles_m, a.tiles_n,
+        gemm_nt_v2_body<SPARSE, OUT_I_CONTIG, EPI, BLOCKED, FP8, TL, BROW>(smem, pid, n_pid, a.a_vals, a.a_meta, a.B, a.bias, a.Ra, a.Rb, a.K, a.out, a.ldo, a.tiles_m, a.tiles_n,
                                                                      a.ep, a.grp, a.alpha);
     }
     static unsigned count(const Args& a) { return grid_tiles(a.Ra, a.Rb, a.grp, TL::BM, TL::BN); }

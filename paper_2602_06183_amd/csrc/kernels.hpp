@@ -122,6 +122,14 @@ struct PrologueArgs {
     unsigned* counters;             // kSplitCounters of them are cleared, or null
 };
 hipError_t launch_step_prologue(const PrologueArgs& a, hipStream_t s);
+// Eq. (1) of a forward call on packed weights with X row-major, and X.T and the counters in the same launch (forward_packed.hip); tile 64 or 128.
+// Taken on both: what the row-major rows cost the loop (128-byte lines instead of 1 KB blocks) is less than a launch in front of it.  T = 64, D = 2048, F = 8192 (a
+// whole forward call) 28.9 us with the copy of X, 25.7 without; T = 1024 84.8 / 78.3; T = 4096, D = 256, F = 1024 22.1 / 18.4; T = 16384, D = 256, F = 1024, the
+// other end, 36.3 / 36.8; M = 64, T = 4096, D = 512, F = 2048 25.4 / 21.2.
+struct TransposeX { int T, D, t_layout; const uint16_t* X; uint16_t* xt; unsigned* counters; };
+hipError_t launch_forward_packed(const uint16_t* a_vals, const uint8_t* a_meta, const float* bias, int64_t F, uint16_t* out, const VnmEpilogue& ep, const TransposeX& x,
+                                 hipStream_t s, const GemmGroup* grp, int tile);
+inline bool forward_reads_x(int tile) { return tile != 256; }
 // The same for the fp8 step (prologue_fp8.hip).  t_codes: xt, dyt as codes instead of bf16.  Canonical codes / metadata (w1c, w1m, w2c, w2m) may be null.
 // amax_*: one float per workgroup of the part (fp8_parts: x and dy have as many), slots_*: the epilogues' slots, cleared by the parts over X / dY; null: not wanted.
 struct Fp8PrologueArgs {

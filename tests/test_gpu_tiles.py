@@ -216,3 +216,29 @@ def test_step_in_shared_launches_of_128_tiles(fp8, T, D, F):
 def test_grouped_step_on_tiles_of_512_tokens(fp8, D, F):
     """Experts of 2, 0, 10 and 23 token blocks (F: eq. (1) of an expert alone takes no 64 tile, which would sum in another order)."""
     test_grouped_step_on_tiles_chosen_by_the_segments(fp8, 8, D, F, [0, 128, 128, 768, 2240])
+
+
+@pytest.mark.parametrize("M,T,D,F,seg", [
+    (8, 64, 64, 64, None),          # the smallest
+    (8, 64, 1088, 2112, None),      # 64 tiles, a half-empty stage round of their four wavefronts
+    (8, 832, 320, 576, None),       # 128 tiles, half-empty in both dimensions
+    (8, 576, 320, 640, [0, 64, 64, 256, 576]),
+    (16, 64, 1088, 2048, None), (16, 832, 320, 1024, None), (32, 64, 2048, 1024, None), (32, 832, 320, 1024, None),
+    (64, 64, 1088, 3072, None), (64, 832, 320, 2048, None),                 # tiles of 128 and 256 hidden units
+    (64, 576, 320, 2048, [0, 64, 64, 256, 576]),
+])
+def test_forward_call_on_packed_weights_reads_x_as_it_is(M, T, D, F, seg):
+    """The same bits as the call that copies X into blocks, in Y3 and, through the backward call, in all gradients (X.T)."""
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(51)
+    randn = lambda *shape: torch.randn(shape, dtype=torch.bfloat16, device="cuda", generator=gen)  # noqa: E731
+    lead = (len(seg) - 1,) if seg else ()
+    X, dY, W1, W2 = randn(T, D), randn(T, D), randn(*lead, F, D).mul_(0.02), randn(*lead, D, F).mul_(0.02)
+    b1 = torch.full(lead + (F,), -0.5 * 0.02 * D ** 0.5, device="cuda")
+    new = (lambda: sffn.FfnStepGrouped(seg, D, F, M=M)) if seg else (lambda: sffn.FfnStep(T, D, F, M=M))  # noqa: E731
+    a, b = new(), new()
+    want = [a.forward(X, W1, W2, b1), *a.backward(W1, dY)]
+    b.forward(dY, W1, W2, b1)               # packs the weights; another X
+    got = [b.forward(X, W1, W2, b1, weights_packed=True), *b.backward(W1, dY)]
+    for g, w in zip(got, want):
+        assert torch.equal(g, w)
