@@ -30,7 +30,9 @@ WGRAD_WIDE = "WgradWideUnit<kept rows of V:N:M A, mfma_f32_32x32x16_bf16>"
 VNM8_GEMM = "Vnm8Unit<V:2:8 A, smfmac_f32_32x32x32_bf16>"
 GATHER_GEMM = "GatherUnit<gathered rows, smfmac_f32_32x32x32_bf16>"
 SHARED = "several units in one launch"
-ROUTER_GEMMS = ("router/y1c+sqrelu+2:4", "router/dy2c+dsqrelu", "router/y3", "router/dX", "router/dW2.T", "router/dW1")
+# the router's launches that hold contractions, and how many (some hold passes of other kinds too)
+ROUTER_GEMMS = {"router/y1c+sqrelu+2:4": 1, "router/dy2c+dsqrelu": 1, "router/y3": 1, "router/dX": 1, "router/dW2.T": 1, "router/dW1": 1,
+                "router/dy2c+dsqrelu+y3": 2, "router/dX+dW2": 1}
 
 
 def shared_parts(stage):
@@ -44,7 +46,7 @@ def algorithmic_flops(stage, T, D, F, M=8):
     tdf = float(T) * D * F
     act = 4.0 / M * tdf                                          # V:2:M activations: 2 of M survive (M = 8: a quarter)
     if stage.startswith("router/"):                              # neuron-level experts: every contraction covers 4 / M of the hidden units
-        return act if stage in ROUTER_GEMMS else None
+        return ROUTER_GEMMS[stage] * act if stage in ROUTER_GEMMS else None
     if shared_parts(stage):
         return sum(algorithmic_flops(p, T, D, F, M) for p in shared_parts(stage))
     return {"step/y1+sqrelu_vnm_compress": tdf, "step/dy2+dsqrelu_vnm": tdf, "step/y1": tdf, "step/dy2": tdf,   # 2:4 weights: half of K survives
@@ -60,7 +62,7 @@ def executed_flops(stage, T, D, F, M=8, gathered=True):
     """Flops the matrix cores are issued for (dense-equivalent of the instructions used)."""
     tdf = float(T) * D * F
     if stage.startswith("router/"):
-        return 8.0 / M * tdf if stage in ROUTER_GEMMS else None
+        return ROUTER_GEMMS[stage] * 8.0 / M * tdf if stage in ROUTER_GEMMS else None
     if shared_parts(stage):
         return sum(executed_flops(p, T, D, F, 8 if p in ("step/dW2", "step/dW1") else M, gathered) for p in shared_parts(stage))
     act = (8.0 / M * tdf) if gathered else 2 * tdf              # eqs. (3), (7): only the kept columns are contracted / all F as plain 2:4
@@ -72,7 +74,7 @@ def executed_flops(stage, T, D, F, M=8, gathered=True):
 KERNEL_OF_STAGE = {"step/y1+sqrelu_vnm_compress": SPARSE_GEMM, "step/dy2+dsqrelu_vnm": SPARSE_GEMM, "step/y1": SPARSE_GEMM, "step/dy2": SPARSE_GEMM,
                    "step/y3": SPARSE_GEMM, "step/dX": SPARSE_GEMM, "step/dW2": WGRAD, "step/dW1": WGRAD,
                    "router/y1c+sqrelu+2:4": SPARSE_GEMM, "router/dy2c+dsqrelu": SPARSE_GEMM, "router/y3": SPARSE_GEMM, "router/dX": SPARSE_GEMM,
-                   "router/dW2.T": DENSE_GEMM, "router/dW1": DENSE_GEMM}
+                   "router/dy2c+dsqrelu+y3": SPARSE_GEMM, "router/dX+dW2": SPARSE_GEMM, "router/dW2.T": DENSE_GEMM, "router/dW1": DENSE_GEMM}
 
 
 def main():

@@ -863,7 +863,8 @@ int venom_expert_matmul(const sffn_cfg* cfg, const int64_t* seg_offsets, const u
 namespace {
 struct RouterLayout {
     sffn_router_layout pub;
-    size_t xpt, xb, dypt, dyb, w1cvb, w1cmb, dw2t, w2cvb, w2cmb, at, avb, amb, w2e, w1et, total;
+    size_t xpt, xb, dypt, dyb, w1cvb, w1cmb, dw2t, w2cvb, w2cmb, at, avb, amb, w2e, w1et, at2, avb2, total;
+    bool share;         // router_shares(): eqs. (4) and (3) in one launch, preparing passes and the transpose of dW2 beside contractions
 };
 bool make_router_layout(const sffn_cfg* c, RouterLayout* L) {
     if (!c || c->T <= 0 || !mult64(c->D) || !mult64(c->F) || !vnm_ok(c->V, c->M)) return false;
@@ -883,6 +884,9 @@ bool make_router_layout(const sffn_cfg* c, RouterLayout* L) {
     L->avb = take(rows * Kc); L->amb = take(rows * Kc / 8);     // packed activation (y2, then dy1) in the blocked operand layout
     L->w2e = take(F * D * 2);                                    // per expert: its slice of W2 as [D, Kc], blocked (eq. (3))
     L->w1et = take(F * D * 2);                                   // per expert: its slice of W1.T as [D, Kc], blocked (eq. (7))
+    // eq. (4)'s survivors beside eq. (1)'s, where eq. (4) shares a launch with eq. (3) and goes before eq. (5)
+    L->share = router_shares(rows, D, F, (int)M);
+    L->at2 = take(L->share ? rows * Kc * 2 : 0); L->avb2 = take(L->share ? rows * Kc : 0);
     L->total = off; L->pub.total = off;
     return true;
 }
@@ -956,6 +960,8 @@ static int run_router_step(const sffn_cfg* cfg, const int64_t* seg_offsets, cons
     uint16_t* w2cvb = (uint16_t*)(ws + L.w2cvb); uint8_t* w2cmb = ws + L.w2cmb;
     uint16_t* at = (uint16_t*)(ws + L.at);
     uint16_t* avb = (uint16_t*)(ws + L.avb); uint8_t* amb = ws + L.amb;
+    uint16_t* at2 = L.share ? (uint16_t*)(ws + L.at2) : at;
+    uint16_t* avb2 = L.share ? (uint16_t*)(ws + L.avb2) : avb;
     uint16_t* w2e = (uint16_t*)(ws + L.w2e); uint16_t* w1et = (uint16_t*)(ws + L.w1et);
     // SFFN_FLAG_WEIGHTS_PACKED: the weights' preparation (all in the forward half) is skipped; the workspace still holds
     // what they wrote for the previous call (Section 3.4: weights are converted once per optimizer step)
@@ -979,36 +985,41 @@ static int run_router_step(const sffn_cfg* cfg, const int64_t* seg_offsets, cons
     if (bwd) { pro.dY = dY; pro.dyt = dypt; pro.dyb = dyb; }
     // one launch for small inputs, else each part right before its readers, as in the plain step
     const bool together = prologue_together(rows, D, F, 1);
-    RouterPrologueArgs p_w2 = pro, p_dy = pro;
+    RouterPrologueArgs p_w2 = pro, p_dy = pro, p_both = pro;
     p_w2.X = p_w2.dY = p_w2.W1 = nullptr; p_w2.colidx = nullptr; p_w2.tail.n = 0;
     p_dy.X = p_dy.W1 = p_dy.W2 = nullptr; p_dy.colidx = nullptr; p_dy.tail.n = 0;
+    p_both.X = p_both.W1 = nullptr; p_both.colidx = nullptr; p_both.tail.n = 0;
     if (!together) { pro.dY = nullptr; pro.W2 = nullptr; }
     if (together || fwd) STAGE(launch_router_prologue(pro, s), "router/prologue");
     // Inside a run every 64-row block keeps the same columns, so eqs. (3), (7) are plain grouped 2:4 contractions of the
-    // packed [rows, Kc] activation with the expert's own [D, Kc] slice of W2 / W1.T (256 x 256 tiles; gathering rows per
-    // 64-row block would re-read the same lines from every CU at once)
-    if (fwd) {
-        VnmEpilogue ep;
-        ep.mode = 3; ep.store_dense = 1; ep.vals = vals; ep.meta = meta; ep.perm = perm; ep.logM = logM; ep.v24 = avb; ep.m24 = amb; ep.at = at; ep.at_ld = rows;
-        STAGE(launch_gemm_vnm_epilogue(w1cvb, w1cmb, xb, b1, Kc, rows, D, y1c, ep, s, &g1), "router/y1c+sqrelu+2:4");    // eqs. (1), (2), Section 2.3
-    }
-    if (fwd && !packed && !together) STAGE(launch_router_prologue(p_w2, s), "router/prepare(W2)");
-    if (fwd) STAGE(launch_spmm_blocked(avb, amb, w2e, nullptr, rows, D, Kc, 0, Y3, D, s, &g0), "router/y3");                       // eq. (3)
+    // packed [rows, Kc] activation with the expert's own [D, Kc] slice of W2 / W1.T (gathering rows per 64-row block would re-read the same lines
+    // from every CU at once)
+    VnmEpilogue ep1, ep4;
+    ep1.mode = 3; ep1.store_dense = 1; ep1.vals = vals; ep1.meta = meta; ep1.perm = perm; ep1.logM = logM; ep1.v24 = avb; ep1.m24 = amb; ep1.at = at; ep1.at_ld = rows;
+    // eq. (4) at the expert's hidden units, then eq. (6) on y2's slots while the tile is in LDS; dy2c itself only on request
+    ep4.mode = 4; ep4.store_dense = (cfg->flags & SFFN_FLAG_KEEP_DENSE) ? 1 : 0; ep4.vals = dvals; ep4.meta = meta; ep4.ykept = y1c; ep4.v24 = avb2; ep4.at = at2; ep4.at_ld = rows;
+    GemmGroup g4 = g1;
+    g4.bias_stride = 0;
+    const VnmEpilogue plain;
+    const GemmV2Args c1 = {w1cvb, w1cmb, xb, b1, (int)Kc, (int)rows, (int)D, y1c, Kc, 0, 0, ep1, g1, 1.0f}, c4 = {w2cvb, w2cmb, dyb, nullptr, (int)Kc, (int)rows, (int)D, dy2c, Kc, 0, 0, ep4, g4, 1.0f};
+    const GemmV2Args c3 = {avb, amb, w2e, nullptr, (int)rows, (int)D, (int)Kc, Y3, D, 0, 0, plain, g0, 1.0f}, c7 = {avb2, amb, w1et, nullptr, (int)rows, (int)D, (int)Kc, dX, D, 0, 0, plain, g0, 1.0f};
+    const bool one_launch = L.share && fwd && bwd;      // eqs. (3), (4)
+    const bool behind = L.share && !together;           // preparing passes over W2 and dY behind the tiles of eq. (1)
+    if (fwd && behind) STAGE(launch_router_y1(c1, p_both, s), "router/y1c+sqrelu+2:4");                                            // eqs. (1), (2), Section 2.3
+    else if (fwd) STAGE(launch_gemm_vnm_epilogue(w1cvb, w1cmb, xb, b1, Kc, rows, D, y1c, ep1, s, &g1), "router/y1c+sqrelu+2:4");
+    if (fwd && !packed && !together && !behind) STAGE(launch_router_prologue(p_w2, s), "router/prepare(W2)");
+    if (fwd && !one_launch) STAGE(launch_spmm_blocked(avb, amb, w2e, nullptr, rows, D, Kc, 0, Y3, D, s, &g0), "router/y3");       // eq. (3)
     // ---- Alg. 2 ------------------------------------------------------------------------------------------------------
-    if (bwd && !together) STAGE(launch_router_prologue(p_dy, s), "router/dY[perm].T");
+    if (bwd && !together && !(fwd && behind)) STAGE(launch_router_prologue(p_dy, s), "router/dY[perm].T");
+    if (one_launch) STAGE(launch_router_dy2_y3(c4, c3, s), "router/dy2c+dsqrelu+y3");                                              // eqs. (4), (6) and (3)
     // eq. (5) is computed as dW2.T [F, D] (whole 2 D-byte rows per hidden unit) and transposed: writing dW2 [D, F] directly
     // would scatter 8-byte pieces M hidden units apart
     if (bwd) STAGE(launch_gemm_nt(0, at, nullptr, dypt, nullptr, Kc, D, rows, 0, dw2t, D, s, &g2), "router/dW2.T");                 // eq. (5)
-    if (bwd) STAGE(launch_transpose(dw2t, F, D, D, dW2, 0, nullptr, s), "router/dW2");
-    if (bwd) {   // eq. (4) at the expert's hidden units, then eq. (6) on y2's slots while the tile is in LDS; dy2c itself only on request
-        GemmGroup g4 = g1;
-        g4.bias_stride = 0;
-        VnmEpilogue ep;
-        ep.mode = 4; ep.store_dense = (cfg->flags & SFFN_FLAG_KEEP_DENSE) ? 1 : 0; ep.vals = dvals; ep.meta = meta; ep.ykept = y1c; ep.v24 = avb; ep.at = at; ep.at_ld = rows;
-        STAGE(launch_gemm_vnm_epilogue(w2cvb, w2cmb, dyb, nullptr, Kc, rows, D, dy2c, ep, s, &g4), "router/dy2c+dsqrelu");
-    }
-    if (bwd) STAGE(launch_spmm_blocked(avb, amb, w1et, nullptr, rows, D, Kc, 0, dX, D, s, &g0), "router/dX");                       // eq. (7)
-    if (bwd) STAGE(launch_gemm_nt(0, at, nullptr, xpt, nullptr, Kc, D, rows, 0, dW1, D, s, &g2), "router/dW1");                    // eq. (8)
+    if (bwd && !L.share) STAGE(launch_transpose(dw2t, F, D, D, dW2, 0, nullptr, s), "router/dW2");
+    if (bwd && !one_launch) STAGE(launch_gemm_vnm_epilogue(w2cvb, w2cmb, dyb, nullptr, Kc, rows, D, dy2c, ep4, s, &g4), "router/dy2c+dsqrelu");
+    if (bwd && L.share) STAGE(launch_router_dx(c7, dw2t, F, D, dW2, s), "router/dX+dW2");                                          // eq. (7), dW2.T -> dW2
+    else if (bwd) STAGE(launch_spmm_blocked(avb2, amb, w1et, nullptr, rows, D, Kc, 0, dX, D, s, &g0), "router/dX");                // eq. (7)
+    if (bwd) STAGE(launch_gemm_nt(0, at2, nullptr, xpt, nullptr, Kc, D, rows, 0, dW1, D, s, &g2), "router/dW1");                   // eq. (8)
     return SFFN_OK;
 }
 

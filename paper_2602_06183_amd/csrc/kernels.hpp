@@ -391,6 +391,22 @@ inline void refine_tiles(StepTiles* t, int64_t D, int64_t F, int M, const GemmGr
     }
 }
 
+// Does the router's step share launches?  Where eqs. (1), (4) and (3), (7) all run on 128 tiles.  Grouped by expert they have a few tiles more than fill the
+// chip, so that the last round of each is nearly empty: T = 8192, D = 2048, F = 8192, M = 16 (1056 tiles each, 512 at a time) eqs. (4) and (3) 90 + 68 us apart,
+// 137 together; eq. (7) and the transpose of dW2 72 + 12, 77; the step 542 / 522; T = 1792, D = 640, F = 1920, M = 8 110 / 94; T = 128, D = 704, F = 2560,
+// M = 16 90 / 78; 120 drawn calls 5.5 % faster together.  Up to 48 Mi elements of tokens and weights: the passes that ride along run two workgroups a CU, which
+// is less than their rate alone (T = 320, D = 4928, F = 21888, M = 8 811 us apart, 894 together).
+inline bool router_shares(int64_t rows, int64_t D, int64_t F, int M) {
+    if ((rows + F) * D > ((int64_t)48 << 20)) return false;
+    GemmGroup g;
+    g.n = M / 4; g.role = 1;
+    const int64_t Kc = 4 * F / M;
+    const int steps = (int)(D / 64), steps3 = (int)(Kc / 64);
+    if (pick_gemm_tile(Kc, rows, steps, g, small_round(kGemmRouter, steps), true, last_round(kGemmRouter, steps)) != 128) return false;
+    g.role = 0;
+    return pick_gemm_tile(rows, D, steps3, g, small_round(kGemmPlain, steps3), true, last_round(kGemmPlain, steps3)) == 128;
+}
+
 hipError_t launch_prune24(const uint16_t* src, int64_t R, int64_t K, int64_t ld, int trans, int mode, uint16_t* vals,
                           uint8_t* meta, hipStream_t stream);
 hipError_t launch_dsqrelu_vnm(const uint16_t* dy2, const uint16_t* y1, const uint8_t* meta, const uint8_t* colidx,
@@ -494,6 +510,11 @@ struct RouterPrologueArgs {
     GemmGroup seg;
 };
 hipError_t launch_router_prologue(const RouterPrologueArgs& a, hipStream_t s);
+// Shared launches of the router's step (router_mix.hip): eq. (1) with preparing passes that later launches read; eqs. (4) and (3); eq. (7) with the transpose of
+// dW2.T [F, D].  128 tiles.
+hipError_t launch_router_y1(const GemmV2Args& g1, const RouterPrologueArgs& p, hipStream_t s);
+hipError_t launch_router_dy2_y3(const GemmV2Args& g4, const GemmV2Args& g3, hipStream_t s);
+hipError_t launch_router_dx(const GemmV2Args& g7, const uint16_t* dw2t, int64_t F, int64_t D, uint16_t* dW2, hipStream_t s);
 hipError_t launch_venom_colidx(const GemmGroup& g, int64_t cap, int64_t groups, uint8_t* colidx, hipStream_t s);
 
 // fp8 operands (fp8.hip; Section 3.4's closing paragraph): E4M3 codes, inv = 1 / scale; amax (optional, device float) receives the largest

@@ -242,3 +242,25 @@ def test_forward_call_on_packed_weights_reads_x_as_it_is(M, T, D, F, seg):
     got = [b.forward(X, W1, W2, b1, weights_packed=True), *b.backward(W1, dY)]
     for g, w in zip(got, want):
         assert torch.equal(g, w)
+
+
+@pytest.mark.parametrize("M,T,D,F", [(8, 700, 2048, 12288), (16, 700, 2048, 12288), (32, 300, 2048, 12288), (64, 700, 2048, 12288), (16, 576, 448, 1280)])
+def test_router_step_in_shared_launches(M, T, D, F):
+    """Eqs. (3) and (4) in one launch, preparing passes behind eq. (1) (not in the last, smallest case), the transpose of dW2 behind eq. (7): the same bits as
+    the forward and backward calls, whose contractions have launches of their own, also with weights that are packed already; the smallest against the oracle."""
+    inp = make_router_inputs(T, D, F, M, seed=61)
+    dev = {k: to_dev(v) for k, v in inp.items()}
+    route = sffn.venom_route(dev["X"], dev["means"], M)
+    one, two = sffn.FfnRouterStep(T, D, F, M), sffn.FfnRouterStep(T, D, F, M)
+    want = [t.clone() for t in one(route, dev["X"], dev["W1"], dev["W2"], dev["b1"], dev["dY"])]
+    got = [two.forward(route, dev["X"], dev["W1"], dev["W2"], dev["b1"]), *two.backward(route, dev["dY"])]
+    for g, w in zip(got, want):
+        assert torch.equal(g, w)
+    for packed in (True, False):
+        for g, w in zip(one(route, dev["X"], dev["W1"], dev["W2"], dev["b1"], dev["dY"], weights_packed=packed), want):
+            assert torch.equal(g, w)
+    if F <= 1280:       # (5 %: the oracle's own run, in which near ties of the 2:4 choice may fall the other way)
+        ref = oracle.ffn_router_step_ref(inp["X"], inp["W1"], inp["W2"], inp["b1"], inp["dY"], inp["means"], M)
+        for name, g in zip(("y3", "dX", "dW1", "dW2"), want):
+            a, b = oracle.bits_to_f64(to_bits(g)), oracle.bits_to_f64(ref[name])
+            assert np.linalg.norm(a - b) <= 0.05 * np.linalg.norm(b), name
