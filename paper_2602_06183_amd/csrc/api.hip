@@ -1108,6 +1108,11 @@ int ffn_router_full_backward(const sffn_cfg* cfg, const uint16_t* dY, uint16_t* 
     return run_router_full(cfg, nullptr, nullptr, nullptr, nullptr, nullptr, dY, nullptr, dX, dW1, dW2, workspace, ws_bytes, stream, 2);
 }
 
+// eq. (1) on X as it is: what it reads itself stays in front of it, the rest goes behind its tiles
+static inline void split_off_eq1(PrologueArgs* front, PrologueArgs* behind) {
+    behind->W1 = nullptr; behind->xb = nullptr;
+    front->X = front->dY = front->W2 = nullptr; front->counters = nullptr;
+}
 static inline void split_prologue(const PrologueArgs& all, PrologueArgs (&part)[3]) {
     part[0] = part[1] = part[2] = all;
     part[0].W2 = nullptr; part[0].dY = nullptr;
@@ -1214,14 +1219,15 @@ static int run_step(const sffn_cfg* cfg, int n_experts, const int64_t* seg, cons
         const bool together = tiles.mix || prologue_together(T, D, F, E);
         PrologueArgs part[3];
         split_prologue(pro, part);
-        const bool x_as_is = fwd && !bwd && packed && forward_reads_x(tiles.g);
-        if (x_as_is) {}
-        else if (together) STAGE(launch_step_prologue(pro, s), "step/prologue");
-        else if (fwd) STAGE(launch_step_prologue(part[0], s), "step/X.T+prune24(W1)");
+        const bool x_as_is = fwd && forward_reads_x(T, D, E * F, packed, tiles.g);
+        PrologueArgs behind = together ? pro : part[0];
+        if (x_as_is) split_off_eq1(&pro, &behind);
+        if (together) STAGE(launch_step_prologue(pro, s), "step/prologue");
+        else if (fwd && !x_as_is) STAGE(launch_step_prologue(part[0], s), "step/X.T+prune24(W1)");
         if (fwd) {
             VnmEpilogue ep;
             ep.mode = 5; ep.logM = logM; ep.store_dense = keep_dense; ep.vals = y2v; ep.meta = y2m; ep.colidx = cix; ep.kmask = kmask; ep.ykept = ykept; ep.at = atb; ep.at_kept = kept;
-            if (x_as_is) STAGE(launch_forward_packed(w1vb, w1mb, b1, F, y1, ep, {(int)T, (int)D, pro.t_layout, X, xtb, split.count}, s, gp, tiles.g), "step/X.T+y1+sqrelu_vnm_compress");
+            if (x_as_is) STAGE(launch_forward_x(w1vb, w1mb, b1, X, y1, ep, behind, s, gp, tiles.g), "step/y1+sqrelu_vnm_compress");
             else STAGE(launch_gemm_vnm_epilogue(w1vb, w1mb, xb, b1, F, T, D, y1, ep, s, gp, tiles.g), "step/y1+sqrelu_vnm_compress");         // eqs. (1), (2), Section 2.3
         }
         VnmEpilogue ep4;
@@ -1336,15 +1342,16 @@ static int run_step(const sffn_cfg* cfg, int n_experts, const int64_t* seg, cons
     const bool together = tiles.mix || prologue_together(T, D, F, E);
     PrologueArgs part[3];
     split_prologue(pro, part);
-    const bool x_as_is = fwd && !bwd && packed && forward_reads_x(tiles.g);
-    if (x_as_is) {}
-    else if (together) STAGE(launch_step_prologue(pro, s), "step/prologue");
-    else if (fwd) STAGE(launch_step_prologue(part[0], s), "step/X.T+prune24(W1)");
+    const bool x_as_is = fwd && forward_reads_x(T, D, E * F, packed, tiles.g);
+    PrologueArgs behind = together ? pro : part[0];
+    if (x_as_is) split_off_eq1(&pro, &behind);
+    if (together) STAGE(launch_step_prologue(pro, s), "step/prologue");
+    else if (fwd && !x_as_is) STAGE(launch_step_prologue(part[0], s), "step/X.T+prune24(W1)");
     if (fwd) {   // eq. (1), then eq. (2) + V:N:M compression on the tile while it is still in LDS
         VnmEpilogue ep;
         ep.mode = 1; ep.store_dense = keep_dense; ep.vals = lean ? nullptr : y2v; ep.meta = y2m; ep.colidx = cix; ep.kmask = kmask; ep.ykept = ykept;
         ep.vcb = vcb; ep.mcb = mcb; ep.cixt = cixt; ep.at = atb;
-        if (x_as_is) STAGE(launch_forward_packed(w1vb, w1mb, b1, F, y1, ep, {(int)T, (int)D, 1, X, xtb, split.count}, s, gp, tiles.g), "step/X.T+y1+sqrelu_vnm_compress");
+        if (x_as_is) STAGE(launch_forward_x(w1vb, w1mb, b1, X, y1, ep, behind, s, gp, tiles.g), "step/y1+sqrelu_vnm_compress");
         else STAGE(launch_gemm_vnm_epilogue(w1vb, w1mb, xb, b1, F, T, D, y1, ep, s, gp, tiles.g), "step/y1+sqrelu_vnm_compress");
     }
     // eq. (4), then eq. (6) on y2's kept slots

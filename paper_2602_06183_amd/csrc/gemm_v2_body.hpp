@@ -112,7 +112,7 @@ struct GemmV2Lds {
     static constexpr int BYTES = RING > EPI_LDS ? RING : EPI_LDS;
 };
 // pid / n_pid: this workgroup's id and the number of workgroups of the contraction (a launch may hold several contractions)
-// BROW: B row-major although A is blocked (the forward call on packed weights and few tokens: forward_packed.hip)
+// BROW: B row-major although A is blocked (forward_x.hip)
 template <bool SPARSE, bool OUT_I_CONTIG, int EPI, bool BLOCKED, bool FP8, class TL, bool BROW>
 __device__ __forceinline__ void gemm_nt_v2_body(unsigned char* __restrict__ smem, int pid, int n_pid,
                                                         const uint16_t* __restrict__ a_vals, const uint8_t* __restrict__ a_meta,

@@ -122,14 +122,16 @@ struct PrologueArgs {
     unsigned* counters;             // kSplitCounters of them are cleared, or null
 };
 hipError_t launch_step_prologue(const PrologueArgs& a, hipStream_t s);
-// Eq. (1) of a forward call on packed weights with X row-major, and X.T and the counters in the same launch (forward_packed.hip); tile 64 or 128.
+// Eq. (1) with X row-major and the passes `behind` in the same launch (forward_x.hip); tile 64 or 128.
+hipError_t launch_forward_x(const uint16_t* a_vals, const uint8_t* a_meta, const float* bias, const uint16_t* X, uint16_t* out, const VnmEpilogue& ep,
+                            const PrologueArgs& behind, hipStream_t s, const GemmGroup* grp, int tile);
 // Taken on both: what the row-major rows cost the loop (128-byte lines instead of 1 KB blocks) is less than a launch in front of it.  T = 64, D = 2048, F = 8192 (a
-// whole forward call) 28.9 us with the copy of X, 25.7 without; T = 1024 84.8 / 78.3; T = 4096, D = 256, F = 1024 22.1 / 18.4; T = 16384, D = 256, F = 1024, the
-// other end, 36.3 / 36.8; M = 64, T = 4096, D = 512, F = 2048 25.4 / 21.2.
-struct TransposeX { int T, D, t_layout; const uint16_t* X; uint16_t* xt; unsigned* counters; };
-hipError_t launch_forward_packed(const uint16_t* a_vals, const uint8_t* a_meta, const float* bias, int64_t F, uint16_t* out, const VnmEpilogue& ep, const TransposeX& x,
-                                 hipStream_t s, const GemmGroup* grp, int tile);
-inline bool forward_reads_x(int tile) { return tile != 256; }
+// forward call on packed weights) 28.9 us with the copy of X, 25.7 without; T = 1024 84.8 / 78.3; T = 4096, D = 256, F = 1024 22.1 / 18.4; T = 16384, D = 256,
+// F = 1024, the other end, 36.3 / 36.8; M = 64, T = 4096, D = 512, F = 2048 25.4 / 21.2.
+// With weights to prune up to 6 Mi elements of tokens and weights, 3.5 Mi on 64 tiles: behind the tiles the pass over W2 runs two workgroups a CU (64 tiles: one),
+// which is less than its rate alone.  A whole step: T = 512, D = 448, F = 1728 38 / 35 us; T = 64, D = 768, F = 2880 44 / 41; T = 128, D = 1088, F = 4096, M = 64
+// 61 / 64; T = 128, D = 1216, F = 5120, M = 16 53 / 58; T = 128, D = 1856, F = 6080 86 / 98.
+inline bool forward_reads_x(int64_t T, int64_t D, int64_t F, bool packed, int tile) { return tile != 256 && (packed || (T + F) * D <= ((int64_t)(tile == 64 ? 7 : 12) << 19)); }
 // The same for the fp8 step (prologue_fp8.hip).  t_codes: xt, dyt as codes instead of bf16.  Canonical codes / metadata (w1c, w1m, w2c, w2m) may be null.
 // amax_*: one float per workgroup of the part (fp8_parts: x and dy have as many), slots_*: the epilogues' slots, cleared by the parts over X / dY; null: not wanted.
 struct Fp8PrologueArgs {
