@@ -32,7 +32,8 @@ struct Tile {
     static constexpr int NW = WVM * WVN, BM = WVM * WM, BN = WVN * 64, THREADS = 64 * NW * KW;
     static_assert(KW == 1 || NW == 1, "a shared output tile belongs to single wavefronts");
 };
-template <bool SPARSE, bool FP8, class TL>
+// MG: row-major 2:4 metadata fetched for four stages at a time, into two buffers behind the ring (see issue())
+template <bool SPARSE, bool FP8, class TL, bool MG = false>
 struct Cfg {
     static constexpr int BM = TL::BM, BN = TL::BN;
     static constexpr int BK = SPARSE ? 64 : 32;
@@ -40,7 +41,8 @@ struct Cfg {
     static constexpr int A_ROW = 64;                        // bytes per A row per stage (32 survivors or 32 dense k)
     static constexpr int B_ROW = SPARSE ? 128 : 64;
     static constexpr int META_ROW = FP8 ? 16 : 8;
-    static constexpr int A_BYTES = BM * A_ROW, B_BYTES = BN * B_ROW, META_BYTES = SPARSE ? BM * META_ROW : 0;
+    static constexpr int A_BYTES = BM * A_ROW, B_BYTES = BN * B_ROW, META_BYTES = SPARSE && !MG ? BM * META_ROW : 0;
+    static constexpr int GROUP_BYTES = MG ? BM * 32 : 0;    // 32 metadata bytes of every A row = 256 k
     static constexpr int STAGE = A_BYTES + B_BYTES + META_BYTES;
     static constexpr int A_LD = A_BYTES / 1024 / TL::NW, B_LD = B_BYTES / 1024 / TL::NW, M_LD = SPARSE ? BM / 32 / TL::NW : 0;   // loads per wave per stage
     static constexpr int LOADS = A_LD + B_LD + M_LD * (FP8 ? 2 : 1);
@@ -104,16 +106,16 @@ __device__ __forceinline__ bool keep4_of(uint32_t sc, int lane) {
     }
     return kept;
 }
-template <bool SPARSE, bool OUT_I_CONTIG, int EPI, bool BLOCKED, bool FP8, class TL>
+template <bool SPARSE, bool OUT_I_CONTIG, int EPI, bool BLOCKED, bool FP8, class TL, bool MG = false>
 struct GemmV2Lds {
-    using C = Cfg<SPARSE, FP8, TL>;
+    using C = Cfg<SPARSE, FP8, TL, MG>;
     static constexpr int EPI_LDS = (EPI != 0) ? TL::NW * (64 + 32) * (64 * 2 + 16) : 0;        // the epilogues' scratch (see below) when the ring is shorter
-    static constexpr int RING = TL::KW * C::NSTAGE * C::STAGE;
+    static constexpr int RING = TL::KW * C::NSTAGE * C::STAGE + 2 * C::GROUP_BYTES;
     static constexpr int BYTES = RING > EPI_LDS ? RING : EPI_LDS;
 };
 // pid / n_pid: this workgroup's id and the number of workgroups of the contraction (a launch may hold several contractions)
 // BROW: B row-major although A is blocked (forward_x.hip)
-template <bool SPARSE, bool OUT_I_CONTIG, int EPI, bool BLOCKED, bool FP8, class TL, bool BROW>
+template <bool SPARSE, bool OUT_I_CONTIG, int EPI, bool BLOCKED, bool FP8, class TL, bool BROW, bool MG>
 __device__ __forceinline__ void gemm_nt_v2_body(unsigned char* __restrict__ smem, int pid, int n_pid,
                                                         const uint16_t* __restrict__ a_vals, const uint8_t* __restrict__ a_meta,
                                                         const uint16_t* __restrict__ B, const float* __restrict__ bias,
@@ -126,7 +128,8 @@ __device__ __forceinline__ void gemm_nt_v2_body(unsigned char* __restrict__ smem
     static_assert(!(GEN_F || GEN_B) || (LOGM >= 4 && LOGM <= 6), "wide V:N:M blocks: M = 16, 32 or 64");
     static_assert(!FP8 || (SPARSE && (EPI == 0 || (BLOCKED && (EPI == 1 || EPI == 2 || GEN_F || GEN_B)))), "fp8 operands: structured-sparse kernel; the step's fused epilogues");
     constexpr bool blocked = BLOCKED, blockedB = BLOCKED && !BROW;       // operands in the blocked layout of common.hpp (fused step) or row-major (stand-alone entry points)
-    using C = Cfg<SPARSE, FP8, TL>;
+    static_assert(!MG || (SPARSE && !BLOCKED && !FP8 && TL::KW == 1 && TL::NST == 3 && TL::WM * TL::WVM == 32 * TL::NW), "metadata of four stages: row-major bf16, 32 rows a wavefront");
+    using C = Cfg<SPARSE, FP8, TL, MG>;
     constexpr int BM = C::BM, BN = C::BN, WM = TL::WM, WN = 64, FM = WM / 32, FN = 2, NH = WM / 64, KW = TL::KW;
     static_assert(LOGM < 6 || WM == 128, "the two blocks of 64 columns that share a metadata byte belong to one wavefront");
     const int tid = threadIdx.x, lane = tid & 63;
@@ -196,6 +199,7 @@ __device__ __forceinline__ void gemm_nt_v2_body(unsigned char* __restrict__ smem
     //      (common.hpp): the 16 rows x 64 bytes are one contiguous block.  Tile rows past the matrix edge
     //      are clamped into it: they only feed outputs that are never stored. --------------------------
     constexpr int A_LD = C::A_LD, B_LD = C::B_LD, M_LD = C::M_LD;          // issues per wave and stage
+    const uint32_t m_again = (uint32_t)((lane >> 3) * (Kld / 8) + (lane & 7) * 4);      // MG: rows 0-7 of the wavefront's 32 (halves in order there)
     // Row-major operands of the sparse kernel: a B row's 64 k of a stage are one 128-byte line, fetched whole (8 rows per
     // load, tile [256][128 bytes], 16-byte chunks swizzled by (row / 2) % 8) rather than as two 64-byte halves.
     constexpr bool lineB = SPARSE && !blockedB;
@@ -240,6 +244,7 @@ __device__ __forceinline__ void gemm_nt_v2_body(unsigned char* __restrict__ smem
         a_kstep = blocked ? 1024 : 64;
         b_kstep = blockedB ? 1024 * (C::BK / 32) : C::BK * 2;
         m_kstep = (blocked && !FP8) ? 256 : C::META_ROW;
+        if (MG) m_lane = (uint32_t)((lane >> 1) * (Kld / 8) + (((lane & 1) ^ ((lane >> 4) & 1)) << 4));      // dma16: row lane / 2, 16-byte half swizzled by (row / 8) % 2
         if (FP8 && blocked) {       // fp8 metadata units of common.hpp (m8blk_off): 512 contiguous bytes per (32 rows, 128 k), row-major inside
             m_lane = lane * 4; m_kstep = 512;
         }
@@ -259,6 +264,18 @@ __device__ __forceinline__ void gemm_nt_v2_body(unsigned char* __restrict__ smem
 #pragma unroll
         for (int n = 0; n < B_LD; ++n)
             if (A_LD + n >= lo && A_LD + n < hi) dma16(b_base[n], (lineB && (n & 1)) ? bo1 : bo, sb + (wt * B_LD + n) * 1024);
+        if (MG) {
+            // Four stages' metadata of a row are 32 bytes: one load of 1 KB per wavefront instead of four of 256 bytes that touch as many lines each (8 bytes of
+            // 32 rows).  Group g (stages 4 g .. 4 g + 3) arrives with the refill for stage 4 g - 2, two stages ahead of its first use and behind the last use of
+            // the group whose buffer it takes; the other refills fetch 8 of its rows once more, so that every stage counts the same number of loads.
+            if (LD - 1 >= lo && LD - 1 < hi) {
+                int g = (kt + 2) >> 2;
+                g = g < (Kld >> 8) ? g : (Kld >> 8) - 1;
+                unsigned char* sg = smem + C::NSTAGE * C::STAGE + (g & 1) * C::GROUP_BYTES + wt * 1024;
+                if (kt == 0 || (kt & 3) == 2) dma16(m_base[0], m_lane + (uint32_t)g * 32, sg);
+                else dma4(m_base[0], m_again + (uint32_t)g * 32, sg);
+            }
+        } else
 #pragma unroll
         for (int n = 0; n < M_LD; ++n) {
             if (!FP8) {
@@ -279,7 +296,8 @@ __device__ __forceinline__ void gemm_nt_v2_body(unsigned char* __restrict__ smem
         const int row = wm * WM + a * 32 + l32;
         a_off[a] = row * 64 + ((lh ^ ((row >> 2) & 3)) << 4);
         // blocked: the lane's word of unit row / 32 holds both 32-k steps (picked by ABID); row-major: [row][8 bytes]
-        m_off[a] = C::A_BYTES + C::B_BYTES + (FP8 ? row * 16 + 4 * lh : blocked ? (row >> 5) * 256 + lane * 4 : row * 8 + 2 * lh);
+        if (MG) m_off[a] = C::NSTAGE * C::STAGE + row * 32 + (((row >> 3) & 1) << 4);
+        else m_off[a] = C::A_BYTES + C::B_BYTES + (FP8 ? row * 16 + 4 * lh : blocked ? (row >> 5) * 256 + lane * 4 : row * 8 + 2 * lh);
     }
 #pragma unroll
     for (int b = 0; b < FN; ++b) {
@@ -305,10 +323,16 @@ __device__ __forceinline__ void gemm_nt_v2_body(unsigned char* __restrict__ smem
         Frag8 b8[FN];       // dense: 8 k-values per lane
     };
     // `prev` = the set that holds the first 32-k step of the same tile (its index word serves both steps)
+    uint32_t m_kt = 0;          // MG: stage whose first fragments are read next
     auto read_a = [&](FragSet& f, const FragSet& prev, const unsigned char* st, int ks, int a) {
         f.a[a].u = *reinterpret_cast<const uint4*>(st + (a_off[a] ^ (32 * ks)));
         if (SPARSE) {
-            if (FP8) f.idx[a] = *reinterpret_cast<const uint32_t*>(st + m_off[a] + 8 * ks);
+            if (MG) {       // the stage's 8 bytes of the row: the 16 index bits of this lane's half of either step side by side
+                if (ks == 0) {
+                    const uint2 w = *reinterpret_cast<const uint2*>(ring + (m_off[a] ^ ((m_kt & 2) << 3)) + ((m_kt & 4) ? C::GROUP_BYTES : 0) + ((m_kt & 1) << 3));
+                    f.idx[a] = __builtin_amdgcn_perm(w.y, w.x, lh ? 0x07060302u : 0x05040100u);
+                } else f.idx[a] = prev.idx[a];
+            } else if (FP8) f.idx[a] = *reinterpret_cast<const uint32_t*>(st + m_off[a] + 8 * ks);
             else if (!blocked) f.idx[a] = *reinterpret_cast<const uint16_t*>(st + m_off[a] + 4 * ks);
             else if (ks == 0) f.idx[a] = *reinterpret_cast<const uint32_t*>(st + m_off[a]);
             else f.idx[a] = prev.idx[a];
@@ -338,7 +362,7 @@ __device__ __forceinline__ void gemm_nt_v2_body(unsigned char* __restrict__ smem
         for (int b = 0; b < FN; ++b) {
             if (FP8)                    acc[a][b] = __builtin_amdgcn_smfmac_f32_32x32x64_fp8_fp8(f.a[a].q, f.b16[b].q, acc[a][b], f.idx[a], 0, 0);
             else if (!SPARSE)           acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.a[a].v, f.b8[b].v, acc[a][b], 0, 0, 0);
-            else if (blocked && second) acc[a][b] = __builtin_amdgcn_smfmac_f32_32x32x32_bf16(f.a[a].v, f.b16[b].v, acc[a][b], f.idx[a], 0, 1);
+            else if ((blocked || MG) && second) acc[a][b] = __builtin_amdgcn_smfmac_f32_32x32x32_bf16(f.a[a].v, f.b16[b].v, acc[a][b], f.idx[a], 0, 1);
             else                        acc[a][b] = __builtin_amdgcn_smfmac_f32_32x32x32_bf16(f.a[a].v, f.b16[b].v, acc[a][b], f.idx[a], 0, 0);
         }
     };
@@ -390,6 +414,7 @@ __device__ __forceinline__ void gemm_nt_v2_body(unsigned char* __restrict__ smem
         else asm volatile("" ::: "memory");
         SB();
         re_kt = step_of((kt + C::NSTAGE < nk) ? kt + C::NSTAGE : nk - 1); re_stage = stage;
+        if (MG) m_kt = (uint32_t)kt + 1;
         mma_row(Q, 0, true); SB();
         ISSUE(0);
         read_a(P, P, sn, 0, 0); read_a(P, P, sn, 0, 1); read_b(P, sn, 0, 0); if (FM == 2) read_b(P, sn, 0, 1); SB();
@@ -443,7 +468,7 @@ __device__ __forceinline__ void gemm_nt_v2_body(unsigned char* __restrict__ smem
         // EPI: second tile (32 compact rows) for the transposed output
         constexpr int WAVE_LDS = (EPI != 0) ? (WN + 32) * EP : WN * EP;
         unsigned char* scratch = smem + wt * WAVE_LDS;
-        static_assert(TL::NW * WAVE_LDS <= GemmV2Lds<SPARSE, OUT_I_CONTIG, EPI, BLOCKED, FP8, TL>::BYTES, "epilogue scratch must fit in the main-loop LDS");
+        static_assert(TL::NW * WAVE_LDS <= GemmV2Lds<SPARSE, OUT_I_CONTIG, EPI, BLOCKED, FP8, TL, MG>::BYTES, "epilogue scratch must fit in the main-loop LDS");
         unsigned char* ttile = scratch + WN * EP;
         // EPI: i = hidden unit f, j = token t; the wave's 64 tokens are exactly one V = 64 block and each half of
         // 64 f holds 8 whole column blocks, so the V:N:M work is wave-local.
@@ -976,12 +1001,12 @@ inline unsigned grid_tiles(int64_t Ra, int64_t Rb, const GemmGroup& g, int BM, i
 }
 
 // one contraction as a unit that launch_units (launch_mix.hpp) puts into a launch, alone or with others
-template <bool SPARSE, bool OUT_I_CONTIG, int EPI, bool BLOCKED, bool FP8, class TL, bool BROW = false>
+template <bool SPARSE, bool OUT_I_CONTIG, int EPI, bool BLOCKED, bool FP8, class TL, bool BROW = false, bool MG = false>
 struct GemmV2Unit {
     using Args = GemmV2Args;
-    static constexpr int THREADS = TL::THREADS, LDS = GemmV2Lds<SPARSE, OUT_I_CONTIG, EPI, BLOCKED, FP8, TL>::BYTES;
+    static constexpr int THREADS = TL::THREADS, LDS = GemmV2Lds<SPARSE, OUT_I_CONTIG, EPI, BLOCKED, FP8, TL, MG>::BYTES;
     static __device__ __forceinline__ void run(unsigned char* smem, int pid, int n_pid, const Args& a) {
-        gemm_nt_v2_body<SPARSE, OUT_I_CONTIG, EPI, BLOCKED, FP8, TL, BROW>(smem, pid, n_pid, a.a_vals, a.a_meta, a.B, a.bias, a.Ra, a.Rb, a.K, a.out, a.ldo, a.tiles_m, a.tiles_n,
+        gemm_nt_v2_body<SPARSE, OUT_I_CONTIG, EPI, BLOCKED, FP8, TL, BROW, MG>(smem, pid, n_pid, a.a_vals, a.a_meta, a.B, a.bias, a.Ra, a.Rb, a.K, a.out, a.ldo, a.tiles_m, a.tiles_n,
                                                                      a.ep, a.grp, a.alpha);
     }
     static unsigned count(const Args& a) { return grid_tiles(a.Ra, a.Rb, a.grp, TL::BM, TL::BN); }
@@ -1005,6 +1030,15 @@ hipError_t launch_gemm_v2(const GemmV2Args& a, hipStream_t s, int tile = 0) {
         constexpr int M = Sel::T128::BM == 256 ? 64 : EPI >= 20 ? 16 : 8;
         tile = pick_gemm_tile(a.Ra, a.Rb, steps, a.grp, small_round(what, steps, M, FP8), SPARSE, last_round(what, steps, M, FP8), M == 64);
     }
+    // Row-major 2:4 operands, whole groups of 256 k: metadata for four stages at a time (MG).  What bounds the loop is the number of lines a stage touches, 256 of
+    // 768 for its metadata: T = 8192, N = 8192, K = 2048 198 -> 178 us, T = 2560, N = 16960, K = 3840 216 / 195; on 128 tiles T = 576, N = 9024, K = 2560 40.7 / 35.0,
+    // but with a workgroup a CU and a short contraction its reads of the index bits cost more (T = 896, N = 3456, K = 768, 189 tiles, 9.7 / 10.2).
+    if constexpr (SPARSE && !BLOCKED && !FP8)
+        if (a.K % 256 == 0) {
+            if (tile == 256) return launch_units<GemmV2Unit<SPARSE, OUT_I_CONTIG, EPI, BLOCKED, FP8, Tile256<SPARSE>, false, true>>(s, a);
+            if (tile == 128 && (a.K >= 2048 || grid_tiles(a.Ra, a.Rb, a.grp, 128, 128) > 256))
+                return launch_units<GemmV2Unit<SPARSE, OUT_I_CONTIG, EPI, BLOCKED, FP8, typename Sel::T128, false, true>>(s, a);
+        }
     if (tile == 256) return launch_units<GemmV2Unit<SPARSE, OUT_I_CONTIG, EPI, BLOCKED, FP8, Tile256<SPARSE>>>(s, a);
     if (tile == 128) return launch_units<GemmV2Unit<SPARSE, OUT_I_CONTIG, EPI, BLOCKED, FP8, typename Sel::T128>>(s, a);
     // (the dense form has no 64 tile)

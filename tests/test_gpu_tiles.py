@@ -264,3 +264,17 @@ def test_router_step_in_shared_launches(M, T, D, F):
         for name, g in zip(("y3", "dX", "dW1", "dW2"), want):
             a, b = oracle.bits_to_f64(to_bits(g)), oracle.bits_to_f64(ref[name])
             assert np.linalg.norm(a - b) <= 0.05 * np.linalg.norm(b), name
+
+
+@pytest.mark.parametrize("T,N,K", [(2112, 4160, 256), (2112, 4160, 512), (2112, 4160, 768), (2112, 4160, 1344), (1984, 2240, 256), (1984, 2240, 768), (576, 3008, 2048)])
+def test_standalone_24_contractions_on_large_tiles(T, N, K):
+    """256 and (the last three) 128 tiles with remainders in both dimensions; metadata fetched for four stages at a time (one, two, three and eight groups), and
+    stage by stage (K = 1344)."""
+    rng = np.random.default_rng(71)
+    X, W = (bf16_bits_from_f32(rng.standard_normal((n, K)).astype(np.float32)) for n in (T, N))
+    b1 = rng.standard_normal(N).astype(np.float32)
+    vals, meta = sffn.prune24_compress(to_dev(W), False, sffn.MODE_HARD)
+    rv, rm = oracle.prune24_compress(W, sffn.MODE_HARD)
+    assert np.array_equal(to_bits(vals), rv) and np.array_equal(to_bits(meta), rm)
+    assert_gemm_close(to_bits(sffn.spmm24_fwd(to_dev(X), vals, meta, to_dev(b1))), oracle.spmm24(X, rv, rm, b1), "fwd")
+    assert_gemm_close(to_bits(sffn.spmm24_dgrad(to_dev(X), vals, meta)), oracle.spmm24(X, rv, rm, None), "dgrad")
