@@ -45,7 +45,7 @@ struct Cfg {
     static constexpr int GROUP_BYTES = MG ? BM * 32 : 0;    // 32 metadata bytes of every A row = 256 k
     static constexpr int STAGE = A_BYTES + B_BYTES + META_BYTES;
     static constexpr int A_LD = A_BYTES / 1024 / TL::NW, B_LD = B_BYTES / 1024 / TL::NW, M_LD = SPARSE ? BM / 32 / TL::NW : 0;   // loads per wave per stage
-    static constexpr int LOADS = A_LD + B_LD + M_LD * (FP8 ? 2 : 1);
+    static constexpr int LOADS = A_LD + B_LD + M_LD * (FP8 ? 2 : 1);       // (MG: one fewer in stages that bring no metadata)
 };
 
 // max(x, 0) in one instruction, 0 for NaN.  (As a comparison, as fmaxf or with an infinity that the compiler sees: two, the first to quiet a NaN.)
@@ -199,7 +199,6 @@ __device__ __forceinline__ void gemm_nt_v2_body(unsigned char* __restrict__ smem
     //      (common.hpp): the 16 rows x 64 bytes are one contiguous block.  Tile rows past the matrix edge
     //      are clamped into it: they only feed outputs that are never stored. --------------------------
     constexpr int A_LD = C::A_LD, B_LD = C::B_LD, M_LD = C::M_LD;          // issues per wave and stage
-    const uint32_t m_again = (uint32_t)((lane >> 3) * (Kld / 8) + (lane & 7) * 4);      // MG: rows 0-7 of the wavefront's 32 (halves in order there)
     // Row-major operands of the sparse kernel: a B row's 64 k of a stage are one 128-byte line, fetched whole (8 rows per
     // load, tile [256][128 bytes], 16-byte chunks swizzled by (row / 2) % 8) rather than as two 64-byte halves.
     constexpr bool lineB = SPARSE && !blockedB;
@@ -244,13 +243,14 @@ __device__ __forceinline__ void gemm_nt_v2_body(unsigned char* __restrict__ smem
         a_kstep = blocked ? 1024 : 64;
         b_kstep = blockedB ? 1024 * (C::BK / 32) : C::BK * 2;
         m_kstep = (blocked && !FP8) ? 256 : C::META_ROW;
-        if (MG) m_lane = (uint32_t)((lane >> 1) * (Kld / 8) + (((lane & 1) ^ ((lane >> 4) & 1)) << 4));      // dma16: row lane / 2, 16-byte half swizzled by (row / 8) % 2
+        if (MG) m_lane = (uint32_t)((lane >> 1) * (Kld / 8) + (((lane & 1) ^ ((lane >> 4) & 1)) << 4));      // row lane / 2, 16-byte half swizzled by (row / 8) % 2
         if (FP8 && blocked) {       // fp8 metadata units of common.hpp (m8blk_off): 512 contiguous bytes per (32 rows, 128 k), row-major inside
             m_lane = lane * 4; m_kstep = 512;
         }
     }
     // DMA loads lo .. hi - 1 of a stage's LD (compile-time bounds): they are issued one at a time between matrix instructions
     constexpr int LD = A_LD + B_LD + (FP8 ? 2 * M_LD : M_LD);
+    auto brings_meta = [](int kt) { return (kt & 3) == 0; };      // MG
     static_assert(LD == C::LOADS, "loads in flight");
     auto issue = [&](int kt, int stage, int lo, int hi) {
         unsigned char* sa = ring + stage * C::STAGE;
@@ -265,16 +265,11 @@ __device__ __forceinline__ void gemm_nt_v2_body(unsigned char* __restrict__ smem
         for (int n = 0; n < B_LD; ++n)
             if (A_LD + n >= lo && A_LD + n < hi) dma16(b_base[n], (lineB && (n & 1)) ? bo1 : bo, sb + (wt * B_LD + n) * 1024);
         if (MG) {
-            // Four stages' metadata of a row are 32 bytes: one load of 1 KB per wavefront instead of four of 256 bytes that touch as many lines each (8 bytes of
-            // 32 rows).  Group g (stages 4 g .. 4 g + 3) arrives with the refill for stage 4 g - 2, two stages ahead of its first use and behind the last use of
-            // the group whose buffer it takes; the other refills fetch 8 of its rows once more, so that every stage counts the same number of loads.
-            if (LD - 1 >= lo && LD - 1 < hi) {
-                int g = (kt + 2) >> 2;
-                g = g < (Kld >> 8) ? g : (Kld >> 8) - 1;
-                unsigned char* sg = smem + C::NSTAGE * C::STAGE + (g & 1) * C::GROUP_BYTES + wt * 1024;
-                if (kt == 0 || (kt & 3) == 2) dma16(m_base[0], m_lane + (uint32_t)g * 32, sg);
-                else dma4(m_base[0], m_again + (uint32_t)g * 32, sg);
-            }
+            // 32 bytes of each of 32 rows in one load every four stages, instead of 8 bytes, as many lines, in every stage.  Group g (stages 4 g .. 4 g + 3) arrives
+            // with stage 4 g, into the buffer of group g - 2, whose last reads ended with the stage that this refill replaces.  (On blocked operands, whose
+            // metadata of a stage are one line a wavefront, it gains nothing: 1840 us for 1821 in eq. (1) at T = D = 8192, F = 28672.)
+            if (LD - 1 >= lo && LD - 1 < hi && brings_meta(kt))
+                dma16(m_base[0], m_lane + (uint32_t)(kt >> 2) * 32, smem + C::NSTAGE * C::STAGE + ((kt >> 2) & 1) * C::GROUP_BYTES + wt * 1024);
         } else
 #pragma unroll
         for (int n = 0; n < M_LD; ++n) {
@@ -378,7 +373,7 @@ __device__ __forceinline__ void gemm_nt_v2_body(unsigned char* __restrict__ smem
     // (KW > 1: the ring belongs to one wavefront, whose own waits order its loads and reads.)
 #pragma unroll
     for (int p = 0; p < C::NSTAGE; ++p) issue(step_of(p < nk ? p : nk - 1), p, 0, LD);
-    wait_vmcnt<(C::NSTAGE - 1) * C::LOADS>();
+    wait_vmcnt<(C::NSTAGE - 1) * (C::LOADS - (MG ? 1 : 0))>();
     if (KW == 1) __syncthreads();
     else asm volatile("" ::: "memory");
     FragSet P, Q;
@@ -409,7 +404,10 @@ __device__ __forceinline__ void gemm_nt_v2_body(unsigned char* __restrict__ smem
         }
         // Q has arrived and tile kt+1 has landed (this wave's part); after the barrier every wave is done
         // reading this stage, which is refilled, and every wave's part of tile kt+1 is in LDS
-        wait_vmcnt_lgkm0<(C::NSTAGE - 2) * C::LOADS>();
+        if constexpr (MG) {
+            if (brings_meta(re_kt)) wait_vmcnt_lgkm0<(C::NSTAGE - 2) * C::LOADS>();
+            else wait_vmcnt_lgkm0<(C::NSTAGE - 2) * C::LOADS - 1>();
+        } else wait_vmcnt_lgkm0<(C::NSTAGE - 2) * C::LOADS>();
         if (KW == 1) __builtin_amdgcn_s_barrier();
         else asm volatile("" ::: "memory");
         SB();
@@ -1031,12 +1029,11 @@ hipError_t launch_gemm_v2(const GemmV2Args& a, hipStream_t s, int tile = 0) {
         tile = pick_gemm_tile(a.Ra, a.Rb, steps, a.grp, small_round(what, steps, M, FP8), SPARSE, last_round(what, steps, M, FP8), M == 64);
     }
     // Row-major 2:4 operands, whole groups of 256 k: metadata for four stages at a time (MG).  What bounds the loop is the number of lines a stage touches, 256 of
-    // 768 for its metadata: T = 8192, N = 8192, K = 2048 198 -> 178 us, T = 2560, N = 16960, K = 3840 216 / 195; on 128 tiles T = 576, N = 9024, K = 2560 40.7 / 35.0,
-    // but with a workgroup a CU and a short contraction its reads of the index bits cost more (T = 896, N = 3456, K = 768, 189 tiles, 9.7 / 10.2).
+    // 768 for its metadata: T = 8192, N = 8192, K = 2048 192 -> 164 us; on 128 tiles T = 576, N = 9024, K = 2560 40.7 -> 33; even where few tiles are short.
     if constexpr (SPARSE && !BLOCKED && !FP8)
         if (a.K % 256 == 0) {
             if (tile == 256) return launch_units<GemmV2Unit<SPARSE, OUT_I_CONTIG, EPI, BLOCKED, FP8, Tile256<SPARSE>, false, true>>(s, a);
-            if (tile == 128 && (a.K >= 2048 || grid_tiles(a.Ra, a.Rb, a.grp, 128, 128) > 256))
+            if (tile == 128)
                 return launch_units<GemmV2Unit<SPARSE, OUT_I_CONTIG, EPI, BLOCKED, FP8, typename Sel::T128, false, true>>(s, a);
         }
     if (tile == 256) return launch_units<GemmV2Unit<SPARSE, OUT_I_CONTIG, EPI, BLOCKED, FP8, Tile256<SPARSE>>>(s, a);
