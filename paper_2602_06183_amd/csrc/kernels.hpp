@@ -152,11 +152,12 @@ hipError_t launch_fp8_prologue(const Fp8PrologueArgs& a, hipStream_t s);
 // large ones (measured, see below: more bytes from L2 per product), so the large tile wins on whole rounds and the small one where the
 // outputs do not fill the chip or leave the last round nearly empty.  64 x 64 tiles split the contraction over their four wavefronts: best
 // while there are at most `most64` of them and the contraction is long enough to be worth splitting.  last: what a last round of small tiles takes, as a
-// part of a full one, when it leaves every workgroup (all but a few, with `few` above 256) a CU of its own.
-inline int pick_tile(float rounds256, unsigned n128, unsigned n64, int steps, float w128, unsigned most64, int least_steps, float last = 1.0f, unsigned few = 256) {
+// part of a full one, when it leaves every workgroup a CU of its own; slope: and from there in line up to a full one.
+inline int pick_tile(float rounds256, unsigned n128, unsigned n64, int steps, float w128, unsigned most64, int least_steps, float last = 1.0f, bool slope = false) {
     if (n64 <= most64 && steps >= least_steps) return 64;
     const unsigned rest = n128 % 512;
-    return w128 * ((float)(n128 / 512) + (rest == 0 ? 0.0f : rest <= few ? last : 1.0f)) < rounds256 ? 128 : 256;
+    const float part = rest == 0 ? 0.0f : rest <= 256 ? last : slope ? last + (1.0f - last) * (float)(rest - 256) / 256.0f : 1.0f;
+    return w128 * ((float)(n128 / 512) + part) < rounds256 ? 128 : 256;
 }
 inline float large_rounds(unsigned n256) { return (float)((n256 + 255) / 256); }
 
@@ -214,7 +215,7 @@ inline int pick_epilogue_tile(int64_t F, int64_t T, int steps, const GemmGroup& 
 // V:2:8 activation GEMM.  The large tile is 512 tokens x 128 columns or 256 x 256 (gemm_vnm8.hip), 0.93 and 1 a round: four fifths of what a stage of the second
 // fetches are the dense slab.  A round of 128 tiles, two per CU, takes more of that the longer the contraction, one per CU 0.86 at most (codes: 0.66).  Large /
 // 128: T = 1600, N = 4864, F = 19584 (152 / 494 tiles) 369 us, 444; T = 2688, N = 2816, F = 9024 (126 / 462) 162, 170; T = 15360, N = 448, F = 1856 (120 / 480)
-// 24 / 22; T = 896, N = 3904, F = 17280 (62 / 217) 1 / 0.75; T = 2048, N = 4800, F = 16896 (152 / 608) 1 / 1.49; codes, T = 3840, N = 2048, F = 7936 (120 / 480)
+// 24 / 22; T = 896, N = 3904, F = 17280 (62 / 217) 1 / 0.75; T = 1792, N = 2816, F = 12096 (88 / 308) 1 / 0.86; T = 2048, N = 4800, F = 16896 (152 / 608) 1 / 1.49; codes, T = 3840, N = 2048, F = 7936 (120 / 480)
 // 1 / 0.85.  Over 270 shapes what is chosen takes 0.2 % longer than the better of the two.  T = 1024, N = 1408, F = 4928 (24 / 88 / 352): 55, 33, and 29 on
 // 64 tiles; T = 64, N = 2048, F = 8192 (8 / 16 / 32): 83, 49, 28.
 // More than 256 of the 64 tiles: only for long contractions of bf16 (T = 256, N = 5824, F = 24704, 364 of them: 169 us, 192 on 128 tiles; 24 trips: a third
@@ -222,15 +223,14 @@ inline int pick_epilogue_tile(int64_t F, int64_t T, int steps, const GemmGroup& 
 // fp8 loses to every other tile there (T = 4864, N = 384, F = 1408, 456 of them: 18.5 us, 10.6 on 128, 16.0 on 256).
 inline float vnm8_rounds(unsigned n512, unsigned n256) { const float a = 0.93f * large_rounds(n512), b = large_rounds(n256); return a < b ? a : b; }
 inline float vnm8_small_round(int steps, bool fp8) {
-    const float w = fp8 ? 0.64f + 0.0012f * (float)steps : 0.63f + 0.0025f * (float)steps, most = fp8 ? 0.86f : 0.98f;
+    const float w = fp8 ? 0.64f + 0.0012f * (float)steps : 0.63f + 0.0025f * (float)steps, most = fp8 ? 0.86f : 1.2f;
     return w < most ? w : most;
 }
-constexpr unsigned kVnm8Few = 320;      // (T = 1792, N = 2816, F = 12096, 88 / 308: 1 / 0.86; T = 1216, N = 4864, F = 19712, 114 / 380: 1 / 1.19)
 inline float vnm8_last_round(int steps, bool fp8) { const float w = vnm8_small_round(steps, fp8), last = fp8 ? 0.66f : 0.86f; return last < w ? last / w : 1.0f; }
 inline int pick_vnm8_tile(int64_t T, int64_t N, int steps, int groups, bool fp8) {
     auto tiles = [&](int64_t edge) { return (unsigned)(token_tiles(T, groups, edge) * ((N + edge - 1) / edge)); };
     const float large = vnm8_rounds((unsigned)(token_tiles(T, groups, 512) * ((N + 127) / 128)), tiles(256));
-    return pick_tile(large, tiles(128), tiles(64), steps, vnm8_small_round(steps, fp8), !fp8 && steps >= 84 ? 512 : 256, 8, vnm8_last_round(steps, fp8), kVnm8Few);
+    return pick_tile(large, tiles(128), tiles(64), steps, vnm8_small_round(steps, fp8), !fp8 && steps >= 84 ? 512 : 256, 8, vnm8_last_round(steps, fp8), true);
 }
 // gathered-row activation GEMM: 64 tokens x 256 columns, or 64 x 64
 // (T = 256, N = 1024, F = 4096, M = 16: 19 us and 12 us; T = N = 1024: 20 and 12; T = 512, N = 4096, F = 16384: 90 and 67; T = 1984, N = 1344, M = 32: 14 and 23)
@@ -337,13 +337,14 @@ inline bool sharing_pays(int64_t T, int64_t D, int64_t F, int M, int groups, boo
     auto more = [](float a, float b) { return a > b ? a : b; };
     const float longest = more(k3.tile, k5.tile);
     const float together = 2.0f * kAlone + kTogether * (2.0f * work(k3) + 2.0f * work(k5) + work(k4)) + kEnd * (longest + more(longest, k4.tile));
-    // 0.92: near even the launches by themselves win as often (T = 12928, D = 960, F = 3584, estimated 0.95 of them: 497 us apart, 520 together), and 0.75 where
+    // 0.90: near even the launches by themselves win as often (T = 12928, D = 960, F = 3584, estimated 0.95 of them: 497 us apart, 520 together), and so they do
+    // where their rounds are many (codes, T = 8576, D = 3328, F = 10624, estimated 0.91: 1418 / 1458; T = 2816, D = 6080, F = 19456, 0.88: 2702 / 2880).  0.75 where
     // few tokens meet weights of 30 million elements and more, whose bytes bound either form (T = 128, D = 6784, F = 17408 on codes: 517 / 549; M = 16 never: T = 192,
-    // D = 4416, F = 19200 468 / 507)
+    // D = 4416, F = 19200 468 / 507).
+    const float alone = k4.alone + 2.0f * (k3.alone + k5.alone) + 5.0f * kAlone;
     const bool bytes = D * F >= 30000000 && T < (fp8 ? 192 : M == 8 ? 384 : 640) * e;
-    if (bytes && M == 16 && !fp8) return false;
-    const float pays = bytes ? 0.75f : 0.92f;
-    return together < pays * (k4.alone + 2.0f * (k3.alone + k5.alone) + 5.0f * kAlone);
+    if (alone > 1200.0f || (bytes && M == 16 && !fp8)) return false;
+    return together < (bytes ? 0.75f : 0.90f) * alone;
 }
 
 // may_share: false where the shared launches are not built for the call
@@ -373,9 +374,9 @@ inline StepTiles step_tiles(int64_t T, int64_t D, int64_t F, int M, int experts,
 }
 
 // the same once the experts' segments are known: 256 or 128 by the exact number of tiles (the two give the same bits; sharing launches and splitting
-// contractions were decided from the sizes alone).  8 experts x 128 tokens, D = 3840, F = 12672: eqs. (3), (7) 181, 138 us on 128 tiles, 221, 191 on 256.
+// contractions were decided from the sizes alone, and shared launches keep their tiles).  8 experts x 128 tokens, D = 3840, F = 12672: eqs. (3), (7) 181, 138 us on 128 tiles, 221, 191 on 256.
 inline void refine_tiles(StepTiles* t, int64_t D, int64_t F, int M, const GemmGroup& g, bool fp8) {
-    if (t->mix || !g.n) return;
+    if (!g.n) return;
     auto count = [&](int64_t other, int64_t other_edge, int64_t edge) {
         int64_t n = 0;
         for (int e = 0; e < g.n; ++e) n += (g.seg[e + 1] - g.seg[e] + edge - 1) / edge;
@@ -386,10 +387,11 @@ inline void refine_tiles(StepTiles* t, int64_t D, int64_t F, int M, const GemmGr
         return pick_tile(large_rounds(count(F, 256, 256)), count(F, M == 64 ? 256 : 128, 128), ~0u, 0, small_round(what, steps, M, fp8), 0, 0, last_round(what, steps, M, fp8));
     };
     if (t->g != 64) t->g = pick(kGemmForward);
-    if (t->g_bwd != 64) t->g_bwd = pick(kGemmBackward);
+    if (t->g_bwd != 64 && !t->mix) t->g_bwd = pick(kGemmBackward);
     if (M == 8 && t->v != 64) {
         const int steps = (int)(F / (fp8 ? 128 : 64));
-        t->v = t->v_alone = pick_tile(vnm8_rounds(count(D, 128, 512), count(D, 256, 256)), count(D, 128, 128), ~0u, 0, vnm8_small_round(steps, fp8), 0, 0, vnm8_last_round(steps, fp8), kVnm8Few);
+        t->v_alone = pick_tile(vnm8_rounds(count(D, 128, 512), count(D, 256, 256)), count(D, 128, 128), ~0u, 0, vnm8_small_round(steps, fp8), 0, 0, vnm8_last_round(steps, fp8), true);
+        if (!t->mix) t->v = t->v_alone;
     }
 }
 
