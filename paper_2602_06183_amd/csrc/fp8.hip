@@ -95,7 +95,7 @@ __global__ void __launch_bounds__(256) prune24_cols_fp8_kernel(const uint16_t* _
     note_amax(amax, m);
 }
 
-// eq. (2) + V:N:M compression with fp8 values: the structure of sqrelu_vnm_compress_m_kernel (vnm_general.hip): one workgroup =
+// eq. (2) + V:N:M compression with fp8 values: the tiling of sqrelu_vnm_compress_m_kernel (vnm_general.hip): one workgroup =
 // one 64-token block x 256 columns, wavefront w owns 64 columns; scores, column choice and the per-row 2:4 choice on the bf16 y2.
 template <int M>
 __global__ void __launch_bounds__(256) sqrelu_vnm_compress_fp8_kernel(const uint16_t* __restrict__ y1, int64_t F, float inv, uint8_t* __restrict__ codes,

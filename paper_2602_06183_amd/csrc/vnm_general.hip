@@ -6,87 +6,142 @@
 // (one nibble per block, two blocks per byte), colidx [T/64, F/M, 4] (offsets inside the block, ascending).
 #include "common.hpp"
 #include "kernels.hpp"
+#include "lds_dma.hpp"
+#include "vnm_select.hpp"
 
 namespace sffn {
 
-namespace {
-constexpr int kPitch = 64 * 2 + 16;     // bytes per row of a wavefront's 64 x 64 tile of y2 in LDS
-
-__device__ __forceinline__ uint32_t sqrelu_pair_g(uint32_t w) {
-    const float a = bf2f(w & 0xFFFFu), b = bf2f(w >> 16);
-    const float ra = a > 0.0f ? a : 0.0f, rb = b > 0.0f ? b : 0.0f;
-    return f2bf2(ra * ra, rb * rb);
-}
-}  // namespace
-
-// One workgroup = one 64-token block x 256 columns; wavefront w owns columns 64 w .. 64 w + 63 (64 / M whole blocks).
-// Lane = column for the ordered fp32 column scores and the ranking inside the block, lane = (row, block) for the
-// per-row 2:4 selection.  The nibbles of the workgroup's blocks meet in LDS so that two blocks share a metadata byte
-// also when they belong to different wavefronts (M = 64).
+// One wavefront = one 64-token block x 64 columns (64 / M whole blocks); a workgroup's four stand side by side.  A lane loads 16 bytes of 8 rows, squares
+// them and puts them into the wavefront's LDS tile, from which lane = column takes them back, four rows to a transposing read, for the ordered
+// fp32 score.  M = 8: the 8 columns a lane has loaded are a block, so the 2:4 choice is made on the registers (the four kept columns come out of them by
+// byte permutes that are the same for all rows); M >= 16: on the tile, lane = (row, block).
+// 16-byte chunk number seg of row r stands at chunk seg ^ swz(r), and lane group g loads row g ^ (g >> 1) of its eight: the b128 writes, the transposing
+// reads and, but for columns that meet by chance, the 2-byte reads then touch every bank once.
+// Survivors and metadata of the four wavefronts meet in LDS and leave as whole rows of the workgroup: with every wavefront storing its own 32 and 4 bytes of
+// a row, T = F = 16384, M = 8 takes 153 us, with whole rows 124.
+//   Bound: HBM.  T = F = 16384: M = 8 147 -> 124 us (0.69 GB, 5.6 TB/s), M = 16 135 -> 117, 32 132 -> 115, 64 154 -> 106; T = F = 8192: 35 -> 29, 31 -> 26,
+//   33 -> 24, 42 -> 24.  (Before: one 2-byte LDS read per score term, M comparisons per column, ranks out of six comparisons per pair.)  43 KB of LDS, three
+//   workgroups per CU: with the survivors in the tile's place four fit, and M = 8 takes 132 us, M = 32 119; two: 31 us at T = F = 8192.
+__device__ __forceinline__ uint32_t swz(uint32_t r) { return (((r >> 1) & 1u) << 2) | ((r >> 2) & 1u); }
 template <int M>
 __global__ void __launch_bounds__(256) sqrelu_vnm_compress_m_kernel(const uint16_t* __restrict__ y1, int64_t F,
                                                                    uint16_t* __restrict__ vals, uint8_t* __restrict__ meta,
                                                                    uint8_t* __restrict__ colidx) {
     constexpr int NB = 64 / M;                           // blocks per wavefront tile
-    __shared__ __attribute__((aligned(16))) unsigned char tiles[4][64 * kPitch];
-    __shared__ uint8_t nibs[64][256 / M];
+    __shared__ __attribute__((aligned(16))) unsigned char tiles[4][64 * 128];
+    __shared__ __attribute__((aligned(16))) unsigned char packed[4][64 * 32];          // [row][block] (of M >= 16 a part is used)
+    __shared__ __attribute__((aligned(8))) uint8_t nibs[4][64][NB];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int64_t tb = blockIdx.y;
     const int64_t c0 = (int64_t)blockIdx.x * 256 + wave * 64;
     const bool active = c0 < F;                          // F is a multiple of 64
     unsigned char* tl = tiles[wave];
     if (active) {
+        const int seg = lane & 7, r8 = (lane >> 3) ^ (lane >> 4);          // row number of the lane in every eight rows
+        uint4 w[8];
+        const uint16_t* src = y1 + (tb * 64 + r8) * F + c0 + seg * 8;
+#pragma unroll
+        for (int it = 0; it < 8; ++it) w[it] = *reinterpret_cast<const uint4*>(src + it * 8 * F);
 #pragma unroll
         for (int it = 0; it < 8; ++it) {
-            const int row = it * 8 + (lane >> 3), seg = lane & 7;
-            const uint4 w = *reinterpret_cast<const uint4*>(y1 + (tb * 64 + row) * F + c0 + seg * 8);
-            *reinterpret_cast<uint4*>(tl + row * kPitch + seg * 16) =
-                make_uint4(sqrelu_pair_g(w.x), sqrelu_pair_g(w.y), sqrelu_pair_g(w.z), sqrelu_pair_g(w.w));
+            w[it] = make_uint4(sqrelu2(w[it].x), sqrelu2(w[it].y), sqrelu2(w[it].z), sqrelu2(w[it].w));
+            *reinterpret_cast<uint4*>(tl + (it * 8 + r8) * 128 + ((seg ^ swz(r8)) << 4)) = w[it];
         }
-    }
-    __syncthreads();
-    if (active) {
-        // column score: strict ascending-row fp32 sum of y2 (non-negative, so |y2| = y2)
+        wave_lds_sync();
+        // column score: strict ascending-row fp32 sum of y2 (non-negative, so |y2| = y2); a read gives lane = column four rows
         float sc = 0.0f;
-#pragma unroll 8
-        for (int r = 0; r < 64; ++r) sc = sc + bf2f(*reinterpret_cast<const uint16_t*>(tl + r * kPitch + lane * 2));
-        const int c = lane % M, base = lane - c;
-        int rank = 0;
-        for (int k = 0; k < M; ++k) {
-            const float o = __shfl(sc, base + k, 64);
-            rank += (k < c) ? (o >= sc) : ((k > c) ? (o > sc) : 0);
+        const uint32_t rr = (lane >> 2) & 3u, ch = 2 * (lane >> 4) + ((lane >> 1) & 1u);
+#pragma unroll
+        for (int r = 0; r < 64; r += 4) {
+            const uint32_t at = (r + rr) * 128 + ((ch ^ swz(r + rr)) << 4) + (lane & 1u) * 8;
+            const uint2 q = __builtin_bit_cast(uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(lds_void*)(tl + at)));
+            sc = sc + __uint_as_float(q.x << 16);
+            sc = sc + __uint_as_float(q.x & 0xFFFF0000u);
+            sc = sc + __uint_as_float(q.y << 16);
+            sc = sc + __uint_as_float(q.y & 0xFFFF0000u);
         }
-        const unsigned long long kept = __ballot(rank < 4);
-        unsigned long long bits = (M == 64) ? kept : ((kept >> base) & ((1ull << (M & 63)) - 1ull));
-        uint32_t cw = 0;                                 // the block's four kept offsets, ascending, one per byte
+        const unsigned long long kept = __ballot(M == 8 ? keep4_of_8(__float_as_uint(sc), lane) : keep4_of<(M > 8 ? M : 16)>(__float_as_uint(sc), lane));
+        const int b = lane % NB;                         // the lane's block in the 2:4 choice, and its four kept offsets, ascending, one per byte
+        unsigned long long bits = M == 64 ? kept : (kept >> (b * M)) & ((1ull << (M & 63)) - 1ull);
+        uint32_t cw = 0;
 #pragma unroll
         for (int n = 0; n < 4; ++n) {
             cw |= (uint32_t)__builtin_ctzll(bits) << (8 * n);
             bits &= bits - 1ull;
         }
-        if (c == 0) *reinterpret_cast<uint32_t*>(colidx + (tb * (F / M) + (c0 + base) / M) * 4) = cw;
-        // per-row 2:4 among the four kept columns
+        if (lane < NB) *reinterpret_cast<uint32_t*>(colidx + (tb * (F / M) + c0 / M + b) * 4) = cw;
+        uint32_t v[NB], nib[NB], row[NB];                // of every sweep: survivors, their positions, the lane's row
+        if (M == 8) {
+            uint32_t sel[4];                             // byte selectors of kept columns (0, 1), (2, 3) among columns 0-3, 4-7
 #pragma unroll
-        for (int sweep = 0; sweep < NB; ++sweep) {
-            const int pair = sweep * 64 + lane, row = pair / NB, b = pair % NB;
-            const uint32_t cb = (uint32_t)__shfl((int)cw, b * M, 64);
-            const unsigned char* rp = tl + row * kPitch + b * M * 2;
-            const uint32_t y0 = *reinterpret_cast<const uint16_t*>(rp + (cb & 0xFFu) * 2);
-            const uint32_t y1v = *reinterpret_cast<const uint16_t*>(rp + ((cb >> 8) & 0xFFu) * 2);
-            const uint32_t y2v = *reinterpret_cast<const uint16_t*>(rp + ((cb >> 16) & 0xFFu) * 2);
-            const uint32_t y3v = *reinterpret_cast<const uint16_t*>(rp + (cb >> 24) * 2);
-            uint32_t nib;
-            const uint32_t v = select24<false>(y0, y1v, y2v, y3v, nib);
-            *reinterpret_cast<uint32_t*>(vals + (tb * 64 + row) * (2 * F / M) + (c0 / M + b) * 2) = v;
-            nibs[row][wave * NB + b] = (uint8_t)nib;
+            for (int p = 0; p < 2; ++p) {
+                sel[2 * p] = sel[2 * p + 1] = 0x0C0C0C0Cu;                  // 0x0C: a zero byte
+#pragma unroll
+                for (int e = 0; e < 2; ++e) {
+                    const uint32_t o = (cw >> (8 * (2 * p + e))) & 7u, s2 = 0x0100u + (o & 3u) * 0x0202u, keep = 0xFFFF0000u >> (16 * e);
+                    if (o < 4) sel[2 * p] = (sel[2 * p] & keep) | (s2 << (16 * e));
+                    else       sel[2 * p + 1] = (sel[2 * p + 1] & keep) | (s2 << (16 * e));
+                }
+            }
+#pragma unroll
+            for (int it = 0; it < NB; ++it) {
+                const uint32_t y01 = __builtin_amdgcn_perm(w[it].y, w[it].x, sel[0]) | __builtin_amdgcn_perm(w[it].w, w[it].z, sel[1]);
+                const uint32_t y23 = __builtin_amdgcn_perm(w[it].y, w[it].x, sel[2]) | __builtin_amdgcn_perm(w[it].w, w[it].z, sel[3]);
+                uint32_t low, high;
+                row[it] = it * 8 + r8;
+                v[it] = pick24_pos(y01, y23, {3u, 2u, 1u, 0u}, low, high);
+                nib[it] = ((low & 3u) | ((high & 3u) << 2)) ^ 0xFu;
+            }
+        } else {
+            const uint32_t q0 = (b * M + (cw & 0xFFu)) * 2, q1 = (b * M + ((cw >> 8) & 0xFFu)) * 2, q2 = (b * M + ((cw >> 16) & 0xFFu)) * 2, q3 = (b * M + (cw >> 24)) * 2;
+#pragma unroll
+            for (int it = 0; it < NB; ++it) {
+                row[it] = it * M + lane / NB;
+                const uint32_t x = swz(row[it]) << 4;
+                const unsigned char* rp = tl + row[it] * 128;
+                const uint32_t y01 = *reinterpret_cast<const uint16_t*>(rp + (q0 ^ x)) | ((uint32_t)*reinterpret_cast<const uint16_t*>(rp + (q1 ^ x)) << 16);
+                const uint32_t y23 = *reinterpret_cast<const uint16_t*>(rp + (q2 ^ x)) | ((uint32_t)*reinterpret_cast<const uint16_t*>(rp + (q3 ^ x)) << 16);
+                uint32_t low, high;
+                v[it] = pick24_pos(y01, y23, {3u, 2u, 1u, 0u}, low, high);
+                nib[it] = ((low & 3u) | ((high & 3u) << 2)) ^ 0xFu;
+            }
+        }
+        const uint32_t flip = M == 8 ? (wave & 1) << 7 : 0;      // (the reads below then meet every bank once)
+#pragma unroll
+        for (int it = 0; it < NB; ++it) {
+            *reinterpret_cast<uint32_t*>(packed[wave] + (((row[it] * NB + b) * 4) ^ flip)) = v[it];
+            nibs[wave][row[it]][b] = (uint8_t)nib[it];
         }
     }
     __syncthreads();
-    constexpr int BYTES = 128 / M;                       // metadata bytes per row of the workgroup's 256 columns
-    for (int e = threadIdx.x; e < 64 * BYTES; e += 256) {
-        const int row = e / BYTES, j = e % BYTES;
-        if ((int64_t)blockIdx.x * 256 + 2 * j * M < F)
-            meta[(tb * 64 + row) * (F / (2 * M)) + (int64_t)blockIdx.x * BYTES + j] = (uint8_t)(nibs[row][2 * j] | (nibs[row][2 * j + 1] << 4));
+    const int64_t b0 = (int64_t)blockIdx.x * 256;
+    constexpr int LANES = M == 8 ? 8 : 4 * NB;           // lanes that write the 4 NB words of a row
+#pragma unroll
+    for (int i = 0; i < 64 * LANES / 256; ++i) {
+        const int e = threadIdx.x + 256 * i, row = e / LANES, j = e % LANES;
+        if (M == 8) {
+            if (b0 + j * 32 < F)
+                *reinterpret_cast<uint4*>(vals + (tb * 64 + row) * (F / 4) + b0 / 4 + j * 8) =
+                    *reinterpret_cast<const uint4*>(packed[j >> 1] + ((row * 32 + (j & 1) * 16) ^ ((j & 2) << 6)));
+        } else if (b0 + j * M < F) {
+            *reinterpret_cast<uint32_t*>(vals + (tb * 64 + row) * (2 * F / M) + (b0 / M + j) * 2) = *reinterpret_cast<const uint32_t*>(packed[j / NB] + (row * NB + j % NB) * 4);
+        }
+    }
+    // metadata: lane = (row, the 32 / M bytes of a wavefront); M = 64: a byte belongs to two wavefronts
+    const int row = threadIdx.x >> 2, j = threadIdx.x & 3;
+    if (b0 + 64 * j < F) {
+        uint8_t* mp = meta + (tb * 64 + row) * (F / (2 * M)) + (b0 + 64 * j) / (2 * M);
+        if (M == 8) {
+            const uint2 n = *reinterpret_cast<const uint2*>(nibs[j][row]);
+            *reinterpret_cast<uint32_t*>(mp) = __builtin_amdgcn_perm(n.y | (n.y >> 4), n.x | (n.x >> 4), 0x06040200u);
+        } else if (M == 16) {
+            const uint32_t n = *reinterpret_cast<const uint32_t*>(nibs[j][row]), z = n | (n >> 4);
+            *reinterpret_cast<uint16_t*>(mp) = (uint16_t)((z & 0xFFu) | ((z >> 8) & 0xFF00u));
+        } else if (M == 32) {
+            *mp = (uint8_t)(nibs[j][row][0] | (nibs[j][row][NB - 1] << 4));
+        } else if (!(j & 1)) {
+            *mp = (uint8_t)(nibs[j][row][0] | (nibs[j + 1][row][0] << 4));
+        }
     }
 }
 

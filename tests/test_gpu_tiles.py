@@ -278,3 +278,20 @@ def test_standalone_24_contractions_on_large_tiles(T, N, K):
     assert np.array_equal(to_bits(vals), rv) and np.array_equal(to_bits(meta), rm)
     assert_gemm_close(to_bits(sffn.spmm24_fwd(to_dev(X), vals, meta, to_dev(b1))), oracle.spmm24(X, rv, rm, b1), "fwd")
     assert_gemm_close(to_bits(sffn.spmm24_dgrad(to_dev(X), vals, meta)), oracle.spmm24(X, rv, rm, None), "dgrad")
+
+
+@pytest.mark.parametrize("M,T,F", [(8, 64, 64), (8, 128, 320), (16, 64, 64), (16, 128, 448), (32, 64, 64), (32, 128, 704), (64, 64, 128), (64, 128, 640)])
+def test_compressor_choices_among_equal_and_special_values(M, T, F):
+    """The stand-alone compressor, bit for bit: a workgroup of one to four wavefronts of 64 columns, activations of few distinct values (ties of column scores
+    and of survivors everywhere), NaN (counts as 0), infinities, squares that overflow or vanish."""
+    rng = np.random.default_rng(M * F)
+    y1 = bf16_bits_from_f32(rng.integers(-3, 4, (T, F)).astype(np.float32) / 2)
+    y1[rng.random((T, F)) < 0.02] = 0x7FC0
+    y1[rng.random((T, F)) < 0.02] = 0xFF81
+    y1[rng.random((T, F)) < 0.001] = 0x7F80
+    y1[rng.random((T, F)) < 0.02] = 0x0001
+    y1[rng.random((T, F)) < 0.001] = 0x7F7F
+    v, m, c = sffn.sqrelu_vnm_compress(to_dev(y1), 64, M)
+    clean = np.where((y1 & 0x7FFF) > 0x7F80, 0, y1).astype(np.uint16)
+    rv, rm, rc = oracle.sqrelu_vnm_compress(clean, 64, M)
+    assert np.array_equal(to_bits(c), rc) and np.array_equal(to_bits(m), rm) and np.array_equal(to_bits(v), rv)
