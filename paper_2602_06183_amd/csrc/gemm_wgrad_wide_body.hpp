@@ -7,10 +7,14 @@
 // into the accumulator of four v_mfma_f32_32x32x16_bf16 (64 tokens), and writes the result back.  Every element is still summed over the tokens in
 // ascending order in one float32 chain, exactly as when the rows of zeros are multiplied too.  The operands go straight from L2 to registers, four
 // token blocks ahead (no wavefront reads what another one has loaded into LDS, so LDS would only be a detour).
-//   Bound: L2 -> CU delivery ((512 / M x 4 rows + 64 columns) x 128 bytes per token block and 32768-element tile, about 20 bytes per clock and CU)
-//   and the chain read - multiply - write of one wavefront per SIMD; 128 KB of LDS is all the tile there can be.  T = F = 16384, N = 4096:
-//   1390 us before, 860 us at M = 32 and 690 us at M = 64.  At M = 16 the same form took 1300 us, and 103 instead of 94 at T = 4096, N = 2048,
-//   F = 8192 (twice the kept rows, the same bytes from L2 as the dense form), so M = 16 stays with gemm_wgrad_body.hpp.
+//   Bound: the chain load - multiply - write - read of one wavefront per SIMD and the vector loads (1 KB each, 16 clocks of the CU's 64 bytes per clock: 576
+//   of about 830 clocks per token block at M = 32); 128 KB of LDS is all the tile there can be.  T = F = 16384, N = 4096: 1390 us with the
+//   rows of zeros, 815 us at M = 32.  The next token block's LDS addresses are worked out between the matrix instructions of this one: M = 64 (two wavefronts)
+//   690 -> 606 us; T = 4096, N = 2048, F = 8192 58 -> 51; M = 32, bound by the loads, 817 -> 815.
+//   Kept rows through an LDS ring on 256 x 128 tiles (20 KB of loads per token block instead of 32): 8 % slower, every token block then has a barrier; loads
+//   between the matrix instructions: M = 64 6 % slower; 6 or 8 token blocks ahead: the same.
+//   At M = 16 the same form took 1300 us, and 103 instead of 94 at T = 4096, N = 2048, F = 8192 (twice the kept rows, the same bytes from L2 as the dense
+//   form), so M = 16 stays with gemm_wgrad_body.hpp.
 //
 // A comes from the V:N:M epilogues (gemm_v2_body.hpp, VnmEpilogue::at_kept) in the order of the instruction's lanes:
 //   [T / 64][R / 32][4 steps of 16 tokens][64 lanes][8 tokens], R = 4 F / M kept rows, lane = 32 (token / 8 % 2) + row % 32
@@ -102,45 +106,49 @@ __device__ __forceinline__ void wgrad_wide_body(unsigned char* __restrict__ smem
 
     // LDS byte address of accumulator register r: kept row 8 (r / 4) + 4 lh + r % 4 = column offset r % 4 of block 2 (r / 4) + lh
     const uint32_t base = (uint32_t)((wr * 8 + lh) * M * PITCH + wn * 32 + l32) * 4;
-    uint32_t addr[16];
-    auto look_up = [&](const Stage& st) {
-        const uint32_t c[4] = {st.c.x, st.c.y, st.c.z, st.c.w};
+    // (of two token blocks: the next one's are worked out while the matrix instructions of this one run)
+    uint32_t addr[2][16];
+    auto look_up = [&](uint32_t (&to)[16], const Stage& st, int g) {
+        const uint32_t c = g == 0 ? st.c.x : g == 1 ? st.c.y : g == 2 ? st.c.z : st.c.w;
 #pragma unroll
-        for (int r = 0; r < 16; ++r) addr[r] = __umul24((c[r >> 2] >> (8 * (r & 3))) & 0xFFu, PITCH * 4) + (base + (r >> 2) * (2 * M * PITCH * 4));
+        for (int r = 0; r < 4; ++r) to[4 * g + r] = __umul24((c >> (8 * r)) & 0xFFu, PITCH * 4) + (base + g * (2 * M * PITCH * 4));
     };
     f32x16 acc;
-    auto rd = [&] {
+    auto rd = [&](const uint32_t (&at_)[16]) {
 #pragma unroll
-        for (int r = 0; r < 16; ++r) acc[r] = *reinterpret_cast<float*>(smem + addr[r]);
+        for (int r = 0; r < 16; ++r) acc[r] = *reinterpret_cast<float*>(smem + at_[r]);
     };
-    auto wrb = [&] {
+    auto wrb = [&](const uint32_t (&at_)[16]) {
 #pragma unroll
-        for (int r = 0; r < 16; ++r) *reinterpret_cast<float*>(smem + addr[r]) = acc[r];
+        for (int r = 0; r < 16; ++r) *reinterpret_cast<float*>(smem + at_[r]) = acc[r];
     };
 #define SB() __builtin_amdgcn_sched_barrier(0)
     if (nk > 0) {
         Stage st[DEPTH];
 #pragma unroll
         for (int p = 0; p < DEPTH; ++p) load(st[p], p);
-        look_up(st[0]);
-        rd();
-        auto block = [&](int kt, Stage& cur, Stage& nxt) {
 #pragma unroll
-            for (int s = 0; s < 4; ++s) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(cur.a[s].v, cur.b[s].v, acc, 0, 0, 0);
-            SB();
-            wrb(); SB();
-            look_up(nxt);           // (past the last block: the rows of a block that is loaded again, read and not used)
-            rd(); SB();
+        for (int g = 0; g < 4; ++g) look_up(addr[0], st[0], g);
+        rd(addr[0]);
+        auto block = [&](int kt, Stage& cur, Stage& nxt, uint32_t (&here)[16], uint32_t (&next)[16]) {
+#pragma unroll
+            for (int s = 0; s < 4; ++s) {
+                acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(cur.a[s].v, cur.b[s].v, acc, 0, 0, 0); SB();
+                look_up(next, nxt, s); SB();           // (past the last block: the rows of a block that is loaded again, read and not used)
+            }
+            wrb(here); SB();
+            rd(next); SB();
             load(cur, kt + DEPTH); SB();
         };
         int kt = 0;
+        static_assert(DEPTH % 2 == 0, "the two sets of addresses alternate");
         for (; kt + DEPTH <= nk; kt += DEPTH) {
 #pragma unroll
-            for (int p = 0; p < DEPTH; ++p) block(kt + p, st[p], st[(p + 1) % DEPTH]);
+            for (int p = 0; p < DEPTH; ++p) block(kt + p, st[p], st[(p + 1) % DEPTH], addr[p & 1], addr[(p + 1) & 1]);
         }
 #pragma unroll
         for (int p = 0; p < DEPTH - 1; ++p)
-            if (kt + p < nk) block(kt + p, st[p], st[(p + 1) % DEPTH]);
+            if (kt + p < nk) block(kt + p, st[p], st[(p + 1) % DEPTH], addr[p & 1], addr[(p + 1) & 1]);
     }
 #undef SB
     __syncthreads();

@@ -295,3 +295,17 @@ def test_compressor_choices_among_equal_and_special_values(M, T, F):
     clean = np.where((y1 & 0x7FFF) > 0x7F80, 0, y1).astype(np.uint16)
     rv, rm, rc = oracle.sqrelu_vnm_compress(clean, 64, M)
     assert np.array_equal(to_bits(c), rc) and np.array_equal(to_bits(m), rm) and np.array_equal(to_bits(v), rv)
+
+
+@pytest.mark.parametrize("M", [32, 64])
+@pytest.mark.parametrize("blocks", [1, 2, 3, 4, 5, 7])
+def test_kept_row_weight_gradients_over_few_token_blocks(M, blocks):
+    """Every number of token blocks around the four in flight (the two sets of LDS addresses alternate), N that no tile divides."""
+    T, F, N = 64 * blocks, 16 * M, 192
+    rng = np.random.default_rng(M + blocks)
+    y1 = bf16_bits_from_f32(rng.standard_normal((T, F)).astype(np.float32) - np.float32(0.5))
+    G = bf16_bits_from_f32(rng.standard_normal((T, N)).astype(np.float32))
+    packed = oracle.sqrelu_vnm_compress(y1, 64, M)
+    dev = [to_dev(x) for x in packed]
+    for f_major in (True, False):
+        assert_gemm_close(to_bits(sffn.vnm_wgrad(*dev, to_dev(G), f_major, 64, M)), oracle.vnm_wgrad(*packed, G, f_major, 64, M), "wgrad")
