@@ -339,11 +339,12 @@ inline bool sharing_pays(int64_t T, int64_t D, int64_t F, int M, int groups, boo
     const float together = 2.0f * kAlone + kTogether * (2.0f * work(k3) + 2.0f * work(k5) + work(k4)) + kEnd * (longest + more(longest, k4.tile));
     // 0.90: near even the launches by themselves win as often (T = 12928, D = 960, F = 3584, estimated 0.95 of them: 497 us apart, 520 together), and so they do
     // where their rounds are many (codes, T = 8576, D = 3328, F = 10624, estimated 0.91: 1418 / 1458; T = 2816, D = 6080, F = 19456, 0.88: 2702 / 2880).  0.75 where
-    // few tokens meet weights of 30 million elements and more, whose bytes bound either form (T = 128, D = 6784, F = 17408 on codes: 517 / 549; M = 16 never: T = 192,
+    // few tokens meet weights of 30 million elements and more, whose bytes bound either form (T = 128, D = 6784, F = 17408 on codes: 517 / 549); bf16 never from 70
+    // million (T = 256, D = 6528, F = 24064: 1026 / 1067; T = 64, D = 7680, F = 26176 885 / 923; at 30 to 70 million even on average) and never at M = 16 (T = 192,
     // D = 4416, F = 19200 468 / 507).
     const float alone = k4.alone + 2.0f * (k3.alone + k5.alone) + 5.0f * kAlone;
     const bool bytes = D * F >= 30000000 && T < (fp8 ? 192 : M == 8 ? 384 : 640) * e;
-    if (alone > 1200.0f || (bytes && M == 16 && !fp8)) return false;
+    if (alone > 1200.0f || (bytes && !fp8 && (M == 16 || D * F >= 70000000))) return false;
     return together < (bytes ? 0.75f : 0.90f) * alone;
 }
 
