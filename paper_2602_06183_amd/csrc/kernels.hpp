@@ -342,10 +342,12 @@ inline bool sharing_pays(int64_t T, int64_t D, int64_t F, int M, int groups, boo
     // few tokens meet weights of 30 million elements and more, whose bytes bound either form (T = 128, D = 6784, F = 17408 on codes: 517 / 549); bf16 never from 70
     // million (T = 256, D = 6528, F = 24064: 1026 / 1067; T = 64, D = 7680, F = 26176 885 / 923; at 30 to 70 million even on average) and never at M = 16 (T = 192,
     // D = 4416, F = 19200 468 / 507).
+    // 0.80 for bf16 experts of 1024 tokens and more on average, whose rounds are full either way (4 experts, T = 10560, D = 1920, F = 6272, estimated 0.87: 1212 apart,
+    // 1249 together; T = 16128, D = 1024, F = 4160 792 / 780; T = 32000, D = 512, F = 2240 513 / 516); with fewer the estimate holds (8 experts, T = 1856, D = 1856, F = 6848, 0.90: 709 / 619).
     const float alone = k4.alone + 2.0f * (k3.alone + k5.alone) + 5.0f * kAlone;
     const bool bytes = D * F >= 30000000 && T < (fp8 ? 192 : M == 8 ? 384 : 640) * e;
     if (alone > 1200.0f || (bytes && !fp8 && (M == 16 || D * F >= 70000000))) return false;
-    return together < (bytes ? 0.75f : 0.90f) * alone;
+    return together < (bytes ? 0.75f : groups && !fp8 && T >= 1024 * e ? 0.80f : 0.90f) * alone;
 }
 
 // may_share: false where the shared launches are not built for the call
