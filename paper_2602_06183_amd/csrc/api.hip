@@ -81,11 +81,6 @@ inline int place_regions(const sffn_buffers* buf, void* workspace, size_t ws_byt
     return SFFN_OK;
 }
 
-// Weight gradients on the kept rows only (gemm_wgrad_wide_body.hpp), from 768 tokens per expert on: with fewer the matrix work that is saved is
-// less than clearing a tile in LDS and reading it out again (D = 4096, F = 16384, M = 32: 82 us for 73 at 512 tokens, 94 for 94 at 768, 840 for
-// 1390 at 16384).
-int wgrad_on_kept_rows(int64_t T, int64_t F, int M, int64_t experts) { return M >= 32 && F % (8 * M) == 0 && T >= 768 * experts; }
-
 // Blocks of M = 16, 32, 64 columns take the fused path (V:N:M epilogues inside eqs. (1), (4), gathered-row eqs. (3), (7)) when the
 // gathered-row kernel covers the shape and the caller does not ask for the unfused reference path.
 bool fused_wide(const sffn_cfg* c) {

@@ -1,7 +1,9 @@
 // Host-side launchers of the gfx950 kernels (internal to the library).
 #pragma once
 #include <hip/hip_runtime.h>
+#include <math.h>
 #include <stdint.h>
+#include <initializer_list>
 
 namespace sffn {
 
@@ -95,10 +97,9 @@ struct WgradArgs {
     const uint16_t* atc; const uint8_t* kmask; const uint16_t* G; float alpha; int F, N, T; uint16_t* out; int64_t ldo; int tiles_m, tiles_n; GemmGroup grp;
 };
 
-// Tiles of a step's contractions: g = eqs. (1), (4), v = eqs. (3), (7) (v_split workgroups each), w = eqs. (5), (8).  mix: none of them wants the 256 tile (the outputs do not fill
-// the chip), so that the contractions that do not depend on each other share launches (step_mix_*.hip): eqs. (3), (5), (4) in one and eqs. (7), (8) in
-// another (a backward call: eqs. (5), (4), then (7), (8)).  Eq. (4) then takes the 128 tile and its results need operand buffers of their own, since
-// eqs. (3), (5) still read those of eq. (1).
+// Tiles of a step's contractions: g, g_bwd = eqs. (1), (4), v = eqs. (3), (7) (v_split workgroups each), w = eqs. (5), (8).  mix: the contractions that do not depend on each other
+// share launches (sharing_pays, step_mix_*.hip): eqs. (3), (5), (4) in one and eqs. (7), (8) in another (a backward call: eqs. (5), (4), then (7), (8)).  Eq. (4) then takes the 128 tile
+// and its results need operand buffers of their own, since eqs. (3), (5) still read those of eq. (1).
 // v_alone: the tile of eq. (3) where it has a launch of its own all the same (forward calls); the same bits as on v.
 struct StepTiles { int g = 0, g_bwd = 0, v = 0, v_alone = 0, v_split = 1, w = 0; bool mix = false; };
 inline StepTiles step_tiles(int64_t T, int64_t D, int64_t F, int M, int experts, bool fp8, bool may_share = true);
@@ -288,66 +289,83 @@ inline int pick_wgrad_tile(int64_t F, int64_t N, int64_t T, int experts, bool sp
     return pick_tile(large_rounds(tiles(256)), tiles(128), tiles(64), (int)(T / 64 / e), 0.58f, split_ok ? 256 : 0, 12);
 }
 
-// Do eqs. (3), (5), (4) and (7), (8) take less time as two launches than as five?  A launch by itself costs its rounds over the chip, the last one nearly
-// empty as often as not, and `kAlone` to start, fill and drain it; a shared one the sum of its tiles, on tiles of 128, and a part of the longest for its
-// end.  What a round takes (us) is measured: see small_round for eq. (4); eqs. (3), (7) 0.75 a stage on large tiles and 0.58 on two small ones a CU, the weight
-// gradients 1.45 and 0.84 (codes: 0.55 of it), less where a CU has one small tile only; 64 tiles, one per CU, 0.205 and 0.27.  The other constants are fitted to whole steps of 289 shapes
-// (T 64 - 16384, D 256 - 8192, 1 - 8 experts) run both ways: what is chosen takes 0.2 - 0.3 % longer than the better one.
-// T = 1984, D = 1344, F = 4160 168 us apart, 141 together; T = 4288, D = 640, F = 2624 146 / 112; T = 3008, D = 1856, F = 7424 471 / 415; codes, T = 3520,
-// D = 640, F = 2560 121 / 81; T = 4864, D = 384, F = 1408 86 / 78 the other way round: 78 apart.
-inline bool sharing_pays(int64_t T, int64_t D, int64_t F, int M, int groups, bool fp8) {
-    constexpr float kAlone = 9.7f, kTogether = 0.86f, kEnd = 0.23f;
+// Weight gradients on the kept rows only (gemm_wgrad_wide_body.hpp; bf16, launches of their own), from 768 tokens per expert on: with fewer the matrix work that
+// is saved is less than clearing a tile in LDS and reading it out again (D = 4096, F = 16384, M = 32: 82 us for 73 at 512 tokens, 94 for 94 at 768, 840 for 1390 at 16384).
+inline bool wgrad_on_kept_rows(int64_t T, int64_t F, int M, int64_t experts) { return M >= 32 && F % (8 * M) == 0 && T >= 768 * experts; }
+
+// Do eqs. (3), (5), (4) and (7), (8) take less time as two launches than as five?  Both are estimated (us).  A launch by itself takes `start` and its rounds
+// over the chip, 256 large or 512 small tiles at a time (a last round of at most 256 small tiles less than a full one), or the time of the weights' bytes where few
+// tokens meet them.  A shared launch takes the sum of its small tiles spread over the chip and `end` of the last unit's tile; no less than `lone` of a tile behind
+// what comes before it, nor than the bytes of all its units.  Tiles and splits are those that the separate launches have.  Eqs. (5), (8) of bf16 blocks of 32 and
+// 64 columns multiply the kept rows only where they have launches of their own, 8 and 16 times fewer products: M = 64, T = 11520, D = 896, F = 2048 the step 224 us apart,
+// 297 together; T = 7680, D = 832, F = 3072 181 / 222; M = 32, T = 5312, D = 1152, F = 3584 186 / 203; small ones share all the same (M = 64, T = 1280, D = 448,
+// F = 2048 63 / 45).
+// The constants are fitted to the launches and whole steps of 987 shapes (T 64 - 16384, D 256 - 8192, 1 - 8 experts, every M, bf16 and fp8), each run both ways,
+// and held against 480 others: there what is chosen takes 0.25 % longer than the better form (0.30 % in bf16, 0.10 % on codes), one call in 37 4 % and more, the
+// worst 7 %; always sharing would take 2.6 % longer, never 17 %.  T = 1984, D = 1344, F = 4160 167 us apart, 140 together; codes, T = 6848, D = 2304, F = 8192
+// 671 / 686.  Near even the estimate errs either way, mostly where 64 - 256 tokens meet large weights (T = 192, D = 6784, F = 24192 930 / 996, shared) and
+// where experts differ in length, which it does not know (8 of them on codes, T = 1920, D = 512, F = 2176, one of 576 tokens 97 / 101, shared).
+struct StepCosts {
+    struct Line { float fixed, step; float operator()(float steps) const { return fixed + step * steps; } };       // us of a tile, and of it per trip of its main loop
+    float start, end, lone, lone_tall;
+    float bytes3, bytes4, bytes5;                       // us per million weights that eqs. (3) / (7), (4), (5) / (8) read or write
+    Line large4, small4, tall4, tiny4;                  // 256, 128 (two a CU), M = 64: 256 x 128 (two a CU), 64
+    Line large3, small3, tiny3, rows3, tiny_rows3;      // M = 8: 512 x 128 or 256, 128, 64; M >= 16: 64 x 256 (two a CU), 64
+    Line large5, small5, tiny5, kept32, kept64;         // 256, 128, 64; on the kept rows
+};
+constexpr StepCosts kStepBf16 = {2.9f, 0.46f, 0.6f, 0.75f, 0.82f, 0.49f, 0.53f, {10.0f, 0.8f}, {6.4f, 0.56f}, {4.9f, 1.1f}, {7.8f, 0.067f},
+                                 {15.0f, 0.62f}, {2.1f, 0.59f}, {4.5f, 0.13f}, {5.1f, 1.2f}, {4.0f, 0.38f}, {7.1f, 1.3f}, {6.3f, 0.65f}, {5.6f, 0.12f}, {7.1f, 0.26f}, {7.1f, 0.25f}};
+constexpr StepCosts kStepFp8 = {3.8f, 0.39f, 0.64f, 0.63f, 0.5f, 0.38f, 0.55f, {14.0f, 0.86f}, {7.9f, 0.54f}, {9.0f, 0.97f}, {1.9f, 0.15f},
+                                {10.0f, 0.7f}, {3.6f, 0.56f}, {3.9f, 0.26f}, {3.5f, 1.3f}, {4.0f, 0.38f}, {7.0f, 0.67f}, {5.2f, 0.37f}, {3.3f, 0.049f}, {}, {}};
+// t: the tiles of the separate launches; v: that of eqs. (3), (7) in the shared ones (256: the next smaller there)
+inline bool sharing_pays(int64_t T, int64_t D, int64_t F, int M, int groups, bool fp8, const StepTiles& t, int v) {
+    const StepCosts& c = fp8 ? kStepFp8 : kStepBf16;
     const int unit = fp8 ? 128 : 64, e = groups ? groups : 1;
-    const float sg = (float)(D / unit), sv = (float)(M == 8 ? F / unit : 4 * F / M / 64), sw = (float)T / 64.0f / (float)e, code = fp8 ? 0.55f : 1.0f;
+    const float sg = (float)(D / unit), sv = (float)(M == 8 ? F / unit : 4 * F / M / unit), sw = (float)T / 64.0f / (float)e;
     auto across = [](int64_t n, int64_t edge) { return (n + edge - 1) / edge; };
-    auto rounds = [](int64_t n) { return (float)((n + 255) / 256); };
-    auto rounds_small = [](int64_t n, float one_a_cu) { return n <= 256 ? one_a_cu : (float)((n + 511) / 512); };
-    auto least = [](float a, float b) { return a < b ? a : b; };
-    struct Kernel { float alone, tile; int64_t tiles; };                 // by itself; a tile of the shared launch and their number
-    Kernel k4, k3, k5;
-    {
-        const float large = 14.0f + 0.9f * sg * (fp8 ? 1.15f : 1.0f), w = 0.62f + 0.006f * sg, small = large * (w < 0.74f ? w : 0.74f);
-        const int64_t n64 = across(F, 64) * token_tiles(T, groups, 64);
-        k4.tile = small; k4.tiles = across(F, 128) * token_tiles(T, groups, 128);
-        k4.alone = least(rounds(across(F, 256) * token_tiles(T, groups, 256)) * large, rounds_small(k4.tiles, 1.0f) * small);
-        if (n64 <= 256) k4.alone = least(k4.alone, rounds(n64) * (8.0f + 0.55f * sg));
-    }
-    {
-        const int64_t n64 = across(D, 64) * token_tiles(T, groups, 64);
-        if (M == 8) {
-            const float small = 4.0f + 0.58f * sv * (fp8 ? 1.05f : 1.0f);
-            k3.tile = small; k3.tiles = across(D, 128) * token_tiles(T, groups, 128);
-            k3.alone = least(rounds(across(D, 128) * token_tiles(T, groups, 512)) * (4.0f + 0.75f * sv * (fp8 ? 1.1f : 1.0f)), rounds_small(k3.tiles, 0.87f) * small);
-        } else {
-            k3.tile = 4.0f + 0.45f * sv; k3.tiles = across(T, 64) * across(D, 256);
-            k3.alone = (float)across(k3.tiles, 512) * k3.tile;
-        }
-        if (n64 <= 512) k3.alone = least(k3.alone, rounds(n64) * (4.0f + (M == 8 ? 0.205f : 0.35f) * sv));
-        if (M == 8 && n64 <= 256 && sv >= 8.0f) { k3.tile = 4.0f + 0.41f * sv; k3.tiles = n64; }
-    }
-    {
-        const float small = 4.0f + 0.84f * sw * code, tiny = 6.0f + 0.27f * sw * code;
-        const int64_t n64 = e * across(F, 64) * across(D, 64);
-        k5.tile = small; k5.tiles = e * across(F, 128) * across(D, 128);
-        k5.alone = least(rounds(e * across(F, 256) * across(D, 256)) * (4.0f + 1.45f * sw * code), rounds_small(k5.tiles, 0.66f) * small);
-        if (n64 <= 256) k5.alone = least(k5.alone, rounds(n64) * tiny);
-        if (n64 <= 256 && sw >= 12.0f) { k5.tile = 2.0f * tiny; k5.tiles = n64; }
-    }
-    auto work = [](const Kernel& k) { return (float)k.tiles * k.tile / 512.0f; };
+    auto large = [](int64_t n) { return (float)((n + 255) / 256); };
+    auto small = [](int64_t n, float last) { const int64_t rest = n % 512; return (float)(n / 512) + (rest == 0 ? 0.0f : rest <= 256 ? last : 1.0f); };
     auto more = [](float a, float b) { return a > b ? a : b; };
-    const float longest = more(k3.tile, k5.tile);
-    const float together = 2.0f * kAlone + kTogether * (2.0f * work(k3) + 2.0f * work(k5) + work(k4)) + kEnd * (longest + more(longest, k4.tile));
-    // 0.90: near even the launches by themselves win as often (T = 12928, D = 960, F = 3584, estimated 0.95 of them: 497 us apart, 520 together), and so they do
-    // where their rounds are many (codes, T = 8576, D = 3328, F = 10624, estimated 0.91: 1418 / 1458; T = 2816, D = 6080, F = 19456, 0.88: 2702 / 2880).  0.75 where
-    // few tokens meet weights of 30 million elements and more, whose bytes bound either form (T = 128, D = 6784, F = 17408 on codes: 517 / 549); bf16 never from 70
-    // million (T = 256, D = 6528, F = 24064: 1026 / 1067; T = 64, D = 7680, F = 26176 885 / 923; at 30 to 70 million even on average) and never at M = 16 (T = 192,
-    // D = 4416, F = 19200 468 / 507).
-    // 0.80 for bf16 experts of 1024 tokens and more on average, whose rounds are full either way (4 experts, T = 10560, D = 1920, F = 6272, estimated 0.87: 1212 apart,
-    // 1249 together; T = 16128, D = 1024, F = 4160 792 / 780; T = 32000, D = 512, F = 2240 513 / 516); with fewer the estimate holds (8 experts, T = 1856, D = 1856, F = 6848, 0.90: 709 / 619).
-    const float alone = k4.alone + 2.0f * (k3.alone + k5.alone) + 5.0f * kAlone;
-    const bool bytes = D * F >= 30000000 && T < (fp8 ? 192 : M == 8 ? 384 : 640) * e;
-    if (alone > 1200.0f || (bytes && !fp8 && (M == 16 || D * F >= 70000000))) return false;
-    return together < (bytes ? 0.75f : groups && !fp8 && T >= 1024 * e ? 0.80f : 0.90f) * alone;
+    struct Unit { float tile; int64_t tiles; float lone; };             // of the shared launches
+    const float weights = (float)(D * F * e) * 1e-6f;
+    float alone3, alone4, alone5;
+    Unit u3, u4, u5;
+    {
+        const int64_t n = across(F, M == 64 ? 256 : 128) * token_tiles(T, groups, 128);
+        u4 = {M == 64 ? c.tall4(sg) : c.small4(sg), n, M == 64 ? c.lone_tall : c.lone};
+        alone4 = t.g_bwd == 256 ? large(across(F, 256) * token_tiles(T, groups, 256)) * c.large4(sg)
+               : t.g_bwd == 128 ? small(n, 0.68f) * u4.tile : large(across(F, 64) * token_tiles(T, groups, 64)) * c.tiny4(sg);
+    }
+    float rows = 1.0f;                                                  // the part of the weights that any token block keeps
+    if (M == 8) {
+        const int64_t n = across(D, 128) * token_tiles(T, groups, 128), n64 = across(D, 64) * token_tiles(T, groups, 64);
+        const float n512 = 0.93f * large(across(D, 128) * token_tiles(T, groups, 512)), n256 = large(across(D, 256) * token_tiles(T, groups, 256));
+        alone3 = t.v == 256 ? (n512 < n256 ? n512 : n256) * c.large3(sv) : t.v == 128 ? small(n, 0.69f) * c.small3(sv) : large(n64 * t.v_split) * c.tiny3(sv / (float)t.v_split);
+        u3 = v == 64 ? Unit{2.0f * c.tiny3(sv), n64, c.lone} : Unit{c.small3(sv), n, c.lone};
+    } else {
+        const int64_t n = T / 64 * across(D, 256), n64 = T / 64 * across(D, 64);
+        alone3 = t.v == 256 ? small(n, 0.66f) * c.rows3(sv) : large(n64 * t.v_split) * c.tiny_rows3(sv / (float)t.v_split);
+        u3 = v == 64 ? Unit{2.0f * c.tiny_rows3(sv), n64, c.lone} : Unit{c.rows3(sv), n, c.lone};
+        rows -= powf(1.0f - 4.0f / (float)M, more(sw, 1.0f));
+    }
+    {
+        const int64_t n = e * across(F, 128) * across(D, 128), n64 = e * across(F, 64) * across(D, 64);
+        if (!fp8 && wgrad_on_kept_rows(T, F, M, e)) alone5 = large(e * across(F, 512) * across(D, 64)) * (M == 32 ? c.kept32(sw) : c.kept64(sw));
+        else alone5 = t.w == 256 ? large(e * across(F, 256) * across(D, 256)) * c.large5(sw) : t.w == 128 ? small(n, 0.6f) * c.small5(sw) : large(n64) * c.tiny5(sw);
+        u5 = t.w == 64 ? Unit{2.0f * c.tiny5(sw), n64, c.lone} : Unit{c.small5(sw), n, c.lone};
+    }
+    if (t.v_split > 1) alone3 += 1.5f;
+    const float b3 = c.bytes3 * weights * rows, b4 = c.bytes4 * weights, b5 = c.bytes5 * weights;
+    auto shared = [&](std::initializer_list<Unit> units, float bytes) {
+        float before = 0.0f, last = 0.0f;
+        for (const Unit& u : units) {
+            const float work = (float)u.tiles * u.tile / 512.0f;
+            last = more(last, before + more(u.lone * u.tile, work + c.end * u.tile));
+            before += work;
+        }
+        return c.start + more(last, 1.1f * bytes);           // (no launch moves all its units' bytes at the best rate of each)
+    };
+    return shared({u3, u5, u4}, b3 + b4 + b5) + shared({u3, u5}, b3 + b5) < 5.0f * c.start + more(alone4, b4) + 2.0f * (more(alone3, b3) + more(alone5, b5));
 }
 
 // may_share: false where the shared launches are not built for the call
@@ -362,17 +380,15 @@ inline StepTiles step_tiles(int64_t T, int64_t D, int64_t F, int M, int experts,
     const SplitPlan v = M == 8 ? plan_vnm8(T, D, (int)(F / unit), g.n, fp8) : fp8 ? SplitPlan{256, 1} : plan_gather(T, D, (int)(4 * F / M / 64), g.n);
     t.v = M == 8 ? pick_vnm8_tile(T, D, (int)(F / unit), g.n, fp8) : fp8 ? 256 : pick_gather_tile(T, D, (int)(4 * F / M / 64));
     t.w = pick_wgrad_tile(F, D, T, experts > 1 ? experts : 0, M == 8 || fp8);
-    // Where eqs. (3), (7) would be shared by several workgroups per tile, and on wide bf16 blocks of more than 16 columns (whose weight gradients by
-    // themselves may run on the kept rows): where no contraction wants the large tile.  (0.56: in a shared launch the small tiles pay where eqs. (1), (4) by
-    // themselves would be even)
-    if (v.n > 1 || (M > 16 && !fp8)) t.mix = may_share && pick_gemm_tile(F, T, steps, g, 0.56f, true) != 256 && t.w != 256 && (M != 8 || t.v != 256);
-    else t.mix = may_share && sharing_pays(T, D, F, M, g.n, fp8);
+    const int v_shared = t.v;
+    t.v = v.tile; t.v_split = v.n;
+    t.mix = may_share && sharing_pays(T, D, F, M, g.n, fp8, t, v_shared);
+    t.v_alone = t.mix ? v_shared : v.tile;
     if (t.mix) {
         t.g_bwd = 128;
-        t.v_alone = t.v;
-        if (M == 8 && t.v == 256) t.v = 128;
+        t.v = M == 8 && v_shared == 256 ? 128 : v_shared; t.v_split = 1;
         if (t.w == 256) t.w = 128;
-    } else { t.v = t.v_alone = v.tile; t.v_split = v.n; }
+    }
     return t;
 }
 

@@ -1,5 +1,7 @@
 """The host-side rules that choose a contraction's output tile (kernels.hpp), against measured times of every tile (tests/golden/tile_times.txt): over
-the calls of a group, what the rules choose takes at most 4 % longer than the best tile of each call (where not said otherwise), and no call a third longer."""
+the calls of a group, what the rules choose takes at most 4 % longer than the best tile of each call (where not said otherwise), and no call a third longer.
+The rule that has a step's contractions share launches, against whole steps timed both ways (tests/golden/step_times.txt)."""
+import math
 import os
 import subprocess
 
@@ -9,13 +11,23 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 TILES = (256, 128, 64)
 
 
+def golden(name):
+    return [line.strip().split(" | ") for line in open(os.path.join(HERE, "golden", name)) if not line.startswith("#")]
+
+
 @pytest.fixture(scope="module")
-def chosen(tmp_path_factory):
-    """[(call, its measured times, what the rules print for it)]"""
-    calls = [line.strip().split(" | ") for line in open(os.path.join(HERE, "golden", "tile_times.txt")) if not line.startswith("#")]
+def rules(tmp_path_factory):
+    """calls -> the lines that the rules print for them"""
     exe = str(tmp_path_factory.mktemp("tiles") / "tile_rules")
     subprocess.run(["g++", "-std=c++17", "-O1", "-w", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include", os.path.join(HERE, "tile_rules.cpp"), "-o", exe], check=True)
-    out = subprocess.run([exe], input="\n".join(c[0] for c in calls), capture_output=True, text=True, check=True).stdout.split("\n")
+    return lambda calls: subprocess.run([exe], input="\n".join(calls), capture_output=True, text=True, check=True).stdout.split("\n")
+
+
+@pytest.fixture(scope="module")
+def chosen(rules):
+    """[(call, its measured times, what the rules print for it)]"""
+    calls = golden("tile_times.txt")
+    out = rules([c[0] for c in calls])
     times = [{t.split()[0]: {e: float(v) for e, v in zip(TILES, t.split()[1:]) if v != "-"} for t in c[1:]} if not c[0].startswith("split") else
              {int(t.split(":")[0]): float(t.split(":")[1]) for t in c[1].split()} for c in calls]
     return [(c[0].split(), t, [int(v) for v in o.split()]) for c, t, o in zip(calls, times, out)]
@@ -30,15 +42,15 @@ def check(rows, most=1.34, total=1.04):
 
 
 def steps(chosen, fp8, grouped, tall=False):
-    """Calls of the step, not those whose contractions share launches."""
-    return [(t, o) for c, t, o in chosen if c[0] == "step" and c[1] == str(int(fp8)) and (c[5] != "1") == grouped and (c[2] == "64") == tall and not o[4]]
+    """Calls of the step; the tiles are those of launches of their own, also where the rules have the step's contractions share launches."""
+    return [(t, o) for c, t, o in chosen if c[0] == "step" and c[1] == str(int(fp8)) and (c[5] != "1") == grouped and (c[2] == "64") == tall]
 
 
 @pytest.mark.parametrize("tall", [False, True])
 def test_tiles_of_the_epilogue_contractions(chosen, tall):
     rows = steps(chosen, False, False, tall)
     check([(t["eq1"], o[0]) for t, o in rows])
-    check([(t["eq4"], o[1]) for t, o in rows])
+    check([(t["eq4"], o[1]) for t, o in rows if "eq4" in t])
 
 
 @pytest.mark.parametrize("M", [(8,), (16, 32), (64,)])
@@ -48,7 +60,7 @@ def test_tiles_of_the_epilogue_contractions_by_type_and_width(chosen, fp8, M):
     rows = [(t, o) for c, t, o in chosen if c[0] == "step" and c[1] == str(int(fp8)) and int(c[2]) in M and c[5] == "1"]
     big = lambda t: {e: t[e] for e in (256, 128) if e in t}
     check([(big(t["eq1"]), o[0]) for t, o in rows if o[0] != 64], 1.05, 1.02)
-    check([(big(t["eq4"]), o[1]) for t, o in rows if "eq4" in t and o[1] != 64 and not o[4]], 1.05, 1.02)
+    check([(big(t["eq4"]), o[1]) for t, o in rows if "eq4" in t and o[1] != 64], 1.05, 1.02)
 
 
 def test_tiles_of_the_plain_contractions(chosen):
@@ -83,3 +95,17 @@ def test_splits_of_the_activation_contractions(chosen):
     rows = [(t, min(t, key=lambda n: abs(n - o[0]))) for c, t, o in chosen if c[0] == "split"]       # (the nearest number that was measured)
     assert len(rows) >= 8 and all(t[n] <= 1.04 * t[1] for t, n in rows), rows
     assert sum(t[n] for t, n in rows) <= 0.95 * sum(t[1] for t, _ in rows), rows
+
+
+def test_shared_launches_of_the_step(rules):
+    """The form that is chosen takes 0.4 % longer than the better one on average (two runs of one form differ by 1 - 2 %), no more than 1 % in any group of calls,
+    and nowhere 10 % (one call in 35 takes 4 % and more)."""
+    calls = golden("step_times.txt")
+    assert len(calls) >= 480
+    losses = {}
+    for (call, times), share in zip(calls, rules(["share " + c[0] for c in calls])):
+        shared, apart = map(float, times.split())
+        losses.setdefault(tuple(call.split()[:2]) + (call.split()[4] != "1",), []).append(math.log((shared if share == "1" else apart) / min(shared, apart)))
+    every = [x for group in losses.values() for x in group]
+    assert sum(every) <= 0.004 * len(every) and max(every) <= 0.10 and sum(x > 0.04 for x in every) <= len(every) / 35, (sum(every) / len(every), max(every))
+    assert all(sum(group) <= 0.01 * len(group) for group in losses.values()), {k: sum(v) / len(v) for k, v in losses.items()}

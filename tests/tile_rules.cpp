@@ -1,5 +1,6 @@
 // Prints what the host-side tile rules (kernels.hpp) choose, for tests/test_tile_rules.py.  One line of standard input is one call:
-//   step <fp8> <M> <D> <F> <experts> <offset 0> ... <offset n>   -> tiles of eq. (1), eq. (4), eqs. (3), (7), weight gradients; shared launches
+//   step <fp8> <M> <D> <F> <experts> <offset 0> ... <offset n>   -> tiles of eq. (1), eq. (4), eqs. (3), (7), weight gradients in launches of their own; do they share
+//   share <fp8> <M> <D> <F> <experts> <T>                        -> do they share launches
 //   router <M> <D> <F> <T>                                       -> tile of its eqs. (1), (4)
 //   split <T> <N> <F>                                            -> workgroups per tile of eq. (3) at M = 8
 //   plain <T> <N> <K>                                            -> tile of a 2:4 contraction with a plain store
@@ -34,13 +35,19 @@ int main() {
             printf("%d\n", pick_gemm_tile(4 * c / a, (d + 63) / 64 * 64 + 16 * a, steps, g, small_round(kGemmRouter, steps), true, last_round(kGemmRouter, steps)));
             continue;
         }
+        if (!strcmp(what, "share")) {
+            long T;
+            if (scanf("%ld %ld %ld %ld %ld %ld", &a, &b, &c, &d, &e, &T) != 6) return 1;
+            printf("%d\n", (int)step_tiles(T, c, d, (int)b, (int)e, a != 0).mix);
+            continue;
+        }
         if (scanf("%ld %ld %ld %ld %ld", &a, &b, &c, &d, &e) != 5 || e > GemmGroup::kMaxExperts) return 1;
         GemmGroup g;
         g.n = e > 1 ? (int)e : 0;
         for (int i = 0; i <= e; ++i) if (scanf("%d", &g.seg[i]) != 1) return 1;
-        StepTiles t = step_tiles(g.seg[e], c, d, (int)b, (int)e, a != 0);
+        StepTiles t = step_tiles(g.seg[e], c, d, (int)b, (int)e, a != 0, false);
         refine_tiles(&t, c, d, (int)b, g, a != 0);
-        printf("%d %d %d %d %d\n", t.g, t.g_bwd, t.v, t.w, (int)t.mix);
+        printf("%d %d %d %d %d\n", t.g, t.g_bwd, t.v, t.w, (int)step_tiles(g.seg[e], c, d, (int)b, (int)e, a != 0).mix);
     }
     return 0;
 }
