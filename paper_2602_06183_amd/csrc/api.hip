@@ -1214,7 +1214,7 @@ static int run_step(const sffn_cfg* cfg, int n_experts, const int64_t* seg, cons
         const bool together = tiles.mix || prologue_together(T, D, F, E);
         PrologueArgs part[3];
         split_prologue(pro, part);
-        const bool x_as_is = fwd && forward_reads_x(T, D, E * F, packed, tiles.g);
+        const bool x_as_is = fwd && forward_reads_x(T, D, E * F, cfg->M, packed, tiles.g);
         PrologueArgs behind = together ? pro : part[0];
         if (x_as_is) split_off_eq1(&pro, &behind);
         if (together) STAGE(launch_step_prologue(pro, s), "step/prologue");
@@ -1337,7 +1337,7 @@ static int run_step(const sffn_cfg* cfg, int n_experts, const int64_t* seg, cons
     const bool together = tiles.mix || prologue_together(T, D, F, E);
     PrologueArgs part[3];
     split_prologue(pro, part);
-    const bool x_as_is = fwd && forward_reads_x(T, D, E * F, packed, tiles.g);
+    const bool x_as_is = fwd && forward_reads_x(T, D, E * F, cfg->M, packed, tiles.g);
     PrologueArgs behind = together ? pro : part[0];
     if (x_as_is) split_off_eq1(&pro, &behind);
     if (together) STAGE(launch_step_prologue(pro, s), "step/prologue");

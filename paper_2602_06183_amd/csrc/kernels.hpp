@@ -126,13 +126,18 @@ hipError_t launch_step_prologue(const PrologueArgs& a, hipStream_t s);
 // Eq. (1) with X row-major and the passes `behind` in the same launch (forward_x.hip); tile 64 or 128.
 hipError_t launch_forward_x(const uint16_t* a_vals, const uint8_t* a_meta, const float* bias, const uint16_t* X, uint16_t* out, const VnmEpilogue& ep,
                             const PrologueArgs& behind, hipStream_t s, const GemmGroup* grp, int tile);
-// Taken on both: what the row-major rows cost the loop (128-byte lines instead of 1 KB blocks) is less than a launch in front of it.  T = 64, D = 2048, F = 8192 (a
-// forward call on packed weights) 28.9 us with the copy of X, 25.7 without; T = 1024 84.8 / 78.3; T = 4096, D = 256, F = 1024 22.1 / 18.4; T = 16384, D = 256,
-// F = 1024, the other end, 36.3 / 36.8; M = 64, T = 4096, D = 512, F = 2048 25.4 / 21.2.
+// Taken on both: what the row-major rows cost the loop (128-byte lines instead of 1 KB blocks) is less than a launch in front of it.  Forward calls on packed weights, 160
+// shapes 0.88 of the time with the copy of X, none above 1.00: T = 64, D = 2048, F = 8192 40.7 us with the copy, 37.7 without; T = 4096, D = 256, F = 1024 22.1 / 17.9; T = 16320,
+// D = 704, F = 2304, M = 16 101 / 97; M = 64, T = 4096, D = 512, F = 2048 27.3 / 20.6.  But the 64 tile of M = 64 (128 hidden units to a wavefront, two stages) does
+// not cover the longer loads where the weights do not come from L2 (T = 64, F = 6144, D = 3072 37.0 / 36.3, D = 3584 41.8 / 43.2; F = 8192, D = 2560 38.2 / 41.3; T = 128, F = 4096,
+// D = 3328 38.5 / 36.5, D = 4352 45.0 / 46.3).
 // With weights to prune up to 6 Mi elements of tokens and weights, 3.5 Mi on 64 tiles: behind the tiles the pass over W2 runs two workgroups a CU (64 tiles: one),
 // which is less than its rate alone.  A whole step: T = 512, D = 448, F = 1728 38 / 35 us; T = 64, D = 768, F = 2880 44 / 41; T = 128, D = 1088, F = 4096, M = 64
 // 61 / 64; T = 128, D = 1216, F = 5120, M = 16 53 / 58; T = 128, D = 1856, F = 6080 86 / 98.
-inline bool forward_reads_x(int64_t T, int64_t D, int64_t F, bool packed, int tile) { return tile != 256 && (packed || (T + F) * D <= ((int64_t)(tile == 64 ? 7 : 12) << 19)); }
+inline bool forward_reads_x(int64_t T, int64_t D, int64_t F, int M, bool packed, int tile) {
+    if (tile == 256 || (M == 64 && tile == 64 && (T + 64) * D * F > 2650000000)) return false;
+    return packed || (T + F) * D <= ((int64_t)(tile == 64 ? 7 : 12) << 19);
+}
 // The same for the fp8 step (prologue_fp8.hip).  t_codes: xt, dyt as codes instead of bf16.  Canonical codes / metadata (w1c, w1m, w2c, w2m) may be null.
 // amax_*: one float per workgroup of the part (fp8_parts: x and dy have as many), slots_*: the epilogues' slots, cleared by the parts over X / dY; null: not wanted.
 struct Fp8PrologueArgs {

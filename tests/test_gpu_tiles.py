@@ -226,6 +226,7 @@ def test_grouped_step_on_tiles_of_512_tokens(fp8, D, F):
     (16, 64, 1088, 2048, None), (16, 832, 320, 1024, None), (32, 64, 2048, 1024, None), (32, 832, 320, 1024, None),
     (64, 64, 1088, 3072, None), (64, 832, 320, 2048, None),                 # tiles of 128 and 256 hidden units
     (64, 576, 320, 2048, [0, 64, 64, 256, 576]),
+    (64, 64, 3072, 6144, None), (64, 64, 3584, 6144, None),                 # either side of the line to weights that L2 does not hold: the second copies X
 ])
 def test_forward_call_on_packed_weights_reads_x_as_it_is(M, T, D, F, seg):
     """The same bits as the call that copies X into blocks, in Y3 and, through the backward call, in all gradients (X.T)."""

@@ -3,6 +3,7 @@
 //   share <fp8> <M> <D> <F> <experts> <T>                        -> do they share launches
 //   router <M> <D> <F> <T>                                       -> tile of its eqs. (1), (4)
 //   split <T> <N> <F>                                            -> workgroups per tile of eq. (3) at M = 8
+//   rowx <M> <D> <F> <T>                                         -> does a forward call on packed weights read X as it is (-1: the tile does not)
 //   plain <T> <N> <K>                                            -> tile of a 2:4 contraction with a plain store
 #include <stdio.h>
 #include <string.h>
@@ -19,6 +20,12 @@ int main() {
             if (scanf("%ld %ld %ld", &a, &b, &c) != 3) return 1;
             const int steps = (int)(c / 64);
             printf("%d\n", pick_gemm_tile(b, a, steps, GemmGroup(), small_round(kGemmPlain, steps), true, last_round(kGemmPlain, steps)));
+            continue;
+        }
+        if (!strcmp(what, "rowx")) {
+            if (scanf("%ld %ld %ld %ld", &a, &b, &c, &d) != 4) return 1;
+            const int tile = step_tiles(d, b, c, (int)a, 1, false).g;
+            printf("%d\n", tile == 256 ? -1 : (int)forward_reads_x(d, b, c, (int)a, true, tile));
             continue;
         }
         if (!strcmp(what, "split")) {
