@@ -306,10 +306,11 @@ inline bool wgrad_on_kept_rows(int64_t T, int64_t F, int M, int64_t experts) { r
 // 297 together; T = 7680, D = 832, F = 3072 181 / 222; M = 32, T = 5312, D = 1152, F = 3584 186 / 203; small ones share all the same (M = 64, T = 1280, D = 448,
 // F = 2048 63 / 45).
 // The constants are fitted to the launches and whole steps of 987 shapes (T 64 - 16384, D 256 - 8192, 1 - 8 experts, every M, bf16 and fp8), each run both ways,
-// and held against 480 others: there what is chosen takes 0.25 % longer than the better form (0.30 % in bf16, 0.10 % on codes), one call in 37 4 % and more, the
-// worst 7 %; always sharing would take 2.6 % longer, never 17 %.  T = 1984, D = 1344, F = 4160 167 us apart, 140 together; codes, T = 6848, D = 2304, F = 8192
-// 671 / 686.  Near even the estimate errs either way, mostly where 64 - 256 tokens meet large weights (T = 192, D = 6784, F = 24192 930 / 996, shared) and
-// where experts differ in length, which it does not know (8 of them on codes, T = 1920, D = 512, F = 2176, one of 576 tokens 97 / 101, shared).
+// and held against 480 others: there what is chosen takes 0.29 % longer than the better form (0.32 % in bf16, 0.19 % on codes), one call in 32 4 % and more, the
+// worst 15 %; always sharing would take 2.6 % longer, never 17 %.  Forward and backward calls after one another: 0.21 % longer, the worst 9 %.  T = 1984, D = 1344,
+// F = 4160 167 us apart, 140 together; codes, T = 6848, D = 2304, F = 8192 671 / 686.  Near even the estimate errs either way, mostly where 64 - 256 tokens meet large
+// weights (T = 256, D = 3648, F = 11648 282 / 300, shared) and where experts differ in length, which it does not know (8 of them on codes, T = 1920, D = 512, F = 2176,
+// one of 576 tokens 97 / 101, shared); the worst have splits to lose (see step_tiles).
 struct StepCosts {
     struct Line { float fixed, step; float operator()(float steps) const { return fixed + step * steps; } };       // us of a tile, and of it per trip of its main loop
     float start, end, lone, lone_tall;
@@ -387,7 +388,11 @@ inline StepTiles step_tiles(int64_t T, int64_t D, int64_t F, int M, int experts,
     t.w = pick_wgrad_tile(F, D, T, experts > 1 ? experts : 0, M == 8 || fp8);
     const int v_shared = t.v;
     t.v = v.tile; t.v_split = v.n;
-    t.mix = may_share && sharing_pays(T, D, F, M, g.n, fp8, t, v_shared);
+    // Shared launches do not split eqs. (3), (7), and calls of either pass alone have to sum as the whole step does: a forward call would lose its split (T = 64, D = 2048,
+    // F = 6784: the step 89 us apart, 84 together, a forward call on packed weights 25 and 34).  So steps with splits share only where no contraction wants the large tile,
+    // which is where they gain most (T = 64, D = 960, F = 4224: 62 / 47, the forward call 21 / 23).
+    const bool loses_split = v.n > 1 && (t.w == 256 || pick_gemm_tile(F, T, steps, g, 0.56f, true) == 256);
+    t.mix = may_share && !loses_split && sharing_pays(T, D, F, M, g.n, fp8, t, v_shared);
     t.v_alone = t.mix ? v_shared : v.tile;
     if (t.mix) {
         t.g_bwd = 128;

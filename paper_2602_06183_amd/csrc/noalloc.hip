@@ -12,8 +12,8 @@ namespace {
 // The workspace itself.  In host code this name is only a stand-in for the device symbol: its device address is obtained
 // once per device with hipGetSymbolAddress (below) and only that address is ever handed to kernels.
 // (11 MiB on top of the documented limit: the operand buffer of shared launches, T F bytes, and the sums of contractions that several workgroups share do
-// not count towards it; a step has one of the two or neither.  Of the shapes within the limit T = 2496, D = 64, F = 4608 without the canonical copies
-// needs most, 42.97 MiB in all.)
+// not count towards it; a step has one of the two or neither.  Of the shapes within the limit T = 3200, D = 64, F = 3584 without the canonical copies
+// needs most, 42.93 MiB in all.)
 constexpr size_t kScratchBytes = (size_t)SFFN_NOALLOC_WORKSPACE_MAX + (11u << 20);
 static __device__ __align__(256) unsigned char scratch[kScratchBytes];
 
