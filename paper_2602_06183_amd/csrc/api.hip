@@ -479,9 +479,6 @@ int vnm_spmm_fp8(const uint8_t* a_codes, const uint8_t* a_meta, const uint8_t* a
     return SFFN_OK;
 }
 
-// The step's preparing passes: all in one launch while X, dY, W1 and W2 together stay below 96 MiB, else in three parts (X and W1 | W2 | dY)
-static inline bool prologue_together(int64_t T, int64_t D, int64_t F, int64_t E) { return 2 * (2 * T * D + 2 * E * F * D) < ((int64_t)96 << 20); }
-
 // ---- the training step with fp8 operands in eqs. (1), (3), (4), (7) (Section 3.4, closing paragraph) ---------------------------
 namespace {
 struct Fp8Layout {

@@ -123,6 +123,8 @@ struct PrologueArgs {
     unsigned* counters;             // kSplitCounters of them are cleared, or null
 };
 hipError_t launch_step_prologue(const PrologueArgs& a, hipStream_t s);
+// The step's preparing passes: all in one launch while X, dY, W1 and W2 together stay below 96 MiB, else in three parts (X and W1 | W2 | dY)
+inline bool prologue_together(int64_t T, int64_t D, int64_t F, int64_t E) { return 2 * (2 * T * D + 2 * E * F * D) < ((int64_t)96 << 20); }
 // Eq. (1) with X row-major and the passes `behind` in the same launch (forward_x.hip); tile 64 or 128.
 hipError_t launch_forward_x(const uint16_t* a_vals, const uint8_t* a_meta, const float* bias, const uint16_t* X, uint16_t* out, const VnmEpilogue& ep,
                             const PrologueArgs& behind, hipStream_t s, const GemmGroup* grp, int tile);

@@ -218,31 +218,59 @@ def test_grouped_step_on_tiles_of_512_tokens(fp8, D, F):
     test_grouped_step_on_tiles_chosen_by_the_segments(fp8, 8, D, F, [0, 128, 128, 768, 2240])
 
 
-@pytest.mark.parametrize("M,T,D,F,seg", [
-    (8, 64, 64, 64, None),          # the smallest
-    (8, 64, 1088, 2112, None),      # 64 tiles, a half-empty stage round of their four wavefronts
-    (8, 832, 320, 576, None),       # 128 tiles, half-empty in both dimensions
-    (8, 576, 320, 640, [0, 64, 64, 256, 576]),
-    (16, 64, 1088, 2048, None), (16, 832, 320, 1024, None), (32, 64, 2048, 1024, None), (32, 832, 320, 1024, None),
-    (64, 64, 1088, 3072, None), (64, 832, 320, 2048, None),                 # tiles of 128 and 256 hidden units
-    (64, 576, 320, 2048, [0, 64, 64, 256, 576]),
-    (64, 64, 3072, 6144, None), (64, 64, 3584, 6144, None),                 # either side of the line to weights that L2 does not hold: the second copies X
-])
-def test_forward_call_on_packed_weights_reads_x_as_it_is(M, T, D, F, seg):
-    """The same bits as the call that copies X into blocks, in Y3 and, through the backward call, in all gradients (X.T)."""
-    gen = torch.Generator(device="cuda")
-    gen.manual_seed(51)
-    randn = lambda *shape: torch.randn(shape, dtype=torch.bfloat16, device="cuda", generator=gen)  # noqa: E731
-    lead = (len(seg) - 1,) if seg else ()
-    X, dY, W1, W2 = randn(T, D), randn(T, D), randn(*lead, F, D).mul_(0.02), randn(*lead, D, F).mul_(0.02)
-    b1 = torch.full(lead + (F,), -0.5 * 0.02 * D ** 0.5, device="cuda")
-    new = (lambda: sffn.FfnStepGrouped(seg, D, F, M=M)) if seg else (lambda: sffn.FfnStep(T, D, F, M=M))  # noqa: E731
-    a, b = new(), new()
-    want = [a.forward(X, W1, W2, b1), *a.backward(W1, dY)]
-    b.forward(dY, W1, W2, b1)               # packs the weights; another X
-    got = [b.forward(X, W1, W2, b1, weights_packed=True), *b.backward(W1, dY)]
+# (M, T, D, F, segments of experts; eq. (1): its tile, does it read X as it is on packed weights, does it on others; are the preparing passes one launch)
+FORWARD_CALLS = [
+    (8, 64, 64, 64, None, 128, 1, 1, 1),            # the smallest
+    (8, 64, 1088, 2112, None, 64, 1, 1, 1),         # 64 tiles, a half-empty stage round of their four wavefronts
+    (8, 832, 320, 576, None, 128, 1, 1, 1),         # 128 tiles, half-empty in both dimensions
+    (8, 576, 320, 640, [0, 64, 64, 256, 576], 128, 1, 1, 1),
+    (16, 64, 1088, 2048, None, 64, 1, 1, 1), (16, 832, 320, 1024, None, 128, 1, 1, 1),
+    (32, 64, 2048, 1024, None, 64, 1, 1, 1), (32, 832, 320, 1024, None, 128, 1, 1, 1),
+    (64, 64, 1088, 3072, None, 64, 1, 1, 1), (64, 832, 320, 2048, None, 128, 1, 1, 1),      # tiles of 128 and 256 hidden units
+    (64, 576, 320, 2048, [0, 64, 64, 256, 576], 128, 1, 1, 1),
+    # larger weights: the call that packs them copies X into blocks
+    (8, 64, 1088, 4160, None, 64, 1, 0, 1), (8, 832, 1344, 4160, None, 128, 1, 0, 1), (8, 576, 1088, 8256, [0, 64, 64, 256, 576], 128, 1, 0, 1),
+    (16, 64, 1088, 4096, None, 64, 1, 0, 1), (16, 832, 1344, 4096, None, 128, 1, 0, 1),
+    (32, 64, 1088, 4096, None, 64, 1, 0, 1), (32, 832, 1344, 4096, None, 128, 1, 0, 1),
+    (64, 64, 3072, 6144, None, 64, 1, 0, 1), (64, 320, 2112, 12288, None, 128, 1, 0, 1), (64, 576, 1088, 8192, [0, 64, 64, 256, 576], 128, 1, 0, 1),
+    (64, 64, 3584, 6144, None, 64, 0, 0, 1),        # the weights do not stay in L2: both copy X
+    # ... and nothing but X.T is prepared in the call on packed weights, behind the tiles of eq. (1)
+    (8, 64, 2112, 12352, None, 64, 1, 0, 0), (8, 192, 2112, 12288, None, 128, 1, 0, 0), (16, 64, 2112, 12288, None, 64, 1, 0, 0),
+    (16, 192, 2112, 12288, None, 128, 1, 0, 0), (32, 128, 1600, 18432, None, 128, 1, 0, 0), (64, 256, 1600, 18432, None, 128, 1, 0, 0),
+]
+
+
+@pytest.mark.parametrize("M,T,D,F,seg,tile,packed_reads,reads,together", FORWARD_CALLS)
+def test_forward_call_on_packed_weights_reads_x_as_it_is(M, T, D, F, seg, tile, packed_reads, reads, together):
+    """The same bits as the call that packs the weights, in Y3 and, through the backward call, in all gradients (X.T); where that call does not copy X into blocks
+    either, both against the oracle."""
+    experts = len(seg) - 1 if seg else 1
+    parts = [make_ffn_inputs(T, D, F, seed=51 + e) for e in range(experts)]
+    inp = {k: np.stack([p[k] for p in parts]) if seg and k in ("W1", "W2", "b1") else parts[0][k] for k in parts[0]}
+    dev = {k: to_dev(inp[k]) for k in ("X", "W1", "W2", "b1", "dY")}
+    weights = [dev[k] for k in ("W1", "W2", "b1")]
+    new = (lambda **kw: sffn.FfnStepGrouped(seg, D, F, M=M, **kw)) if seg else (lambda **kw: sffn.FfnStep(T, D, F, M=M, **kw))  # noqa: E731
+    a, b = new(), new(keep_dense=bool(reads))
+    want = [a.forward(dev["X"], *weights), *a.backward(dev["W1"], dev["dY"])]
+    b.forward(dev["dY"], *weights)          # packs the weights; another X
+    got = [b.forward(dev["X"], *weights, weights_packed=True), *b.backward(dev["W1"], dev["dY"])]
     for g, w in zip(got, want):
         assert torch.equal(g, w)
+    if not reads:
+        return
+    s = {k: to_bits(v) for k, v in b.saved().items()}
+    outs = {k: to_bits(v) for k, v in zip(("Y3", "dX", "dW1", "dW2"), got)}
+    if not seg:
+        _check_wide_step_against_oracle(inp, s, outs, sffn.MODE_HARD, M)
+    for e in range(experts if seg else 0):
+        lo, hi = seg[e], seg[e + 1]
+        if lo == hi:
+            continue
+        one = dict(X=inp["X"][lo:hi], dY=inp["dY"][lo:hi], W1=inp["W1"][e], W2=inp["W2"][e], b1=inp["b1"][e])
+        se = {k: s[k][e] for k in ("w1_vals", "w1_meta", "w2t_vals", "w2t_meta")}
+        se.update({k: s[k][lo:hi] for k in ("y1", "y2_vals", "y2_meta", "dy2", "dy1_vals")}, colidx=s["colidx"][lo // 64:hi // 64],
+                  y1_kept=s["y1_kept"].reshape(-1)[lo * 2 * F // M:hi * 2 * F // M])
+        _check_wide_step_against_oracle(one, se, dict(Y3=outs["Y3"][lo:hi], dX=outs["dX"][lo:hi], dW1=outs["dW1"][e], dW2=outs["dW2"][e]), sffn.MODE_HARD, M)
 
 
 @pytest.mark.parametrize("M,T,D,F", [(8, 700, 2048, 12288), (16, 700, 2048, 12288), (32, 300, 2048, 12288), (64, 700, 2048, 12288), (16, 576, 448, 1280)])

@@ -103,6 +103,15 @@ def test_splits_of_the_activation_contractions(chosen):
     assert sum(t[n] for t, n in rows) <= 0.95 * sum(t[1] for t, _ in rows), rows
 
 
+def test_routes_of_the_gpu_tests(rules):
+    """tests/test_gpu_tiles.py compares the routes that it means to: a call that reads X as it is with one that copies it, or with the oracle."""
+    from tests.test_gpu_tiles import FORWARD_CALLS
+    offsets = [seg or [0, T] for _, T, _, _, seg, *_ in FORWARD_CALLS]
+    lines = rules(["forward %d %d %d %d %s" % (M, D, F, len(o) - 1, " ".join(map(str, o))) for (M, _, D, F, *_), o in zip(FORWARD_CALLS, offsets)])
+    for call, line in zip(FORWARD_CALLS, lines):
+        assert line.split() == [str(v) for v in call[5:]], (call, line)
+
+
 @pytest.mark.parametrize("what,mean,most", [("step", 0.004, 0.15), ("calls", 0.004, 0.10), ("forward", 0.0075, 0.20)])
 def test_shared_launches_of_the_step(rules, what, mean, most):
     """The form that is chosen takes 0.4 % longer than the better one on average, for the whole step as for its calls of one pass each (two runs of one form differ by

@@ -1,5 +1,7 @@
 // Prints what the host-side tile rules (kernels.hpp) choose, for tests/test_tile_rules.py.  One line of standard input is one call:
 //   step <fp8> <M> <D> <F> <experts> <offset 0> ... <offset n>   -> tiles of eq. (1), eq. (4), eqs. (3), (7), weight gradients in launches of their own; do they share
+//   forward <M> <D> <F> <experts> <offset 0> ... <offset n>      -> tile of eq. (1) in a bf16 call; does it read X as it is on packed weights, does it on others; are its
+//                                                                   preparing passes one launch
 //   share <fp8> <M> <D> <F> <experts> <T>                        -> do they share launches
 //   router <M> <D> <F> <T>                                       -> tile of its eqs. (1), (4)
 //   split <T> <N> <F>                                            -> workgroups per tile of eq. (3) at M = 8
@@ -40,6 +42,18 @@ int main() {
             g.role = 1;
             const int steps = (int)(b / 64);
             printf("%d\n", pick_gemm_tile(4 * c / a, (d + 63) / 64 * 64 + 16 * a, steps, g, small_round(kGemmRouter, steps), true, last_round(kGemmRouter, steps)));
+            continue;
+        }
+        if (!strcmp(what, "forward")) {
+            if (scanf("%ld %ld %ld %ld", &b, &c, &d, &e) != 4 || e > GemmGroup::kMaxExperts) return 1;
+            GemmGroup g;
+            g.n = e > 1 ? (int)e : 0;
+            for (int i = 0; i <= e; ++i) if (scanf("%d", &g.seg[i]) != 1) return 1;
+            const int64_t T = g.seg[e];
+            StepTiles t = step_tiles(T, c, d, (int)b, (int)e, false);
+            refine_tiles(&t, c, d, (int)b, g, false);
+            printf("%d %d %d %d\n", t.g, (int)forward_reads_x(T, c, e * d, (int)b, true, t.g), (int)forward_reads_x(T, c, e * d, (int)b, false, t.g),
+                   (int)(t.mix || prologue_together(T, c, d, e)));
             continue;
         }
         if (!strcmp(what, "share")) {
