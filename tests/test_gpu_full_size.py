@@ -282,13 +282,19 @@ def test_full_size_router_step(name, M):
     from workload import make_router_inputs
     T, D, F = CONFIGS[name]
     inp = make_router_inputs(T, D, F, M, seed=0)
-    dev = {k: to_dev(v) for k, v in inp.items()}
+    sampled_router_step_check(inp, {k: to_dev(v) for k, v in inp.items()}, M)
+
+
+def sampled_router_step_check(inp, dev, M, mode=sffn.MODE_HARD):
+    """One-call form against the form on a routing given by the caller, the latter stage by stage against the oracle; returns Y3, dX, dW1, dW2."""
+    T, D = inp["X"].shape
+    F = inp["W1"].shape[0]
     route = sffn.venom_route(dev["X"], dev["means"], M)
-    fast = sffn.FfnRouterStep(T, D, F, M)                           # the timed configuration: routing inside, dy2c not stored
+    fast = sffn.FfnRouterStep(T, D, F, M, mode)                           # the timed configuration: routing inside, dy2c not stored
     outs_fast = [to_bits(t).copy() for t in fast.full(dev["means"], dev["X"], dev["W1"], dev["W2"], dev["b1"], dev["dY"])]
     del fast
     torch.cuda.empty_cache()
-    step = sffn.FfnRouterStep(T, D, F, M, keep_dense=True)
+    step = sffn.FfnRouterStep(T, D, F, M, mode, keep_dense=True)
     outs = step(route, dev["X"], dev["W1"], dev["W2"], dev["b1"], dev["dY"])
     torch.cuda.synchronize()
     Y3, dX, dW1, dW2 = (to_bits(t) for t in outs)
@@ -298,9 +304,9 @@ def test_full_size_router_step(name, M):
     perm, seg = oracle.expert_permutation(expert, M // 4)
     assert np.array_equal(to_bits(route["perm"]), perm) and route["seg"] == [int(v) for v in seg]
     rng = np.random.default_rng(5 + M)
-    w1s = oracle.prune24_dense(inp["W1"])
-    w2t_s = oracle.prune24_dense(np.ascontiguousarray(inp["W2"].T))
-    for tb in sorted(set(int(b) for b in rng.choice(int(seg[-1]) // 64, 5, replace=False)) | {0}):
+    w1s = oracle.prune24_dense(inp["W1"], mode)
+    w2t_s = oracle.prune24_dense(np.ascontiguousarray(inp["W2"].T), mode)
+    for tb in sorted(set(int(b) for b in rng.choice(int(seg[-1]) // 64, min(5, int(seg[-1]) // 64), replace=False)) | {0}):
         rows = np.arange(64 * tb, 64 * tb + 64)
         e = int(np.searchsorted(seg, 64 * tb, side="right") - 1)
         cl = oracle.cluster_rows(e, M, F)
@@ -327,6 +333,7 @@ def test_full_size_router_step(name, M):
         for packed, G, got in ((sv["vals"], inp["dY"], np.ascontiguousarray(dW2[:, f].T)), (sv["dvals"], inp["X"], dW1[f])):
             a = oracle.bits_to_f64(oracle.prune24_decompress(packed[real], sv["meta"][real])[:, js])
             assert_gemm_close(got, oracle.f64_to_bits(a.T @ oracle.bits_to_f64(G[perm[real]])), "wgrad rows")
+    return Y3, dX, dW1, dW2
 
 
 @pytest.mark.parametrize("wgrad_fp8", [False, True])

@@ -6,6 +6,7 @@ import torch
 
 import oracle
 import paper_2602_06183_amd as sffn
+from tests.test_gpu_full_size import sampled_router_step_check
 from tests.test_gpu_fp8 import _check_fp8_step_against_oracle, _fp8_step_scales
 from tests.test_gpu_kernels import _check_wide_step_against_oracle, _teacher_forced_step_check
 from tests.util import assert_gemm_close, to_bits, to_dev
@@ -273,14 +274,20 @@ def test_forward_call_on_packed_weights_reads_x_as_it_is(M, T, D, F, seg, tile, 
         _check_wide_step_against_oracle(one, se, dict(Y3=outs["Y3"][lo:hi], dX=outs["dX"][lo:hi], dW1=outs["dW1"][e], dW2=outs["dW2"][e]), sffn.MODE_HARD, M)
 
 
-@pytest.mark.parametrize("M,T,D,F", [(8, 700, 2048, 12288), (16, 700, 2048, 12288), (32, 300, 2048, 12288), (64, 700, 2048, 12288), (16, 576, 448, 1280)])
-def test_router_step_in_shared_launches(M, T, D, F):
-    """Eqs. (3) and (4) in one launch, preparing passes behind eq. (1) (not in the last, smallest case), the transpose of dW2 behind eq. (7): the same bits as
-    the forward and backward calls, whose contractions have launches of their own, also with weights that are packed already; the smallest against the oracle."""
+# (M, T, D, F, are the preparing passes one launch): the router's step shares launches in all of them
+ROUTER_CALLS = [(8, 700, 2048, 12288, 0), (16, 700, 2048, 12288, 0), (32, 300, 2048, 12288, 0), (64, 700, 2048, 12288, 0), (16, 576, 448, 1280, 1)]
+
+
+@pytest.mark.parametrize("mode", [sffn.MODE_HARD, sffn.MODE_SOFT])
+@pytest.mark.parametrize("M,T,D,F,together", ROUTER_CALLS)
+def test_router_step_in_shared_launches(M, T, D, F, together, mode):
+    """Preparing passes behind the tiles of eq. (1) (not in the last, smallest case), eqs. (3) and (4) in one launch, the transpose of dW2 behind eq. (7): every stage on
+    sampled rows and hidden units against the oracle.  The forward and backward calls, whose eqs. (3), (4) have launches of their own, and calls on weights that are
+    packed already: the same bits."""
     inp = make_router_inputs(T, D, F, M, seed=61)
     dev = {k: to_dev(v) for k, v in inp.items()}
     route = sffn.venom_route(dev["X"], dev["means"], M)
-    one, two = sffn.FfnRouterStep(T, D, F, M), sffn.FfnRouterStep(T, D, F, M)
+    one, two = sffn.FfnRouterStep(T, D, F, M, mode), sffn.FfnRouterStep(T, D, F, M, mode)
     want = [t.clone() for t in one(route, dev["X"], dev["W1"], dev["W2"], dev["b1"], dev["dY"])]
     got = [two.forward(route, dev["X"], dev["W1"], dev["W2"], dev["b1"]), *two.backward(route, dev["dY"])]
     for g, w in zip(got, want):
@@ -288,7 +295,9 @@ def test_router_step_in_shared_launches(M, T, D, F):
     for packed in (True, False):
         for g, w in zip(one(route, dev["X"], dev["W1"], dev["W2"], dev["b1"], dev["dY"], weights_packed=packed), want):
             assert torch.equal(g, w)
-    if F <= 1280:       # (5 %: the oracle's own run, in which near ties of the 2:4 choice may fall the other way)
+    for g, w in zip(sampled_router_step_check(inp, dev, M, mode), want):
+        assert np.array_equal(g, to_bits(w))
+    if mode == sffn.MODE_HARD and F <= 1280:       # (5 %: the oracle's own run, in which near ties of the 2:4 choice may fall the other way)
         ref = oracle.ffn_router_step_ref(inp["X"], inp["W1"], inp["W2"], inp["b1"], inp["dY"], inp["means"], M)
         for name, g in zip(("y3", "dX", "dW1", "dW2"), want):
             a, b = oracle.bits_to_f64(to_bits(g)), oracle.bits_to_f64(ref[name])

@@ -104,12 +104,14 @@ def test_splits_of_the_activation_contractions(chosen):
 
 
 def test_routes_of_the_gpu_tests(rules):
-    """tests/test_gpu_tiles.py compares the routes that it means to: a call that reads X as it is with one that copies it, or with the oracle."""
-    from tests.test_gpu_tiles import FORWARD_CALLS
+    """tests/test_gpu_tiles.py compares the routes that it means to: a call that reads X as it is with one that copies it, or with the oracle; the router's shared launches."""
+    from tests.test_gpu_tiles import FORWARD_CALLS, ROUTER_CALLS
     offsets = [seg or [0, T] for _, T, _, _, seg, *_ in FORWARD_CALLS]
     lines = rules(["forward %d %d %d %d %s" % (M, D, F, len(o) - 1, " ".join(map(str, o))) for (M, _, D, F, *_), o in zip(FORWARD_CALLS, offsets)])
     for call, line in zip(FORWARD_CALLS, lines):
         assert line.split() == [str(v) for v in call[5:]], (call, line)
+    for call, line in zip(ROUTER_CALLS, rules(["shares %d %d %d %d" % (M, D, F, T) for M, T, D, F, _ in ROUTER_CALLS])):
+        assert line.split() == ["1", str(call[4])], (call, line)
 
 
 @pytest.mark.parametrize("what,mean,most", [("step", 0.004, 0.15), ("calls", 0.004, 0.10), ("forward", 0.0075, 0.20)])

@@ -2,6 +2,7 @@
 //   step <fp8> <M> <D> <F> <experts> <offset 0> ... <offset n>   -> tiles of eq. (1), eq. (4), eqs. (3), (7), weight gradients in launches of their own; do they share
 //   forward <M> <D> <F> <experts> <offset 0> ... <offset n>      -> tile of eq. (1) in a bf16 call; does it read X as it is on packed weights, does it on others; are its
 //                                                                   preparing passes one launch
+//   shares <M> <D> <F> <T>                                       -> does the router's step share launches; are its preparing passes one launch
 //   share <fp8> <M> <D> <F> <experts> <T>                        -> do they share launches
 //   router <M> <D> <F> <T>                                       -> tile of its eqs. (1), (4)
 //   split <T> <N> <F>                                            -> workgroups per tile of eq. (3) at M = 8
@@ -42,6 +43,12 @@ int main() {
             g.role = 1;
             const int steps = (int)(b / 64);
             printf("%d\n", pick_gemm_tile(4 * c / a, (d + 63) / 64 * 64 + 16 * a, steps, g, small_round(kGemmRouter, steps), true, last_round(kGemmRouter, steps)));
+            continue;
+        }
+        if (!strcmp(what, "shares")) {
+            if (scanf("%ld %ld %ld %ld", &a, &b, &c, &d) != 4) return 1;
+            const int64_t rows = (d + 63) / 64 * 64 + 16 * a;
+            printf("%d %d\n", (int)router_shares(rows, b, c, (int)a), (int)prologue_together(rows, b, c, 1));
             continue;
         }
         if (!strcmp(what, "forward")) {
