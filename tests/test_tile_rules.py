@@ -1,6 +1,6 @@
 """The host-side rules that choose a contraction's output tile (kernels.hpp), against measured times of every tile (tests/golden/tile_times.txt): over
 the calls of a group, what the rules choose takes at most 4 % longer than the best tile of each call (where not said otherwise), and no call a third longer.
-The rule that has a step's contractions share launches, against whole steps timed both ways (tests/golden/step_times.txt)."""
+The rules that have a step's contractions share launches, against whole steps timed both ways (tests/golden/step_times.txt, router_times.txt)."""
 import math
 import os
 import subprocess
@@ -75,14 +75,15 @@ def test_tiles_of_grouped_steps(chosen, fp8):
     check([(t["eq1"], o[0]) for t, o in rows])
     check([(t["eq4"], o[1]) for t, o in rows])
     # (one call of the list has experts whose weights do not stay in a cache for a second round of small tiles: 396 us for 320)
-    check([(t["eq3"], o[2]) for t, o in rows if "eq3" in t and o[2] != 64], total=1.08)
+    for v in (2, 5):
+        check([(t["eq3"], o[v]) for t, o in rows if "eq3" in t and o[v] != 64], total=1.04)
 
 
 @pytest.mark.parametrize("fp8", [False, True])
 def test_tiles_of_the_activation_contractions(chosen, fp8):
-    """Eqs. (3), (7) at M = 8 by themselves and in a shared launch."""
-    rows = [(t["eq3"], o[2]) for c, t, o in chosen if c[0] == "step" and c[1] == str(int(fp8)) and "eq3" in t and 64 in t["eq3"]]
-    check(rows, 1.3, 1.06)
+    """Eqs. (3), (7) at M = 8 in launches of their own, where the step's contractions have such launches and in the forward call of a step whose contractions share them."""
+    for v in (2, 5):
+        check([(t["eq3"], o[v]) for c, t, o in chosen if c[0] == "step" and c[1] == str(int(fp8)) and "eq3" in t and o[v] in t["eq3"]], 1.3, 1.06)
 
 
 def test_tiles_of_the_routers_contractions(chosen):
@@ -101,6 +102,14 @@ def test_splits_of_the_activation_contractions(chosen):
     rows = [(t, min(t, key=lambda n: abs(n - o[0]))) for c, t, o in chosen if c[0] == "split"]       # (the nearest number that was measured)
     assert len(rows) >= 8 and all(t[n] <= 1.04 * t[1] for t, n in rows), rows
     assert sum(t[n] for t, n in rows) <= 0.95 * sum(t[1] for t, _ in rows), rows
+
+
+def test_shared_launches_of_the_routers_step(rules):
+    """Where the router's step shares launches it is faster, by 5 % and more over all calls, and no call 4 % slower."""
+    calls = golden("router_times.txt")
+    rows = [tuple(map(float, t.split())) for (c, t), line in zip(calls, rules(["shares " + c for c, _ in calls])) if line.split()[0] == "1"]
+    assert len(rows) >= 30 and all(shared <= 1.04 * apart for shared, apart in rows), rows
+    assert sum(math.log(shared / apart) for shared, apart in rows) <= -0.05 * len(rows), rows
 
 
 def test_routes_of_the_gpu_tests(rules):

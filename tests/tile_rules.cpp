@@ -1,5 +1,6 @@
 // Prints what the host-side tile rules (kernels.hpp) choose, for tests/test_tile_rules.py.  One line of standard input is one call:
-//   step <fp8> <M> <D> <F> <experts> <offset 0> ... <offset n>   -> tiles of eq. (1), eq. (4), eqs. (3), (7), weight gradients in launches of their own; do they share
+//   step <fp8> <M> <D> <F> <experts> <offset 0> ... <offset n>   -> tiles of eq. (1), eq. (4), eqs. (3), (7), weight gradients in launches of their own; do they share;
+//                                                                   tile of eq. (3) in a forward call
 //   forward <M> <D> <F> <experts> <offset 0> ... <offset n>      -> tile of eq. (1) in a bf16 call; does it read X as it is on packed weights, does it on others; are its
 //                                                                   preparing passes one launch
 //   shares <M> <D> <F> <T>                                       -> does the router's step share launches; are its preparing passes one launch
@@ -74,8 +75,10 @@ int main() {
         g.n = e > 1 ? (int)e : 0;
         for (int i = 0; i <= e; ++i) if (scanf("%d", &g.seg[i]) != 1) return 1;
         StepTiles t = step_tiles(g.seg[e], c, d, (int)b, (int)e, a != 0, false);
+        StepTiles whole = step_tiles(g.seg[e], c, d, (int)b, (int)e, a != 0);
         refine_tiles(&t, c, d, (int)b, g, a != 0);
-        printf("%d %d %d %d %d\n", t.g, t.g_bwd, t.v, t.w, (int)step_tiles(g.seg[e], c, d, (int)b, (int)e, a != 0).mix);
+        refine_tiles(&whole, c, d, (int)b, g, a != 0);
+        printf("%d %d %d %d %d %d\n", t.g, t.g_bwd, t.v, t.w, (int)whole.mix, whole.v_alone);
     }
     return 0;
 }
