@@ -292,7 +292,8 @@ int venom_expert_matmul(const sffn_cfg* cfg, const int64_t* seg_offsets, const u
  * come back in token order; dW1 [F,D], dW2 [D,F] are fully overwritten (hidden units of an expert without tokens: zeros).
  * Intermediates land in `workspace` at the offsets of sffn_router_workspace_layout() (row order of perm, rows =
  * sffn_venom_rows(T, M)); dy2c is stored only with SFFN_FLAG_KEEP_DENSE (eq. (6) runs in the epilogue of eq. (4)).
- * Needs 4F/M a multiple of 64. */
+ * Needs 4F/M a multiple of 64.  Where eq. (4) shares a launch with eq. (3) the workspace holds its packed survivors beside eq. (1)'s: 3 rows 4F/M bytes
+ * more; sffn_router_workspace_bytes() counts them. */
 typedef struct {
     size_t y1c, vals, meta, colidx, dy2c, dvals, total;   /* y1c, dy2c [rows,4F/M] bf16; vals, dvals [rows,2F/M]; meta [rows,F/(2M)] */
 } sffn_router_layout;

@@ -309,7 +309,8 @@ inline bool wgrad_on_kept_rows(int64_t T, int64_t F, int M, int64_t experts) { r
 // F = 2048 63 / 45).
 // The constants are fitted to the launches and whole steps of 987 shapes (T 64 - 16384, D 256 - 8192, 1 - 8 experts, every M, bf16 and fp8), each run both ways,
 // and held against 480 others: there what is chosen takes 0.29 % longer than the better form (0.32 % in bf16, 0.19 % on codes), one call in 32 4 % and more, the
-// worst 15 %; always sharing would take 2.6 % longer, never 17 %.  Forward and backward calls after one another: 0.21 % longer, the worst 9 %.  T = 1984, D = 1344,
+// worst 15 %; always sharing would take 2.6 % longer, never 17 %.  Forward and backward calls after one another, whose eq. (3) has a launch of its own as in a
+// step with float32 accumulation: 0.21 % longer, the worst 9 %.  T = 1984, D = 1344,
 // F = 4160 167 us apart, 140 together; codes, T = 6848, D = 2304, F = 8192 671 / 686.  Near even the estimate errs either way, mostly where 64 - 256 tokens meet large
 // weights (T = 256, D = 3648, F = 11648 282 / 300, shared) and where experts differ in length, which it does not know (8 of them on codes, T = 1920, D = 512, F = 2176,
 // one of 576 tokens 97 / 101, shared); the worst have splits to lose (see step_tiles).
@@ -429,7 +430,7 @@ inline void refine_tiles(StepTiles* t, int64_t D, int64_t F, int M, const GemmGr
 // Does the router's step share launches?  Where eqs. (1), (4) and (3), (7) all run on 128 tiles.  Grouped by expert they have a few tiles more than fill the
 // chip, so that the last round of each is nearly empty: T = 8192, D = 2048, F = 8192, M = 16 (1056 tiles each, 512 at a time) eqs. (4) and (3) 90 + 68 us apart,
 // 137 together; eq. (7) and the transpose of dW2 72 + 12, 77; the step 542 / 522; T = 1792, D = 640, F = 1920, M = 8 110 / 94; T = 128, D = 704, F = 2560,
-// M = 16 90 / 78; 120 drawn calls 5.5 % faster together.  Up to 48 Mi elements of tokens and weights: the passes that ride along run two workgroups a CU, which
+// M = 16 90 / 78.  Of 100 drawn calls 57 share, in 0.90 of the time apart, the slowest 1.02 (T = 13952, D = 1216, F = 5248, M = 8 734 / 748).  Up to 48 Mi elements of tokens and weights: the passes that ride along run two workgroups a CU, which
 // is less than their rate alone (T = 320, D = 4928, F = 21888, M = 8 811 us apart, 894 together).
 inline bool router_shares(int64_t rows, int64_t D, int64_t F, int M) {
     if ((rows + F) * D > ((int64_t)48 << 20)) return false;

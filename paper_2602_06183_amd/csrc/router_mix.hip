@@ -1,4 +1,4 @@
-// Shared launches of the router's step (RouterShare in kernels.hpp).  Its contractions are grouped by expert, so they have a few tiles more than fill the chip
+// Shared launches of the router's step (where: router_shares() in kernels.hpp).  Its contractions are grouped by expert, so they have a few tiles more than fill the chip
 // a whole number of times, and the last round of each is nearly empty: what does not depend on them fills it.
 #include "gemm_v2_body.hpp"
 #include "router_prologue.hpp"
