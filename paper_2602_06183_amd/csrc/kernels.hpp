@@ -301,78 +301,92 @@ inline int pick_wgrad_tile(int64_t F, int64_t N, int64_t T, int experts, bool sp
 inline bool wgrad_on_kept_rows(int64_t T, int64_t F, int M, int64_t experts) { return M >= 32 && F % (8 * M) == 0 && T >= 768 * experts; }
 
 // Do eqs. (3), (5), (4) and (7), (8) take less time as two launches than as five?  Both are estimated (us).  A launch by itself takes `start` and its rounds
-// over the chip, 256 large or 512 small tiles at a time (a last round of at most 256 small tiles less than a full one), or the time of the weights' bytes where few
+// over the chip, 256 large or 512 small tiles at a time (a last round of fewer less than a full one), or the time of the weights' bytes where few
 // tokens meet them.  A shared launch takes the sum of its small tiles spread over the chip and `end` of the last unit's tile; no less than `lone` of a tile behind
 // what comes before it, nor than the bytes of all its units.  Tiles and splits are those that the separate launches have.  Eqs. (5), (8) of bf16 blocks of 32 and
 // 64 columns multiply the kept rows only where they have launches of their own, 8 and 16 times fewer products: M = 64, T = 11520, D = 896, F = 2048 the step 224 us apart,
 // 297 together; T = 7680, D = 832, F = 3072 181 / 222; M = 32, T = 5312, D = 1152, F = 3584 186 / 203; small ones share all the same (M = 64, T = 1280, D = 448,
 // F = 2048 63 / 45).
-// The constants are fitted to the launches and whole steps of 987 shapes (T 64 - 16384, D 256 - 8192, 1 - 8 experts, every M, bf16 and fp8), each run both ways,
-// and held against 480 others: there what is chosen takes 0.29 % longer than the better form (0.32 % in bf16, 0.19 % on codes), one call in 32 4 % and more, the
-// worst 15 %; always sharing would take 2.6 % longer, never 17 %.  Forward and backward calls after one another, whose eq. (3) has a launch of its own as in a
-// step with float32 accumulation: 0.21 % longer, the worst 9 %.  T = 1984, D = 1344,
-// F = 4160 167 us apart, 140 together; codes, T = 6848, D = 2304, F = 8192 671 / 686.  Near even the estimate errs either way, mostly where 64 - 256 tokens meet large
-// weights (T = 256, D = 3648, F = 11648 282 / 300, shared) and where experts differ in length, which it does not know (8 of them on codes, T = 1920, D = 512, F = 2176,
-// one of 576 tokens 97 / 101, shared); the worst have splits to lose (see step_tiles).
+// The constants are fitted to whole steps of 28000 drawn shapes (T 64 - 16384, D 256 - 8192, 1 - 32 experts of uneven length, every M, bf16 and codes), each run both
+// ways.  Over 4000 others what is chosen takes 0.10 % longer than the better form (one expert 0.10 % in bf16, 0.04 % on codes), one call in 180 4 % and more, the
+// worst 12 %; always sharing would take 2.3 % longer, never 16 %.  Over 487 measured apart from both: 0.18 %, forward and backward calls after one another, whose eq. (3)
+// has a launch of its own as in a step with float32 accumulation, 0.11 %.  T = 1984, D = 1344, F = 4160 167 us apart, 140 together; codes, T = 6848, D = 2304, F = 8192
+// 671 / 686.  Near even it errs either way, mostly where 64 - 640 tokens meet large weights (T = 192, D = 5504, F = 17408, M = 32 497 / 536, shared) and on experts, whose
+// lengths it does not know (8 of them, T = 640, D = 1600, F = 6720 419 / 465, shared); the worst have splits to lose (see step_tiles).
 struct StepCosts {
     struct Line { float fixed, step; float operator()(float steps) const { return fixed + step * steps; } };       // us of a tile, and of it per trip of its main loop
-    float start, end, lone, lone_tall;
-    float bytes3, bytes4, bytes5;                       // us per million weights that eqs. (3) / (7), (4), (5) / (8) read or write
-    Line large4, small4, tall4, tiny4;                  // 256, 128 (two a CU), M = 64: 256 x 128 (two a CU), 64
+    float start;
+    struct { float v, w, g, g_tall; } lone;             // by unit: eqs. (3) / (7), (5) / (8), (4), (4) at M = 64
+    struct { float v, w, g; } end;
+    struct { float v, rows, g, w; } last;               // a last round of at most 256 small tiles: M = 8, M >= 16 in eqs. (3), (7), eq. (4), eqs. (5), (8)
+    float knee, part;                                   // ... of just over 256; a last round of a few large tiles
+    float two_v, two_w;                                 // a 64 tile in a shared launch, as a part of a 128 tile's slot
+    struct { float v, g, w, all; } bytes;               // us per million weights read or written; all: of a shared launch's units together
+    Line large4, large4_mid, large4_tall, small4, small4_mid, tall4, tiny4;        // 256 (M = 8; 16, 32; 64), 128 (two a CU; M = 8; 16, 32), M = 64: 256 x 128 (two a CU), 64
     Line large3, small3, tiny3, rows3, tiny_rows3;      // M = 8: 512 x 128 or 256, 128, 64; M >= 16: 64 x 256 (two a CU), 64
     Line large5, small5, tiny5, kept32, kept64;         // 256, 128, 64; on the kept rows
 };
-constexpr StepCosts kStepBf16 = {2.9f, 0.46f, 0.6f, 0.75f, 0.82f, 0.49f, 0.53f, {10.0f, 0.8f}, {6.4f, 0.56f}, {4.9f, 1.1f}, {7.8f, 0.067f},
-                                 {15.0f, 0.62f}, {2.1f, 0.59f}, {4.5f, 0.13f}, {5.1f, 1.2f}, {4.0f, 0.38f}, {7.1f, 1.3f}, {6.3f, 0.65f}, {5.6f, 0.12f}, {7.1f, 0.26f}, {7.1f, 0.25f}};
-constexpr StepCosts kStepFp8 = {3.8f, 0.39f, 0.64f, 0.63f, 0.5f, 0.38f, 0.55f, {14.0f, 0.86f}, {7.9f, 0.54f}, {9.0f, 0.97f}, {1.9f, 0.15f},
-                                {10.0f, 0.7f}, {3.6f, 0.56f}, {3.9f, 0.26f}, {3.5f, 1.3f}, {4.0f, 0.38f}, {7.0f, 0.67f}, {5.2f, 0.37f}, {3.3f, 0.049f}, {}, {}};
+constexpr StepCosts kStepBf16 = {3.34f, {0.51f, 0.556f, 0.869f, 0.968f}, {0.402f, 0.411f, 0.436f}, {0.664f, 0.788f, 0.653f, 0.591f}, 0.882f, 0.856f, 2.69f, 1.98f, {0.263f, 0.285f, 0.485f, 1.12f},
+                                 {8.92f, 0.722f}, {11.6f, 0.825f}, {7.85f, 0.511f}, {5.16f, 0.407f}, {4.99f, 0.639f}, {4.73f, 0.86f}, {11.8f, 0.0731f},
+                                 {15.4f, 0.632f}, {2.0f, 0.69f}, {3.59f, 0.103f}, {3.2f, 1.49f}, {4.31f, 0.338f}, {6.46f, 1.17f}, {4.09f, 0.63f}, {4.46f, 0.164f}, {5.62f, 0.201f}, {7.12f, 0.229f}};
+constexpr StepCosts kStepFp8 = {4.84f, {0.421f, 0.727f, 1.24f, 0.658f}, {0.297f, 0.255f, 0.254f}, {0.618f, 0.683f, 0.639f, 0.631f}, 1.0f, 0.942f, 2.75f, 1.9f, {0.247f, 0.26f, 0.452f, 1.03f},
+                                 {11.8f, 0.858f}, {16.0f, 0.776f}, {13.6f, 0.8f}, {6.33f, 0.52f}, {7.82f, 0.545f}, {8.93f, 0.977f}, {1.9f, 0.15f},
+                                 {11.0f, 0.608f}, {3.16f, 0.586f}, {3.4f, 0.206f}, {2.86f, 1.28f}, {4.0f, 0.38f}, {6.57f, 0.503f}, {4.15f, 0.29f}, {3.27f, 0.0483f}, {}, {}};
 // t: the tiles of the separate launches; v: that of eqs. (3), (7) in the shared ones (256: the next smaller there)
 inline bool sharing_pays(int64_t T, int64_t D, int64_t F, int M, int groups, bool fp8, const StepTiles& t, int v) {
     const StepCosts& c = fp8 ? kStepFp8 : kStepBf16;
     const int unit = fp8 ? 128 : 64, e = groups ? groups : 1;
     const float sg = (float)(D / unit), sv = (float)(M == 8 ? F / unit : 4 * F / M / unit), sw = (float)T / 64.0f / (float)e;
-    auto across = [](int64_t n, int64_t edge) { return (n + edge - 1) / edge; };
-    auto large = [](int64_t n) { return (float)((n + 255) / 256); };
-    auto small = [](int64_t n, float last) { const int64_t rest = n % 512; return (float)(n / 512) + (rest == 0 ? 0.0f : rest <= 256 ? last : 1.0f); };
+    auto across = [](int64_t n, int64_t edge) { return (float)((n + edge - 1) / edge); };
+    // tiles along the tokens: experts end anywhere in their last tile, half a tile on average
+    auto tokens = [&](int64_t edge) { return groups ? (float)T / (float)edge + 0.5f * (float)groups * (1.0f - 64.0f / (float)edge) : across(T, edge); };
+    auto large = [&](float n) {
+        const float all = ceilf(n), full = floorf(all / 256.0f), rest = all - 256.0f * full;
+        return rest == 0.0f ? full : full + c.part + (1.0f - c.part) * rest / 256.0f;
+    };
+    auto small = [&](float n, float last) {
+        const float all = ceilf(n), full = floorf(all / 512.0f), rest = all - 512.0f * full;
+        return rest == 0.0f ? full : rest <= 256.0f ? full + last : full + last + (1.0f - last) * (c.knee + (1.0f - c.knee) * (rest - 256.0f) / 256.0f);
+    };
     auto more = [](float a, float b) { return a > b ? a : b; };
-    struct Unit { float tile; int64_t tiles; float lone; };             // of the shared launches
+    struct Unit { float tile, tiles, lone, end; };                      // of the shared launches
     const float weights = (float)(D * F * e) * 1e-6f;
     float alone3, alone4, alone5;
     Unit u3, u4, u5;
     {
-        const int64_t n = across(F, M == 64 ? 256 : 128) * token_tiles(T, groups, 128);
-        u4 = {M == 64 ? c.tall4(sg) : c.small4(sg), n, M == 64 ? c.lone_tall : c.lone};
-        alone4 = t.g_bwd == 256 ? large(across(F, 256) * token_tiles(T, groups, 256)) * c.large4(sg)
-               : t.g_bwd == 128 ? small(n, 0.68f) * u4.tile : large(across(F, 64) * token_tiles(T, groups, 64)) * c.tiny4(sg);
+        const StepCosts::Line big = M == 8 ? c.large4 : M == 64 ? c.large4_tall : c.large4_mid, two = M == 8 ? c.small4 : M == 64 ? c.tall4 : c.small4_mid;
+        const float n = across(F, M == 64 ? 256 : 128) * tokens(128);
+        u4 = {two(sg), n, M == 64 ? c.lone.g_tall : c.lone.g, c.end.g};
+        alone4 = t.g_bwd == 256 ? large(across(F, 256) * tokens(256)) * big(sg) : t.g_bwd == 128 ? small(n, c.last.g) * u4.tile : large(across(F, 64) * tokens(64)) * c.tiny4(sg);
     }
     float rows = 1.0f;                                                  // the part of the weights that any token block keeps
     if (M == 8) {
-        const int64_t n = across(D, 128) * token_tiles(T, groups, 128), n64 = across(D, 64) * token_tiles(T, groups, 64);
-        const float n512 = 0.93f * large(across(D, 128) * token_tiles(T, groups, 512)), n256 = large(across(D, 256) * token_tiles(T, groups, 256));
-        alone3 = t.v == 256 ? (n512 < n256 ? n512 : n256) * c.large3(sv) : t.v == 128 ? small(n, 0.69f) * c.small3(sv) : large(n64 * t.v_split) * c.tiny3(sv / (float)t.v_split);
-        u3 = v == 64 ? Unit{2.0f * c.tiny3(sv), n64, c.lone} : Unit{c.small3(sv), n, c.lone};
+        const float n = across(D, 128) * tokens(128), n64 = across(D, 64) * tokens(64);
+        const float n512 = 0.93f * large(across(D, 128) * tokens(512)), n256 = large(across(D, 256) * tokens(256));
+        alone3 = t.v == 256 ? (n512 < n256 ? n512 : n256) * c.large3(sv) : t.v == 128 ? small(n, c.last.v) * c.small3(sv) : large(n64 * (float)t.v_split) * c.tiny3(sv / (float)t.v_split);
+        u3 = v == 64 ? Unit{c.two_v * c.tiny3(sv), n64, c.lone.v, c.end.v} : Unit{c.small3(sv), n, c.lone.v, c.end.v};
     } else {
-        const int64_t n = T / 64 * across(D, 256), n64 = T / 64 * across(D, 64);
-        alone3 = t.v == 256 ? small(n, 0.66f) * c.rows3(sv) : large(n64 * t.v_split) * c.tiny_rows3(sv / (float)t.v_split);
-        u3 = v == 64 ? Unit{2.0f * c.tiny_rows3(sv), n64, c.lone} : Unit{c.rows3(sv), n, c.lone};
+        const float n = across(T, 64) * across(D, 256), n64 = across(T, 64) * across(D, 64);
+        alone3 = t.v == 256 ? small(n, c.last.rows) * c.rows3(sv) : large(n64 * (float)t.v_split) * c.tiny_rows3(sv / (float)t.v_split);
+        u3 = v == 64 ? Unit{c.two_v * c.tiny_rows3(sv), n64, c.lone.v, c.end.v} : Unit{c.rows3(sv), n, c.lone.v, c.end.v};
         rows -= powf(1.0f - 4.0f / (float)M, more(sw, 1.0f));
     }
     {
-        const int64_t n = e * across(F, 128) * across(D, 128), n64 = e * across(F, 64) * across(D, 64);
-        if (!fp8 && wgrad_on_kept_rows(T, F, M, e)) alone5 = large(e * across(F, 512) * across(D, 64)) * (M == 32 ? c.kept32(sw) : c.kept64(sw));
-        else alone5 = t.w == 256 ? large(e * across(F, 256) * across(D, 256)) * c.large5(sw) : t.w == 128 ? small(n, 0.6f) * c.small5(sw) : large(n64) * c.tiny5(sw);
-        u5 = t.w == 64 ? Unit{2.0f * c.tiny5(sw), n64, c.lone} : Unit{c.small5(sw), n, c.lone};
+        const float n = (float)e * across(F, 128) * across(D, 128), n64 = (float)e * across(F, 64) * across(D, 64);
+        if (!fp8 && wgrad_on_kept_rows(T, F, M, e)) alone5 = large((float)e * across(F, 512) * across(D, 64)) * (M == 32 ? c.kept32(sw) : c.kept64(sw));
+        else alone5 = t.w == 256 ? large((float)e * across(F, 256) * across(D, 256)) * c.large5(sw) : t.w == 128 ? small(n, c.last.w) * c.small5(sw) : large(n64) * c.tiny5(sw);
+        u5 = t.w == 64 ? Unit{c.two_w * c.tiny5(sw), n64, c.lone.w, c.end.w} : Unit{c.small5(sw), n, c.lone.w, c.end.w};
     }
     if (t.v_split > 1) alone3 += 1.5f;
-    const float b3 = c.bytes3 * weights * rows, b4 = c.bytes4 * weights, b5 = c.bytes5 * weights;
+    const float b3 = c.bytes.v * weights * rows, b4 = c.bytes.g * weights, b5 = c.bytes.w * weights;
     auto shared = [&](std::initializer_list<Unit> units, float bytes) {
         float before = 0.0f, last = 0.0f;
         for (const Unit& u : units) {
-            const float work = (float)u.tiles * u.tile / 512.0f;
-            last = more(last, before + more(u.lone * u.tile, work + c.end * u.tile));
+            const float work = u.tiles * u.tile / 512.0f;
+            last = more(last, before + more(u.lone * u.tile, work + u.end * u.tile));
             before += work;
         }
-        return c.start + more(last, 1.1f * bytes);           // (no launch moves all its units' bytes at the best rate of each)
+        return c.start + more(last, c.bytes.all * bytes);
     };
     return shared({u3, u5, u4}, b3 + b4 + b5) + shared({u3, u5}, b3 + b5) < 5.0f * c.start + more(alone4, b4) + 2.0f * (more(alone3, b3) + more(alone5, b5));
 }

@@ -237,7 +237,7 @@ FORWARD_CALLS = [
     (64, 64, 3584, 6144, None, 64, 0, 0, 1),        # the weights do not stay in L2: both copy X
     # ... and nothing but X.T is prepared in the call on packed weights, behind the tiles of eq. (1)
     (8, 64, 2112, 12352, None, 64, 1, 0, 0), (8, 192, 2112, 12288, None, 128, 1, 0, 0), (16, 64, 2112, 12288, None, 64, 1, 0, 0),
-    (16, 192, 2112, 12288, None, 128, 1, 0, 0), (32, 128, 1600, 18432, None, 128, 1, 0, 0), (64, 256, 1600, 18432, None, 128, 1, 0, 0),
+    (16, 192, 2112, 12288, None, 128, 1, 0, 0), (32, 128, 1600, 18432, None, 128, 1, 0, 0), (64, 256, 2112, 14336, None, 128, 1, 0, 0),
 ]
 
 

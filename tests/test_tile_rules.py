@@ -123,10 +123,10 @@ def test_routes_of_the_gpu_tests(rules):
         assert line.split() == ["1", str(call[4])], (call, line)
 
 
-@pytest.mark.parametrize("what,mean,most", [("step", 0.004, 0.15), ("calls", 0.004, 0.10), ("forward", 0.0075, 0.20)])
+@pytest.mark.parametrize("what,mean,most", [("step", 0.0025, 0.15), ("calls", 0.0025, 0.08), ("forward", 0.0075, 0.20)])
 def test_shared_launches_of_the_step(rules, what, mean, most):
-    """The form that is chosen takes 0.4 % longer than the better one on average, for the whole step as for its calls of one pass each (two runs of one form differ by
-    1 - 2 %), no more than 1 % in any group of calls, and 4 % in one call of 30; a forward call that loses a split (StepTiles) up to a fifth."""
+    """The form that is chosen takes 0.25 % longer than the better one on average, for the whole step as for its calls of one pass each (two runs of one form differ by
+    1 - 2 %), no more than 1 % in any group of calls, and 4 % in one call of 40; a forward call that loses a split (StepTiles) up to a fifth."""
     calls = golden("step_times.txt")
     assert len(calls) >= 480
     losses = {}
@@ -134,5 +134,5 @@ def test_shared_launches_of_the_step(rules, what, mean, most):
         shared, apart = next(map(float, t.split()[1:]) for t in times if t.split()[0] == what)
         losses.setdefault(tuple(call.split()[:2]) + (call.split()[4] != "1",), []).append(math.log((shared if share == "1" else apart) / min(shared, apart)))
     every = [x for group in losses.values() for x in group]
-    assert sum(every) <= mean * len(every) and max(every) <= most and sum(x > 0.04 for x in every) <= len(every) / 30, (sum(every) / len(every), max(every))
+    assert sum(every) <= mean * len(every) and max(every) <= most and sum(x > 0.04 for x in every) <= len(every) / 40, (sum(every) / len(every), max(every))
     assert what == "forward" or all(sum(group) <= 0.01 * len(group) for group in losses.values()), {k: sum(v) / len(v) for k, v in losses.items()}
