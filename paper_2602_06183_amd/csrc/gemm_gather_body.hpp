@@ -56,19 +56,15 @@ __device__ __forceinline__ void vnm_gather_body(unsigned char* __restrict__ smem
 
     // Consecutive workgroup ids go to different XCDs; give each XCD a run of consecutive logical ids, and let logical
     // ids walk the token blocks of one column slab, so an XCD's L2 holds one slab of Wk at a time.
-    int L;
-    {
-        const int per = n_pid >> 3;
-        L = (pid < per * 8) ? (pid & 7) * per + (pid >> 3) : pid;
-    }
+    int L = xcd_run(pid, n_pid);
     int ks0 = 0, ks1 = Kc >> 6, sp = 0;                  // this workgroup's stages (split.hpp)
     if (KW > 1 && split.n > 1) {
         const int per = nblk_tok * tiles_n;
-        sp = L / per;
+        sp = uniform(L / per);
         L -= sp * per;
         ks0 = sp * (Kc >> 6) / split.n; ks1 = (sp + 1) * (Kc >> 6) / split.n;
     }
-    const int tn = L / nblk_tok, tb = L - tn * nblk_tok;
+    const int tn = uniform(L / nblk_tok), tb = L - tn * nblk_tok;
     const int t0 = tb * 64, n0 = tn * TL::BN;
     if (grp.n) {                                         // grouped form: the token block's segment names the expert whose matrix it meets
         int e = 0;
@@ -298,12 +294,8 @@ __device__ __forceinline__ void vnm_gather_fp8_body(unsigned char* __restrict__ 
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l32 = lane & 31, lh = lane >> 5;
 
-    int L;
-    {
-        const int per = n_pid >> 3;
-        L = (pid < per * 8) ? (pid & 7) * per + (pid >> 3) : pid;
-    }
-    const int tn = L / nblk_tok, tb = L - tn * nblk_tok;
+    int L = xcd_run(pid, n_pid);
+    const int tn = uniform(L / nblk_tok), tb = L - tn * nblk_tok;
     const int t0 = tb * 64, n0 = tn * 256;
     if (grp.n) {
         int e = 0;

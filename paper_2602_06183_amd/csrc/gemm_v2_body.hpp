@@ -84,21 +84,17 @@ __device__ __forceinline__ void gemm_nt_v2_body(unsigned char* __restrict__ smem
 
     // Workgroup -> tile.  Consecutive workgroup ids go to different XCDs; the remap gives each XCD a run of
     // consecutive logical ids, and logical ids walk bands of 4 tile rows, so an XCD's L2 sees few operand panels.
-    int L;
-    {
-        const int per = n_pid >> 3;
-        L = (pid < per * 8) ? (pid & 7) * per + (pid >> 3) : pid;
-    }
+    int L = xcd_run(pid, n_pid);
     // Grouped form: find the expert of this tile and narrow the problem to its token segment.
     const int Kld = K;                   // K extent of the stored operands (block-row stride)
-#define SEG(i) (grp.seg_dev ? grp.seg_dev[i] : grp.seg[i])
+#define SEG(i) (grp.seg_dev ? uniform(grp.seg_dev[i]) : grp.seg[i])
     const int tok_ld = grp.n ? SEG(grp.n) : Rb;       // tokens in the token-indexed outputs of the V:N:M epilogue
     int i_base = 0, j_base = 0;
     int expert_id = 0;
     if (!SPARSE && !BLOCKED && grp.n && grp.role == 2) {
         // every expert has its own tiles_m x tiles_n output and contracts over its own k range of the shared operands
         const int per = tiles_m * tiles_n;
-        expert_id = L / per;
+        expert_id = uniform(L / per);
         L -= expert_id * per;
         if (expert_id >= grp.n) return;
         const int k0 = SEG(expert_id);
@@ -116,8 +112,8 @@ __device__ __forceinline__ void gemm_nt_v2_body(unsigned char* __restrict__ smem
                 L -= cnt;
             }
             if (e == grp.n) return;      // (the launcher sizes the grid exactly; kept as a guard)
-            if (grp.role == 0) { tiles_m = cnt / other; i_base = SEG(e); Ra = SEG(e + 1); }
-            else               { tiles_n = cnt / other; j_base = SEG(e); Rb = SEG(e + 1); }
+            if (grp.role == 0) { tiles_m = uniform(cnt / other); i_base = SEG(e); Ra = SEG(e + 1); }
+            else               { tiles_n = uniform(cnt / other); j_base = SEG(e); Rb = SEG(e + 1); }
 #undef SEG
         }
         if (grp.role != 0) { a_vals += e * grp.a_stride; if (SPARSE) a_meta += e * grp.m_stride; }
@@ -126,13 +122,7 @@ __device__ __forceinline__ void gemm_nt_v2_body(unsigned char* __restrict__ smem
         out += e * grp.out_stride;
     }
     int tm, tn;
-    {
-        constexpr int GROUP = SFFN_TILE_GROUP;
-        const int width = GROUP * tiles_n, group = L / width, first = group * GROUP;
-        const int gsz = (tiles_m - first) < GROUP ? (tiles_m - first) : GROUP;
-        tm = first + (L % width) % gsz;
-        tn = (L % width) / gsz;
-    }
+    band_tile(L, tiles_m, tiles_n, SFFN_TILE_GROUP, tm, tn);
     const int i0 = i_base + tm * BM, j0 = j_base + tn * BN;
     const int lda = SPARSE ? Kld / 2 : Kld;
 

@@ -84,11 +84,7 @@ __device__ __forceinline__ void vnm8_gemm_body(unsigned char* __restrict__ smem,
     const int kg = KW > 1 ? wave : 0, wt = KW > 1 ? 0 : wave;       // share of the contraction / place in the tile
     unsigned char* const ring = smem + kg * (kStages * kStage);
 
-    int L;
-    {
-        const int per = n_pid >> 3;
-        L = (pid < per * 8) ? (pid & 7) * per + (pid >> 3) : pid;
-    }
+    int L = xcd_run(pid, n_pid);
     // Grouped form (role 0): the token tiles of segment e meet expert e's matrix
     int i_base = 0;
     if (grp.n) {
@@ -99,7 +95,7 @@ __device__ __forceinline__ void vnm8_gemm_body(unsigned char* __restrict__ smem,
             L -= cnt;
         }
         if (e == grp.n) return;
-        tiles_m = cnt / tiles_n; i_base = grp.seg[e]; Ra = grp.seg[e + 1];
+        tiles_m = uniform(cnt / tiles_n); i_base = grp.seg[e]; Ra = grp.seg[e + 1];
         Wk += (int64_t)e * grp.b_stride * ES;
     }
     constexpr bool SPLIT = KW == 4;
@@ -107,19 +103,13 @@ __device__ __forceinline__ void vnm8_gemm_body(unsigned char* __restrict__ smem,
     int ks0 = 0, ks1 = KS, sp = 0, tile = 0;         // this workgroup's stages
     if (SPLIT && split.n > 1) {
         const int per = tiles_m * tiles_n;
-        sp = L / per;
+        sp = uniform(L / per);
         L -= sp * per;
         tile = L;
         ks0 = sp * KS / split.n; ks1 = (sp + 1) * KS / split.n;
     }
     int tm, tn;
-    {
-        constexpr int GROUP = TL::BAND;
-        const int width = GROUP * tiles_n, group = L / width, first = group * GROUP;
-        const int gsz = (tiles_m - first) < GROUP ? (tiles_m - first) : GROUP;
-        tm = first + (L % width) % gsz;
-        tn = (L % width) / gsz;
-    }
+    band_tile(L, tiles_m, tiles_n, TL::BAND, tm, tn);
     const int i0 = i_base + tm * BT, n0 = tn * BN;
     const int NTB = Ttot >> 6;
 

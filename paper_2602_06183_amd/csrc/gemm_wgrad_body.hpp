@@ -224,27 +224,17 @@ __device__ __forceinline__ void wgrad_vnm_body(unsigned char* __restrict__ smem,
     unsigned char* const ring = smem + kg * (kStages * kStage);
 
     // workgroup -> tile: an XCD gets a run of consecutive logical ids, which walk bands of 4 tile rows
-    int L;
-    {
-        const int per = n_pid >> 3;
-        L = (pid < per * 8) ? (pid & 7) * per + (pid >> 3) : pid;
-    }
+    int L = xcd_run(pid, n_pid);
     int k_base = 0, K = Ttot;                     // grouped: every expert contracts over its own token segment
     if (grp.n) {
-        const int per = tiles_m * tiles_n, e = L / per;
+        const int per = tiles_m * tiles_n, e = uniform(L / per);
         L -= e * per;
         k_base = grp.seg[e];
         K = grp.seg[e + 1] - k_base;
         out += e * grp.out_stride * (ACC32 ? 2 : 1);          // (float32 elements are two uint16_t wide)
     }
     int tm, tn;
-    {
-        constexpr int GROUP = SFFN_TILE_GROUP;
-        const int width = GROUP * tiles_n, group = L / width, first = group * GROUP;
-        const int gsz = (tiles_m - first) < GROUP ? (tiles_m - first) : GROUP;
-        tm = first + (L % width) % gsz;
-        tn = (L % width) / gsz;
-    }
+    band_tile(L, tiles_m, tiles_n, SFFN_TILE_GROUP, tm, tn);
     const int i0 = tm * BM, j0 = tn * BN;
     const int KC = Ttot / 32;                     // 32-token chunks per row of the blocked operands
 
@@ -437,27 +427,17 @@ __device__ __forceinline__ void wgrad_vnm_fp8_body(unsigned char* __restrict__ s
     const int wm = wt / TL::WVN, wn = wt % TL::WVN;
     const int l32 = lane & 31, lh = lane >> 5;
     unsigned char* const ring = smem + kg * (kStages * kStage);
-    int L;
-    {
-        const int per = n_pid >> 3;
-        L = (pid < per * 8) ? (pid & 7) * per + (pid >> 3) : pid;
-    }
+    int L = xcd_run(pid, n_pid);
     int k_base = 0, K = Ttot;                     // grouped: every expert contracts over its own token segment
     if (grp.n) {
-        const int per = tiles_m * tiles_n, e = L / per;
+        const int per = tiles_m * tiles_n, e = uniform(L / per);
         L -= e * per;
         k_base = grp.seg[e];
         K = grp.seg[e + 1] - k_base;
         out += e * grp.out_stride * (ACC32 ? 2 : 1);          // (float32 elements are two uint16_t wide)
     }
     int tm, tn;
-    {
-        constexpr int GROUP = SFFN_TILE_GROUP;
-        const int width = GROUP * tiles_n, group = L / width, first = group * GROUP;
-        const int gsz = (tiles_m - first) < GROUP ? (tiles_m - first) : GROUP;
-        tm = first + (L % width) % gsz;
-        tn = (L % width) / gsz;
-    }
+    band_tile(L, tiles_m, tiles_n, SFFN_TILE_GROUP, tm, tn);
     const int i0 = tm * BM, j0 = tn * BN;
     const int KC = Ttot / 64;                     // 64-token chunks (64 bytes) per row of the blocked operands
 

@@ -50,27 +50,17 @@ __device__ __forceinline__ void wgrad_wide_body(unsigned char* __restrict__ smem
     const int wr = wave / TL::WN, wn = wave % TL::WN;
     const int l32 = lane & 31, lh = lane >> 5;
 
-    int L;
-    {
-        const int per = n_pid >> 3;
-        L = (pid < per * 8) ? (pid & 7) * per + (pid >> 3) : pid;
-    }
+    int L = xcd_run(pid, n_pid);
     int tb0 = 0, nk = Ttot / 64;                  // grouped: every expert contracts over its own token segment
     if (grp.n) {
-        const int per = tiles_m * tiles_n, e = L / per;
+        const int per = tiles_m * tiles_n, e = uniform(L / per);
         L -= e * per;
         tb0 = grp.seg[e] / 64;
         nk = grp.seg[e + 1] / 64 - tb0;
         out += e * grp.out_stride * (ACC32 ? 2 : 1);
     }
     int tm, tn;
-    {   // bands of 4 tile rows, as in the other tile kernels
-        constexpr int GROUP = 4;
-        const int width = GROUP * tiles_n, group = L / width, first = group * GROUP;
-        const int gsz = (tiles_m - first) < GROUP ? (tiles_m - first) : GROUP;
-        tm = first + (L % width) % gsz;
-        tn = (L % width) / gsz;
-    }
+    band_tile(L, tiles_m, tiles_n, 4, tm, tn);
     const int i0 = tm * BF, j0 = tn * BN;
 
     static_assert(BF * PITCH % 4 == 0, "cleared in 16-byte pieces");

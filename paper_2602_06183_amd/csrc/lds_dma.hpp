@@ -47,6 +47,23 @@ __device__ __forceinline__ uint64_t uniform64(const void* p) {
     return ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(v >> 32)) << 32) |
            (uint32_t)__builtin_amdgcn_readfirstlane((int)(v & 0xFFFFFFFFu));
 }
+// A value that is the same in every lane, in an SGPR.  A quotient, or a word read through a pointer, is uniform but comes in a VGPR, and all that is derived from it
+// would follow: the places of a tile in its operands and outputs as 64-bit vector arithmetic, the tests on its edges as masks.
+__device__ __forceinline__ int uniform(int x) { return __builtin_amdgcn_readfirstlane(x); }
+// Workgroup -> logical id: consecutive ids go to different XCDs, so an XCD gets a run of consecutive logical ids
+__device__ __forceinline__ int xcd_run(int pid, int n_pid) {
+    const int per = n_pid >> 3;
+    return pid < per * 8 ? (pid & 7) * per + (pid >> 3) : pid;
+}
+// Logical id -> tile: bands of `band` tile rows, column by column, so that the ids which an XCD runs at a time share few operand panels
+__device__ __forceinline__ void band_tile(int L, int tiles_m, int tiles_n, int band, int& tm, int& tn) {
+    const uint32_t width = (uint32_t)(band * tiles_n);
+    const int group = uniform((int)((uint32_t)L / width)), first = group * band;
+    const int gsz = tiles_m - first < band ? tiles_m - first : band;
+    const uint32_t in = (uint32_t)L - (uint32_t)group * width;
+    tn = uniform((int)(in / (uint32_t)gsz));
+    tm = first + (int)in - tn * gsz;
+}
 __device__ __forceinline__ void dma16(uint64_t base, uint32_t lane_off, unsigned char* lds_wave_base) {
     // every lane fetches 16 bytes at base + lane_off; the wave's 64 chunks land at lds_wave_base + 16 * lane
     const uint32_t dst = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(lds_void*)lds_wave_base);
