@@ -5,11 +5,14 @@
 // The producer (the V:N:M epilogue of gemm_v2.hip) therefore stores the transposed activation compacted to those
 // rows ("atc": row 4 g + p of token block tb = hidden unit 8 g + colidx[tb, g, p]; [F / 2 rows, T tokens], blocked
 // layout of common.hpp), which halves its bytes in HBM, in L2 and on the way into LDS.  This kernel runs dense
-// v_mfma_f32_32x32x16_bf16 on a 256 (hidden) x 256 tile; a lane that needs hidden unit f looks up, once per
+// v_mfma_f32_16x16x32_bf16 on a 256 (hidden) x 256 tile; a lane that needs hidden unit f looks up, once per
 // 64-token stage, whether f is one of its group's four kept units (a bit mask per group, written by the producer;
 // the position among the kept units is a population count) and reads either that compact row or a row of zeros
 // kept at the end of the tile.  Same ring / barrier / LDS-DMA discipline as gemm_v2.hip: 3 stages of 64
 // tokens (A 16 KB as two 32-token halves, G 32 KB as two halves, 8 private copies of the tile's 32 mask bytes).
+// What bounds it is the power that the matrix instructions take, at 77 % of the pipe's cycles.  The 16 x 16 form does the same products (and sums: same bits) as
+// 32 x 32 x 16 for 12 % less of it (registers only, half of the rows zero: 2167 TFLOP/s with 32 x 32 x 16, 2433 with this one): T = N = 8192, F = 28672 2580 -> 2380 us
+// at a clock of 1.84 -> 2.01 GHz; T = 8192, N = 2048, F = 8192 220 -> 206.
 #pragma once
 #include "common.hpp"
 #include "kernels.hpp"
@@ -44,29 +47,29 @@ struct WTile {
 __device__ __forceinline__ int zero_lane(int l32) { return (l32 & 4) ? 0 : 3 * 64; }
 
 // partial sums of KW wavefronts -> the first one, in ascending order; returns false for the wavefronts that are done
-template <class TL>
-__device__ __forceinline__ bool wgrad_join(f32x16 (&acc)[TL::FM][TL::FN], unsigned char* smem, int kg, int lane) {
-    constexpr int PART = TL::FM * TL::FN * 16 * 256;
+template <class TL, class V, int FM, int FN>
+__device__ __forceinline__ bool wgrad_join(V (&acc)[FM][FN], unsigned char* smem, int kg, int lane) {
+    constexpr int R = sizeof(V) / 4, PART = FM * FN * R * 256;
     static_assert((TL::KW - 1) * PART <= TL::BYTES && (TL::KW - 1) * PART <= TL::BYTES8, "partial sums must fit in the main-loop LDS");
     if (kg > 0) {
         float* p = reinterpret_cast<float*>(smem + (kg - 1) * PART) + lane;
 #pragma unroll
-        for (int a = 0; a < TL::FM; ++a)
+        for (int a = 0; a < FM; ++a)
 #pragma unroll
-            for (int b = 0; b < TL::FN; ++b)
+            for (int b = 0; b < FN; ++b)
 #pragma unroll
-                for (int r = 0; r < 16; ++r) p[((a * TL::FN + b) * 16 + r) * 64] = acc[a][b][r];
+                for (int r = 0; r < R; ++r) p[((a * FN + b) * R + r) * 64] = acc[a][b][r];
     }
     __syncthreads();
     if (kg > 0) return false;
     for (int g = 1; g < TL::KW; ++g) {
         const float* p = reinterpret_cast<const float*>(smem + (g - 1) * PART) + lane;
 #pragma unroll
-        for (int a = 0; a < TL::FM; ++a)
+        for (int a = 0; a < FM; ++a)
 #pragma unroll
-            for (int b = 0; b < TL::FN; ++b)
+            for (int b = 0; b < FN; ++b)
 #pragma unroll
-                for (int r = 0; r < 16; ++r) acc[a][b][r] += p[((a * TL::FN + b) * 16 + r) * 64];
+                for (int r = 0; r < R; ++r) acc[a][b][r] += p[((a * FN + b) * R + r) * 64];
     }
     wave_lds_sync();
     return true;
@@ -207,12 +210,109 @@ __device__ __forceinline__ void wgrad_store(f32x16 (&acc)[TL::FM][TL::FN], float
     }
 }
 
+// The same for accumulators of the 16 x 16 instructions (lane: column l % 16, rows 4 (l / 16) .. + 3 of a fragment).
+template <bool OUT_I_CONTIG, bool ACC32, class TL>
+__device__ __forceinline__ void wgrad_store(f32x4 (&acc)[TL::WM / 16][4], float alpha, unsigned char* smem, int wave, int lane, int i0, int j0, int F, int N,
+                                            uint16_t* __restrict__ out, int64_t ldo) {
+    constexpr int WM = TL::WM, WN = 64;
+    const int wm = wave / TL::WVN, wn = wave % TL::WVN, l16 = lane & 15, lq = lane >> 4;
+    if (ACC32) {
+        // rows of 64 float32 of the output: (OUT_I_CONTIG) 32 columns j x 64 hidden units, else 32 hidden units x 64 columns.  The products are rounded to float32 before
+        // they are staged, so the addition is never a fused multiply-add
+        float* out32 = reinterpret_cast<float*>(out);
+        constexpr int EP = 64 * 4 + 16, NQ = OUT_I_CONTIG ? WM / 64 * 2 : WM / 32;
+        unsigned char* scratch = smem + wave * (32 * EP);
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) {
+            const int row0 = OUT_I_CONTIG ? j0 + wn * WN + (q & 1) * 32 : i0 + wm * WM + q * 32, col0 = OUT_I_CONTIG ? i0 + wm * WM + (q >> 1) * 64 : j0 + wn * WN;
+            const int rows = OUT_I_CONTIG ? N : F, cols = OUT_I_CONTIG ? F : N;
+#pragma unroll
+            for (int x = 0; x < 2; ++x)
+#pragma unroll
+                for (int y = 0; y < 4; ++y) {
+                    if (OUT_I_CONTIG) {
+                        const f32x4 v = acc[(q >> 1) * 4 + y][(q & 1) * 2 + x];
+                        *reinterpret_cast<float4*>(scratch + (x * 16 + l16) * EP + (y * 16 + 4 * lq) * 4) = make_float4(v[0] * alpha, v[1] * alpha, v[2] * alpha, v[3] * alpha);
+                    } else {
+                        const f32x4 v = acc[q * 2 + x][y];
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) *reinterpret_cast<float*>(scratch + (x * 16 + 4 * lq + r) * EP + (y * 16 + l16) * 4) = v[r] * alpha;
+                    }
+                }
+            wave_lds_sync();
+            // all of the slab's old values are requested before the first sum is stored (a store would otherwise stand between the loads)
+            float4 old[8];
+#pragma unroll
+            for (int p = 0; p < 8; ++p) {
+                const int r = row0 + p * 4 + (lane >> 4), c = col0 + (lane & 15) * 4;
+                old[p] = (r < rows && c < cols) ? *reinterpret_cast<const float4*>(out32 + (int64_t)r * ldo + c) : make_float4(0.f, 0.f, 0.f, 0.f);
+            }
+#pragma unroll
+            for (int p = 0; p < 8; ++p) {
+                const int r = row0 + p * 4 + (lane >> 4), c = col0 + (lane & 15) * 4;
+                if (r < rows && c < cols) {
+                    const float4 add = *reinterpret_cast<const float4*>(scratch + (p * 4 + (lane >> 4)) * EP + (lane & 15) * 16);
+                    *reinterpret_cast<float4*>(out32 + (int64_t)r * ldo + c) = make_float4(old[p].x + add.x, old[p].y + add.y, old[p].z + add.z, old[p].w + add.w);
+                }
+            }
+            wave_lds_sync();
+        }
+    } else if (OUT_I_CONTIG) {
+        // out[j * ldo + i]: a lane owns 4 consecutive i of one j; stage [j][i] through LDS (two halves of 64 i) so that HBM sees 128-byte row segments
+        constexpr int EP = 64 * 2 + 16;
+        unsigned char* scratch = smem + wave * (WN * EP);
+#pragma unroll
+        for (int h = 0; h < WM / 64; ++h) {
+            const int f0 = i0 + wm * WM + h * 64, n0 = j0 + wn * WN;
+#pragma unroll
+            for (int a = 0; a < 4; ++a)
+#pragma unroll
+                for (int b = 0; b < 4; ++b) {
+                    const f32x4 v = acc[4 * h + a][b];
+                    *reinterpret_cast<uint2*>(scratch + (b * 16 + l16) * EP + (a * 16 + 4 * lq) * 2) = make_uint2(f2bf2(v[0] * alpha, v[1] * alpha), f2bf2(v[2] * alpha, v[3] * alpha));
+                }
+            wave_lds_sync();
+#pragma unroll
+            for (int p = 0; p < WN / 8; ++p) {
+                const int row = p * 8 + (lane >> 3), ch = lane & 7;
+                const int j = n0 + row, i = f0 + ch * 8;
+                if (j < N && i < F)
+                    *reinterpret_cast<uint4*>(out + (int64_t)j * ldo + i) = *reinterpret_cast<const uint4*>(scratch + row * EP + ch * 16);
+            }
+            wave_lds_sync();
+        }
+    } else {
+        // out[i * ldo + j]: transpose each 32-row slab through LDS for 16-byte row stores
+        constexpr int EP = WN * 2 + 16;
+        unsigned char* scratch = smem + wave * (32 * EP);
+#pragma unroll
+        for (int a = 0; a < WM / 32; ++a) {
+#pragma unroll
+            for (int x = 0; x < 2; ++x)
+#pragma unroll
+                for (int b = 0; b < 4; ++b)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r)
+                        *reinterpret_cast<uint16_t*>(scratch + (x * 16 + 4 * lq + r) * EP + (b * 16 + l16) * 2) = (uint16_t)f2bf(acc[2 * a + x][b][r] * alpha);
+            wave_lds_sync();
+#pragma unroll
+            for (int p = 0; p < 32 * (WN / 8) / 64; ++p) {
+                const int e = lane + 64 * p, row = e / (WN / 8), ch = e % (WN / 8);
+                const int i = i0 + wm * WM + a * 32 + row, j = j0 + wn * WN + ch * 8;
+                if (i < F && j < N)
+                    *reinterpret_cast<uint4*>(out + (int64_t)i * ldo + j) = *reinterpret_cast<const uint4*>(scratch + row * EP + ch * 16);
+            }
+            wave_lds_sync();
+        }
+    }
+}
+
 template <bool OUT_I_CONTIG, bool ACC32, class TL>
 __device__ __forceinline__ void wgrad_vnm_body(unsigned char* __restrict__ smem, int pid, int n_pid, const uint16_t* __restrict__ atc, const uint8_t* __restrict__ kmask,
                                                        const uint16_t* __restrict__ G, int F, int N, int Ttot,
                                                        uint16_t* __restrict__ out, int64_t ldo, int tiles_m, int tiles_n,
                                                        const GemmGroup& grp) {
-    constexpr int BM = TL::BM, BN = TL::BN, WM = TL::WM, WN = 64, FM = TL::FM, FN = TL::FN, KW = TL::KW;
+    constexpr int BM = TL::BM, BN = TL::BN, WM = TL::WM, WN = 64, FM = WM / 16, FN = 4, KW = TL::KW;
     constexpr int kStages = TL::NST, kStage = TL::kStage, kAHalf = TL::kAHalf, kABytes = TL::kABytes, kBHalf = TL::kBHalf, kBBytes = TL::kBBytes, kLoads = TL::kLoads;
     constexpr int A_LD = TL::A_LD, B_LD = TL::B_LD;
 
@@ -220,7 +320,7 @@ __device__ __forceinline__ void wgrad_vnm_body(unsigned char* __restrict__ smem,
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int kg = KW > 1 ? wave : 0, wt = KW > 1 ? 0 : wave;       // share of the contraction / place in the tile
     const int wm = wt / TL::WVN, wn = wt % TL::WVN;
-    const int l32 = lane & 31, lh = lane >> 5;
+    const int l16 = lane & 15, lq = lane >> 4;
     unsigned char* const ring = smem + kg * (kStages * kStage);
 
     // workgroup -> tile: an XCD gets a run of consecutive logical ids, which walk bands of 4 tile rows
@@ -242,7 +342,7 @@ __device__ __forceinline__ void wgrad_vnm_body(unsigned char* __restrict__ smem,
     //      matrix edge are clamped into it: they only feed outputs that are never stored. ------------------
     uint64_t a_base[A_LD][2], b_base[B_LD], c_base;
     const int rb = lane >> 2;
-    const uint32_t blk_lane = (uint32_t)(rb * 32 + ((lane & 3) ^ ((rb >> 2) & 3)) * 8) * 2;   // chunk swizzle, see gemm_v2.hip
+    const uint32_t blk_lane = (uint32_t)(rb * 32 + ((lane & 3) ^ swz4(rb >> 2)) * 8) * 2;
     {
 #pragma unroll
         for (int n = 0; n < A_LD; ++n) {
@@ -282,56 +382,45 @@ __device__ __forceinline__ void wgrad_vnm_body(unsigned char* __restrict__ smem,
             if (1 + 2 * A_LD + n >= lo && 1 + 2 * A_LD + n < hi) dma16(b_base[n], o, sb + (wt * B_LD + n) * 1024);
     };
 
-    // ---- fragment reads.  Sub-step s (16 tokens) of a stage lives in half s / 2 at chunk pair s % 2. ----
-    int b_off[FN];
-#pragma unroll
-    for (int b = 0; b < FN; ++b) {
-        const int row = wn * WN + b * 32 + l32;
-        b_off[b] = kABytes + row * 64 + ((lh ^ ((row >> 2) & 3)) << 4);
-    }
-    // hidden unit of fragment a in this lane: f = i0 + wm * WM + a * 32 + l32 -> group wm * WM / 8 + a * 4 + l32 / 8 of the tile,
-    // column l32 % 8 of the group.  a_off[a] = its row in a half-tile (or the zero row), set per stage by lookup().
-    // a_off[a][0 / 1] = LDS address of its row (or of the zero row) for the even / odd 16-token sub-steps of a half-tile
-    int a_off[FM][2], a_next[FM][2];
-    const uint32_t col = l32 & 7, below = (1u << col) - 1u;
-    // a hidden unit that is not kept reads zeros, from the row that its half-group leaves free (zero_lane)
-    const int zero_row = TL::kZero + zero_lane(l32) + ((lh ^ (l32 >> 3)) << 4);
-    uint32_t mk[FM];
-    auto lookup_read = [&](int stage) {
-        const unsigned char* sc = ring + stage * kStage + kABytes + kBBytes + wt * 256;
-#pragma unroll
-        for (int a = 0; a < FM; ++a) mk[a] = sc[wm * (WM / 8) + a * 4 + (l32 >> 3)];
-    };
-    auto lookup = [&](int stage) {
-        const int sa = stage * kStage;
-#pragma unroll
-        for (int a = 0; a < FM; ++a) {
-            const int gl = wm * (WM / 8) + a * 4 + (l32 >> 3);
-            const int row = gl * 4 + __builtin_popcount(mk[a] & below);                   // (row >> 2) & 3 == l32 >> 3
-            const int off = ((mk[a] >> col) & 1u) ? row * 64 + ((lh ^ (l32 >> 3)) << 4) : zero_row;
-            a_next[a][0] = sa + off;
-            a_next[a][1] = sa + (off ^ 32);
+    // ---- fragment reads.  Sub-step s (32 tokens) of a stage is its half s; lane -> row l16 of a fragment, 16-byte chunk lq of its 64 bytes. ----
+    const int b_off = kABytes + (wn * WN + l16) * 64 + ((lq ^ swz4(l16 >> 2)) << 4);
+    // hidden unit of fragment a in this lane: i0 + wm * WM + a * 16 + l16 -> group 2 a + hb of the wavefront's WM / 8, column l16 % 8 of the group.  Its row in a half-tile
+    // is 4 groups + the number of kept units below it; a unit that is not kept reads zeros, from the row that its half-group leaves free (zero_lane).
+    // a_off[a] = LDS address for fragment a less a * 512, looked up once per stage.
+    const int hb = l16 >> 3, col = l16 & 7, g0 = wm * (WM / 8) + hb;
+    const uint32_t below[2] = {((1u << col) - 1u) << (8 * hb), ((1u << col) - 1u) << (8 * hb + 16)};      // even / odd a: two groups to a half of a mask word
+    const uint32_t bit[2] = {(uint32_t)(8 * hb + col), (uint32_t)(8 * hb + col + 16)};
+    const uint32_t lb[2] = {(uint32_t)(g0 * 256 + ((lq ^ swz4(hb)) << 4)), (uint32_t)(g0 * 256 + ((lq ^ swz4(2 + hb)) << 4))};
+    const uint32_t no_row = (uint32_t)(TL::kZero / 64 + zero_lane(l16) / 64 - g0 * 4);
+    uint32_t a_off[FM], mk[FM / 2];
+    auto lookup_read = [&](int stage) {         // the wavefront's mask bytes: the same words in every lane
+        const unsigned char* sc = ring + stage * kStage + kABytes + kBBytes + wt * 256 + wm * (WM / 8);
+        if constexpr (FM == 8) {
+            const uint4 w = *reinterpret_cast<const uint4*>(sc);
+            mk[0] = w.x; mk[1] = w.y; mk[FM / 2 - 2] = w.z; mk[FM / 2 - 1] = w.w;
+        } else {
+            const uint2 w = *reinterpret_cast<const uint2*>(sc);
+            mk[0] = w.x; mk[1] = w.y;
         }
     };
-    struct FragSet { Frag8 a[FM]; Frag8 b[FN]; };
-    auto read_a = [&](FragSet& f, const unsigned char* st, int s, int a) {
-        (void)st;
-        f.a[a].u = *reinterpret_cast<const uint4*>(ring + a_off[a][s & 1] + (s >> 1) * kAHalf);
+    auto lookup = [&](int stage, int a) {
+        const uint32_t kept = (uint32_t)__builtin_amdgcn_sbfe((int)mk[a >> 1], bit[a & 1], 1), row = (uint32_t)__builtin_popcount(mk[a >> 1] & below[a & 1]);
+        a_off[a] = ((row & kept) | ((no_row - 8 * a) & ~kept)) * 64 + (lb[a & 1] + (uint32_t)(stage * kStage));
     };
-    auto read_b = [&](FragSet& f, const unsigned char* st, int s, int b) {
-        f.b[b].u = *reinterpret_cast<const uint4*>(st + (s >> 1) * kBHalf + (b_off[b] ^ (32 * (s & 1))));
-    };
+    auto read_a = [&](Frag8& f, int s, int a) { f.u = *reinterpret_cast<const uint4*>(ring + a_off[a] + (a * 512 + s * kAHalf)); };
+    auto read_b = [&](Frag8& f, const unsigned char* st, int s, int b) { f.u = *reinterpret_cast<const uint4*>(st + b_off + (b * 1024 + s * kBHalf)); };
 
-    f32x16 acc[FM][FN];
+    f32x4 acc[FM][FN];
 #pragma unroll
     for (int a = 0; a < FM; ++a)
 #pragma unroll
         for (int b = 0; b < FN; ++b)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) acc[a][b][r] = 0.0f;
-    auto mma_row = [&](const FragSet& f, int a) {
+            for (int r = 0; r < 4; ++r) acc[a][b][r] = 0.0f;
+    Frag8 A[4], B[2][FN];
+    auto mma_row = [&](int s, int a) {
 #pragma unroll
-        for (int b = 0; b < FN; ++b) acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.a[a].v, f.b[b].v, acc[a][b], 0, 0, 0);
+        for (int b = 0; b < FN; ++b) acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A[a & 3].v, B[s][b].v, acc[a][b], 0, 0, 0);
     };
 #define SB() __builtin_amdgcn_sched_barrier(0)
 
@@ -348,54 +437,69 @@ __device__ __forceinline__ void wgrad_vnm_body(unsigned char* __restrict__ smem,
         wait_vmcnt<(kStages - 1) * kLoads>();
         if (KW == 1) __syncthreads();
         else { wave_lds_sync(); asm volatile("" ::: "memory"); }
-        FragSet P, Q;
         lookup_read(0);
-        lookup(0);
 #pragma unroll
-        for (int a = 0; a < FM; ++a) { a_off[a][0] = a_next[a][0]; a_off[a][1] = a_next[a][1]; read_a(P, ring, 0, a); }
+        for (int a = 0; a < FM; ++a) lookup(0, a);
 #pragma unroll
-        for (int b = 0; b < FN; ++b) read_b(P, ring, 0, b);
+        for (int a = 0; a < 4; ++a) read_a(A[a], 0, a);
+#pragma unroll
+        for (int b = 0; b < FN; ++b) read_b(B[0][b], ring, 0, b);
+        constexpr int BAR = FM - 4;
         int stage = 0;
-        // the matrix instructions of sub-step set C with the reads of the next sub-step s (into set R) in between
-        auto sub_step = [&](const FragSet& C, FragSet& R, const unsigned char* st, int s, auto mid, auto late) {
-            mma_row(C, 0); SB();
-            read_a(R, st, s, 0); read_a(R, st, s, 1); read_b(R, st, s, 0); if (FM == 2) read_b(R, st, s, 1); SB();
-            mma_row(C, 1); SB();
-            if (FM == 4) { read_a(R, st, s, FM - 2); read_a(R, st, s, FM - 1); read_b(R, st, s, 1); SB(); }
-            mid(); SB();
-            if (FM == 4) { mma_row(C, FM - 2); SB(); }
-            late(); SB();
-            if (FM == 4) { mma_row(C, FM - 1); SB(); }
-        };
-        // One step = one stage = four sub-steps of FM x FN matrix instructions; the fragments of a sub-step are read
-        // while the matrix cores work on the one before.  Before the last sub-step every wavefront has read all of
-        // the stage (barrier), which is then refilled with the tile three steps ahead while the next stage's rows
-        // are looked up and its first fragments fetched.  The loads are spread over three sub-steps (gemm_v2_body.hpp says why), all of them
-        // before the wait for the next mask bytes; the first step's first ones repeat the last stage's.
+        // One step = one stage = two sub-steps of FM rows of four matrix instructions.  A row's fragment is read four rows ahead, G's fragments one sub-step
+        // ahead.  The next stage's mask bytes are the first load of its batch; its rows are looked up as the last reads of this stage are issued, and once every
+        // wavefront has issued all of them (barrier, four rows before the step's end) the stage is refilled with the tile three steps ahead.
+        // The loads are spread over the step (gemm_v2_body.hpp says why); the first step's first ones repeat the last stage's.
         int re_kt = step_of(kStages - 1 < nk ? kStages - 1 : nk - 1), re_stage = kStages - 1;
 #define ISSUE(i) issue(re_kt, re_stage, kLoads * (i) / 6, kLoads * ((i) + 1) / 6)
         for (int kt = 0; kt < nk; ++kt) {
             const int next_stage = (stage + 1 == kStages) ? 0 : stage + 1;
             const unsigned char* st = ring + stage * kStage;
             const unsigned char* sn = ring + next_stage * kStage;
-            sub_step(P, Q, st, 1, [&] { ISSUE(2); }, [&] { ISSUE(3); });
-            sub_step(Q, P, st, 2, [&] {
-                ISSUE(4); ISSUE(5);
-                // the next tile's mask bytes were the first load of its batch: all but kLoads - 1 of that batch and
-                // the batch after it may still be in flight
-                wait_vmcnt<(kStages - 2) * kLoads + kLoads - 1>();
-                if (KW > 1) asm volatile("" ::: "memory");
-                lookup_read(next_stage);
-            }, [&] {});
-            sub_step(P, Q, st, 3, [&] { lookup(next_stage); }, [&] {});
-            wait_vmcnt_lgkm0<(kStages - 2) * kLoads>();      // Q is here, tile kt + 1 has landed (this wavefront's part)
-            if (KW == 1) __builtin_amdgcn_s_barrier();
-            else asm volatile("" ::: "memory");
-            SB();
 #pragma unroll
-            for (int a = 0; a < FM; ++a) { a_off[a][0] = a_next[a][0]; a_off[a][1] = a_next[a][1]; }
-            re_kt = step_of((kt + kStages < nk) ? kt + kStages : nk - 1); re_stage = stage;
-            sub_step(Q, P, sn, 0, [&] { ISSUE(0); }, [&] { ISSUE(1); });
+            for (int a = 0; a < FM; ++a) {
+                mma_row(0, a); SB();
+                if (a + 4 < FM) read_a(A[a & 3], 0, a + 4);
+                else read_a(A[a & 3], 1, a + 4 - FM);
+                if (FM == 8) { if (a < FN) read_b(B[1][a], st, 1, a); }
+                else if (a < 2) { read_b(B[1][2 * a], st, 1, 2 * a); read_b(B[1][2 * a + 1], st, 1, 2 * a + 1); }
+                SB();
+                if (FM == 8) { if (a < 4) ISSUE(2 + a); }
+                else if (a < 2) { ISSUE(2 + 2 * a); ISSUE(3 + 2 * a); }
+                if (a == FM - 2) {
+                    // all but kLoads - 1 of the next stage's batch and the batch after it may still be in flight
+                    wait_vmcnt<(kStages - 2) * kLoads + kLoads - 1>();
+                    if (KW > 1) asm volatile("" ::: "memory");
+                    lookup_read(next_stage);
+                }
+                SB();
+            }
+#pragma unroll
+            for (int a = 0; a < FM; ++a) {
+                mma_row(1, a); SB();
+                if (a + 4 < FM) { read_a(A[a & 3], 1, a + 4); SB(); }
+                if (FM == 8 && a < 4) { lookup(next_stage, a); lookup(next_stage, a + FM - 4); SB(); }
+                if (FM == 4 && a == 0) {
+#pragma unroll
+                    for (int r = 0; r < FM; ++r) lookup(next_stage, r);
+                    SB();
+                }
+                if (a == BAR) {
+                    wait_vmcnt_lgkm0<(kStages - 2) * kLoads>();      // this wavefront's reads of the stage are here, and its part of tile kt + 1
+                    if (KW == 1) __builtin_amdgcn_s_barrier();
+                    else asm volatile("" ::: "memory");
+                    SB();
+                    re_kt = step_of((kt + kStages < nk) ? kt + kStages : nk - 1); re_stage = stage;
+#pragma unroll
+                    for (int r = 0; r <= BAR - (FM - 4); ++r) read_a(A[r], 0, r);
+#pragma unroll
+                    for (int b = 0; b < FN; ++b) read_b(B[0][b], sn, 0, b);
+                    SB();
+                }
+                if (a > BAR) { read_a(A[a & 3], 0, a - (FM - 4)); SB(); }
+                if (a == FM - 2) { ISSUE(0); SB(); }
+                if (a == FM - 1) { ISSUE(1); SB(); }
+            }
             stage = next_stage;
         }
 #undef ISSUE

@@ -21,6 +21,7 @@ namespace sffn {
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(16))) __bf16 bf16x16;
 typedef __attribute__((ext_vector_type(16))) float f32x16;
+typedef __attribute__((ext_vector_type(4))) float f32x4;
 
 typedef __attribute__((ext_vector_type(4))) int i32x4;
 typedef __attribute__((ext_vector_type(8))) int i32x8;
@@ -47,6 +48,10 @@ __device__ __forceinline__ uint64_t uniform64(const void* p) {
     return ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(v >> 32)) << 32) |
            (uint32_t)__builtin_amdgcn_readfirstlane((int)(v & 0xFFFFFFFFu));
 }
+// Where a 16-byte chunk of a 64-byte tile row lies: chunk ^ swz4(row / 4 % 4).  The 16 x 16 instructions' fragments are 16 rows x 4 chunks, lane -> row l % 16, chunk l / 16, and a
+// ds_read_b128 is served in phases of 16 lanes: 0-3, 12-15, 20-27 of a half wavefront, or its other 16.  With 0, 2, 3, 1 every phase meets 64 banks, also where the
+// rows are the kept ones of a group of 8 hidden units (gemm_wgrad_body.hpp).
+__device__ __forceinline__ int swz4(int g) { return (0x1320 >> (4 * (g & 3))) & 3; }
 // A value that is the same in every lane, in an SGPR.  A quotient, or a word read through a pointer, is uniform but comes in a VGPR, and all that is derived from it
 // would follow: the places of a tile in its operands and outputs as 64-bit vector arithmetic, the tests on its edges as masks.
 __device__ __forceinline__ int uniform(int x) { return __builtin_amdgcn_readfirstlane(x); }
