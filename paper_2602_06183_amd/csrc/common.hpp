@@ -114,16 +114,14 @@ __host__ __device__ __forceinline__ int64_t lane_off(int64_t r, int64_t t, int64
 }
 
 // Metadata of a 2:4 matrix, blocked for the sparse matrix instruction: one 256-byte unit per (32 rows, 64 k).
-// v_smfmac_f32_32x32x32_bf16 wants, in lane (row % 32) + 32 * h, the sixteen index bits of the row's survivors
-// in k 16h..16h+15 of a 32-k step; a unit stores, for each such lane, the two 32-k steps s = 0, 1 of its 64 k as
-// one 32-bit word (low half: s = 0) at byte 128 h + 4 (row % 32).  A wavefront therefore fetches a unit with one
-// 4-byte-per-lane LDS-DMA load, reads it back with one conflict-free ds_read_b32 and picks the step through the
-// instruction's ABID field.  mblk_off = byte address of the metadata byte covering k..k+7 of row r, KS = K / 64.
+// v_smfmac_f32_16x16x64_bf16 wants, in lane r % 16 + 16 q, the sixteen index bits of the row's survivors in k 16 q .. + 15; a unit stores, for each such
+// lane, its two fragments of 16 rows as one 32-bit word (low half: the first) at byte 4 lane.  A wavefront therefore fetches a unit with one
+// 4-byte-per-lane LDS-DMA load and reads it back with one conflict-free ds_read_b32.  mblk_off = byte address of the metadata byte covering k..k+7 of row r, KS = K / 64.
 __host__ __device__ __forceinline__ int64_t mblk_off(int64_t r, int64_t k, int64_t KS) {
-    return (((r >> 5) * KS + (k >> 6)) << 8) + (((k >> 4) & 1) << 7) + ((r & 31) << 2) + (((k >> 5) & 1) << 1) + ((k >> 3) & 1);
+    return (((r >> 5) * KS + (k >> 6)) << 8) + (((k >> 4) & 3) << 6) + ((r & 15) << 2) + (((r >> 4) & 1) << 1) + ((k >> 3) & 1);
 }
 
-// The same for fp8 operands (v_smfmac_f32_32x32x64_fp8_fp8 wants a 32-bit index word per lane and 64-k step, no ABID halves): one
+// The same for fp8 operands (v_smfmac_f32_16x16x128_fp8_fp8 wants a 32-bit index word per lane): one
 // 512-byte unit per (32 rows, 128 k), row-major inside (16 bytes per row); a wavefront fetches its 32 rows of a stage with two
 // contiguous 4-byte-per-lane loads.  m8blk_off = byte address of the metadata byte covering k..k+7 of row r, KS = K / 128.
 __host__ __device__ __forceinline__ int64_t m8blk_off(int64_t r, int64_t k, int64_t KS) {

@@ -53,6 +53,7 @@ __device__ __forceinline__ void vnm_gather_body(unsigned char* __restrict__ smem
     const int l32 = lane & 31, lh = lane >> 5;
     const int kg = KW > 1 ? wave : 0, wt = KW > 1 ? 0 : wave;
     unsigned char* const ring = smem + kg * (kGStages * kGStage);
+    const uint32_t ring_lds = lds_addr(smem) + kg * (kGStages * kGStage);
 
     // Consecutive workgroup ids go to different XCDs; give each XCD a run of consecutive logical ids, and let logical
     // ids walk the token blocks of one column slab, so an XCD's L2 holds one slab of Wk at a time.
@@ -117,9 +118,7 @@ __device__ __forceinline__ void vnm_gather_body(unsigned char* __restrict__ smem
         }
     };
     auto issue = [&](int kt, int stage) {
-        unsigned char* sb = ring + stage * kGStage;
-        unsigned char* sa = sb + kGB;
-        unsigned char* sm = sa + kGA;
+        const uint32_t sb = ring_lds + stage * kGStage, sa = sb + kGB, sm = sa + kGA;
 #pragma unroll
         for (int i = 0; i < 8; ++i) dma16(w_base, b_row[i] + b_col[i & 1], sb + (8 * wt + i) * 1024);
 #pragma unroll
@@ -293,6 +292,7 @@ __device__ __forceinline__ void vnm_gather_fp8_body(unsigned char* __restrict__ 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l32 = lane & 31, lh = lane >> 5;
+    const uint32_t smem_lds = lds_addr(smem);
 
     int L = xcd_run(pid, n_pid);
     const int tn = uniform(L / nblk_tok), tb = L - tn * nblk_tok;
@@ -334,9 +334,8 @@ __device__ __forceinline__ void vnm_gather_fp8_body(unsigned char* __restrict__ 
     };
     const int bsh = (lane >> 4) * 8;                     // the lane's row inside a block of four
     auto issue = [&](int kt, int stage) {
-        unsigned char* sb = smem + stage * kStage;
-        unsigned char* sa = sb + kB;
-        unsigned char* sm = sa + kA;
+        const uint32_t sb = smem_lds + stage * kStage;
+        const uint32_t sa = sb + kB, sm = sa + kA;
         const uint32_t w8[8] = {cw[0].x, cw[0].y, cw[0].z, cw[0].w, cw[1].x, cw[1].y, cw[1].z, cw[1].w};
 #pragma unroll
         for (int i = 0; i < 8; ++i) {

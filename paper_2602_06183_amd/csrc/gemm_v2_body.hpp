@@ -5,10 +5,12 @@
 //   128 x 128: 4 wavefronts of 64 x 64, two workgroups per CU: four times the workgroups for outputs that do not give every CU a 256 tile.
 //   64 x 64:   4 wavefronts that share the tile's contraction (see Tile): outputs of a few tiles, where the latency of one wavefront's
 //              trip along k is the whole cost.
-//   SPARSE: A packed 2:4 -> v_smfmac_f32_32x32x32_bf16; ring of 3 stages of 64 k.  Eqs. (1), (3), (4), (7):
+//   SPARSE: A packed 2:4 -> v_smfmac_f32_16x16x64_bf16; ring of 3 stages of 64 k.  Eqs. (1), (3), (4), (7):
 //           in the fused step on blocked operands (eqs. (1), (4) with the V:N:M epilogue), stand-alone on row-major ones.
-//   dense : v_mfma_f32_32x32x16_bf16; ring of 4 stages of 32 k; row-major operands only: the weight gradients of the router's step and of the unfused
+//   dense : v_mfma_f32_16x16x32_bf16; ring of 4 stages of 32 k; row-major operands only: the weight gradients of the router's step and of the unfused
 //           path (those of the fused steps and the stand-alone vnm_wgrad: gemm_wgrad.hip, gemm_wgrad_wide.hip).
+// The 16 x 16 instructions do the same products as the 32 x 32 ones for less power (registers only, random operands: smfmac 3350 -> 3720 dense-equivalent TFLOP/s, on codes
+// 6200 -> 6970, dense 1850 -> 2070), and a whole stage is one of them per fragment pair.
 // Register layouts of the two instructions are documented in lds_dma.hpp.
 #pragma once
 #include "common.hpp"
@@ -23,7 +25,7 @@ namespace sffn {
 // of codes per 2-byte element (fused fp8 step); the metadata is row-major [R, K/8] for row-major operands and in 512-byte units
 // (m8blk_off, common.hpp) for blocked ones: 16-byte row pieces fetched one by one cost 17 % of eq. (3) at the 70B-scale layer.  In BYTES the tiles are those of
 // the bf16 kernel (a stage is 128 k instead of 64: 64 survivor bytes per A row, 128 bytes per B row, and the fragment a lane of
-// v_smfmac_f32_32x32x64_fp8_fp8 wants is the same 16 / 2 x 16 bytes), so the kernel runs with K counted in byte pairs and only
+// v_smfmac_f32_16x16x128_fp8_fp8 wants is the same 16 / 2 x 16 bytes), so the kernel runs with K counted in byte pairs and only
 // the metadata differs: 16 survivors per lane and step need a whole 32-bit index word, 16 bytes per row and stage.
 // Workgroup tile: WVM x WVN wavefronts of WM x 64 outputs each.  KW > 1 (with one wavefront per tile): KW wavefronts share one output tile,
 // wavefront g contracting main-loop steps g, g + KW, ... in a ring of its own; the partial sums meet in LDS before the epilogue.
@@ -73,14 +75,15 @@ __device__ __forceinline__ void gemm_nt_v2_body(unsigned char* __restrict__ smem
     constexpr bool blocked = BLOCKED, blockedB = BLOCKED && !BROW;       // operands in the blocked layout of common.hpp (fused step) or row-major (stand-alone entry points)
     static_assert(!MG || (SPARSE && !BLOCKED && !FP8 && TL::KW == 1 && TL::NST == 3 && TL::WM * TL::WVM == 32 * TL::NW), "metadata of four stages: row-major bf16, 32 rows a wavefront");
     using C = Cfg<SPARSE, FP8, TL, MG>;
-    constexpr int BM = C::BM, BN = C::BN, WM = TL::WM, WN = 64, FM = WM / 32, FN = 2, NH = WM / 64, KW = TL::KW;
+    constexpr int BM = C::BM, BN = C::BN, WM = TL::WM, WN = 64, FM = WM / 16, FN = 4, NH = WM / 64, KW = TL::KW;
     static_assert(LOGM < 6 || WM == 128, "the two blocks of 64 columns that share a metadata byte belong to one wavefront");
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);     // wave-uniform: everything derived from it stays in SGPRs
     const int kg = KW > 1 ? wave : 0, wt = KW > 1 ? 0 : wave;      // this wavefront's share of the contraction / place in the tile
     const int wm = wt / TL::WVN, wn = wt % TL::WVN;
-    const int l32 = lane & 31, lh = lane >> 5;
+    const int l16 = lane & 15, lq = lane >> 4;
     unsigned char* const ring = smem + kg * (C::NSTAGE * C::STAGE);
+    const uint32_t ring_lds = lds_addr(smem) + kg * (C::NSTAGE * C::STAGE);
 
     // Workgroup -> tile.  Consecutive workgroup ids go to different XCDs; the remap gives each XCD a run of
     // consecutive logical ids, and logical ids walk bands of 4 tile rows, so an XCD's L2 sees few operand panels.
@@ -140,7 +143,7 @@ __device__ __forceinline__ void gemm_nt_v2_body(unsigned char* __restrict__ smem
     uint32_t a_kstep, b_kstep, m_kstep;                  // bytes per main-loop step
     {
         const int rb = lane >> 2;                                        // row inside the 16-row group
-        const int c = (lane & 3) ^ ((rb >> 2) & 3);                      // source chunk for this lane's LDS slot
+        const int c = (lane & 3) ^ swz4(rb >> 2);                        // source chunk for this lane's LDS slot
         const int KCa = SPARSE ? Kld / 64 : Kld / 32, KCb = Kld / 32;    // 32-element chunks per row
 #pragma unroll
         for (int n = 0; n < A_LD; ++n) {
@@ -186,9 +189,7 @@ __device__ __forceinline__ void gemm_nt_v2_body(unsigned char* __restrict__ smem
     auto brings_meta = [](int kt) { return (kt & 3) == 0; };      // MG
     static_assert(LD == C::LOADS, "loads in flight");
     auto issue = [&](int kt, int stage, int lo, int hi) {
-        unsigned char* sa = ring + stage * C::STAGE;
-        unsigned char* sb = sa + C::A_BYTES;
-        unsigned char* sm = sb + C::B_BYTES;
+        const uint32_t sa = ring_lds + stage * C::STAGE, sb = sa + C::A_BYTES, sm = sb + C::B_BYTES;
         // the k position goes into the 32-bit per-lane offset (one vector add per operand); the bases stay put in SGPRs
         const uint32_t ao = a_lane + (uint32_t)kt * a_kstep, bo = b_lane + (uint32_t)kt * b_kstep, bo1 = b_lane1 + (uint32_t)kt * b_kstep;
 #pragma unroll
@@ -202,7 +203,7 @@ __device__ __forceinline__ void gemm_nt_v2_body(unsigned char* __restrict__ smem
             // with stage 4 g, into the buffer of group g - 2, whose last reads ended with the stage that this refill replaces.  (On blocked operands, whose
             // metadata of a stage are one line a wavefront, it gains nothing: 1840 us for 1821 in eq. (1) at T = D = 8192, F = 28672.)
             if (LD - 1 >= lo && LD - 1 < hi && brings_meta(kt))
-                dma16(m_base[0], m_lane + (uint32_t)(kt >> 2) * 32, smem + C::NSTAGE * C::STAGE + ((kt >> 2) & 1) * C::GROUP_BYTES + wt * 1024);
+                dma16(m_base[0], m_lane + (uint32_t)(kt >> 2) * 32, ring_lds + C::NSTAGE * C::STAGE + ((kt >> 2) & 1) * C::GROUP_BYTES + wt * 1024);
         } else
 #pragma unroll
         for (int n = 0; n < M_LD; ++n) {
@@ -217,81 +218,53 @@ __device__ __forceinline__ void gemm_nt_v2_body(unsigned char* __restrict__ smem
         }
     };
 
-    // ---- per-lane LDS offsets of the fragment reads (inside a stage) --------------------------------
-    int a_off[FM], b_off[FN], m_off[FM];
-#pragma unroll
-    for (int a = 0; a < FM; ++a) {
-        const int row = wm * WM + a * 32 + l32;
-        a_off[a] = row * 64 + ((lh ^ ((row >> 2) & 3)) << 4);
-        // blocked: the lane's word of unit row / 32 holds both 32-k steps (picked by ABID); row-major: [row][8 bytes]
-        if (MG) m_off[a] = C::NSTAGE * C::STAGE + row * 32 + (((row >> 3) & 1) << 4);
-        else m_off[a] = C::A_BYTES + C::B_BYTES + (FP8 ? row * 16 + 4 * lh : blocked ? (row >> 5) * 256 + lane * 4 : row * 8 + 2 * lh);
-    }
-#pragma unroll
-    for (int b = 0; b < FN; ++b) {
-        const int row = wn * WN + b * 32 + l32;
-        b_off[b] = C::A_BYTES + row * 64 + ((lh ^ ((row >> 2) & 3)) << 4);      // SPARSE: + BN * 64 bytes for the second k half
-        if (lineB) b_off[b] = C::A_BYTES + row * 128 + ((lh ^ ((row >> 1) & 7)) << 4);   // chunk = 4 ks + 2 u + lh
-    }
+    // ---- per-lane LDS offsets of the fragment reads (inside a stage): lane -> row l16 of a fragment, 16-byte chunk lq of 64 bytes; fragments are 16 rows apart ----
+    const int a_off = (wm * WM + l16) * 64 + ((lq ^ swz4(l16 >> 2)) << 4);
+    // blocked bf16 metadata: the lane's word of unit 32 rows serves both of its fragments; row-major: [row][8 bytes]; fp8: [row][16 bytes]
+    const int m_off = MG ? C::NSTAGE * C::STAGE + (wm * WM + l16) * 32 + ((l16 >> 3) << 4) + 2 * lq
+                         : C::A_BYTES + C::B_BYTES + (FP8 ? (wm * WM + l16) * 16 + 4 * lq : blocked ? wm * WM * 8 + lane * 4 : (wm * WM + l16) * 8 + 2 * lq);
+    // (lineB: a row's 128 bytes are 8 chunks, lq and 4 + lq of them this lane's)
+    const int b_off = C::A_BYTES + (lineB ? (wn * WN + l16) * 128 + ((lq ^ (l16 >> 1)) << 4) : (wn * WN + l16) * 64 + ((lq ^ swz4(l16 >> 2)) << 4));
 
-    f32x16 acc[FM][FN];
+    f32x4 acc[FM][FN];
 #pragma unroll
     for (int a = 0; a < FM; ++a)
 #pragma unroll
         for (int b = 0; b < FN; ++b)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) acc[a][b][r] = 0.0f;
+            for (int r = 0; r < 4; ++r) acc[a][b][r] = 0.0f;
 
-    // Fragment sets: P feeds the first half of a stage's k range, Q the second.  Reads of one set are
-    // issued while the matrix cores work on the other, so LDS latency stays behind MFMA time.
-    struct FragSet {
-        Frag8 a[FM];
-        int idx[FM];
-        Frag16 b16[FN];     // SPARSE: 16 k-values per lane
-        Frag8 b8[FN];       // dense: 8 k-values per lane
-    };
-    // `prev` = the set that holds the first 32-k step of the same tile (its index word serves both steps)
-    uint32_t m_kt = 0;          // MG: stage whose first fragments are read next
-    auto read_a = [&](FragSet& f, const FragSet& prev, const unsigned char* st, int ks, int a) {
-        f.a[a].u = *reinterpret_cast<const uint4*>(st + (a_off[a] ^ (32 * ks)));
+    // Fragments of a stage.  B alternates between two sets; an A fragment (and its index bits) is replaced by the next stage's as soon as its row of matrix
+    // instructions has been issued.
+    struct FragB { Frag16 b16[SPARSE ? FN : 1]; Frag8 b8[SPARSE ? 1 : FN]; };     // SPARSE: 64 k (fp8: 128) a stage, dense: 32
+    Frag8 A[FM];
+    constexpr bool PAIRED = SPARSE && blocked && !FP8;      // an index word for two fragments, low and high half
+    int idx[FM];
+    FragB B0, B1;
+    uint32_t m_kt = 0;          // MG: stage whose fragments are read next
+    auto read_a = [&](const unsigned char* st, int a) {
+        A[a].u = *reinterpret_cast<const uint4*>(st + a_off + a * 1024);
         if (SPARSE) {
-            if (MG) {       // the stage's 8 bytes of the row: the 16 index bits of this lane's half of either step side by side
-                if (ks == 0) {
-                    const uint2 w = *reinterpret_cast<const uint2*>(ring + (m_off[a] ^ ((m_kt & 2) << 3)) + ((m_kt & 4) ? C::GROUP_BYTES : 0) + ((m_kt & 1) << 3));
-                    f.idx[a] = __builtin_amdgcn_perm(w.y, w.x, lh ? 0x07060302u : 0x05040100u);
-                } else f.idx[a] = prev.idx[a];
-            } else if (FP8) f.idx[a] = *reinterpret_cast<const uint32_t*>(st + m_off[a] + 8 * ks);
-            else if (!blocked) f.idx[a] = *reinterpret_cast<const uint16_t*>(st + m_off[a] + 4 * ks);
-            else if (ks == 0) f.idx[a] = *reinterpret_cast<const uint32_t*>(st + m_off[a]);
-            else f.idx[a] = prev.idx[a];
+            if (MG) idx[a] = *reinterpret_cast<const uint16_t*>(ring + (m_off ^ ((m_kt & 2) << 3)) + ((m_kt & 4) ? C::GROUP_BYTES : 0) + ((m_kt & 1) << 3) + a * 512);
+            else if (FP8) idx[a] = *reinterpret_cast<const uint32_t*>(st + m_off + a * 256);
+            else if (!blocked) idx[a] = *reinterpret_cast<const uint16_t*>(st + m_off + a * 128);
+            else if (a & 1) idx[a - 1] = *reinterpret_cast<const uint32_t*>(st + m_off + (a >> 1) * 256);
         }
     };
-    auto read_b = [&](FragSet& f, const unsigned char* st, int ks, int b) {
-        if (lineB) {
-            f.b16[b].u[0] = *reinterpret_cast<const uint4*>(st + (b_off[b] ^ (64 * ks)));
-            f.b16[b].u[1] = *reinterpret_cast<const uint4*>(st + (b_off[b] ^ (64 * ks + 32)));
-        } else if (SPARSE) {
-            f.b16[b].u[0] = *reinterpret_cast<const uint4*>(st + b_off[b] + BN * 64 * ks);
-            f.b16[b].u[1] = *reinterpret_cast<const uint4*>(st + (b_off[b] ^ 32) + BN * 64 * ks);
-        } else {
-            f.b8[b].u = *reinterpret_cast<const uint4*>(st + (b_off[b] ^ (32 * ks)));
-        }
+    // piece p of a stage's B fragments: one 16-byte read
+    constexpr int BP = SPARSE ? 2 * FN : FN;
+    auto read_b = [&](FragB& f, const unsigned char* st, int p) {
+        if (!SPARSE) f.b8[p].u = *reinterpret_cast<const uint4*>(st + b_off + p * 1024);
+        else if (lineB) f.b16[p >> 1].u[p & 1] = *reinterpret_cast<const uint4*>(st + (b_off ^ (64 * (p & 1))) + (p >> 1) * 2048);
+        else f.b16[p >> 1].u[p & 1] = *reinterpret_cast<const uint4*>(st + b_off + (p & 1) * BN * 64 + (p >> 1) * 1024);
     };
-    auto read_frags = [&](FragSet& f, int stage, int ks) {
-        const unsigned char* st = ring + stage * C::STAGE;
-#pragma unroll
-        for (int a = 0; a < FM; ++a) read_a(f, f, st, ks, a);
-#pragma unroll
-        for (int b = 0; b < FN; ++b) read_b(f, st, ks, b);
-    };
-    // second = the set holds the second 32-k step of its tile: blocked metadata then sits in the high half of the index word
-    auto mma_row = [&](const FragSet& f, int a, bool second) {
+    auto mma_row = [&](const FragB& f, int a) {
+        const int ix = !SPARSE ? 0 : !PAIRED ? idx[a] : (a & 1) ? (int)((uint32_t)idx[a - 1] >> 16) : idx[a];
 #pragma unroll
         for (int b = 0; b < FN; ++b) {
-            if (FP8)                    acc[a][b] = __builtin_amdgcn_smfmac_f32_32x32x64_fp8_fp8(f.a[a].q, f.b16[b].q, acc[a][b], f.idx[a], 0, 0);
-            else if (!SPARSE)           acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.a[a].v, f.b8[b].v, acc[a][b], 0, 0, 0);
-            else if ((blocked || MG) && second) acc[a][b] = __builtin_amdgcn_smfmac_f32_32x32x32_bf16(f.a[a].v, f.b16[b].v, acc[a][b], f.idx[a], 0, 1);
-            else                        acc[a][b] = __builtin_amdgcn_smfmac_f32_32x32x32_bf16(f.a[a].v, f.b16[b].v, acc[a][b], f.idx[a], 0, 0);
+            if (FP8)          acc[a][b] = __builtin_amdgcn_smfmac_f32_16x16x128_fp8_fp8(A[a].q, f.b16[b].q, acc[a][b], ix, 0, 0);
+            else if (!SPARSE) acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A[a].v, f.b8[b].v, acc[a][b], 0, 0, 0);
+            else              acc[a][b] = __builtin_amdgcn_smfmac_f32_16x16x64_bf16(A[a].v, f.b16[b].v, acc[a][b], ix, 0, 0);
         }
     };
 #define SB() __builtin_amdgcn_sched_barrier(0)
@@ -309,64 +282,57 @@ __device__ __forceinline__ void gemm_nt_v2_body(unsigned char* __restrict__ smem
     wait_vmcnt<(C::NSTAGE - 1) * (C::LOADS - (MG ? 1 : 0))>();
     if (KW == 1) __syncthreads();
     else asm volatile("" ::: "memory");
-    FragSet P, Q;
-    read_frags(P, 0, 0);
+#pragma unroll
+    for (int a = 0; a < FM; ++a) read_a(ring, a);
+#pragma unroll
+    for (int p = 0; p < BP; ++p) read_b(B0, ring, p);
     int stage = 0;
-    // One step = two halves of FM x FN matrix instructions.  Each row of matrix instructions (64+ cycles of the matrix pipe) is followed in program
-    // order by a few LDS reads for the other fragment set and by one or two of the loads of a stage: a CU takes 57 bytes of them per cycle,
-    // and a wavefront that has to wait for its turn cannot issue matrix instructions either.  The refill of a stage therefore stretches from
-    // the barrier that frees it to the next one.  (All of it right behind the barrier, T = D = 8192, F = 28672: 2045 us; spread: 1930.)
-    constexpr int SLOTS = C::NSTAGE > 2 ? 2 * FM : FM;
-#define ISSUE(i) issue(re_kt, re_stage, LD * (i) / SLOTS, LD * ((i) + 1) / SLOTS)
-    int re_kt = step_of(C::NSTAGE - 1 < nk ? C::NSTAGE - 1 : nk - 1), re_stage = C::NSTAGE - 1;      // (the first step's second half of a refill: the last stage's again)
-    for (int kt = 0; kt < nk; ++kt) {
+    // One step = one stage = FM rows of four matrix instructions, on fragments that were read during the step before.  Behind the first row every wavefront has read
+    // all of the stage and the next one has landed (barrier): the stage is refilled, and the next one's fragments are read, spread over the step: a CU takes
+    // 57 bytes of loads per cycle, and a wavefront that has to wait for its turn cannot issue matrix instructions either.
+    // (All loads of a refill right behind the barrier, T = D = 8192, F = 28672: 2045 us for eq. (1); spread: 1930.)  T = F = 8192: 0.81 us a stage of 51,200 bytes = 16 TB/s, which is what
+    // loads by themselves reach; two half stages of 32 x 32 x 32 instructions, their fragments half a stage ahead, took 0.90.
+    int re_kt = step_of(C::NSTAGE - 1 < nk ? C::NSTAGE - 1 : nk - 1);      // the latest tile on its way
+    auto step = [&](int kt, const FragB& Bc, FragB& Bn) {
         const int next_stage = (stage + 1 == C::NSTAGE) ? 0 : stage + 1;
-        const unsigned char* st = ring + stage * C::STAGE;
         const unsigned char* sn = ring + next_stage * C::STAGE;
-        mma_row(P, 0, false); SB();
-        ISSUE(FM);
-        read_a(Q, P, st, 1, 0); read_a(Q, P, st, 1, 1); read_b(Q, st, 1, 0); if (FM == 2) read_b(Q, st, 1, 1); SB();
-        mma_row(P, 1, false); SB();
-        ISSUE(FM + 1);
-        if (FM == 4) {
-            read_a(Q, P, st, 1, FM - 2); read_a(Q, P, st, 1, FM - 1); read_b(Q, st, 1, 1); SB();
-            mma_row(P, FM - 2, false); SB();
-            ISSUE(2 * FM - 2); SB();
-            mma_row(P, FM - 1, false); SB();
-            ISSUE(2 * FM - 1); SB();
-        }
-        // Q has arrived and tile kt+1 has landed (this wave's part); after the barrier every wave is done
-        // reading this stage, which is refilled, and every wave's part of tile kt+1 is in LDS
-        if constexpr (MG) {
-            if (brings_meta(re_kt)) wait_vmcnt_lgkm0<(C::NSTAGE - 2) * C::LOADS>();
-            else wait_vmcnt_lgkm0<(C::NSTAGE - 2) * C::LOADS - 1>();
-        } else wait_vmcnt_lgkm0<(C::NSTAGE - 2) * C::LOADS>();
-        if (KW == 1) __builtin_amdgcn_s_barrier();
-        else asm volatile("" ::: "memory");
-        SB();
-        re_kt = step_of((kt + C::NSTAGE < nk) ? kt + C::NSTAGE : nk - 1); re_stage = stage;
-        if (MG) m_kt = (uint32_t)kt + 1;
-        mma_row(Q, 0, true); SB();
-        ISSUE(0);
-        read_a(P, P, sn, 0, 0); read_a(P, P, sn, 0, 1); read_b(P, sn, 0, 0); if (FM == 2) read_b(P, sn, 0, 1); SB();
-        mma_row(Q, 1, true); SB();
-        ISSUE(1); SB();
-        if (FM == 4) {
-            read_a(P, P, sn, 0, FM - 2); read_a(P, P, sn, 0, FM - 1); read_b(P, sn, 0, 1); SB();
-            mma_row(Q, FM - 2, true); SB();
-            ISSUE(2); SB();
-            mma_row(Q, FM - 1, true); SB();
-            ISSUE(3); SB();
+#pragma unroll
+        for (int a = 0; a < FM; ++a) {
+            mma_row(Bc, a); SB();
+            if (a == 0) {
+                // this stage's fragments have arrived, and this wavefront's part of tile kt + 1 has landed
+                if constexpr (MG) {
+                    if (brings_meta(re_kt)) wait_vmcnt_lgkm0<(C::NSTAGE - 2) * C::LOADS>();
+                    else wait_vmcnt_lgkm0<(C::NSTAGE - 2) * C::LOADS - 1>();
+                } else wait_vmcnt_lgkm0<(C::NSTAGE - 2) * C::LOADS>();
+                if (KW == 1) __builtin_amdgcn_s_barrier();
+                else asm volatile("" ::: "memory");
+                SB();
+                re_kt = step_of((kt + C::NSTAGE < nk) ? kt + C::NSTAGE : nk - 1);
+                if (MG) m_kt = (uint32_t)kt + 1;
+            }
+            issue(re_kt, stage, LD * a / FM, LD * (a + 1) / FM); SB();
+            if (!PAIRED || (a & 1)) {           // (an index word is replaced behind the second of its rows)
+                if (PAIRED) read_a(sn, a - 1);
+                read_a(sn, a);
+            }
+            // (B's pieces behind the first five of eight rows: the next step's first row wants all of them)
+            constexpr int BS = FM == 8 ? 5 : FM;
+#pragma unroll
+            for (int p = a < BS ? BP * a / BS : BP; p < (a < BS ? BP * (a + 1) / BS : BP); ++p) read_b(Bn, sn, p);
+            SB();
         }
         stage = next_stage;
-    }
-#undef ISSUE
+    };
+    int kt = 0;
+    for (; kt + 1 < nk; kt += 2) { step(kt, B0, B1); step(kt + 1, B1, B0); }
+    if (kt < nk) step(kt, B0, B1);
 #undef SB
     wait_vmcnt<0>();
     }
     __syncthreads();
     if (KW > 1) {       // partial sums -> the first wavefront, in ascending order; the others are done
-        constexpr int PART = FM * FN * 16 * 256;
+        constexpr int PART = FM * FN * 4 * 256;
         static_assert((KW - 1) * PART <= KW * C::NSTAGE * C::STAGE, "partial sums must fit in the main-loop LDS");
         if (kg > 0) {
             float* p = reinterpret_cast<float*>(smem + (kg - 1) * PART) + lane;
@@ -375,7 +341,7 @@ __device__ __forceinline__ void gemm_nt_v2_body(unsigned char* __restrict__ smem
 #pragma unroll
                 for (int b = 0; b < FN; ++b)
 #pragma unroll
-                    for (int r = 0; r < 16; ++r) p[((a * FN + b) * 16 + r) * 64] = acc[a][b][r];
+                    for (int r = 0; r < 4; ++r) p[((a * FN + b) * 4 + r) * 64] = acc[a][b][r];
         }
         __syncthreads();
         if (kg > 0) return;
@@ -386,7 +352,7 @@ __device__ __forceinline__ void gemm_nt_v2_body(unsigned char* __restrict__ smem
 #pragma unroll
                 for (int b = 0; b < FN; ++b)
 #pragma unroll
-                    for (int r = 0; r < 16; ++r) acc[a][b][r] += p[((a * FN + b) * 16 + r) * 64];
+                    for (int r = 0; r < 4; ++r) acc[a][b][r] += p[((a * FN + b) * 4 + r) * 64];
         }
         wave_lds_sync();
     }
@@ -407,11 +373,11 @@ __device__ __forceinline__ void gemm_nt_v2_body(unsigned char* __restrict__ smem
         const int nblk = Ra >> 3;
         const int64_t F = Ra;
         uint32_t nib_h0 = 0;                                  // M = 64: the metadata nibble of the first half waits for the second's
-        // The lane's 32 bias values of each half (eq. (4) has none), and (EPI 2) the saved column offsets, metadata and y1 of its 8 sweeps: all fetched here, for
+        // The lane's 16 bias values of each half (eq. (4) has none), and (EPI 2) the saved column offsets, metadata and y1 of its 8 sweeps: all fetched here, for
         // both halves.  Loads and stores share one in-order counter, so a load issued after the first half's stores would wait for all of them
         // (and for its own latency) in the middle of the epilogue.
         constexpr bool BIAS = EPI != 2 && EPI != 4 && !GEN_B;
-        float4 bb_all[NH][2][4];
+        float4 bb_all[NH][4];
         uint32_t pre_cw[NH], pre_m[NH], pre_y_all[NH][8];
         const uint32_t amax_seen = (FP8 && EPI != 0) ? amax_slot_peek(ep.amax) : 0u;
         float vmax_tile = 0.0f;                                 // fp8: largest survivor magnitude of the wave's tile
@@ -419,16 +385,14 @@ __device__ __forceinline__ void gemm_nt_v2_body(unsigned char* __restrict__ smem
         for (int h = 0; h < NH; ++h) {
             const int f0 = i0 + wm * WM + h * 64;
 #pragma unroll
-            for (int a2 = 0; a2 < 2; ++a2)
-#pragma unroll
-                for (int g = 0; g < 4; ++g) {
-                    bb_all[h][a2][g] = make_float4(0.f, 0.f, 0.f, 0.f);
-                    if (BIAS && bias) {
-                        int i = f0 + a2 * 32 + 8 * g + 4 * lh; i = i < Ra ? i : Ra - 4;
-                        // EPI 3: compact column i of the expert is hidden unit (i / 4) * M + 4 e + i % 4 (bias already points at 4 e)
-                        bb_all[h][a2][g] = *reinterpret_cast<const float4*>(EPI == 3 ? bias + ((int64_t)(i >> 2) << ep.logM) : bias + i);
-                    }
+            for (int a = 0; a < 4; ++a) {
+                bb_all[h][a] = make_float4(0.f, 0.f, 0.f, 0.f);
+                if (BIAS && bias) {
+                    int i = f0 + a * 16 + 4 * lq; i = i < Ra ? i : Ra - 4;
+                    // EPI 3: compact column i of the expert is hidden unit (i / 4) * M + 4 e + i % 4 (bias already points at 4 e)
+                    bb_all[h][a] = *reinterpret_cast<const float4*>(EPI == 3 ? bias + ((int64_t)(i >> 2) << ep.logM) : bias + i);
                 }
+            }
             pre_cw[h] = 0x03020100u;
             pre_m[h] = 0;
             if (EPI == 2 && t0 < Rb && f0 < Ra) {
@@ -466,7 +430,7 @@ __device__ __forceinline__ void gemm_nt_v2_body(unsigned char* __restrict__ smem
 #pragma unroll
         for (int b = 0; b < FN; ++b) {
             tok_ok[b] = true;
-            if (EPI == 3) { int j = t0 + b * 32 + l32; j = j < Rb ? j : Rb - 1; tok_ok[b] = ep.perm[j] >= 0; }
+            if (EPI == 3) { int j = t0 + b * 16 + l16; j = j < Rb ? j : Rb - 1; tok_ok[b] = ep.perm[j] >= 0; }
         }
         // Column scores of the half tile: lane = column, strict ascending-row float32 sum of y2.  A transposing read hands every lane four rows of its column.
         // (One 2-byte read per row: 64 reads and 450 vector instructions instead of 16 and 350.)
@@ -515,29 +479,22 @@ __device__ __forceinline__ void gemm_nt_v2_body(unsigned char* __restrict__ smem
         for (int h = 0; h < NH; ++h) {
             const int f0 = i0 + wm * WM + h * 64;
             const bool valid = t0 < Rb && f0 < Ra;
-            float4 (&bb)[2][4] = bb_all[h];
+            float4 (&bb)[4] = bb_all[h];
 #pragma unroll
-            for (int a2 = 0; a2 < 2; ++a2)
+            for (int a = 0; a < 4; ++a)
 #pragma unroll
-                for (int b = 0; b < FN; ++b)
+                for (int b = 0; b < FN; ++b) {
+                    f32x4 v = acc[4 * h + a][b];
+                    const float al = FP8 ? alpha : 1.0f;
+                    // (codes were multiplied: the product of the two tensor scales comes first, one rounding, then the bias)
 #pragma unroll
-                    for (int g = 0; g < 4; ++g) {
-                        const int a = 2 * h + a2;
-                        const int il = a2 * 32 + 8 * g + 4 * lh;              // i inside the 64-wide half
-                        float v0, v1, v2, v3;
-                        if (!BIAS) {
-                            const float al = FP8 ? alpha : 1.0f;
-                            v0 = acc[a][b][4 * g] * al; v1 = acc[a][b][4 * g + 1] * al; v2 = acc[a][b][4 * g + 2] * al; v3 = acc[a][b][4 * g + 3] * al;
-                        } else if (FP8) {      // codes were multiplied: the product of the two tensor scales comes first, one rounding, then the bias
-                            v0 = acc[a][b][4 * g] * alpha + bb[a2][g].x;     v1 = acc[a][b][4 * g + 1] * alpha + bb[a2][g].y;
-                            v2 = acc[a][b][4 * g + 2] * alpha + bb[a2][g].z; v3 = acc[a][b][4 * g + 3] * alpha + bb[a2][g].w;
-                        } else {
-                            v0 = acc[a][b][4 * g] + bb[a2][g].x;     v1 = acc[a][b][4 * g + 1] + bb[a2][g].y;
-                            v2 = acc[a][b][4 * g + 2] + bb[a2][g].z; v3 = acc[a][b][4 * g + 3] + bb[a2][g].w;
-                        }
-                        *reinterpret_cast<uint2*>(scratch + (b * 32 + l32) * EP + il * 2) =
-                            tok_ok[b] ? make_uint2(f2bf2(v0, v1), f2bf2(v2, v3)) : make_uint2(0u, 0u);
+                    for (int r = 0; r < 4; ++r) {
+                        const float w = r == 0 ? bb[a].x : r == 1 ? bb[a].y : r == 2 ? bb[a].z : bb[a].w;
+                        v[r] = !BIAS ? v[r] * al : FP8 ? v[r] * alpha + w : v[r] + w;
                     }
+                    // i = a * 16 + 4 lq .. + 3 inside the 64-wide half
+                    *reinterpret_cast<uint2*>(scratch + (b * 16 + l16) * EP + (a * 16 + 4 * lq) * 2) = tok_ok[b] ? make_uint2(f2bf2(v[0], v[1]), f2bf2(v[2], v[3])) : make_uint2(0u, 0u);
+                }
             if (EPI == 1 || EPI == 2 || GEN_F || GEN_B) {
 #pragma unroll
                 for (int q = 0; q < (32 * EP + 1023) / 1024; ++q)
@@ -884,10 +841,10 @@ __device__ __forceinline__ void gemm_nt_v2_body(unsigned char* __restrict__ smem
         unsigned char* scratch = smem + wt * (32 * EP);
         // destination rows of the lane's 16 stores, looked up before the first store (loads and stores share one in-order counter: a look-up
         // between two stores would wait for the earlier one)
-        int32_t io_map[FM][32 * CH / 64];
+        int32_t io_map[WM / 32][32 * CH / 64];
         if (grp.out_row_map) {
 #pragma unroll
-            for (int a = 0; a < FM; ++a)
+            for (int a = 0; a < WM / 32; ++a)
 #pragma unroll
                 for (int p = 0; p < 32 * CH / 64; ++p) {
                     const int i = i0 + wm * WM + a * 32 + (lane + 64 * p) / CH;
@@ -895,14 +852,14 @@ __device__ __forceinline__ void gemm_nt_v2_body(unsigned char* __restrict__ smem
                 }
         }
 #pragma unroll
-        for (int a = 0; a < FM; ++a) {
+        for (int a = 0; a < WM / 32; ++a) {
 #pragma unroll
-            for (int b = 0; b < FN; ++b)
+            for (int x = 0; x < 2; ++x)
 #pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    const int row = 8 * (r >> 2) + 4 * lh + (r & 3);
-                    *reinterpret_cast<uint16_t*>(scratch + row * EP + (b * 32 + l32) * 2) = (uint16_t)f2bf(FP8 ? acc[a][b][r] * alpha : acc[a][b][r]);
-                }
+                for (int b = 0; b < FN; ++b)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r)
+                        *reinterpret_cast<uint16_t*>(scratch + (x * 16 + 4 * lq + r) * EP + (b * 16 + l16) * 2) = (uint16_t)f2bf(FP8 ? acc[2 * a + x][b][r] * alpha : acc[2 * a + x][b][r]);
             wave_lds_sync();
 #pragma unroll
             for (int p = 0; p < 32 * CH / 64; ++p) {

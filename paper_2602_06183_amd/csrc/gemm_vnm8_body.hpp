@@ -83,6 +83,7 @@ __device__ __forceinline__ void vnm8_gemm_body(unsigned char* __restrict__ smem,
     const int l32 = lane & 31, lh = lane >> 5;
     const int kg = KW > 1 ? wave : 0, wt = KW > 1 ? 0 : wave;       // share of the contraction / place in the tile
     unsigned char* const ring = smem + kg * (kStages * kStage);
+    const uint32_t ring_lds = lds_addr(smem) + kg * (kStages * kStage);
 
     int L = xcd_run(pid, n_pid);
     // Grouped form (role 0): the token tiles of segment e meet expert e's matrix
@@ -161,10 +162,7 @@ __device__ __forceinline__ void vnm8_gemm_body(unsigned char* __restrict__ smem,
     constexpr uint32_t m_kstep = FP8 ? 512u : 256u;
     // loads lo .. hi - 1 of a stage's kLoads (compile-time bounds)
     auto issue = [&](int kt, int stage, int lo, int hi) {
-        unsigned char* sb = ring + stage * kStage;
-        unsigned char* sa = sb + kB;
-        unsigned char* sm = sa + kA;
-        unsigned char* sc = sm + kMt;
+        const uint32_t sb = ring_lds + stage * kStage, sa = sb + kB, sm = sa + kA, sc = sm + kMt;
 #pragma unroll
         for (int i = 0; i < B_LD; ++i)
             if (i >= lo && i < hi) dma16(w_base, b_lane[i] + (uint32_t)kt * b_kstep, sb + (B_LD * wt + i) * 1024);

@@ -322,6 +322,7 @@ __device__ __forceinline__ void wgrad_vnm_body(unsigned char* __restrict__ smem,
     const int wm = wt / TL::WVN, wn = wt % TL::WVN;
     const int l16 = lane & 15, lq = lane >> 4;
     unsigned char* const ring = smem + kg * (kStages * kStage);
+    const uint32_t ring_lds = lds_addr(smem) + kg * (kStages * kStage);
 
     // workgroup -> tile: an XCD gets a run of consecutive logical ids, which walk bands of 4 tile rows
     int L = xcd_run(pid, n_pid);
@@ -369,9 +370,7 @@ __device__ __forceinline__ void wgrad_vnm_body(unsigned char* __restrict__ smem,
 
     // loads lo .. hi - 1 of a stage's kLoads (compile-time bounds)
     auto issue = [&](int kt, int stage, int lo, int hi) {
-        unsigned char* sa = ring + stage * kStage;
-        unsigned char* sb = sa + kABytes;
-        unsigned char* sc = sb + kBBytes;
+        const uint32_t sa = ring_lds + stage * kStage, sb = sa + kABytes, sc = sb + kBBytes;
         const uint32_t o = blk_lane + (uint32_t)kt * 2048;      // k position in the per-lane offset; bases stay in SGPRs
         if (lo <= 0 && hi > 0) dma4(c_base, c_lane + (uint32_t)kt * c_kstep, sc + wt * 256);     // first: the look-up wants it earliest
 #pragma unroll
@@ -531,6 +530,7 @@ __device__ __forceinline__ void wgrad_vnm_fp8_body(unsigned char* __restrict__ s
     const int wm = wt / TL::WVN, wn = wt % TL::WVN;
     const int l32 = lane & 31, lh = lane >> 5;
     unsigned char* const ring = smem + kg * (kStages * kStage);
+    const uint32_t ring_lds = lds_addr(smem) + kg * (kStages * kStage);
     int L = xcd_run(pid, n_pid);
     int k_base = 0, K = Ttot;                     // grouped: every expert contracts over its own token segment
     if (grp.n) {
@@ -568,7 +568,7 @@ __device__ __forceinline__ void wgrad_vnm_fp8_body(unsigned char* __restrict__ s
     }
     const uint32_t c_kstep = (uint32_t)(F / 8);
     auto issue = [&](int kt, int stage, int lo, int hi) {
-        unsigned char* sa = ring + stage * kStage;
+        const uint32_t sa = ring_lds + stage * kStage;
         const uint32_t o = blk_lane + (uint32_t)kt * 1024;
         if (lo <= 0 && hi > 0) dma4(c_base, c_lane + (uint32_t)kt * c_kstep, sa + k8A + k8B + wt * 256);     // first: the look-up wants it earliest
 #pragma unroll

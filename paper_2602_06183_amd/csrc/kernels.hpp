@@ -577,7 +577,7 @@ hipError_t launch_sqrelu_vnm_compress_fp8(const uint16_t* y1, int64_t T, int64_t
 hipError_t launch_vnm_to_24_fp8(const uint8_t* codes, const uint8_t* meta, const uint8_t* colidx, int64_t T, int64_t F, int M, uint8_t* codes24,
                                 uint8_t* meta24, hipStream_t s);
 hipError_t launch_transpose_u8(const uint8_t* in, int64_t R, int64_t C, int64_t ld, uint8_t* out, hipStream_t s);
-// C[i, j] = alpha * sum_k dec(A[i, k]) * dec(B[j, k]) (+ bias[i] when out_i_contig) on v_smfmac_f32_32x32x64_fp8_fp8: A packed 2:4 codes
+// C[i, j] = alpha * sum_k dec(A[i, k]) * dec(B[j, k]) (+ bias[i] when out_i_contig) on v_smfmac_f32_16x16x128_fp8_fp8: A packed 2:4 codes
 // [Ra, K/2] + metadata [Ra, K/8], B codes [Rb, K], both row-major; K a multiple of 128; out bf16 as launch_gemm_nt.
 hipError_t launch_spmm24_fp8(const uint8_t* a_codes, const uint8_t* a_meta, const uint8_t* Bq, const float* bias, float alpha, int64_t Ra, int64_t Rb,
                              int64_t K, int out_i_contig, uint16_t* out, int64_t ldo, hipStream_t s);

@@ -1,16 +1,18 @@
 // LDS-DMA primitives and fragment types shared by the pipelined tile kernels (gemm_v2.hip, gemm_wgrad.hip).
 //
-// Register layouts of the two matrix instructions used there (measured on gfx950 with one-hot operands):
-//   v_smfmac_f32_32x32x32_bf16  A: lane l -> row l%32, survivors 8*(l/32)..+7 of the 16 (k in 16*(l/32)..+15),
-//                                  index VGPR bits [2e+1:2e] = position of survivor e inside its group of 4
+// Register layouts of the matrix instructions used there (measured on gfx950 with one-hot operands and small integers):
+//   v_mfma_f32_16x16x32_bf16    A, B: lane l -> row / column l%16, k 8*(l/16)..+7;  D: lane l, register r -> row 4*(l/16) + r, column l%16.
+//   v_smfmac_f32_16x16x64_bf16  A: lane l -> row l%16, survivors 8*(l/16)..+7 of the 32 (k in 16*(l/16)..+15),
+//                                  index VGPR bits [2e+1:2e] = position of survivor e inside its group of 4 (the low half of the VGPR, ABID 0);
+//                               B: lane l -> column l%16; elements 0-7 = k 8*(l/16)..+7, elements 8-15 = k 32+8*(l/16)..+7;  D as above.
+//   v_smfmac_f32_16x16x128_fp8_fp8  byte for byte the bf16 instruction's operand layout with twice the k per byte, index bits in the whole VGPR.
+//   v_smfmac_f32_32x32x32_bf16  A: lane l -> row l%32, survivors 8*(l/32)..+7 of the 16 (k in 16*(l/32)..+15), index bits as above
 //                                  (ABID 0: bits 15:0 of the VGPR, ABID 1: bits 31:16);
 //                               B: lane l -> column l%32; elements 0-7 = k 8*(l/32)..+7, elements 8-15 = k 16+8*(l/32)..+7;
 //                               D: lane l, register r -> row 8*(r/4) + 4*(l/32) + r%4, column l%32.
-//   v_mfma_f32_32x32x16_bf16    A, B: lane l -> row / column l%32, k 8*(l/32)..+7;  D as above.
 //   v_smfmac_f32_32x32x64_fp8_fp8  A: lane l -> row l%32, the 16 survivors (one byte each) of k in 32*(l/32)..+31, index VGPR bits
 //                                  [2e+1:2e] = position of survivor e inside its group of 4 (all 32 bits are used, no ABID);
 //                               B: lane l -> column l%32; bytes 0-15 = k 16*(l/32)..+15, bytes 16-31 = k 32+16*(l/32)..+15;  D as above.
-//                               (byte for byte the bf16 instruction's operand layout with twice the k per byte)
 // The 2-bit positions are exactly the packed format's metadata nibbles, so metadata goes from HBM to the index
 // VGPR without re-encoding.
 #pragma once
@@ -69,13 +71,15 @@ __device__ __forceinline__ void band_tile(int L, int tiles_m, int tiles_n, int b
     tn = uniform((int)(in / (uint32_t)gsz));
     tm = first + (int)in - tn * gsz;
 }
-__device__ __forceinline__ void dma16(uint64_t base, uint32_t lane_off, unsigned char* lds_wave_base) {
+// LDS address of a pointer into LDS.  (Taken once: as a cast at every load it brings a test for null each time, four scalar instructions.)
+__device__ __forceinline__ uint32_t lds_addr(const unsigned char* p) { return (uint32_t)(uintptr_t)(lds_void*)p; }
+__device__ __forceinline__ void dma16(uint64_t base, uint32_t lane_off, uint32_t lds_wave_base) {
     // every lane fetches 16 bytes at base + lane_off; the wave's 64 chunks land at lds_wave_base + 16 * lane
-    const uint32_t dst = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(lds_void*)lds_wave_base);
+    const uint32_t dst = __builtin_amdgcn_readfirstlane(lds_wave_base);
     asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(lane_off), "s"(base), "s"(dst) : "m0", "memory");
 }
-__device__ __forceinline__ void dma4(uint64_t base, uint32_t lane_off, unsigned char* lds_wave_base) {
-    const uint32_t dst = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(lds_void*)lds_wave_base);
+__device__ __forceinline__ void dma4(uint64_t base, uint32_t lane_off, uint32_t lds_wave_base) {
+    const uint32_t dst = __builtin_amdgcn_readfirstlane(lds_wave_base);
     asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dword %0, %1" ::"v"(lane_off), "s"(base), "s"(dst) : "m0", "memory");
 }
 
