@@ -184,31 +184,35 @@ __device__ __forceinline__ void vnm_gather_body(unsigned char* __restrict__ smem
     if (nk > 0) {
 #pragma unroll
     for (int p = 0; p < kGStages; ++p) {
-        const int kt = step_of(p < nk ? p : nk - 1);
-        lookup(kt);
-        issue(kt, p);
+        if (p >= nk) break;
+        lookup(step_of(p));
+        issue(step_of(p), p);
     }
-    wait_vmcnt<(kGStages - 1) * kGLoads>();
+    if (nk >= kGStages) wait_vmcnt<(kGStages - 1) * kGLoads>();
+    else wait_vmcnt<0>();
     if (KW == 1) __syncthreads();
     else asm volatile("" ::: "memory");
     FragSet P, Q;
     read_frags(P, ring, 0);
     int stage = 0;
     for (int kt = 0; kt < nk; ++kt) {
-        const int nxt = step_of((kt + kGStages < nk) ? kt + kGStages : nk - 1);
+        const bool more = kt + kGStages < nk;         // (the last steps load nothing: gemm_v2_body.hpp)
         const int next_stage = (stage + 1 == kGStages) ? 0 : stage + 1;
         const unsigned char* st = ring + stage * kGStage;
         const unsigned char* sn = ring + next_stage * kGStage;
-        lookup(nxt); SB();
+        if (more) lookup(step_of(kt + kGStages));
+        SB();
         mma(P); SB();
         read_frags(Q, st, 1); SB();
         // Q has arrived and this wave's part of tile kt + 1 has landed; after the barrier every wave is done reading
         // this stage, which is refilled at once
-        wait_vmcnt_lgkm0<(kGStages - 2) * kGLoads>();
+        if (kt + kGStages - 1 < nk) wait_vmcnt_lgkm0<(kGStages - 2) * kGLoads>();
+        else wait_vmcnt_lgkm0<0>();
         if (KW == 1) __builtin_amdgcn_s_barrier();
         else asm volatile("" ::: "memory");
         SB();
-        issue(nxt, stage); SB();
+        if (more) issue(step_of(kt + kGStages), stage);
+        SB();
         mma(Q); SB();
         read_frags(P, sn, 0); SB();
         stage = next_stage;
@@ -400,27 +404,31 @@ __device__ __forceinline__ void vnm_gather_fp8_body(unsigned char* __restrict__ 
     const int nk = Kc >> 7;
 #pragma unroll
     for (int p = 0; p < kGStages; ++p) {
-        const int kt = p < nk ? p : nk - 1;
-        lookup(kt);
-        issue(kt, p);
+        if (p >= nk) break;
+        lookup(p);
+        issue(p, p);
     }
-    wait_vmcnt<(kGStages - 1) * kGLoads>();
+    if (nk >= kGStages) wait_vmcnt<(kGStages - 1) * kGLoads>();
+    else wait_vmcnt<0>();
     __syncthreads();
     FragSet P, Q;
     read_frags(P, smem, 0);
     int stage = 0;
     for (int kt = 0; kt < nk; ++kt) {
-        const int nxt = (kt + kGStages < nk) ? kt + kGStages : nk - 1;
+        const bool more = kt + kGStages < nk;
         const int next_stage = (stage + 1 == kGStages) ? 0 : stage + 1;
         const unsigned char* st = smem + stage * kStage;
         const unsigned char* sn = smem + next_stage * kStage;
-        lookup(nxt); SB();
+        if (more) lookup(kt + kGStages);
+        SB();
         mma(P); SB();
         read_frags(Q, st, 1); SB();
-        wait_vmcnt_lgkm0<(kGStages - 2) * kGLoads>();
+        if (kt + kGStages - 1 < nk) wait_vmcnt_lgkm0<(kGStages - 2) * kGLoads>();
+        else wait_vmcnt_lgkm0<0>();
         __builtin_amdgcn_s_barrier();
         SB();
-        issue(nxt, stage); SB();
+        if (more) issue(kt + kGStages, stage);
+        SB();
         mma(Q); SB();
         read_frags(P, sn, 0); SB();
         stage = next_stage;

@@ -242,8 +242,10 @@ __device__ __forceinline__ void vnm8_gemm_body(unsigned char* __restrict__ smem,
     auto step_of = [&](int kt) { return ks0 + kg + kt * KW; };
     if (nk > 0) {
 #pragma unroll
-    for (int p = 0; p < kStages; ++p) issue(step_of(p < nk ? p : nk - 1), p, 0, kLoads);
-    wait_vmcnt<(kStages - 1) * kLoads>();
+    for (int p = 0; p < kStages; ++p)
+        if (p < nk) issue(step_of(p), p, 0, p < kStages - 1 ? kLoads : kLoads * 2 / 4);           // (the rest of the last one's loads are the first step's)
+    if (nk >= kStages) wait_vmcnt<(kStages - 2) * kLoads + kLoads * 2 / 4>();
+    else wait_vmcnt<0>();
     if (KW == 1) __syncthreads();
     else asm volatile("" ::: "memory");
     AFrags A0, A1;
@@ -252,39 +254,36 @@ __device__ __forceinline__ void vnm8_gemm_body(unsigned char* __restrict__ smem,
     read_b(P, ring, A0.cw, 0);
     int stage = 0;
     // two stages per trip so that the A fragment buffers alternate without copies.  The loads of a refill are spread from the barrier that frees its stage
-    // to the next one (gemm_v2_body.hpp says why); the first step's first ones repeat the last stage's.
-    int re_kt = step_of(kStages - 1 < nk ? kStages - 1 : nk - 1), re_stage = kStages - 1;
-#define ISSUE(i) issue(re_kt, re_stage, kLoads * (i) / 4, kLoads * ((i) + 1) / 4)
-    auto step = [&](int kt, AFrags& cur, AFrags& nxt_a) {
-        const int next_stage = (stage + 1 == kStages) ? 0 : stage + 1;
+    // to the next one, and the last steps load nothing (gemm_v2_body.hpp says why).  t: the tile that is loaded, s: its stage; full: both of a step's exist.
+#define ISSUE(t, s, i) if (full.value || (t) < nk) issue(step_of(t), s, kLoads * (i) / 4, kLoads * ((i) + 1) / 4)
+    auto step = [&](auto full, int kt, AFrags& cur, AFrags& nxt_a) {
+        const int next_stage = (stage + 1 == kStages) ? 0 : stage + 1, last_stage = stage == 0 ? kStages - 1 : stage - 1;
         const unsigned char* st = ring + stage * kStage;
         const unsigned char* sn = ring + next_stage * kStage;
         mma_half(cur, P, 0, 0); SB();
-        ISSUE(2); SB();
+        ISSUE(kt + kStages - 1, last_stage, 2); SB();
         mma_half(cur, P, 0, 1); SB();
         read_b(Q, st, cur.cw, 1); SB();
-        ISSUE(3); SB();
+        ISSUE(kt + kStages - 1, last_stage, 3); SB();
         // Q has arrived and this wave's part of tile kt + 1 has landed; after the barrier every wave is done reading this stage
-        wait_vmcnt_lgkm0<(kStages - 2) * kLoads>();
+        if (full.value || kt + kStages - 1 < nk) wait_vmcnt_lgkm0<(kStages - 2) * kLoads>();
+        else wait_vmcnt_lgkm0<0>();
         if (KW == 1) __builtin_amdgcn_s_barrier();
         else asm volatile("" ::: "memory");
         SB();
-        re_kt = step_of((kt + kStages < nk) ? kt + kStages : nk - 1); re_stage = stage;
-        ISSUE(0); SB();
+        ISSUE(kt + kStages, stage, 0); SB();
         read_a(nxt_a, sn); SB();
         mma_half(cur, Q, 1, 0); SB();
-        ISSUE(1); SB();
+        ISSUE(kt + kStages, stage, 1); SB();
         mma_half(cur, Q, 1, 1); SB();
         read_b(P, sn, nxt_a.cw, 0); SB();
         stage = next_stage;
     };
 #undef ISSUE
     int kt = 0;
-    for (; kt + 1 < nk; kt += 2) {
-        step(kt, A0, A1);
-        step(kt + 1, A1, A0);
-    }
-    if (kt < nk) step(kt, A0, A1);
+    for (; kt + 1 + kStages < nk; kt += 2) { step(Flag<true>(), kt, A0, A1); step(Flag<true>(), kt + 1, A1, A0); }
+    for (; kt + 1 < nk; kt += 2) { step(Flag<false>(), kt, A0, A1); step(Flag<false>(), kt + 1, A1, A0); }
+    if (kt < nk) step(Flag<false>(), kt, A0, A1);
 #undef SB
     wait_vmcnt<0>();
     }

@@ -89,6 +89,9 @@ __device__ __forceinline__ void wait_vmcnt() {
     __builtin_amdgcn_s_waitcnt((N & 0xF) | ((N >> 4) << 14) | (0x7 << 4) | (0xF << 8));
 }
 
+// a compile-time flag as a function argument
+template <bool V> struct Flag { static constexpr bool value = V; };
+
 // ordering point between LDS writes and reads of lanes of the same wavefront (its LDS operations execute in
 // issue order; this only stops the compiler from moving them)
 __device__ __forceinline__ void wave_lds_sync() {
