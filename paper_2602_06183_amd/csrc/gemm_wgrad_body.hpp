@@ -26,17 +26,14 @@ namespace sffn {
 template <int WVM_, int WVN_, int WM_, int NST_, int KW_>
 struct WTile {
     static constexpr int WVM = WVM_, WVN = WVN_, WM = WM_, NST = NST_, KW = KW_;
-    static constexpr int NW = WVM * WVN, BM = WVM * WM, BN = WVN * 64, FM = WM / 32, FN = 2, THREADS = 64 * NW * KW;
+    static constexpr int NW = WVM * WVN, BM = WVM * WM, BN = WVN * 64, THREADS = 64 * NW * KW;
     static_assert(KW == 1 || NW == 1, "a shared output tile belongs to single wavefronts");
-    // bf16 stage (64 tokens): BM / 2 compact rows x 32 tokens and four rows of zeros, twice; G likewise in two halves; a private copy of the mask bytes per wavefront
+    // stage (64 tokens; on codes 128): BM / 2 compact rows x 64 bytes and four rows of zeros, twice; G likewise in two halves; a private copy of the mask bytes per wavefront
     static constexpr int kZero = BM / 2 * 64, kZeros = 256, kAHalf = kZero + kZeros, kABytes = 2 * kAHalf, kBHalf = BN * 64, kBBytes = 2 * kBHalf;
     static constexpr int kStage = kABytes + kBBytes + NW * 256;
     static constexpr int A_LD = BM / 32 / NW, B_LD = kBBytes / 1024 / NW, kLoads = 1 + 2 * A_LD + B_LD;      // LDS-DMA loads per wavefront per stage
-    // fp8 stage (64 tokens, one byte each): half of everything
-    static constexpr int k8A = kAHalf, k8B = kBHalf, k8Stage = k8A + k8B + NW * 256, B8_LD = k8B / 1024 / NW, k8Loads = 1 + A_LD + B8_LD;
     static constexpr int EPI = NW * 64 * (64 * 4 + 16) / 2 > NW * 64 * (64 * 2 + 16) ? NW * 64 * (64 * 4 + 16) / 2 : NW * 64 * (64 * 2 + 16);   // wgrad_store's staging
     static constexpr int BYTES = KW * NST * kStage > EPI ? KW * NST * kStage : EPI;
-    static constexpr int BYTES8 = KW * NST * k8Stage > EPI ? KW * NST * k8Stage : EPI;
 };
 
 // Which of the four rows of zeros a lane reads for a hidden unit that is not kept.  A ds_read_b128 is served in phases of 16 lanes, and a phase is
@@ -50,7 +47,7 @@ __device__ __forceinline__ int zero_lane(int l32) { return (l32 & 4) ? 0 : 3 * 6
 template <class TL, class V, int FM, int FN>
 __device__ __forceinline__ bool wgrad_join(V (&acc)[FM][FN], unsigned char* smem, int kg, int lane) {
     constexpr int R = sizeof(V) / 4, PART = FM * FN * R * 256;
-    static_assert((TL::KW - 1) * PART <= TL::BYTES && (TL::KW - 1) * PART <= TL::BYTES8, "partial sums must fit in the main-loop LDS");
+    static_assert((TL::KW - 1) * PART <= TL::BYTES, "partial sums must fit in the main-loop LDS");
     if (kg > 0) {
         float* p = reinterpret_cast<float*>(smem + (kg - 1) * PART) + lane;
 #pragma unroll
@@ -75,142 +72,9 @@ __device__ __forceinline__ bool wgrad_join(V (&acc)[FM][FN], unsigned char* smem
     return true;
 }
 
-// Accumulators of one WM x 64 wave tile -> bf16 output (one rounding; `alpha` = product of the operand scales of the fp8 form, 1 otherwise).
-// ACC32: `out` is a float32 matrix of the same shape that the tile is ADDED to (gradient accumulation over the micro-batches of an
+// Accumulators of one WM x 64 wave tile (lane: column l % 16, rows 4 (l / 16) .. + 3 of a fragment) -> bf16 output (one rounding; `alpha` = product of the operand scales of
+// the fp8 form, 1 otherwise).  ACC32: `out` is a float32 matrix of the same shape that the tile is ADDED to (gradient accumulation over the micro-batches of an
 // optimizer step): out32 = out32 + alpha * sum, both in float32.
-template <bool OUT_I_CONTIG, bool ACC32, class TL>
-__device__ __forceinline__ void wgrad_store(f32x16 (&acc)[TL::FM][TL::FN], float alpha, unsigned char* smem, int wave, int lane, int i0, int j0, int F, int N,
-                                            uint16_t* __restrict__ out, int64_t ldo) {
-    constexpr int WM = TL::WM, WN = 64, FM = TL::FM, FN = TL::FN;
-    const int wm = wave / TL::WVN, wn = wave % TL::WVN, l32 = lane & 31, lh = lane >> 5;
-    if (ACC32 && OUT_I_CONTIG) {
-        // out32[j * ldo + i]: a lane owns 4 consecutive i of one j; stage [32 j][64 i] through LDS so that HBM sees 256-byte row
-        // segments in 16-byte accesses (read, add, write)
-        float* out32 = reinterpret_cast<float*>(out);
-        constexpr int EP = 64 * 4 + 16;
-        unsigned char* scratch = smem + wave * (32 * EP);
-#pragma unroll
-        for (int h = 0; h < WM / 64; ++h)
-#pragma unroll
-            for (int b = 0; b < FN; ++b) {
-                const int f0 = i0 + wm * WM + h * 64, n0 = j0 + wn * WN + b * 32;
-#pragma unroll
-                for (int a2 = 0; a2 < 2; ++a2)
-#pragma unroll
-                    for (int g = 0; g < 4; ++g) {
-                        const int a = 2 * h + a2;
-                        *reinterpret_cast<float4*>(scratch + l32 * EP + (a2 * 32 + 8 * g + 4 * lh) * 4) =
-                            make_float4(acc[a][b][4 * g] * alpha, acc[a][b][4 * g + 1] * alpha, acc[a][b][4 * g + 2] * alpha, acc[a][b][4 * g + 3] * alpha);
-                    }
-                wave_lds_sync();
-                // all of the slab's old values are requested before the first sum is stored (a store would otherwise stand between the loads)
-                float4 old[8];
-#pragma unroll
-                for (int p = 0; p < 8; ++p) {
-                    const int row = p * 4 + (lane >> 4), ch = lane & 15;
-                    const int j = n0 + row, i = f0 + ch * 4;
-                    old[p] = (j < N && i < F) ? *reinterpret_cast<const float4*>(out32 + (int64_t)j * ldo + i) : make_float4(0.f, 0.f, 0.f, 0.f);
-                }
-#pragma unroll
-                for (int p = 0; p < 8; ++p) {
-                    const int row = p * 4 + (lane >> 4), ch = lane & 15;
-                    const int j = n0 + row, i = f0 + ch * 4;
-                    if (j < N && i < F) {
-                        const float4 add = *reinterpret_cast<const float4*>(scratch + row * EP + ch * 16);
-                        *reinterpret_cast<float4*>(out32 + (int64_t)j * ldo + i) = make_float4(old[p].x + add.x, old[p].y + add.y, old[p].z + add.z, old[p].w + add.w);
-                    }
-                }
-                wave_lds_sync();
-            }
-    } else if (ACC32) {
-        // out32[i * ldo + j]: each 32-row slab goes through LDS, as in the bf16 form below, for 16-byte accesses on 256-byte row segments;
-        // the products are rounded to float32 before they are staged, so the addition is never a fused multiply-add
-        float* out32 = reinterpret_cast<float*>(out);
-        constexpr int EP = WN * 4 + 16;
-        unsigned char* scratch = smem + wave * (32 * EP);
-#pragma unroll
-        for (int a = 0; a < FM; ++a) {
-#pragma unroll
-            for (int b = 0; b < FN; ++b)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    const int row = 8 * (r >> 2) + 4 * lh + (r & 3);
-                    *reinterpret_cast<float*>(scratch + row * EP + (b * 32 + l32) * 4) = acc[a][b][r] * alpha;
-                }
-            wave_lds_sync();
-            float4 old[8];
-#pragma unroll
-            for (int p = 0; p < 8; ++p) {
-                const int row = p * 4 + (lane >> 4), ch = lane & 15;
-                const int i = i0 + wm * WM + a * 32 + row, j = j0 + wn * WN + ch * 4;
-                old[p] = (i < F && j < N) ? *reinterpret_cast<const float4*>(out32 + (int64_t)i * ldo + j) : make_float4(0.f, 0.f, 0.f, 0.f);
-            }
-#pragma unroll
-            for (int p = 0; p < 8; ++p) {
-                const int row = p * 4 + (lane >> 4), ch = lane & 15;
-                const int i = i0 + wm * WM + a * 32 + row, j = j0 + wn * WN + ch * 4;
-                if (i < F && j < N) {
-                    const float4 add = *reinterpret_cast<const float4*>(scratch + row * EP + ch * 16);
-                    *reinterpret_cast<float4*>(out32 + (int64_t)i * ldo + j) = make_float4(old[p].x + add.x, old[p].y + add.y, old[p].z + add.z, old[p].w + add.w);
-                }
-            }
-            wave_lds_sync();
-        }
-    } else if (OUT_I_CONTIG) {
-        // out[j * ldo + i]: a lane owns 4 consecutive i of one j; stage [j][i] through LDS (two halves of 64 i)
-        // so that HBM sees 128-byte row segments
-        constexpr int EP = 64 * 2 + 16;
-        unsigned char* scratch = smem + wave * (WN * EP);
-#pragma unroll
-        for (int h = 0; h < WM / 64; ++h) {
-            const int f0 = i0 + wm * WM + h * 64, n0 = j0 + wn * WN;
-#pragma unroll
-            for (int a2 = 0; a2 < 2; ++a2)
-#pragma unroll
-                for (int b = 0; b < FN; ++b)
-#pragma unroll
-                    for (int g = 0; g < 4; ++g) {
-                        const int a = 2 * h + a2, il = a2 * 32 + 8 * g + 4 * lh;
-                        *reinterpret_cast<uint2*>(scratch + (b * 32 + l32) * EP + il * 2) =
-                            make_uint2(f2bf2(acc[a][b][4 * g] * alpha, acc[a][b][4 * g + 1] * alpha), f2bf2(acc[a][b][4 * g + 2] * alpha, acc[a][b][4 * g + 3] * alpha));
-                    }
-            wave_lds_sync();
-#pragma unroll
-            for (int p = 0; p < WN / 8; ++p) {
-                const int row = p * 8 + (lane >> 3), ch = lane & 7;
-                const int j = n0 + row, i = f0 + ch * 8;
-                if (j < N && i < F)
-                    *reinterpret_cast<uint4*>(out + (int64_t)j * ldo + i) = *reinterpret_cast<const uint4*>(scratch + row * EP + ch * 16);
-            }
-            wave_lds_sync();
-        }
-    } else {
-        // out[i * ldo + j]: transpose each 32-row slab through LDS for 16-byte row stores
-        constexpr int EP = WN * 2 + 16;
-        unsigned char* scratch = smem + wave * (32 * EP);
-#pragma unroll
-        for (int a = 0; a < FM; ++a) {
-#pragma unroll
-            for (int b = 0; b < FN; ++b)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    const int row = 8 * (r >> 2) + 4 * lh + (r & 3);
-                    *reinterpret_cast<uint16_t*>(scratch + row * EP + (b * 32 + l32) * 2) = (uint16_t)f2bf(acc[a][b][r] * alpha);
-                }
-            wave_lds_sync();
-#pragma unroll
-            for (int p = 0; p < 32 * (WN / 8) / 64; ++p) {
-                const int e = lane + 64 * p, row = e / (WN / 8), ch = e % (WN / 8);
-                const int i = i0 + wm * WM + a * 32 + row, j = j0 + wn * WN + ch * 8;
-                if (i < F && j < N)
-                    *reinterpret_cast<uint4*>(out + (int64_t)i * ldo + j) = *reinterpret_cast<const uint4*>(scratch + row * EP + ch * 16);
-            }
-            wave_lds_sync();
-        }
-    }
-}
-
-// The same for accumulators of the 16 x 16 instructions (lane: column l % 16, rows 4 (l / 16) .. + 3 of a fragment).
 template <bool OUT_I_CONTIG, bool ACC32, class TL>
 __device__ __forceinline__ void wgrad_store(f32x4 (&acc)[TL::WM / 16][4], float alpha, unsigned char* smem, int wave, int lane, int i0, int j0, int F, int N,
                                             uint16_t* __restrict__ out, int64_t ldo) {
@@ -426,14 +290,20 @@ __device__ __forceinline__ void wgrad_vnm_body(unsigned char* __restrict__ smem,
     // token blocks of this wavefront: all of them, or (KW > 1) every KW-th one from its own on.  0 for an expert without tokens: its gradient is zero
     const int nk = KW == 1 ? K / 64 : (K / 64 - kg + KW - 1) / KW;
     auto step_of = [&](int kt) { return KW == 1 ? kt : kg + kt * KW; };
+    // The last steps load nothing (gemm_v2_body.hpp says why), except on the 256 tile, whose last tile is loaded again in their place: a second copy of its step, without loads, runs
+    // out of registers (on codes T = N = 8192, F = 28672 1270 -> 1660 us).
+    constexpr bool REPEAT = FM == 8;
+    auto tile_of = [&](int t) { return step_of(REPEAT && t >= nk ? nk - 1 : t); };
     if (nk > 0) {
         // rows of zeros behind both half-tiles of every stage (never touched by the DMA)
         constexpr int ZW = TL::kZeros / 4;
         for (int i = wt * 64 + lane; i < kStages * 2 * ZW; i += TL::NW * 64)
             *reinterpret_cast<uint32_t*>(ring + i / (2 * ZW) * kStage + (i / ZW & 1) * kAHalf + TL::kZero + i % ZW * 4) = 0u;
 #pragma unroll
-        for (int p = 0; p < kStages; ++p) issue(step_of(p < nk ? p : nk - 1), p, 0, kLoads);
-        wait_vmcnt<(kStages - 1) * kLoads>();
+        for (int p = 0; p < kStages; ++p)
+            if (REPEAT || p < nk) issue(tile_of(p), p, 0, p < kStages - 1 ? kLoads : kLoads * 2 / 6);           // (the rest of the last one's loads are the first step's)
+        if (REPEAT || nk >= kStages) wait_vmcnt<(kStages - 2) * kLoads + kLoads * 2 / 6>();
+        else wait_vmcnt<0>();
         if (KW == 1) __syncthreads();
         else { wave_lds_sync(); asm volatile("" ::: "memory"); }
         lookup_read(0);
@@ -448,10 +318,11 @@ __device__ __forceinline__ void wgrad_vnm_body(unsigned char* __restrict__ smem,
         // One step = one stage = two sub-steps of FM rows of four matrix instructions.  A row's fragment is read four rows ahead, G's fragments one sub-step
         // ahead.  The next stage's mask bytes are the first load of its batch; its rows are looked up as the last reads of this stage are issued, and once every
         // wavefront has issued all of them (barrier, four rows before the step's end) the stage is refilled with the tile three steps ahead.
-        // The loads are spread over the step (gemm_v2_body.hpp says why); the first step's first ones repeat the last stage's.
-        int re_kt = step_of(kStages - 1 < nk ? kStages - 1 : nk - 1), re_stage = kStages - 1;
-#define ISSUE(i) issue(re_kt, re_stage, kLoads * (i) / 6, kLoads * ((i) + 1) / 6)
-        for (int kt = 0; kt < nk; ++kt) {
+        // The loads are spread over the step (gemm_v2_body.hpp says why).
+        // re_kt, re_stage: the tile that is loaded and its stage; full: both of a step's exist
+#define ISSUE(t, i) if (full.value || (t) < nk) issue(re_kt, re_stage, kLoads * (i) / 6, kLoads * ((i) + 1) / 6)
+        int re_kt = tile_of(kStages - 1), re_stage = kStages - 1;
+        auto step = [&](auto full, int kt) {
             const int next_stage = (stage + 1 == kStages) ? 0 : stage + 1;
             const unsigned char* st = ring + stage * kStage;
             const unsigned char* sn = ring + next_stage * kStage;
@@ -463,11 +334,12 @@ __device__ __forceinline__ void wgrad_vnm_body(unsigned char* __restrict__ smem,
                 if (FM == 8) { if (a < FN) read_b(B[1][a], st, 1, a); }
                 else if (a < 2) { read_b(B[1][2 * a], st, 1, 2 * a); read_b(B[1][2 * a + 1], st, 1, 2 * a + 1); }
                 SB();
-                if (FM == 8) { if (a < 4) ISSUE(2 + a); }
-                else if (a < 2) { ISSUE(2 + 2 * a); ISSUE(3 + 2 * a); }
+                if (FM == 8) { if (a < 4) { ISSUE(kt + kStages - 1, 2 + a); } }
+                else if (a < 2) { ISSUE(kt + kStages - 1, 2 + 2 * a); ISSUE(kt + kStages - 1, 3 + 2 * a); }
                 if (a == FM - 2) {
                     // all but kLoads - 1 of the next stage's batch and the batch after it may still be in flight
-                    wait_vmcnt<(kStages - 2) * kLoads + kLoads - 1>();
+                    if (full.value || kt + kStages - 1 < nk) wait_vmcnt<(kStages - 2) * kLoads + kLoads - 1>();
+                    else wait_vmcnt<0>();
                     if (KW > 1) asm volatile("" ::: "memory");
                     lookup_read(next_stage);
                 }
@@ -484,11 +356,13 @@ __device__ __forceinline__ void wgrad_vnm_body(unsigned char* __restrict__ smem,
                     SB();
                 }
                 if (a == BAR) {
-                    wait_vmcnt_lgkm0<(kStages - 2) * kLoads>();      // this wavefront's reads of the stage are here, and its part of tile kt + 1
+                    // this wavefront's reads of the stage are here, and its part of tile kt + 1
+                    if (full.value || kt + kStages - 1 < nk) wait_vmcnt_lgkm0<(kStages - 2) * kLoads>();
+                    else wait_vmcnt_lgkm0<0>();
                     if (KW == 1) __builtin_amdgcn_s_barrier();
                     else asm volatile("" ::: "memory");
                     SB();
-                    re_kt = step_of((kt + kStages < nk) ? kt + kStages : nk - 1); re_stage = stage;
+                    re_kt = tile_of(kt + kStages); re_stage = stage;
 #pragma unroll
                     for (int r = 0; r <= BAR - (FM - 4); ++r) read_a(A[r], 0, r);
 #pragma unroll
@@ -496,11 +370,15 @@ __device__ __forceinline__ void wgrad_vnm_body(unsigned char* __restrict__ smem,
                     SB();
                 }
                 if (a > BAR) { read_a(A[a & 3], 0, a - (FM - 4)); SB(); }
-                if (a == FM - 2) { ISSUE(0); SB(); }
-                if (a == FM - 1) { ISSUE(1); SB(); }
+                if (a == FM - 2) { ISSUE(kt + kStages, 0); SB(); }
+                if (a == FM - 1) { ISSUE(kt + kStages, 1); SB(); }
             }
             stage = next_stage;
-        }
+        };
+        int kt = 0;
+        for (; kt < (REPEAT ? nk : nk - kStages); ++kt) step(Flag<true>(), kt);
+        if constexpr (!REPEAT)
+            for (; kt < nk; ++kt) step(Flag<false>(), kt);
 #undef ISSUE
         wait_vmcnt<0>();
     }
@@ -512,23 +390,24 @@ __device__ __forceinline__ void wgrad_vnm_body(unsigned char* __restrict__ smem,
 }
 
 // The same contraction on E4M3 codes (the fp8 step with SFFN_FLAG_FP8_WGRAD): atc and G hold one code per element, in the blocked layout
-// with a pair of codes per 2-byte element, so one 64-byte chunk of a row is exactly one 64-token block.  v_mfma_scale_f32_32x32x64_f8f6f4 with
-// unit scales contracts one such block per instruction (measured: lane l supplies k 32 (l / 32) .. + 31 of row / column l % 32 in both
-// operands; 2x the bf16 rate).  A stage of the ring is therefore ONE token block: compact A 8 KB + a row of zeros, G 16 KB, 8 private copies
-// of the block's 32 mask bytes; 5 stages; per stage four rows of two matrix instructions, the A fragments read one row ahead, the G
-// fragments one stage ahead.  out = bf16(alpha * sum), alpha = product of the two tensor scales.
+// with a pair of codes per 2-byte element, so one 64-byte chunk of a row is exactly one 64-token block.  v_mfma_scale_f32_16x16x128_f8f6f4 with
+// unit scales contracts two such blocks per instruction (measured: lane l supplies k 32 (l / 16) .. + 31 of row / column l % 16 in both operands), so a stage is the bf16
+// kernel's with a block for a half: the upper 32 lanes look their rows up in the second block's masks.  A block that is not there (an odd number of them) is one that
+// keeps nothing.  A fragment is read two rows ahead.  out = bf16(alpha * sum), alpha = product of the two tensor scales.
+// (v_mfma_scale_f32_32x32x64_f8f6f4, one block per instruction, takes 9 % more power for the same products: registers only 3900 TFLOP/s, this one 4240.)
 template <bool OUT_I_CONTIG, bool ACC32, class TL>
 __device__ __forceinline__ void wgrad_vnm_fp8_body(unsigned char* __restrict__ smem, int pid, int n_pid, const uint16_t* __restrict__ atc, const uint8_t* __restrict__ kmask,
                                                            const uint16_t* __restrict__ G, int F, int N, int Ttot, float alpha,
                                                            uint16_t* __restrict__ out, int64_t ldo, int tiles_m, int tiles_n, const GemmGroup& grp) {
-    constexpr int BM = TL::BM, BN = TL::BN, WM = TL::WM, WN = 64, FM = TL::FM, FN = TL::FN, KW = TL::KW;
-    constexpr int kStages = TL::NST, kStage = TL::k8Stage, k8A = TL::k8A, k8B = TL::k8B, kLoads = TL::k8Loads, A_LD = TL::A_LD, B_LD = TL::B8_LD;
+    constexpr int BM = TL::BM, BN = TL::BN, WM = TL::WM, WN = 64, FM = WM / 16, FN = 4, KW = TL::KW;
+    constexpr int kStages = TL::NST, kStage = TL::kStage, kAHalf = TL::kAHalf, kABytes = TL::kABytes, kBHalf = TL::kBHalf, kBBytes = TL::kBBytes, kLoads = TL::kLoads;
+    constexpr int A_LD = TL::A_LD, B_LD = TL::B_LD;
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int kg = KW > 1 ? wave : 0, wt = KW > 1 ? 0 : wave;       // share of the contraction / place in the tile
     const int wm = wt / TL::WVN, wn = wt % TL::WVN;
-    const int l32 = lane & 31, lh = lane >> 5;
+    const int l16 = lane & 15, lq = lane >> 4, blk = lq >> 1;
     unsigned char* const ring = smem + kg * (kStages * kStage);
     const uint32_t ring_lds = lds_addr(smem) + kg * (kStages * kStage);
     int L = xcd_run(pid, n_pid);
@@ -544,10 +423,13 @@ __device__ __forceinline__ void wgrad_vnm_fp8_body(unsigned char* __restrict__ s
     band_tile(L, tiles_m, tiles_n, SFFN_TILE_GROUP, tm, tn);
     const int i0 = tm * BM, j0 = tn * BN;
     const int KC = Ttot / 64;                     // 64-token chunks (64 bytes) per row of the blocked operands
+    const int nblk = K / 64;
 
+    // chunk c of row group g lies in slot c ^ swz8(g): a lane takes chunks 2 (lq % 2) and the next, and again every phase of a read meets 64 banks (swz4 in lds_dma.hpp)
+    auto swz8 = [](int g) { return (g & 3) ^ ((g & 3) >> 1); };
     uint64_t a_base[A_LD], b_base[B_LD], c_base;
     const int rb = lane >> 2;
-    const uint32_t blk_lane = (uint32_t)(rb * 32 + ((lane & 3) ^ ((rb >> 2) & 3)) * 8) * 2;   // chunk swizzle, as in the bf16 kernel
+    const uint32_t blk_lane = (uint32_t)(rb * 32 + ((lane & 3) ^ swz8(rb >> 2)) * 8) * 2;
     {
 #pragma unroll
         for (int n = 0; n < A_LD; ++n) {
@@ -556,11 +438,12 @@ __device__ __forceinline__ void wgrad_vnm_fp8_body(unsigned char* __restrict__ s
         }
 #pragma unroll
         for (int n = 0; n < B_LD; ++n) {
-            int gr = j0 + (wt * B_LD + n) * 16; gr = gr < N ? gr : N - 16;
+            int gr = j0 + ((wt * B_LD + n) % (BN / 16)) * 16; gr = gr < N ? gr : N - 16;
             b_base[n] = uniform64(G + (((int64_t)(gr >> 4) * KC + k_base / 64) << 9));
         }
         c_base = uniform64(kmask + (int64_t)(k_base / 64) * (F / 8));
     }
+    // mask bytes: lanes 0-7 bring the first block's 32, lanes 8-15 the second's, the others repeat them
     uint32_t c_lane;
     {
         int g = i0 / 8 + 4 * (lane & 7); g = g < F / 8 ? g : F / 8 - 4;
@@ -568,124 +451,143 @@ __device__ __forceinline__ void wgrad_vnm_fp8_body(unsigned char* __restrict__ s
     }
     const uint32_t c_kstep = (uint32_t)(F / 8);
     auto issue = [&](int kt, int stage, int lo, int hi) {
-        const uint32_t sa = ring_lds + stage * kStage;
-        const uint32_t o = blk_lane + (uint32_t)kt * 1024;
-        if (lo <= 0 && hi > 0) dma4(c_base, c_lane + (uint32_t)kt * c_kstep, sa + k8A + k8B + wt * 256);     // first: the look-up wants it earliest
+        const uint32_t sa = ring_lds + stage * kStage, sb = sa + kABytes, sc = sb + kBBytes;
+        const int second = 2 * kt + 1 < nblk ? 2 * kt + 1 : nblk - 1;           // (clamped into the operand; its rows then keep nothing)
+        const uint32_t o[2] = {blk_lane + (uint32_t)kt * 2048, blk_lane + (uint32_t)second * 1024};
+        if (lo <= 0 && hi > 0) dma4(c_base, c_lane + (uint32_t)((lane & 8) ? second : 2 * kt) * c_kstep, sc + wt * 256);     // first: the look-up wants it earliest
 #pragma unroll
-        for (int n = 0; n < A_LD; ++n)
-            if (1 + n >= lo && 1 + n < hi) dma16(a_base[n], o, sa + (wt * A_LD + n) * 1024);
+        for (int n = 0; n < 2 * A_LD; ++n)
+            if (1 + n >= lo && 1 + n < hi) dma16(a_base[n >> 1], o[n & 1], sa + (n & 1) * kAHalf + (wt * A_LD + (n >> 1)) * 1024);
 #pragma unroll
         for (int n = 0; n < B_LD; ++n)
-            if (1 + A_LD + n >= lo && 1 + A_LD + n < hi) dma16(b_base[n], o, sa + k8A + (wt * B_LD + n) * 1024);
+            if (1 + 2 * A_LD + n >= lo && 1 + 2 * A_LD + n < hi) dma16(b_base[n], o[(wt * B_LD + n) / (BN / 16)], sb + (wt * B_LD + n) * 1024);
     };
 
-    // fragment reads: a lane wants the 32 bytes k 32 lh .. + 31 of its row = 16-byte chunks 2 lh, 2 lh + 1 (slot = chunk ^ ((row >> 2) & 3))
-    int b_off[FN];
-#pragma unroll
-    for (int b = 0; b < FN; ++b) {
-        const int row = wn * WN + b * 32 + l32;
-        b_off[b] = k8A + row * 64 + (((2 * lh) ^ ((row >> 2) & 3)) << 4);
-    }
-    int a_off[FM], a_next[FM];
-    const uint32_t col = l32 & 7, below = (1u << col) - 1u;
-    const int zero_row = TL::kZero + zero_lane(l32) + (((2 * lh) ^ (l32 >> 3)) << 4);
-    uint32_t mk[FM];
+    const int c0 = 2 * (lq & 1);
+    const int b_off = kABytes + blk * kBHalf + (wn * WN + l16) * 64 + ((c0 ^ swz8(l16 >> 2)) << 4);
+    // as in the bf16 kernel
+    const int hb = l16 >> 3, col = l16 & 7, g0 = wm * (WM / 8) + hb;
+    const uint32_t below[2] = {((1u << col) - 1u) << (8 * hb), ((1u << col) - 1u) << (8 * hb + 16)};
+    const uint32_t bit[2] = {(uint32_t)(8 * hb + col), (uint32_t)(8 * hb + col + 16)};
+    const uint32_t lb[2] = {(uint32_t)(blk * kAHalf + g0 * 256 + ((c0 ^ swz8(hb)) << 4)), (uint32_t)(blk * kAHalf + g0 * 256 + ((c0 ^ swz8(2 + hb)) << 4))};
+    const uint32_t no_row = (uint32_t)(TL::kZero / 64 + zero_lane(l16) / 64 - g0 * 4);
+    uint32_t a_off[FM], mk[FM / 2];
     auto lookup_read = [&](int stage) {
-        const unsigned char* sc = ring + stage * kStage + k8A + k8B + wt * 256;
-#pragma unroll
-        for (int a = 0; a < FM; ++a) mk[a] = sc[wm * (WM / 8) + a * 4 + (l32 >> 3)];
-    };
-    auto lookup = [&](int stage) {
-        const int sa = stage * kStage;
-#pragma unroll
-        for (int a = 0; a < FM; ++a) {
-            const int gl = wm * (WM / 8) + a * 4 + (l32 >> 3);
-            const int row = gl * 4 + __builtin_popcount(mk[a] & below);                   // (row >> 2) & 3 == l32 >> 3
-            a_next[a] = sa + (((mk[a] >> col) & 1u) ? row * 64 + (((2 * lh) ^ (l32 >> 3)) << 4) : zero_row);
+        const unsigned char* sc = ring + stage * kStage + kABytes + kBBytes + wt * 256 + wm * (WM / 8) + blk * 32;
+        if constexpr (FM == 8) {
+            const uint4 w = *reinterpret_cast<const uint4*>(sc);
+            mk[0] = w.x; mk[1] = w.y; mk[FM / 2 - 2] = w.z; mk[FM / 2 - 1] = w.w;
+        } else {
+            const uint2 w = *reinterpret_cast<const uint2*>(sc);
+            mk[0] = w.x; mk[1] = w.y;
         }
     };
-    auto read_a = [&](Frag16& f, int off) {
-        f.u[0] = *reinterpret_cast<const uint4*>(ring + off);
-        f.u[1] = *reinterpret_cast<const uint4*>(ring + (off ^ 16));
+    auto drop_second = [&](int kt) {             // kt: the step whose masks have been read
+        if (2 * kt + 1 >= nblk) {
+#pragma unroll
+            for (int i = 0; i < FM / 2; ++i) mk[i] = blk ? 0u : mk[i];
+        }
+    };
+    auto lookup = [&](int stage, int a) {
+        const uint32_t kept = (uint32_t)__builtin_amdgcn_sbfe((int)mk[a >> 1], bit[a & 1], 1), row = (uint32_t)__builtin_popcount(mk[a >> 1] & below[a & 1]);
+        a_off[a] = ((row & kept) | ((no_row - 8 * a) & ~kept)) * 64 + (lb[a & 1] + (uint32_t)(stage * kStage));
+    };
+    auto read_a = [&](Frag16& f, int a) {
+        f.u[0] = *reinterpret_cast<const uint4*>(ring + a_off[a] + a * 512);
+        f.u[1] = *reinterpret_cast<const uint4*>(ring + (a_off[a] ^ 16) + a * 512);
     };
     auto read_b = [&](Frag16& f, const unsigned char* st, int b) {
-        f.u[0] = *reinterpret_cast<const uint4*>(st + b_off[b]);
-        f.u[1] = *reinterpret_cast<const uint4*>(st + (b_off[b] ^ 16));
+        f.u[0] = *reinterpret_cast<const uint4*>(st + b_off + b * 1024);
+        f.u[1] = *reinterpret_cast<const uint4*>(st + (b_off ^ 16) + b * 1024);
     };
-    f32x16 acc[FM][FN];
+    f32x4 acc[FM][FN];
 #pragma unroll
     for (int a = 0; a < FM; ++a)
 #pragma unroll
         for (int b = 0; b < FN; ++b)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) acc[a][b][r] = 0.0f;
-    auto mma_row = [&](const Frag16& fa, const Frag16 (&fb)[FN], int a) {
-#pragma unroll
-        for (int b = 0; b < FN; ++b)
-            acc[a][b] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(fa.q, fb[b].q, acc[a][b], 0, 0, 0, 0x7F, 0, 0x7F);   // fp8 x fp8, scales 2^0
+            for (int r = 0; r < 4; ++r) acc[a][b][r] = 0.0f;
+    Frag16 A[2], B[FN];
+    auto mma = [&](int a, int b) {
+        acc[a][b] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(A[a & 1].q, B[b].q, acc[a][b], 0, 0, 0, 0x7F, 0, 0x7F);   // fp8 x fp8, scales 2^0
     };
 #define SB() __builtin_amdgcn_sched_barrier(0)
-    const int nk = KW == 1 ? K / 64 : (K / 64 - kg + KW - 1) / KW;                // 0 for an expert without tokens: its gradient is zero
+    const int ns = (nblk + 1) / 2, nk = KW == 1 ? ns : (ns - kg + KW - 1) / KW;                // 0 for an expert without tokens: its gradient is zero
     auto step_of = [&](int kt) { return KW == 1 ? kt : kg + kt * KW; };
+    // The last steps load nothing (gemm_v2_body.hpp says why), except on the 256 tile, whose last tile is loaded again in their place: a second copy of its step, without loads, runs
+    // out of registers (on codes T = N = 8192, F = 28672 1270 -> 1660 us).
+    constexpr bool REPEAT = FM == 8;
+    auto tile_of = [&](int t) { return step_of(REPEAT && t >= nk ? nk - 1 : t); };
     if (nk > 0) {
         constexpr int ZW = TL::kZeros / 4;
-        for (int i = wt * 64 + lane; i < kStages * ZW; i += TL::NW * 64) *reinterpret_cast<uint32_t*>(ring + i / ZW * kStage + TL::kZero + i % ZW * 4) = 0u;   // the rows of zeros
+        for (int i = wt * 64 + lane; i < kStages * 2 * ZW; i += TL::NW * 64)
+            *reinterpret_cast<uint32_t*>(ring + i / (2 * ZW) * kStage + (i / ZW & 1) * kAHalf + TL::kZero + i % ZW * 4) = 0u;
 #pragma unroll
-        for (int p = 0; p < kStages; ++p) issue(step_of(p < nk ? p : nk - 1), p, 0, kLoads);
-        wait_vmcnt<(kStages - 1) * kLoads>();
+        for (int p = 0; p < kStages; ++p)
+            if (REPEAT || p < nk) issue(tile_of(p), p, 0, p < kStages - 1 ? kLoads : kLoads * 2 / 4);           // (the rest of the last one's loads are the first step's)
+        if (REPEAT || nk >= kStages) wait_vmcnt<(kStages - 2) * kLoads + kLoads * 2 / 4>();
+        else wait_vmcnt<0>();
         if (KW == 1) __syncthreads();
         else { wave_lds_sync(); asm volatile("" ::: "memory"); }
-        Frag16 A0, A1, B0[FN], B1[FN];
         lookup_read(0);
-        lookup(0);
+        drop_second(step_of(0));
 #pragma unroll
-        for (int a = 0; a < FM; ++a) a_off[a] = a_next[a];
-        read_a(A0, a_off[0]);
+        for (int a = 0; a < FM; ++a) lookup(0, a);
+        read_a(A[0], 0);
+        read_a(A[1], 1);
 #pragma unroll
-        for (int b = 0; b < FN; ++b) read_b(B0[b], ring, b);
+        for (int b = 0; b < FN; ++b) read_b(B[b], ring, b);
         int stage = 0;
-        // One step = one token block; two steps per loop trip so that the two G fragment sets alternate by name.  The loads of a refill are spread
-        // as in the bf16 kernel.
-        constexpr int SLOTS = FM == 4 ? 4 : 2;
-        int re_kt = step_of(kStages - 1 < nk ? kStages - 1 : nk - 1), re_stage = kStages - 1;
-#define ISSUE(i) issue(re_kt, re_stage, kLoads * (i) / SLOTS, kLoads * ((i) + 1) / SLOTS)
-        auto step = [&](int kt, Frag16 (&Bc)[FN], Frag16 (&Bn)[FN]) {
+        // One step = one stage = FM rows of four matrix instructions.  Behind the last but one the last reads of the stage have arrived (barrier): it is refilled, and the next one's
+        // first fragments are read, G's each in the place of the one whose last instruction has been issued.  Its rows are looked up as the last ones of this stage have been read.
+#define ISSUE(t, i) if (full.value || (t) < nk) issue(re_kt, re_stage, kLoads * (i) / 4, kLoads * ((i) + 1) / 4)
+        int re_kt = tile_of(kStages - 1), re_stage = kStages - 1;
+        auto step = [&](auto full, int kt) {
             const int next_stage = (stage + 1 == kStages) ? 0 : stage + 1;
             const unsigned char* sn = ring + next_stage * kStage;
-            read_a(A1, a_off[1]); SB();
-            if (FM == 4) {
-                mma_row(A0, Bc, 0); SB();
-                ISSUE(2);
-                read_a(A0, a_off[FM - 2]); SB();
-                mma_row(A1, Bc, 1); SB();
-                ISSUE(3);
-                read_a(A1, a_off[FM - 1]); SB();
+#pragma unroll
+            for (int a = 0; a < FM; ++a) {
+#pragma unroll
+                for (int b = 0; b < FN; ++b) {
+                    mma(a, b);
+                    if (a == FM - 1) { SB(); read_b(B[b], sn, b); SB(); }
+                }
+                SB();
+                if (a + 2 < FM) { read_a(A[a & 1], a + 2); SB(); }
+                if (a == 0) { ISSUE(kt + kStages - 1, 2); if (FM == 4) { ISSUE(kt + kStages - 1, 3); } SB(); }
+                if (FM == 8 && a == 1) { ISSUE(kt + kStages - 1, 3); SB(); }
+                if (a == FM - 4) {
+                    // the next stage's masks were the first load of its batch: all but kLoads - 1 of that batch and the batch after it may still be in flight
+                    if (full.value || kt + kStages - 1 < nk) wait_vmcnt<(kStages - 2) * kLoads + kLoads - 1>();
+                    else wait_vmcnt<0>();
+                    if (KW > 1) asm volatile("" ::: "memory");
+                    lookup_read(next_stage); SB();
+                }
+                if (a == FM - 3) {
+                    drop_second(step_of(kt + 1));
+#pragma unroll
+                    for (int r = 0; r < FM; ++r) lookup(next_stage, r);
+                    SB();
+                }
+                if (a == FM - 2) {
+                    // this wavefront's reads of the stage are here, and its part of tile kt + 1
+                    if (full.value || kt + kStages - 1 < nk) wait_vmcnt_lgkm0<(kStages - 2) * kLoads>();
+                    else wait_vmcnt_lgkm0<0>();
+                    if (KW == 1) __builtin_amdgcn_s_barrier();
+                    else asm volatile("" ::: "memory");
+                    SB();
+                    re_kt = tile_of(kt + kStages); re_stage = stage;
+                    read_a(A[0], 0); SB();
+                    ISSUE(kt + kStages, 0); SB();
+                }
+                if (a == FM - 1) { read_a(A[1], 1); SB(); ISSUE(kt + kStages, 1); SB(); }
             }
-            // the next block's mask bytes were the first load of its batch
-            wait_vmcnt<(kStages - 2) * kLoads + kLoads - 1>();
-            if (KW > 1) asm volatile("" ::: "memory");
-            lookup_read(next_stage); SB();
-            mma_row(A0, Bc, FM - 2); SB();
-            wait_vmcnt_lgkm0<(kStages - 2) * kLoads>();      // my reads of this stage are done, block kt + 1 has landed (this wavefront's part)
-            if (KW == 1) __builtin_amdgcn_s_barrier();
-            else asm volatile("" ::: "memory");
-            SB();
-            re_kt = step_of((kt + kStages < nk) ? kt + kStages : nk - 1); re_stage = stage;
-            ISSUE(0); SB();
-            lookup(next_stage); SB();
-#pragma unroll
-            for (int a = 0; a < FM; ++a) a_off[a] = a_next[a];
-            read_a(A0, a_off[0]);
-#pragma unroll
-            for (int b = 0; b < FN; ++b) read_b(Bn[b], sn, b);
-            SB();
-            mma_row(A1, Bc, FM - 1); SB();
-            ISSUE(1); SB();
             stage = next_stage;
         };
         int kt = 0;
-        for (; kt + 1 < nk; kt += 2) { step(kt, B0, B1); step(kt + 1, B1, B0); }
-        if (kt < nk) step(kt, B0, B1);
+        for (; kt < (REPEAT ? nk : nk - kStages); ++kt) step(Flag<true>(), kt);
+        if constexpr (!REPEAT)
+            for (; kt < nk; ++kt) step(Flag<false>(), kt);
 #undef ISSUE
         wait_vmcnt<0>();
     }
@@ -698,7 +600,7 @@ __device__ __forceinline__ void wgrad_vnm_fp8_body(unsigned char* __restrict__ s
 template <bool FP8, bool OUT_I_CONTIG, bool ACC32, class TL>
 struct WgradUnit {
     using Args = WgradArgs;
-    static constexpr int THREADS = TL::THREADS, LDS = FP8 ? TL::BYTES8 : TL::BYTES;
+    static constexpr int THREADS = TL::THREADS, LDS = TL::BYTES;
     static __device__ __forceinline__ void run(unsigned char* smem, int pid, int n_pid, const Args& a) {
         if constexpr (FP8) wgrad_vnm_fp8_body<OUT_I_CONTIG, ACC32, TL>(smem, pid, n_pid, a.atc, a.kmask, a.G, a.F, a.N, a.T, a.alpha, a.out, a.ldo, a.tiles_m, a.tiles_n, a.grp);
         else               wgrad_vnm_body<OUT_I_CONTIG, ACC32, TL>(smem, pid, n_pid, a.atc, a.kmask, a.G, a.F, a.N, a.T, a.out, a.ldo, a.tiles_m, a.tiles_n, a.grp);
@@ -706,8 +608,8 @@ struct WgradUnit {
     static unsigned count(const Args& a) { return (unsigned)((a.F + TL::BM - 1) / TL::BM * ((a.N + TL::BN - 1) / TL::BN) * (a.grp.n ? a.grp.n : 1)); }
     static Args args(Args a) { a.tiles_m = (a.F + TL::BM - 1) / TL::BM; a.tiles_n = (a.N + TL::BN - 1) / TL::BN; return a; }
 };
-template <bool FP8, bool OUT_I_CONTIG, bool ACC32> using WgradUnit256 = WgradUnit<FP8, OUT_I_CONTIG, ACC32, WTile<2, 4, 128, FP8 ? 5 : 3, 1>>;
-template <bool FP8, bool OUT_I_CONTIG, bool ACC32> using WgradUnit128 = WgradUnit<FP8, OUT_I_CONTIG, ACC32, WTile<2, 2, 64, FP8 ? 5 : 3, 1>>;
+template <bool FP8, bool OUT_I_CONTIG, bool ACC32> using WgradUnit256 = WgradUnit<FP8, OUT_I_CONTIG, ACC32, WTile<2, 4, 128, 3, 1>>;
+template <bool FP8, bool OUT_I_CONTIG, bool ACC32> using WgradUnit128 = WgradUnit<FP8, OUT_I_CONTIG, ACC32, WTile<2, 2, 64, 3, 1>>;
 template <bool FP8, bool OUT_I_CONTIG, bool ACC32> using WgradUnit64 = WgradUnit<FP8, OUT_I_CONTIG, ACC32, WTile<1, 1, 64, 3, 4>>;
 
 }  // namespace sffn
