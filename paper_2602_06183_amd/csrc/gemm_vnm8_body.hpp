@@ -123,6 +123,7 @@ __device__ __forceinline__ void vnm8_gemm_body(unsigned char* __restrict__ smem,
     uint32_t b_lane[B_LD];
 #pragma unroll
     for (int i = 0; i < B_LD; ++i) {
+        // (the stage goes into the scalar base: a vector instruction less for every load)
         const int row = RPL * (B_LD * wt + i) + lane / LPR, slot = lane % LPR;
         constexpr int SPP = PB / 16;                         // slots per piece
         int c = (((slot / SPP) ^ (row & PM)) * SPP) | (slot & (SPP - 1));
@@ -165,7 +166,7 @@ __device__ __forceinline__ void vnm8_gemm_body(unsigned char* __restrict__ smem,
         const uint32_t sb = ring_lds + stage * kStage, sa = sb + kB, sm = sa + kA, sc = sm + kMt;
 #pragma unroll
         for (int i = 0; i < B_LD; ++i)
-            if (i >= lo && i < hi) dma16(w_base, b_lane[i] + (uint32_t)kt * b_kstep, sb + (B_LD * wt + i) * 1024);
+            if (i >= lo && i < hi) dma16(w_base + (uint64_t)((uint32_t)kt * b_kstep), b_lane[i], sb + (B_LD * wt + i) * 1024);
 #pragma unroll
         for (int i = 0; i < A_LD; ++i)
             if (B_LD + i >= lo && B_LD + i < hi) dma16(a_base[i], a_lane + (uint32_t)kt * 1024u, sa + (wt * A_LD + i) * 1024);
@@ -178,24 +179,25 @@ __device__ __forceinline__ void vnm8_gemm_body(unsigned char* __restrict__ smem,
     // ---- per-lane LDS offsets of the fragment reads (inside a stage).  A wave owns one token block (64 tokens) x 32 FN output columns: the
     //      B fragments it gathers belong to one column selection. ----------------------
     const int tbw = wt / TL::WH, nh = wt % TL::WH;
-    int a_off[2], m_off[2];
-#pragma unroll
-    for (int a = 0; a < 2; ++a) {
-        const int row = tbw * 64 + a * 32 + l32;
-        a_off[a] = kB + row * 32 + ((lh ^ ((row >> 3) & 1)) << 4);
-        m_off[a] = kB + kA + (FP8 ? row * 8 + 4 * lh : row * 4 + 2 * lh);
-    }
+    // (fragments are 32 tokens apart: 1024 bytes of survivors, 128 (FP8: 256) of metadata)
+    const int arow = tbw * 64 + l32;
+    const int a_off = kB + arow * 32 + ((lh ^ ((arow >> 3) & 1)) << 4);
+    const int m_off = kB + kA + (FP8 ? arow * 8 + 4 * lh : arow * 4 + 2 * lh);
     // bf16: transpose read j of fragment fn: slab row = 8 cb(j) + c with cb(j) = 4 (j / 2) + j % 2 + 2 h and c = byte j of the lane's offsets
     // word; byte address = row * ROW + ((FN nh + fn) ^ (c % pieces)) * 64 + 32 (column half) + 8 (lane % 4)
     // FP8: the lane addresses row p = (lane % 16) / 2 of the read's 8: cb(j) = 8 (j / 2) + 4 h + 2 (j % 2) + p / 4, c = byte j of word (h, p);
     // byte address = row * ROW + ((FN nh + fn) ^ (c % pieces)) * 32 + 16 (column half) + 8 (lane % 2)
+    // The part that depends on c is (c * pieces | (c % pieces) ^ FN nh) * PB: a byte of a table of eight, looked up for the four of a word at once (v_perm_b32); the fragments of a
+    // row of four differ in two bits of the address.  (Worked out read by read, 30 more vector instructions in a stage of 16 matrix instructions: T = D = 8192, F = 28672 1280 us, now 1200;
+    // T = 6400, N = 4096, F = 14336 315, 293; 128 tile, T = 1984, N = 1408, F = 4224 26.8, 25.0, on codes 17.9, 15.8.)
     const int r4 = (lane & 15) >> 2, p8 = (lane & 15) >> 1, g = lane >> 4;
     const int c_off = kB + kA + kMt + (FP8 ? 64 * tbw + (lh * 8 + p8) * 4 : 32 * tbw + (lh * 4 + r4) * 4);
-    const int b_fix = FP8 ? ((g & 1) << 4) + ((lane & 1) << 3) : ((g & 1) << 5) + ((lane & 3) << 3);
-    int b_cb[4];
-#pragma unroll
-    for (int j = 0; j < 4; ++j)
-        b_cb[j] = FP8 ? (8 * (j >> 1) + 4 * lh + 2 * (j & 1) + (p8 >> 2)) * 8 * ROW + b_fix : (4 * (j >> 1) + (j & 1) + 2 * lh) * 8 * ROW + b_fix;
+    const uint32_t b_lane0 = FP8 ? (uint32_t)((4 * lh + (p8 >> 2)) * 8 * ROW + ((g & 1) << 4) + ((lane & 1) << 3)) : (uint32_t)(2 * lh * 8 * ROW + ((g & 1) << 5) + ((lane & 3) << 3));
+    constexpr int NP = GG::NP;
+    static_assert(NP <= 8, "a byte holds 8 pieces x 8 rows");
+    constexpr auto entry = [](uint32_t c) { return c * NP | (c & (NP - 1)); };
+    const uint32_t col = 0x01010101u * (uint32_t)(FN * nh);
+    const uint32_t tab_lo = (entry(0) | entry(1) << 8 | entry(2) << 16 | entry(3) << 24) ^ col, tab_hi = (entry(4) | entry(5) << 8 | entry(6) << 16 | entry(7) << 24) ^ col;
 
     f32x16 acc[2][FN];
 #pragma unroll
@@ -214,19 +216,27 @@ __device__ __forceinline__ void vnm8_gemm_body(unsigned char* __restrict__ smem,
         f.cw = *reinterpret_cast<const uint32_t*>(st + c_off);
 #pragma unroll
         for (int a2 = 0; a2 < 2; ++a2) {
-            f.a[a2].u = *reinterpret_cast<const uint4*>(st + a_off[a2]);
-            f.idx[a2] = FP8 ? (int)*reinterpret_cast<const uint32_t*>(st + m_off[a2]) : (int)*reinterpret_cast<const uint16_t*>(st + m_off[a2]);
+            f.a[a2].u = *reinterpret_cast<const uint4*>(st + a_off + a2 * 1024);
+            f.idx[a2] = FP8 ? (int)*reinterpret_cast<const uint32_t*>(st + m_off + a2 * 256) : (int)*reinterpret_cast<const uint16_t*>(st + m_off + a2 * 128);
         }
     };
-    auto read_b = [&](BPair& f, const unsigned char* st, uint32_t cw, int half) {
+    // the four addresses of a stage's reads, for its first fragment
+    struct BAddr { uint32_t j[4]; };
+    auto address_b = [&](BAddr& ad, int stage, uint32_t cw) {
+        const uint32_t e = __builtin_amdgcn_perm(tab_hi, tab_lo, cw), base = ring_lds + (uint32_t)(stage * kStage) + b_lane0;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) ad.j[j] = base + ((e >> (8 * j)) & 0xFFu) * (uint32_t)PB;
+    };
+    auto read_b = [&](BPair& f, const BAddr& ad, int half) {
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-            const uint32_t c = (cw >> (8 * j)) & 7u;
-            const uint32_t addr = (uint32_t)b_cb[j] + c * (uint32_t)ROW + ((((uint32_t)(FN * nh + HB * half)) ^ (c & (uint32_t)PM)) * PB);
+            constexpr int kBlk = 8 * ROW;
+            const int cb = FP8 ? 8 * (j >> 1) + 2 * (j & 1) : 4 * (j >> 1) + (j & 1);
 #pragma unroll
             for (int q = 0; q < HB; ++q) {
-                if (FP8) f.b[q].q8[j] = __builtin_amdgcn_ds_read_tr8_b64_v2i32((lds_v2i*)(st + (addr ^ (uint32_t)(q * PB))));
-                else     f.b[q].q[j] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(st + (addr ^ (uint32_t)(q * PB))));
+                const uint32_t at = (ad.j[j] ^ (uint32_t)((HB * half + q) * PB)) + (uint32_t)(cb * kBlk);
+                if (FP8) f.b[q].q8[j] = __builtin_amdgcn_ds_read_tr8_b64_v2i32((lds_v2i*)at);
+                else     f.b[q].q[j] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)at);
             }
         }
     };
@@ -250,20 +260,21 @@ __device__ __forceinline__ void vnm8_gemm_body(unsigned char* __restrict__ smem,
     else asm volatile("" ::: "memory");
     AFrags A0, A1;
     BPair P, Q;
+    BAddr ad;
     read_a(A0, ring);
-    read_b(P, ring, A0.cw, 0);
+    address_b(ad, 0, A0.cw);
+    read_b(P, ad, 0);
     int stage = 0;
     // two stages per trip so that the A fragment buffers alternate without copies.  The loads of a refill are spread from the barrier that frees its stage
     // to the next one, and the last steps load nothing (gemm_v2_body.hpp says why).  t: the tile that is loaded, s: its stage; full: both of a step's exist.
 #define ISSUE(t, s, i) if (full.value || (t) < nk) issue(step_of(t), s, kLoads * (i) / 4, kLoads * ((i) + 1) / 4)
     auto step = [&](auto full, int kt, AFrags& cur, AFrags& nxt_a) {
         const int next_stage = (stage + 1 == kStages) ? 0 : stage + 1, last_stage = stage == 0 ? kStages - 1 : stage - 1;
-        const unsigned char* st = ring + stage * kStage;
         const unsigned char* sn = ring + next_stage * kStage;
         mma_half(cur, P, 0, 0); SB();
         ISSUE(kt + kStages - 1, last_stage, 2); SB();
         mma_half(cur, P, 0, 1); SB();
-        read_b(Q, st, cur.cw, 1); SB();
+        read_b(Q, ad, 1); SB();
         ISSUE(kt + kStages - 1, last_stage, 3); SB();
         // Q has arrived and this wave's part of tile kt + 1 has landed; after the barrier every wave is done reading this stage
         if (full.value || kt + kStages - 1 < nk) wait_vmcnt_lgkm0<(kStages - 2) * kLoads>();
@@ -276,7 +287,8 @@ __device__ __forceinline__ void vnm8_gemm_body(unsigned char* __restrict__ smem,
         mma_half(cur, Q, 1, 0); SB();
         ISSUE(kt + kStages, stage, 1); SB();
         mma_half(cur, Q, 1, 1); SB();
-        read_b(P, sn, nxt_a.cw, 0); SB();
+        address_b(ad, next_stage, nxt_a.cw);
+        read_b(P, ad, 0); SB();
         stage = next_stage;
     };
 #undef ISSUE
