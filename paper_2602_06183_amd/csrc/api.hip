@@ -367,7 +367,7 @@ int vnm_wgrad(const uint16_t* a_vals, const uint8_t* a_meta, const uint8_t* a_co
     // C[i=f][j=n]; out_f_major: out[f*N + n] (j contiguous) else out[n*F + f] (i contiguous)
     const int i_contig = !out_f_major;
     const int64_t ldo = out_f_major ? N : F;
-    if (kept) LAUNCH(launch_wgrad_wide(at, mask, gt, F, N, T, M == 32 ? 5 : 6, i_contig, out, ldo, s), "vnm_wgrad/gemm");
+    if (kept) LAUNCH(launch_wgrad_wide(at, a_colidx, gt, F, N, T, M == 32 ? 5 : 6, i_contig, out, ldo, s), "vnm_wgrad/gemm");
     else      LAUNCH(launch_wgrad_vnm(at, mask, gt, F, N, T, i_contig, out, ldo, s), "vnm_wgrad/gemm");
     return SFFN_OK;
 }
@@ -1243,11 +1243,11 @@ static int run_step(const sffn_cfg* cfg, int n_experts, const int64_t* seg, cons
         if (fwd && !packed && !together) STAGE(launch_step_prologue(part[1], s), "step/prune24(W2.T)");
         if (fwd) STAGE(launch_vnm_spmm_gather(y2v, y2m, cix, w2t, D, T, D, F, M, Y3, D, s, gr, &split), "step/y3");                              // eq. (3)
         if (bwd && !together) STAGE(launch_step_prologue(part[2], s), "step/dY.T");
-        if (bwd && kept) STAGE(launch_wgrad_wide(atb, kmask, dytb, F, D, T, logM, 1, dW2, F, s, gw, acc32), "step/dW2");                       // eq. (5)
+        if (bwd && kept) STAGE(launch_wgrad_wide(atb, cix, dytb, F, D, T, logM, 1, dW2, F, s, gw, acc32), "step/dW2");                       // eq. (5)
         else if (bwd) STAGE(launch_wgrad_vnm(atb, kmask, dytb, F, D, T, 1, dW2, F, s, gw, acc32, false, tiles.w), "step/dW2");                       // eq. (5)
         if (bwd) STAGE(launch_gemm_vnm_epilogue(w2vb, w2mb, dyb, nullptr, F, T, D, dy2, ep4, s, gp, tiles.g_bwd), "step/dy2+dsqrelu_vnm");      // eqs. (4), (6)
         if (bwd) STAGE(launch_vnm_spmm_gather(dy1v, y2m, cix, W1, D, T, D, F, M, dX, D, s, gr, &split), "step/dX");                              // eq. (7), dense W1 as is
-        if (bwd && kept) STAGE(launch_wgrad_wide(at2, kmask, xtb, F, D, T, logM, 0, dW1, D, s, gw, acc32), "step/dW1");                        // eq. (8)
+        if (bwd && kept) STAGE(launch_wgrad_wide(at2, cix, xtb, F, D, T, logM, 0, dW1, D, s, gw, acc32), "step/dW1");                        // eq. (8)
         else if (bwd) STAGE(launch_wgrad_vnm(at2, kmask, xtb, F, D, T, 0, dW1, D, s, gw, acc32, false, tiles.w), "step/dW1");                        // eq. (8)
         return SFFN_OK;
     }

@@ -113,6 +113,11 @@ __host__ __device__ __forceinline__ int64_t lane_off(int64_t r, int64_t t, int64
     return ((((t >> 6) * R32 + (r >> 5)) * 4 + ((t >> 4) & 3)) * 64 + ((t >> 3) & 1) * 32 + (r & 31)) * 8;
 }
 
+// The kept rows of a V:N:M activation (row = 4 block + position) in the same order, but the 32 rows of 8 blocks at the lanes kept_lane: any 8 lanes next to
+// each other hold rows of 8 different blocks, which is what gemm_wgrad_wide_body.hpp's LDS accesses want.
+__host__ __device__ __forceinline__ int kept_lane(int row) { return (row & 3) * 8 + (row >> 2); }
+__host__ __device__ __forceinline__ int64_t kept_off(int64_t r, int64_t t, int64_t R32) { return lane_off((r & ~(int64_t)31) | kept_lane((int)(r & 31)), t, R32); }
+
 // Metadata of a 2:4 matrix, blocked for the sparse matrix instruction: one 256-byte unit per (32 rows, 64 k).
 // v_smfmac_f32_16x16x64_bf16 wants, in lane r % 16 + 16 q, the sixteen index bits of the row's survivors in k 16 q .. + 15; a unit stores, for each such
 // lane, its two fragments of 16 rows as one 32-bit word (low half: the first) at byte 4 lane.  A wavefront therefore fetches a unit with one

@@ -604,10 +604,7 @@ __device__ __forceinline__ void gemm_nt_v2_body(unsigned char* __restrict__ smem
                     }
                     if (valid && c < (ep.at_kept ? 1 : M / 8)) {          // lane c of a block: its column offsets (c = 0) and the mask byte of its group c of 8 hidden units
                         if (c == 0) *reinterpret_cast<uint32_t*>(ep.colidx + ((int64_t)(t0 >> 6) * nblkM + blk0 + (lane >> LOGM)) * 4) = cw;
-                        if (ep.at_kept) {       // the offsets once more, grouped as gemm_wgrad_wide_body.hpp reads them
-                            const int64_t blk = blk0 + (lane >> LOGM);
-                            reinterpret_cast<uint32_t*>(ep.kmask)[((int64_t)(t0 >> 6) * (nblkM >> 3) + (blk >> 3)) * 8 + (blk & 1) * 4 + ((blk & 7) >> 1)] = cw;
-                        } else ep.kmask[(int64_t)(t0 >> 6) * (F >> 3) + (f0 >> 3) + (lane >> LOGM) * (M / 8) + c] = (uint8_t)(mine >> (8 * c));
+                        if (!ep.at_kept) ep.kmask[(int64_t)(t0 >> 6) * (F >> 3) + (f0 >> 3) + (lane >> LOGM) * (M / 8) + c] = (uint8_t)(mine >> (8 * c));
                     }
                     cb = (uint32_t)__shfl((int)cw, b << LOGM, 64);
                     bmask = (unsigned long long)(uint32_t)__shfl((int)(uint32_t)mine, b << LOGM, 64);
@@ -686,7 +683,7 @@ __device__ __forceinline__ void gemm_nt_v2_body(unsigned char* __restrict__ smem
                         const int e = q * 64 + lane, rr = e % (4 * NB), c8 = e / (4 * NB);
                         const int64_t R = (f0 >> LOGM) * 4 + rr;
                         if (valid && c8 < 8)
-                            *reinterpret_cast<uint4*>(ep.at + lane_off(R, t0 + 8 * c8, R32)) =
+                            *reinterpret_cast<uint4*>(ep.at + kept_off(R, t0 + 8 * c8, R32)) =
                                 *reinterpret_cast<const uint4*>(ttile + rr * EP + c8 * 16);
                     }
                 } else {

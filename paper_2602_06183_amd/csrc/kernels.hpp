@@ -47,7 +47,7 @@ struct VnmEpilogue {
     // modes 1 / 2: the operands of the V:2:8 activation GEMM (gemm_vnm8.hip; layouts: vcb_off, mcb_off, cixt_off in common.hpp, fp8: vcb8_off, ...):
     // vcb = the survivors (both modes; fp8: their codes), mcb = their metadata and cixt = the regrouped kept-column offsets (mode 1; mode 2 reuses them)
     int64_t at_ld = 0;
-    int at_kept = 0;                // modes 5 / 6, bf16, M = 32, 64: `at` receives only the kept rows, in the order of gemm_wgrad_wide_body.hpp, and `kmask` (mode 5) that kernel's column offsets
+    int at_kept = 0;                // modes 5 / 6, bf16, M = 32, 64: `at` receives only the kept rows, in the order of gemm_wgrad_wide_body.hpp; no `kmask`
     uint16_t* vcb = nullptr;
     uint8_t* mcb = nullptr;
     uint8_t* cixt = nullptr;
@@ -296,17 +296,19 @@ inline int pick_wgrad_tile(int64_t F, int64_t N, int64_t T, int experts, bool sp
     return pick_tile(large_rounds(tiles(256)), tiles(128), tiles(64), (int)(T / 64 / e), 0.58f, split_ok ? 256 : 0, 12);
 }
 
-// Weight gradients on the kept rows only (gemm_wgrad_wide_body.hpp; bf16, launches of their own), from 768 tokens per expert on: with fewer the matrix work that
-// is saved is less than clearing a tile in LDS and reading it out again (D = 4096, F = 16384, M = 32: 82 us for 73 at 512 tokens, 94 for 94 at 768, 840 for 1390 at 16384).
-inline bool wgrad_on_kept_rows(int64_t T, int64_t F, int M, int64_t experts) { return M >= 32 && F % (8 * M) == 0 && T >= 768 * experts; }
+// Weight gradients on the kept rows only (gemm_wgrad_wide_body.hpp; bf16, launches of their own), from 320 tokens per expert on: with fewer the matrix work that
+// is saved is less than clearing a tile in LDS and reading it out again (F = 16384, N = 4096, M = 32: 50 us for 50 at 256 tokens, 51 for 54 at 320, 173 for 354 at 4096;
+// M = 64: 43 for 45 at 192; F = 8192, N = 2048, M = 32: 17.9 for 17.4 at 256, 17.9 for 18.4 at 320, 22.4 for 30.7 at 1024).
+inline bool wgrad_on_kept_rows(int64_t T, int64_t F, int M, int64_t experts) { return M >= 32 && F % (8 * M) == 0 && T >= 320 * experts; }
 
 // Do eqs. (3), (5), (4) and (7), (8) take less time as two launches than as five?  Both are estimated (us).  A launch by itself takes `start` and its rounds
 // over the chip, 256 large or 512 small tiles at a time (a last round of fewer less than a full one), or the time of the weights' bytes where few
 // tokens meet them.  A shared launch takes the sum of its small tiles spread over the chip and `end` of the last unit's tile; no less than `lone` of a tile behind
 // what comes before it, nor than the bytes of all its units.  Tiles and splits are those that the separate launches have.  Eqs. (5), (8) of bf16 blocks of 32 and
-// 64 columns multiply the kept rows only where they have launches of their own, 8 and 16 times fewer products: M = 64, T = 11520, D = 896, F = 2048 the step 224 us apart,
-// 297 together; T = 7680, D = 832, F = 3072 181 / 222; M = 32, T = 5312, D = 1152, F = 3584 186 / 203; small ones share all the same (M = 64, T = 1280, D = 448,
-// F = 2048 63 / 45).
+// 64 columns multiply the kept rows only where they have launches of their own, 8 and 16 times fewer products: M = 64, T = 11520, D = 896, F = 2048 the step 172 us apart,
+// 286 together; T = 7680, D = 832, F = 3072 142 / 210; M = 32, T = 5312, D = 1152, F = 3584 148 / 185; small ones share all the same (M = 64, T = 1280, D = 448,
+// F = 2048 51 / 44).  The two lines of those launches are fitted by themselves, to 1600 steps with M = 32, 64 each run both ways: what is chosen takes 0.40 and 0.09 % longer
+// than the better form; they lean to sharing, so that 9 and 4 of 800 are apart where that is 2 % and more slower (0.30 % and 29 without that).
 // The constants are fitted to whole steps of 28000 drawn shapes (T 64 - 16384, D 256 - 8192, 1 - 32 experts of uneven length, every M, bf16 and codes), each run both
 // ways.  Over 4000 others what is chosen takes 0.10 % longer than the better form (one expert 0.10 % in bf16, 0.04 % on codes), one call in 180 4 % and more, the
 // worst 12 %; always sharing would take 2.3 % longer, never 16 %.  Over 487 measured apart from both: 0.18 %, forward and backward calls after one another, whose eq. (3)
@@ -328,7 +330,7 @@ struct StepCosts {
 };
 constexpr StepCosts kStepBf16 = {3.34f, {0.51f, 0.556f, 0.869f, 0.968f}, {0.402f, 0.411f, 0.436f}, {0.664f, 0.788f, 0.653f, 0.591f}, 0.882f, 0.856f, 2.69f, 1.98f, {0.263f, 0.285f, 0.485f, 1.12f},
                                  {8.92f, 0.722f}, {11.6f, 0.825f}, {7.85f, 0.511f}, {5.16f, 0.407f}, {4.99f, 0.639f}, {4.73f, 0.86f}, {11.8f, 0.0731f},
-                                 {15.4f, 0.632f}, {2.0f, 0.69f}, {3.59f, 0.103f}, {3.2f, 1.49f}, {4.31f, 0.338f}, {6.46f, 1.17f}, {4.09f, 0.63f}, {4.46f, 0.164f}, {5.62f, 0.201f}, {7.12f, 0.229f}};
+                                 {15.4f, 0.632f}, {2.0f, 0.69f}, {3.59f, 0.103f}, {3.2f, 1.49f}, {4.31f, 0.338f}, {6.46f, 1.17f}, {4.09f, 0.63f}, {4.46f, 0.164f}, {8.0f, 0.0f}, {7.0f, 0.0f}};
 constexpr StepCosts kStepFp8 = {4.84f, {0.421f, 0.727f, 1.24f, 0.658f}, {0.297f, 0.255f, 0.254f}, {0.618f, 0.683f, 0.639f, 0.631f}, 1.0f, 0.942f, 2.75f, 1.9f, {0.247f, 0.26f, 0.452f, 1.03f},
                                  {11.8f, 0.858f}, {16.0f, 0.776f}, {13.6f, 0.8f}, {6.33f, 0.52f}, {7.82f, 0.545f}, {8.93f, 0.977f}, {1.9f, 0.15f},
                                  {11.0f, 0.608f}, {3.16f, 0.586f}, {3.4f, 0.206f}, {2.86f, 1.28f}, {4.0f, 0.38f}, {6.57f, 0.503f}, {4.15f, 0.29f}, {3.27f, 0.0483f}, {}, {}};
@@ -505,7 +507,7 @@ hipError_t launch_vnm_spmm_gather_fp8(const uint8_t* a_codes, const uint8_t* a_m
 hipError_t launch_vnm_to_24(const uint16_t* vals, const uint8_t* meta, const uint8_t* colidx, int64_t T, int64_t F,
                             uint16_t* vals24, uint8_t* meta24, hipStream_t s);
 // vnm.hip: the transposed operand of eqs. (5), (8) from the canonical arrays: kept = 0: at [F / 2, T], mask [T / 64, F / 8] for launch_wgrad_vnm;
-// kept = 1 (M = 32, 64, F a multiple of 8 M): at [4 F / M, T], mask [T / 64, F / M] words for launch_wgrad_wide; and gt = the transpose of G [T, N] in
+// kept = 1 (M = 32, 64, F a multiple of 8 M): at [4 F / M, T] for launch_wgrad_wide; and gt = the transpose of G [T, N] in
 // the layout that kernel reads
 hipError_t launch_vnm_compact_t(const uint16_t* vals, const uint8_t* meta, const uint8_t* colidx, int64_t T, int64_t F, int M, int kept, uint16_t* at,
                                 uint8_t* mask, const uint16_t* G, int64_t N, uint16_t* gt, hipStream_t s);
@@ -598,8 +600,8 @@ hipError_t launch_wgrad_vnm(const uint16_t* atc, const uint8_t* kmask, const uin
 
 
 // the same for blocks of M = 2^logM = 32, 64 columns on the kept rows only: at_kept = the epilogues' `at` with at_kept set, [4 F / M rows, T];
-// cixl = their `kmask` with it; 4 F / M a multiple of 32.  Same sums, bit for bit, as launch_wgrad_vnm on the other form of `at`.
-hipError_t launch_wgrad_wide(const uint16_t* at_kept, const uint8_t* cixl, const uint16_t* G, int64_t F, int64_t N, int64_t T, int logM, int out_i_contig, uint16_t* out,
+// colidx = the packed activation's; 4 F / M a multiple of 32.  Same sums, bit for bit, as launch_wgrad_vnm on the other form of `at`.
+hipError_t launch_wgrad_wide(const uint16_t* at_kept, const uint8_t* colidx, const uint16_t* G, int64_t F, int64_t N, int64_t T, int logM, int out_i_contig, uint16_t* out,
                              int64_t ldo, hipStream_t s, const GemmGroup* grp = nullptr, bool acc32 = false);
 
 }  // namespace sffn

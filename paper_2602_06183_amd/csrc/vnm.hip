@@ -53,7 +53,7 @@ __global__ void __launch_bounds__(256) vnm_to_24_kernel(const uint16_t* __restri
 
 // The transposed operand of the weight-gradient contractions from the canonical arrays, as the fused epilogues write it: KEPT = false: at = the
 // survivors compacted to 4 rows per 8 hidden units (gemm_wgrad_body.hpp), [F / 2, T] blocked, and mask = the kept-column bits of every 8;
-// KEPT = true (M = 32, 64): the 4 kept rows of every block in the order of gemm_wgrad_wide_body.hpp, and that kernel's column offsets.
+// KEPT = true (M = 32, 64): the 4 kept rows of every block in the order of gemm_wgrad_wide_body.hpp.
 // One workgroup = 64 tokens x 256 (KEPT: 16 M) hidden units through LDS: rows of 128 bytes at M = 8 in, whole 1 KB blocks out.
 //   Bound: HBM.  T = F = 8192, M = 8: 42 MB in, 67 MB out: 29 us; the dense [F, T] expansion took 51 us.
 constexpr int kCompactRows = 128, kCompactPitch = 64 + 2, kCompactLds = kCompactRows * kCompactPitch * 2 + 32 * 4 + 32;
@@ -71,7 +71,7 @@ __device__ __forceinline__ void vnm_compact_t_body(void* smem, int bx, int64_t t
     const int64_t b0 = (int64_t)bx << lognb;
     const int here = nblk - b0 < nb ? (int)(nblk - b0) : nb;
     for (int i = tid; i < ROWS * PITCH / 2; i += 256) tile32[i] = 0;
-    if (tid < here) cols[tid] = *reinterpret_cast<const uint32_t*>(colidx + (tb * nblk + b0 + tid) * 4);
+    if (!KEPT && tid < here) cols[tid] = *reinterpret_cast<const uint32_t*>(colidx + (tb * nblk + b0 + tid) * 4);
     __syncthreads();
     if (!KEPT) {
         if (tid < here << (logM - 3)) {            // a group of 8 hidden units: which of them are among its block's kept columns
@@ -86,9 +86,6 @@ __device__ __forceinline__ void vnm_compact_t_body(void* smem, int bx, int64_t t
             mask[tb * (F >> 3) + (b0 << (logM - 3)) + tid] = (uint8_t)m;
         }
         __syncthreads();
-    } else if (tid < here) {                       // word (b % 2, b % 8 / 2) of every 8 blocks
-        const int64_t blk = b0 + tid;
-        reinterpret_cast<uint32_t*>(mask)[(tb * (nblk >> 3) + (blk >> 3)) * 8 + (blk & 1) * 4 + ((blk & 7) >> 1)] = cols[tid];
     }
     for (int e = tid; e < 64 << lognb; e += 256) {
         const int r = e >> lognb, bl = e & (nb - 1);
@@ -116,7 +113,7 @@ __device__ __forceinline__ void vnm_compact_t_body(void* smem, int bx, int64_t t
         const int tc = KEPT ? ((e >> 6) & 3) * 16 + ((e >> 5) & 1) * 8 : ((e >> 6) & 1) * 32 + (l & 3) * 8;
         if (row0 + fr >= rows) continue;
         const uint32_t* p = tile32 + (fr * PITCH + tc) / 2;
-        *reinterpret_cast<uint4*>(at + (KEPT ? lane_off(row0 + fr, tb * 64 + tc, rows >> 5) : blk_off(row0 + fr, tb * 64 + tc, T / 32))) = make_uint4(p[0], p[1], p[2], p[3]);
+        *reinterpret_cast<uint4*>(at + (KEPT ? kept_off(row0 + fr, tb * 64 + tc, rows >> 5) : blk_off(row0 + fr, tb * 64 + tc, T / 32))) = make_uint4(p[0], p[1], p[2], p[3]);
     }
 }
 

@@ -347,3 +347,20 @@ def test_kept_row_weight_gradients_over_few_token_blocks(M, blocks):
     dev = [to_dev(x) for x in packed]
     for f_major in (True, False):
         assert_gemm_close(to_bits(sffn.vnm_wgrad(*dev, to_dev(G), f_major, 64, M)), oracle.vnm_wgrad(*packed, G, f_major, 64, M), "wgrad")
+
+
+@pytest.mark.parametrize("M", [32, 64])
+@pytest.mark.parametrize("blocks", [5, 6, 7, 10, 11, 12, 13])
+def test_kept_row_weight_gradients_on_large_tiles(M, blocks):
+    """512 x 64 tiles (17 x 17 of them, at M = 32 the last row half full) at every place in the six token blocks that are in flight, from the fewest
+    tokens of this form on.  Small integers: every sum is exact in float32, so the results are equal to the bit."""
+    T, F, N = 64 * blocks, 8704 - 256 * (M == 32), 1088
+    rng = np.random.default_rng(M + blocks)
+    y1 = bf16_bits_from_f32(rng.integers(-3, 4, (T, F)).astype(np.float32))
+    G = bf16_bits_from_f32(rng.integers(-2, 3, (T, N)).astype(np.float32))
+    packed = oracle.sqrelu_vnm_compress(y1, 64, M)
+    dense, g = to_dev(oracle.vnm_decompress(*packed, 64, M)).float(), to_dev(G).float()
+    dev = [to_dev(x) for x in packed]
+    want = (dense.t().contiguous() @ g).bfloat16()
+    assert torch.equal(sffn.vnm_wgrad(*dev, to_dev(G), True, 64, M), want)
+    assert torch.equal(sffn.vnm_wgrad(*dev, to_dev(G), False, 64, M), want.t())
