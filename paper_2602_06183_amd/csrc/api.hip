@@ -964,7 +964,7 @@ static int run_router_step(const sffn_cfg* cfg, const int64_t* seg_offsets, cons
     RouterPrologueArgs pro = {};
     pro.rows = (int)rows; pro.D = (int)D; pro.F = (int)F; pro.logM = logM; pro.mode = cfg->mode; pro.perm = perm; pro.seg = g1;
     if (fwd) {
-        pro.X = X; pro.xt = xpt; pro.xb = xb;           // permuted rows: transposed (eq. (8)) and blocked (eq. (1))
+        pro.X = X; pro.xt = xpt; pro.xb = xb;           // permuted rows: transposed (eq. (8)) and as they are (eq. (1)), both blocked
         pro.colidx = colidx;
         // rows past the last run are padding that no contraction writes (device table: at most 64 (E + 1) of them)
         pro.max_tail = (int)(seg_dev ? 64 * (E + 1) : rows - used);
@@ -1006,12 +1006,12 @@ static int run_router_step(const sffn_cfg* cfg, const int64_t* seg_offsets, cons
     if (one_launch) STAGE(launch_router_dy2_y3(c4, c3, s), "router/dy2c+dsqrelu+y3");                                              // eqs. (4), (6) and (3)
     // eq. (5) is computed as dW2.T [F, D] (whole 2 D-byte rows per hidden unit) and transposed: writing dW2 [D, F] directly
     // would scatter 8-byte pieces M hidden units apart
-    if (bwd) STAGE(launch_gemm_nt(0, at, nullptr, dypt, nullptr, Kc, D, rows, 0, dw2t, D, s, &g2), "router/dW2.T");                 // eq. (5)
+    if (bwd) STAGE(launch_wgrad_router(at, dypt, Kc, D, rows, dw2t, D, s, g2), "router/dW2.T");                 // eq. (5)
     if (bwd && !L.share) STAGE(launch_transpose(dw2t, F, D, D, dW2, 0, nullptr, s), "router/dW2");
     if (bwd && !one_launch) STAGE(launch_gemm_vnm_epilogue(w2cvb, w2cmb, dyb, nullptr, Kc, rows, D, dy2c, ep4, s, &g4), "router/dy2c+dsqrelu");
     if (bwd && L.share) STAGE(launch_router_dx(c7, dw2t, F, D, dW2, s), "router/dX+dW2");                                          // eq. (7), dW2.T -> dW2
     else if (bwd) STAGE(launch_spmm_blocked(avb2, amb, w1et, nullptr, rows, D, Kc, 0, dX, D, s, &g0), "router/dX");                // eq. (7)
-    if (bwd) STAGE(launch_gemm_nt(0, at2, nullptr, xpt, nullptr, Kc, D, rows, 0, dW1, D, s, &g2), "router/dW1");                   // eq. (8)
+    if (bwd) STAGE(launch_wgrad_router(at2, xpt, Kc, D, rows, dW1, D, s, g2), "router/dW1");                   // eq. (8)
     return SFFN_OK;
 }
 

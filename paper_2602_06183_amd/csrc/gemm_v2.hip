@@ -11,6 +11,13 @@ hipError_t launch_spmm_blocked(const uint16_t* a_vals, const uint8_t* a_meta, co
     return launch_gemm_v2<true, false, 0, true, false>({a_vals, a_meta, B, bias, (int)Ra, (int)Rb, (int)K, out, ldo, 0, 0, VnmEpilogue(), g, 1.0f}, s);
 }
 
+// Dense operands, blocked: a load is 1 KB of consecutive bytes.  (Row-major ones were fetched as 64-byte halves of 16 lines: 8192 tokens, 4 experts, D = 2048, F = 8192
+// 72 -> 60 us each for eqs. (5), (8).)
+hipError_t launch_wgrad_router(const uint16_t* at, const uint16_t* G, int64_t Kc, int64_t N, int64_t rows, uint16_t* out, int64_t ldo, hipStream_t s, const GemmGroup& grp) {
+    if (!grp.n || grp.n > GemmGroup::kMaxExperts || grp.role != 2 || rows % 64 || Kc % 64 || N % 64) return hipErrorInvalidValue;
+    return launch_gemm_v2<false, false, 0, true, false>({at, nullptr, G, nullptr, (int)Kc, (int)N, (int)rows, out, ldo, 0, 0, VnmEpilogue(), grp, 1.0f}, s);
+}
+
 hipError_t launch_gemm_vnm_epilogue(const uint16_t* a_vals, const uint8_t* a_meta, const uint16_t* B, const float* bias, int64_t F,
                                     int64_t T, int64_t K, uint16_t* out, const VnmEpilogue& ep, hipStream_t s, const GemmGroup* grp, int tile) {
     const GemmGroup g = grp ? *grp : GemmGroup();

@@ -94,15 +94,15 @@ __device__ __forceinline__ void gemm_nt_v2_body(unsigned char* __restrict__ smem
     const int tok_ld = grp.n ? SEG(grp.n) : Rb;       // tokens in the token-indexed outputs of the V:N:M epilogue
     int i_base = 0, j_base = 0;
     int expert_id = 0;
-    if (!SPARSE && !BLOCKED && grp.n && grp.role == 2) {
-        // every expert has its own tiles_m x tiles_n output and contracts over its own k range of the shared operands
+    if (!SPARSE && BLOCKED && grp.n && grp.role == 2) {
+        // every expert has its own tiles_m x tiles_n output and contracts over its own k range (whole chunks of 32) of the shared operands
         const int per = tiles_m * tiles_n;
         expert_id = uniform(L / per);
         L -= expert_id * per;
         if (expert_id >= grp.n) return;
         const int k0 = SEG(expert_id);
         K = SEG(expert_id + 1) - k0;
-        a_vals += k0; B += k0;
+        a_vals += (int64_t)k0 * 16; B += (int64_t)k0 * 16;
         out += expert_id * grp.out_stride;
     } else if (grp.n) {
         int e = 0;
@@ -477,7 +477,7 @@ __device__ __forceinline__ void gemm_nt_v2_body(unsigned char* __restrict__ smem
             for (int p = 0; p < 8; ++p) {
                 const int row = p * 8 + (lane >> 3), ch = lane & 7;
                 if (valid)
-                    *reinterpret_cast<uint4*>(ep.at + (int64_t)(f0 + row) * ep.at_ld + t0 + ch * 8) = *reinterpret_cast<const uint4*>(scratch + row * EP + (ch ^ ((row >> 4) & 3)) * 16);
+                    *reinterpret_cast<uint4*>(ep.at + blk_off(f0 + row, t0 + ch * 8, ep.at_ld / 32)) = *reinterpret_cast<const uint4*>(scratch + row * EP + (ch ^ ((row >> 4) & 3)) * 16);
             }
         };
 #pragma unroll

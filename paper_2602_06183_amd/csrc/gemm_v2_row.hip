@@ -4,11 +4,8 @@
 namespace sffn {
 
 hipError_t launch_gemm_nt(int sparse_a, const uint16_t* a_vals, const uint8_t* a_meta, const uint16_t* B, const float* bias,
-                             int64_t Ra, int64_t Rb, int64_t K, int out_i_contig, uint16_t* out, int64_t ldo, hipStream_t s,
-                             const GemmGroup* grp) {
-    const GemmGroup g = grp ? *grp : GemmGroup();
-    if (g.n && (sparse_a || g.role != 2 || g.n > GemmGroup::kMaxExperts)) return hipErrorInvalidValue;
-    const GemmV2Args a = {a_vals, a_meta, B, bias, (int)Ra, (int)Rb, (int)K, out, ldo, 0, 0, VnmEpilogue(), g, 1.0f};
+                             int64_t Ra, int64_t Rb, int64_t K, int out_i_contig, uint16_t* out, int64_t ldo, hipStream_t s) {
+    const GemmV2Args a = {a_vals, a_meta, B, bias, (int)Ra, (int)Rb, (int)K, out, ldo, 0, 0, VnmEpilogue(), GemmGroup(), 1.0f};
     if (sparse_a) return out_i_contig ? launch_gemm_v2<true, true, 0, false, false>(a, s)
                                       : launch_gemm_v2<true, false, 0, false, false>(a, s);
     return out_i_contig ? launch_gemm_v2<false, true, 0, false, false>(a, s)

@@ -31,7 +31,7 @@ struct VnmEpilogue {
     //        compact columns: outputs vals, meta; padding rows (perm < 0) come out as zeros; `out` = y1c [rows, F] if store_dense.
     // mode 4 (the same experts, backward): the tile of dy2c meets (meta, ykept = the stored y1c [rows, F]) and becomes dy1 in y2's
     //        slots: outputs vals (canonical) and v24 (the same, blocked); `out` = dy2c if store_dense.
-    //        Both, with `at`: the survivors as a dense transposed matrix [F, at_ld tokens], row-major, zeros at the dropped positions.
+    //        Both, with `at`: the survivors as a dense transposed matrix [F, at_ld tokens], blocked, zeros at the dropped positions.
     // mode 5 / 6 (blocks of M = 2^logM = 16, 32, 64 columns, Table 5): as modes 1 / 2 with outputs vals, meta, colidx (mode 5), ykept
     //        ([T/64][F/64][64 tokens][64/M blocks] pairs), `at` + kmask (mode 5) exactly as for modes 1 / 2 (a block of M columns keeps 4, so no
     //        group of 8 hidden units keeps more than 4); no v24 / m24 (eqs. (3), (7) gather the kept rows of the dense operand from the
@@ -529,8 +529,10 @@ hipError_t launch_gemm_vnm_epilogue(const uint16_t* a_vals, const uint8_t* a_met
 hipError_t launch_spmm_blocked(const uint16_t* a_vals, const uint8_t* a_meta, const uint16_t* B, const float* bias, int64_t Ra, int64_t Rb,
                                int64_t K, int out_i_contig, uint16_t* out, int64_t ldo, hipStream_t s, const GemmGroup* grp = nullptr);
 hipError_t launch_gemm_nt(int sparse_a, const uint16_t* a_vals, const uint8_t* a_meta, const uint16_t* B, const float* bias,
-                          int64_t Ra, int64_t Rb, int64_t K, int out_i_contig, uint16_t* out, int64_t ldo, hipStream_t s,
-                          const GemmGroup* grp = nullptr);   // grp: dense A only, role 2 (every expert contracts over its own k range)
+                          int64_t Ra, int64_t Rb, int64_t K, int out_i_contig, uint16_t* out, int64_t ldo, hipStream_t s);
+// eqs. (5), (8) of the neuron-level router: out[i * ldo + j] = sum over expert e's rows of at[i, row] * G[j, row], both blocked, dense [Kc, rows] and [N, rows];
+// grp: role 2 (every expert contracts over its own run of rows, output rows by map_logM)
+hipError_t launch_wgrad_router(const uint16_t* at, const uint16_t* G, int64_t Kc, int64_t N, int64_t rows, uint16_t* out, int64_t ldo, hipStream_t s, const GemmGroup& grp);
 
 // eqs. (5), (8): C[f, n] = sum_t A[t, f] * G[t, n] with A given as `atc` (compacted transposed activation written by the
 // V:N:M epilogue) + kmask (kept-column bit masks, [T / 64, F / 8]), G = [N rows, T] in the blocked layout; out_i_contig: out[n * ldo + f], else out[f * ldo + n].

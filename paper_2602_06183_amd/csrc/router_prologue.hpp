@@ -116,9 +116,9 @@ struct RouterPrologueUnit {
         b -= u.n_w2;
         if (b < u.n_w1) { router_w1_body<LOGM, SOFT>(smem, b % gw, b / gw, a); return; }
         b -= u.n_w1;
-        if (b < u.n_x) { transpose_bf16_body(smem, b % gx, b / gx, a.X, a.rows, a.D, a.D, a.xt, 0, a.xb, a.perm); return; }
+        if (b < u.n_x) { transpose_bf16_body(smem, b % gx, b / gx, a.X, a.rows, a.D, a.D, a.xt, 1, a.xb, a.perm); return; }
         b -= u.n_x;
-        if (b < u.n_dy) { transpose_bf16_body(smem, b % gx, b / gx, a.dY, a.rows, a.D, a.D, a.dyt, 0, a.dyb, a.perm); return; }
+        if (b < u.n_dy) { transpose_bf16_body(smem, b % gx, b / gx, a.dY, a.rows, a.D, a.D, a.dyt, 1, a.dyb, a.perm); return; }
         b -= u.n_dy;
         if (b < u.n_c) {
             const int groups = a.F >> LOGM;
