@@ -296,6 +296,24 @@ inline int pick_wgrad_tile(int64_t F, int64_t N, int64_t T, int experts, bool sp
     return pick_tile(large_rounds(tiles(256)), tiles(128), tiles(64), (int)(T / 64 / e), 0.58f, split_ok ? 256 : 0, 12);
 }
 
+// Weight gradients of few tokens, bf16, launches of their own: 128 tiles on a ring of two stages, three workgroups a CU (768 tiles at a time), so that the stores of one
+// tile run under the loads of two others.  A tile of few stages is mostly its start and its stores: T = 64, N = 7040, F = 23552 85 / 82 us on 256 tiles / 128 tiles of three
+// stages, 62 on this form; T = 256 119 / 122, 101; T = 512, N = 1728, F = 5504 18 / 17, 16; T = 1024, N = 4032, F = 13440 101 / 102, 96; into float32 T = 384, N = 4608,
+// F = 20160 174 / 170, 158.  Tiles that two workgroups a CU hold at once gain nothing (T = 448, N = 704, F = 2432, 114 of them: 13 / 7.4 / 8.3; 374 at T = 512: 16 / 12.2 / 11.9), nor does it pay where large
+// tiles just fill their rounds (T = 768, N = 1920, F = 7296, 232 of them: 23.0 / 24.7 / 25.9; T = 1280, N = 2944, F = 10368, 492: 65 / 69 / 69).  Above 20 token blocks not measured but for
+// T = 1984, N = 4096, F = 14336 (178 / 177 / 174) and T = 4096, N = 2048, F = 8192 (93 / 104 / 109).  Not for experts, whose tiles are of different lengths (8 of 630
+// tokens on average, D = 1536, F = 4992: the step 591 us, 606 with it).  Codes: 200 registers, two workgroups a CU; with 168 they spill (T = 1216, a whole step a quarter slower).
+// The order of the sums is that of the other tiles: same bits.
+inline bool wgrad_three_a_cu(int64_t F, int64_t N, int64_t T, int experts, int tile) {
+    auto tiles = [&](int64_t edge) { return (unsigned)((F + edge - 1) / edge * ((N + edge - 1) / edge)); };
+    const unsigned n = tiles(128), rest = n % 768;
+    if (experts || tile == 64 || T > 1280 || n <= (T > 512 ? 512u : 320u)) return false;
+    if (tile == 128) return true;
+    // a round of 768 in rounds of 256 large tiles; the last one takes less where it leaves the workgroups of a CU alone
+    const float rounds = (float)(n / 768) + (rest == 0 ? 0.0f : rest <= 256 ? 0.65f : rest <= 512 ? 0.9f : 1.0f);
+    return rounds * (0.68f + 0.07f * (float)T / 768.0f) < large_rounds(tiles(256));
+}
+
 // Weight gradients on the kept rows only (gemm_wgrad_wide_body.hpp; bf16, launches of their own), from 320 tokens per expert on: with fewer the matrix work that
 // is saved is less than clearing a tile in LDS and reading it out again (F = 16384, N = 4096, M = 32: 50 us for 50 at 256 tokens, 51 for 54 at 320, 173 for 354 at 4096;
 // M = 64: 43 for 45 at 192; F = 8192, N = 2048, M = 32: 17.9 for 17.4 at 256, 17.9 for 18.4 at 320, 22.4 for 30.7 at 1024).

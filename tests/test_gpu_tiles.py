@@ -364,3 +364,35 @@ def test_kept_row_weight_gradients_on_large_tiles(M, blocks):
     want = (dense.t().contiguous() @ g).bfloat16()
     assert torch.equal(sffn.vnm_wgrad(*dev, to_dev(G), True, 64, M), want)
     assert torch.equal(sffn.vnm_wgrad(*dev, to_dev(G), False, 64, M), want.t())
+
+
+@pytest.mark.parametrize("T,N,F", [
+    (64, 2560, 2624), (128, 2560, 2624), (192, 2560, 2624),     # one stage, as many as the ring has, one more; 420 tiles, the last row half full
+    (320, 1088, 12352),         # 873 tiles: a second round of three workgroups a CU, both edges half full
+    (1280, 3008, 3136),         # the most tokens, 600 tiles
+])
+def test_weight_gradients_with_three_workgroups_a_cu(T, N, F):
+    """Small integers: every sum is exact in float32, so the results are equal to the bit; added to float32 gradients in a backward call."""
+    rng = np.random.default_rng(T + N)
+    y1 = bf16_bits_from_f32(rng.integers(-3, 4, (T, F)).astype(np.float32))
+    G = bf16_bits_from_f32(rng.integers(-2, 3, (T, N)).astype(np.float32))
+    packed = oracle.sqrelu_vnm_compress(y1, 64, 8)
+    dense, g = to_dev(oracle.vnm_decompress(*packed, 64, 8)).float(), to_dev(G).float()
+    dev = [to_dev(x) for x in packed]
+    want = (dense.t().contiguous() @ g).bfloat16()
+    assert torch.equal(sffn.vnm_wgrad(*dev, to_dev(G), True, 64, 8), want)
+    assert torch.equal(sffn.vnm_wgrad(*dev, to_dev(G), False, 64, 8), want.t())
+
+
+def test_float32_weight_gradients_with_three_workgroups_a_cu():
+    """A backward call into float32 (T = 192: eqs. (5), (8) in launches of their own) rounds to the bits of the bf16 step."""
+    T, D, F = 192, 4544, 11264
+    inp = make_ffn_inputs(T, D, F, seed=31)
+    dev = [to_dev(inp[k]) for k in ("X", "W1", "W2", "b1", "dY")]
+    plain = [t.clone() for t in sffn.FfnStep(T, D, F, lean=True)(*dev)]
+    step = sffn.FfnStep(T, D, F, lean=True, dw_fp32=True)
+    step.dW1.zero_(), step.dW2.zero_()
+    step.forward(*dev[:4])
+    step.backward(dev[1], dev[4])
+    for a, b in zip(plain[2:], (step.dW1, step.dW2)):
+        assert torch.equal(a, b.bfloat16())
