@@ -336,8 +336,10 @@ __device__ __forceinline__ void gemm_nt_v2_body(unsigned char* __restrict__ smem
     wait_vmcnt<0>();
     }
     __syncthreads();
-    if (KW > 1) {       // partial sums -> the first wavefront, in ascending order; the others are done
-        constexpr int PART = FM * FN * 4 * 256;
+    // SHARE: the wavefronts of a shared tile share its epilogue too (below)
+    constexpr bool SHARE = KW > 1 && (EPI == 1 || EPI == 2);
+    constexpr int PART = FM * FN * 4 * 256;
+    if (KW > 1 && !SHARE) {       // partial sums -> the first wavefront, in ascending order; the others are done
         static_assert((KW - 1) * PART <= KW * C::NSTAGE * C::STAGE, "partial sums must fit in the main-loop LDS");
         if (kg > 0) {
             float* p = reinterpret_cast<float*>(smem + (kg - 1) * PART) + lane;
@@ -369,8 +371,9 @@ __device__ __forceinline__ void gemm_nt_v2_body(unsigned char* __restrict__ smem
         constexpr int EP = 64 * 2 + 16;
         // EPI: second tile (32 compact rows) for the transposed output
         constexpr int WAVE_LDS = (EPI != 0) ? (WN + 32) * EP : WN * EP;
-        unsigned char* scratch = smem + wt * WAVE_LDS;
-        static_assert(TL::NW * WAVE_LDS <= GemmV2Lds<SPARSE, OUT_I_CONTIG, EPI, BLOCKED, FP8, TL, MG>::BYTES, "epilogue scratch must fit in the main-loop LDS");
+        static_assert(!SHARE || (KW == 4 && FM == 4 && NH == 1), "four wavefronts, 16 tokens and two sweeps each");
+        unsigned char* scratch = smem + (SHARE ? KW * PART : wt * WAVE_LDS);
+        static_assert((SHARE ? KW * PART : 0) + TL::NW * WAVE_LDS <= GemmV2Lds<SPARSE, OUT_I_CONTIG, EPI, BLOCKED, FP8, TL, MG>::BYTES, "epilogue scratch must fit in the main-loop LDS");
         unsigned char* ttile = scratch + WN * EP;
         // EPI: i = hidden unit f, j = token t; the wave's 64 tokens are exactly one V = 64 block and each half of
         // 64 f holds 8 whole column blocks, so the V:N:M work is wave-local.
@@ -378,12 +381,16 @@ __device__ __forceinline__ void gemm_nt_v2_body(unsigned char* __restrict__ smem
         const int nblk = Ra >> 3;
         const int64_t F = Ra;
         uint32_t nib_h0 = 0;                                  // M = 64: the metadata nibble of the first half waits for the second's
+        // Of the eight sweeps over a half's tokens (lane = (token, column block)) this wavefront does NSW from it0 on.  On a shared tile the scores are every wavefront's own: one has to
+        // add the 64 tokens in order, and the others would wait for it.  (All of the epilogue in the first wavefront: T = 64, D = 2048, F = 8192 a forward call on packed weights 24.2 us, now 23.0; the fp8 step of that size 97.5, 91.9.)
+        constexpr int NSW = SHARE ? 2 : 8;
+        const int it0 = SHARE ? 2 * kg : 0;
         // The lane's 16 bias values of each half (eq. (4) has none), and (EPI 2) the saved column offsets, metadata and y1 of its 8 sweeps: all fetched here, for
         // both halves.  Loads and stores share one in-order counter, so a load issued after the first half's stores would wait for all of them
         // (and for its own latency) in the middle of the epilogue.
         constexpr bool BIAS = EPI != 2 && EPI != 4 && !GEN_B;
         float4 bb_all[NH][4];
-        uint32_t pre_cw[NH], pre_m[NH], pre_y_all[NH][8];
+        uint32_t pre_cw[NH], pre_m[NH], pre_y_all[NH][NSW];
         const uint32_t amax_seen = (FP8 && EPI != 0) ? amax_slot_peek(ep.amax) : 0u;
         float vmax_tile = 0.0f;                                 // fp8: largest survivor magnitude of the wave's tile
 #pragma unroll
@@ -406,7 +413,7 @@ __device__ __forceinline__ void gemm_nt_v2_body(unsigned char* __restrict__ smem
                 pre_m[h] = *reinterpret_cast<const uint32_t*>(ep.mcb + (FP8 ? mcb8_off(t0, f0 >> 6, F) : mcb_off(t0, f0 >> 6, F)) + ((lane >> 3) + 8 * (lane & 7)) * (FP8 ? 8 : 4));
                 const uint32_t* kp = reinterpret_cast<const uint32_t*>(ep.ykept) + ykept_off(t0, f0 >> 3, F);
 #pragma unroll
-                for (int it = 0; it < 8; ++it) pre_y_all[h][it] = kp[lane + it * 64];
+                for (int it = 0; it < NSW; ++it) pre_y_all[h][it] = kp[lane + (it0 + it) * 64];
             }
         }
         // (the same for the backward epilogue of the wide blocks)
@@ -453,7 +460,7 @@ __device__ __forceinline__ void gemm_nt_v2_body(unsigned char* __restrict__ smem
             }
             return sc;
         };
-        const uint32_t s_off = (uint32_t)(wt * WAVE_LDS);      // the scratch tile as an offset into smem (a multiple of 16, and so are its rows)
+        const uint32_t s_off = (uint32_t)(SHARE ? KW * PART : wt * WAVE_LDS);      // the scratch tile as an offset into smem (a multiple of 16, and so are its rows)
         auto lds_u16 = [&](uint32_t off) { return (uint32_t)*reinterpret_cast<const uint16_t*>(smem + off); };
         // EPI 3, 4: the survivors as the dense transposed matrix at[f, t] (row length ep.at_ld), zeros at the dropped positions: the A operand of the
         // experts' weight gradients.  The half tile is turned in place (its rows have been read): two tokens make a word of one of the four rows of
@@ -480,6 +487,22 @@ __device__ __forceinline__ void gemm_nt_v2_body(unsigned char* __restrict__ smem
                     *reinterpret_cast<uint4*>(ep.at + blk_off(f0 + row, t0 + ch * 8, ep.at_ld / 32)) = *reinterpret_cast<const uint4*>(scratch + row * EP + (ch ^ ((row >> 4) & 3)) * 16);
             }
         };
+        auto tile_sync = [&]() { if (SHARE) __syncthreads(); else wave_lds_sync(); };
+        f32x4 mine[4];                                         // SHARE: the sums, in the order of the shares of the contraction, for the 16 tokens of fragment kg
+        if (SHARE) {
+            f32x4* p = reinterpret_cast<f32x4*>(smem) + lane;
+#pragma unroll
+            for (int b = 0; b < FN; ++b)
+#pragma unroll
+                for (int a = 0; a < 4; ++a) p[(kg * FN * 4 + b * 4 + a) * 64] = acc[a][b];
+            __syncthreads();
+#pragma unroll
+            for (int a = 0; a < 4; ++a) {
+                mine[a] = p[(kg * 4 + a) * 64];
+#pragma unroll
+                for (int g = 1; g < KW; ++g) mine[a] += p[((g * FN + kg) * 4 + a) * 64];
+            }
+        }
 #pragma unroll
         for (int h = 0; h < NH; ++h) {
             const int f0 = i0 + wm * WM + h * 64;
@@ -488,8 +511,9 @@ __device__ __forceinline__ void gemm_nt_v2_body(unsigned char* __restrict__ smem
 #pragma unroll
             for (int a = 0; a < 4; ++a)
 #pragma unroll
-                for (int b = 0; b < FN; ++b) {
-                    f32x4 v = acc[4 * h + a][b];
+                for (int b = 0; b < (SHARE ? 1 : FN); ++b) {
+                    f32x4 v = SHARE ? mine[a] : acc[4 * h + a][b];
+                    const int row = (SHARE ? kg : b) * 16 + l16;
                     const float al = FP8 ? alpha : 1.0f;
                     // (codes were multiplied: the product of the two tensor scales comes first, one rounding, then the bias)
 #pragma unroll
@@ -498,18 +522,20 @@ __device__ __forceinline__ void gemm_nt_v2_body(unsigned char* __restrict__ smem
                         v[r] = !BIAS ? v[r] * al : FP8 ? v[r] * alpha + w : v[r] + w;
                     }
                     // i = a * 16 + 4 lq .. + 3 inside the 64-wide half
-                    *reinterpret_cast<uint2*>(scratch + (b * 16 + l16) * EP + (a * 16 + 4 * lq) * 2) = tok_ok[b] ? make_uint2(f2bf2(v[0], v[1]), f2bf2(v[2], v[3])) : make_uint2(0u, 0u);
+                    *reinterpret_cast<uint2*>(scratch + row * EP + (a * 16 + 4 * lq) * 2) = tok_ok[b] ? make_uint2(f2bf2(v[0], v[1]), f2bf2(v[2], v[3])) : make_uint2(0u, 0u);
                 }
             if (EPI == 1 || EPI == 2 || GEN_F || GEN_B) {
 #pragma unroll
-                for (int q = 0; q < (32 * EP + 1023) / 1024; ++q)
-                    if ((q * 64 + lane) * 16 < 32 * EP) *reinterpret_cast<uint4*>(ttile + (q * 64 + lane) * 16) = make_uint4(0, 0, 0, 0);
+                for (int q = 0; q < (32 * EP / (SHARE ? KW : 1) + 1023) / 1024; ++q) {
+                    const int at = (SHARE ? q * 64 * KW + tid : q * 64 + lane) * 16;
+                    if (at < 32 * EP) *reinterpret_cast<uint4*>(ttile + at) = make_uint4(0, 0, 0, 0);
+                }
             }
-            wave_lds_sync();
+            tile_sync();
             if (EPI == 0 || ep.store_dense) {
 #pragma unroll
-                for (int p = 0; p < WN / 8; ++p) {
-                    const int row = p * 8 + (lane >> 3), ch = lane & 7;
+                for (int p = 0; p < (EPI == 1 || EPI == 2 ? NSW : WN / 8); ++p) {
+                    const int row = (it0 + p) * 8 + (lane >> 3), ch = lane & 7;
                     const int j = t0 + row, i = f0 + ch * 8;
                     if (j < Rb && i < Ra) {
                         const uint4 w = *reinterpret_cast<const uint4*>(scratch + row * EP + ch * 16);
@@ -712,7 +738,7 @@ __device__ __forceinline__ void gemm_nt_v2_body(unsigned char* __restrict__ smem
                     // kept column number n of the block goes to byte n of the word of all of its lanes
                     uint32_t mine = (bits >> bl) & 1u ? (uint32_t)bl << (8 * __builtin_popcount(bits & ((1u << bl) - 1u))) : 0u;
                     mine = or_of_8(mine);
-                    if (valid && bl == 0)
+                    if (valid && bl == 0 && kg == 0)
                     {
                         *reinterpret_cast<uint32_t*>(ep.colidx + ((int64_t)(t0 >> 6) * nblk + (f0 >> 3) + (lane >> 3)) * 4) = mine;
                         ep.kmask[(int64_t)(t0 >> 6) * nblk + (f0 >> 3) + (lane >> 3)] = (uint8_t)bits;
@@ -722,7 +748,7 @@ __device__ __forceinline__ void gemm_nt_v2_body(unsigned char* __restrict__ smem
                         const int q = lane & 15, hq = q >> 3, pq = q & 7, hf = (f0 >> 6) & 1;
                         const uint32_t b0 = ((uint32_t)__shfl((int)mine, (4 * hq + (pq >> 2)) * 8, 64) >> (8 * (pq & 3))) & 0xFFu;
                         const uint32_t b1 = ((uint32_t)__shfl((int)mine, (4 * hq + 2 + (pq >> 2)) * 8, 64) >> (8 * (pq & 3))) & 0xFFu;
-                        if (valid && lane < 16)
+                        if (valid && lane < 16 && kg == 0)
                             *reinterpret_cast<uint16_t*>(ep.cixt + cixt8_off(t0 >> 6, f0 >> 7, tok_ld >> 6) + q * 4 + 2 * hf) = (uint16_t)(b0 | (b1 << 8));
                     }
                     if (!FP8 && ep.cixt) {      // the same offsets regrouped for the transposing reads of gemm_vnm8.hip: word q = (h, r), byte j
@@ -731,7 +757,7 @@ __device__ __forceinline__ void gemm_nt_v2_body(unsigned char* __restrict__ smem
 #pragma unroll
                         for (int j = 0; j < 4; ++j)
                             dw |= (((uint32_t)__shfl((int)mine, (4 * (j >> 1) + (j & 1) + 2 * hq) * 8, 64) >> (8 * rq)) & 0xFFu) << (8 * j);
-                        if (valid && lane < 8) *reinterpret_cast<uint32_t*>(ep.cixt + cixt_off(t0 >> 6, f0 >> 6, tok_ld >> 6) + q * 4) = dw;
+                        if (valid && lane < 8 && kg == 0) *reinterpret_cast<uint32_t*>(ep.cixt + cixt_off(t0 >> 6, f0 >> 6, tok_ld >> 6) + q * 4) = dw;
                     }
                 } else {
                     cw = pre_cw[h];
@@ -739,46 +765,50 @@ __device__ __forceinline__ void gemm_nt_v2_body(unsigned char* __restrict__ smem
                 // Per-row pass: lane = (column block bl, token t); 8 tokens per sweep, 8 sweeps.  Every output but the canonical copies is a run of
                 // consecutive bytes per sweep: a wave-uniform base, 4 bytes per lane and constant offsets, no address arithmetic.
                 // (This pass, the choice and the scores together, T = D = 8192, F = 28672: 1950 -> 1895 us for eq. (1), 1815 -> 1775 for eq. (4); 18 -> 12 us a tile.)
-                uint32_t* vals_p = reinterpret_cast<uint32_t*>(ep.vals) + ((int64_t)(t0 + (lane >> 3)) * (F / 4) + blk_g * 2) / 2;
-                uint32_t* kept_p = reinterpret_cast<uint32_t*>(ep.ykept) + ykept_off(t0, f0 >> 3, F);
+                uint32_t* vals_p = reinterpret_cast<uint32_t*>(ep.vals) + ((int64_t)(t0 + 8 * it0 + (lane >> 3)) * (F / 4) + blk_g * 2) / 2;
+                uint32_t* kept_p = reinterpret_cast<uint32_t*>(ep.ykept) + ykept_off(t0, f0 >> 3, F) + it0 * 64;
                 // operands of eq. (3) / eq. (7) on the V:2:8 kernel (gemm_vnm8.hip); sweep it: + (it / 4) 32-token groups + 8 (it % 4) tokens
                 uint32_t* vcb_p = FP8 ? nullptr : reinterpret_cast<uint32_t*>(ep.vcb + vcb_off(t0, f0 >> 3, F));
                 uint8_t* vcb8_p = FP8 ? reinterpret_cast<uint8_t*>(ep.vcb) + vcb8_off(t0 + (lane >> 3), blk_g, F) : nullptr;   // (the lane of block 0 stores its row's 8 pairs of codes)
                 const uint32_t c2 = cw * 2;                                 // the four kept columns as byte offsets
                 const uint32_t q0 = c2 & 0xFFu, q1 = (c2 >> 8) & 0xFFu, q2 = (c2 >> 16) & 0xFFu, q3 = c2 >> 24;
                 const uint32_t tag[4] = {0x30u | q0, 0x20u | q1, 0x10u | q2, q3};
-                const uint32_t row0 = s_off + (lane >> 3) * EP + bl * 16;    // (rows and blocks are multiples of 16 bytes: a byte of c2 goes in by OR)
-                const uint32_t tt0 = s_off + WN * EP + bl * 4 * EP + (lane >> 3) * 2;
-                const uint32_t (&pre_y)[8] = pre_y_all[h];
-                uint32_t v[8], pos[8];                                     // of every sweep: the survivors, their positions among the four kept columns
+                const uint32_t row0 = s_off + (8 * it0 + (lane >> 3)) * EP + bl * 16;    // (rows and blocks are multiples of 16 bytes: a byte of c2 goes in by OR)
+                const uint32_t tt0 = s_off + WN * EP + bl * 4 * EP + (8 * it0 + (lane >> 3)) * 2;
+                const uint32_t (&pre_y)[NSW] = pre_y_all[h];
+                uint32_t v[NSW], pos[NSW];                                     // of every sweep: the survivors, their positions among the four kept columns
                 // (all reads of the tile come first: a sweep that branches or writes LDS waits for its own two LDS latencies before the next one starts)
                 if (EPI == 1) {
-                    uint32_t low[8], high[8], mword = 0;                   // mword: the metadata of token lane / 8 + 8 bl
+                    uint32_t low[NSW], high[NSW], mword = 0;                   // mword: the metadata of token lane / 8 + 8 bl
 #pragma unroll
-                    for (int it = 0; it < 8; ++it) {
+                    for (int it = 0; it < NSW; ++it) {
                         const uint32_t r = row0 + it * 8 * EP;
                         v[it] = pick24_pos(sqrelu2(lds_u16(r + q0) | (lds_u16(r + q1) << 16)), sqrelu2(lds_u16(r + q2) | (lds_u16(r + q3) << 16)), tag, low[it], high[it]);
                     }
 #pragma unroll
-                    for (int it = 0; it < 8; ++it) {
+                    for (int it = 0; it < NSW; ++it) {
                         pos[it] = (((low[it] >> 4) & 3u) | ((high[it] >> 2) & 0xCu)) ^ 0xFu;
                         const uint32_t mw = or_of_8(pos[it] << (4 * bl));   // the row's 8 blocks
-                        mword = bl == it ? mw : mword;
+                        mword = bl == it0 + it ? mw : mword;
                         low[it] = lds_u16(((low[it] & 15u) | row0) + it * 8 * EP) | (lds_u16(((high[it] & 15u) | row0) + it * 8 * EP) << 16);
                     }
                     if (valid) {
 #pragma unroll
-                        for (int it = 0; it < 8; ++it) kept_p[lane + it * 64] = low[it];
+                        for (int it = 0; it < NSW; ++it) kept_p[lane + it * 64] = low[it];
                         const uint32_t mt = (lane >> 3) + 8 * bl;
-                        *reinterpret_cast<uint32_t*>(ep.meta + (int64_t)t0 * (F / 16) + (f0 >> 4) + mt * (uint32_t)(F / 16)) = mword;
-                        *reinterpret_cast<uint32_t*>(ep.mcb + (FP8 ? mcb8_off(t0, f0 >> 6, F) : mcb_off(t0, f0 >> 6, F)) + mt * (FP8 ? 8 : 4)) = mword;
+                        if (!SHARE || bl >> 1 == kg) *reinterpret_cast<uint32_t*>(ep.meta + (int64_t)t0 * (F / 16) + (f0 >> 4) + mt * (uint32_t)(F / 16)) = mword;
+                        if (!SHARE || bl >> 1 == kg) *reinterpret_cast<uint32_t*>(ep.mcb + (FP8 ? mcb8_off(t0, f0 >> 6, F) : mcb_off(t0, f0 >> 6, F)) + mt * (FP8 ? 8 : 4)) = mword;
                     }
                 } else {
                     const uint32_t m = pre_m[h];
-                    pos[0] = bcast_of_8<0>(m); pos[1] = bcast_of_8<1>(m); pos[2] = bcast_of_8<2>(m); pos[3] = bcast_of_8<3>(m);
-                    pos[4] = bcast_of_8<4>(m); pos[5] = bcast_of_8<5>(m); pos[6] = bcast_of_8<6>(m); pos[7] = bcast_of_8<7>(m);
+                    if constexpr (SHARE) {
+                        pos[0] = (uint32_t)__shfl((int)m, (lane & 56) + it0, 64); pos[1] = (uint32_t)__shfl((int)m, (lane & 56) + it0 + 1, 64);
+                    } else {
+                        pos[0] = bcast_of_8<0>(m); pos[1] = bcast_of_8<1>(m); pos[2] = bcast_of_8<2>(m); pos[3] = bcast_of_8<3>(m);
+                        pos[4] = bcast_of_8<4>(m); pos[5] = bcast_of_8<5>(m); pos[6] = bcast_of_8<6>(m); pos[7] = bcast_of_8<7>(m);
+                    }
 #pragma unroll
-                    for (int it = 0; it < 8; ++it) {
+                    for (int it = 0; it < NSW; ++it) {
                         pos[it] >>= 4 * bl;
                         const float d0 = bf2f(lds_u16(((__builtin_amdgcn_alignbyte(0u, c2, pos[it]) & 15u) | row0) + it * 8 * EP));
                         const float d1 = bf2f(lds_u16(((__builtin_amdgcn_alignbyte(0u, c2, pos[it] >> 2) & 15u) | row0) + it * 8 * EP));
@@ -789,39 +819,41 @@ __device__ __forceinline__ void gemm_nt_v2_body(unsigned char* __restrict__ smem
                 // transposed tile for the weight-gradient GEMM, compacted to the block's four kept hidden units:
                 // row = 4 * block + position among the kept units, column = token
 #pragma unroll
-                for (int it = 0; it < 8; ++it) {
+                for (int it = 0; it < NSW; ++it) {
                     *reinterpret_cast<uint16_t*>(smem + __umul24(pos[it] & 3u, EP) + tt0 + it * 16) = (uint16_t)(v[it] & 0xFFFFu);
                     *reinterpret_cast<uint16_t*>(smem + __umul24((pos[it] >> 2) & 3u, EP) + tt0 + it * 16) = (uint16_t)(v[it] >> 16);
                 }
                 if (valid && ep.vals) {    // (lean form: no canonical copy; vcb and the compact transpose carry the values)
 #pragma unroll
-                    for (int it = 0; it < 8; ++it) {
+                    for (int it = 0; it < NSW; ++it) {
                         if (FP8 && EPI == 1)    // canonical values are the survivors' codes [T, F / 4]
-                            reinterpret_cast<uint16_t*>(ep.vals)[(int64_t)(t0 + (lane >> 3) + 8 * it) * (F / 8) + blk_g] =
+                            reinterpret_cast<uint16_t*>(ep.vals)[(int64_t)(t0 + (lane >> 3) + 8 * (it0 + it)) * (F / 8) + blk_g] =
                                 (uint16_t)fp8_enc2(bf2f(v[it] & 0xFFFFu), bf2f(v[it] >> 16), ep.inv_out);
                         else vals_p[(int64_t)it * 8 * (F / 8)] = v[it];
                     }
                 }
                 if (FP8 && valid) {        // the largest survivor magnitude of this half tile
 #pragma unroll
-                    for (int it = 0; it < 8; ++it)
+                    for (int it = 0; it < NSW; ++it)
                         vmax_tile = __builtin_fmaxf(vmax_tile, __builtin_fmaxf(__builtin_fabsf(bf2f(v[it] & 0xFFFFu)), __builtin_fabsf(bf2f(v[it] >> 16))));
                 }
                 if (valid && ep.vcb) {
 #pragma unroll
-                    for (int it = 0; it < 8; ++it) {
-                        if (!FP8) vcb_p[(int64_t)(it >> 2) * (F >> 6) * 256 + lane + (it & 3) * 64] = v[it];
+                    for (int it = 0; it < NSW; ++it) {
+                        const int sw = it0 + it;
+                        if (!FP8) vcb_p[(int64_t)(sw >> 2) * (F >> 6) * 256 + lane + (sw & 3) * 64] = v[it];
                         else {             // the survivors' codes: the row's 8 pairs gathered into the lane of block 0, one 16-byte store
                             const uint32_t q2w = fp8_enc2(bf2f(v[it] & 0xFFFFu), bf2f(v[it] >> 16), ep.inv_out);
                             const uint32_t w2 = q2w | (row_shl<1>(q2w) << 16);
                             const uint4 w8 = make_uint4(w2, row_shl<2>(w2), row_shl<4>(w2), row_shl<6>(w2));
-                            if (bl == 0) *reinterpret_cast<uint4*>(vcb8_p + (int64_t)(it >> 2) * (F >> 7) * 1024 + (it & 3) * 256) = w8;
+                            if (bl == 0) *reinterpret_cast<uint4*>(vcb8_p + (int64_t)(sw >> 2) * (F >> 7) * 1024 + (sw & 3) * 256) = w8;
                         }
                     }
                 }
-                wave_lds_sync();
+                tile_sync();
 #pragma unroll
-                for (int q = 0; q < 4; ++q) {          // 2 groups of 16 compact rows x 2 chunks of 32 tokens, 1 KB each
+                for (int n = 0; n < (SHARE ? 1 : 4); ++n) {          // 2 groups of 16 compact rows x 2 chunks of 32 tokens, 1 KB each
+                    const int q = SHARE ? kg : n;
                     const int fr = (q >> 1) * 16 + (lane >> 2), tc = (q & 1) * 32 + (lane & 3) * 8;
                     const uint4 w = *reinterpret_cast<const uint4*>(ttile + fr * EP + tc * 2);
                     if (FP8 && ep.at_fp8) {     // fp8 weight gradients: the compact transposed survivors leave as codes (a 64-token block = one 64-byte chunk)
