@@ -221,36 +221,16 @@ __device__ __forceinline__ void vnm_gather_body(unsigned char* __restrict__ smem
     }
 #undef SB
     __syncthreads();
-    if constexpr (KW == 4)
-        if (split.n > 1) {
-            float q[16];
-            if (split_join4(acc, smem, split, L, sp, wave, lane, q)) store_quarter(q, 1.0f, smem, wave, lane, out, ldo, t0, n0, t0 + 64, N);
-            return;
+    if constexpr (KW > 1) {
+        static_assert(KW == 4 && kJoin4 + 4 * 32 * 80 <= TL::RING, "four wavefronts; sums and their staging must fit in the main-loop LDS");
+        float q[16];
+        if (split.n == 1) {
+            join4(acc, smem, wave, lane, q);
+            store_quarter(q, 1.0f, smem + kJoin4, wave, lane, out, ldo, t0, n0, t0 + 64, N);
+        } else if (split_join4(acc, smem, split, L, sp, wave, lane, q)) {
+            store_quarter(q, 1.0f, smem, wave, lane, out, ldo, t0, n0, t0 + 64, N);
         }
-    if (KW > 1) {       // partial sums -> the first wavefront, in ascending order; the others are done
-        constexpr int PART = 4 * 16 * 256;
-        static_assert((KW - 1) * PART <= TL::RING, "partial sums must fit in the main-loop LDS");
-        if (kg > 0) {
-            float* p = reinterpret_cast<float*>(smem + (kg - 1) * PART) + lane;
-#pragma unroll
-            for (int a = 0; a < 2; ++a)
-#pragma unroll
-                for (int b = 0; b < 2; ++b)
-#pragma unroll
-                    for (int r = 0; r < 16; ++r) p[((a * 2 + b) * 16 + r) * 64] = acc[a][b][r];
-        }
-        __syncthreads();
-        if (kg > 0) return;
-        for (int g = 1; g < KW; ++g) {
-            const float* p = reinterpret_cast<const float*>(smem + (g - 1) * PART) + lane;
-#pragma unroll
-            for (int a = 0; a < 2; ++a)
-#pragma unroll
-                for (int b = 0; b < 2; ++b)
-#pragma unroll
-                    for (int r = 0; r < 16; ++r) acc[a][b][r] += p[((a * 2 + b) * 16 + r) * 64];
-        }
-        wave_lds_sync();
+        return;
     }
 
     // ---- output: the wave's 64 x 64 tile goes through LDS as [t][n] so that HBM sees 128-byte row segments --------

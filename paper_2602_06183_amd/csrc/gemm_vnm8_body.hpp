@@ -43,7 +43,7 @@ template <int WT_, int WH_, int FN_, int NST_, int KW_>
 struct VTile {
     static constexpr int WT = WT_, WH = WH_, FN = FN_, NST = NST_, KW = KW_;
     static constexpr int NW = WT * WH, BT = 64 * WT, BN = 32 * FN * WH, THREADS = 64 * NW * KW;
-    static_assert(KW == 1 || NW == 1, "a shared output tile belongs to single wavefronts");
+    static_assert(KW == 1 || (KW == 4 && NW == 1 && FN == 2), "a shared output tile is 64 x 64 and belongs to four single wavefronts");
     // Tile rows per band of the workgroup -> tile map (see SFFN_TILE_GROUP in common.hpp).  A tile of 256 x 256 fetches four times as many bytes of Wk as of the
     // packed activation, so the 32 tiles that an XCD runs at a time should share few column slabs of Wk: tall bands (T = D = 8192, F = 28672: 1.49 / 1.42 /
     // 1.38 / 1.36 ms per launch with 2 / 4 / 8 / 16 tile rows).  A tile of 512 x 128 fetches about as many of either (8 rows 1222 us, 16 rows 1233; on codes 687, 706).
@@ -300,36 +300,16 @@ __device__ __forceinline__ void vnm8_gemm_body(unsigned char* __restrict__ smem,
     wait_vmcnt<0>();
     }
     __syncthreads();
-    if constexpr (SPLIT)
-        if (split.n > 1) {
-            float q[16];
-            if (split_join4(acc, smem, split, tile, sp, wave, lane, q)) store_quarter(q, FP8 ? alpha : 1.0f, smem, wave, lane, out, ldo, i0, n0, Ra, N);
-            return;
+    if constexpr (SPLIT) {      // (all four wavefronts store: the first alone 0.3 - 0.7 us more in a launch of 10)
+        static_assert(kJoin4 + 4 * 32 * 80 <= GG::BYTES, "sums and their staging must fit in the main-loop LDS");
+        float q[16];
+        if (split.n == 1) {
+            join4(acc, smem, wave, lane, q);
+            store_quarter(q, FP8 ? alpha : 1.0f, smem + kJoin4, wave, lane, out, ldo, i0, n0, Ra, N);
+        } else if (split_join4(acc, smem, split, tile, sp, wave, lane, q)) {
+            store_quarter(q, FP8 ? alpha : 1.0f, smem, wave, lane, out, ldo, i0, n0, Ra, N);
         }
-    if (KW > 1) {       // partial sums -> the first wavefront, in ascending order; the others are done
-        constexpr int PART = 2 * FN * 16 * 256;
-        static_assert((KW - 1) * PART <= GG::BYTES, "partial sums must fit in the main-loop LDS");
-        if (kg > 0) {
-            float* p = reinterpret_cast<float*>(smem + (kg - 1) * PART) + lane;
-#pragma unroll
-            for (int a = 0; a < 2; ++a)
-#pragma unroll
-                for (int b = 0; b < FN; ++b)
-#pragma unroll
-                    for (int r = 0; r < 16; ++r) p[((a * FN + b) * 16 + r) * 64] = acc[a][b][r];
-        }
-        __syncthreads();
-        if (kg > 0) return;
-        for (int g = 1; g < KW; ++g) {
-            const float* p = reinterpret_cast<const float*>(smem + (g - 1) * PART) + lane;
-#pragma unroll
-            for (int a = 0; a < 2; ++a)
-#pragma unroll
-                for (int b = 0; b < FN; ++b)
-#pragma unroll
-                    for (int r = 0; r < 16; ++r) acc[a][b][r] += p[((a * FN + b) * 16 + r) * 64];
-        }
-        wave_lds_sync();
+        return;
     }
 
     // ---- output: the wave's 32 x 64 sub-tiles go through LDS as [t][n] so that HBM sees 128-byte row segments -----------------------------

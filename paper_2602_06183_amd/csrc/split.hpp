@@ -13,24 +13,31 @@ namespace sffn {
 // The sums travel as agent-scope atomics (written through to memory and read from there: every XCD has its own L2), which the count follows once they are
 // complete.  A fence would write back and invalidate the whole L2 instead, for every wavefront: 250 us for a contraction of 130.
 
-// Sum over the KW wavefronts of a workgroup, which share a 64 x 64 tile (64 sums a lane, in `acc`), and over the workgroups that share it.  Wavefront w
-// is left with its quarter of the tile's sums, q[16] (accumulators 16 w .. 16 w + 15 of a lane in the order [a][b][r]); false: the others are not there
-// yet, the workgroup is done.  smem: 4 x 16 KB.
-__device__ __forceinline__ bool split_join4(const f32x16 (&acc)[2][2], unsigned char* smem, const Split& sp, int tile, int s, int wave, int lane, float (&q)[16]) {
-    float* const part = reinterpret_cast<float*>(smem) + lane;
+// Sum over the four wavefronts of a workgroup, which share a 64 x 64 tile (64 sums a lane, in `acc`), in ascending order.  Wavefront w is left with its quarter of the
+// tile's sums, q[16] (accumulators 16 w .. 16 w + 15 of a lane in the order [a][b][r]).  smem: kJoin4 bytes, which other wavefronts may still be reading afterwards.
+constexpr int kJoin4 = 4 * 16 * 1024;
+__device__ __forceinline__ void join4(const f32x16 (&acc)[2][2], unsigned char* smem, int wave, int lane, float (&q)[16]) {
+    f32x4* const part = reinterpret_cast<f32x4*>(smem) + lane;
 #pragma unroll
-    for (int a = 0; a < 2; ++a)
-#pragma unroll
-        for (int b = 0; b < 2; ++b)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) part[(wave * 64 + (a * 2 + b) * 16 + r) * 64] = acc[a][b][r];
+    for (int k = 0; k < 16; ++k) {
+        const f32x16& v = acc[k >> 3][k >> 2 & 1];
+        const int r = (k & 3) * 4;
+        part[(wave * 16 + k) * 64] = f32x4{v[r], v[r + 1], v[r + 2], v[r + 3]};
+    }
     __syncthreads();
 #pragma unroll
-    for (int k = 0; k < 16; ++k) q[k] = part[(wave * 16 + k) * 64];
+    for (int k = 0; k < 4; ++k) {
+        f32x4 sum = part[(wave * 4 + k) * 64];
 #pragma unroll
-    for (int g = 1; g < 4; ++g)
+        for (int g = 1; g < 4; ++g) sum += part[(g * 16 + wave * 4 + k) * 64];
 #pragma unroll
-        for (int k = 0; k < 16; ++k) q[k] += part[(g * 64 + wave * 16 + k) * 64];
+        for (int r = 0; r < 4; ++r) q[4 * k + r] = sum[r];
+    }
+}
+
+// The same over the workgroups that share the tile too.  false: the others are not there yet, the workgroup is done.
+__device__ __forceinline__ bool split_join4(const f32x16 (&acc)[2][2], unsigned char* smem, const Split& sp, int tile, int s, int wave, int lane, float (&q)[16]) {
+    join4(acc, smem, wave, lane, q);
     unsigned long long* const p = reinterpret_cast<unsigned long long*>(sp.part) + ((int64_t)tile * sp.n * 4 + wave) * (8 * 64) + lane;
 #pragma unroll
     for (int k = 0; k < 8; ++k)
