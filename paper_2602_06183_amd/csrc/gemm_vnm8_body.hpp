@@ -22,6 +22,11 @@
 //                                                      stage: the four rows that lane (h = lane / 32, r = (lane % 16) / 4) addresses in read j
 // A stage = 64 hidden units = 32 k' = one matrix instruction step per fragment pair; 3 stages.
 //
+// The 64 x 64 tile (few tokens) has one token block, so its stages hold the kept rows only: the loads themselves pick them, half the bytes of the slab from memory and into LDS, and
+// two workgroups a CU (77 KB of LDS; with the slab 126 KB), in launches that are shared with other contractions too.  Their addresses need the offsets first: those of the first
+// three stages come from memory, the others with the batch three stages ahead.  With the slab / kept rows: T = 64, D = 4096, F = 14336 a forward call on packed weights 40.4 / 32.1 us,
+// D = 2048, F = 8192 22.9 / 21.0; steps: T = 512, D = 2624, F = 8000 197 / 160, T = 64, D = 1024, F = 4096 44.3 / 40.4, on codes T = 448, D = 2176, F = 7936 145 / 110.
+//
 // FP8 (the fp8 step): the same kernel on E4M3 codes with v_smfmac_f32_32x32x64_fp8_fp8, out = bf16(alpha * sum).  A stage is 128 hidden
 // units = 64 k' (the instruction's K): the slab is 128 rows x 256 bytes, the survivors' codes fill the same 32 bytes per token and stage,
 // the metadata 8 bytes.  The B fragments are read with ds_read_b64_tr_b8 (inside a group of 16 lanes, lane s supplies 8 consecutive bytes of
@@ -54,11 +59,12 @@ struct G {
     static constexpr int ES = FP8 ? 1 : 2;               // bytes per element of Wk
     static constexpr int SLAB = FP8 ? 128 : 64;         // hidden units per stage
     static constexpr int ROW = TL::BN * ES;              // bytes of a slab row
-    static constexpr int kB = SLAB * ROW;
+    static constexpr bool KEPT = TL::KW > 1;             // the stage holds the kept rows of its one token block only
+    static constexpr int kB = (KEPT ? SLAB / 2 : SLAB) * ROW;
     static constexpr int kA = TL::BT * 32;
     static constexpr int kMt = FP8 ? TL::BT * 8 : TL::BT * 4;
-    static constexpr int kC = TL::WT * (FP8 ? 64 : 32) > 256 ? TL::WT * (FP8 ? 64 : 32) : 256;
-    static constexpr int C_PARTS = kC / 256;             // wave-wide loads of the offsets; every wavefront issues one of them
+    static constexpr int kC = KEPT ? 64 : TL::WT * (FP8 ? 64 : 32) > 256 ? TL::WT * (FP8 ? 64 : 32) : 256;
+    static constexpr int C_PARTS = KEPT ? 1 : kC / 256;             // wave-wide loads of the offsets; every wavefront issues one of them
     static constexpr int kStage = kB + kA + kMt + kC;
     static constexpr int B_LD = kB / 1024 / TL::NW, A_LD = kA / 1024 / TL::NW, M_LD = (kMt / 256 + TL::NW - 1) / TL::NW;    // loads per wave and stage
     static constexpr int LOADS = B_LD + A_LD + M_LD + 1;
@@ -75,7 +81,7 @@ __device__ __forceinline__ void vnm8_gemm_body(unsigned char* __restrict__ smem,
                                                int Ra, int N, int F, int Ttot, uint16_t* __restrict__ out, int64_t ldo,
                                                int tiles_m, int tiles_n, const GemmGroup& grp, float alpha, const Split& split) {
     using GG = G<FP8, TL>;
-    constexpr int kB = GG::kB, kA = GG::kA, kMt = GG::kMt, kStage = GG::kStage, ES = GG::ES, kStages = TL::NST, kLoads = GG::LOADS, KW = TL::KW, FN = TL::FN;
+    constexpr int kB = GG::kB, kA = GG::kA, kMt = GG::kMt, kC = GG::kC, kStage = GG::kStage, ES = GG::ES, kStages = TL::NST, kLoads = GG::LOADS, KW = TL::KW, FN = TL::FN;
     constexpr int BT = TL::BT, BN = TL::BN, ROW = GG::ROW, B_LD = GG::B_LD, A_LD = GG::A_LD, M_LD = GG::M_LD, PB = GG::PIECE, PM = GG::PMASK;
 
     const int tid = threadIdx.x, lane = tid & 63;
@@ -120,7 +126,14 @@ __device__ __forceinline__ void vnm8_gemm_body(unsigned char* __restrict__ smem,
     // piece p of row f sits at p ^ (f % min(8, pieces)).  Chunks past the right edge of Wk are redirected into the first 64 columns.
     const uint64_t w_base = uniform64(Wk);
     constexpr int LPR = ROW / 16, RPL = 1024 / ROW;         // 16-byte slots per slab row, rows per load
-    uint32_t b_lane[B_LD];
+    // KEPT: a load brings the kept rows that the words of the offsets name with one of their bytes, word by word, 128 (FP8: 64) bytes of each: row j RPL + q of the stage is byte j of
+    // word q.  That is the order in which the transposing reads want them, so their addresses do not depend on data.  The pieces of a row are exchanged where that puts the rows
+    // of a read (4; FP8: 8) on different banks.
+    constexpr bool KEPT = GG::KEPT;
+    const int kq = lane / LPR, kf = FP8 ? kq >> 2 & 1 : kq >> 1 & 1;
+    const uint32_t kept_lane = (uint32_t)(8 * (FP8 ? 4 * (kq >> 3) + (kq >> 2 & 1) : 2 * (kq >> 2))) * (uint32_t)ldw * ES + (uint32_t)n0 * ES + (uint32_t)((lane % LPR) ^ (kf * (PB / 16))) * 16;
+    uint32_t b_lane[KEPT ? 1 : B_LD];
+    if constexpr (!KEPT)
 #pragma unroll
     for (int i = 0; i < B_LD; ++i) {
         // (the stage goes into the scalar base: a vector instruction less for every load)
@@ -153,7 +166,7 @@ __device__ __forceinline__ void vnm8_gemm_body(unsigned char* __restrict__ smem,
         m_lane = lane * 4;
         // offsets of the tile's token blocks, 32 (FP8: 64) bytes each: a load brings 256 bytes (slots past the tile's last block repeat it)
         const int words = FP8 ? 16 : 8;
-        int tb = (wt % GG::C_PARTS * 64 + lane) / words;
+        int tb = KEPT ? 0 : (wt % GG::C_PARTS * 64 + lane) / words;
         tb = (i0 >> 6) + (tb < TL::WT ? tb : TL::WT - 1);
         tb = tb < NTB ? tb : NTB - 1;
         c_base = uniform64(cixt);
@@ -161,19 +174,27 @@ __device__ __forceinline__ void vnm8_gemm_body(unsigned char* __restrict__ smem,
     }
     const uint32_t c_kstep = (uint32_t)NTB * (FP8 ? 64u : 32u);
     constexpr uint32_t m_kstep = FP8 ? 512u : 256u;
-    // loads lo .. hi - 1 of a stage's kLoads (compile-time bounds)
-    auto issue = [&](int kt, int stage, int lo, int hi) {
+    // loads lo .. hi - 1 of a stage's kLoads (compile-time bounds).  KEPT: w = the lane's word of the stage's offsets, ahead = the stage whose offsets come with this one's
+    auto issue = [&](int kt, int stage, int lo, int hi, uint32_t w = 0, int ahead = 0) {
         const uint32_t sb = ring_lds + stage * kStage, sa = sb + kB, sm = sa + kA, sc = sm + kMt;
 #pragma unroll
         for (int i = 0; i < B_LD; ++i)
-            if (i >= lo && i < hi) dma16(w_base + (uint64_t)((uint32_t)kt * b_kstep), b_lane[i], sb + (B_LD * wt + i) * 1024);
+            if (i >= lo && i < hi) {
+                if constexpr (KEPT)
+                    dma16(w_base + (uint64_t)((uint32_t)kt * b_kstep + (uint32_t)((FP8 ? 8 * (i >> 1) + 2 * (i & 1) : 4 * (i >> 1) + (i & 1)) * 8) * (uint32_t)ldw * ES),
+                          __umul24((w >> (8 * i)) & 0xFFu, (uint32_t)ldw * ES) + kept_lane, sb + i * 1024);
+                else dma16(w_base + (uint64_t)((uint32_t)kt * b_kstep), b_lane[i], sb + (B_LD * wt + i) * 1024);
+            }
 #pragma unroll
         for (int i = 0; i < A_LD; ++i)
             if (B_LD + i >= lo && B_LD + i < hi) dma16(a_base[i], a_lane + (uint32_t)kt * 1024u, sa + (wt * A_LD + i) * 1024);
 #pragma unroll
         for (int i = 0; i < M_LD; ++i)
             if (B_LD + A_LD + i >= lo && B_LD + A_LD + i < hi) dma4(m_base[i], m_lane + (uint32_t)kt * m_kstep, sm + ((wt * M_LD + i) % (kMt / 256)) * 256);
-        if (kLoads - 1 >= lo && kLoads - 1 < hi) dma4(c_base, c_lane + (uint32_t)kt * c_kstep, sc + wt % GG::C_PARTS * 256);
+        if (kLoads - 1 >= lo && kLoads - 1 < hi) {
+            if constexpr (KEPT) { if (lane < kC / 4) dma4(c_base, c_lane + (uint32_t)ahead * c_kstep, sc); }      // (bf16: 8 words, twice)
+            else dma4(c_base, c_lane + (uint32_t)kt * c_kstep, sc + wt % GG::C_PARTS * 256);
+        }
     };
 
     // ---- per-lane LDS offsets of the fragment reads (inside a stage).  A wave owns one token block (64 tokens) x 32 FN output columns: the
@@ -193,6 +214,11 @@ __device__ __forceinline__ void vnm8_gemm_body(unsigned char* __restrict__ smem,
     const int r4 = (lane & 15) >> 2, p8 = (lane & 15) >> 1, g = lane >> 4;
     const int c_off = kB + kA + kMt + (FP8 ? 64 * tbw + (lh * 8 + p8) * 4 : 32 * tbw + (lh * 4 + r4) * 4);
     const uint32_t b_lane0 = FP8 ? (uint32_t)((4 * lh + (p8 >> 2)) * 8 * ROW + ((g & 1) << 4) + ((lane & 1) << 3)) : (uint32_t)(2 * lh * 8 * ROW + ((g & 1) << 5) + ((lane & 3) << 3));
+    // KEPT: row q = 4 h + r4 (FP8: 8 h + p8) of each of the four loads, both halves of the columns
+    const int rq = FP8 ? lh * 8 + p8 : lh * 4 + r4, rf = FP8 ? rq >> 2 & 1 : rq >> 1 & 1;
+    const uint32_t kept_row = (uint32_t)(rq * ROW + (FP8 ? ((g & 1) << 4) + ((lane & 1) << 3) : ((g & 1) << 5) + ((lane & 3) << 3)));
+    const uint32_t kept_off[2] = {kept_row + rf * PB, kept_row + (rf ^ 1) * PB};
+    const int w_off = kB + kA + kMt + kq * 4;
     constexpr int NP = GG::NP;
     static_assert(NP <= 8, "a byte holds 8 pieces x 8 rows");
     constexpr auto entry = [](uint32_t c) { return c * NP | (c & (NP - 1)); };
@@ -213,7 +239,7 @@ __device__ __forceinline__ void vnm8_gemm_body(unsigned char* __restrict__ smem,
     struct BPair { union { s16x4 q[4]; v2i q8[4]; bf16x16 v; i32x8 v8; } b[HB]; };
     struct AFrags { Frag8 a[2]; int idx[2]; uint32_t cw; };
     auto read_a = [&](AFrags& f, const unsigned char* st) {
-        f.cw = *reinterpret_cast<const uint32_t*>(st + c_off);
+        if (!KEPT) f.cw = *reinterpret_cast<const uint32_t*>(st + c_off);
 #pragma unroll
         for (int a2 = 0; a2 < 2; ++a2) {
             f.a[a2].u = *reinterpret_cast<const uint4*>(st + a_off + a2 * 1024);
@@ -223,6 +249,7 @@ __device__ __forceinline__ void vnm8_gemm_body(unsigned char* __restrict__ smem,
     // the four addresses of a stage's reads, for its first fragment
     struct BAddr { uint32_t j[4]; };
     auto address_b = [&](BAddr& ad, int stage, uint32_t cw) {
+        if constexpr (KEPT) { ad.j[0] = ring_lds + (uint32_t)(stage * kStage) + kept_off[0]; ad.j[1] = ring_lds + (uint32_t)(stage * kStage) + kept_off[1]; return; }
         const uint32_t e = __builtin_amdgcn_perm(tab_hi, tab_lo, cw), base = ring_lds + (uint32_t)(stage * kStage) + b_lane0;
 #pragma unroll
         for (int j = 0; j < 4; ++j) ad.j[j] = base + ((e >> (8 * j)) & 0xFFu) * (uint32_t)PB;
@@ -234,7 +261,7 @@ __device__ __forceinline__ void vnm8_gemm_body(unsigned char* __restrict__ smem,
             const int cb = FP8 ? 8 * (j >> 1) + 2 * (j & 1) : 4 * (j >> 1) + (j & 1);
 #pragma unroll
             for (int q = 0; q < HB; ++q) {
-                const uint32_t at = (ad.j[j] ^ (uint32_t)((HB * half + q) * PB)) + (uint32_t)(cb * kBlk);
+                const uint32_t at = KEPT ? ad.j[half] + (uint32_t)(j * 1024) : (ad.j[j] ^ (uint32_t)((HB * half + q) * PB)) + (uint32_t)(cb * kBlk);
                 if (FP8) f.b[q].q8[j] = __builtin_amdgcn_ds_read_tr8_b64_v2i32((lds_v2i*)at);
                 else     f.b[q].q[j] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)at);
             }
@@ -250,10 +277,18 @@ __device__ __forceinline__ void vnm8_gemm_body(unsigned char* __restrict__ smem,
 
     const int nk = (ks1 - ks0 - kg + KW - 1) / KW;
     auto step_of = [&](int kt) { return ks0 + kg + kt * KW; };
+    // KEPT: the offsets of a tile come with the batch three before it, so they are read from its stage just before the stage is refilled; those of the first three from memory
+    auto ahead_of = [&](int kt) { return step_of(kt + kStages < nk ? kt + kStages : nk - 1); };
+    uint32_t w = 0;
     if (nk > 0) {
+    uint32_t first[kStages];
+    if constexpr (KEPT)
+#pragma unroll
+        for (int p = 0; p < kStages; ++p)
+            first[p] = *reinterpret_cast<const uint32_t*>(cixt + (c_lane + (uint32_t)((kq - lane % (FP8 ? 16 : 8)) * 4)) + (uint32_t)step_of(p < nk ? p : nk - 1) * c_kstep);
 #pragma unroll
     for (int p = 0; p < kStages; ++p)
-        if (p < nk) issue(step_of(p), p, 0, p < kStages - 1 ? kLoads : kLoads * 2 / 4);           // (the rest of the last one's loads are the first step's)
+        if (p < nk) issue(step_of(p), p, 0, p < kStages - 1 ? kLoads : kLoads * 2 / 4, KEPT ? first[p] : 0u, KEPT ? ahead_of(p) : 0);           // (the rest of the last one's loads are the first step's)
     if (nk >= kStages) wait_vmcnt<(kStages - 2) * kLoads + kLoads * 2 / 4>();
     else wait_vmcnt<0>();
     if (KW == 1) __syncthreads();
@@ -265,17 +300,21 @@ __device__ __forceinline__ void vnm8_gemm_body(unsigned char* __restrict__ smem,
     address_b(ad, 0, A0.cw);
     read_b(P, ad, 0);
     int stage = 0;
+    if (KEPT) w = first[kStages - 1];
     // two stages per trip so that the A fragment buffers alternate without copies.  The loads of a refill are spread from the barrier that frees its stage
     // to the next one, and the last steps load nothing (gemm_v2_body.hpp says why).  t: the tile that is loaded, s: its stage; full: both of a step's exist.
-#define ISSUE(t, s, i) if (full.value || (t) < nk) issue(step_of(t), s, kLoads * (i) / 4, kLoads * ((i) + 1) / 4)
+#define ISSUE(t, s, i) if (full.value || (t) < nk) issue(step_of(t), s, kLoads * (i) / 4, kLoads * ((i) + 1) / 4, w, KEPT ? ahead_of(t) : 0)
     auto step = [&](auto full, int kt, AFrags& cur, AFrags& nxt_a) {
         const int next_stage = (stage + 1 == kStages) ? 0 : stage + 1, last_stage = stage == 0 ? kStages - 1 : stage - 1;
         const unsigned char* sn = ring + next_stage * kStage;
+        uint32_t w_next = 0;
+        if (KEPT) { w_next = *reinterpret_cast<const uint32_t*>(ring + stage * kStage + w_off); SB(); }
         mma_half(cur, P, 0, 0); SB();
         ISSUE(kt + kStages - 1, last_stage, 2); SB();
         mma_half(cur, P, 0, 1); SB();
         read_b(Q, ad, 1); SB();
         ISSUE(kt + kStages - 1, last_stage, 3); SB();
+        w = w_next;
         // Q has arrived and this wave's part of tile kt + 1 has landed; after the barrier every wave is done reading this stage
         if (full.value || kt + kStages - 1 < nk) wait_vmcnt_lgkm0<(kStages - 2) * kLoads>();
         else wait_vmcnt_lgkm0<0>();

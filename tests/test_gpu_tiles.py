@@ -396,3 +396,26 @@ def test_float32_weight_gradients_with_three_workgroups_a_cu():
     step.backward(dev[1], dev[4])
     for a, b in zip(plain[2:], (step.dW1, step.dW2)):
         assert torch.equal(a, b.bfloat16())
+
+
+@pytest.mark.parametrize("fp8", [False, True])
+@pytest.mark.parametrize("T,N,F", [
+    (64, 64, 128), (64, 192, 384),          # fewer stages than wavefronts; a wavefront with one stage, others with none
+    (64, 128, 768), (64, 64, 1024), (64, 64, 1152),         # rings that are just full, and one stage more, for some of the wavefronts
+    (192, 320, 2176),                       # three token blocks with selections of their own
+    (64, 64, 9216),                         # contractions shared by workgroups
+])
+def test_activation_contractions_on_kept_rows(fp8, T, N, F):
+    """Eqs. (3), (7) on 64 tiles.  Small integers (codes: with scales of 1): every sum is exact in float32, so the results are equal to the bit."""
+    rng = np.random.default_rng(T + N + F)
+    y1 = bf16_bits_from_f32(rng.integers(-2, 3, (T, F)).astype(np.float32))
+    W = bf16_bits_from_f32(rng.integers(-2, 3, (N, F)).astype(np.float32))
+    packed = oracle.sqrelu_vnm_compress(y1, 64, 8)
+    want = (to_dev(oracle.vnm_decompress(*packed, 64, 8)).float() @ to_dev(W).float().t()).bfloat16()
+    if fp8:
+        codes = sffn.sqrelu_vnm_compress_fp8(to_dev(y1), 1.0, 64, 8)
+        assert torch.equal(sffn.vnm_spmm_fp8(*codes, 1.0, sffn.quantize_fp8(to_dev(np.ascontiguousarray(W.T)), 1.0), 1.0, 1, 64, 8), want)
+        return
+    dev = [to_dev(x) for x in packed]
+    assert torch.equal(sffn.vnm_spmm(*dev, to_dev(W), 0, 64, 8), want)
+    assert torch.equal(sffn.vnm_spmm(*dev, to_dev(np.ascontiguousarray(W.T)), 1, 64, 8), want)
