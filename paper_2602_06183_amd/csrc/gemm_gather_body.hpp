@@ -449,6 +449,7 @@ struct GatherUnit {
         vnm_gather_body<TL>(smem, pid, n_pid, (const uint16_t*)a.a_vals, a.a_meta, a.colidx, (const uint16_t*)a.Wk, a.ldw, a.N, a.Kc, a.logM, a.T >> 6, a.tiles_n, a.out, a.ldo, a.grp, a.split);
     }
     static unsigned count(const Args& a) { return (unsigned)((a.T >> 6) * ((a.N + TL::BN - 1) / TL::BN) * a.split.n); }
+    static int stages(const Args& a) { return a.Kc / 64 / (TL::KW * a.split.n); }      // of a tile, a wavefront's (wgrad_first)
     static Args args(Args a) { a.tiles_n = (a.N + TL::BN - 1) / TL::BN; return a; }
 };
 using GatherUnit256 = GatherUnit<GTile<4, 2, 1>>;      // 64 tokens x 256 columns, two workgroups per CU
@@ -460,6 +461,7 @@ struct GatherFp8Unit {
         vnm_gather_fp8_body(smem, pid, n_pid, (const uint8_t*)a.a_vals, a.a_meta, a.colidx, (const uint8_t*)a.Wk, a.ldw, a.N, a.Kc, a.logM, a.T >> 6, a.tiles_n, a.alpha, a.out, a.ldo, a.grp);
     }
     static unsigned count(const Args& a) { return (unsigned)((a.T >> 6) * ((a.N + 255) / 256)); }
+    static int stages(const Args& a) { return a.Kc / 128; }
     static Args args(Args a) { a.tiles_n = (a.N + 255) / 256; return a; }
 };
 

@@ -391,6 +391,7 @@ struct Vnm8Unit {
         vnm8_gemm_body<FP8, TL>(smem, pid, n_pid, a.vcb, a.mcb, a.cixt, a.Wk, a.ldw, a.T, a.N, a.F, a.T, a.out, a.ldo, a.tiles_m, a.tiles_n, a.grp, a.alpha, a.split);
     }
     static unsigned count(const Args& a) { return vnm8_tiles(a.T, a.N, a.grp, TL::BT, TL::BN) * (unsigned)a.split.n; }
+    static int stages(const Args& a) { return a.F / (FP8 ? 128 : 64) / (TL::KW * a.split.n); }      // of a tile, a wavefront's (wgrad_first)
     static Args args(Args a) { a.tiles_m = (a.T + TL::BT - 1) / TL::BT; a.tiles_n = (a.N + TL::BN - 1) / TL::BN; return a; }
 };
 template <bool FP8> using Vnm8Unit512 = Vnm8Unit<FP8, VTile<8, 1, 4, 3, 1>>;

@@ -34,6 +34,9 @@ struct WTile {
     static constexpr int A_LD = BM / 32 / NW, B_LD = kBBytes / 1024 / NW, kLoads = 1 + 2 * A_LD + B_LD;      // LDS-DMA loads per wavefront per stage
     static constexpr int EPI = NW * 64 * (64 * 4 + 16) / 2 > NW * 64 * (64 * 2 + 16) ? NW * 64 * (64 * 4 + 16) / 2 : NW * 64 * (64 * 2 + 16);   // wgrad_store's staging
     static constexpr int BYTES = KW * NST * kStage > EPI ? KW * NST * kStage : EPI;
+    // on codes a stage of the shared tile (KW > 1) is one token block, half of everything
+    static constexpr int k8A = kAHalf, k8B = kBHalf, k8Stage = k8A + k8B + NW * 256, B8_LD = k8B / 1024 / NW, k8Loads = 1 + A_LD + B8_LD;
+    static constexpr int BYTES8 = KW == 1 ? BYTES : KW * NST * k8Stage > EPI ? KW * NST * k8Stage : EPI;
 };
 
 // Which of the four rows of zeros a lane reads for a hidden unit that is not kept.  A ds_read_b128 is served in phases of 16 lanes, and a phase is
@@ -47,7 +50,7 @@ __device__ __forceinline__ int zero_lane(int l32) { return (l32 & 4) ? 0 : 3 * 6
 template <class TL, class V, int FM, int FN>
 __device__ __forceinline__ bool wgrad_join(V (&acc)[FM][FN], unsigned char* smem, int kg, int lane) {
     constexpr int R = sizeof(V) / 4, PART = FM * FN * R * 256;
-    static_assert((TL::KW - 1) * PART <= TL::BYTES, "partial sums must fit in the main-loop LDS");
+    static_assert((TL::KW - 1) * PART <= TL::BYTES && (TL::KW - 1) * PART <= TL::BYTES8, "partial sums must fit in the main-loop LDS");
     if (kg > 0) {
         float* p = reinterpret_cast<float*>(smem + (kg - 1) * PART) + lane;
 #pragma unroll
@@ -294,6 +297,9 @@ __device__ __forceinline__ void wgrad_vnm_body(unsigned char* __restrict__ smem,
     // out of registers (on codes T = N = 8192, F = 28672 1270 -> 1660 us).
     constexpr bool REPEAT = FM == 8;
     auto tile_of = [&](int t) { return step_of(REPEAT && t >= nk ? nk - 1 : t); };
+    // (Nothing is in flight here, but the compiler, which does not see the ring's loads, may believe it of other units' loads to the same registers and wait in every step: as the
+    // second unit of three, T = 3072, N = 448, F = 1792, the launch took 43 us, 25 without those waits.)
+    wait_vmcnt<0>();
     if (nk > 0) {
         // rows of zeros behind both half-tiles of every stage (never touched by the DMA)
         constexpr int ZW = TL::kZeros / 4;
@@ -399,17 +405,18 @@ template <bool OUT_I_CONTIG, bool ACC32, class TL>
 __device__ __forceinline__ void wgrad_vnm_fp8_body(unsigned char* __restrict__ smem, int pid, int n_pid, const uint16_t* __restrict__ atc, const uint8_t* __restrict__ kmask,
                                                            const uint16_t* __restrict__ G, int F, int N, int Ttot, float alpha,
                                                            uint16_t* __restrict__ out, int64_t ldo, int tiles_m, int tiles_n, const GemmGroup& grp) {
-    constexpr int BM = TL::BM, BN = TL::BN, WM = TL::WM, WN = 64, FM = WM / 16, FN = 4, KW = TL::KW;
+    constexpr int BM = TL::BM, BN = TL::BN, WM = TL::WM, WN = 64, FM = WM / 16, FN = 4;
+    static_assert(TL::KW == 1, "the shared tile has a kernel of its own");
     constexpr int kStages = TL::NST, kStage = TL::kStage, kAHalf = TL::kAHalf, kABytes = TL::kABytes, kBHalf = TL::kBHalf, kBBytes = TL::kBBytes, kLoads = TL::kLoads;
     constexpr int A_LD = TL::A_LD, B_LD = TL::B_LD;
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int kg = KW > 1 ? wave : 0, wt = KW > 1 ? 0 : wave;       // share of the contraction / place in the tile
+    const int wt = wave;                          // place in the tile
     const int wm = wt / TL::WVN, wn = wt % TL::WVN;
     const int l16 = lane & 15, lq = lane >> 4, blk = lq >> 1;
-    unsigned char* const ring = smem + kg * (kStages * kStage);
-    const uint32_t ring_lds = lds_addr(smem) + kg * (kStages * kStage);
+    unsigned char* const ring = smem;
+    const uint32_t ring_lds = lds_addr(smem);
     int L = xcd_run(pid, n_pid);
     int k_base = 0, K = Ttot;                     // grouped: every expert contracts over its own token segment
     if (grp.n) {
@@ -512,12 +519,14 @@ __device__ __forceinline__ void wgrad_vnm_fp8_body(unsigned char* __restrict__ s
         acc[a][b] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(A[a & 1].q, B[b].q, acc[a][b], 0, 0, 0, 0x7F, 0, 0x7F);   // fp8 x fp8, scales 2^0
     };
 #define SB() __builtin_amdgcn_sched_barrier(0)
-    const int ns = (nblk + 1) / 2, nk = KW == 1 ? ns : (ns - kg + KW - 1) / KW;                // 0 for an expert without tokens: its gradient is zero
-    auto step_of = [&](int kt) { return KW == 1 ? kt : kg + kt * KW; };
+    const int nk = (nblk + 1) / 2;                // 0 for an expert without tokens: its gradient is zero
     // The last steps load nothing (gemm_v2_body.hpp says why), except on the 256 tile, whose last tile is loaded again in their place: a second copy of its step, without loads, runs
     // out of registers (on codes T = N = 8192, F = 28672 1270 -> 1660 us).
     constexpr bool REPEAT = FM == 8;
-    auto tile_of = [&](int t) { return step_of(REPEAT && t >= nk ? nk - 1 : t); };
+    auto tile_of = [&](int t) { return REPEAT && t >= nk ? nk - 1 : t; };
+    // (Nothing is in flight here, but the compiler, which does not see the ring's loads, may believe it of other units' loads to the same registers and wait in every step: as the
+    // second unit of three, T = 3072, N = 448, F = 1792, the launch took 43 us, 25 without those waits.)
+    wait_vmcnt<0>();
     if (nk > 0) {
         constexpr int ZW = TL::kZeros / 4;
         for (int i = wt * 64 + lane; i < kStages * 2 * ZW; i += TL::NW * 64)
@@ -527,10 +536,9 @@ __device__ __forceinline__ void wgrad_vnm_fp8_body(unsigned char* __restrict__ s
             if (REPEAT || p < nk) issue(tile_of(p), p, 0, p < kStages - 1 ? kLoads : kLoads * 2 / 4);           // (the rest of the last one's loads are the first step's)
         if (REPEAT || nk >= kStages) wait_vmcnt<(kStages - 2) * kLoads + kLoads * 2 / 4>();
         else wait_vmcnt<0>();
-        if (KW == 1) __syncthreads();
-        else { wave_lds_sync(); asm volatile("" ::: "memory"); }
+        __syncthreads();
         lookup_read(0);
-        drop_second(step_of(0));
+        drop_second(0);
 #pragma unroll
         for (int a = 0; a < FM; ++a) lookup(0, a);
         read_a(A[0], 0);
@@ -560,11 +568,10 @@ __device__ __forceinline__ void wgrad_vnm_fp8_body(unsigned char* __restrict__ s
                     // the next stage's masks were the first load of its batch: all but kLoads - 1 of that batch and the batch after it may still be in flight
                     if (full.value || kt + kStages - 1 < nk) wait_vmcnt<(kStages - 2) * kLoads + kLoads - 1>();
                     else wait_vmcnt<0>();
-                    if (KW > 1) asm volatile("" ::: "memory");
                     lookup_read(next_stage); SB();
                 }
                 if (a == FM - 3) {
-                    drop_second(step_of(kt + 1));
+                    drop_second(kt + 1);
 #pragma unroll
                     for (int r = 0; r < FM; ++r) lookup(next_stage, r);
                     SB();
@@ -573,8 +580,7 @@ __device__ __forceinline__ void wgrad_vnm_fp8_body(unsigned char* __restrict__ s
                     // this wavefront's reads of the stage are here, and its part of tile kt + 1
                     if (full.value || kt + kStages - 1 < nk) wait_vmcnt_lgkm0<(kStages - 2) * kLoads>();
                     else wait_vmcnt_lgkm0<0>();
-                    if (KW == 1) __builtin_amdgcn_s_barrier();
-                    else asm volatile("" ::: "memory");
+                    __builtin_amdgcn_s_barrier();
                     SB();
                     re_kt = tile_of(kt + kStages); re_stage = stage;
                     read_a(A[0], 0); SB();
@@ -593,19 +599,208 @@ __device__ __forceinline__ void wgrad_vnm_fp8_body(unsigned char* __restrict__ s
     }
 #undef SB
     __syncthreads();
-    if (KW > 1 && !wgrad_join<TL>(acc, smem, kg, lane)) return;
     wgrad_store<OUT_I_CONTIG, ACC32, TL>(acc, alpha, smem, wt, lane, i0, j0, F, N, out, ldo);
+}
+
+// The 64 tile on codes: one token block a stage and an instruction (v_mfma_scale_f32_32x32x64_f8f6f4, lane l: k 32 (l / 32) .. + 31 of row / column l % 32).  Few tiles and long
+// contractions are bound by the chain of a step, not by power, and with two blocks a stage (156,672 bytes for 79,872) launches that hold such tiles run one workgroup a CU: fp8
+// steps T = 3968, D = 384, F = 1152 50 us for 46.5, T = 13952, D = 512, F = 1792 154 for 143.  (One block a stage on the 16 x 16 x 128 instruction, half of it zeros: T = 4224,
+// D = 256, F = 768 46 for 41.)  A's fragments are read one row ahead, G's one step ahead.
+template <bool OUT_I_CONTIG, bool ACC32, class TL>
+__device__ __forceinline__ void wgrad_vnm_fp8_shared_body(unsigned char* __restrict__ smem, int pid, int n_pid, const uint16_t* __restrict__ atc, const uint8_t* __restrict__ kmask,
+                                                           const uint16_t* __restrict__ G, int F, int N, int Ttot, float alpha,
+                                                           uint16_t* __restrict__ out, int64_t ldo, int tiles_m, int tiles_n, const GemmGroup& grp) {
+    constexpr int BM = TL::BM, BN = TL::BN, FM = 2, FN = 2, KW = TL::KW;
+    static_assert(KW == 4 && BM == 64 && BN == 64, "a 64 x 64 tile of four wavefronts");
+    constexpr int kStages = TL::NST, kStage = TL::k8Stage, k8A = TL::k8A, k8B = TL::k8B, kLoads = TL::k8Loads, A_LD = TL::A_LD, B_LD = TL::B8_LD;
+
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int kg = wave;                          // share of the contraction
+    const int l32 = lane & 31, lh = lane >> 5;
+    unsigned char* const ring = smem + kg * (kStages * kStage);
+    const uint32_t ring_lds = lds_addr(smem) + kg * (kStages * kStage);
+    int L = xcd_run(pid, n_pid);
+    int k_base = 0, K = Ttot;                     // grouped: every expert contracts over its own token segment
+    if (grp.n) {
+        const int per = tiles_m * tiles_n, e = uniform(L / per);
+        L -= e * per;
+        k_base = grp.seg[e];
+        K = grp.seg[e + 1] - k_base;
+        out += e * grp.out_stride * (ACC32 ? 2 : 1);          // (float32 elements are two uint16_t wide)
+    }
+    int tm, tn;
+    band_tile(L, tiles_m, tiles_n, SFFN_TILE_GROUP, tm, tn);
+    const int i0 = tm * BM, j0 = tn * BN;
+    const int KC = Ttot / 64;                     // 64-token chunks (64 bytes) per row of the blocked operands
+
+    uint64_t a_base[A_LD], b_base[B_LD], c_base;
+    const int rb = lane >> 2;
+    const uint32_t blk_lane = (uint32_t)(rb * 32 + ((lane & 3) ^ ((rb >> 2) & 3)) * 8) * 2;   // chunk swizzle, as in the bf16 kernel
+    {
+#pragma unroll
+        for (int n = 0; n < A_LD; ++n) {
+            int cr = i0 / 2 + n * 16; cr = cr < F / 2 ? cr : F / 2 - 16;
+            a_base[n] = uniform64(atc + (((int64_t)(cr >> 4) * KC + k_base / 64) << 9));
+        }
+#pragma unroll
+        for (int n = 0; n < B_LD; ++n) {
+            int gr = j0 + n * 16; gr = gr < N ? gr : N - 16;
+            b_base[n] = uniform64(G + (((int64_t)(gr >> 4) * KC + k_base / 64) << 9));
+        }
+        c_base = uniform64(kmask + (int64_t)(k_base / 64) * (F / 8));
+    }
+    uint32_t c_lane;
+    {
+        int g = i0 / 8 + 4 * (lane & 7); g = g < F / 8 ? g : F / 8 - 4;
+        c_lane = (uint32_t)g;
+    }
+    const uint32_t c_kstep = (uint32_t)(F / 8);
+    auto issue = [&](int kt, int stage, int lo, int hi) {
+        const uint32_t sa = ring_lds + stage * kStage;
+        const uint32_t o = blk_lane + (uint32_t)kt * 1024;
+        if (lo <= 0 && hi > 0) dma4(c_base, c_lane + (uint32_t)kt * c_kstep, sa + k8A + k8B);     // first: the look-up wants it earliest
+#pragma unroll
+        for (int n = 0; n < A_LD; ++n)
+            if (1 + n >= lo && 1 + n < hi) dma16(a_base[n], o, sa + n * 1024);
+#pragma unroll
+        for (int n = 0; n < B_LD; ++n)
+            if (1 + A_LD + n >= lo && 1 + A_LD + n < hi) dma16(b_base[n], o, sa + k8A + n * 1024);
+    };
+
+    // fragment reads: a lane wants the 32 bytes k 32 lh .. + 31 of its row = 16-byte chunks 2 lh, 2 lh + 1 (slot = chunk ^ ((row >> 2) & 3))
+    int b_off[FN];
+#pragma unroll
+    for (int b = 0; b < FN; ++b) {
+        const int row = b * 32 + l32;
+        b_off[b] = k8A + row * 64 + (((2 * lh) ^ ((row >> 2) & 3)) << 4);
+    }
+    int a_off[FM], a_next[FM];
+    const uint32_t col = l32 & 7, below = (1u << col) - 1u;
+    const int zero_row = TL::kZero + zero_lane(l32) + (((2 * lh) ^ (l32 >> 3)) << 4);
+    uint32_t mk[FM];
+    auto lookup_read = [&](int stage) {
+        const unsigned char* sc = ring + stage * kStage + k8A + k8B;
+#pragma unroll
+        for (int a = 0; a < FM; ++a) mk[a] = sc[a * 4 + (l32 >> 3)];
+    };
+    auto lookup = [&](int stage) {
+        const int sa = stage * kStage;
+#pragma unroll
+        for (int a = 0; a < FM; ++a) {
+            const int gl = a * 4 + (l32 >> 3);
+            const int row = gl * 4 + __builtin_popcount(mk[a] & below);                   // (row >> 2) & 3 == l32 >> 3
+            a_next[a] = sa + (((mk[a] >> col) & 1u) ? row * 64 + (((2 * lh) ^ (l32 >> 3)) << 4) : zero_row);
+        }
+    };
+    auto read_a = [&](Frag16& f, int off) {
+        f.u[0] = *reinterpret_cast<const uint4*>(ring + off);
+        f.u[1] = *reinterpret_cast<const uint4*>(ring + (off ^ 16));
+    };
+    auto read_b = [&](Frag16& f, const unsigned char* st, int b) {
+        f.u[0] = *reinterpret_cast<const uint4*>(st + b_off[b]);
+        f.u[1] = *reinterpret_cast<const uint4*>(st + (b_off[b] ^ 16));
+    };
+    f32x16 acc[FM][FN];
+#pragma unroll
+    for (int a = 0; a < FM; ++a)
+#pragma unroll
+        for (int b = 0; b < FN; ++b)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[a][b][r] = 0.0f;
+    auto mma_row = [&](const Frag16& fa, const Frag16 (&fb)[FN], int a) {
+#pragma unroll
+        for (int b = 0; b < FN; ++b)
+            acc[a][b] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(fa.q, fb[b].q, acc[a][b], 0, 0, 0, 0x7F, 0, 0x7F);   // fp8 x fp8, scales 2^0
+    };
+#define SB() __builtin_amdgcn_sched_barrier(0)
+    const int nk = (K / 64 - kg + KW - 1) / KW;                // 0 for an expert without tokens: its gradient is zero
+    auto step_of = [&](int kt) { return kg + kt * KW; };
+    wait_vmcnt<0>();                              // (see the bf16 kernel)
+    if (nk > 0) {
+        constexpr int ZW = TL::kZeros / 4;
+        for (int i = lane; i < kStages * ZW; i += 64) *reinterpret_cast<uint32_t*>(ring + i / ZW * kStage + TL::kZero + i % ZW * 4) = 0u;   // the rows of zeros
+#pragma unroll
+        for (int p = 0; p < kStages; ++p) issue(step_of(p < nk ? p : nk - 1), p, 0, kLoads);
+        wait_vmcnt<(kStages - 1) * kLoads>();
+        wave_lds_sync();
+        asm volatile("" ::: "memory");
+        Frag16 A0, A1, B0[FN], B1[FN];
+        lookup_read(0);
+        lookup(0);
+#pragma unroll
+        for (int a = 0; a < FM; ++a) a_off[a] = a_next[a];
+        read_a(A0, a_off[0]);
+#pragma unroll
+        for (int b = 0; b < FN; ++b) read_b(B0[b], ring, b);
+        int stage = 0;
+        // One step = one token block; two steps per loop trip so that the two G fragment sets alternate by name.
+        int re_kt = step_of(kStages - 1 < nk ? kStages - 1 : nk - 1), re_stage = kStages - 1;
+#define ISSUE(i) issue(re_kt, re_stage, kLoads * (i) / 2, kLoads * ((i) + 1) / 2)
+        auto step = [&](int kt, Frag16 (&Bc)[FN], Frag16 (&Bn)[FN]) {
+            const int next_stage = (stage + 1 == kStages) ? 0 : stage + 1;
+            const unsigned char* sn = ring + next_stage * kStage;
+            read_a(A1, a_off[1]); SB();
+            // the next block's mask bytes were the first load of its batch
+            wait_vmcnt<(kStages - 2) * kLoads + kLoads - 1>();
+            asm volatile("" ::: "memory");
+            lookup_read(next_stage); SB();
+            mma_row(A0, Bc, 0); SB();
+            wait_vmcnt_lgkm0<(kStages - 2) * kLoads>();      // my reads of this stage are done, block kt + 1 has landed (this wavefront's part)
+            asm volatile("" ::: "memory");
+            SB();
+            re_kt = step_of((kt + kStages < nk) ? kt + kStages : nk - 1); re_stage = stage;
+            ISSUE(0); SB();
+            lookup(next_stage); SB();
+#pragma unroll
+            for (int a = 0; a < FM; ++a) a_off[a] = a_next[a];
+            read_a(A0, a_off[0]);
+#pragma unroll
+            for (int b = 0; b < FN; ++b) read_b(Bn[b], sn, b);
+            SB();
+            mma_row(A1, Bc, 1); SB();
+            ISSUE(1); SB();
+            stage = next_stage;
+        };
+        int kt = 0;
+        for (; kt + 1 < nk; kt += 2) { step(kt, B0, B1); step(kt + 1, B1, B0); }
+        if (kt < nk) step(kt, B0, B1);
+#undef ISSUE
+        wait_vmcnt<0>();
+    }
+#undef SB
+    __syncthreads();
+    if (!wgrad_join<TL>(acc, smem, kg, lane)) return;
+    // four rows of a column at a time to the lanes that wgrad_store expects them in
+    f32x4* const quad = reinterpret_cast<f32x4*>(smem);          // [row / 4][column]
+#pragma unroll
+    for (int a = 0; a < FM; ++a)
+#pragma unroll
+        for (int b = 0; b < FN; ++b)
+#pragma unroll
+            for (int g = 0; g < 4; ++g)
+                quad[(8 * a + 2 * g + lh) * 64 + 32 * b + l32] = f32x4{acc[a][b][4 * g], acc[a][b][4 * g + 1], acc[a][b][4 * g + 2], acc[a][b][4 * g + 3]};
+    wave_lds_sync();
+    f32x4 sum[4][4];
+#pragma unroll
+    for (int a = 0; a < 4; ++a)
+#pragma unroll
+        for (int b = 0; b < 4; ++b) sum[a][b] = quad[(4 * a + (lane >> 4)) * 64 + 16 * b + (lane & 15)];
+    wave_lds_sync();
+    wgrad_store<OUT_I_CONTIG, ACC32, TL>(sum, alpha, smem, 0, lane, i0, j0, F, N, out, ldo);
 }
 
 template <bool FP8, bool OUT_I_CONTIG, bool ACC32, class TL>
 struct WgradUnit {
     using Args = WgradArgs;
-    static constexpr int THREADS = TL::THREADS, LDS = TL::BYTES;
+    static constexpr int THREADS = TL::THREADS, LDS = FP8 ? TL::BYTES8 : TL::BYTES;
     static __device__ __forceinline__ void run(unsigned char* smem, int pid, int n_pid, const Args& a) {
-        if constexpr (FP8) wgrad_vnm_fp8_body<OUT_I_CONTIG, ACC32, TL>(smem, pid, n_pid, a.atc, a.kmask, a.G, a.F, a.N, a.T, a.alpha, a.out, a.ldo, a.tiles_m, a.tiles_n, a.grp);
+        if constexpr (FP8 && TL::KW > 1) wgrad_vnm_fp8_shared_body<OUT_I_CONTIG, ACC32, TL>(smem, pid, n_pid, a.atc, a.kmask, a.G, a.F, a.N, a.T, a.alpha, a.out, a.ldo, a.tiles_m, a.tiles_n, a.grp);
+        else if constexpr (FP8) wgrad_vnm_fp8_body<OUT_I_CONTIG, ACC32, TL>(smem, pid, n_pid, a.atc, a.kmask, a.G, a.F, a.N, a.T, a.alpha, a.out, a.ldo, a.tiles_m, a.tiles_n, a.grp);
         else               wgrad_vnm_body<OUT_I_CONTIG, ACC32, TL>(smem, pid, n_pid, a.atc, a.kmask, a.G, a.F, a.N, a.T, a.out, a.ldo, a.tiles_m, a.tiles_n, a.grp);
     }
     static unsigned count(const Args& a) { return (unsigned)((a.F + TL::BM - 1) / TL::BM * ((a.N + TL::BN - 1) / TL::BN) * (a.grp.n ? a.grp.n : 1)); }
+    static int stages(const Args& a) { return a.T / (FP8 && TL::KW == 1 ? 128 : 64) / (TL::KW * (a.grp.n ? a.grp.n : 1)); }      // of a tile, a wavefront's, on average (wgrad_first)
     static Args args(Args a) { a.tiles_m = (a.F + TL::BM - 1) / TL::BM; a.tiles_n = (a.N + TL::BN - 1) / TL::BN; return a; }
 };
 template <bool FP8, bool OUT_I_CONTIG, bool ACC32> using WgradUnit256 = WgradUnit<FP8, OUT_I_CONTIG, ACC32, WTile<2, 4, 128, 3, 1>>;

@@ -9,7 +9,7 @@ template <class V, bool ACC32, class W2, class W1>
 static hipError_t pick(int what, const Vnm8Args* v, const GemmV2Args* g, const WgradArgs& w, hipStream_t s) {
     using G = GemmV2Unit<true, true, 2, true, false, TileSel<true, 2>::T128>;
     if constexpr (ACC32) if (what == kMixForwardTail) return hipErrorInvalidValue;
-    if constexpr (ACC32) return what == kMixBackwardHead ? launch_units<W2, G>(s, w, *g) : launch_units<V, W1>(s, *v, w);
+    if constexpr (ACC32) return what == kMixBackwardHead ? launch_units<W2, G>(s, w, *g) : launch_units<V, W1>(s, *v, w, wgrad_first<W1, V>(*v, w));
     else return launch_mix<V, G, W2, W1>(what, v, g, w, s);
 }
 template <class V, bool ACC32>

@@ -7,7 +7,7 @@ namespace sffn {
 template <class V, int EPI, class W2, class W1, class VArgs>
 static hipError_t pick(int what, const VArgs* v, const GemmV2Args* g, const WgradArgs& w, hipStream_t s, const AmaxFold* amax) {
     using G = GemmV2Unit<true, true, EPI, true, true, typename TileSel<true, EPI>::T128>;
-    if (what == kMixBackwardTail && amax) return launch_units<V, W1, AmaxUnit>(s, *v, w, *amax);
+    if (what == kMixBackwardTail && amax) return launch_units<V, W1, AmaxUnit>(s, *v, w, *amax, wgrad_first<W1, V>(*v, w));
     return launch_mix<V, G, W2, W1>(what, v, g, w, s);
 }
 template <class V, int EPI, class VArgs>

@@ -9,7 +9,7 @@ static hipError_t pick(int what, const GatherArgs* v, const GemmV2Args* g, const
     using W2 = WgradUnit128<false, true, ACC32>;
     using W1 = WgradUnit128<false, false, ACC32>;
     if constexpr (ACC32) if (what == kMixForwardTail) return hipErrorInvalidValue;
-    if (what == kMixBackwardTail) return launch_units<V, W1>(s, *v, w);
+    if (what == kMixBackwardTail) return launch_units<V, W1>(s, *v, w, wgrad_first<W1, V>(*v, w));
     if constexpr (ACC32) return launch_units<W2, G>(s, w, *g);
     else return launch_mix<V, G, W2, W1>(what, v, g, w, s);
 }
