@@ -325,8 +325,7 @@ inline bool wgrad_on_kept_rows(int64_t T, int64_t F, int M, int64_t experts) { r
 // what comes before it, nor than the bytes of all its units.  Tiles and splits are those that the separate launches have.  Eqs. (5), (8) of bf16 blocks of 32 and
 // 64 columns multiply the kept rows only where they have launches of their own, 8 and 16 times fewer products: M = 64, T = 11520, D = 896, F = 2048 the step 172 us apart,
 // 286 together; T = 7680, D = 832, F = 3072 142 / 210; M = 32, T = 5312, D = 1152, F = 3584 148 / 185; small ones share all the same (M = 64, T = 1280, D = 448,
-// F = 2048 51 / 44).  The two lines of those launches are fitted by themselves, to 1600 steps with M = 32, 64 each run both ways: what is chosen takes 0.40 and 0.09 % longer
-// than the better form; they lean to sharing, so that 9 and 4 of 800 are apart where that is 2 % and more slower (0.30 % and 29 without that).
+// F = 2048 51 / 44).
 // The constants are fitted to whole steps of 28000 drawn shapes (T 64 - 16384, D 256 - 8192, 1 - 32 experts of uneven length, every M, bf16 and codes), each run both
 // ways.  Over 4000 others what is chosen takes 0.10 % longer than the better form (one expert 0.10 % in bf16, 0.04 % on codes), one call in 180 4 % and more, the
 // worst 12 %; always sharing would take 2.3 % longer, never 16 %.  Over 487 measured apart from both: 0.18 %, forward and backward calls after one another, whose eq. (3)
@@ -348,7 +347,7 @@ struct StepCosts {
 };
 constexpr StepCosts kStepBf16 = {3.34f, {0.51f, 0.556f, 0.869f, 0.968f}, {0.402f, 0.411f, 0.436f}, {0.664f, 0.788f, 0.653f, 0.591f}, 0.882f, 0.856f, 2.69f, 1.98f, {0.263f, 0.285f, 0.485f, 1.12f},
                                  {8.92f, 0.722f}, {11.6f, 0.825f}, {7.85f, 0.511f}, {5.16f, 0.407f}, {4.99f, 0.639f}, {4.73f, 0.86f}, {11.8f, 0.0731f},
-                                 {15.4f, 0.632f}, {2.0f, 0.69f}, {3.59f, 0.103f}, {3.2f, 1.49f}, {4.31f, 0.338f}, {6.46f, 1.17f}, {4.09f, 0.63f}, {4.46f, 0.164f}, {8.0f, 0.0f}, {7.0f, 0.0f}};
+                                 {15.4f, 0.632f}, {2.0f, 0.69f}, {3.59f, 0.103f}, {3.2f, 1.49f}, {4.31f, 0.338f}, {6.46f, 1.17f}, {4.09f, 0.63f}, {4.46f, 0.164f}, {5.62f, 0.201f}, {7.12f, 0.229f}};
 constexpr StepCosts kStepFp8 = {4.84f, {0.421f, 0.727f, 1.24f, 0.658f}, {0.297f, 0.255f, 0.254f}, {0.618f, 0.683f, 0.639f, 0.631f}, 1.0f, 0.942f, 2.75f, 1.9f, {0.247f, 0.26f, 0.452f, 1.03f},
                                  {11.8f, 0.858f}, {16.0f, 0.776f}, {13.6f, 0.8f}, {6.33f, 0.52f}, {7.82f, 0.545f}, {8.93f, 0.977f}, {1.9f, 0.15f},
                                  {11.0f, 0.608f}, {3.16f, 0.586f}, {3.4f, 0.206f}, {2.86f, 1.28f}, {4.0f, 0.38f}, {6.57f, 0.503f}, {4.15f, 0.29f}, {3.27f, 0.0483f}, {}, {}};
