@@ -13,6 +13,14 @@ namespace sffn {
 
 __device__ __forceinline__ float bf2f(uint32_t h) { return __uint_as_float(h << 16); }
 
+// 16 bytes of an output, non-temporal: stored the ordinary way the outputs push the operands that the other tiles share out of L2 and of the
+// last-level cache.  The loads of eq. (1) alone beside its stores, T = F = 8192, 256 tiles: D = 8192 433 -> 281 us, D = 2048, F = 28672 345 -> 306; whole contractions, which the power of
+// the matrix instructions bounds as well, 139 -> 136 and 503 -> 472; steps, ordinary / this: T = 8192, D = 2048, F = 8192 913 / 901 us, T = 1984, D = 1344, F = 4160 134 / 132; the six contractions
+// of the first by themselves 937 / 912.
+typedef __attribute__((ext_vector_type(4))) uint32_t sffn_u32x4;
+__device__ __forceinline__ void store_out(void* p, const uint4& w) { __builtin_nontemporal_store(__builtin_bit_cast(sffn_u32x4, w), reinterpret_cast<sffn_u32x4*>(p)); }
+__device__ __forceinline__ void store_out(void* p, const float4& w) { store_out(p, __builtin_bit_cast(uint4, w)); }
+
 // fp32 -> bf16 bits, round to nearest even, through gfx950's v_cvt_pk_bf16_f32 (checked against integer
 // rounding on every bf16 pattern x tie / near-tie low halves, subnormals included; only NaN payloads differ).
 typedef __attribute__((ext_vector_type(2))) float sffn_f32x2;

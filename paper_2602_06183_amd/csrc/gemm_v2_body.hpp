@@ -547,7 +547,7 @@ __device__ __forceinline__ void gemm_nt_v2_body(unsigned char* __restrict__ smem
                             *reinterpret_cast<uint2*>(o) = make_uint2(w.x, w.y);
                             *reinterpret_cast<uint2*>(o + ((int64_t)1 << grp.map_logM)) = make_uint2(w.z, w.w);
                         } else {
-                            *reinterpret_cast<uint4*>(out + (int64_t)j * ldo + i) = w;
+                            store_out(out + (int64_t)j * ldo + i, w);
                         }
                     }
                 }
@@ -905,7 +905,7 @@ __device__ __forceinline__ void gemm_nt_v2_body(unsigned char* __restrict__ smem
                 if (i < Ra && j < Rb) {
                     int64_t io = grp.map_logM ? ((int64_t)(i >> 2) << grp.map_logM) + 4 * expert_id + (i & 3) : i;
                     if (grp.out_row_map) io = io_map[a][p];
-                    if (io >= 0) *reinterpret_cast<uint4*>(out + io * ldo + j) = *reinterpret_cast<const uint4*>(scratch + row * EP + ch * 16);
+                    if (io >= 0) store_out(out + io * ldo + j, *reinterpret_cast<const uint4*>(scratch + row * EP + ch * 16));
                 }
             }
             wave_lds_sync();

@@ -119,7 +119,7 @@ __device__ __forceinline__ void wgrad_store(f32x4 (&acc)[TL::WM / 16][4], float 
                 const int r = row0 + p * 4 + (lane >> 4), c = col0 + (lane & 15) * 4;
                 if (r < rows && c < cols) {
                     const float4 add = *reinterpret_cast<const float4*>(scratch + (p * 4 + (lane >> 4)) * EP + (lane & 15) * 16);
-                    *reinterpret_cast<float4*>(out32 + (int64_t)r * ldo + c) = make_float4(old[p].x + add.x, old[p].y + add.y, old[p].z + add.z, old[p].w + add.w);
+                    store_out(out32 + (int64_t)r * ldo + c, make_float4(old[p].x + add.x, old[p].y + add.y, old[p].z + add.z, old[p].w + add.w));
                 }
             }
             wave_lds_sync();
@@ -144,7 +144,7 @@ __device__ __forceinline__ void wgrad_store(f32x4 (&acc)[TL::WM / 16][4], float 
                 const int row = p * 8 + (lane >> 3), ch = lane & 7;
                 const int j = n0 + row, i = f0 + ch * 8;
                 if (j < N && i < F)
-                    *reinterpret_cast<uint4*>(out + (int64_t)j * ldo + i) = *reinterpret_cast<const uint4*>(scratch + row * EP + ch * 16);
+                    store_out(out + (int64_t)j * ldo + i, *reinterpret_cast<const uint4*>(scratch + row * EP + ch * 16));
             }
             wave_lds_sync();
         }
@@ -167,7 +167,7 @@ __device__ __forceinline__ void wgrad_store(f32x4 (&acc)[TL::WM / 16][4], float 
                 const int e = lane + 64 * p, row = e / (WN / 8), ch = e % (WN / 8);
                 const int i = i0 + wm * WM + a * 32 + row, j = j0 + wn * WN + ch * 8;
                 if (i < F && j < N)
-                    *reinterpret_cast<uint4*>(out + (int64_t)i * ldo + j) = *reinterpret_cast<const uint4*>(scratch + row * EP + ch * 16);
+                    store_out(out + (int64_t)i * ldo + j, *reinterpret_cast<const uint4*>(scratch + row * EP + ch * 16));
             }
             wave_lds_sync();
         }

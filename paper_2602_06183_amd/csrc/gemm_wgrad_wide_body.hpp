@@ -220,11 +220,11 @@ __device__ __forceinline__ void wgrad_wide_body(unsigned char* __restrict__ smem
 #pragma unroll
             for (int j = 0; j < NS; ++j) { p[j] = reinterpret_cast<float4*>(reinterpret_cast<float*>(out) + o + j * step); old[j] = *p[j]; }
 #pragma unroll
-            for (int j = 0; j < NS; ++j) *p[j] = make_float4(old[j].x + v[j][0], old[j].y + v[j][1], old[j].z + v[j][2], old[j].w + v[j][3]);
+            for (int j = 0; j < NS; ++j) store_out(p[j], make_float4(old[j].x + v[j][0], old[j].y + v[j][1], old[j].z + v[j][2], old[j].w + v[j][3]));
         } else
 #pragma unroll
             for (int j = 0; j < NS; ++j)
-                *reinterpret_cast<uint4*>(out + o + j * step) = make_uint4(f2bf2(v[j][0], v[j][1]), f2bf2(v[j][2], v[j][3]), f2bf2(v[j][4], v[j][5]), f2bf2(v[j][6], v[j][7]));
+                store_out(out + o + j * step, make_uint4(f2bf2(v[j][0], v[j][1]), f2bf2(v[j][2], v[j][3]), f2bf2(v[j][4], v[j][5]), f2bf2(v[j][6], v[j][7])));
     };
     auto get4 = [&](int row, int col) { return *reinterpret_cast<const float4*>(smem + TL::at(row, col)); };
     if constexpr (OUT_I_CONTIG) {
