@@ -6,7 +6,7 @@ import sys
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libsparseffn.so")
-SOURCES = ["api.hip", "prune24.hip", "vnm.hip", "vnm_general.hip", "gemm_v2.hip", "gemm_v2_row.hip", "forward_x.hip", "gemm_v2_fp8.hip", "step_mix_bf16.hip", "step_mix_wide.hip", "step_mix_fp8.hip", "prologue.hip", "prologue_fp8.hip", "gemm_wgrad.hip", "gemm_wgrad_wide.hip", "gemm_gather.hip", "gemm_vnm8.hip", "router.hip", "router_mix.hip", "dense_ref.hip", "noalloc.hip", "fp8.hip"]
+SOURCES = ["api.hip", "prune24.hip", "vnm.hip", "vnm_general.hip", "gemm_v2.hip", "gemm_v2_row.hip", "forward_x.hip", "gemm_v2_fp8.hip", "step_mix_bf16.hip", "step_mix_wide.hip", "step_mix_fp8.hip", "step_mix_fp8_wide.hip", "prologue.hip", "prologue_fp8.hip", "gemm_wgrad.hip", "gemm_wgrad_wide.hip", "gemm_gather.hip", "gemm_vnm8.hip", "router.hip", "router_mix.hip", "dense_ref.hip", "noalloc.hip", "fp8.hip"]
 FLAGS = ["-O3", "--offload-arch=gfx950", "-fPIC", "-std=c++17",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops", "-Wno-unused-command-line-argument", "-Wno-inline-asm",
          # accumulators in VGPRs: where one wavefront has a SIMD to itself the compiler takes AGPRs and moves the 16 x 16 instructions' sums between the two in the loop

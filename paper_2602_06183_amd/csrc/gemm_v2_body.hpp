@@ -935,14 +935,16 @@ struct GemmV2Unit {
                                                                      a.ep, a.grp, a.alpha);
     }
     static unsigned count(const Args& a) { return grid_tiles(a.Ra, a.Rb, a.grp, TL::BM, TL::BN); }
+    static int stages(const Args& a) { return a.K / (SPARSE ? 64 : 32) / TL::KW; }      // of a tile, a wavefront's (K in byte pairs on codes)
     static Args args(Args a) { a.tiles_m = (a.Ra + TL::BM - 1) / TL::BM; a.tiles_n = (a.Rb + TL::BN - 1) / TL::BN; return a; }
 };
 
 // the three tiles; blocks of M = 64 columns want 128 hidden units in one wavefront (two blocks share a metadata byte): 256 x 128 in the place of 128 x 128
 template <bool SPARSE> using Tile256 = Tile<2, 4, 128, SPARSE ? 3 : 4, 1>;
+using TileTall = Tile<2, 2, 128, 2, 1>;       // 256 x 128, four wavefronts, two workgroups a CU (structured-sparse, with an epilogue)
 template <bool SPARSE, int EPI> struct TileSel { using T128 = Tile<2, 2, 64, SPARSE ? 3 : 4, 1>; using T64 = Tile<1, 1, 64, 3, 4>; };
-template <> struct TileSel<true, 22> { using T128 = Tile<2, 2, 128, 2, 1>; using T64 = Tile<1, 1, 128, 2, 4>; };
-template <> struct TileSel<true, 38> { using T128 = Tile<2, 2, 128, 2, 1>; using T64 = Tile<1, 1, 128, 2, 4>; };
+template <> struct TileSel<true, 22> { using T128 = TileTall; using T64 = Tile<1, 1, 128, 2, 4>; };
+template <> struct TileSel<true, 38> { using T128 = TileTall; using T64 = Tile<1, 1, 128, 2, 4>; };
 
 // tile: 256 / 128 / 64, or 0 to choose here
 template <bool SPARSE, bool OUT_I_CONTIG, int EPI, bool BLOCKED, bool FP8>

@@ -416,6 +416,7 @@ struct Vnm8Unit {
 };
 template <bool FP8> using Vnm8Unit512 = Vnm8Unit<FP8, VTile<8, 1, 4, 3, 1>>;
 template <bool FP8> using Vnm8Unit256 = Vnm8Unit<FP8, VTile<4, 2, 4, 3, 1>>;
+template <bool FP8> using Vnm8UnitTall = Vnm8Unit<FP8, VTile<4, 1, 4, 3, 1>>;          // 256 tokens x 128 columns
 template <bool FP8> using Vnm8Unit128 = Vnm8Unit<FP8, VTile<2, 2, 2, 3, 1>>;
 template <bool FP8> using Vnm8Unit64 = Vnm8Unit<FP8, VTile<1, 1, 2, 3, 4>>;
 

@@ -804,6 +804,7 @@ struct WgradUnit {
     static Args args(Args a) { a.tiles_m = (a.F + TL::BM - 1) / TL::BM; a.tiles_n = (a.N + TL::BN - 1) / TL::BN; return a; }
 };
 template <bool FP8, bool OUT_I_CONTIG, bool ACC32> using WgradUnit256 = WgradUnit<FP8, OUT_I_CONTIG, ACC32, WTile<2, 4, 128, 3, 1>>;
+template <bool FP8, bool OUT_I_CONTIG, bool ACC32> using WgradUnitTall = WgradUnit<FP8, OUT_I_CONTIG, ACC32, WTile<2, 2, 128, 2, 1>>;      // 256 hidden units x 128 columns
 template <bool FP8, bool OUT_I_CONTIG, bool ACC32> using WgradUnit128 = WgradUnit<FP8, OUT_I_CONTIG, ACC32, WTile<2, 2, 64, 3, 1>>;
 template <bool FP8, bool OUT_I_CONTIG, bool ACC32> using WgradUnit64 = WgradUnit<FP8, OUT_I_CONTIG, ACC32, WTile<1, 1, 64, 3, 4>>;
 

@@ -4,6 +4,7 @@
 #include <math.h>
 #include <stdint.h>
 #include <initializer_list>
+#include "mix_plan.hpp"
 
 namespace sffn {
 
@@ -103,7 +104,6 @@ struct WgradArgs {
 // v_alone: the tile of eq. (3) where it has a launch of its own all the same (forward calls); the same bits as on v.
 struct StepTiles { int g = 0, g_bwd = 0, v = 0, v_alone = 0, v_split = 1, w = 0; bool mix = false; };
 inline StepTiles step_tiles(int64_t T, int64_t D, int64_t F, int M, int experts, bool fp8, bool may_share = true);
-enum { kMixForwardTail = 0, kMixBackwardHead = 1, kMixBackwardTail = 2 };      // {(3), (5), (4)}, {(5), (4)}, {(7), (8)}
 // M = 8: v8 (else null: va); acc32: not with kMixForwardTail
 hipError_t launch_step_mix_bf16(int what, int logM, const StepTiles& t, bool acc32, const Vnm8Args* v8, const GatherArgs* va, const GemmV2Args* g, const WgradArgs& w, hipStream_t s);
 // (amax: with kMixBackwardTail, the fold of the step's maxima in the same launch)

@@ -3,24 +3,25 @@
 
 namespace sffn {
 
-template <class V, bool ACC32, int EPI>
-static hipError_t pick(int what, const GatherArgs* v, const GemmV2Args* g, const WgradArgs& w, hipStream_t s) {
-    using G = GemmV2Unit<true, true, EPI, true, false, typename TileSel<true, EPI>::T128>;
-    using W2 = WgradUnit128<false, true, ACC32>;
-    using W1 = WgradUnit128<false, false, ACC32>;
-    if constexpr (ACC32) if (what == kMixForwardTail) return hipErrorInvalidValue;
-    if (what == kMixBackwardTail) return launch_units<V, W1>(s, *v, w, wgrad_first<W1, V>(*v, w));
-    if constexpr (ACC32) return launch_units<W2, G>(s, w, *g);
-    else return launch_mix<V, G, W2, W1>(what, v, g, w, s);
+template <bool ACC32, int EPI>
+static hipError_t launch_impl(int what, const StepTiles& t, const GatherArgs* v, const GemmV2Args* g, const WgradArgs& w, hipStream_t s) {
+    constexpr bool TALL = EPI == 38;              // M = 64: eq. (4) is on tall tiles as it is
+    using V = Units<GatherUnit64, GatherUnit256, void>;
+    using W2 = Units<void, WgradUnit128<false, true, ACC32>, WgradUnitTall<false, true, ACC32>>;
+    using W1 = Units<void, WgradUnit128<false, false, ACC32>, WgradUnitTall<false, false, ACC32>>;
+    using GT = GemmV2Unit<true, true, EPI, true, false, TileTall>;
+    using G = std::conditional_t<TALL, Units<void, GT, void>, Units<void, GemmV2Unit<true, true, EPI, true, false, typename TileSel<true, EPI>::T128>, GT>>;
+    MixTiles k = kMixWideBf16;
+    if (TALL) k.g[0] = kMixTallBf16;
+    return launch_mix<!ACC32, false, V, W2, W1, G>(k, what, t, v, g, w, 64.0f, s);
 }
-template <class V, bool ACC32>
-static hipError_t pick_m(int what, int logM, const GatherArgs* v, const GemmV2Args* g, const WgradArgs& w, hipStream_t s) {
-    return logM == 4 ? pick<V, ACC32, 36>(what, v, g, w, s) : logM == 5 ? pick<V, ACC32, 37>(what, v, g, w, s) : pick<V, ACC32, 38>(what, v, g, w, s);
+template <bool ACC32>
+static hipError_t launch_m(int what, int logM, const StepTiles& t, const GatherArgs* v, const GemmV2Args* g, const WgradArgs& w, hipStream_t s) {
+    return logM == 4 ? launch_impl<ACC32, 36>(what, t, v, g, w, s) : logM == 5 ? launch_impl<ACC32, 37>(what, t, v, g, w, s) : launch_impl<ACC32, 38>(what, t, v, g, w, s);
 }
 
 hipError_t launch_step_mix_bf16_wide(int what, int logM, const StepTiles& t, bool acc32, const GatherArgs* va, const GemmV2Args* g, const WgradArgs& w, hipStream_t s) {
-    if (t.v == 64) return acc32 ? pick_m<GatherUnit64, true>(what, logM, va, g, w, s) : pick_m<GatherUnit64, false>(what, logM, va, g, w, s);
-    return acc32 ? pick_m<GatherUnit256, true>(what, logM, va, g, w, s) : pick_m<GatherUnit256, false>(what, logM, va, g, w, s);
+    return acc32 ? launch_m<true>(what, logM, t, va, g, w, s) : launch_m<false>(what, logM, t, va, g, w, s);
 }
 
 }  // namespace sffn
