@@ -29,6 +29,12 @@ static hipError_t launch_impl(Vnm8Args a, hipStream_t s, const GemmGroup* grp, i
     if (!tile) tile = pick_vnm8_tile(a.T, a.N, a.F / (FP8 ? 128 : 64), a.grp.n, FP8);
     if (split) a.split = *split;
     if (a.split.n > 1 && (a.grp.n || tile == 256)) return hipErrorInvalidValue;
+    if (tile != 64 && a.split.n <= 1) {
+        const AloneTiles& k = FP8 ? kAloneActivationFp8 : kAloneActivationBf16;
+        const unsigned n512 = (unsigned)(0.93f * (float)Vnm8Unit512<FP8>::count(a)), n256 = Vnm8Unit256<FP8>::count(a);
+        if (tall_alone(k, tile == 256 ? rounds_of_large(n512 < n256 ? n512 : n256, k.part) : 0.0f, Vnm8Unit128<FP8>::count(a), Vnm8UnitTall<FP8>::count(a), Vnm8UnitTall<FP8>::stages(a)))
+            return launch_units<Vnm8UnitTall<FP8>>(s, a);
+    }
     if (tile == 256) return long_tile<FP8>(a) ? launch_units<Vnm8Unit512<FP8>>(s, a) : launch_units<Vnm8Unit256<FP8>>(s, a);
     return tile == 128 ? launch_units<Vnm8Unit128<FP8>>(s, a) : launch_units<Vnm8Unit64<FP8>>(s, a);
 }

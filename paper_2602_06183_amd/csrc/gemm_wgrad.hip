@@ -6,6 +6,12 @@ namespace sffn {
 template <bool FP8, bool OUT_I_CONTIG, bool ACC32>
 static hipError_t launch_sized(const WgradArgs& a, hipStream_t s, int tile) {
     if constexpr (!FP8) if (wgrad_three_a_cu(a.F, a.N, a.T, a.grp.n, tile)) return launch_units<WgradUnit<FP8, OUT_I_CONTIG, ACC32, WTile<2, 2, 64, 2, 1>>>(s, a);
+    if constexpr (!FP8) {
+        using Tall = WgradUnitTall<false, OUT_I_CONTIG, ACC32>;
+        const unsigned n256 = WgradUnit256<false, OUT_I_CONTIG, ACC32>::count(a);
+        if (tile != 64 && tall_alone(kAloneGradientBf16, tile == 256 ? rounds_of_large(n256, kAloneGradientBf16.part) : 0.0f, WgradUnit128<false, OUT_I_CONTIG, ACC32>::count(a), Tall::count(a), Tall::stages(a)))
+            return launch_units<Tall>(s, a);
+    }
     if (tile == 256) return launch_units<WgradUnit256<FP8, OUT_I_CONTIG, ACC32>>(s, a);
     if (tile == 128) return launch_units<WgradUnit128<FP8, OUT_I_CONTIG, ACC32>>(s, a);
     return launch_units<WgradUnit64<FP8, OUT_I_CONTIG, ACC32>>(s, a);

@@ -98,4 +98,21 @@ inline unsigned mix_form(const MixTiles& k, int what, const MixCount& v, const M
     return best;
 }
 
+// A contraction in a launch of its own, on the large tile (a round of 256 at a time: fixed + step x stages; a last round of few tiles `part` of that and up), on 128 or on tall tiles; `start` comes
+// on top of each.  Fitted to launches inside 130 steps of any size (T 128 - 16384, D 320 - 8192) on each tile; tall tiles where the estimate saves `save`.  Over the tile that the rules of
+// kernels.hpp choose: eqs. (3), (7) 0.943 of the time in bf16 and 0.961 on codes over all of them, none longer (T = 1664, D = 3968, F = 15616 155 us on the large tile, 169 on 128, 119;
+// T = 2304, D = 1856, F = 4864 41, 41, 34); eqs. (5), (8) in bf16 0.90 where they are chosen, one in nine, none above 0.945 (T = 2944, D = 3456, F = 9344 151 -> 137), on codes nothing;
+// eqs. (1), (4) 0.994, not built.
+struct AloneTiles { MixTile large; float part; MixTile small, tall; float large_start, small_start, tall_start, save; };
+constexpr AloneTiles kAloneActivationBf16 = {{0.0f, 0.636f, 1.0f}, 0.621f, {0.0f, 0.582f, 0.501f}, {0.0f, 0.759f, 0.492f}, 8.15f, 5.56f, 6.88f, 0.06f};
+constexpr AloneTiles kAloneActivationFp8 = {{0.0f, 0.705f, 1.0f}, 0.69f, {0.0f, 0.629f, 0.476f}, {0.0f, 0.844f, 0.495f}, 9.2f, 6.46f, 7.95f, 0.06f};
+constexpr AloneTiles kAloneGradientBf16 = {{6.46f, 1.258f, 1.0f}, 0.778f, {2.74f, 0.715f, 0.534f}, {4.53f, 1.255f, 0.546f}, 3.73f, 5.93f, 6.05f, 0.05f};
+// large: rounds of the large tile, or 0 where `small` tiles of 128 are chosen
+inline bool tall_alone(const AloneTiles& k, float large, unsigned small, unsigned tall, int stages) {
+    if (tall > 8192) return false;                             // (16 rounds: what they end in no longer counts)
+    const MixUnit t = mix_unit(k.tall, tall, stages), s = mix_unit(k.small, small, stages);
+    const float now = large > 0.0f ? k.large_start + large * (k.large.fixed + k.large.step * (float)stages) : k.small_start + mix_time(&s, 1, 64.0f);
+    return k.tall_start + mix_time(&t, 1, 64.0f) < (1.0f - k.save) * now;
+}
+
 }  // namespace sffn

@@ -1,5 +1,6 @@
 // Prints which contractions of a step's shared launches take tall tiles (mix_plan.hpp), for tests/test_mix_forms.py.  One line of standard input is one call:
 //   <fp8> <M> <D> <F> <T>   -> does the step share launches; the forms of eqs. (3), (5), (4), of (5), (4) and of (7), (8)
+//   alone <fp8> <T> <N> <F> -> eqs. (3), (7) and (bf16) (5), (8) in launches of their own: the tile that the rules choose, is it a tall one instead (64 tiles, three workgroups a CU: no)
 //   play <slots> <n> <time> <alone> ... (three times)   -> time of the launch
 #include <stdio.h>
 #include <string.h>
@@ -19,6 +20,18 @@ int main() {
             if (scanf("%f", &slots) != 1) return 1;
             for (MixUnit& x : u) if (scanf("%f %f %f", &x.n, &x.time, &x.alone) != 3) return 1;
             printf("%.4f\n", mix_time(u, 3, slots));
+            continue;
+        }
+        if (!strcmp(first, "alone")) {
+            long f8, T, N, F;
+            if (scanf("%ld %ld %ld %ld", &f8, &T, &N, &F) != 4) return 1;
+            const AloneTiles& k = f8 ? kAloneActivationFp8 : kAloneActivationBf16;
+            const int steps = (int)(F / (f8 ? 128 : 64)), v = plan_vnm8(T, N, steps, 0, f8 != 0).tile, w = pick_wgrad_tile(F, N, T, 0, true, f8 != 0);
+            const unsigned n512 = (unsigned)(0.93f * (float)tiles(T, 512, N, 128)), n256 = tiles(T, 256, N, 256);
+            const bool v_tall = v != 64 && tall_alone(k, v == 256 ? rounds_of_large(n512 < n256 ? n512 : n256, k.part) : 0.0f, tiles(T, 128, N, 128), tiles(T, 256, N, 128), steps);
+            const bool w_tall = !f8 && w != 64 && !wgrad_three_a_cu(F, N, T, 0, w) &&
+                                tall_alone(kAloneGradientBf16, w == 256 ? rounds_of_large(tiles(F, 256, N, 256), kAloneGradientBf16.part) : 0.0f, tiles(F, 128, N, 128), tiles(F, 256, N, 128), (int)(T / 64));
+            printf("%d %d %d %d\n", v, (int)v_tall, w, (int)w_tall);
             continue;
         }
         const int fp8 = first[0] == '1';

@@ -85,3 +85,41 @@ def test_experts():
         alone = sffn.FfnStep(b - a, D, F, lean=True)(X[a:b].contiguous(), W1[e], W2[e], b1[e], dY[a:b].contiguous())
         for got, want in ((Y3[a:b], alone[0]), (dX[a:b], alone[1]), (dW1[e], alone[2]), (dW2[e], alone[3])):
             assert same(got, want)
+
+
+# fp8, T, N, F: launches of their own, on tall tiles instead of 256 or 128
+ALONE_ACTIVATION = [(0, 2496, 2944, 256), (0, 1600, 3456, 960), (1, 2624, 2624, 1664), (1, 3776, 3328, 512)]
+ALONE_GRADIENT = [(0, 448, 1856, 8256), (0, 704, 2624, 9408)]
+
+
+def compressed(T, F, seed):
+    X = to_dev(make_ffn_inputs(T, 64, 64, seed=seed)["X"])
+    return X.repeat(1, F // 64) * torch.linspace(0.5, 2.0, F, device="cuda").to(torch.bfloat16)
+
+
+@pytest.mark.parametrize("fp8,T,N,F", ALONE_ACTIVATION)
+def test_activation_contraction_alone(fp8, T, N, F):
+    """As on the tokens in three pieces, which take other tiles."""
+    y1, W = compressed(T, F, 65), to_dev(make_ffn_inputs(64, N, F, seed=66)["W2"])
+    if fp8:
+        y2, Wq = sffn.sqrelu_vnm_compress_fp8(y1, 0.05), sffn.quantize_fp8(W, 1e-3)
+        spmm = lambda *v: sffn.vnm_spmm_fp8(*v, 0.05, Wq, 1e-3, 0)  # noqa: E731
+    else:
+        y2 = sffn.sqrelu_vnm_compress(y1)
+        spmm = lambda *v: sffn.vnm_spmm(*v, W, 0)  # noqa: E731
+    whole = spmm(*y2)
+    assert float(whole.float().abs().max()) > 0
+    for a, b in ((0, 448), (448, 1024), (1024, T)):
+        assert same(whole[a:b], spmm(*(t[a // d:b // d].contiguous() for t, d in zip(y2, (1, 1, 64)))))
+
+
+@pytest.mark.parametrize("fp8,T,N,F", ALONE_GRADIENT)
+@pytest.mark.parametrize("f_major", [False, True])
+def test_gradient_contraction_alone(fp8, T, N, F, f_major):
+    """As on the columns of the dense operand in three pieces, which take other tiles."""
+    y2, G = sffn.sqrelu_vnm_compress(compressed(T, F, 67)), to_dev(make_ffn_inputs(T, N, 64, seed=68)["X"])
+    whole = sffn.vnm_wgrad(*y2, G, f_major)
+    assert float(whole.float().abs().max()) > 0
+    for a, b in ((0, 320), (320, 1024), (1024, N)):
+        piece = sffn.vnm_wgrad(*y2, G[:, a:b].contiguous(), f_major)
+        assert same(whole[:, a:b] if f_major else whole[a:b], piece)

@@ -36,3 +36,14 @@ def test_every_form_is_one_that_is_built(forms):
         assert not (fwd & 4) or fwd == (7 if call[1] == 8 else 6), (call, line)
         assert head in (0, 2, 6) and tail in ((0, 1, 2, 3) if call[1] == 8 else (0, 2)), (call, line)
         assert call[1] != 64 or not (fwd | head) & 4, (call, line)
+
+
+def test_launches_of_their_own_of_the_gpu_tests(forms):
+    from tests.test_gpu_tall_tiles import ALONE_ACTIVATION, ALONE_GRADIENT
+    for call, line in zip(ALONE_ACTIVATION, forms(["alone %d %d %d %d" % c for c in ALONE_ACTIVATION])):
+        assert line[0] in ("128", "256") and line[1] == "1", (call, line)
+    for call, line in zip(ALONE_GRADIENT, forms(["alone %d %d %d %d" % c for c in ALONE_GRADIENT])):
+        assert line[2] in ("128", "256") and line[3] == "1", (call, line)
+    # codes: gradients never; no activation contraction whose tiles all have a CU
+    small = [(fp8, T, 512, F) for fp8 in (0, 1) for T in (64, 512, 2048) for F in (512, 4096)]
+    assert all(line[1] == "0" and line[3] == "0" for line in forms(["alone %d %d %d %d" % c for c in small]))
