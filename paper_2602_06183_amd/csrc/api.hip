@@ -1101,8 +1101,10 @@ int ffn_router_full_backward(const sffn_cfg* cfg, const uint16_t* dY, uint16_t* 
 }
 
 // eq. (1) on X as it is: what it reads itself stays in front of it, the rest goes behind its tiles
-static inline void split_off_eq1(PrologueArgs* front, PrologueArgs* behind) {
-    behind->W1 = nullptr; behind->xb = nullptr;
+static inline void split_off_eq1(PrologueArgs* front, PrologueArgs* behind, bool prunes) {
+    if (!prunes) behind->W1 = nullptr;
+    behind->xb = nullptr;
+    if (prunes) front->W1 = nullptr;
     front->X = front->dY = front->W2 = nullptr; front->counters = nullptr;
 }
 static inline void split_prologue(const PrologueArgs& all, PrologueArgs (&part)[3]) {
@@ -1213,7 +1215,7 @@ static int run_step(const sffn_cfg* cfg, int n_experts, const int64_t* seg, cons
         split_prologue(pro, part);
         const bool x_as_is = fwd && forward_reads_x(T, D, F, E, cfg->M, packed, tiles.g);
         PrologueArgs behind = together ? pro : part[0];
-        if (x_as_is) split_off_eq1(&pro, &behind);
+        if (x_as_is) split_off_eq1(&pro, &behind, forward_prunes_w1(D, cfg->M, packed, tiles.g));
         if (together) STAGE(launch_step_prologue(pro, s), "step/prologue");
         else if (fwd && !x_as_is) STAGE(launch_step_prologue(part[0], s), "step/X.T+prune24(W1)");
         if (fwd) {
@@ -1336,7 +1338,7 @@ static int run_step(const sffn_cfg* cfg, int n_experts, const int64_t* seg, cons
     split_prologue(pro, part);
     const bool x_as_is = fwd && forward_reads_x(T, D, F, E, cfg->M, packed, tiles.g);
     PrologueArgs behind = together ? pro : part[0];
-    if (x_as_is) split_off_eq1(&pro, &behind);
+    if (x_as_is) split_off_eq1(&pro, &behind, forward_prunes_w1(D, cfg->M, packed, tiles.g));
     if (together) STAGE(launch_step_prologue(pro, s), "step/prologue");
     else if (fwd && !x_as_is) STAGE(launch_step_prologue(part[0], s), "step/X.T+prune24(W1)");
     if (fwd) {   // eq. (1), then eq. (2) + V:N:M compression on the tile while it is still in LDS

@@ -36,7 +36,8 @@ struct Tile {
     static_assert(KW == 1 || NW == 1, "a shared output tile belongs to single wavefronts");
 };
 // MG: row-major 2:4 metadata fetched for four stages at a time, into two buffers behind the ring (see issue())
-template <bool SPARSE, bool FP8, class TL, bool MG = false>
+// PRUNE: A is the weight itself, which the wavefronts prune as they read it (see below): the stages hold B only
+template <bool SPARSE, bool FP8, class TL, bool MG = false, bool PRUNE = false>
 struct Cfg {
     static constexpr int BM = TL::BM, BN = TL::BN;
     static constexpr int BK = SPARSE ? 64 : 32;
@@ -44,23 +45,26 @@ struct Cfg {
     static constexpr int A_ROW = 64;                        // bytes per A row per stage (32 survivors or 32 dense k)
     static constexpr int B_ROW = SPARSE ? 128 : 64;
     static constexpr int META_ROW = FP8 ? 16 : 8;
-    static constexpr int A_BYTES = BM * A_ROW, B_BYTES = BN * B_ROW, META_BYTES = SPARSE && !MG ? BM * META_ROW : 0;
+    static constexpr int A_BYTES = PRUNE ? 0 : BM * A_ROW, B_BYTES = BN * B_ROW, META_BYTES = SPARSE && !MG && !PRUNE ? BM * META_ROW : 0;
     static constexpr int GROUP_BYTES = MG ? BM * 32 : 0;    // 32 metadata bytes of every A row = 256 k
     static constexpr int STAGE = A_BYTES + B_BYTES + META_BYTES;
-    static constexpr int A_LD = A_BYTES / 1024 / TL::NW, B_LD = B_BYTES / 1024 / TL::NW, M_LD = SPARSE ? BM / 32 / TL::NW : 0;   // loads per wave per stage
+    static constexpr int A_LD = A_BYTES / 1024 / TL::NW, B_LD = B_BYTES / 1024 / TL::NW, M_LD = SPARSE && !PRUNE ? BM / 32 / TL::NW : 0;   // loads per wave per stage
     static constexpr int LOADS = A_LD + B_LD + M_LD * (FP8 ? 2 : 1);       // (MG: one fewer in stages that bring no metadata)
 };
 
-template <bool SPARSE, bool OUT_I_CONTIG, int EPI, bool BLOCKED, bool FP8, class TL, bool MG = false>
+template <bool SPARSE, bool OUT_I_CONTIG, int EPI, bool BLOCKED, bool FP8, class TL, bool MG = false, bool PRUNE = false>
 struct GemmV2Lds {
-    using C = Cfg<SPARSE, FP8, TL, MG>;
+    using C = Cfg<SPARSE, FP8, TL, MG, PRUNE>;
     static constexpr int EPI_LDS = (EPI != 0) ? TL::NW * (64 + 32) * (64 * 2 + 16) : 0;        // the epilogues' scratch (see below) when the ring is shorter
     static constexpr int RING = TL::KW * C::NSTAGE * C::STAGE + 2 * C::GROUP_BYTES;
-    static constexpr int BYTES = RING > EPI_LDS ? RING : EPI_LDS;
+    static constexpr int SUMS = PRUNE ? TL::KW * (TL::WM / 16) * 4 * 4 * 256 + EPI_LDS : 0;     // the partial sums of a shared tile and the scratch, where the ring does not hold them
+    static constexpr int LONGER = RING > EPI_LDS ? RING : EPI_LDS, BYTES = LONGER > SUMS ? LONGER : SUMS;
 };
 // pid / n_pid: this workgroup's id and the number of workgroups of the contraction (a launch may hold several contractions)
 // BROW: B row-major although A is blocked (forward_x.hip)
-template <bool SPARSE, bool OUT_I_CONTIG, int EPI, bool BLOCKED, bool FP8, class TL, bool BROW, bool MG>
+// PRUNE: 1 + SFFN_MODE of a contraction whose A (a_vals) is the unpruned row-major weight (forward_x.hip): a lane's 16 k of a row are four whole groups, which it prunes in registers.  All of a
+// wavefront's stages are in flight at once, at most NST of them (K <= 64 KW NST).
+template <bool SPARSE, bool OUT_I_CONTIG, int EPI, bool BLOCKED, bool FP8, class TL, bool BROW, bool MG, int PRUNE>
 __device__ __forceinline__ void gemm_nt_v2_body(unsigned char* __restrict__ smem, int pid, int n_pid,
                                                         const uint16_t* __restrict__ a_vals, const uint8_t* __restrict__ a_meta,
                                                         const uint16_t* __restrict__ B, const float* __restrict__ bias,
@@ -74,7 +78,8 @@ __device__ __forceinline__ void gemm_nt_v2_body(unsigned char* __restrict__ smem
     static_assert(!FP8 || (SPARSE && (EPI == 0 || (BLOCKED && (EPI == 1 || EPI == 2 || GEN_F || GEN_B)))), "fp8 operands: structured-sparse kernel; the step's fused epilogues");
     constexpr bool blocked = BLOCKED, blockedB = BLOCKED && !BROW;       // operands in the blocked layout of common.hpp (fused step) or row-major (stand-alone entry points)
     static_assert(!MG || (SPARSE && !BLOCKED && !FP8 && TL::KW == 1 && TL::NST == 3 && TL::WM * TL::WVM == 32 * TL::NW), "metadata of four stages: row-major bf16, 32 rows a wavefront");
-    using C = Cfg<SPARSE, FP8, TL, MG>;
+    static_assert(!PRUNE || (BROW && TL::KW > 1 && !FP8), "the weight itself: 64 tiles of eq. (1) in bf16, on row-major operands");
+    using C = Cfg<SPARSE, FP8, TL, MG, PRUNE != 0>;
     constexpr int BM = C::BM, BN = C::BN, WM = TL::WM, WN = 64, FM = WM / 16, FN = 4, NH = WM / 64, KW = TL::KW;
     static_assert(LOGM < 6 || WM == 128, "the two blocks of 64 columns that share a metadata byte belong to one wavefront");
     const int tid = threadIdx.x, lane = tid & 63;
@@ -138,7 +143,7 @@ __device__ __forceinline__ void gemm_nt_v2_body(unsigned char* __restrict__ smem
     // Row-major operands of the sparse kernel: a B row's 64 k of a stage are one 128-byte line, fetched whole (8 rows per
     // load, tile [256][128 bytes], 16-byte chunks swizzled by (row / 2) % 8) rather than as two 64-byte halves.
     constexpr bool lineB = SPARSE && !blockedB;
-    uint64_t a_base[A_LD], b_base[B_LD], m_base[M_LD > 0 ? M_LD : 1];     // wave-uniform byte addresses of kt = 0
+    uint64_t a_base[A_LD > 0 ? A_LD : 1], b_base[B_LD], m_base[M_LD > 0 ? M_LD : 1];     // wave-uniform byte addresses of kt = 0
     uint32_t a_lane, b_lane, m_lane;                     // per-lane byte offsets
     uint32_t a_kstep, b_kstep, m_kstep;                  // bytes per main-loop step
     {
@@ -241,7 +246,7 @@ __device__ __forceinline__ void gemm_nt_v2_body(unsigned char* __restrict__ smem
     // instructions has been issued.
     struct FragB { Frag16 b16[SPARSE ? FN : 1]; Frag8 b8[SPARSE ? 1 : FN]; };     // SPARSE: 64 k (fp8: 128) a stage, dense: 32
     Frag8 A[FM];
-    constexpr bool PAIRED = SPARSE && blocked && !FP8;      // an index word for two fragments, low and high half
+    constexpr bool PAIRED = SPARSE && blocked && !FP8 && !PRUNE;      // an index word for two fragments, low and high half
     int idx[FM];
     FragB B0, B1;
     uint32_t m_kt = 0;          // MG: stage whose fragments are read next
@@ -275,7 +280,40 @@ __device__ __forceinline__ void gemm_nt_v2_body(unsigned char* __restrict__ smem
     // steps of this wavefront: all of them, or (KW > 1) every KW-th one from its own on.  0 for an expert without tokens (weight gradients): zeros
     const int nk = KW == 1 ? K / C::BK : (K / C::BK - kg + KW - 1) / KW;
     auto step_of = [&](int kt) { return KW == 1 ? kt : kg + kt * KW; };
-    if (nk > 0) {
+    if constexpr (PRUNE) {
+        const uint16_t* const row = a_vals + (int64_t)(i0 + l16) * Kld + 16 * lq;
+        uint4 raw[C::NSTAGE][FM][2];
+#pragma unroll
+        for (int p = 0; p < C::NSTAGE; ++p)
+            if (p < nk) issue(step_of(p), p, 0, LD);
+#pragma unroll
+        for (int p = 0; p < C::NSTAGE; ++p)
+            if (p < nk)
+#pragma unroll
+                for (int a = 0; a < FM; ++a) {
+                    const uint4* w = reinterpret_cast<const uint4*>(row + (int64_t)a * 16 * Kld + step_of(p) * 64);
+                    raw[p][a][0] = w[0]; raw[p][a][1] = w[1];
+                }
+        wait_vmcnt<0>();
+        asm volatile("" ::: "memory");
+#pragma unroll
+        for (int p = 0; p < C::NSTAGE; ++p)
+            if (p < nk) {
+#pragma unroll
+                for (int q = 0; q < BP; ++q) read_b(B0, ring + p * C::STAGE, q);
+#pragma unroll
+                for (int a = 0; a < FM; ++a) {
+                    const uint4 w0 = raw[p][a][0], w1 = raw[p][a][1];
+                    uint32_t n0, n1, n2, n3;
+                    A[a].u.x = select24<PRUNE == 2>(w0.x & 0xFFFFu, w0.x >> 16, w0.y & 0xFFFFu, w0.y >> 16, n0);
+                    A[a].u.y = select24<PRUNE == 2>(w0.z & 0xFFFFu, w0.z >> 16, w0.w & 0xFFFFu, w0.w >> 16, n1);
+                    A[a].u.z = select24<PRUNE == 2>(w1.x & 0xFFFFu, w1.x >> 16, w1.y & 0xFFFFu, w1.y >> 16, n2);
+                    A[a].u.w = select24<PRUNE == 2>(w1.z & 0xFFFFu, w1.z >> 16, w1.w & 0xFFFFu, w1.w >> 16, n3);
+                    idx[a] = (int)(n0 | (n1 << 4) | (n2 << 8) | (n3 << 12));
+                    mma_row(B0, a);
+                }
+            }
+    } else if (nk > 0) {
     // The ring holds NSTAGE tiles: the one being multiplied, the next one (landed by the middle of the step,
     // when its first fragments are read) and NSTAGE - 2 in flight.  A stage is refilled right after the
     // barrier that ends its last fragment reads, so a tile has almost NSTAGE - 1 steps to arrive.
@@ -343,7 +381,7 @@ __device__ __forceinline__ void gemm_nt_v2_body(unsigned char* __restrict__ smem
     constexpr bool SHARE = KW > 1 && (EPI == 1 || EPI == 2);
     constexpr int PART = FM * FN * 4 * 256;
     if (KW > 1 && !SHARE) {       // partial sums -> the first wavefront, in ascending order; the others are done
-        static_assert((KW - 1) * PART <= KW * C::NSTAGE * C::STAGE, "partial sums must fit in the main-loop LDS");
+        static_assert((KW - 1) * PART <= GemmV2Lds<SPARSE, OUT_I_CONTIG, EPI, BLOCKED, FP8, TL, MG, PRUNE != 0>::BYTES, "partial sums must fit in the main-loop LDS");
         if (kg > 0) {
             float* p = reinterpret_cast<float*>(smem + (kg - 1) * PART) + lane;
 #pragma unroll
@@ -376,7 +414,7 @@ __device__ __forceinline__ void gemm_nt_v2_body(unsigned char* __restrict__ smem
         constexpr int WAVE_LDS = (EPI != 0) ? (WN + 32) * EP : WN * EP;
         static_assert(!SHARE || (KW == 4 && FM == 4 && NH == 1), "four wavefronts, 16 tokens and two sweeps each");
         unsigned char* scratch = smem + (SHARE ? KW * PART : wt * WAVE_LDS);
-        static_assert((SHARE ? KW * PART : 0) + TL::NW * WAVE_LDS <= GemmV2Lds<SPARSE, OUT_I_CONTIG, EPI, BLOCKED, FP8, TL, MG>::BYTES, "epilogue scratch must fit in the main-loop LDS");
+        static_assert((SHARE ? KW * PART : 0) + TL::NW * WAVE_LDS <= GemmV2Lds<SPARSE, OUT_I_CONTIG, EPI, BLOCKED, FP8, TL, MG, PRUNE != 0>::BYTES, "epilogue scratch must fit in the main-loop LDS");
         unsigned char* ttile = scratch + WN * EP;
         // EPI: i = hidden unit f, j = token t; the wave's 64 tokens are exactly one V = 64 block and each half of
         // 64 f holds 8 whole column blocks, so the V:N:M work is wave-local.
@@ -926,12 +964,12 @@ inline unsigned grid_tiles(int64_t Ra, int64_t Rb, const GemmGroup& g, int BM, i
 }
 
 // one contraction as a unit that launch_units (launch_mix.hpp) puts into a launch, alone or with others
-template <bool SPARSE, bool OUT_I_CONTIG, int EPI, bool BLOCKED, bool FP8, class TL, bool BROW = false, bool MG = false>
+template <bool SPARSE, bool OUT_I_CONTIG, int EPI, bool BLOCKED, bool FP8, class TL, bool BROW = false, bool MG = false, int PRUNE = 0>
 struct GemmV2Unit {
     using Args = GemmV2Args;
-    static constexpr int THREADS = TL::THREADS, LDS = GemmV2Lds<SPARSE, OUT_I_CONTIG, EPI, BLOCKED, FP8, TL, MG>::BYTES;
+    static constexpr int THREADS = TL::THREADS, LDS = GemmV2Lds<SPARSE, OUT_I_CONTIG, EPI, BLOCKED, FP8, TL, MG, PRUNE != 0>::BYTES;
     static __device__ __forceinline__ void run(unsigned char* smem, int pid, int n_pid, const Args& a) {
-        gemm_nt_v2_body<SPARSE, OUT_I_CONTIG, EPI, BLOCKED, FP8, TL, BROW, MG>(smem, pid, n_pid, a.a_vals, a.a_meta, a.B, a.bias, a.Ra, a.Rb, a.K, a.out, a.ldo, a.tiles_m, a.tiles_n,
+        gemm_nt_v2_body<SPARSE, OUT_I_CONTIG, EPI, BLOCKED, FP8, TL, BROW, MG, PRUNE>(smem, pid, n_pid, a.a_vals, a.a_meta, a.B, a.bias, a.Ra, a.Rb, a.K, a.out, a.ldo, a.tiles_m, a.tiles_n,
                                                                      a.ep, a.grp, a.alpha);
     }
     static unsigned count(const Args& a) { return grid_tiles(a.Ra, a.Rb, a.grp, TL::BM, TL::BN); }
