@@ -990,6 +990,7 @@ static int run_router_step(const sffn_cfg* cfg, const int64_t* seg_offsets, cons
     ep1.mode = 3; ep1.store_dense = 1; ep1.vals = vals; ep1.meta = meta; ep1.perm = perm; ep1.logM = logM; ep1.v24 = avb; ep1.m24 = amb; ep1.at = at; ep1.at_ld = rows;
     // eq. (4) at the expert's hidden units, then eq. (6) on y2's slots while the tile is in LDS; dy2c itself only on request
     ep4.mode = 4; ep4.store_dense = (cfg->flags & SFFN_FLAG_KEEP_DENSE) ? 1 : 0; ep4.vals = dvals; ep4.meta = meta; ep4.ykept = y1c; ep4.v24 = avb2; ep4.at = at2; ep4.at_ld = rows;
+    ep1.stream = ep4.stream = streams_between(rows, D, F, 1, 6 * rows * Kc + 4 * F * D);
     GemmGroup g4 = g1;
     g4.bias_stride = 0;
     const VnmEpilogue plain;
@@ -1333,7 +1334,7 @@ static int run_step(const sffn_cfg* cfg, int n_experts, const int64_t* seg, cons
     }
     // Small inputs: one launch.  Larger ones (half of the last-level cache and more): each pass right before the contraction that reads its
     // results, while they are still cached (T = D = 8192, F = 28672: eq. (1) is 1-2 % slower when all passes come first).
-    const bool together = tiles.mix || prologue_together(T, D, F, E);
+    const bool together = tiles.mix || prologue_together(T, D, F, E), streamed = streams_between(T, D, F, E, 2 * T * F);
     PrologueArgs part[3];
     split_prologue(pro, part);
     const bool x_as_is = fwd && forward_reads_x(T, D, F, E, cfg->M, packed, tiles.g);
@@ -1344,14 +1345,14 @@ static int run_step(const sffn_cfg* cfg, int n_experts, const int64_t* seg, cons
     if (fwd) {   // eq. (1), then eq. (2) + V:N:M compression on the tile while it is still in LDS
         VnmEpilogue ep;
         ep.mode = 1; ep.store_dense = keep_dense; ep.vals = lean ? nullptr : y2v; ep.meta = y2m; ep.colidx = cix; ep.kmask = kmask; ep.ykept = ykept;
-        ep.vcb = vcb; ep.mcb = mcb; ep.cixt = cixt; ep.at = atb;
+        ep.vcb = vcb; ep.mcb = mcb; ep.cixt = cixt; ep.at = atb; ep.stream = streamed;
         if (x_as_is) STAGE(launch_forward_x(w1vb, w1mb, b1, X, y1, ep, behind, s, gp, tiles.g), "step/y1+sqrelu_vnm_compress");
         else STAGE(launch_gemm_vnm_epilogue(w1vb, w1mb, xb, b1, F, T, D, y1, ep, s, gp, tiles.g), "step/y1+sqrelu_vnm_compress");
     }
     // eq. (4), then eq. (6) on y2's kept slots
     VnmEpilogue ep4;
     ep4.mode = 2; ep4.store_dense = keep_dense; ep4.vals = lean ? nullptr : dy1v; ep4.meta = y2m; ep4.colidx = cix; ep4.ykept = ykept;
-    ep4.vcb = vcb2; ep4.mcb = mcb; ep4.at = at2;
+    ep4.vcb = vcb2; ep4.mcb = mcb; ep4.at = at2; ep4.stream = streamed;
     if (tiles.mix) {
         const GemmGroup none;
         const Vnm8Args v3 = {vcb, mcb, cixt, (const uint8_t*)w2t, (int)D, (int)T, (int)D, (int)F, Y3, D, 0, 0, gd ? *gd : none, 1.0f, split};

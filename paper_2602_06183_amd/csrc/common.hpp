@@ -20,6 +20,13 @@ __device__ __forceinline__ float bf2f(uint32_t h) { return __uint_as_float(h << 
 typedef __attribute__((ext_vector_type(4))) uint32_t sffn_u32x4;
 __device__ __forceinline__ void store_out(void* p, const uint4& w) { __builtin_nontemporal_store(__builtin_bit_cast(sffn_u32x4, w), reinterpret_cast<sffn_u32x4*>(p)); }
 __device__ __forceinline__ void store_out(void* p, const float4& w) { store_out(p, __builtin_bit_cast(uint4, w)); }
+// What an epilogue leaves for the launches that follow, non-temporal where `stream` (the same in the whole launch: streams_between() in kernels.hpp).  Without the barriers the compiler makes one
+// ordinary store of the two.
+template <class T> __device__ __forceinline__ void store_between(T* p, T w, bool stream) {
+    if (stream) { asm volatile("" ::: "memory"); __builtin_nontemporal_store(w, p); asm volatile("" ::: "memory"); }
+    else *p = w;
+}
+__device__ __forceinline__ void store_between(void* p, const uint4& w, bool stream) { store_between(reinterpret_cast<sffn_u32x4*>(p), __builtin_bit_cast(sffn_u32x4, w), stream); }
 
 // fp32 -> bf16 bits, round to nearest even, through gfx950's v_cvt_pk_bf16_f32 (checked against integer
 // rounding on every bf16 pattern x tie / near-tie low halves, subnormals included; only NaN payloads differ).

@@ -19,6 +19,7 @@ namespace sffn {
 struct VnmEpilogue {
     int mode = 0;                   // 0: no V:N:M epilogue, only the dense output
     int store_dense = 1;
+    int stream = 0;                 // modes 1 / 2 (bf16), 3 / 4: at, ykept, vcb, vals go out non-temporal (streams_between)
     uint16_t* vals = nullptr;
     uint8_t* meta = nullptr;
     uint8_t* colidx = nullptr;
@@ -125,6 +126,12 @@ struct PrologueArgs {
 hipError_t launch_step_prologue(const PrologueArgs& a, hipStream_t s);
 // The step's preparing passes: all in one launch while X, dY, W1 and W2 together stay below 96 MiB, else in three parts (X and W1 | W2 | dY)
 inline bool prologue_together(int64_t T, int64_t D, int64_t F, int64_t E) { return 2 * (2 * T * D + 2 * E * F * D) < ((int64_t)96 << 20); }
+// Do the epilogues at M = 8 in bf16, and the router's, store what later launches read (`between`: bytes of a direction, prepared copies) non-temporal?  Where that and the inputs are more than the
+// last-level cache of 256 MiB holds: ordinary stores then push the operands that the tiles share out of it, and are themselves gone before they are read.  Where all of it fits the readers find
+// it there.  Steps, ordinary / non-temporal: T = 8192, D = 2048, F = 8192 (256 MiB) 907 / 894 us, T = 9664, D = 2752, F = 6016 (274) 1252 / 1228, T = 10496, D = 576, F = 13120 (313) 794 / 768,
+// T = D = 8192, F = 28672 11034 / 10963; T = 896, D = 1792, F = 5184 (50) 110 / 124, T = 6720, D = 2752, F = 7488 (245) 1147 / 1165; the router's, T = 8192, D = 2048, F = 8192, M = 16 498 / 492,
+// T = 10240, D = 576, F = 2560, M = 8 202 / 221.  Over 37 drawn steps that it takes 0.992, two of them 0.7 and 1.0 % longer.  M = 16, 32, 64 0.97 - 0.99 and codes 1.00 of the rate: not there.
+inline bool streams_between(int64_t T, int64_t D, int64_t F, int64_t E, int64_t between) { return 4 * (T * D + E * F * D) + between >= (int64_t)250 << 20; }
 // Eq. (1) with X row-major and the passes `behind` in the same launch (forward_x.hip); tile 64 or 128.
 hipError_t launch_forward_x(const uint16_t* a_vals, const uint8_t* a_meta, const float* bias, const uint16_t* X, uint16_t* out, const VnmEpilogue& ep,
                             const PrologueArgs& behind, hipStream_t s, const GemmGroup* grp, int tile);

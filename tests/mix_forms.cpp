@@ -1,6 +1,7 @@
 // Prints which contractions of a step's shared launches take tall tiles (mix_plan.hpp), for tests/test_mix_forms.py.  One line of standard input is one call:
 //   <fp8> <M> <D> <F> <T>   -> does the step share launches; the forms of eqs. (3), (5), (4), of (5), (4) and of (7), (8)
 //   alone <fp8> <T> <N> <F> -> eqs. (3), (7) and (bf16) (5), (8) in launches of their own: the tile that the rules choose, is it a tall one instead (64 tiles, three workgroups a CU: no)
+//   streams <T> <D> <F>     -> do the epilogues' stores go past the caches
 //   play <slots> <n> <time> <alone> ... (three times)   -> time of the launch
 #include <stdio.h>
 #include <string.h>
@@ -20,6 +21,12 @@ int main() {
             if (scanf("%f", &slots) != 1) return 1;
             for (MixUnit& x : u) if (scanf("%f %f %f", &x.n, &x.time, &x.alone) != 3) return 1;
             printf("%.4f\n", mix_time(u, 3, slots));
+            continue;
+        }
+        if (!strcmp(first, "streams")) {
+            long T, D, F;
+            if (scanf("%ld %ld %ld", &T, &D, &F) != 3) return 1;
+            printf("%d\n", (int)streams_between(T, D, F, 1, 2 * T * F));
             continue;
         }
         if (!strcmp(first, "alone")) {

@@ -51,6 +51,15 @@ def test_step(T, D, F, forms):
     assert torch.equal(two.dW1.to(torch.bfloat16), dW1) and torch.equal(two.dW2.to(torch.bfloat16), dW2)
 
 
+# T, D, F whose epilogues store past the caches, on tiles of 64, 128, 256
+STREAMED = [(64, 8192, 8128), (704, 5760, 10944), (1344, 5120, 11264)]
+
+
+@pytest.mark.parametrize("T,D,F", STREAMED)
+def test_step_that_stores_past_the_caches(T, D, F):
+    test_step(T, D, F, None)
+
+
 @pytest.mark.parametrize("M,T,D,F,forms", WIDE)
 def test_step_of_wide_blocks(M, T, D, F, forms):
     inp = make_ffn_inputs(T, D, F, seed=62)

@@ -47,3 +47,9 @@ def test_launches_of_their_own_of_the_gpu_tests(forms):
     # codes: gradients never; no activation contraction whose tiles all have a CU
     small = [(fp8, T, 512, F) for fp8 in (0, 1) for T in (64, 512, 2048) for F in (512, 4096)]
     assert all(line[1] == "0" and line[3] == "0" for line in forms(["alone %d %d %d %d" % c for c in small]))
+
+
+def test_streamed_steps_of_the_gpu_tests(forms):
+    from tests.test_gpu_tall_tiles import STREAMED
+    assert [r[0] for r in forms(["streams %d %d %d" % c for c in STREAMED])] == ["1"] * len(STREAMED)
+    assert [r[0] for r in forms(["streams 4096 1024 4096", "streams 8192 8192 28672"])] == ["0", "1"]
