@@ -228,7 +228,7 @@ __device__ __forceinline__ void vnm_gather_body(unsigned char* __restrict__ smem
             join4(acc, smem, wave, lane, q);
             store_quarter(q, 1.0f, smem + kJoin4, wave, lane, out, ldo, t0, n0, t0 + 64, N);
         } else if (split_join4(acc, smem, split, L, sp, wave, lane, q)) {
-            store_quarter(q, 1.0f, smem, wave, lane, out, ldo, t0, n0, t0 + 64, N);
+            store_quarter(q, 1.0f, smem + kJoin4, wave, lane, out, ldo, t0, n0, t0 + 64, N);
         }
         return;
     }

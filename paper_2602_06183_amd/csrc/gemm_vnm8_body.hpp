@@ -366,7 +366,7 @@ __device__ __forceinline__ void vnm8_gemm_body(unsigned char* __restrict__ smem,
             join4(acc, smem, wave, lane, q);
             store_quarter(q, FP8 ? alpha : 1.0f, smem + kJoin4, wave, lane, out, ldo, i0, n0, Ra, N);
         } else if (split_join4(acc, smem, split, tile, sp, wave, lane, q)) {
-            store_quarter(q, FP8 ? alpha : 1.0f, smem, wave, lane, out, ldo, i0, n0, Ra, N);
+            store_quarter(q, FP8 ? alpha : 1.0f, smem + kJoin4, wave, lane, out, ldo, i0, n0, Ra, N);
         }
         return;
     }

@@ -316,7 +316,7 @@ inline SplitPlan plan_gather(int64_t T, int64_t N, int steps, int groups) {
     auto split = [](int64_t w, float stages) { return 0.5f * (float)((w + 255) / 256) * stages + 6.0f + (float)(w * 64 * 64) * 8.0f / 4.0e6f; };
     return plan_split(T, N, steps, tile, 0.85f * 0.5f * (float)((((T + 63) / 64) * ((N + 63) / 64) + 255) / 256) * (float)steps, split);
 }
-// bytes of the sums and, behind them, of the counters (one per tile: with 2 and more splits of 8 and more stages there are at most kSplitMost / 32 KB)
+// bytes of the sums and, behind them, of the counters (a word per tile, spread over the lines: with 2 and more splits of 8 and more stages there are at most kSplitMost / 32 KB)
 inline size_t split_part_bytes(const SplitPlan& p, int64_t T, int64_t N) {
     return p.n > 1 ? (size_t)(((T + p.tile - 1) / p.tile) * ((N + p.tile - 1) / p.tile)) * p.tile * p.tile * 4 * p.n : 0;
 }

@@ -1,7 +1,7 @@
 // A contraction shared by several workgroups of one output tile (eqs. (3), (7) on few tokens: 64 x 64 tiles of a T = 64 call occupy N / 64 of the 256
 // CUs, and what bounds them is the rate at which one CU can be fed).  Split s contracts its own range of stages; every workgroup leaves its float32
-// sums in memory and counts itself in; the one that finds the others there adds all of them in the order of the splits, so the result does not depend
-// on who was last, and goes on to the output.  Nothing waits.  The counters are zero before the launch (the step's preparing launch clears them)
+// sums in memory and counts itself in; those that find the others there add all of them in the order of the splits, so the result does not depend
+// on who was last, and go on to the output.  Nothing waits.  The counters are zero before the launch (the step's preparing launch clears them)
 // and zero after it.
 #pragma once
 #include "common.hpp"
@@ -35,7 +35,10 @@ __device__ __forceinline__ void join4(const f32x16 (&acc)[2][2], unsigned char* 
     }
 }
 
-// The same over the workgroups that share the tile too.  false: the others are not there yet, the workgroup is done.
+// The same over the workgroups that share the tile too.  false: the others are not there yet, the wavefront is done.  Every wavefront counts in by itself when its quarter is out and sums that
+// quarter if it is the last to come.  The counts bound it: an atomic takes its line for 6 ns, and 32 tiles of 8 splits that count on one line are 1.5 us.  Forward calls of T = 64, D = 2048,
+// F = 8192 (32 tiles, 8 splits) and T = 128 (64, 4): one count a workgroup, on consecutive words 21.1 and 23.2 us; on a line a tile 20.3, 22.9; one a wavefront on those lines 19.8, 22.6,
+// on consecutive words 25.1, 27.0.  Eight splits' loads at a time instead of four: 0.4 us of the first.
 __device__ __forceinline__ bool split_join4(const f32x16 (&acc)[2][2], unsigned char* smem, const Split& sp, int tile, int s, int wave, int lane, float (&q)[16]) {
     join4(acc, smem, wave, lane, q);
     unsigned long long* const p = reinterpret_cast<unsigned long long*>(sp.part) + ((int64_t)tile * sp.n * 4 + wave) * (8 * 64) + lane;
@@ -44,28 +47,30 @@ __device__ __forceinline__ bool split_join4(const f32x16 (&acc)[2][2], unsigned 
         __hip_atomic_store(p + (s * 4 * 8 + k) * 64, (unsigned long long)__float_as_uint(q[2 * k]) | ((unsigned long long)__float_as_uint(q[2 * k + 1]) << 32), __ATOMIC_RELAXED,
                            __HIP_MEMORY_SCOPE_AGENT);
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    __syncthreads();                     // (all four quarters are out, and the LDS sums have been read)
-    unsigned* const last = reinterpret_cast<unsigned*>(smem);
-    if (wave == 0 && lane == 0) *last = __hip_atomic_fetch_add(sp.count + tile, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1 == (unsigned)sp.n;
-    __syncthreads();
-    const bool go = *last != 0;
-    __syncthreads();
-    if (!go) return false;
-    if (wave == 0 && lane == 0) sp.count[tile] = 0;
+    // a byte of the tile's word for each quarter; consecutive tiles on different lines
+    unsigned* const count = sp.count + (tile & 31) * 32 + (tile >> 5);
+    const unsigned one = 1u << (8 * wave);
+    unsigned before = 0;
+    if (lane == 0) before = __hip_atomic_fetch_add(count, one, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if ((uniform((int)before) >> (8 * wave) & 0xFF) + 1 != sp.n) return false;
+    if (lane == 0) __hip_atomic_fetch_sub(count, one * (unsigned)sp.n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 #pragma unroll
     for (int k = 0; k < 16; ++k) q[k] = 0.0f;
-    for (int g0 = 0; g0 < sp.n; g0 += 4) {                  // four splits' loads at a time
-        unsigned long long v[4][8];
+    auto add = [&](int g0, auto batch) {                    // the loads of `batch` splits at a time
+        constexpr int B = decltype(batch)::value;
+        unsigned long long v[B][8];
 #pragma unroll
-        for (int g = 0; g < 4; ++g)
+        for (int g = 0; g < B; ++g)
 #pragma unroll
             for (int k = 0; k < 8; ++k)
                 v[g][k] = g0 + g < sp.n ? __hip_atomic_load(p + ((g0 + g) * 4 * 8 + k) * 64, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0ull;
 #pragma unroll
-        for (int g = 0; g < 4; ++g)
+        for (int g = 0; g < B; ++g)
 #pragma unroll
             for (int k = 0; k < 8; ++k) { q[2 * k] += __uint_as_float((uint32_t)v[g][k]); q[2 * k + 1] += __uint_as_float((uint32_t)(v[g][k] >> 32)); }
-    }
+    };
+    if (sp.n <= 4) add(0, std::integral_constant<int, 4>());
+    else for (int g0 = 0; g0 < sp.n; g0 += 8) add(g0, std::integral_constant<int, 8>());
     return true;
 }
 

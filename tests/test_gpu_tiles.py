@@ -132,6 +132,19 @@ def test_split_activation_contractions(M, T, D, F):
     assert_gemm_close(to_bits(alone), to_bits(first[0]), "y3 alone")
 
 
+@pytest.mark.parametrize("M,T,N,F", [(8, 64, 192, 16384), (8, 512, 1024, 16384), (16, 64, 64, 65536)])
+def test_most_splits_and_most_tiles(M, T, N, F):
+    """16 workgroups a tile; 128 tiles, whose counters share lines.  Over and over: every call finds its counters as it needs them."""
+    rng = np.random.default_rng(36)
+    y1 = bf16_bits_from_f32(rng.standard_normal((T, F)).astype(np.float32))
+    W = bf16_bits_from_f32(rng.standard_normal((N, F)).astype(np.float32) * np.float32(0.02))
+    a = sffn.sqrelu_vnm_compress(to_dev(y1), 64, M)
+    first = sffn.vnm_spmm(*a, to_dev(W), 0, 64, M)
+    assert_gemm_close(to_bits(first), oracle.vnm_spmm(*[to_bits(t) for t in a], W, 0, 64, M), "spmm")
+    for _ in range(20):
+        assert torch.equal(first, sffn.vnm_spmm(*a, to_dev(W), 0, 64, M))
+
+
 @pytest.mark.parametrize("wgrad_fp8,dw_fp32", [(False, False), (True, True)])
 def test_split_activation_contractions_of_the_fp8_step(wgrad_fp8, dw_fp32):
     """The same on codes, in the steps that do not share launches: against the oracle, and twice in a row."""
