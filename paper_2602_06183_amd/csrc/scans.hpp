@@ -17,15 +17,20 @@ __device__ __forceinline__ void transpose_bf16_body(void* smem, int bx, int by, 
     uint16_t (*tile)[64 + 2] = reinterpret_cast<uint16_t (*)[64 + 2]>(smem);
     const int tid = threadIdx.x;
     const int64_t r0 = (int64_t)by * 64, c0 = (int64_t)bx * 64;
+    uint4 w[2];                              // both loads before either is waited for, so no branch around them
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
         const int e = tid + 256 * i, rr = e >> 3, seg = e & 7;
         int64_t rs = r0 + rr;
         if (in_perm) rs = in_perm[rs];
-        uint4 w = make_uint4(0, 0, 0, 0);
-        if (rs >= 0) w = *reinterpret_cast<const uint4*>(in + rs * ld + c0 + seg * 8);
+        w[i] = *reinterpret_cast<const uint4*>(in + (rs < 0 ? 0 : rs) * ld + c0 + seg * 8);
+        if (rs < 0) w[i] = make_uint4(0, 0, 0, 0);
+    }
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const int e = tid + 256 * i, rr = e >> 3, seg = e & 7;
         uint32_t* p = reinterpret_cast<uint32_t*>(&tile[rr][seg * 8]);
-        p[0] = w.x; p[1] = w.y; p[2] = w.z; p[3] = w.w;
+        p[0] = w[i].x; p[1] = w[i].y; p[2] = w[i].z; p[3] = w[i].w;
     }
     __syncthreads();
 #pragma unroll
@@ -73,13 +78,17 @@ __device__ __forceinline__ void prune24_cols_body(void* smem, int bx, int by, in
         if (vblk) { vblk += m / 2; mblk += m / 8; }
         if (src_t) src_t += m;
     }
+    // all four loads before the first is waited for, so no branch around them: rows past the end, whose results go nowhere, are the last row again (T = 4096 x 8192: 9.8 -> 8.1 us)
+    uint4 w[4];
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-        const int kk = tid / 8 + 32 * i, seg = tid % 8;
-        uint4 w = make_uint4(0, 0, 0, 0);
-        if (k0 + kk < K) w = *reinterpret_cast<const uint4*>(src + (int64_t)(k0 + kk) * ld + r0 + seg * 8);
-        uint32_t* p = reinterpret_cast<uint32_t*>(&tile[kk * PITCH + seg * 8]);
-        p[0] = w.x; p[1] = w.y; p[2] = w.z; p[3] = w.w;
+        const int k = k0 + tid / 8 + 32 * i;
+        w[i] = *reinterpret_cast<const uint4*>(src + (int64_t)(k < K ? k : K - 1) * ld + r0 + (tid % 8) * 8);
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        uint32_t* p = reinterpret_cast<uint32_t*>(&tile[(tid / 8 + 32 * i) * PITCH + (tid % 8) * 8]);
+        p[0] = w[i].x; p[1] = w[i].y; p[2] = w[i].z; p[3] = w[i].w;
     }
     __syncthreads();
     if (src_t) {        // the unpruned transposed tile: logical rows r (64) x k (128) -> [R, K] row-major, 16 bytes per thread and pass
@@ -88,11 +97,11 @@ __device__ __forceinline__ void prune24_cols_body(void* smem, int bx, int by, in
             // row r0 + tr, k segment of 8 starting at 8 ks: 16 lanes take 256 consecutive bytes of a row
             const int e = tid + 256 * i, tr = e >> 4, ks = e & 15;
             if (k0 + 8 * ks < K) {
-                uint32_t w[4];
+                uint32_t o[4];
 #pragma unroll
                 for (int j = 0; j < 4; ++j)
-                    w[j] = tile[(8 * ks + 2 * j) * PITCH + tr] | ((uint32_t)tile[(8 * ks + 2 * j + 1) * PITCH + tr] << 16);
-                *reinterpret_cast<uint4*>(src_t + (r0 + tr) * K + k0 + 8 * ks) = make_uint4(w[0], w[1], w[2], w[3]);
+                    o[j] = tile[(8 * ks + 2 * j) * PITCH + tr] | ((uint32_t)tile[(8 * ks + 2 * j + 1) * PITCH + tr] << 16);
+                *reinterpret_cast<uint4*>(src_t + (r0 + tr) * K + k0 + 8 * ks) = make_uint4(o[0], o[1], o[2], o[3]);
             }
         }
     }

@@ -60,6 +60,21 @@ def test_prune24_hard_on_every_bit_pattern(trans):
     assert np.array_equal(to_bits(vals), rv)
 
 
+@pytest.mark.parametrize("trans", [False, True])
+@pytest.mark.parametrize("mode", [sffn.MODE_HARD, sffn.MODE_SOFT])
+def test_prune24_on_all_groups_of_special_values(mode, trans):
+    """Every group of four of zeros, subnormals, equal magnitudes of either sign, the largest finite values, infinities and (HARD: bit copies) NaN."""
+    pick = [0x0000, 0x8000, 0x0001, 0x8001, 0x007F, 0x0080, 0x8080, 0x3F80, 0xBF80, 0x3F81, 0x7F7F, 0xFF7F, 0x7F80, 0xFF80] + ([0x7FC1, 0xFFFF] if mode == sffn.MODE_HARD else [])
+    g = np.array(np.meshgrid(pick, pick, pick, pick), dtype=np.uint16).reshape(4, -1).T
+    S = np.zeros((64, (-(-len(g) // 64) + 15) // 16 * 64), dtype=np.uint16)
+    S.reshape(-1)[:g.size] = g.reshape(-1)
+    vals, meta = sffn.prune24_compress(to_dev(np.ascontiguousarray(S.T) if trans else S), trans=trans, mode=mode)
+    rv, rm = oracle.prune24_compress(S, mode)
+    assert np.array_equal(to_bits(meta), rm)
+    v, nan = to_bits(vals), lambda b: (b & 0x7FFF) > 0x7F80
+    assert np.array_equal(nan(v), nan(rv)) and np.array_equal(np.where(nan(v), 0, v), np.where(nan(rv), 0, rv)) and (mode == sffn.MODE_SOFT or np.array_equal(v, rv))
+
+
 def test_prune24_rows_strided():
     rng = np.random.default_rng(5)
     big = rnd_bits(rng, (128, 384), 0.02)
