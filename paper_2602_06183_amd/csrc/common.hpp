@@ -20,6 +20,11 @@ __device__ __forceinline__ float bf2f(uint32_t h) { return __uint_as_float(h << 
 typedef __attribute__((ext_vector_type(4))) uint32_t sffn_u32x4;
 __device__ __forceinline__ void store_out(void* p, const uint4& w) { __builtin_nontemporal_store(__builtin_bit_cast(sffn_u32x4, w), reinterpret_cast<sffn_u32x4*>(p)); }
 __device__ __forceinline__ void store_out(void* p, const float4& w) { store_out(p, __builtin_bit_cast(uint4, w)); }
+// 16 bytes of an operand that is read once; PAST: non-temporal
+template <bool PAST> __device__ __forceinline__ uint4 load_in(const void* p) {
+    if (PAST) return __builtin_bit_cast(uint4, __builtin_nontemporal_load(reinterpret_cast<const sffn_u32x4*>(p)));
+    return *reinterpret_cast<const uint4*>(p);
+}
 // What an epilogue leaves for the launches that follow, non-temporal where `stream` (the same in the whole launch: streams_between() in kernels.hpp).  Without the barriers the compiler makes one
 // ordinary store of the two.
 template <class T> __device__ __forceinline__ void store_between(T* p, T w, bool stream) {

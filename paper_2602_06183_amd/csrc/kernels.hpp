@@ -531,6 +531,10 @@ inline bool router_shares(int64_t rows, int64_t D, int64_t F, int M) {
     return pick_gemm_tile(rows, D, steps3, g, small_round(kGemmPlain, steps3), true, last_round(kGemmPlain, steps3)) == 128;
 }
 
+// Do the stand-alone packing operations read their operands past the caches?  Where these are as large as the last-level cache, which then holds none of them, whoever wrote them, but takes time to be
+// filled.  Ordinary / past, operands in turn: SquaredReLU and compression of 512 MiB 123 / 113 us, of 896 MiB 222 / 196, eq. (6) on 256 MiB 50 / 46, on 1 GiB 205 / 191, pruning of 448 MiB along rows
+// 128 / 109, across 161 / 136; right after a copy has written them 332 / 321, 92 / 88, 412 / 400.  Smaller ones are found there: 64 MiB of y1 18 / 19, the same 128 MiB at M = 16 over and over 25 / 29.
+inline bool reads_past(int64_t bytes) { return bytes >= (int64_t)256 << 20; }
 hipError_t launch_prune24(const uint16_t* src, int64_t R, int64_t K, int64_t ld, int trans, int mode, uint16_t* vals,
                           uint8_t* meta, hipStream_t stream);
 hipError_t launch_dsqrelu_vnm(const uint16_t* dy2, const uint16_t* y1, const uint8_t* meta, const uint8_t* colidx,

@@ -19,11 +19,11 @@ namespace sffn {
 // reads and, but for columns that meet by chance, the 2-byte reads then touch every bank once.
 // Survivors and metadata of the four wavefronts meet in LDS and leave as whole rows of the workgroup: with every wavefront storing its own 32 and 4 bytes of
 // a row, T = F = 16384, M = 8 takes 153 us, with whole rows 124.
-//   Bound: HBM.  T = F = 16384: M = 8 147 -> 124 us (0.69 GB, 5.6 TB/s), M = 16 135 -> 117, 32 132 -> 115, 64 154 -> 106; T = F = 8192: 35 -> 29, 31 -> 26,
+//   Bound: HBM.  T = F = 16384: M = 8 147 -> 124 us (0.69 GB, 5.6 TB/s; 111 with the loads past the caches and the rows stored non-temporal), M = 16 135 -> 117, 32 132 -> 115, 64 154 -> 106; T = F = 8192: 35 -> 29, 31 -> 26,
 //   33 -> 24, 42 -> 24.  (Before: one 2-byte LDS read per score term, M comparisons per column, ranks out of six comparisons per pair.)  43 KB of LDS, three
 //   workgroups per CU: with the survivors in the tile's place four fit, and M = 8 takes 132 us, M = 32 119; two: 31 us at T = F = 8192.
 __device__ __forceinline__ uint32_t swz(uint32_t r) { return (((r >> 1) & 1u) << 2) | ((r >> 2) & 1u); }
-template <int M>
+template <int M, bool PAST>
 __global__ void __launch_bounds__(256) sqrelu_vnm_compress_m_kernel(const uint16_t* __restrict__ y1, int64_t F,
                                                                    uint16_t* __restrict__ vals, uint8_t* __restrict__ meta,
                                                                    uint8_t* __restrict__ colidx) {
@@ -41,7 +41,7 @@ __global__ void __launch_bounds__(256) sqrelu_vnm_compress_m_kernel(const uint16
         uint4 w[8];
         const uint16_t* src = y1 + (tb * 64 + r8) * F + c0 + seg * 8;
 #pragma unroll
-        for (int it = 0; it < 8; ++it) w[it] = *reinterpret_cast<const uint4*>(src + it * 8 * F);
+        for (int it = 0; it < 8; ++it) w[it] = load_in<PAST>(src + it * 8 * F);
 #pragma unroll
         for (int it = 0; it < 8; ++it) {
             w[it] = make_uint4(sqrelu2(w[it].x), sqrelu2(w[it].y), sqrelu2(w[it].z), sqrelu2(w[it].w));
@@ -121,8 +121,7 @@ __global__ void __launch_bounds__(256) sqrelu_vnm_compress_m_kernel(const uint16
         const int e = threadIdx.x + 256 * i, row = e / LANES, j = e % LANES;
         if (M == 8) {
             if (b0 + j * 32 < F)
-                *reinterpret_cast<uint4*>(vals + (tb * 64 + row) * (F / 4) + b0 / 4 + j * 8) =
-                    *reinterpret_cast<const uint4*>(packed[j >> 1] + ((row * 32 + (j & 1) * 16) ^ ((j & 2) << 6)));
+                store_out(vals + (tb * 64 + row) * (F / 4) + b0 / 4 + j * 8, *reinterpret_cast<const uint4*>(packed[j >> 1] + ((row * 32 + (j & 1) * 16) ^ ((j & 2) << 6))));
         } else if (b0 + j * M < F) {
             *reinterpret_cast<uint32_t*>(vals + (tb * 64 + row) * (2 * F / M) + (b0 / M + j) * 2) = *reinterpret_cast<const uint32_t*>(packed[j / NB] + (row * NB + j % NB) * 4);
         }
@@ -218,13 +217,18 @@ __global__ void __launch_bounds__(256) vnm_expand_t_m_kernel(const uint16_t* __r
     }
 }
 
+template <int M>
+static void launch_compress(const uint16_t* y1, int64_t T, int64_t F, uint16_t* vals, uint8_t* meta, uint8_t* colidx, hipStream_t s) {
+    const dim3 grid((unsigned)((F + 255) / 256), (unsigned)(T / 64));
+    if (reads_past(2 * T * F)) hipLaunchKernelGGL((sqrelu_vnm_compress_m_kernel<M, true>), grid, dim3(256), 0, s, y1, F, vals, meta, colidx);
+    else hipLaunchKernelGGL((sqrelu_vnm_compress_m_kernel<M, false>), grid, dim3(256), 0, s, y1, F, vals, meta, colidx);
+}
 hipError_t launch_sqrelu_vnm_compress_m(const uint16_t* y1, int64_t T, int64_t F, int M, uint16_t* vals, uint8_t* meta, uint8_t* colidx,
                                         hipStream_t s) {
-    dim3 grid((unsigned)((F + 255) / 256), (unsigned)(T / 64));
-    if (M == 8)       hipLaunchKernelGGL((sqrelu_vnm_compress_m_kernel<8>), grid, dim3(256), 0, s, y1, F, vals, meta, colidx);
-    else if (M == 16) hipLaunchKernelGGL((sqrelu_vnm_compress_m_kernel<16>), grid, dim3(256), 0, s, y1, F, vals, meta, colidx);
-    else if (M == 32) hipLaunchKernelGGL((sqrelu_vnm_compress_m_kernel<32>), grid, dim3(256), 0, s, y1, F, vals, meta, colidx);
-    else if (M == 64) hipLaunchKernelGGL((sqrelu_vnm_compress_m_kernel<64>), grid, dim3(256), 0, s, y1, F, vals, meta, colidx);
+    if (M == 8)       launch_compress<8>(y1, T, F, vals, meta, colidx, s);
+    else if (M == 16) launch_compress<16>(y1, T, F, vals, meta, colidx, s);
+    else if (M == 32) launch_compress<32>(y1, T, F, vals, meta, colidx, s);
+    else if (M == 64) launch_compress<64>(y1, T, F, vals, meta, colidx, s);
     else return hipErrorInvalidValue;
     return hipGetLastError();
 }

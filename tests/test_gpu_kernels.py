@@ -75,6 +75,30 @@ def test_prune24_on_all_groups_of_special_values(mode, trans):
     assert np.array_equal(nan(v), nan(rv)) and np.array_equal(np.where(nan(v), 0, v), np.where(nan(rv), 0, rv)) and (mode == sffn.MODE_SOFT or np.array_equal(v, rv))
 
 
+@pytest.mark.parametrize("M", [8, 16, 32, 64])
+def test_packing_operations_past_the_caches(M):
+    """Operands of 256 MiB and more, which are read past the caches, in pieces that are not."""
+    T, F, cut = 8192, 16640, 4160
+    gen = torch.Generator(device="cuda").manual_seed(91)
+    y1, dy2 = (torch.randn((T, F), device="cuda", generator=gen).to(torch.bfloat16) for _ in range(2))
+    y2 = sffn.sqrelu_vnm_compress(y1, 64, M)
+    dvals = sffn.dsqrelu_vnm(dy2, y1, *y2[1:], 64, M)
+    for a, b in ((0, cut - 64), (cut - 64, T)):
+        part = sffn.sqrelu_vnm_compress(y1[a:b], 64, M)
+        for whole, piece, d in zip(y2, part, (1, 1, 64)):
+            assert torch.equal(whole[a // d:b // d], piece)
+    for a in range(0, T, 2048):
+        assert torch.equal(dvals[a:a + 2048], sffn.dsqrelu_vnm(dy2[a:a + 2048], y1[a:a + 2048], y2[1][a:a + 2048], y2[2][a // 64:a // 64 + 32], 64, M))
+    for mode in (sffn.MODE_HARD, sffn.MODE_SOFT):
+        for W in (y1, torch.cat([dy2, y1], 1)[:, 128:128 + F]):       # rows one after the other, and rows of a wider matrix
+            vals, meta = sffn.prune24_compress(W, mode=mode)
+            vt, mt = sffn.prune24_compress(W, trans=True, mode=mode)
+            for a, b in ((0, 4096), (4096, T)):
+                assert all(torch.equal(x[a:b].view(torch.uint8), y.view(torch.uint8)) for x, y in zip((vals, meta), sffn.prune24_compress(W[a:b], mode=mode)))
+                assert all(torch.equal(x.view(torch.uint8), y.view(torch.uint8)) for x, y in zip((vt[:, a // 2:b // 2].contiguous(), mt[:, a // 8:b // 8].contiguous()),
+                                                                                               sffn.prune24_compress(W[a:b], trans=True, mode=mode)))
+
+
 def test_prune24_rows_strided():
     rng = np.random.default_rng(5)
     big = rnd_bits(rng, (128, 384), 0.02)
