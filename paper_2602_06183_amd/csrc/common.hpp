@@ -25,13 +25,17 @@ template <bool PAST> __device__ __forceinline__ uint4 load_in(const void* p) {
     if (PAST) return __builtin_bit_cast(uint4, __builtin_nontemporal_load(reinterpret_cast<const sffn_u32x4*>(p)));
     return *reinterpret_cast<const uint4*>(p);
 }
-// What an epilogue leaves for the launches that follow, non-temporal where `stream` (the same in the whole launch: streams_between() in kernels.hpp).  Without the barriers the compiler makes one
-// ordinary store of the two.
-template <class T> __device__ __forceinline__ void store_between(T* p, T w, bool stream) {
-    if (stream) { asm volatile("" ::: "memory"); __builtin_nontemporal_store(w, p); asm volatile("" ::: "memory"); }
-    else *p = w;
+// What an epilogue leaves for the launches that follow, non-temporal where `stream` (the same in the whole launch: streams_between() in kernels.hpp): `stores` is called with the store to use.
+// Without the barriers the compiler makes ordinary stores of both.
+template <class F> __device__ __forceinline__ void store_between(bool stream, F stores) {
+    if (stream) {
+        asm volatile("" ::: "memory");
+        stores([](auto* p, auto w) { if constexpr (sizeof(w) == 16) store_out(p, w); else __builtin_nontemporal_store(w, p); });
+        asm volatile("" ::: "memory");
+    } else {
+        stores([](auto* p, auto w) { *reinterpret_cast<decltype(w)*>(p) = w; });
+    }
 }
-__device__ __forceinline__ void store_between(void* p, const uint4& w, bool stream) { store_between(reinterpret_cast<sffn_u32x4*>(p), __builtin_bit_cast(sffn_u32x4, w), stream); }
 
 // fp32 -> bf16 bits, round to nearest even, through gfx950's v_cvt_pk_bf16_f32 (checked against integer
 // rounding on every bf16 pattern x tie / near-tie low halves, subnormals included; only NaN payloads differ).

@@ -521,12 +521,13 @@ __device__ __forceinline__ void gemm_nt_v2_body(unsigned char* __restrict__ smem
                 }
             }
             wave_lds_sync();
+            store_between(ep.stream, [&](auto store) {
 #pragma unroll
-            for (int p = 0; p < 8; ++p) {
-                const int row = p * 8 + (lane >> 3), ch = lane & 7;
-                if (valid)
-                    store_between(ep.at + blk_off(f0 + row, t0 + ch * 8, ep.at_ld / 32), *reinterpret_cast<const uint4*>(scratch + row * EP + (ch ^ ((row >> 4) & 3)) * 16), ep.stream);
-            }
+                for (int p = 0; p < 8; ++p) {
+                    const int row = p * 8 + (lane >> 3), ch = lane & 7;
+                    if (valid) store(ep.at + blk_off(f0 + row, t0 + ch * 8, ep.at_ld / 32), *reinterpret_cast<const uint4*>(scratch + row * EP + (ch ^ ((row >> 4) & 3)) * 16));
+                }
+            });
         };
         const bool stream = !FP8 && ep.stream;
         auto tile_sync = [&]() { if (SHARE) __syncthreads(); else wave_lds_sync(); };
@@ -607,7 +608,7 @@ __device__ __forceinline__ void gemm_nt_v2_body(unsigned char* __restrict__ smem
                     mw |= row_shl<2>(mw) << 8;
                     mw |= row_shl<4>(mw) << 16;
                     if (valid && t0 + t < Rb) {
-                        store_between(reinterpret_cast<uint32_t*>(ep.vals + (int64_t)(t0 + t) * (F / 2) + (f0 >> 1) + 2 * g), v, ep.stream);
+                        store_between(ep.stream, [&](auto store) { store(reinterpret_cast<uint32_t*>(ep.vals + (int64_t)(t0 + t) * (F / 2) + (f0 >> 1) + 2 * g), v); });
                         if ((g & 7) == 0) *reinterpret_cast<uint32_t*>(ep.meta + (int64_t)(t0 + t) * (F / 8) + (f0 >> 3) + (g >> 1)) = mw;
                         if (ep.v24) {       // the same packed matrix in the blocked operand layout (A operand of eqs. (3), (7) over the expert's run)
                             *reinterpret_cast<uint32_t*>(ep.v24 + blk_off(t0 + t, (f0 >> 1) + 2 * g, F / 64)) = v;
@@ -640,7 +641,7 @@ __device__ __forceinline__ void gemm_nt_v2_body(unsigned char* __restrict__ smem
                     const float ya = bf2f(y0 & 0xFFFFu), yb = bf2f(y1 & 0xFFFFu);
                     const uint32_t v = f2bf2(2.0f * bf2f(d0 & 0xFFFFu) * (ya > 0.0f ? ya : 0.0f), 2.0f * bf2f(d1 & 0xFFFFu) * (yb > 0.0f ? yb : 0.0f));
                     if (valid && t0 + t < Rb) {
-                        store_between(reinterpret_cast<uint32_t*>(ep.vals + (int64_t)(t0 + t) * (F / 2) + (f0 >> 1) + 2 * g), v, ep.stream);
+                        store_between(ep.stream, [&](auto store) { store(reinterpret_cast<uint32_t*>(ep.vals + (int64_t)(t0 + t) * (F / 2) + (f0 >> 1) + 2 * g), v); });
                         *reinterpret_cast<uint32_t*>(ep.v24 + blk_off(t0 + t, (f0 >> 1) + 2 * g, F / 64)) = v;
                     }
                     vv[it] = v; nn[it >> 3] |= nib << (4 * (it & 7));
@@ -835,8 +836,10 @@ __device__ __forceinline__ void gemm_nt_v2_body(unsigned char* __restrict__ smem
                         low[it] = lds_u16(((low[it] & 15u) | row0) + it * 8 * EP) | (lds_u16(((high[it] & 15u) | row0) + it * 8 * EP) << 16);
                     }
                     if (valid) {
+                        store_between(stream, [&](auto store) {
 #pragma unroll
-                        for (int it = 0; it < NSW; ++it) store_between(kept_p + lane + it * 64, low[it], stream);
+                            for (int it = 0; it < NSW; ++it) store(kept_p + lane + it * 64, low[it]);
+                        });
                         const uint32_t mt = (lane >> 3) + 8 * bl;
                         if (!SHARE || bl >> 1 == kg) *reinterpret_cast<uint32_t*>(ep.meta + (int64_t)t0 * (F / 16) + (f0 >> 4) + mt * (uint32_t)(F / 16)) = mword;
                         if (!SHARE || bl >> 1 == kg) *reinterpret_cast<uint32_t*>(ep.mcb + (FP8 ? mcb8_off(t0, f0 >> 6, F) : mcb_off(t0, f0 >> 6, F)) + mt * (FP8 ? 8 : 4)) = mword;
@@ -880,33 +883,38 @@ __device__ __forceinline__ void gemm_nt_v2_body(unsigned char* __restrict__ smem
                         vmax_tile = __builtin_fmaxf(vmax_tile, __builtin_fmaxf(__builtin_fabsf(bf2f(v[it] & 0xFFFFu)), __builtin_fabsf(bf2f(v[it] >> 16))));
                 }
                 if (valid && ep.vcb) {
+                    if constexpr (!FP8)
+                        store_between(stream, [&](auto store) {
 #pragma unroll
-                    for (int it = 0; it < NSW; ++it) {
-                        const int sw = it0 + it;
-                        if (!FP8) store_between(vcb_p + (int64_t)(sw >> 2) * (F >> 6) * 256 + lane + (sw & 3) * 64, v[it], stream);
-                        else {             // the survivors' codes: the row's 8 pairs gathered into the lane of block 0, one 16-byte store
+                            for (int it = 0; it < NSW; ++it) store(vcb_p + (int64_t)((it0 + it) >> 2) * (F >> 6) * 256 + lane + ((it0 + it) & 3) * 64, v[it]);
+                        });
+                    else
+#pragma unroll
+                        for (int it = 0; it < NSW; ++it) {             // the survivors' codes: the row's 8 pairs gathered into the lane of block 0, one 16-byte store
+                            const int sw = it0 + it;
                             const uint32_t q2w = fp8_enc2(bf2f(v[it] & 0xFFFFu), bf2f(v[it] >> 16), ep.inv_out);
                             const uint32_t w2 = q2w | (row_shl<1>(q2w) << 16);
                             const uint4 w8 = make_uint4(w2, row_shl<2>(w2), row_shl<4>(w2), row_shl<6>(w2));
                             if (bl == 0) *reinterpret_cast<uint4*>(vcb8_p + (int64_t)(sw >> 2) * (F >> 7) * 1024 + (sw & 3) * 256) = w8;
                         }
-                    }
                 }
                 tile_sync();
+                store_between(stream, [&](auto store) {
 #pragma unroll
-                for (int n = 0; n < (SHARE ? 1 : 4); ++n) {          // 2 groups of 16 compact rows x 2 chunks of 32 tokens, 1 KB each
-                    const int q = SHARE ? kg : n;
-                    const int fr = (q >> 1) * 16 + (lane >> 2), tc = (q & 1) * 32 + (lane & 3) * 8;
-                    const uint4 w = *reinterpret_cast<const uint4*>(ttile + fr * EP + tc * 2);
-                    if (FP8 && ep.at_fp8) {     // fp8 weight gradients: the compact transposed survivors leave as codes (a 64-token block = one 64-byte chunk)
-                        if (valid)
-                            *reinterpret_cast<uint2*>(ep.at + blk_off(f0 / 2 + fr, (t0 + tc) / 2, tok_ld / 64)) =
-                                make_uint2(fp8_enc2(bf2f(w.x & 0xFFFFu), bf2f(w.x >> 16), ep.inv_out) | (fp8_enc2(bf2f(w.y & 0xFFFFu), bf2f(w.y >> 16), ep.inv_out) << 16),
-                                           fp8_enc2(bf2f(w.z & 0xFFFFu), bf2f(w.z >> 16), ep.inv_out) | (fp8_enc2(bf2f(w.w & 0xFFFFu), bf2f(w.w >> 16), ep.inv_out) << 16));
-                    } else if (valid) {
-                        store_between(ep.at + blk_off(f0 / 2 + (q >> 1) * 16, t0 + (q & 1) * 32, tok_ld / 32) + lane * 8, w, stream);
+                    for (int n = 0; n < (SHARE ? 1 : 4); ++n) {          // 2 groups of 16 compact rows x 2 chunks of 32 tokens, 1 KB each
+                        const int q = SHARE ? kg : n;
+                        const int fr = (q >> 1) * 16 + (lane >> 2), tc = (q & 1) * 32 + (lane & 3) * 8;
+                        const uint4 w = *reinterpret_cast<const uint4*>(ttile + fr * EP + tc * 2);
+                        if (FP8 && ep.at_fp8) {     // fp8 weight gradients: the compact transposed survivors leave as codes (a 64-token block = one 64-byte chunk)
+                            if (valid)
+                                *reinterpret_cast<uint2*>(ep.at + blk_off(f0 / 2 + fr, (t0 + tc) / 2, tok_ld / 64)) =
+                                    make_uint2(fp8_enc2(bf2f(w.x & 0xFFFFu), bf2f(w.x >> 16), ep.inv_out) | (fp8_enc2(bf2f(w.y & 0xFFFFu), bf2f(w.y >> 16), ep.inv_out) << 16),
+                                               fp8_enc2(bf2f(w.z & 0xFFFFu), bf2f(w.z >> 16), ep.inv_out) | (fp8_enc2(bf2f(w.w & 0xFFFFu), bf2f(w.w >> 16), ep.inv_out) << 16));
+                        } else if (valid) {
+                            store(ep.at + blk_off(f0 / 2 + (q >> 1) * 16, t0 + (q & 1) * 32, tok_ld / 32) + lane * 8, w);
+                        }
                     }
-                }
+                });
             }
             wave_lds_sync();
         }
