@@ -1,4 +1,4 @@
-"""Eq. (1) on W1 itself, pruned as it is read (unpacked weights, K <= 256): bit for bit what it gives on the packed weight that the same launch writes for later calls."""
+"""Eq. (1) on W1 itself, pruned as it is read (unpacked weights, K <= 448): bit for bit what it gives on the packed weight that the same launch writes for later calls."""
 import pytest
 import torch
 
@@ -19,7 +19,7 @@ def inputs(T, D, F, seed):
 
 
 @pytest.mark.parametrize("mode", [sffn.MODE_HARD, sffn.MODE_SOFT])
-@pytest.mark.parametrize("T,D,F,M", [(64, 64, 128, 8), (192, 128, 896, 8), (320, 192, 320, 8), (512, 256, 1024, 8), (64, 256, 192, 8), (192, 192, 512, 16), (256, 256, 1024, 32)])
+@pytest.mark.parametrize("T,D,F,M", [(64, 64, 128, 8), (192, 128, 896, 8), (320, 192, 320, 8), (512, 256, 1024, 8), (64, 256, 192, 8), (192, 320, 576, 8), (128, 384, 512, 8), (64, 448, 1600, 8), (192, 192, 512, 16), (256, 256, 1024, 32), (64, 448, 512, 16)])
 def test_step(T, D, F, M, mode):
     x = inputs(T, D, F, 71)
     step = sffn.FfnStep(T, D, F, mode, M=M)
@@ -38,9 +38,9 @@ def test_step(T, D, F, M, mode):
         assert torch.equal(a, b)
 
 
-@pytest.mark.parametrize("M", [8, 16])
-def test_experts(M):
-    seg, D, F = [0, 64, 64, 256, 384], 192, 256
+@pytest.mark.parametrize("M,D", [(8, 192), (16, 192), (8, 320)])
+def test_experts(M, D):
+    seg, F = [0, 64, 64, 256, 384], 256
     per = [inputs(seg[-1], D, F, 72 + e) for e in range(4)]
     X, dY = per[0][0], per[0][4]
     W1, W2, b1 = (torch.stack([p[i] for p in per]) for i in (1, 2, 3))
