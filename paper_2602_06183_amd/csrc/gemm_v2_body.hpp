@@ -333,8 +333,8 @@ __device__ __forceinline__ void gemm_nt_v2_body(unsigned char* __restrict__ smem
     // One step = one stage = FM rows of four matrix instructions, on fragments that were read during the step before.  Behind the first row every wavefront has read
     // all of the stage and the next one has landed (barrier): the stage is refilled, and the next one's fragments are read, spread over the step: a CU takes
     // 57 bytes of loads per cycle, and a wavefront that has to wait for its turn cannot issue matrix instructions either.
-    // (All loads of a refill right behind the barrier, T = D = 8192, F = 28672: 2045 us for eq. (1); spread: 1930.)  T = F = 8192: 0.81 us a stage of 51,200 bytes = 16 TB/s, which is what
-    // loads by themselves reach; two half stages of 32 x 32 x 32 instructions, their fragments half a stage ahead, took 0.90.
+    // (All loads of a refill right behind the barrier, T = D = 8192, F = 28672: 2045 us for eq. (1); spread: 1930.)  T = F = 8192: 0.81 us a stage of 51,200 bytes, of
+    // which the matrix instructions alone take 0.64 at the clock that their power leaves, the loads alone 0.51 - 0.58 (0.70 - 0.83 beside ordinary stores of the outputs); two half stages of 32 x 32 x 32 instructions, their fragments half a stage ahead, took 0.90.
     // full: tiles up to kt + NSTAGE exist.  The last steps load nothing: a repeated tile in their place costs what any other does, and the epilogue waits for it
     // (T = F = 8192, D = 512, 128 tile: 90.7 -> 88.0 us for eq. (1), 74.2 -> 71.7 for eq. (4); 256 tile 0.5 %).
     auto step = [&](auto full, int kt, const FragB& Bc, FragB& Bn) {

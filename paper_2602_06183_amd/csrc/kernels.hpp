@@ -298,7 +298,7 @@ inline SplitPlan plan_split(int64_t T, int64_t N, int steps, int tile, float und
     return best;
 }
 // M = 8: a launch takes 5.6 us, and 0.257 us a stage of a round of 512 of the 64 tiles, 0.42 of that with a CU for each; the sums 3.7 us and 10 ns per workgroup.  Taken where that saves
-// 5 %.  Fitted to 99 calls with 1 to 16 splits (what is chosen takes 2.0 % longer than the best of each, always undivided 10.6 %): T = 64, N = 4544, F = 19520 42.0 us undivided, 25.3 with 3,
+// 5 %.  (The counts, 6 of those 10 ns, have been spread over lines since.)  Fitted to 99 calls with 1 to 16 splits (what is chosen takes 2.0 % longer than the best of each, always undivided 10.6 %): T = 64, N = 4544, F = 19520 42.0 us undivided, 25.3 with 3,
 // 27.4 with 7; T = 256, N = 4352, F = 19584 83.6, 60.5 with 3; T = 64, N = 896, F = 3648 9.6, 11.3 with 7.
 inline SplitPlan plan_vnm8(int64_t T, int64_t N, int steps, int groups, bool fp8) {
     const int tile = pick_vnm8_tile(T, N, steps, groups, fp8);

@@ -59,8 +59,8 @@ __device__ __forceinline__ void transpose_bf16_body(void* smem, int bx, int by, 
 // A workgroup takes 64 logical rows x 128 k: the 128 x 64 source tile goes through LDS so that both the HBM reads (128-byte row segments) and the
 // packed writes stay contiguous: lane = (row, 32 k), 4 lanes write 128 consecutive bytes of a row and a wavefront whole blocks.  Bound: HBM.
 // PAST: non-temporal loads (reads_past() in kernels.hpp); the stores stay ordinary, two of which make a line (R = 28672, K = 8192: 151 us, non-temporal 179).
-//   R = 16384, K = 4096: 65 us with one row per lane (32 bytes at a row's distance), 52 now; with the unpruned transpose, R = 28672, K = 8192:
-//   296 and 248 us (5.0 TB/s, a large copy's rate).
+//   R = 16384, K = 4096: 65 us with one row per lane (32 bytes at a row's distance), 52 with four; with the unpruned transpose, R = 28672, K = 8192:
+//   296 and 248 us, 234 with the loads in flight together (5.1 TB/s).
 template <bool SOFT, bool PAST = false>
 __device__ __forceinline__ void prune24_cols_body(void* smem, int bx, int by, int bz, const uint16_t* __restrict__ src, int64_t R, int K, int64_t ld,
                                                           uint16_t* __restrict__ vals, uint8_t* __restrict__ meta,
