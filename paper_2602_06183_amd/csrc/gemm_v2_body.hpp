@@ -529,6 +529,16 @@ __device__ __forceinline__ void gemm_nt_v2_body(unsigned char* __restrict__ smem
                 }
             });
         };
+        // and as the packed rows.  One branch for all sixteen stores: one in every sweep holds the next sweep's LDS reads back (T = 64, D = 256, F = 1024, M = 8: eq. (1) 14.4 us, so 12.8; eqs. (4),
+        // (3) 11.1 and 9.6; the step 53.8 and 50.4).
+        auto rows_out = [&](const uint32_t (&v)[16], int f0, bool valid) {
+            if (!valid) return;                // (runs of tokens are whole blocks of 64)
+            uint16_t* const p = ep.vals + (int64_t)(t0 + 2 * (lane >> 4)) * (F / 2) + (f0 >> 1) + 2 * (lane & 15);
+            store_between(ep.stream, [&](auto store) {
+#pragma unroll
+                for (int it = 0; it < 16; ++it) store(reinterpret_cast<uint32_t*>(p + (int64_t)(8 * (it >> 1) + (it & 1)) * (F / 2)), v[it]);
+            });
+        };
         const bool stream = !FP8 && ep.stream;
         auto tile_sync = [&]() { if (SHARE) __syncthreads(); else wave_lds_sync(); };
         f32x4 mine[4];                                         // SHARE: the sums, in the order of the shares of the contraction, for the 16 tokens of fragment kg
@@ -608,7 +618,6 @@ __device__ __forceinline__ void gemm_nt_v2_body(unsigned char* __restrict__ smem
                     mw |= row_shl<2>(mw) << 8;
                     mw |= row_shl<4>(mw) << 16;
                     if (valid && t0 + t < Rb) {
-                        store_between(ep.stream, [&](auto store) { store(reinterpret_cast<uint32_t*>(ep.vals + (int64_t)(t0 + t) * (F / 2) + (f0 >> 1) + 2 * g), v); });
                         if ((g & 7) == 0) *reinterpret_cast<uint32_t*>(ep.meta + (int64_t)(t0 + t) * (F / 8) + (f0 >> 3) + (g >> 1)) = mw;
                         if (ep.v24) {       // the same packed matrix in the blocked operand layout (A operand of eqs. (3), (7) over the expert's run)
                             *reinterpret_cast<uint32_t*>(ep.v24 + blk_off(t0 + t, (f0 >> 1) + 2 * g, F / 64)) = v;
@@ -616,6 +625,7 @@ __device__ __forceinline__ void gemm_nt_v2_body(unsigned char* __restrict__ smem
                         }
                     }
                 }
+                rows_out(vv, f0, valid);
                 if (ep.at) transposed_out(vv, nn, f0, valid);
             }
             if (EPI == 4) {
@@ -640,12 +650,10 @@ __device__ __forceinline__ void gemm_nt_v2_body(unsigned char* __restrict__ smem
                     const uint32_t y0 = ((p0 >> 1) ? yv[it].y : yv[it].x) >> (16 * (p0 & 1)), y1 = ((p1 >> 1) ? yv[it].y : yv[it].x) >> (16 * (p1 & 1));
                     const float ya = bf2f(y0 & 0xFFFFu), yb = bf2f(y1 & 0xFFFFu);
                     const uint32_t v = f2bf2(2.0f * bf2f(d0 & 0xFFFFu) * (ya > 0.0f ? ya : 0.0f), 2.0f * bf2f(d1 & 0xFFFFu) * (yb > 0.0f ? yb : 0.0f));
-                    if (valid && t0 + t < Rb) {
-                        store_between(ep.stream, [&](auto store) { store(reinterpret_cast<uint32_t*>(ep.vals + (int64_t)(t0 + t) * (F / 2) + (f0 >> 1) + 2 * g), v); });
-                        *reinterpret_cast<uint32_t*>(ep.v24 + blk_off(t0 + t, (f0 >> 1) + 2 * g, F / 64)) = v;
-                    }
+                    if (valid && t0 + t < Rb) *reinterpret_cast<uint32_t*>(ep.v24 + blk_off(t0 + t, (f0 >> 1) + 2 * g, F / 64)) = v;
                     vv[it] = v; nn[it >> 3] |= nib << (4 * (it & 7));
                 }
+                rows_out(vv, f0, valid);
                 if (ep.at) transposed_out(vv, nn, f0, valid);
             }
             if (GEN_F || GEN_B) {

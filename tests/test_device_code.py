@@ -38,3 +38,16 @@ def test_row_major_contractions_keep_their_registers(kernels):
     units = {name: code for name, code in kernels("gemm_v2_row.hip").items() if "GemmV2Unit" in name}
     assert len(units) >= 12
     assert [name for name, code in units.items() if re.search(r"\tscratch_(load|store)", code)] == []
+
+
+def router_epilogues(kernels):
+    units = {name: code for name, code in kernels("gemm_v2.hip").items() if re.search(r"unit_kernelINS_10GemmV2UnitILb1ELb1ELi[34]E", name)}
+    assert len(units) >= 4
+    return units
+
+
+def test_packed_rows_of_the_router_leave_in_one_group(kernels):
+    """A branch per store keeps the LDS reads of the next sweep behind it."""
+    for name, code in router_epilogues(kernels).items():
+        groups = re.findall(r"(?:\tglobal_store_dword v[^\n]* nt\n(?:\t(?!s_cbranch|s_branch|ds_read)[^\n]*\n)*){16}", code)
+        assert groups, name
