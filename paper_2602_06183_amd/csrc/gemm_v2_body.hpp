@@ -585,7 +585,7 @@ __device__ __forceinline__ void gemm_nt_v2_body(unsigned char* __restrict__ smem
                 }
             }
             tile_sync();
-            if (EPI == 0 || ep.store_dense) {
+            auto dense_out = [&](auto store) {
 #pragma unroll
                 for (int p = 0; p < (EPI == 1 || EPI == 2 ? NSW : WN / 8); ++p) {
                     const int row = (it0 + p) * 8 + (lane >> 3), ch = lane & 7;
@@ -597,11 +597,15 @@ __device__ __forceinline__ void gemm_nt_v2_body(unsigned char* __restrict__ smem
                             *reinterpret_cast<uint2*>(o) = make_uint2(w.x, w.y);
                             *reinterpret_cast<uint2*>(o + ((int64_t)1 << grp.map_logM)) = make_uint2(w.z, w.w);
                         } else {
-                            store_out(out + (int64_t)j * ldo + i, w);
+                            store(out + (int64_t)j * ldo + i, w);
                         }
                     }
                 }
-            }
+            };
+            // (EPI 3: y1 at the experts' hidden units, which eq. (4)'s epilogue reads.  Non-temporal at every size: T = 4096, D = 1024, F = 4096, M = 8 175.8 us the step, so 172.1;
+            // T = 10240, D = 576, F = 2560 195.6 and 191.8.)
+            if (EPI == 3) { if (ep.store_dense) store_between(ep.stream, dense_out); }
+            else if (EPI == 0 || ep.store_dense) dense_out([](uint16_t* p, const uint4& w) { store_out(p, w); });
             if (EPI == 3) {
                 // lane = (tokens t = 2 (lane / 16) + 8 (it / 2) + it % 2, group of four compact columns g = lane % 16): eq. (2), then the 2:4 rule
                 const int g = lane & 15;

@@ -51,3 +51,11 @@ def test_packed_rows_of_the_router_leave_in_one_group(kernels):
     for name, code in router_epilogues(kernels).items():
         groups = re.findall(r"(?:\tglobal_store_dword v[^\n]* nt\n(?:\t(?!s_cbranch|s_branch|ds_read)[^\n]*\n)*){16}", code)
         assert groups, name
+
+
+def test_router_keeps_y1_for_eq_4_by_the_rule_of_the_launch(kernels):
+    """What the epilogue of eq. (1) leaves for later launches has an ordinary store for every non-temporal one."""
+    for name, code in router_epilogues(kernels).items():
+        if "Li3E" in name.split("GemmV2Unit")[1][:30]:
+            wide = re.findall(r"\tglobal_store_dwordx4 [^\n]*", code)
+            assert len(wide) >= 32 and sum(" nt" in w for w in wide) * 2 == len(wide), name
