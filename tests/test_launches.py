@@ -1,0 +1,74 @@
+"""Which kernels the built library launches for a call (tests/launches.cpp stands in for the HIP runtime)."""
+import os
+import re
+import subprocess
+
+import pytest
+
+import paper_2602_06183_amd as sffn
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+FORWARD, HEAD, TAIL = 0, 1, 2          # launches of eqs. (3), (5), (4), of (5), (4) and of (7), (8)
+
+
+@pytest.fixture(scope="module")
+def launches(tmp_path_factory):
+    """calls (lines for launches.cpp) -> the kernels of each"""
+    exe = str(tmp_path_factory.mktemp("launches") / "launches")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-rdynamic", os.path.join(HERE, "launches.cpp"), "-o", exe, "-ldl"], check=True)
+
+    def run(calls):
+        out = subprocess.run([exe, sffn.lib_path()], input="\n".join(calls), capture_output=True, text=True, check=True).stdout.strip().split("\n")
+        assert len(out) == len(calls) and not any(line.startswith("refused") for line in out), out
+        return [line.split(" ; ") for line in out]
+    return run
+
+
+def step(call, M, T, D, F, fp8=0, seg=None, flags=sffn.FLAG_LEAN):
+    return "step %s %d %d %d %d %d %d %d %s" % (call, fp8, M, T, D, F, flags | (sffn.FLAG_FP8_WGRAD if fp8 else 0), len(seg) - 1 if seg else 0, " ".join(map(str, seg or [])))
+
+
+GRADIENT = {"1, 1, 64, 3, 4": 64, "2, 2, 64, 2, 1": 3, "2, 2, 64, 3, 1": 128, "2, 2, 128, 2, 1": "tall", "2, 4, 128, 3, 1": 256}
+ACTIVATION = {"1, 1, 2, 3, 4": 64, "2, 2, 2, 3, 1": 128, "4, 1, 4, 3, 1": "tall", "4, 2, 4, 3, 1": 256, "8, 1, 4, 3, 1": 512}
+WEIGHT = {"1, 1, 64, 1, 4": 64, "1, 1, 64, 2, 4": 64, "1, 1, 64, 3, 4": 64, "1, 1, 128, 2, 4": 64, "2, 2, 64, 3, 1": 128, "2, 2, 128, 2, 1": "tall", "2, 4, 128, 3, 1": 256}
+
+
+def tiles(kernel):
+    """The tiles of a launch's contractions: activation (eqs. (3), (7)), gradient (eqs. (5), (8)), weight (eqs. (1), (4)); gathered rows: 0"""
+    found = {}
+    for kind, known, pattern in (("activation", ACTIVATION, r"Vnm8Unit<\w+, sffn::VTile<([^>]*)>"), ("gradient", GRADIENT, r"WgradUnit<[^:]*sffn::WTile<([^>]*)>"), ("weight", WEIGHT, r"GemmV2Unit<true, true, [^:]*sffn::Tile<([^>]*)>")):
+        m = re.search(pattern, kernel)
+        if m:
+            found[kind] = known[m.group(1)]
+    if "Gather" in kernel:
+        found["activation"] = 0
+    return found
+
+
+def form(kernels, what, M=8):
+    """Bits 0, 1, 2: eqs. (3) / (7), (5) / (8), (4) on tall tiles where 128 would do; None: the call shares no such launch"""
+    want = {FORWARD: ["activation", "gradient", "weight"], HEAD: ["gradient", "weight"], TAIL: ["activation", "gradient"]}[what]
+    for k in kernels:
+        t = tiles(k)
+        if sorted(t) == sorted(want):
+            return sum(bit for kind, bit in (("activation", 1), ("gradient", 2), ("weight", 4)) if t.get(kind) == "tall" and not (kind == "weight" and M == 64))
+    return None
+
+
+def test_shared_launches_of_the_gpu_tests(launches):
+    from tests.test_gpu_tall_tiles import FP8, PLAIN, WIDE
+    cases = [(0, 8, *c) for c in PLAIN] + [(0, *c) for c in WIDE] + [(1, *c) for c in FP8]
+    calls = [step(call, M, T, D, F, fp8) for fp8, M, T, D, F, _ in cases for call in ("step", "backward")]
+    got = launches(calls)
+    for (fp8, M, T, D, F, want), whole, back in zip(cases, got[::2], got[1::2]):
+        assert (form(whole, FORWARD, M), form(back, HEAD, M), form(whole, TAIL, M)) == want, (fp8, M, T, D, F)
+        assert form(back, TAIL, M) == want[2]
+
+
+def test_launches_of_their_own_of_the_gpu_tests(launches):
+    from tests.test_gpu_tall_tiles import ALONE_ACTIVATION, ALONE_GRADIENT
+    for call, kernels in zip(ALONE_ACTIVATION, launches(["spmm %d 8 %d %d %d" % c for c in ALONE_ACTIVATION])):
+        assert tiles(kernels[-1]) == {"activation": "tall"}, call
+    for major in (0, 1):
+        for call, kernels in zip(ALONE_GRADIENT, launches(["wgrad %d 8 %d %d %d" % (major, T, F, N) for _, T, N, F in ALONE_GRADIENT])):
+            assert tiles(kernels[-1]) == {"gradient": "tall"}, call
