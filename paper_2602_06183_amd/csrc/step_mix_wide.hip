@@ -11,7 +11,7 @@ static hipError_t launch_impl(int what, const StepTiles& t, const GatherArgs* v,
     using W1 = Units<void, WgradUnit128<false, false, ACC32>, WgradUnitTall<false, false, ACC32>>;
     using GT = GemmV2Unit<true, true, EPI, true, false, TileTall>;
     using G = std::conditional_t<TALL, Units<void, GT, void>, Units<void, GemmV2Unit<true, true, EPI, true, false, typename TileSel<true, EPI>::T128>, GT>>;
-    MixTiles k = kMixWideBf16;
+    MixTiles k = ACC32 ? kMixWideBf16Sums : kMixWideBf16;
     if (TALL) k.g[0] = kMixTallBf16;
     return launch_mix<!ACC32, false, V, W2, W1, G>(k, what, t, v, g, w, 64.0f, s);
 }

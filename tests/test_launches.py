@@ -72,3 +72,16 @@ def test_launches_of_their_own_of_the_gpu_tests(launches):
     for major in (0, 1):
         for call, kernels in zip(ALONE_GRADIENT, launches(["wgrad %d 8 %d %d %d" % (major, T, F, N) for _, T, N, F in ALONE_GRADIENT])):
             assert tiles(kernels[-1]) == {"gradient": "tall"}, call
+
+
+def test_tall_tiles_beside_float32_sums(launches):
+    """Against backward calls that were timed on every form: chosen, they take no longer than tiles of 128 do, and less on average."""
+    rows = [line.split(" | ") for line in open(os.path.join(HERE, "golden", "sums_times.txt")) if not line.startswith("#")]
+    cases = [([int(v) for v in c.split()[:4]], [int(v) for v in c.split()[4].split(",")] if "," in c else None, list(map(float, h.split())), list(map(float, t.split()))) for c, h, t in rows]
+    got = launches([step("backward", *shape, seg=seg, flags=sffn.FLAG_LEAN | sffn.FLAG_DW_FP32_ACCUMULATE) for shape, seg, _, _ in cases])
+    ratios = []
+    for (shape, seg, head, tail), kernels in zip(cases, got):
+        h, t = form(kernels, HEAD, shape[0]), form(kernels, TAIL, shape[0])
+        ratios += [(head[{0: 0, 2: 1, 6: 2}[h]] / head[0], shape, seg, h), (tail[t] / tail[0], shape, seg, t)]
+    assert max(ratios)[0] <= 1.04, max(ratios)
+    assert sum(r[0] for r in ratios) / len(ratios) <= 0.985
