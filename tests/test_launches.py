@@ -85,3 +85,12 @@ def test_tall_tiles_beside_float32_sums(launches):
         ratios += [(head[{0: 0, 2: 1, 6: 2}[h]] / head[0], shape, seg, h), (tail[t] / tail[0], shape, seg, t)]
     assert max(ratios)[0] <= 1.04, max(ratios)
     assert sum(r[0] for r in ratios) / len(ratios) <= 0.985
+
+
+def test_tall_tiles_beside_few_tokens(launches):
+    """The same for steps of few tokens: eq. (5) beside 64 tiles of eq. (3)."""
+    rows = [line.split(" | ") for line in open(os.path.join(HERE, "golden", "few_tokens_times.txt")) if not line.startswith("#")]
+    cases = [(list(map(int, c.split())), list(map(float, t.split()))) for c, t in rows]
+    ratios = [(t[form(kernels, FORWARD) // 2] / t[0], shape) for (shape, t), kernels in zip(cases, launches([step("step", 8, *shape) for shape, _ in cases]))]
+    assert max(ratios)[0] <= 1.03, max(ratios)
+    assert sum(r[0] for r in ratios) / len(ratios) <= 0.97
