@@ -9,7 +9,7 @@ template <int EPI, bool SOFT>
 static hipError_t launch_impl(const GemmV2Args& a, const PrologueArgs& behind, int tile, hipStream_t s) {
     using Sel = TileSel<true, EPI>;
     using P = PrologueUnit<SOFT>;
-    if constexpr (EPI != 22)
+    if constexpr (EPI == 1)
         if (behind.W1) {
             GemmV2Args raw = a;
             raw.a_vals = behind.W1;
@@ -29,7 +29,7 @@ hipError_t launch_forward_x(const uint16_t* a_vals, const uint8_t* a_meta, const
                             const PrologueArgs& behind, hipStream_t s, const GemmGroup* grp, int tile) {
     const GemmGroup g = grp ? *grp : GemmGroup();
     const PrologueArgs& p = behind;
-    if (p.T % 64 || p.D % 64 || p.F % 64 || (tile != 64 && tile != 128) || (p.W1 && (tile != 64 || p.D > 512 || ep.logM == 6)) || (g.n && (g.n > GemmGroup::kMaxExperts || g.role != 1))) return hipErrorInvalidValue;
+    if (p.T % 64 || p.D % 64 || p.F % 64 || (tile != 64 && tile != 128) || (p.W1 && (tile != 64 || p.D > 512 || ep.mode != 1)) || (g.n && (g.n > GemmGroup::kMaxExperts || g.role != 1))) return hipErrorInvalidValue;
     const GemmV2Args a = {a_vals, a_meta, X, bias, p.F, p.T, p.D, out, p.F, 0, 0, ep, g, 1.0f};
     if (ep.mode == 1) return launch_mode<1>(a, p, tile, s);
     if (ep.mode == 5 && ep.logM >= 4 && ep.logM <= 6) return ep.logM == 4 ? launch_mode<20>(a, p, tile, s) : ep.logM == 5 ? launch_mode<21>(a, p, tile, s) : launch_mode<22>(a, p, tile, s);

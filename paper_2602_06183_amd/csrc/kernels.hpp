@@ -150,8 +150,8 @@ inline bool forward_reads_x(int64_t T, int64_t D, int64_t F, int64_t E, int M, b
 // Where eq. (1) also prunes the rows of W1 that it reads, so that no launch is in front of it: on 64 tiles while a wavefront has two stages of the contraction at most.  The pruning, 25 to 33
 // instructions a group of four and done again for every 64 tokens, and the longer trip of twice the bytes cost eq. (1) 1 us a stage, the launch 3.  A step, with the launch / without:
 // T = 512, D = 256, F = 1024 26.2 / 24.5 us, T = 192, D = 384, F = 1728 24.3 / 23.4, T = 64, D = 448, F = 1600 23.2 / 22.5; with eight stages for four wavefronts nothing is left of it
-// (T = 256, D = 512, F = 1600 26.4 / 26.3, T = 576, D = 512, F = 1856 32.0 / 32.2).
-inline bool forward_prunes_w1(int64_t D, int M, bool packed, int tile) { return !packed && tile == 64 && M != 64 && D <= 448; }
+// (T = 256, D = 512, F = 1600 26.4 / 26.3, T = 576, D = 512, F = 1856 32.0 / 32.2).  At M = 8: wider blocks have 64 tiles from 16 stages on only.
+inline bool forward_prunes_w1(int64_t D, int M, bool packed, int tile) { return !packed && tile == 64 && M == 8 && D <= 448; }
 // The same for the fp8 step (prologue_fp8.hip).  t_codes: xt, dyt as codes instead of bf16.  Canonical codes / metadata (w1c, w1m, w2c, w2m) may be null.
 // amax_*: one float per workgroup of the part (fp8_parts: x and dy have as many), slots_*: the epilogues' slots, cleared by the parts over X / dY; null: not wanted.
 struct Fp8PrologueArgs {

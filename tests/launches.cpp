@@ -1,6 +1,7 @@
 // The launches of the built library's calls, without a GPU: this program stands in for the HIP runtime, loads the library (argv[1]) and prints, for every line of standard input, the kernels that
 // the call launches, by name, one after the other with " ; " between them.  For tests/test_launches.py.
 //   step <step | forward | backward> <fp8> <M> <T> <D> <F> <flags> <n> [<n + 1 segment offsets>]   (n = 0: the plain step)
+//   kernels           all that the library has
 //   spmm <fp8> <M> <T> <N> <F>           wgrad <out_f_major> <M> <T> <F> <N>
 #include <cxxabi.h>
 #include <dlfcn.h>
@@ -17,6 +18,13 @@
 namespace {
 std::map<const void*, std::string>& names() { static std::map<const void*, std::string> m; return m; }
 std::vector<std::string> launched;
+std::string readable(const std::string& name) {          // without the parameters
+    int status = 0;
+    char* s = abi::__cxa_demangle(name.c_str(), nullptr, nullptr, &status);
+    const std::string r = s ? s : name;
+    free(s);
+    return r.substr(0, r.find('('));
+}
 }  // namespace
 struct Dim3 { uint32_t x, y, z; };
 extern "C" {
@@ -26,14 +34,7 @@ void __hipRegisterVar(void**, void*, char*, char*, int, size_t, int, int) {}
 void __hipRegisterFunction(void**, const void* host, char*, const char* device, unsigned, void*, void*, void*, void*, int*) { names()[host] = device; }
 int __hipPushCallConfiguration(Dim3, Dim3, size_t, void*) { return 0; }
 int __hipPopCallConfiguration(Dim3* grid, Dim3* block, size_t* lds, void** stream) { *grid = *block = {1, 1, 1}; *lds = 0; *stream = nullptr; return 0; }
-int hipLaunchKernel(const void* host, Dim3, Dim3, void**, size_t, void*) {
-    int status = 0;
-    char* s = abi::__cxa_demangle(names()[host].c_str(), nullptr, nullptr, &status);
-    const std::string name = s ? s : names()[host];
-    launched.push_back(name.substr(0, name.find('(')));
-    free(s);
-    return 0;
-}
+int hipLaunchKernel(const void* host, Dim3, Dim3, void**, size_t, void*) { launched.push_back(readable(names()[host])); return 0; }
 int hipGetLastError() { return 0; }
 }
 
@@ -50,7 +51,10 @@ int main(int argc, char** argv) {
     while (scanf("%15s", what) == 1) {
         launched.clear();
         int rc = -100;
-        if (!strcmp(what, "step")) {
+        if (!strcmp(what, "kernels")) {
+            for (const auto& k : names()) launched.push_back(readable(k.second));
+            rc = SFFN_OK;
+        } else if (!strcmp(what, "step")) {
             int fp8, n;
             sffn_cfg c;
             memset(&c, 0, sizeof(c));

@@ -94,3 +94,24 @@ def test_tall_tiles_beside_few_tokens(launches):
     ratios = [(t[form(kernels, FORWARD) // 2] / t[0], shape) for (shape, t), kernels in zip(cases, launches([step("step", 8, *shape) for shape, _ in cases]))]
     assert max(ratios)[0] <= 1.03, max(ratios)
     assert sum(r[0] for r in ratios) / len(ratios) <= 0.97
+
+
+PRUNES = re.compile(r"GemmV2Unit<true, true, (\d+), true, false, sffn::Tile<[^>]*>, true, false, [12]>")
+
+
+def test_eq_1_prunes_what_it_reads_in_the_gpu_tests(launches):
+    """The shapes of test_gpu_prune_in_place.py at M = 8, experts too, and no others; every such kernel of the library is one of those."""
+    import tests.test_gpu_prune_in_place as t
+    shapes = next(m.args[1] for m in t.test_step.pytestmark if m.name == "parametrize" and m.args[0].startswith("T"))
+    calls = [step(call, M, T, D, F, flags=flags) for T, D, F, M in shapes for call in ("step", "forward") for flags in (0, sffn.FLAG_WEIGHTS_PACKED)]
+    experts = [(M, D) for M, D in next(m.args[1] for m in t.test_experts.pytestmark if m.name == "parametrize")]
+    calls += [step("step", M, 384, D, 256, seg=[0, 64, 64, 256, 384]) for M, D in experts]
+    seen = set()
+    for call, kernels in zip(calls, launches(calls)):
+        found = PRUNES.findall(" ".join(kernels))
+        assert bool(found) == (call.split()[3] == "8" and not int(call.split()[7]) & sffn.FLAG_WEIGHTS_PACKED), call
+        assert not found or "PrologueUnit" not in kernels[0].split("GemmV2Unit")[0], call          # nothing in front of it
+        seen |= {k for k in kernels if PRUNES.search(k)}
+    built = {k for k in launches(["kernels"])[0] if PRUNES.search(k)}
+    # (soft pruning: the same calls in the other mode)
+    assert {k.replace("false, 2>", "false, 1>").replace("<true> ", "<false> ") for k in built} == seen, (built, seen)
