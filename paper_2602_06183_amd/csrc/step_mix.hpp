@@ -53,11 +53,10 @@ hipError_t launch_mix(const MixTiles& k, int what, const StepTiles& t, const VAr
         return with_unit<W2>(w64, w_tall, [&](auto tw) { return launch_units<typename decltype(tw)::type, typename G::U128>(s, w, *g); });
     }
     if constexpr (FORWARD) if (what == kMixForwardTail) {
-        if constexpr (kBuilt<typename G::Tall>) if (g_tall)          // (eqs. (5) and, where it has them, (3) on tall tiles too)
-            return with_unit<Units<void, typename V::U128, typename V::Tall>>(false, true, [&](auto tv) {
-                using VU = typename decltype(tv)::type; using WU = typename W2::Tall;
-                return launch_units<VU, WU, typename G::Tall>(s, *v, w, *g, wgrad_first<WU, VU>(*v, w));
-            });
+        if constexpr (kBuilt<typename G::Tall>) if (g_tall) {        // (eqs. (5) and, where it has them, (3) on tall tiles too)
+            using VU = std::conditional_t<kBuilt<typename V::Tall>, typename V::Tall, typename V::U128>; using WU = typename W2::Tall;
+            return launch_units<VU, WU, typename G::Tall>(s, *v, w, *g, wgrad_first<WU, VU>(*v, w));
+        }
         return with_unit<V>(v64, v_tall, [&](auto tv) {
             return with_unit<W2>(w64, w_tall, [&](auto tw) {
                 using VU = typename decltype(tv)::type; using WU = typename decltype(tw)::type;

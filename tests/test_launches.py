@@ -115,3 +115,12 @@ def test_eq_1_prunes_what_it_reads_in_the_gpu_tests(launches):
     built = {k for k in launches(["kernels"])[0] if PRUNES.search(k)}
     # (soft pruning: the same calls in the other mode)
     assert {k.replace("false, 2>", "false, 1>").replace("<true> ", "<false> ") for k in built} == seen, (built, seen)
+
+
+def test_no_kernel_for_a_form_that_is_never_chosen(launches):
+    """Eq. (4) on tall tiles only beside eqs. (5) and, at M = 8, (3) on tall ones."""
+    shared = [k for k in launches(["kernels"])[0] if sorted(tiles(k)) == ["activation", "gradient", "weight"]]
+    assert len(shared) >= 40
+    for k in shared:
+        t = tiles(k)
+        assert t["weight"] == 128 or t["gradient"] == "tall" and t["activation"] in (0, "tall") or ", 38, " in k, k
