@@ -53,6 +53,7 @@ __device__ __forceinline__ bool split_join4(const f32x16 (&acc)[2][2], unsigned 
     unsigned before = 0;
     if (lane == 0) before = __hip_atomic_fetch_add(count, one, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if ((uniform((int)before) >> (8 * wave) & 0xFF) + 1 != sp.n) return false;
+    asm volatile("" ::: "memory");       // relaxed loads of other addresses: nothing else keeps the compiler from reading the sums before the count
     if (lane == 0) __hip_atomic_fetch_sub(count, one * (unsigned)sp.n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 #pragma unroll
     for (int k = 0; k < 16; ++k) q[k] = 0.0f;

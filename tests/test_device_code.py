@@ -59,3 +59,14 @@ def test_router_keeps_y1_for_eq_4_by_the_rule_of_the_launch(kernels):
         if "Li3E" in name.split("GemmV2Unit")[1][:30]:
             wide = re.findall(r"\tglobal_store_dwordx4 [^\n]*", code)
             assert len(wide) >= 32 and sum(" nt" in w for w in wide) * 2 == len(wide), name
+
+
+def test_sums_of_the_other_splits_are_read_behind_the_count(tmp_path):
+    """Counting in and the loads of the sums are relaxed atomics of different addresses, which a compiler may reorder; before any optimisation a barrier for it stands between them."""
+    path = str(tmp_path / "vnm8.ll")
+    subprocess.run([os.environ.get("HIPCC", "/opt/rocm/bin/hipcc"), *build.FLAGS, "--cuda-device-only", "-S", "-emit-llvm", "-Xclang", "-disable-llvm-passes", os.path.join(build.CSRC, "gemm_vnm8.hip"), "-o", path],
+                   check=True, stderr=subprocess.DEVNULL)
+    body = re.search(r"^define [^\n]*split_join4[^\n]*\{\n(.*?)^\}", open(path).read(), re.M | re.S).group(1)
+    counted = body.index("atomicrmw add")
+    barrier, sums = body.find('asm sideeffect "", "~{memory}"', counted), re.compile(r"call [^\n]*split_join4[^\n]*ENKUl").search(body, counted)
+    assert sums and counted < barrier < sums.start()
