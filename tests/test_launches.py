@@ -124,3 +124,18 @@ def test_no_kernel_for_a_form_that_is_never_chosen(launches):
     for k in shared:
         t = tiles(k)
         assert t["weight"] == 128 or t["gradient"] == "tall" and t["activation"] in (0, "tall") or ", 38, " in k, k
+
+
+def test_launches_of_the_exact_gpu_tests(launches):
+    """The forms that test_gpu_tall_tiles_exact.py names, experts and float32 sums among them, and no 64 tile of an activation or a gradient on either side of its comparisons."""
+    from tests.test_gpu_tall_tiles_exact import EXACT
+    for T, D, F, seg, want in EXACT:
+        sums = sffn.FLAG_LEAN | sffn.FLAG_DW_FP32_ACCUMULATE
+        calls = [step("step", 8, T, D, F, seg=seg, flags=0), step("backward", 8, T, D, F, seg=seg), step("backward", 8, T, D, F, seg=seg, flags=sums), step("forward", 8, T, D, F, seg=seg, flags=sums)]
+        other = [step("step", 8, b - a, D, F) for a, b in zip(seg, seg[1:]) if b > a] if seg else ["spmm 0 8 %d %d %d" % (T, D, F)] + ["wgrad %d 8 %d %d %d" % (m, T, F, D) for m in (0, 1)]
+        got = launches(calls + other)
+        whole, back, back_sums = got[:3]
+        assert (form(whole, FORWARD), form(back, HEAD), form(whole, TAIL), form(back_sums, HEAD), form(back_sums, TAIL)) == want, (T, D, F, seg)
+        assert all(t.get(kind) != 64 for kernels in got for t in map(tiles, kernels) for kind in ("activation", "gradient")), (T, D, F, seg)
+        if want[0] is None:
+            assert all({"gradient": "tall"} in list(map(tiles, kernels)) for kernels in (whole, back, back_sums))
