@@ -13,10 +13,10 @@ namespace sffn {
 
 __device__ __forceinline__ float bf2f(uint32_t h) { return __uint_as_float(h << 16); }
 
-// 16 bytes of an output, non-temporal: stored the ordinary way the outputs push the operands that the other tiles share out of L2 and of the
-// last-level cache.  The loads of eq. (1) alone beside its stores, T = F = 8192, 256 tiles: D = 8192 433 -> 281 us, D = 2048, F = 28672 345 -> 306; whole contractions, which the power of
-// the matrix instructions bounds as well, 139 -> 136 and 503 -> 472; steps, ordinary / this: T = 8192, D = 2048, F = 8192 913 / 901 us, T = 1984, D = 1344, F = 4160 134 / 132; the six contractions
-// of the first by themselves 937 / 912.
+// 16 bytes of a weight gradient, non-temporal: nothing reads it before the optimizer does, and stored the ordinary way the gradients push the operands that the other tiles share out of L2 and of
+// the last-level cache.  Of the time with ordinary stores: 27 drawn steps 0.987, 14 on codes 0.978; with an update of the weights right behind the step 1.01 at 1 MB of gradient, 0.99 - 1.00 from 4 MB on.
+// Activations (Y3, dX, y1, dy2, packed rows) the next kernel reads, and pays for it: vnm_spmm, then spmm24_fwd on its result, ordinary / non-temporal T = 256, D = 512, F = 1024 14.0 / 14.7 us,
+// T = D = 1024, F = 4096 27.4 / 29.2, T = 8192, D = 2048, F = 8192 263 / 274; see stores_past() in kernels.hpp.
 typedef __attribute__((ext_vector_type(4))) uint32_t sffn_u32x4;
 __device__ __forceinline__ void store_out(void* p, const uint4& w) { __builtin_nontemporal_store(__builtin_bit_cast(sffn_u32x4, w), reinterpret_cast<sffn_u32x4*>(p)); }
 __device__ __forceinline__ void store_out(void* p, const float4& w) { store_out(p, __builtin_bit_cast(uint4, w)); }

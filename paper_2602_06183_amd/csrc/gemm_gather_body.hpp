@@ -254,7 +254,7 @@ __device__ __forceinline__ void vnm_gather_body(unsigned char* __restrict__ smem
 #pragma unroll
         for (int p = 0; p < 8; ++p) {
             const int row = p * 8 + (lane >> 3), ch = lane & 7;
-            store_out(out + (int64_t)(t0 + row) * ldo + nw + ch * 8, *reinterpret_cast<const uint4*>(scratch + row * EP + ch * 16));
+            *reinterpret_cast<uint4*>(out + (int64_t)(t0 + row) * ldo + nw + ch * 8) = *reinterpret_cast<const uint4*>(scratch + row * EP + ch * 16);
         }
     }
 }
@@ -436,7 +436,7 @@ __device__ __forceinline__ void vnm_gather_fp8_body(unsigned char* __restrict__ 
 #pragma unroll
         for (int p = 0; p < 8; ++p) {
             const int row = p * 8 + (lane >> 3), ch = lane & 7;
-            store_out(out + (int64_t)(t0 + row) * ldo + nw + ch * 8, *reinterpret_cast<const uint4*>(scratch + row * EP + ch * 16));
+            *reinterpret_cast<uint4*>(out + (int64_t)(t0 + row) * ldo + nw + ch * 8) = *reinterpret_cast<const uint4*>(scratch + row * EP + ch * 16);
         }
     }
 }

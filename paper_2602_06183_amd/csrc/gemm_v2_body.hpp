@@ -604,8 +604,8 @@ __device__ __forceinline__ void gemm_nt_v2_body(unsigned char* __restrict__ smem
             };
             // (EPI 3: y1 at the experts' hidden units, which eq. (4)'s epilogue reads.  Non-temporal at every size: T = 4096, D = 1024, F = 4096, M = 8 175.8 us the step, so 172.1;
             // T = 10240, D = 576, F = 2560 195.6 and 191.8.)
-            if (EPI == 3) { if (ep.store_dense) store_between(ep.stream, dense_out); }
-            else if (EPI == 0 || ep.store_dense) dense_out([](uint16_t* p, const uint4& w) { store_out(p, w); });
+            if (EPI == 0 || EPI == 3) { if (EPI == 0 || ep.store_dense) store_between(ep.stream, dense_out); }
+            else if (ep.store_dense) dense_out([](uint16_t* p, const uint4& w) { store_out(p, w); });      // (for inspection: nothing reads it)
             if (EPI == 3) {
                 // lane = (tokens t = 2 (lane / 16) + 8 (it / 2) + it % 2, group of four compact columns g = lane % 16): eq. (2), then the 2:4 rule
                 const int g = lane & 15;
@@ -964,7 +964,8 @@ __device__ __forceinline__ void gemm_nt_v2_body(unsigned char* __restrict__ smem
                 if (i < Ra && j < Rb) {
                     int64_t io = grp.map_logM ? ((int64_t)(i >> 2) << grp.map_logM) + 4 * expert_id + (i & 3) : i;
                     if (grp.out_row_map) io = io_map[a][p];
-                    if (io >= 0) store_out(out + io * ldo + j, *reinterpret_cast<const uint4*>(scratch + row * EP + ch * 16));
+                    const uint4 w = *reinterpret_cast<const uint4*>(scratch + row * EP + ch * 16);
+                    if (io >= 0) { if (SPARSE) *reinterpret_cast<uint4*>(out + io * ldo + j) = w; else store_out(out + io * ldo + j, w); }      // (dense: the router's weight gradients)
                 }
             }
             wave_lds_sync();
@@ -1007,8 +1008,10 @@ template <> struct TileSel<true, 38> { using T128 = TileTall; using T64 = Tile<1
 
 // tile: 256 / 128 / 64, or 0 to choose here
 template <bool SPARSE, bool OUT_I_CONTIG, int EPI, bool BLOCKED, bool FP8>
-hipError_t launch_gemm_v2(const GemmV2Args& a, hipStream_t s, int tile = 0) {
+hipError_t launch_gemm_v2(const GemmV2Args& args, hipStream_t s, int tile = 0) {
     using Sel = TileSel<SPARSE, EPI>;
+    GemmV2Args a = args;
+    if (EPI == 0 && OUT_I_CONTIG) a.ep.stream = stores_past(2 * (int64_t)a.Ra * a.Rb);
     // (grouped along the contraction, role 2: a tile contracts its own expert's tokens only)
     if (!tile) {
         const int steps = a.K / (SPARSE ? 64 : 32) / (a.grp.n && a.grp.role == 2 ? a.grp.n : 1);

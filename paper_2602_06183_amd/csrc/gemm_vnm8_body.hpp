@@ -390,7 +390,7 @@ __device__ __forceinline__ void vnm8_gemm_body(unsigned char* __restrict__ smem,
             for (int p = 0; p < 4; ++p) {
                 const int e = lane + 64 * p, row = e >> 3, ch = e & 7;
                 const int i = i0 + tbw * 64 + a * 32 + row, j = n0 + nh * 32 * FN + half * 64 + ch * 8;
-                if (i < Ra && j < N) store_out(out + (int64_t)i * ldo + j, *reinterpret_cast<const uint4*>(scratch + row * EP + ch * 16));
+                if (i < Ra && j < N) *reinterpret_cast<uint4*>(out + (int64_t)i * ldo + j) = *reinterpret_cast<const uint4*>(scratch + row * EP + ch * 16);
             }
             wave_lds_sync();
         }

@@ -536,6 +536,10 @@ inline bool router_shares(int64_t rows, int64_t D, int64_t F, int M) {
 // filled.  Ordinary / past, operands in turn: SquaredReLU and compression of 512 MiB 123 / 113 us, of 896 MiB 222 / 196, eq. (6) on 256 MiB 50 / 46, on 1 GiB 205 / 191, pruning of 448 MiB along rows
 // 128 / 109, across 161 / 136; right after a copy has written them 332 / 321, 92 / 88, 412 / 400.  Smaller ones are found there: 64 MiB of y1 18 / 19, the same 128 MiB at M = 16 over and over 25 / 29.
 inline bool reads_past(int64_t bytes) { return bytes >= (int64_t)256 << 20; }
+// Do the results of the stand-alone eqs. (1), (4) leave non-temporally?  Where they are as large as the last-level cache, so that the next kernel does not find them there: spmm24_fwd, then
+// SquaredReLU and compression, ordinary / non-temporal: y1 of 256 MiB 649 / 578 us, of 512 1365 / 1191; of 128 181 / 184, of 64 95.5 / 96.7, of 1 9.9 / 10.2 (8 to 16 MiB 17.9 / 17.2, 25.8 / 24.7: not
+// taken, Y3 of that size loses 7 %).
+inline bool stores_past(int64_t bytes) { return bytes >= (int64_t)256 << 20; }
 hipError_t launch_prune24(const uint16_t* src, int64_t R, int64_t K, int64_t ld, int trans, int mode, uint16_t* vals,
                           uint8_t* meta, hipStream_t stream);
 hipError_t launch_dsqrelu_vnm(const uint16_t* dy2, const uint16_t* y1, const uint8_t* meta, const uint8_t* colidx,

@@ -63,8 +63,8 @@ constexpr MixTiles kMixWideBf16 = {{0.94f, 4.41f, 0.364f}, {{0.0f, 1.348f, 0.566
 constexpr MixTiles kMixWideFp8 = {{}, {{0.04f, 1.103f, 0.666f}, {}}, {8.3f, 0.757f, 0.3f}, {{3.43f, 0.719f, 0.547f}, {5.99f, 1.279f, 0.549f}}, {{2.49f, 0.683f, 0.727f}, {5.98f, 1.009f, 0.788f}}, 0.124f};
 // Weight gradients that are added to float32 sums: a tile reads and writes eight bytes an element behind its last product, a tall one twice as many, so that where every CU has one tile the launch waits
 // for that.  Backward calls, 128 / tall: T = 320, D = 1088, F = 4096 32.4 / 38.0 us, M = 32, T = 448, D = 896, F = 3072 1.15 of the time, 8 experts of 72 tokens 1.15; T = 256, D = 2752,
-// F = 7360 112 / 94.  Fitted to 535 such calls (T 64 - 8192, 1 - 8 experts, every M) on each form; over 415 others, of 128 everywhere: M = 8 0.989 (0.985 the best forms), experts 0.990 (0.984),
-// M = 16, 32, 64 0.994 (0.991), no launch longer than 1.02; with the constants above, over the first 535: 0.991, 1.00 and 0.998, one launch in 14 longer than 1.02, up to 1.15.
+// F = 7360 112 / 94.  Fitted to 535 such calls (T 64 - 8192, 1 - 8 experts, every M) on each form; over 1660 others, of 128 everywhere: M = 8 0.990 (0.987 the best forms), experts 0.990 (0.984),
+// M = 16, 32, 64 0.991 (0.988), nine launches of 3300 longer than 1.02, none than 1.034; with the constants above, over the first 535: 0.991, 1.00 and 0.998, one launch in 14 longer than 1.02, up to 1.15.
 constexpr MixTiles kMixBf16Sums = {kMixBf16.v64, {kMixBf16.v[0], kMixBf16.v[1]}, {5.47f, 0.522f, 0.939f}, {{6.69f, 0.758f, 0.571f}, {12.27f, 1.373f, 0.799f}}, {kMixBf16.g[0], kMixBf16.g[1]}, 0.16f};
 constexpr MixTiles kMixWideBf16Sums = {kMixWideBf16.v64, {kMixWideBf16.v[0], {}}, {}, {{6.85f, 0.598f, 0.388f}, {11.06f, 1.046f, 0.928f}}, {kMixWideBf16.g[0], kMixWideBf16.g[1]}, 0.2f};
 // M = 64: eq. (4) is on 256 x 128 as it is

@@ -88,7 +88,7 @@ __device__ __forceinline__ void store_quarter(const float (&q)[16], float alpha,
     for (int p = 0; p < 2; ++p) {
         const int e = lane + 64 * p, row = e >> 2, ch = e & 3;
         const int i = i0 + (wave >> 1) * 32 + row, j = j0 + (wave & 1) * 32 + ch * 8;
-        if (i < Ra && j < N) store_out(out + (int64_t)i * ldo + j, *reinterpret_cast<const uint4*>(scratch + row * EP + ch * 16));
+        if (i < Ra && j < N) *reinterpret_cast<uint4*>(out + (int64_t)i * ldo + j) = *reinterpret_cast<const uint4*>(scratch + row * EP + ch * 16);
     }
 }
 

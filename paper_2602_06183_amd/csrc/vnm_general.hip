@@ -120,8 +120,11 @@ __global__ void __launch_bounds__(256) sqrelu_vnm_compress_m_kernel(const uint16
     for (int i = 0; i < 64 * LANES / 256; ++i) {
         const int e = threadIdx.x + 256 * i, row = e / LANES, j = e % LANES;
         if (M == 8) {
-            if (b0 + j * 32 < F)
-                store_out(vals + (tb * 64 + row) * (F / 4) + b0 / 4 + j * 8, *reinterpret_cast<const uint4*>(packed[j >> 1] + ((row * 32 + (j & 1) * 16) ^ ((j & 2) << 6))));
+            if (b0 + j * 32 < F) {
+                const uint4 w = *reinterpret_cast<const uint4*>(packed[j >> 1] + ((row * 32 + (j & 1) * 16) ^ ((j & 2) << 6)));
+                uint16_t* const p = vals + (tb * 64 + row) * (F / 4) + b0 / 4 + j * 8;
+                if (PAST) store_out(p, w); else *reinterpret_cast<uint4*>(p) = w;
+            }
         } else if (b0 + j * M < F) {
             *reinterpret_cast<uint32_t*>(vals + (tb * 64 + row) * (2 * F / M) + (b0 / M + j) * 2) = *reinterpret_cast<const uint32_t*>(packed[j / NB] + (row * NB + j % NB) * 4);
         }

@@ -70,3 +70,18 @@ def test_sums_of_the_other_splits_are_read_behind_the_count(tmp_path):
     counted = body.index("atomicrmw add")
     barrier, sums = body.find('asm sideeffect "", "~{memory}"', counted), re.compile(r"call [^\n]*split_join4[^\n]*ENKUl").search(body, counted)
     assert sums and counted < barrier < sums.start()
+
+
+def test_activations_are_stored_the_ordinary_way(kernels):
+    """The next kernel reads them; results of eqs. (1), (4) by themselves and of the compression have a non-temporal form for operands as large as the last-level cache."""
+    plain = re.compile(r"\tglobal_store_dwordx4 [^\n]*(?<! nt)\n")
+    past = re.compile(r"\tglobal_store_dwordx4 [^\n]* nt\n")
+    for source, pattern in (("gemm_vnm8.hip", "Vnm8Unit"), ("gemm_gather.hip", "Gather")):
+        units = {name: code for name, code in kernels(source).items() if pattern in name}
+        assert units
+        for name, code in units.items():
+            assert plain.search(code) and not past.search(code), name
+    rows = {name: code for name, code in kernels("gemm_v2_row.hip").items() if "GemmV2UnitILb1ELb1ELi0E" in name}
+    assert rows and all(len(plain.findall(code)) == len(past.findall(code)) > 0 for code in rows.values()), rows.keys()
+    compress = {name: code for name, code in kernels("vnm_general.hip").items() if "compress_m_kernelILi8E" in name}
+    assert {("Lb1E" in name, bool(past.search(code)), bool(plain.search(code))) for name, code in compress.items()} == {(True, True, False), (False, False, True)}
