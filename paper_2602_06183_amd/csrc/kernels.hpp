@@ -298,7 +298,7 @@ inline SplitPlan plan_split(int64_t T, int64_t N, int steps, int tile, float und
     return best;
 }
 // M = 8: a launch takes 5.6 us, and 0.257 us a stage of a round of 512 of the 64 tiles, 0.42 of that with a CU for each; the sums 3.7 us and 10 ns per workgroup.  Taken where that saves
-// 5 %.  (The counts, 6 of those 10 ns, have been spread over lines since.)  Fitted to 99 calls with 1 to 16 splits (what is chosen takes 2.0 % longer than the best of each, always undivided 10.6 %): T = 64, N = 4544, F = 19520 42.0 us undivided, 25.3 with 3,
+// 5 %.  (The counts, 6 of those 10 ns, have been spread over lines since: over 70 calls of 64 to 512 tokens what is chosen now takes 0.65 % longer than the best number of splits, always undivided 2.0 %.)  Fitted to 99 calls with 1 to 16 splits (what is chosen takes 2.0 % longer than the best of each, always undivided 10.6 %): T = 64, N = 4544, F = 19520 42.0 us undivided, 25.3 with 3,
 // 27.4 with 7; T = 256, N = 4352, F = 19584 83.6, 60.5 with 3; T = 64, N = 896, F = 3648 9.6, 11.3 with 7.
 inline SplitPlan plan_vnm8(int64_t T, int64_t N, int steps, int groups, bool fp8) {
     const int tile = pick_vnm8_tile(T, N, steps, groups, fp8);
@@ -368,6 +368,8 @@ inline bool wgrad_on_kept_rows(int64_t T, int64_t F, int M, int64_t experts) { r
 // and codes, at most 1e11 token-weight elements), each run both ways with three sets of inputs and weights in turn; some no longer stand for the part that they are named after.  Over
 // 2062 others what it chooses by itself takes 0.38 % longer than the better form in bf16 and 0.09 % on codes (the two calls 0.35 and 0.08 %, a forward call on packed weights 1.2 and 1.0 %: it takes the step's
 // tile in eq. (3), see step_tiles), one step in 36 4 % and more, the worst 25 %; always sharing would take 4.3 % longer in bf16 and, as far as these sizes go, nothing on codes.  T = 1984, D = 1344, F = 4160 181 us apart, 150 together.
+// (All of that on tiles of 128 in the shared launches.  With the tall ones of mix_plan.hpp in both forms, over 69 steps in bf16, 57 with experts and 149 on codes: 0.27, 0.30 and 0.37 % longer than
+// the better form, 9 of them 4 % and more, the worst 12 %.)
 // It errs mostly on experts, whose lengths it does not know (32 of them, T = 15104, D = 448, F = 1792, M = 16 411 / 322, apart), and on steps that have splits to lose (see step_tiles).
 struct StepCosts {
     struct Line { float fixed, step; float operator()(float steps) const { return fixed + step * steps; } };       // us of a tile, and of it per trip of its main loop
@@ -533,8 +535,8 @@ inline bool router_shares(int64_t rows, int64_t D, int64_t F, int M) {
 }
 
 // Do the stand-alone packing operations read their operands past the caches?  Where these are as large as the last-level cache, which then holds none of them, whoever wrote them, but takes time to be
-// filled.  Ordinary / past, operands in turn: SquaredReLU and compression of 512 MiB 123 / 113 us, of 896 MiB 222 / 196, eq. (6) on 256 MiB 50 / 46, on 1 GiB 205 / 191, pruning of 448 MiB along rows
-// 128 / 109, across 161 / 136; right after a copy has written them 332 / 321, 92 / 88, 412 / 400.  Smaller ones are found there: 64 MiB of y1 18 / 19, the same 128 MiB at M = 16 over and over 25 / 29.
+// filled.  Ordinary / past, operands in turn: SquaredReLU and compression of 448 MiB 113 / 100 us, of 512 126 / 111, of 896 223 / 195, eq. (6) on 256 MiB 52 / 50, on 1 GiB 207 / 193, pruning of
+// 448 MiB along rows 128 / 115, across 177 / 140; the same one over and over alike.  Smaller ones are found there: 64 MiB of y1 18 / 19, the same 128 MiB at M = 16 over and over 25 / 29.
 inline bool reads_past(int64_t bytes) { return bytes >= (int64_t)256 << 20; }
 // Do the results of the stand-alone eqs. (1), (4) leave non-temporally?  Where they are as large as the last-level cache, so that the next kernel does not find them there: spmm24_fwd, then
 // SquaredReLU and compression, ordinary / non-temporal: y1 of 256 MiB 649 / 578 us, of 512 1365 / 1191; of 128 181 / 184, of 64 95.5 / 96.7, of 1 9.9 / 10.2 (8 to 16 MiB 17.9 / 17.2, 25.8 / 24.7: not

@@ -47,6 +47,8 @@ inline float mix_time(const MixUnit* u, int m, float slots) {
 //   bf16, M = 8           from 1000 tokens on 0.909 (0.899), 300 - 1000 0.947 (0.933), below 0.986 (0.965)
 //   codes, M = 8          0.942 (0.925), 0.959 (0.936), 0.993 (0.969)
 //   M = 16, 32, 64        bf16 0.969 (0.960), 0.958 (0.947), 0.967 (0.959); codes 0.980 (0.968), 0.956 (0.945), 0.977 (0.965)
+// The bytes are those of one expert's weight where there are several: all of them hold every form down alike where tall ones save operand bytes (142 backward calls of 4 and 8 experts 0.973, with
+// the bytes of all 0.981).
 // Eqs. (3), (5), (4) and (7), (8) at M = 8: T = 1216, D = 5248, F = 17536 491 -> 411 us and 324 -> 256, T = 1344, D = 2240, F = 7424 92 -> 87 and 62 -> 57; with few tiles tall ones take
 // longer, a step of T = 2176, D = 832, F = 2752 76 us, all tall 85.
 // few: a launch of eqs. (3), (5), (4) with 64 tiles in eq. (3) and between one and that many rounds of the chip stays on 128: the estimate has the workgroups past the first round wait for a whole one,
@@ -114,7 +116,8 @@ inline unsigned mix_form(const MixTiles& k, int what, const MixCount& v, const M
 // on top of each.  Fitted to launches inside 130 steps of any size (T 128 - 16384, D 320 - 8192) on each tile; tall tiles where the estimate saves `save`.  Over the tile that the rules of
 // kernels.hpp choose: eqs. (3), (7) 0.943 of the time in bf16 and 0.961 on codes over all of them, none longer (T = 1664, D = 3968, F = 15616 155 us on the large tile, 169 on 128, 119;
 // T = 2304, D = 1856, F = 4864 41, 41, 34); eqs. (5), (8) in bf16 0.90 where they are chosen, one in nine, none above 0.945 (T = 2944, D = 3456, F = 9344 151 -> 137), on codes nothing;
-// eqs. (1), (4) 0.994, not built.
+// eqs. (1), (4) 0.994, not built.  Experts, not among the 130: their gradients are offered it nearly always where a step shares no launches, 22 backward calls 0.95, none above 1.00; with float32 sums
+// 87 calls 0.994, none above 1.02, without experts 15 calls 0.975.
 struct AloneTiles { MixTile large; float part; MixTile small, tall; float large_start, small_start, tall_start, save; };
 constexpr AloneTiles kAloneActivationBf16 = {{0.0f, 0.636f, 1.0f}, 0.621f, {0.0f, 0.582f, 0.501f}, {0.0f, 0.759f, 0.492f}, 8.15f, 5.56f, 6.88f, 0.06f};
 constexpr AloneTiles kAloneActivationFp8 = {{0.0f, 0.705f, 1.0f}, 0.69f, {0.0f, 0.629f, 0.476f}, {0.0f, 0.844f, 0.495f}, 9.2f, 6.46f, 7.95f, 0.06f};

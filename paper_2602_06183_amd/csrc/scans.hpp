@@ -58,8 +58,9 @@ __device__ __forceinline__ void transpose_bf16_body(void* smem, int bx, int by, 
 // ---- groups run along the strided axis: S[r,k] = src[k*ld + r] ---------------------------------
 // A workgroup takes 64 logical rows x 128 k: the 128 x 64 source tile goes through LDS so that both the HBM reads (128-byte row segments) and the
 // packed writes stay contiguous: lane = (row, 32 k), 4 lanes write 128 consecutive bytes of a row and a wavefront whole blocks.  Bound: HBM.
-// PAST: non-temporal loads (reads_past() in kernels.hpp); the stores stay ordinary, two of which make a line (R = 28672, K = 8192: 151 us, non-temporal 179).
-//   R = 16384, K = 4096: 65 us with one row per lane (32 bytes at a row's distance), 52 with four; with the unpruned transpose, R = 28672, K = 8192:
+// PAST: non-temporal loads (reads_past() in kernels.hpp); the stores stay ordinary, two of which make a line (R = 28672, K = 8192: 140 us, non-temporal 179).
+//   R = 16384, K = 4096, operands in turn past the last-level cache: 65 us with one row per lane (32 bytes at a row's distance), 47 with four, 43 (4.9 TB/s) with the loads in flight together and
+//   the selection on keys; one operand over and over, which that cache serves, 36 and 34; R = 8192, K = 4096 27 and 24, 22 and 20; with the unpruned transpose, R = 28672, K = 8192:
 //   296 and 248 us, 234 with the loads in flight together (5.1 TB/s).
 template <bool SOFT, bool PAST = false>
 __device__ __forceinline__ void prune24_cols_body(void* smem, int bx, int by, int bz, const uint16_t* __restrict__ src, int64_t R, int K, int64_t ld,
@@ -79,7 +80,7 @@ __device__ __forceinline__ void prune24_cols_body(void* smem, int bx, int by, in
         if (vblk) { vblk += m / 2; mblk += m / 8; }
         if (src_t) src_t += m;
     }
-    // all four loads before the first is waited for, so no branch around them: rows past the end, whose results go nowhere, are the last row again (T = 4096 x 8192: 9.8 -> 8.1 us)
+    // all four loads before the first is waited for, so no branch around them: rows past the end, whose results go nowhere, are the last row again
     uint4 w[4];
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
