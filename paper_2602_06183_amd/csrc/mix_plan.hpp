@@ -51,11 +51,11 @@ inline float mix_time(const MixUnit* u, int m, float slots) {
 // the bytes of all 0.981).
 // Eqs. (3), (5), (4) and (7), (8) at M = 8: T = 1216, D = 5248, F = 17536 491 -> 411 us and 324 -> 256, T = 1344, D = 2240, F = 7424 92 -> 87 and 62 -> 57; with few tiles tall ones take
 // longer, a step of T = 2176, D = 832, F = 2752 76 us, all tall 85.
-// few: a launch of eqs. (3), (5), (4) with 64 tiles in eq. (3) and between one and that many rounds of the chip stays on 128: the estimate has the workgroups past the first round wait for a whole one,
-// but the 64 tiles, first and short, make way for them at once.  Steps at M = 8 in bf16, 128 / tall: 1.02 rounds (T = 128, D = 1280,
-// F = 5568) 47.5 / 51.2 us, 1.03 (T = 64, D = 1408, F = 5312) 45.9 / 49.0, 1.21 (T = 192, D = 1536, F = 4992) 51.2 / 53.5, 1.30 (T = 128, D = 1664, F = 5568) 52.6 / 50.8;
-// 306 steps of up to 512 tokens that have such launches 0.991 of the time on 128 with and without this, the longest 1.00 and 1.08, 186 others 0.989 and 1.02.  Codes lose by it (0.995 -> 0.998),
-// wider blocks gain from tall tiles there (0.96 - 0.98 in four of five).
+// few: a launch of eqs. (3), (5), (4) with 64 tiles in eq. (3), up to three stages in eq. (5) and between one and that many rounds of the chip stays on 128: the estimate has the workgroups past the
+// first round wait for a whole one, but the 64 tiles, first and short, make way for them at once.  Steps at M = 8 in bf16, 128 / tall: 1.02 rounds (T = 128, D = 1280, F = 5568) 47.5 / 51.2 us, 1.03
+// (T = 64, D = 1408, F = 5312) 45.9 / 49.0, 1.21 (T = 192, D = 1536, F = 4992) 51.2 / 53.5, 1.30 (T = 128, D = 1664, F = 5568) 52.6 / 50.8; with more stages the shorter launch is worth more: T = 448,
+// D = 1472, F = 3648 0.87 of the time on tall tiles.  231 steps of 1.0 - 1.25 rounds, of the time on 128: 0.962, the longest 1.02; tall always 0.965, 1.08.  Not for experts (26 steps 1.05 of the time
+// on tall tiles), on codes (0.995 -> 0.998) and for wider blocks (tall 0.96 - 0.98 in four of five).
 struct MixTiles { MixTile v64, v[2], w64, w[2], g[2]; float bytes, few = 0.0f; };
 constexpr MixTiles kMixBf16 = {{3.77f, 0.227f, 0.86f}, {{0.0f, 0.434f, 0.674f}, {0.19f, 0.518f, 0.757f}}, {3.81f, 0.522f, 0.939f}, {{5.37f, 0.758f, 0.495f}, {9.28f, 1.373f, 0.45f}},
                                {{1.65f, 0.652f, 0.658f}, {3.68f, 1.01f, 0.808f}}, 0.23f, 1.25f};
@@ -95,7 +95,7 @@ inline unsigned mix_form(const MixTiles& k, int what, const MixCount& v, const M
     if (has_v && !w_first) add(1, k.w64, k.w, w);
     if (what != kMixBackwardTail) add(2, k.g[0], k.g, g);
     if (all <= 0.5f * slots) return 0;                         // (a CU for each)
-    if (what == kMixForwardTail && v.n64 && all > slots && all <= k.few * slots) return 0;
+    if (what == kMixForwardTail && v.n64 && w.stages <= 3 && all > slots && all <= k.few * slots) return 0;
     const unsigned may = (has_v && v.tall ? 1u : 0u) | (w.tall ? 2u : 0u), most = may | (what != kMixBackwardTail && g.tall && w.tall && (v.tall || !has_v || !v.n64) ? 4u : 0u);
     if (all > 16.0f * slots) return most;
     unsigned best = 0;
