@@ -571,6 +571,7 @@ int run_fp8_step(const sffn_cfg* cfg, const sffn_fp8_scales* sc, int n_experts, 
         REQUIRE(rc == SFFN_OK, SFFN_EWORKSPACE, "ffn_sparse_step_fp8: workspace missing or too small (sffn_fp8_workspace_bytes)");
     }
     hipStream_t s = (hipStream_t)stream;
+    const bool past = results_past(T, D);
     uint8_t *w1c = rg.at(L.pub.w1_codes), *w1m = rg.at(L.pub.w1_meta), *w2c = rg.at(L.pub.w2t_codes), *w2m = rg.at(L.pub.w2t_meta);
     uint16_t *y1 = (uint16_t*)(rg.at(L.pub.y1)), *dy2 = (uint16_t*)(rg.at(L.pub.dy2)), *dy1v = (uint16_t*)(rg.at(L.pub.dy1_vals)), *ykept = (uint16_t*)(rg.at(L.pub.y1_kept));
     uint8_t *y2c = rg.at(L.pub.y2_codes), *y2m = rg.at(L.pub.y2_meta), *cix = rg.at(L.pub.colidx);
@@ -661,17 +662,17 @@ int run_fp8_step(const sffn_cfg* cfg, const sffn_fp8_scales* sc, int n_experts, 
         const GemmGroup none;
         const int Kc = (int)(4 * F / M);
         const float a3 = sc->y2 * sc->w2, a7 = sc->dy1 * sc->w1;
-        const Vnm8Args v3 = {(const uint16_t*)vcb, mcb, cixt, w2tq, (int)D, (int)T, (int)D, (int)F, Y3, D, 0, 0, gr ? *gr : none, a3, split};
-        const Vnm8Args v7 = {(const uint16_t*)vcb2, mcb, cixt, w1q, (int)D, (int)T, (int)D, (int)F, dX, D, 0, 0, gr ? *gr : none, a7, split};
-        const GatherArgs u3 = {y2c, y2m, cix, w2tq, (int)D, (int)T, (int)D, Kc, logM, 0, a3, Y3, D, gr ? *gr : none, Split()};
-        const GatherArgs u7 = {dy1c, y2m, cix, w1q, (int)D, (int)T, (int)D, Kc, logM, 0, a7, dX, D, gr ? *gr : none, Split()};
+        const Vnm8Args v3 = {(const uint16_t*)vcb, mcb, cixt, w2tq, (int)D, (int)T, (int)D, (int)F, Y3, D, 0, 0, gr ? *gr : none, a3, split, past};
+        const Vnm8Args v7 = {(const uint16_t*)vcb2, mcb, cixt, w1q, (int)D, (int)T, (int)D, (int)F, dX, D, 0, 0, gr ? *gr : none, a7, split, past};
+        const GatherArgs u3 = {y2c, y2m, cix, w2tq, (int)D, (int)T, (int)D, Kc, logM, 0, a3, Y3, D, gr ? *gr : none, Split(), past};
+        const GatherArgs u7 = {dy1c, y2m, cix, w1q, (int)D, (int)T, (int)D, Kc, logM, 0, a7, dX, D, gr ? *gr : none, Split(), past};
         const GemmV2Args g4 = {(const uint16_t*)w2b, w2mb, (const uint16_t*)dyq, nullptr, (int)F, (int)T, (int)(D / 2), dy2, F, 0, 0, ep4, gp ? *gp : none, sc->dy * sc->w2};
         const WgradArgs w5 = {atb, kmask, dytb, sc->y2 * sc->dy, (int)F, (int)D, (int)T, dW2, F, 0, 0, gw ? *gw : none};
         const WgradArgs w8a = {at2, kmask, xtb, sc->dy1 * sc->x, (int)F, (int)D, (int)T, dW1, D, 0, 0, gw ? *gw : none};
         if (fwd && bwd) STAGE(launch_step_mix_fp8(kMixForwardTail, logM, tiles, &v3, &u3, &g4, w5, s), "step/y3+dW2+dy2");
         else if (fwd) {
-            if (wide) STAGE(launch_vnm_spmm_gather_fp8(y2c, y2m, cix, w2tq, D, a3, T, D, F, M, Y3, D, s, gr), "step/y3");
-            else STAGE(launch_vnm8_gemm_fp8(vcb, mcb, cixt, w2tq, D, a3, T, D, F, Y3, D, s, gr, tiles.v_alone, &split), "step/y3");
+            if (wide) STAGE(launch_vnm_spmm_gather_fp8(y2c, y2m, cix, w2tq, D, a3, T, D, F, M, Y3, D, s, gr, past), "step/y3");
+            else STAGE(launch_vnm8_gemm_fp8(vcb, mcb, cixt, w2tq, D, a3, T, D, F, Y3, D, s, gr, tiles.v_alone, &split, past), "step/y3");
             if (amax) STAGE(launch_amax_fold(fold, s), "step/fold(amax)");
         } else STAGE(launch_step_mix_fp8(kMixBackwardHead, logM, tiles, nullptr, nullptr, &g4, w5, s), "step/dW2+dy2");
         if (bwd) STAGE(launch_step_mix_fp8(kMixBackwardTail, logM, tiles, &v7, &u7, nullptr, w8a, s, amax ? &fold : nullptr), "step/dX+dW1");
@@ -679,8 +680,8 @@ int run_fp8_step(const sffn_cfg* cfg, const sffn_fp8_scales* sc, int n_experts, 
     }
     if (fwd && !packed && !together) STAGE(launch_fp8_prologue(p_w2, s), "step/prune24_fp8(W2.T)");
     if (fwd) {
-        if (wide) STAGE(launch_vnm_spmm_gather_fp8(y2c, y2m, cix, w2tq, D, sc->y2 * sc->w2, T, D, F, M, Y3, D, s, gr), "step/y3");      // eq. (3)
-        else STAGE(launch_vnm8_gemm_fp8(vcb, mcb, cixt, w2tq, D, sc->y2 * sc->w2, T, D, F, Y3, D, s, gr, tiles.v, &split), "step/y3");
+        if (wide) STAGE(launch_vnm_spmm_gather_fp8(y2c, y2m, cix, w2tq, D, sc->y2 * sc->w2, T, D, F, M, Y3, D, s, gr, past), "step/y3");      // eq. (3)
+        else STAGE(launch_vnm8_gemm_fp8(vcb, mcb, cixt, w2tq, D, sc->y2 * sc->w2, T, D, F, Y3, D, s, gr, tiles.v, &split, past), "step/y3");
     }
     // ---- Alg. 2 -------------------------------------------------------------------------------
     if (bwd && !together) STAGE(launch_fp8_prologue(p_dy, s), "step/quantize(dY, dY.T)");
@@ -690,8 +691,8 @@ int run_fp8_step(const sffn_cfg* cfg, const sffn_fp8_scales* sc, int n_experts, 
     }
     if (bwd) STAGE(launch_gemm_fp8_blocked(w2b, w2mb, dyq, nullptr, sc->dy * sc->w2, F, T, D, dy2, F, &ep4, s, gp, tiles.g_bwd), "step/dy2+dsqrelu_vnm");
     if (bwd) {
-        if (wide) STAGE(launch_vnm_spmm_gather_fp8(dy1c, y2m, cix, w1q, D, sc->dy1 * sc->w1, T, D, F, M, dX, D, s, gr), "step/dX");     // eq. (7)
-        else STAGE(launch_vnm8_gemm_fp8(vcb, mcb, cixt, w1q, D, sc->dy1 * sc->w1, T, D, F, dX, D, s, gr, tiles.v, &split), "step/dX");
+        if (wide) STAGE(launch_vnm_spmm_gather_fp8(dy1c, y2m, cix, w1q, D, sc->dy1 * sc->w1, T, D, F, M, dX, D, s, gr, past), "step/dX");     // eq. (7)
+        else STAGE(launch_vnm8_gemm_fp8(vcb, mcb, cixt, w1q, D, sc->dy1 * sc->w1, T, D, F, dX, D, s, gr, tiles.v, &split, past), "step/dX");
     }
     if (bwd) {
         if (w8) STAGE(launch_wgrad_vnm_fp8((const uint8_t*)atb, kmask, (const uint8_t*)xtb, sc->dy1 * sc->x, F, D, T, 0, dW1, D, s, gw, acc32), "step/dW1");   // eq. (8) on codes
@@ -993,7 +994,9 @@ static int run_router_step(const sffn_cfg* cfg, const int64_t* seg_offsets, cons
     ep1.stream = ep4.stream = streams_between(rows, D, F, 1, 6 * rows * Kc + 4 * F * D);
     GemmGroup g4 = g1;
     g4.bias_stride = 0;
-    const VnmEpilogue plain;
+    const bool past = results_past(T, D);
+    VnmEpilogue plain;
+    plain.stream = past;
     const GemmV2Args c1 = {w1cvb, w1cmb, xb, b1, (int)Kc, (int)rows, (int)D, y1c, Kc, 0, 0, ep1, g1, 1.0f}, c4 = {w2cvb, w2cmb, dyb, nullptr, (int)Kc, (int)rows, (int)D, dy2c, Kc, 0, 0, ep4, g4, 1.0f};
     const GemmV2Args c3 = {avb, amb, w2e, nullptr, (int)rows, (int)D, (int)Kc, Y3, D, 0, 0, plain, g0, 1.0f}, c7 = {avb2, amb, w1et, nullptr, (int)rows, (int)D, (int)Kc, dX, D, 0, 0, plain, g0, 1.0f};
     const bool one_launch = L.share && fwd && bwd;      // eqs. (3), (4)
@@ -1001,7 +1004,7 @@ static int run_router_step(const sffn_cfg* cfg, const int64_t* seg_offsets, cons
     if (fwd && behind) STAGE(launch_router_y1(c1, p_both, s), "router/y1c+sqrelu+2:4");                                            // eqs. (1), (2), Section 2.3
     else if (fwd) STAGE(launch_gemm_vnm_epilogue(w1cvb, w1cmb, xb, b1, Kc, rows, D, y1c, ep1, s, &g1), "router/y1c+sqrelu+2:4");
     if (fwd && !packed && !together && !behind) STAGE(launch_router_prologue(p_w2, s), "router/prepare(W2)");
-    if (fwd && !one_launch) STAGE(launch_spmm_blocked(avb, amb, w2e, nullptr, rows, D, Kc, 0, Y3, D, s, &g0), "router/y3");       // eq. (3)
+    if (fwd && !one_launch) STAGE(launch_spmm_blocked(avb, amb, w2e, nullptr, rows, D, Kc, 0, Y3, D, s, &g0, past), "router/y3");       // eq. (3)
     // ---- Alg. 2 ------------------------------------------------------------------------------------------------------
     if (bwd && !together && !(fwd && behind)) STAGE(launch_router_prologue(p_dy, s), "router/dY[perm].T");
     if (one_launch) STAGE(launch_router_dy2_y3(c4, c3, s), "router/dy2c+dsqrelu+y3");                                              // eqs. (4), (6) and (3)
@@ -1011,7 +1014,7 @@ static int run_router_step(const sffn_cfg* cfg, const int64_t* seg_offsets, cons
     if (bwd && !L.share) STAGE(launch_transpose(dw2t, F, D, D, dW2, 0, nullptr, s), "router/dW2");
     if (bwd && !one_launch) STAGE(launch_gemm_vnm_epilogue(w2cvb, w2cmb, dyb, nullptr, Kc, rows, D, dy2c, ep4, s, &g4), "router/dy2c+dsqrelu");
     if (bwd && L.share) STAGE(launch_router_dx(c7, dw2t, F, D, dW2, s), "router/dX+dW2");                                          // eq. (7), dW2.T -> dW2
-    else if (bwd) STAGE(launch_spmm_blocked(avb2, amb, w1et, nullptr, rows, D, Kc, 0, dX, D, s, &g0), "router/dX");                // eq. (7)
+    else if (bwd) STAGE(launch_spmm_blocked(avb2, amb, w1et, nullptr, rows, D, Kc, 0, dX, D, s, &g0, past), "router/dX");                // eq. (7)
     if (bwd) STAGE(launch_wgrad_router(at2, xpt, Kc, D, rows, dW1, D, s, g2), "router/dW1");                   // eq. (8)
     return SFFN_OK;
 }
@@ -1158,6 +1161,7 @@ static int run_step(const sffn_cfg* cfg, int n_experts, const int64_t* seg, cons
     }
 
     hipStream_t s = (hipStream_t)stream;
+    const bool past = results_past(T, D);
     uint16_t* w1v = (uint16_t*)(rg.at(L.pub.w1_vals));    uint8_t* w1m = rg.at(L.pub.w1_meta);
     uint16_t* w2v = (uint16_t*)(rg.at(L.pub.w2t_vals));   uint8_t* w2m = rg.at(L.pub.w2t_meta);
     uint16_t* y1 = (uint16_t*)(rg.at(L.pub.y1));
@@ -1230,26 +1234,26 @@ static int run_step(const sffn_cfg* cfg, int n_experts, const int64_t* seg, cons
         if (tiles.mix) {
             const GemmGroup none;
             const int Kc = (int)(4 * F / M);
-            const GatherArgs v3 = {y2v, y2m, cix, w2t, (int)D, (int)T, (int)D, Kc, logM, 0, 1.0f, Y3, D, gr ? *gr : none, split};
-            const GatherArgs v7 = {dy1v, y2m, cix, W1, (int)D, (int)T, (int)D, Kc, logM, 0, 1.0f, dX, D, gr ? *gr : none, split};
+            const GatherArgs v3 = {y2v, y2m, cix, w2t, (int)D, (int)T, (int)D, Kc, logM, 0, 1.0f, Y3, D, gr ? *gr : none, split, past};
+            const GatherArgs v7 = {dy1v, y2m, cix, W1, (int)D, (int)T, (int)D, Kc, logM, 0, 1.0f, dX, D, gr ? *gr : none, split, past};
             const GemmV2Args g4 = {w2vb, w2mb, dyb, nullptr, (int)F, (int)T, (int)D, dy2, F, 0, 0, ep4, gp ? *gp : none, 1.0f};
             const WgradArgs w5 = {atb, kmask, dytb, 1.0f, (int)F, (int)D, (int)T, dW2, F, 0, 0, gw ? *gw : none};
             const WgradArgs w8 = {at2, kmask, xtb, 1.0f, (int)F, (int)D, (int)T, dW1, D, 0, 0, gw ? *gw : none};
             if (fwd && bwd && !acc32) STAGE(launch_step_mix_bf16(kMixForwardTail, logM, tiles, false, nullptr, &v3, &g4, w5, s), "step/y3+dW2+dy2");
             else {
-                if (fwd) STAGE(launch_vnm_spmm_gather(y2v, y2m, cix, w2t, D, T, D, F, M, Y3, D, s, gr, &split), "step/y3");
+                if (fwd) STAGE(launch_vnm_spmm_gather(y2v, y2m, cix, w2t, D, T, D, F, M, Y3, D, s, gr, &split, past), "step/y3");
                 if (bwd) STAGE(launch_step_mix_bf16(kMixBackwardHead, logM, tiles, acc32, nullptr, nullptr, &g4, w5, s), "step/dW2+dy2");
             }
             if (bwd) STAGE(launch_step_mix_bf16(kMixBackwardTail, logM, tiles, acc32, nullptr, &v7, nullptr, w8, s), "step/dX+dW1");
             return SFFN_OK;
         }
         if (fwd && !packed && !together) STAGE(launch_step_prologue(part[1], s), "step/prune24(W2.T)");
-        if (fwd) STAGE(launch_vnm_spmm_gather(y2v, y2m, cix, w2t, D, T, D, F, M, Y3, D, s, gr, &split), "step/y3");                              // eq. (3)
+        if (fwd) STAGE(launch_vnm_spmm_gather(y2v, y2m, cix, w2t, D, T, D, F, M, Y3, D, s, gr, &split, past), "step/y3");                              // eq. (3)
         if (bwd && !together) STAGE(launch_step_prologue(part[2], s), "step/dY.T");
         if (bwd && kept) STAGE(launch_wgrad_wide(atb, cix, dytb, F, D, T, logM, 1, dW2, F, s, gw, acc32), "step/dW2");                       // eq. (5)
         else if (bwd) STAGE(launch_wgrad_vnm(atb, kmask, dytb, F, D, T, 1, dW2, F, s, gw, acc32, false, tiles.w), "step/dW2");                       // eq. (5)
         if (bwd) STAGE(launch_gemm_vnm_epilogue(w2vb, w2mb, dyb, nullptr, F, T, D, dy2, ep4, s, gp, tiles.g_bwd), "step/dy2+dsqrelu_vnm");      // eqs. (4), (6)
-        if (bwd) STAGE(launch_vnm_spmm_gather(dy1v, y2m, cix, W1, D, T, D, F, M, dX, D, s, gr, &split), "step/dX");                              // eq. (7), dense W1 as is
+        if (bwd) STAGE(launch_vnm_spmm_gather(dy1v, y2m, cix, W1, D, T, D, F, M, dX, D, s, gr, &split, past), "step/dX");                              // eq. (7), dense W1 as is
         if (bwd && kept) STAGE(launch_wgrad_wide(at2, cix, xtb, F, D, T, logM, 0, dW1, D, s, gw, acc32), "step/dW1");                        // eq. (8)
         else if (bwd) STAGE(launch_wgrad_vnm(at2, kmask, xtb, F, D, T, 0, dW1, D, s, gw, acc32, false, tiles.w), "step/dW1");                        // eq. (8)
         return SFFN_OK;
@@ -1275,7 +1279,7 @@ static int run_step(const sffn_cfg* cfg, int n_experts, const int64_t* seg, cons
         const bool gather = vnm_spmm_gather_ok(T, D, F, M) && F * D * 2 < ((int64_t)1 << 31);
         if (gather) {
             STAGE(launch_transpose(W2, D, F, F, w1t, 0, nullptr, s), "step/W2.T");
-            STAGE(launch_vnm_spmm_gather(y2v, y2m, cix, w1t, D, T, D, F, M, Y3, D, s, nullptr, &split), "step/y3");                    // eq. (3)
+            STAGE(launch_vnm_spmm_gather(y2v, y2m, cix, w1t, D, T, D, F, M, Y3, D, s, nullptr, &split, past), "step/y3");                    // eq. (3)
         } else {
             STAGE(launch_vnm_to_24_m(y2v, y2m, cix, T, F, M, a24v, a24m, s), "step/to24(y2)");
             STAGE(launch_gemm_nt(1, a24v, a24m, W2, nullptr, T, D, F, 0, Y3, D, s), "step/y3");                       // eq. (3)
@@ -1288,7 +1292,7 @@ static int run_step(const sffn_cfg* cfg, int n_experts, const int64_t* seg, cons
         STAGE(launch_gemm_vnm_epilogue(w2vb, w2mb, dyb, nullptr, F, T, D, dy2, plain, s), "step/dy2");                // eq. (4)
         STAGE(launch_dsqrelu_vnm_m(dy2, y1, y2m, cix, T, F, M, dy1v, s), "step/dsqrelu_vnm");                         // eq. (6)
         if (gather) {
-            STAGE(launch_vnm_spmm_gather(dy1v, y2m, cix, W1, D, T, D, F, M, dX, D, s, nullptr, &split), "step/dX");                    // eq. (7)
+            STAGE(launch_vnm_spmm_gather(dy1v, y2m, cix, W1, D, T, D, F, M, dX, D, s, nullptr, &split, past), "step/dX");                    // eq. (7)
         } else {
             STAGE(launch_vnm_to_24_m(dy1v, y2m, cix, T, F, M, a24v, a24m, s), "step/to24(dy1)");
             STAGE(launch_transpose(W1, F, D, D, w1t, 0, nullptr, s), "step/W1.T");
@@ -1355,26 +1359,26 @@ static int run_step(const sffn_cfg* cfg, int n_experts, const int64_t* seg, cons
     ep4.vcb = vcb2; ep4.mcb = mcb; ep4.at = at2; ep4.stream = streamed;
     if (tiles.mix) {
         const GemmGroup none;
-        const Vnm8Args v3 = {vcb, mcb, cixt, (const uint8_t*)w2t, (int)D, (int)T, (int)D, (int)F, Y3, D, 0, 0, gd ? *gd : none, 1.0f, split};
-        const Vnm8Args v7 = {vcb2, mcb, cixt, (const uint8_t*)W1, (int)D, (int)T, (int)D, (int)F, dX, D, 0, 0, gd ? *gd : none, 1.0f, split};
+        const Vnm8Args v3 = {vcb, mcb, cixt, (const uint8_t*)w2t, (int)D, (int)T, (int)D, (int)F, Y3, D, 0, 0, gd ? *gd : none, 1.0f, split, past};
+        const Vnm8Args v7 = {vcb2, mcb, cixt, (const uint8_t*)W1, (int)D, (int)T, (int)D, (int)F, dX, D, 0, 0, gd ? *gd : none, 1.0f, split, past};
         const GemmV2Args g4 = {w2vb, w2mb, dyb, nullptr, (int)F, (int)T, (int)D, dy2, F, 0, 0, ep4, gp ? *gp : none, 1.0f};
         const WgradArgs w5 = {atb, kmask, dytb, 1.0f, (int)F, (int)D, (int)T, dW2, F, 0, 0, gw ? *gw : none};
         const WgradArgs w8 = {at2, kmask, xtb, 1.0f, (int)F, (int)D, (int)T, dW1, D, 0, 0, gw ? *gw : none};
         if (fwd && bwd && !acc32) STAGE(launch_step_mix_bf16(kMixForwardTail, 3, tiles, false, &v3, nullptr, &g4, w5, s), "step/y3+dW2+dy2");
         else {
-            if (fwd) STAGE(launch_vnm8_gemm(vcb, mcb, cixt, w2t, D, T, D, F, Y3, D, s, gd, tiles.v_alone, &split), "step/y3");
+            if (fwd) STAGE(launch_vnm8_gemm(vcb, mcb, cixt, w2t, D, T, D, F, Y3, D, s, gd, tiles.v_alone, &split, past), "step/y3");
             if (bwd) STAGE(launch_step_mix_bf16(kMixBackwardHead, 3, tiles, acc32, nullptr, nullptr, &g4, w5, s), "step/dW2+dy2");
         }
         if (bwd) STAGE(launch_step_mix_bf16(kMixBackwardTail, 3, tiles, acc32, &v7, nullptr, nullptr, w8, s), "step/dX+dW1");
         return SFFN_OK;
     }
     if (fwd && !packed && !together) STAGE(launch_step_prologue(part[1], s), "step/prune24(W2.T)");
-    if (fwd) STAGE(launch_vnm8_gemm(vcb, mcb, cixt, w2t, D, T, D, F, Y3, D, s, gd, tiles.v, &split), "step/y3");                // eq. (3)
+    if (fwd) STAGE(launch_vnm8_gemm(vcb, mcb, cixt, w2t, D, T, D, F, Y3, D, s, gd, tiles.v, &split, past), "step/y3");                // eq. (3)
     if (bwd && !together) STAGE(launch_step_prologue(part[2], s), "step/dY.T");
     // ---- Alg. 2 -------------------------------------------------------------------------------
     if (bwd) STAGE(launch_wgrad_vnm(atb, kmask, dytb, F, D, T, 1, dW2, F, s, gw, acc32, true, tiles.w), "step/dW2");           // eq. (5)
     if (bwd) STAGE(launch_gemm_vnm_epilogue(w2vb, w2mb, dyb, nullptr, F, T, D, dy2, ep4, s, gp, tiles.g_bwd), "step/dy2+dsqrelu_vnm");
-    if (bwd) STAGE(launch_vnm8_gemm(vcb2, mcb, cixt, W1, D, T, D, F, dX, D, s, gd, tiles.v, &split), "step/dX");                // eq. (7), dense W1 as is
+    if (bwd) STAGE(launch_vnm8_gemm(vcb2, mcb, cixt, W1, D, T, D, F, dX, D, s, gd, tiles.v, &split, past), "step/dX");                // eq. (7), dense W1 as is
     if (bwd) STAGE(launch_wgrad_vnm(at2, kmask, xtb, F, D, T, 0, dW1, D, s, gw, acc32, true, tiles.w), "step/dW1");            // eq. (8)
     (void)w1tb;
     return SFFN_OK;

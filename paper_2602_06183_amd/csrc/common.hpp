@@ -16,7 +16,7 @@ __device__ __forceinline__ float bf2f(uint32_t h) { return __uint_as_float(h << 
 // 16 bytes of a weight gradient, non-temporal: nothing reads it before the optimizer does, and stored the ordinary way the gradients push the operands that the other tiles share out of L2 and of
 // the last-level cache.  Of the time with ordinary stores: 27 drawn steps 0.987, 14 on codes 0.978; with an update of the weights right behind the step 1.01 at 1 MB of gradient, 0.99 - 1.00 from 4 MB on.
 // Activations (Y3, dX, y1, dy2, packed rows) the next kernel reads, and pays for it: vnm_spmm, then spmm24_fwd on its result, ordinary / non-temporal T = 256, D = 512, F = 1024 14.0 / 14.7 us,
-// T = D = 1024, F = 4096 27.4 / 29.2, T = 8192, D = 2048, F = 8192 263 / 274; see stores_past() in kernels.hpp.
+// T = D = 1024, F = 4096 27.4 / 29.2, T = 8192, D = 2048, F = 8192 263 / 274; where they leave so all the same: stores_past(), results_past(), streams_between() in kernels.hpp.
 typedef __attribute__((ext_vector_type(4))) uint32_t sffn_u32x4;
 __device__ __forceinline__ void store_out(void* p, const uint4& w) { __builtin_nontemporal_store(__builtin_bit_cast(sffn_u32x4, w), reinterpret_cast<sffn_u32x4*>(p)); }
 __device__ __forceinline__ void store_out(void* p, const float4& w) { store_out(p, __builtin_bit_cast(uint4, w)); }

@@ -44,7 +44,7 @@ template <class TL>
 __device__ __forceinline__ void vnm_gather_body(unsigned char* __restrict__ smem, int pid, int n_pid, const uint16_t* __restrict__ a_vals, const uint8_t* __restrict__ a_meta,
                                                              const uint8_t* __restrict__ colidx, const uint16_t* __restrict__ Wk,
                                                              int ldw, int N, int Kc, int logM, int nblk_tok, int tiles_n,
-                                                             uint16_t* __restrict__ out, int64_t ldo, const GemmGroup& grp, const Split& split) {
+                                                             uint16_t* __restrict__ out, int64_t ldo, const GemmGroup& grp, const Split& split, bool past) {
     constexpr int KW = TL::KW, ROW = TL::ROW, kGB = TL::kB, kGA = TL::kA, kGStage = TL::kStage, kGStages = TL::NST, kGLoads = TL::kLoads;
     unsigned char* const cix = smem + TL::RING;
 
@@ -250,13 +250,14 @@ __device__ __forceinline__ void vnm_gather_body(unsigned char* __restrict__ smem
             }
     wave_lds_sync();
     const int nw = n0 + 64 * wt;
-    if (nw < N) {
+    if (nw < N)
+        store_between(past, [&](auto store) {
 #pragma unroll
-        for (int p = 0; p < 8; ++p) {
-            const int row = p * 8 + (lane >> 3), ch = lane & 7;
-            *reinterpret_cast<uint4*>(out + (int64_t)(t0 + row) * ldo + nw + ch * 8) = *reinterpret_cast<const uint4*>(scratch + row * EP + ch * 16);
-        }
-    }
+            for (int p = 0; p < 8; ++p) {
+                const int row = p * 8 + (lane >> 3), ch = lane & 7;
+                store(out + (int64_t)(t0 + row) * ldo + nw + ch * 8, *reinterpret_cast<const uint4*>(scratch + row * EP + ch * 16));
+            }
+        });
 }
 
 // The same contraction on E4M3 codes (the fp8 step with blocks of M >= 16 columns): Ac = the survivors' codes [T, K' / 2] + the same
@@ -270,7 +271,7 @@ constexpr int kG8Stage = 128 * 256 + 64 * 64 + 64 * 16;
 __device__ __forceinline__ void vnm_gather_fp8_body(unsigned char* __restrict__ smem, int pid, int n_pid, const uint8_t* __restrict__ a_codes, const uint8_t* __restrict__ a_meta,
                                                                  const uint8_t* __restrict__ colidx, const uint8_t* __restrict__ Wq,
                                                                  int ldw, int N, int Kc, int logM, int nblk_tok, int tiles_n, float alpha,
-                                                                 uint16_t* __restrict__ out, int64_t ldo, const GemmGroup& grp) {
+                                                                 uint16_t* __restrict__ out, int64_t ldo, const GemmGroup& grp, bool past) {
     constexpr int kB = 128 * 256, kA = 64 * 64, kStage = kG8Stage;      // 37888 bytes; two stages = 74 KB: two workgroups per CU
 
     const int tid = threadIdx.x, lane = tid & 63;
@@ -432,13 +433,14 @@ __device__ __forceinline__ void vnm_gather_fp8_body(unsigned char* __restrict__ 
             }
     wave_lds_sync();
     const int nw = n0 + 64 * wave;
-    if (nw < N) {
+    if (nw < N)
+        store_between(past, [&](auto store) {
 #pragma unroll
-        for (int p = 0; p < 8; ++p) {
-            const int row = p * 8 + (lane >> 3), ch = lane & 7;
-            *reinterpret_cast<uint4*>(out + (int64_t)(t0 + row) * ldo + nw + ch * 8) = *reinterpret_cast<const uint4*>(scratch + row * EP + ch * 16);
-        }
-    }
+            for (int p = 0; p < 8; ++p) {
+                const int row = p * 8 + (lane >> 3), ch = lane & 7;
+                store(out + (int64_t)(t0 + row) * ldo + nw + ch * 8, *reinterpret_cast<const uint4*>(scratch + row * EP + ch * 16));
+            }
+        });
 }
 
 template <class TL>
@@ -446,7 +448,7 @@ struct GatherUnit {
     using Args = GatherArgs;
     static constexpr int THREADS = TL::THREADS, LDS = TL::RING + kGMaxKc;
     static __device__ __forceinline__ void run(unsigned char* smem, int pid, int n_pid, const Args& a) {
-        vnm_gather_body<TL>(smem, pid, n_pid, (const uint16_t*)a.a_vals, a.a_meta, a.colidx, (const uint16_t*)a.Wk, a.ldw, a.N, a.Kc, a.logM, a.T >> 6, a.tiles_n, a.out, a.ldo, a.grp, a.split);
+        vnm_gather_body<TL>(smem, pid, n_pid, (const uint16_t*)a.a_vals, a.a_meta, a.colidx, (const uint16_t*)a.Wk, a.ldw, a.N, a.Kc, a.logM, a.T >> 6, a.tiles_n, a.out, a.ldo, a.grp, a.split, a.past != 0);
     }
     static unsigned count(const Args& a) { return (unsigned)((a.T >> 6) * ((a.N + TL::BN - 1) / TL::BN) * a.split.n); }
     static int stages(const Args& a) { return a.Kc / 64 / (TL::KW * a.split.n); }      // of a tile, a wavefront's (wgrad_first)
@@ -458,7 +460,7 @@ struct GatherFp8Unit {
     using Args = GatherArgs;
     static constexpr int THREADS = 256, LDS = kGStages * kG8Stage;
     static __device__ __forceinline__ void run(unsigned char* smem, int pid, int n_pid, const Args& a) {
-        vnm_gather_fp8_body(smem, pid, n_pid, (const uint8_t*)a.a_vals, a.a_meta, a.colidx, (const uint8_t*)a.Wk, a.ldw, a.N, a.Kc, a.logM, a.T >> 6, a.tiles_n, a.alpha, a.out, a.ldo, a.grp);
+        vnm_gather_fp8_body(smem, pid, n_pid, (const uint8_t*)a.a_vals, a.a_meta, a.colidx, (const uint8_t*)a.Wk, a.ldw, a.N, a.Kc, a.logM, a.T >> 6, a.tiles_n, a.alpha, a.out, a.ldo, a.grp, a.past != 0);
     }
     static unsigned count(const Args& a) { return (unsigned)((a.T >> 6) * ((a.N + 255) / 256)); }
     static int stages(const Args& a) { return a.Kc / 128; }

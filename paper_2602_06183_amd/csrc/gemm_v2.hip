@@ -5,10 +5,12 @@
 namespace sffn {
 
 hipError_t launch_spmm_blocked(const uint16_t* a_vals, const uint8_t* a_meta, const uint16_t* B, const float* bias, int64_t Ra, int64_t Rb,
-                               int64_t K, int out_i_contig, uint16_t* out, int64_t ldo, hipStream_t s, const GemmGroup* grp) {
+                               int64_t K, int out_i_contig, uint16_t* out, int64_t ldo, hipStream_t s, const GemmGroup* grp, bool past) {
     const GemmGroup g = grp ? *grp : GemmGroup();
+    VnmEpilogue ep;
+    ep.stream = past;
     if (out_i_contig || g.n > GemmGroup::kMaxExperts || (g.n && g.role == 2)) return hipErrorInvalidValue;
-    return launch_gemm_v2<true, false, 0, true, false>({a_vals, a_meta, B, bias, (int)Ra, (int)Rb, (int)K, out, ldo, 0, 0, VnmEpilogue(), g, 1.0f}, s);
+    return launch_gemm_v2<true, false, 0, true, false>({a_vals, a_meta, B, bias, (int)Ra, (int)Rb, (int)K, out, ldo, 0, 0, ep, g, 1.0f}, s);
 }
 
 // Dense operands, blocked: a load is 1 KB of consecutive bytes.  (Row-major ones were fetched as 64-byte halves of 16 lines: 8192 tokens, 4 experts, D = 2048, F = 8192

@@ -957,17 +957,20 @@ __device__ __forceinline__ void gemm_nt_v2_body(unsigned char* __restrict__ smem
                     for (int r = 0; r < 4; ++r)
                         *reinterpret_cast<uint16_t*>(scratch + (x * 16 + 4 * lq + r) * EP + (b * 16 + l16) * 2) = (uint16_t)f2bf(FP8 ? acc[2 * a + x][b][r] * alpha : acc[2 * a + x][b][r]);
             wave_lds_sync();
+            auto rows = [&](auto store) {
 #pragma unroll
-            for (int p = 0; p < 32 * CH / 64; ++p) {
-                const int e = lane + 64 * p, row = e / CH, ch = e % CH;
-                const int i = i0 + wm * WM + a * 32 + row, j = j0 + wn * WN + ch * 8;
-                if (i < Ra && j < Rb) {
-                    int64_t io = grp.map_logM ? ((int64_t)(i >> 2) << grp.map_logM) + 4 * expert_id + (i & 3) : i;
-                    if (grp.out_row_map) io = io_map[a][p];
-                    const uint4 w = *reinterpret_cast<const uint4*>(scratch + row * EP + ch * 16);
-                    if (io >= 0) { if (SPARSE) *reinterpret_cast<uint4*>(out + io * ldo + j) = w; else store_out(out + io * ldo + j, w); }      // (dense: the router's weight gradients)
+                for (int p = 0; p < 32 * CH / 64; ++p) {
+                    const int e = lane + 64 * p, row = e / CH, ch = e % CH;
+                    const int i = i0 + wm * WM + a * 32 + row, j = j0 + wn * WN + ch * 8;
+                    if (i < Ra && j < Rb) {
+                        int64_t io = grp.map_logM ? ((int64_t)(i >> 2) << grp.map_logM) + 4 * expert_id + (i & 3) : i;
+                        if (grp.out_row_map) io = io_map[a][p];
+                        if (io >= 0) store(out + io * ldo + j, *reinterpret_cast<const uint4*>(scratch + row * EP + ch * 16));
+                    }
                 }
-            }
+            };
+            if (SPARSE) store_between(ep.stream, rows);
+            else rows([](uint16_t* p, const uint4& w) { store_out(p, w); });       // the router's weight gradients
             wave_lds_sync();
         }
     }

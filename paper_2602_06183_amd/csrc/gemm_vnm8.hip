@@ -23,7 +23,8 @@ static bool long_tile(const Vnm8Args& a) {
 }
 
 template <bool FP8>
-static hipError_t launch_impl(Vnm8Args a, hipStream_t s, const GemmGroup* grp, int tile, const Split* split) {
+static hipError_t launch_impl(Vnm8Args a, hipStream_t s, const GemmGroup* grp, int tile, const Split* split, bool past) {
+    a.past = past;
     a.grp = grp ? *grp : GemmGroup();
     if (a.grp.n && (a.grp.role != 0 || a.grp.seg_dev || a.grp.n > GemmGroup::kMaxExperts)) return hipErrorInvalidValue;
     if (!tile) tile = pick_vnm8_tile(a.T, a.N, a.F / (FP8 ? 128 : 64), a.grp.n, FP8);
@@ -40,15 +41,15 @@ static hipError_t launch_impl(Vnm8Args a, hipStream_t s, const GemmGroup* grp, i
 }
 
 hipError_t launch_vnm8_gemm(const uint16_t* vcb, const uint8_t* mcb, const uint8_t* cixt, const uint16_t* Wk, int64_t ldw, int64_t T, int64_t N,
-                            int64_t F, uint16_t* out, int64_t ldo, hipStream_t s, const GemmGroup* grp, int tile, const Split* split) {
+                            int64_t F, uint16_t* out, int64_t ldo, hipStream_t s, const GemmGroup* grp, int tile, const Split* split, bool past) {
     if (!vnm8_gemm_ok(T, N, F, ldw)) return hipErrorInvalidValue;
-    return launch_impl<false>({vcb, mcb, cixt, reinterpret_cast<const uint8_t*>(Wk), (int)ldw, (int)T, (int)N, (int)F, out, ldo, 0, 0, GemmGroup(), 1.0f, Split()}, s, grp, tile, split);
+    return launch_impl<false>({vcb, mcb, cixt, reinterpret_cast<const uint8_t*>(Wk), (int)ldw, (int)T, (int)N, (int)F, out, ldo, 0, 0, GemmGroup(), 1.0f, Split()}, s, grp, tile, split, past);
 }
 
 hipError_t launch_vnm8_gemm_fp8(const uint8_t* vcb, const uint8_t* mcb, const uint8_t* cixt, const uint8_t* Wq, int64_t ldw, float alpha, int64_t T,
-                                int64_t N, int64_t F, uint16_t* out, int64_t ldo, hipStream_t s, const GemmGroup* grp, int tile, const Split* split) {
+                                int64_t N, int64_t F, uint16_t* out, int64_t ldo, hipStream_t s, const GemmGroup* grp, int tile, const Split* split, bool past) {
     if (!vnm8_gemm_fp8_ok(T, N, F, ldw)) return hipErrorInvalidValue;
-    return launch_impl<true>({reinterpret_cast<const uint16_t*>(vcb), mcb, cixt, Wq, (int)ldw, (int)T, (int)N, (int)F, out, ldo, 0, 0, GemmGroup(), alpha, Split()}, s, grp, tile, split);
+    return launch_impl<true>({reinterpret_cast<const uint16_t*>(vcb), mcb, cixt, Wq, (int)ldw, (int)T, (int)N, (int)F, out, ldo, 0, 0, GemmGroup(), alpha, Split()}, s, grp, tile, split, past);
 }
 
 }  // namespace sffn

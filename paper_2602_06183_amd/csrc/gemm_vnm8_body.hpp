@@ -79,7 +79,7 @@ template <bool FP8, class TL>
 __device__ __forceinline__ void vnm8_gemm_body(unsigned char* __restrict__ smem, int pid, int n_pid, const uint16_t* __restrict__ vcb, const uint8_t* __restrict__ mcb,
                                                const uint8_t* __restrict__ cixt, const uint8_t* __restrict__ Wk, int ldw,
                                                int Ra, int N, int F, int Ttot, uint16_t* __restrict__ out, int64_t ldo,
-                                               int tiles_m, int tiles_n, const GemmGroup& grp, float alpha, const Split& split) {
+                                               int tiles_m, int tiles_n, const GemmGroup& grp, float alpha, const Split& split, bool past) {
     using GG = G<FP8, TL>;
     constexpr int kB = GG::kB, kA = GG::kA, kMt = GG::kMt, kC = GG::kC, kStage = GG::kStage, ES = GG::ES, kStages = TL::NST, kLoads = GG::LOADS, KW = TL::KW, FN = TL::FN;
     constexpr int BT = TL::BT, BN = TL::BN, ROW = GG::ROW, B_LD = GG::B_LD, A_LD = GG::A_LD, M_LD = GG::M_LD, PB = GG::PIECE, PM = GG::PMASK;
@@ -386,12 +386,14 @@ __device__ __forceinline__ void vnm8_gemm_body(unsigned char* __restrict__ smem,
                     *reinterpret_cast<uint16_t*>(scratch + row * EP + (b * 32 + l32) * 2) = (uint16_t)f2bf(FP8 ? acc[a][2 * half + b][r] * alpha : acc[a][2 * half + b][r]);
                 }
             wave_lds_sync();
+            store_between(past, [&](auto store) {
 #pragma unroll
-            for (int p = 0; p < 4; ++p) {
-                const int e = lane + 64 * p, row = e >> 3, ch = e & 7;
-                const int i = i0 + tbw * 64 + a * 32 + row, j = n0 + nh * 32 * FN + half * 64 + ch * 8;
-                if (i < Ra && j < N) *reinterpret_cast<uint4*>(out + (int64_t)i * ldo + j) = *reinterpret_cast<const uint4*>(scratch + row * EP + ch * 16);
-            }
+                for (int p = 0; p < 4; ++p) {
+                    const int e = lane + 64 * p, row = e >> 3, ch = e & 7;
+                    const int i = i0 + tbw * 64 + a * 32 + row, j = n0 + nh * 32 * FN + half * 64 + ch * 8;
+                    if (i < Ra && j < N) store(out + (int64_t)i * ldo + j, *reinterpret_cast<const uint4*>(scratch + row * EP + ch * 16));
+                }
+            });
             wave_lds_sync();
         }
 }
@@ -408,7 +410,7 @@ struct Vnm8Unit {
     using Args = Vnm8Args;
     static constexpr int THREADS = TL::THREADS, LDS = G<FP8, TL>::BYTES;
     static __device__ __forceinline__ void run(unsigned char* smem, int pid, int n_pid, const Args& a) {
-        vnm8_gemm_body<FP8, TL>(smem, pid, n_pid, a.vcb, a.mcb, a.cixt, a.Wk, a.ldw, a.T, a.N, a.F, a.T, a.out, a.ldo, a.tiles_m, a.tiles_n, a.grp, a.alpha, a.split);
+        vnm8_gemm_body<FP8, TL>(smem, pid, n_pid, a.vcb, a.mcb, a.cixt, a.Wk, a.ldw, a.T, a.N, a.F, a.T, a.out, a.ldo, a.tiles_m, a.tiles_n, a.grp, a.alpha, a.split, a.past != 0);
     }
     static unsigned count(const Args& a) { return vnm8_tiles(a.T, a.N, a.grp, TL::BT, TL::BN) * (unsigned)a.split.n; }
     static int stages(const Args& a) { return a.F / (FP8 ? 128 : 64) / (TL::KW * a.split.n); }      // of a tile, a wavefront's (wgrad_first)

@@ -89,11 +89,11 @@ struct GemmV2Args {
 struct Split { float* part = nullptr; unsigned* count = nullptr; int n = 1; };
 struct Vnm8Args {
     const uint16_t* vcb; const uint8_t* mcb; const uint8_t* cixt; const uint8_t* Wk; int ldw, T, N, F; uint16_t* out; int64_t ldo; int tiles_m, tiles_n;
-    GemmGroup grp; float alpha; Split split;
+    GemmGroup grp; float alpha; Split split; int past = 0;
 };
 struct GatherArgs {
     const void* a_vals; const uint8_t* a_meta; const uint8_t* colidx; const void* Wk; int ldw, T, N, Kc, logM, tiles_n; float alpha; uint16_t* out; int64_t ldo; GemmGroup grp;
-    Split split;
+    Split split; int past = 0;
 };
 struct WgradArgs {
     const uint16_t* atc; const uint8_t* kmask; const uint16_t* G; float alpha; int F, N, T; uint16_t* out; int64_t ldo; int tiles_m, tiles_n; GemmGroup grp;
@@ -542,6 +542,11 @@ inline bool reads_past(int64_t bytes) { return bytes >= (int64_t)256 << 20; }
 // SquaredReLU and compression, ordinary / non-temporal: y1 of 256 MiB 649 / 578 us, of 512 1365 / 1191; of 128 181 / 184, of 64 95.5 / 96.7, of 1 9.9 / 10.2 (8 to 16 MiB 17.9 / 17.2, 25.8 / 24.7: not
 // taken, Y3 of that size loses 7 %).
 inline bool stores_past(int64_t bytes) { return bytes >= (int64_t)256 << 20; }
+// Do Y3 and dX of a step?  From 16 MiB on, half of what the L2s hold together: the next layer's passes read them once, in order, and are no slower, while the step gains.  Of the time with ordinary
+// stores, bf16 and M = 32 at 16 - 64 MiB: the step alone 0.971 - 1.000, with residuals added to both 0.978 - 1.006, two layers in a row 0.960 - 1.004, two forward calls in a row 0.985 - 1.016; below, up
+// to 1.016, 1.013, 1.034 and 1.055 (T = 6144, D = 1024, F = 4096 159 -> 168 us the forward calls).  Codes 0.97 - 1.01 at any size.  Not the stand-alone vnm_spmm: spmm24_fwd, which reads its operand from
+// many tiles, takes 2 - 9 % longer on such a result at every size.
+inline bool results_past(int64_t T, int64_t D) { return 2 * T * D >= (int64_t)16 << 20; }
 hipError_t launch_prune24(const uint16_t* src, int64_t R, int64_t K, int64_t ld, int trans, int mode, uint16_t* vals,
                           uint8_t* meta, hipStream_t stream);
 hipError_t launch_dsqrelu_vnm(const uint16_t* dy2, const uint16_t* y1, const uint8_t* meta, const uint8_t* colidx,
@@ -565,12 +570,12 @@ hipError_t launch_vnm_expand_t_m(const uint16_t* vals, const uint8_t* meta, cons
 bool vnm_spmm_gather_ok(int64_t T, int64_t N, int64_t F, int M);
 // grp (role 0, host segment table): the token blocks of segment e take expert e's matrix Wk + e * b_stride.
 hipError_t launch_vnm_spmm_gather(const uint16_t* a_vals, const uint8_t* a_meta, const uint8_t* colidx, const uint16_t* Wk, int64_t ldw,
-                                  int64_t T, int64_t N, int64_t F, int M, uint16_t* out, int64_t ldo, hipStream_t s, const GemmGroup* grp = nullptr, const Split* split = nullptr);
+                                  int64_t T, int64_t N, int64_t F, int M, uint16_t* out, int64_t ldo, hipStream_t s, const GemmGroup* grp = nullptr, const Split* split = nullptr, bool past = false);
 // eqs. (3), (7) for M = 8 on a 256-token tile (gemm_vnm8.hip): the activation as the epilogues' vcb / mcb / cixt arrays, Wk = [F, ldw] with the
 // contraction index as row; T, N, F multiples of 64.  grp as above (b_stride in elements).
 bool vnm8_gemm_ok(int64_t T, int64_t N, int64_t F, int64_t ldw);
 hipError_t launch_vnm8_gemm(const uint16_t* vcb, const uint8_t* mcb, const uint8_t* cixt, const uint16_t* Wk, int64_t ldw, int64_t T, int64_t N,
-                            int64_t F, uint16_t* out, int64_t ldo, hipStream_t s, const GemmGroup* grp = nullptr, int tile = 0, const Split* split = nullptr);
+                            int64_t F, uint16_t* out, int64_t ldo, hipStream_t s, const GemmGroup* grp = nullptr, int tile = 0, const Split* split = nullptr, bool past = false);
 // vnm.hip: the canonical V:2:8 arrays (vals [T, F/4], meta [T, F/16], colidx [T/64, F/8, 4]) regrouped into those units; with W [R, C] (row stride ld)
 // also its transpose wt [C, R]; counters (or null): kSplitCounters of them are cleared
 hipError_t launch_vnm8_repack(const uint16_t* vals, const uint8_t* meta, const uint8_t* colidx, int64_t T, int64_t F, uint16_t* vcb, uint8_t* mcb,
@@ -581,12 +586,12 @@ bool vnm8_gemm_fp8_ok(int64_t T, int64_t N, int64_t F, int64_t ldw);
 hipError_t launch_vnm8_repack_fp8(const uint8_t* codes, const uint8_t* meta, const uint8_t* colidx, int64_t T, int64_t F, uint8_t* vcb, uint8_t* mcb,
                                   uint8_t* cixt, hipStream_t s);
 hipError_t launch_vnm8_gemm_fp8(const uint8_t* vcb, const uint8_t* mcb, const uint8_t* cixt, const uint8_t* Wq, int64_t ldw, float alpha, int64_t T,
-                                int64_t N, int64_t F, uint16_t* out, int64_t ldo, hipStream_t s, const GemmGroup* grp = nullptr, int tile = 0, const Split* split = nullptr);
+                                int64_t N, int64_t F, uint16_t* out, int64_t ldo, hipStream_t s, const GemmGroup* grp = nullptr, int tile = 0, const Split* split = nullptr, bool past = false);
 // The same on E4M3 codes: a_codes [T, 2 F / M] + the same metadata and column offsets, Wq = codes [F, ldw bytes], out = bf16(alpha * sum);
 // 4 F / M a multiple of 128; b_stride of grp in bytes.
 bool vnm_spmm_gather_fp8_ok(int64_t T, int64_t N, int64_t F, int M);
 hipError_t launch_vnm_spmm_gather_fp8(const uint8_t* a_codes, const uint8_t* a_meta, const uint8_t* colidx, const uint8_t* Wq, int64_t ldw, float alpha,
-                                      int64_t T, int64_t N, int64_t F, int M, uint16_t* out, int64_t ldo, hipStream_t s, const GemmGroup* grp = nullptr);
+                                      int64_t T, int64_t N, int64_t F, int M, uint16_t* out, int64_t ldo, hipStream_t s, const GemmGroup* grp = nullptr, bool past = false);
 hipError_t launch_vnm_to_24(const uint16_t* vals, const uint8_t* meta, const uint8_t* colidx, int64_t T, int64_t F,
                             uint16_t* vals24, uint8_t* meta24, hipStream_t s);
 // vnm.hip: the transposed operand of eqs. (5), (8) from the canonical arrays: kept = 0: at [F / 2, T], mask [T / 64, F / 8] for launch_wgrad_vnm;
@@ -610,7 +615,7 @@ hipError_t launch_gemm_vnm_epilogue(const uint16_t* a_vals, const uint8_t* a_met
                                     int64_t T, int64_t K, uint16_t* out, const VnmEpilogue& ep, hipStream_t s,
                                     const GemmGroup* grp = nullptr, int tile = 0);
 hipError_t launch_spmm_blocked(const uint16_t* a_vals, const uint8_t* a_meta, const uint16_t* B, const float* bias, int64_t Ra, int64_t Rb,
-                               int64_t K, int out_i_contig, uint16_t* out, int64_t ldo, hipStream_t s, const GemmGroup* grp = nullptr);
+                               int64_t K, int out_i_contig, uint16_t* out, int64_t ldo, hipStream_t s, const GemmGroup* grp = nullptr, bool past = false);
 hipError_t launch_gemm_nt(int sparse_a, const uint16_t* a_vals, const uint8_t* a_meta, const uint16_t* B, const float* bias,
                           int64_t Ra, int64_t Rb, int64_t K, int out_i_contig, uint16_t* out, int64_t ldo, hipStream_t s);
 // eqs. (5), (8) of the neuron-level router: out[i * ldo + j] = sum over expert e's rows of at[i, row] * G[j, row], both blocked, dense [Kc, rows] and [N, rows];

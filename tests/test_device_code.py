@@ -73,14 +73,15 @@ def test_sums_of_the_other_splits_are_read_behind_the_count(tmp_path):
 
 
 def test_activations_are_stored_the_ordinary_way(kernels):
-    """The next kernel reads them; results of eqs. (1), (4) by themselves and of the compression have a non-temporal form for operands as large as the last-level cache."""
+    """The next kernel reads them.  Results of eqs. (1), (4) by themselves and of the compression have a non-temporal form for sizes of the last-level cache, those of eqs. (3), (7) for those of the L2s;
+    tiles of few tokens and shared contractions have none."""
     plain = re.compile(r"\tglobal_store_dwordx4 [^\n]*(?<! nt)\n")
     past = re.compile(r"\tglobal_store_dwordx4 [^\n]* nt\n")
-    for source, pattern in (("gemm_vnm8.hip", "Vnm8Unit"), ("gemm_gather.hip", "Gather")):
+    for source, pattern, few in (("gemm_vnm8.hip", "Vnm8Unit", "VTileILi1ELi1E"), ("gemm_gather.hip", "Gather", "GTileILi1E")):
         units = {name: code for name, code in kernels(source).items() if pattern in name}
-        assert units
+        assert len(units) >= 3 and any(few in name for name in units)
         for name, code in units.items():
-            assert plain.search(code) and not past.search(code), name
+            assert len(plain.findall(code)) > 0 and len(past.findall(code)) == (0 if few in name else len(plain.findall(code))), name
     rows = {name: code for name, code in kernels("gemm_v2_row.hip").items() if "GemmV2UnitILb1ELb1ELi0E" in name}
     assert rows and all(len(plain.findall(code)) == len(past.findall(code)) > 0 for code in rows.values()), rows.keys()
     compress = {name: code for name, code in kernels("vnm_general.hip").items() if "compress_m_kernelILi8E" in name}
