@@ -139,3 +139,13 @@ def test_launches_of_the_exact_gpu_tests(launches):
         assert all(t.get(kind) != 64 for kernels in got for t in map(tiles, kernels) for kind in ("activation", "gradient")), (T, D, F, seg)
         if want[0] is None:
             assert all({"gradient": "tall"} in list(map(tiles, kernels)) for kernels in (whole, back, back_sums))
+
+
+def test_launches_of_the_gpu_tests_of_results_past_the_caches(launches):
+    """No 64 tile of eqs. (3), (7), which would sum in another order, on either side."""
+    from tests.test_gpu_results_past import FEW, STEPS, T
+    for fp8, M, D, F in STEPS:
+        assert 2 * T * D >= 16 << 20 > 2 * FEW * D and 2 * (T - FEW) * D < 16 << 20
+        for kernels in launches([step("step", M, n, D, F, fp8) for n in (T, FEW, T - FEW)]):
+            units = " ".join(kernels)
+            assert ("Vnm8Unit" in units) == (M == 8) and "GTile<1, 3, 4>" not in units and all(t.get("activation") != 64 for t in map(tiles, kernels)), (fp8, M, D, F)
